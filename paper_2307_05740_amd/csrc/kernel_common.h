@@ -54,12 +54,52 @@ __device__ __forceinline__ void vstore(float* p, typename Vec<VEC>::type v) {
   *reinterpret_cast<typename Vec<VEC>::type*>(p) = v;
 }
 
+// The same for global memory at any 4-byte boundary: one 16-byte instruction does it there, so rows
+// whose length is no multiple of 4 columns are still moved four columns per lane (lane_columns).
+typedef float stream_v2f __attribute__((ext_vector_type(2), aligned(4)));
+typedef float stream_v4f __attribute__((ext_vector_type(4), aligned(4)));
+template <int VEC> __device__ __forceinline__ typename Vec<VEC>::type gload(const float* p);
+template <> __device__ __forceinline__ float gload<1>(const float* p) { return *p; }
+template <> __device__ __forceinline__ float2 gload<2>(const float* p) {
+  const stream_v2f t = *reinterpret_cast<const stream_v2f*>(p); return make_float2(t.x, t.y);
+}
+template <> __device__ __forceinline__ float4 gload<4>(const float* p) {
+  const stream_v4f t = *reinterpret_cast<const stream_v4f*>(p); return make_float4(t.x, t.y, t.z, t.w);
+}
+template <int VEC> __device__ __forceinline__ void gstore(float* p, typename Vec<VEC>::type v);
+template <> __device__ __forceinline__ void gstore<1>(float* p, float v) { *p = v; }
+template <> __device__ __forceinline__ void gstore<2>(float* p, float2 v) {
+  stream_v2f t; t.x = v.x; t.y = v.y;
+  *reinterpret_cast<stream_v2f*>(p) = t;
+}
+template <> __device__ __forceinline__ void gstore<4>(float* p, float4 v) {
+  stream_v4f t; t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
+  *reinterpret_cast<stream_v4f*>(p) = t;
+}
+
+// First column of lane l's VEC columns in the slice that starts at column c0; a lane whose columns
+// would run past the last one is moved back so that they end there.  It then shares `shared` columns
+// with the lane before it: both hold and store the same values for them.  Lanes that start at or
+// beyond column k have none (ok = false) and read column 0.
+struct LaneColumns {
+  int c;         // first column
+  int shared;    // columns that the lane before holds as well
+  bool ok;
+};
+template <int VEC>
+__device__ __forceinline__ LaneColumns lane_columns(int l, int c0, int k) {
+  LaneColumns r;
+  r.c = c0 + l * VEC;
+  r.shared = 0;
+  r.ok = r.c < k;
+  if (VEC > 1 && r.ok && r.c + VEC > k) { r.shared = r.c + VEC - k; r.c = k - VEC; }
+  return r;
+}
+
 // Store of a result row that this product does not read again: the non-temporal hint keeps the
 // 4 k bytes per output row from displacing rows of X in the L2 (measured on the R-MAT workload:
 // rows kernel 3.97 -> 3.71 ms, reduction 0.38 -> 0.33 ms; the same hint on loads of X rows or of
 // the entry stream made the product slower).
-typedef float stream_v2f __attribute__((ext_vector_type(2)));
-typedef float stream_v4f __attribute__((ext_vector_type(4)));
 template <int VEC>
 __device__ __forceinline__ void vstore_stream(float* p, typename Vec<VEC>::type v);
 template <> __device__ __forceinline__ void vstore_stream<1>(float* p, float v) { __builtin_nontemporal_store(v, p); }
@@ -93,10 +133,10 @@ __device__ __forceinline__ typename Vec<VEC>::type load_row(const char* base, in
                                                             uint32_t row_bytes, uint32_t col_bytes) {
   if (SMALL) {
     const uint32_t off = __umul24((uint32_t)row, row_bytes) + col_bytes;
-    return *reinterpret_cast<const typename Vec<VEC>::type*>(base + off);
+    return gload<VEC>(reinterpret_cast<const float*>(base + off));
   } else {
     const uint64_t off = (uint64_t)(uint32_t)row * row_bytes + col_bytes;
-    return *reinterpret_cast<const typename Vec<VEC>::type*>(base + off);
+    return gload<VEC>(reinterpret_cast<const float*>(base + off));
   }
 }
 
@@ -115,9 +155,16 @@ struct Shape {
   int vec, lpr, slices;
 };
 
-[[maybe_unused]] Shape pick_shape(int k, int kc) {
+// Columns per lane: 4 wherever a row has that many (the last lane of a row may share columns with
+// its neighbour, see lane_columns): a 16-byte load moves four times as much per instruction as the
+// 4-byte load an odd k would otherwise take, and a row needs a quarter of the lanes.  `exact` asks
+// for lanes that share nothing: kernels that lay lanes' columns out side by side in LDS, and
+// launches that add to Y whose last slice would reach back into the one before (two workgroups
+// would then add to the same elements).
+[[maybe_unused]] Shape pick_shape(int k, int kc, bool exact = false) {
   Shape s;
-  s.vec = (k % 4 == 0) ? 4 : (k % 2 == 0) ? 2 : 1;
+  s.vec = k >= 4 ? 4 : (k == 2 ? 2 : 1);
+  if (exact) s.vec = (k % 4 == 0) ? 4 : (k % 2 == 0) ? 2 : 1;
   int width = k;                                   // columns per slice
   if (kc > 0 && kc < width) width = kc;
   if (width > 64 * s.vec) width = 64 * s.vec;
@@ -141,6 +188,13 @@ int dispatch_shape(const Shape& s, F&& f) {
 #undef ARROW_CASES
 #undef ARROW_CASE
   return (int)hipErrorInvalidValue;
+}
+
+// the shape of a launch that writes Y: exact where it adds to Y and its last slice holds fewer than 4 columns
+[[maybe_unused]] Shape pick_output_shape(int k, int kc, bool accumulate) {
+  const Shape s = pick_shape(k, kc);
+  const int last = k - (s.slices - 1) * s.lpr * s.vec;
+  return accumulate && s.slices > 1 && last < s.vec ? pick_shape(k, kc, true) : s;
 }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

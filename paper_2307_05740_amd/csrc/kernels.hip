@@ -79,10 +79,11 @@ __global__ __launch_bounds__(kBlock) void rows_kernel(
   __shared__ int32_t s_dst[kItemsPerGroupBlock];
   const int tid = threadIdx.x;
   const int l = tid % LPR;
-  const int c = l * VEC + blockIdx.y * (LPR * VEC);
-  const bool col_ok = c < k;
+  const LaneColumns lc = lane_columns<VEC>(l, blockIdx.y * (LPR * VEC), k);
+  const int c = lc.c;
+  const bool col_ok = lc.ok;
   const uint32_t row_bytes = 4u * (uint32_t)k;
-  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;   // lanes past the last column read column 0
+  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;
   const int64_t first = (int64_t)blockIdx.x * kItemsPerGroupBlock;
   const int n_it = n_rows - first < kItemsPerGroupBlock ? (int)(n_rows - first) : kItemsPerGroupBlock;
   if (n_it <= 0) return;
@@ -188,10 +189,11 @@ __global__ __launch_bounds__(kBlock) void chunks_kernel(
   const uint32_t mid = chunk_mid[ch];
   const int lane = threadIdx.x % 64;
   const int g = lane / LPR;
-  const int c = (lane % LPR) * VEC + blockIdx.y * (LPR * VEC);
-  const bool col_ok = c < k;
+  const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * (LPR * VEC), k);
+  const int c = lc.c;
+  const bool col_ok = lc.ok;
   const uint32_t row_bytes = 4u * (uint32_t)k;
-  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;   // lanes past the last column read column 0
+  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;
   Entry* mine = strip[wave];
   const Entry* grp = mine + g;
   V acc = vzero<VEC>();
@@ -276,8 +278,9 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
   const WindowTile t = tiles[blockIdx.x];
   const int l = threadIdx.x % LPR;
   const int grp = threadIdx.x / LPR;
-  const int c = l * VEC + blockIdx.y * W;
-  const bool col_ok = c < k;
+  const LaneColumns lc = lane_columns<VEC>(l, blockIdx.y * W, k);   // lane l's columns sit at [l * VEC] of an LDS row
+  const int c = lc.c;
+  const bool col_ok = lc.ok;
   const float* Xc = X + (col_ok ? c : 0);
   // stage: lane group j loads window rows j, j + GPB, ... four at a time
   for (uint32_t i0 = grp; i0 < t.win_count; i0 += 4 * GPB) {
@@ -290,7 +293,7 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      v[u] = (src[u] >= 0 && col_ok) ? vload<VEC>(Xc + (size_t)src[u] * (size_t)k) : vzero<VEC>();
+      v[u] = (src[u] >= 0 && col_ok) ? gload<VEC>(Xc + (size_t)src[u] * (size_t)k) : vzero<VEC>();
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const uint32_t i = i0 + u * GPB;
@@ -308,7 +311,7 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
       for (int u = 0; u < 4; ++u) e[u] = ent[j + u < mid ? j + u : lo];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        x[u] = (j + u < mid) ? vload<VEC>(Xc + (size_t)e[u].xrow * (size_t)k) : vzero<VEC>();
+        x[u] = (j + u < mid) ? gload<VEC>(Xc + (size_t)e[u].xrow * (size_t)k) : vzero<VEC>();
 #pragma unroll
       for (int u = 0; u < 4; ++u) vfma(acc, (j + u < mid) ? e[u].val : 0.f, x[u]);
     }
@@ -342,6 +345,15 @@ __device__ __forceinline__ float vdot(float u, float x) { return u * x; }
 __device__ __forceinline__ float vdot(float2 u, float2 x) { return fmaf(u.y, x.y, u.x * x.x); }
 __device__ __forceinline__ float vdot(float4 u, float4 x) {
   return fmaf(u.w, x.w, fmaf(u.z, x.z, fmaf(u.y, x.y, u.x * x.x)));
+}
+
+// A lane that shares columns with the one before it (lane_columns) leaves them out of its dot products.
+__device__ __forceinline__ void drop_shared(float&, int) {}
+__device__ __forceinline__ void drop_shared(float2& v, int shared) { if (shared) v.x = 0.f; }
+__device__ __forceinline__ void drop_shared(float4& v, int shared) {
+  if (shared > 0) v.x = 0.f;
+  if (shared > 1) v.y = 0.f;
+  if (shared > 2) v.z = 0.f;
 }
 
 template <int NB, int LPR>
@@ -383,6 +395,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_rows_kernel(
   __shared__ Entry strip[GPB * SG];
   const int tid = threadIdx.x;
   const int l = tid % LPR;
+  const LaneColumns lc0 = lane_columns<VEC>(l, 0, k);
+  const bool ragged = k % VEC != 0;
   const uint32_t row_bytes = 4u * (uint32_t)k;
   Entry* grp = strip + (tid / LPR) * SG;
   const int64_t first = (int64_t)blockIdx.x * kItemsPerGroupBlock;
@@ -396,7 +410,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_rows_kernel(
     const uint32_t hi = item_ptr[r + 1];
     const uint32_t win = MODE == 1 ? item_win[r] : 0u;
     const float* Urow = U + (size_t)row * (size_t)k;
-    const V u0 = l * VEC < k ? vload<VEC>(Urow + l * VEC) : vzero<VEC>();
+    V u0 = lc0.ok ? gload<VEC>(Urow + lc0.c) : vzero<VEC>();
+    drop_shared(u0, lc0.shared);
     for (uint32_t b0 = lo; b0 < hi; b0 += SG) {
       const uint32_t nb = hi - b0 < (uint32_t)SG ? hi - b0 : (uint32_t)SG;
 #pragma unroll
@@ -419,15 +434,23 @@ __global__ __launch_bounds__(kBlock) void sddmm_rows_kernel(
 #pragma unroll
           for (int u = 0; u < NB; ++u) { xr[u] = grp[(j + u) % SG].xrow; p[u] = 0.f; }
           for (int sl = 0; sl < slices; ++sl) {
-            const int c = l * VEC + sl * W;
-            const bool col_ok = c < k;
-            const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;
-            const V uu = sl == 0 ? u0 : (col_ok ? vload<VEC>(Urow + c) : vzero<VEC>());
+            const LaneColumns lc = lane_columns<VEC>(l, sl * W, k);
+            const bool col_ok = lc.ok;
+            const uint32_t col_bytes = col_ok ? 4u * (uint32_t)lc.c : 0u;
+            V uu = u0;
+            if (sl > 0) {
+              uu = col_ok ? gload<VEC>(Urow + lc.c) : vzero<VEC>();
+              drop_shared(uu, lc.shared);
+            }
             V x[NB];
 #pragma unroll
             for (int u = 0; u < NB; ++u)
               x[u] = (j + u < j_hi && col_ok) ? load_row<VEC, SMALL>(base, xr[u], row_bytes, col_bytes)
                                               : vzero<VEC>();
+            if (ragged) {
+#pragma unroll
+              for (int u = 0; u < NB; ++u) drop_shared(x[u], lc.shared);
+            }
 #pragma unroll
             for (int u = 0; u < NB; ++u) p[u] += vdot(uu, x[u]);
           }
@@ -467,9 +490,12 @@ __global__ __launch_bounds__(kBlock) void sddmm_chunks_kernel(
   const int lane = threadIdx.x % 64;
   const int g = lane / LPR;
   const int l = lane % LPR;
+  const LaneColumns lc0 = lane_columns<VEC>(l, 0, k);
+  const bool ragged = k % VEC != 0;
   const uint32_t row_bytes = 4u * (uint32_t)k;
   const float* Urow = U + (size_t)row * (size_t)k;
-  const V u0 = l * VEC < k ? vload<VEC>(Urow + l * VEC) : vzero<VEC>();
+  V u0 = lc0.ok ? gload<VEC>(Urow + lc0.c) : vzero<VEC>();
+  drop_shared(u0, lc0.shared);
   Entry* mine = strip[wave];
   for (int seg = 0; seg < 2; ++seg) {
     const char* base = reinterpret_cast<const char*>(seg == 0 ? Vh : Vm);
@@ -491,14 +517,22 @@ __global__ __launch_bounds__(kBlock) void sddmm_chunks_kernel(
           p[u] = 0.f;
         }
         for (int sl = 0; sl < slices; ++sl) {
-          const int c = l * VEC + sl * W;
-          const bool col_ok = c < k;
-          const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;
-          const V uu = sl == 0 ? u0 : (col_ok ? vload<VEC>(Urow + c) : vzero<VEC>());
+          const LaneColumns lc = lane_columns<VEC>(l, sl * W, k);
+          const bool col_ok = lc.ok;
+          const uint32_t col_bytes = col_ok ? 4u * (uint32_t)lc.c : 0u;
+          V uu = u0;
+          if (sl > 0) {
+            uu = col_ok ? gload<VEC>(Urow + lc.c) : vzero<VEC>();
+            drop_shared(uu, lc.shared);
+          }
           V x[NB];
 #pragma unroll
           for (int u = 0; u < NB; ++u)
             x[u] = (ok[u] && col_ok) ? load_row<VEC, SMALL>(base, xr[u], row_bytes, col_bytes) : vzero<VEC>();
+          if (ragged) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) drop_shared(x[u], lc.shared);
+          }
 #pragma unroll
           for (int u = 0; u < NB; ++u) p[u] += vdot(uu, x[u]);
         }
@@ -926,8 +960,9 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(
   if (row >= n_split) return;
   const int lane = threadIdx.x % 64;
   const int g = lane / LPR;
-  const int c = (lane % LPR) * VEC + blockIdx.y * (LPR * VEC);
-  const bool col_ok = c < k;
+  const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * (LPR * VEC), k);
+  const int c = lc.c;
+  const bool col_ok = lc.ok;
   const uint32_t lo = split_ptr[row], hi = split_ptr[row + 1];
   const float* __restrict__ Pc = partials + (col_ok ? c : 0);
   V acc = vzero<VEC>();
@@ -955,9 +990,10 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(const int32_t* __restric
                                                         float* __restrict__ Xp, int k) {
   constexpr int GPB = kBlock / LPR;
   const int64_t p = (int64_t)blockIdx.x * GPB + threadIdx.x / LPR;
-  const int c = (threadIdx.x % LPR) * VEC + blockIdx.y * (LPR * VEC);
-  if (p >= n_i || c >= k) return;
-  vstore<VEC>(Xp + (size_t)p * (size_t)k + c, vload<VEC>(X + (size_t)perm[p] * (size_t)k + c));
+  const LaneColumns lc = lane_columns<VEC>(threadIdx.x % LPR, blockIdx.y * (LPR * VEC), k);
+  const int c = lc.c;
+  if (p >= n_i || !lc.ok) return;
+  gstore<VEC>(Xp + (size_t)p * (size_t)k + c, gload<VEC>(X + (size_t)perm[p] * (size_t)k + c));
 }
 
 }  // namespace
@@ -967,7 +1003,7 @@ int launch_rows(const uint32_t* rows_ptr, const uint32_t* rows_mid, const int32_
                 const float* Xh, float* Y, float* partials, int32_t k, bool accumulate,
                 const LaunchTuning& t, void* stream) {
   if (n_rows <= 0) return 0;
-  const Shape s = pick_shape(k, t.kc);
+  const Shape s = pick_output_shape(k, t.kc, accumulate);
   const bool small = small_matrix(x_rows, k);
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
@@ -992,7 +1028,7 @@ int launch_chunks(const uint32_t* chunk_ptr, const uint32_t* chunk_mid, const in
                   const float* Xh, float* Y, float* partials, int32_t k, bool accumulate,
                   const LaunchTuning& t, void* stream) {
   if (n_chunks <= 0) return 0;
-  const Shape s = pick_shape(k, t.kc);
+  const Shape s = pick_output_shape(k, t.kc, accumulate);
   const bool small = small_matrix(x_rows, k);    // the staged buffer has at most as many rows as X
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
@@ -1016,7 +1052,7 @@ int launch_chunks(const uint32_t* chunk_ptr, const uint32_t* chunk_mid, const in
 int launch_reduce(const uint32_t* split_ptr, const int32_t* split_y, int64_t n_split,
                   const float* partials, float* Y, int32_t k, bool accumulate, void* stream) {
   if (n_split <= 0) return 0;
-  const Shape s = pick_shape(k, 0);
+  const Shape s = pick_output_shape(k, 0, accumulate);
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
     const int64_t blocks = ceil_div(n_split, kBlock / 64);
@@ -1053,7 +1089,7 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, co
   int kc = 256;
   while (kc > 1 && max_span * kc * 4 > lds_budget) kc >>= 1;
   if (max_span * kc * 4 > lds_budget) return (int)hipErrorInvalidValue;
-  const Shape s = pick_shape(k, kc);
+  const Shape s = pick_output_shape(k, kc, accumulate);
   if (max_span * (int64_t)(s.lpr * s.vec) * 4 > lds_budget) return (int)hipErrorInvalidValue;
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
@@ -1140,7 +1176,7 @@ int launch_panel(const uint32_t* panel_ptr, const int32_t* panel_y, const Entry*
                  int64_t n_groups, const float* Xh, int64_t xh_rows, float* part, int32_t k, void* stream) {
   if (n_groups <= 0) return 0;
   const int vec = (k % 4 == 0) ? 4 : (k % 2 == 0) ? 2 : 1;
-  const Shape s = pick_shape(k, 32 * vec);         // at most 32 lanes per row: LDS rows of at most 128 floats
+  const Shape s = pick_shape(k, 32 * vec, true);         // at most 32 lanes per row: LDS rows of at most 128 floats
   const bool small = small_matrix(xh_rows, k);
   return dispatch_narrow(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;
@@ -1161,7 +1197,7 @@ int launch_panel(const uint32_t* panel_ptr, const int32_t* panel_y, const Entry*
 int launch_panel_combine(const int32_t* panel_y, int64_t n_slots, const float* part, float* Y, int32_t k,
                          void* stream) {
   if (n_slots <= 0) return 0;
-  const Shape s = pick_shape(k, 0);
+  const Shape s = pick_shape(k, 0, true);
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;
     const int64_t blocks = ceil_div(n_slots, kBlock / LPR);
@@ -1177,7 +1213,7 @@ int launch_sddmm_panel(const uint32_t* panel_ptr, const int32_t* panel_y, const 
                        const uint32_t* emap, int64_t n_bins, const float* U, const float* Vh,
                        int64_t vh_rows, float* S, int32_t k, void* stream) {
   if (n_bins <= 0) return 0;
-  const Shape s = pick_shape(k, 0);
+  const Shape s = pick_shape(k, 0, true);
   const bool small = small_matrix(vh_rows, k);
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value, NB = BatchOf<LPR>::value;
@@ -1214,7 +1250,7 @@ int launch_corner(const uint32_t* tiles, const uint32_t* items, int64_t n_items,
   if (n_items <= 0) return 0;
   (void)xh_rows;
   // 64-column slices: accumulators and tile copy take 64 KiB of LDS each
-  const Shape s = pick_shape(k, 64);
+  const Shape s = pick_shape(k, 64, true);
   return dispatch_w64(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;
     if (n_items > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
@@ -1228,7 +1264,7 @@ int launch_corner(const uint32_t* tiles, const uint32_t* items, int64_t n_items,
 int launch_corner_combine(const uint32_t* panel_ptr, const int32_t* corner_y, int64_t corner,
                           const float* part, float* Y, int32_t k, void* stream) {
   if (corner <= 0) return 0;
-  const Shape s = pick_shape(k, 0);
+  const Shape s = pick_shape(k, 0, true);
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;
     const int64_t blocks = ceil_div(corner, kBlock / LPR);
@@ -1244,7 +1280,7 @@ int launch_sddmm_corner(const uint32_t* tiles, int64_t n_tiles, const int32_t* c
                         const uint32_t* emap, const float* U, const float* Vh, int64_t vh_rows, float* S,
                         int32_t k, void* stream) {
   if (n_tiles <= 0) return 0;
-  const Shape s = pick_shape(k, 0);
+  const Shape s = pick_shape(k, 0, true);
   const bool small = small_matrix(vh_rows, k);
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value, NB = BatchOf<LPR>::value;

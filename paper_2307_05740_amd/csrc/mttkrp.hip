@@ -60,10 +60,11 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(
   if (over_limit) { n_seg = 0; n_ent = 0; }
   const int lane = threadIdx.x % 64;
   const int g = lane / LPR;
-  const int c = (lane % LPR) * VEC + blockIdx.y * (LPR * VEC);
-  const bool col_ok = c < R;
+  const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * (LPR * VEC), R);
+  const int c = lc.c;
+  const bool col_ok = lc.ok;
   const uint32_t row_bytes = 4u * (uint32_t)R;
-  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;   // lanes past the last column read column 0
+  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;
   const char* Bb = reinterpret_cast<const char*>(B);
   const char* Cb = reinterpret_cast<const char*>(C);
   // stage the item: n_seg <= kCsfItemSegs and n_ent <= kCsfItemNnz by construction of the image
@@ -95,8 +96,8 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(
   if (over_limit) vfma(acc, __builtin_nanf(""), acc);
   if (g == 0 && col_ok) {
     const int32_t dst = item_dst[it];
-    if (dst >= 0) vstore<VEC>(A + (size_t)dst * (size_t)R + c, acc);
-    else vstore<VEC>(partials + (size_t)(-1 - dst) * (size_t)R + c, acc);
+    if (dst >= 0) gstore<VEC>(A + (size_t)dst * (size_t)R + c, acc);
+    else gstore<VEC>(partials + (size_t)(-1 - dst) * (size_t)R + c, acc);
   }
 }
 

@@ -1,0 +1,47 @@
+"""GPU parity at the edges of the launch shapes: column counts that are no multiple of the columns a
+lane owns, slices that end with a few columns, work lists at the edges of their blocks."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2307_05740_amd import binding, synth
+from tests.test_gpu_parity import TOL, assert_within, csr_of, torch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k,kc", [(5, 0), (9, 0), (63, 16), (65, 64), (66, 64), (67, 64), (127, 32), (257, 0), (259, 0)])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_last_lane_shares_columns(torch, k, kc, fuse):
+    """The last lane of a row reaches back into its neighbour's columns; with separate levels the
+    launches add to Y, where two slices must not both own a column."""
+    w = synth.make_config(2, 8)
+    X = synth.normal_matrix(w.n, k, seed=11)
+    opt = binding.arrow_options_default(fuse_levels=fuse, kc=kc)
+    op = binding.ArrowSpMM(*csr_of(w), w.b, options=opt)
+    Y = torch.full((w.n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    Yref, B = oracle.spmm(*csr_of(w), X)
+    assert_within(Y.cpu().numpy(), Yref, B)
+    op.close()
+
+
+@pytest.mark.parametrize("k", [5, 6, 7, 33, 261])
+def test_shared_columns_count_once_in_dot_products(torch, k):
+    """Infinite factors in the last columns stay infinite (a shared column is dropped, not multiplied by 0)."""
+    w = synth.make_config(0, 2)
+    U = synth.normal_matrix(w.n, k, seed=12)
+    V = synth.normal_matrix(w.n, k, seed=13)
+    V[::7, k - 1] = np.inf
+    V[3::11, k - 3] = -np.inf
+    op = binding.ArrowSpMM(*csr_of(w), w.b)
+    S = op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda()).cpu().numpy()
+    op.close()
+    rows = np.repeat(np.arange(w.n), np.diff(w.rowptr))
+    with np.errstate(invalid="ignore"):
+        ref = w.vals.astype(np.float64) * np.einsum("ij,ij->i", U[rows].astype(np.float64), V[w.colidx].astype(np.float64))
+    assert np.array_equal(np.isnan(S), np.isnan(ref)) and np.array_equal(np.isinf(S), np.isinf(ref))
+    assert np.array_equal(S[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32))
+    fin = np.isfinite(ref)
+    bound = np.abs(w.vals[fin]) * np.einsum("ij,ij->i", np.abs(U[rows[fin]]), np.abs(V[w.colidx[fin]]))
+    assert np.all(np.abs(S[fin] - ref[fin]) <= TOL * bound)
