@@ -164,7 +164,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
     const arrow::Entry* ent = at<arrow::Entry>(h, im.off_entries);
     const float* Xh = X;
     arrow::LaunchTuning tune = h->tuning;
-    if (im.staged) {
+    if (im.stage_used) {
       // the first-block-column window X_0 = (P_i X)[0:b], made contiguous once per product
       Scoped sc(h, kStage, (int)li, stream, prof);
       int rc = arrow::launch_gather(at<int32_t>(h, im.off_stage_perm), im.n_stage, X, stage, k, stream);
@@ -183,26 +183,37 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
         tune.kc = 64;
       }
     }
-    if (im.n_chunks > 0) {
-      Scoped sc(h, kChunks, (int)li, stream, prof);
-      int rc = arrow::launch_chunks(at<uint32_t>(h, im.off_chunk_ptr), at<uint32_t>(h, im.off_chunk_mid),
-                                    at<int32_t>(h, im.off_chunk_dst), ent, im.n_chunks, X, h->n, Xh, Y,
-                                    partials, k, acc, tune, stream);
-      if (rc) return check_hip(rc, "chunks kernel launch");
-    }
-    if (im.n_rows > 0) {
-      Scoped sc(h, kRows, (int)li, stream, prof);
-      // class pieces (die queues) follow the chunk kernel's column slicing; the short rows behind
-      // them run in one pass over whole rows
-      const int64_t np = im.piece_slots;
-      int rc = arrow::launch_rows(at<uint32_t>(h, im.off_rows_ptr), at<uint32_t>(h, im.off_rows_mid),
-                                  at<int32_t>(h, im.off_rows_dst), ent, np, X, h->n, Xh, Y, partials, k,
-                                  acc, tune, stream);
-      if (rc) return check_hip(rc, "rows kernel launch (pieces)");
-      rc = arrow::launch_rows(at<uint32_t>(h, im.off_rows_ptr) + np, at<uint32_t>(h, im.off_rows_mid) + np,
-                              at<int32_t>(h, im.off_rows_dst) + np, ent, im.n_rows - np, X, h->n, Xh, Y,
-                              partials, k, acc, h->tuning, stream);
-      if (rc) return check_hip(rc, "rows kernel launch");
+    {
+      arrow::ProductArgs a{};
+      a.chunk_ptr = at<uint32_t>(h, im.off_chunk_ptr); a.chunk_mid = at<uint32_t>(h, im.off_chunk_mid);
+      a.chunk_dst = at<int32_t>(h, im.off_chunk_dst); a.n_chunks = im.n_chunks;
+      a.rows_ptr = at<uint32_t>(h, im.off_rows_ptr); a.rows_mid = at<uint32_t>(h, im.off_rows_mid);
+      a.rows_dst = at<int32_t>(h, im.off_rows_dst);
+      a.ent = ent; a.X = X; a.Xh = Xh; a.Y = Y; a.partials = partials;
+      a.k = k; a.accumulate = acc ? 1 : 0;
+      auto launch = [&](int parts, int32_t kc) -> int {
+        return check_hip(arrow::launch_product(a, parts, im.piece_slots, im.n_rows, im.empty_slots, im.classes > 0,
+                                               h->n, kc, stream), "product kernel launch");
+      };
+      // the wave list and the pieces follow the chunk kernel's column slicing, the short rows run in
+      // one pass over whole rows; where that is the same shape, one launch takes all of it.  A
+      // profiled product keeps the lists apart so that each has a time of its own.
+      using namespace arrow;
+      int rc = ARROW_OK;
+      if (h->profiling && prof) {
+        if (im.n_chunks > 0) { Scoped sc(h, kChunks, (int)li, stream); rc = launch(kPartChunks, tune.kc); }
+        if (!rc && im.n_rows > 0) {
+          Scoped sc(h, kRows, (int)li, stream);
+          rc = launch(kPartPieces, tune.kc);
+          if (!rc) rc = launch(kPartShort, h->tuning.kc);
+        }
+      } else if (same_shape(k, tune.kc, h->tuning.kc, acc)) {
+        rc = launch(kPartAll, tune.kc);
+      } else {
+        rc = launch(kPartChunks | kPartPieces, tune.kc);
+        if (!rc) rc = launch(kPartShort, h->tuning.kc);
+      }
+      if (rc) return rc;
     }
     if (im.n_wtiles > 0) {
       Scoped sc(h, kWindow, (int)li, stream, prof);
@@ -252,7 +263,7 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
     const uint32_t* emap = h->sddmm_image_order ? nullptr : h->dev_map + im.map_offset;
     float* S = h->sddmm_image_order ? S_out + im.map_offset : S_out;
     const float* Vh = V;
-    if (im.staged) {
+    if (im.stage_used) {
       Scoped sc(h, kStage, (int)li, stream);
       int rc = arrow::launch_gather(at<int32_t>(h, im.off_stage_perm), im.n_stage, V, stage, k, stream);
       if (rc) return check_hip(rc, "head staging launch");

@@ -64,7 +64,8 @@ struct Entry {
 
 constexpr int kDies = 8;             // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
 constexpr int kChunksPerGroup = 4;   // wave-list items (one per wavefront) per workgroup of the chunk kernel
-constexpr int kItemsPerGroupBlock = 64;  // group-list items per workgroup of the rows kernel, whatever its lane-group width
+constexpr int kItemsPerGroupBlock = 64;  // most group-list items per workgroup, and exactly that many of a die queue
+constexpr int kDieRun = 256;         // consecutive wave-list workgroups that one die takes where the list has no die queues
 // head panels: kPanelRows head rows form a group; the group's head-block entries are dealt by column
 // class (staged head row mod kDies) to kDies workgroups, one per accelerator die, each keeping the
 // group's accumulators in LDS and streaming its entries in kPanelBins lane-group streams
@@ -89,6 +90,7 @@ struct LevelImage {
   size_t off_perm = 0;
   // staged head: rows of X gathered into a contiguous buffer before the level runs
   bool staged = false;
+  bool stage_used = false;      // an entry reads the buffer (else it need not be filled)
   int64_t n_stage = 0;          // rows of the staging buffer (min(b, n_i) or 0)
   int64_t stage_class_rows = 0; // rows of the first column class in the buffer
   size_t off_stage_perm = 0;    // int32 n_stage : buffer row -> X row
@@ -96,6 +98,7 @@ struct LevelImage {
   // group list: items handled one per lane group (class pieces in die queues, then the short rows)
   int64_t n_rows = 0, n_real_rows = 0, rows_partials = 0, nnz_rows = 0;
   int64_t piece_slots = 0;   // slots [0, piece_slots) hold the class pieces (die queues), the rest the short rows
+  int64_t empty_slots = 0;   // the last empty_slots slots are rows of Y without entries
   size_t off_rows_ptr = 0;   // uint32 n_rows + 1 (offsets into the level's entry array)
   size_t off_rows_mid = 0;   // uint32 n_rows : entries before it read the staged head buffer, the rest read X
   size_t off_rows_dst = 0;   // int32  n_rows : >= 0 -> Y row, < 0 -> partial slot (-1 - slot), INT32_MIN -> padding
@@ -196,15 +199,30 @@ struct LaunchTuning {
   int64_t l2_resident_bytes = 2 << 20;  // share of a die's 4 MiB L2 a resident slice of X_0 may take
 };
 
-// x_rows = rows of X (it decides whether 32-bit offsets are enough).
-int launch_rows(const uint32_t* rows_ptr, const uint32_t* rows_mid, const int32_t* rows_dst,
-                const Entry* entries, int64_t n_rows, const float* X, int64_t x_rows,
-                const float* Xh, float* Y, float* partials, int32_t k, bool accumulate,
-                const LaunchTuning& t, void* stream);
-int launch_chunks(const uint32_t* chunk_ptr, const uint32_t* chunk_mid, const int32_t* chunk_dst,
-                  const Entry* entries, int64_t n_chunks, const float* X, int64_t x_rows,
-                  const float* Xh, float* Y, float* partials, int32_t k, bool accumulate,
-                  const LaunchTuning& t, void* stream);
+// The work lists of one level for one launch (device pointers; launch_product fills in the grid).
+struct ProductArgs {
+  const uint32_t* chunk_ptr; const uint32_t* chunk_mid; const int32_t* chunk_dst;   // wave list
+  const uint32_t* rows_ptr; const uint32_t* rows_mid; const int32_t* rows_dst;      // group list
+  const Entry* ent;
+  const float* X; const float* Xh;      // dense operand; staged head (X where nothing is staged)
+  float* Y; float* partials;
+  int64_t n_chunks;
+  int32_t k, accumulate;                // accumulate: add to the rows of Y instead of storing them
+  // parts 0 .. 3: wave list, pieces, short rows, rows without entries
+  int64_t begin[4], count[4];           // slots of the part
+  uint32_t blocks[4];                   // workgroups per column slice
+  int32_t items[4];                     // slots per workgroup
+  uint32_t slices;
+  int32_t runs;                         // deal the wave list to the dies in runs of kDieRun workgroups
+};
+enum { kPartChunks = 1, kPartPieces = 2, kPartShort = 4, kPartAll = 7 };
+// Launches the given parts.  n_pieces, n_rows, n_empty: pieces, all items and trailing empty rows of
+// the group list; x_rows = rows of X (it decides whether 32-bit offsets are enough); kc = columns per
+// pass (0: the whole row).
+int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, int64_t n_empty, bool die_queues,
+                   int64_t x_rows, int32_t kc, void* stream);
+// whether launches with these two kc have the same shape, so that their parts can share one
+bool same_shape(int32_t k, int32_t kc_a, int32_t kc_b, bool accumulate);
 int launch_reduce(const uint32_t* split_ptr, const int32_t* split_y, int64_t n_split,
                   const float* partials, float* Y, int32_t k, bool accumulate, void* stream);
 int launch_gather(const int32_t* perm, int64_t n_i, const float* X, float* Xp, int32_t k,

@@ -34,10 +34,8 @@ hipError_t hipEventDestroy(hipEvent_t) { reached("hipEventDestroy"); }
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { reached("hipMemcpyAsync"); }
 }
 namespace arrow {
-int launch_rows(const uint32_t*, const uint32_t*, const int32_t*, const Entry*, int64_t, const float*, int64_t,
-                const float*, float*, float*, int32_t, bool, const LaunchTuning&, void*) { reached("launch_rows"); }
-int launch_chunks(const uint32_t*, const uint32_t*, const int32_t*, const Entry*, int64_t, const float*, int64_t,
-                  const float*, float*, float*, int32_t, bool, const LaunchTuning&, void*) { reached("launch_chunks"); }
+int launch_product(ProductArgs, int, int64_t, int64_t, int64_t, bool, int64_t, int32_t, void*) { reached("launch_product"); }
+bool same_shape(int32_t, int32_t, int32_t, bool) { reached("same_shape"); }
 int launch_reduce(const uint32_t*, const int32_t*, int64_t, const float*, float*, int32_t, bool, void*) { reached("launch_reduce"); }
 int launch_gather(const int32_t*, int64_t, const float*, float*, int32_t, void*) { reached("launch_gather"); }
 int launch_panel(const uint32_t*, const int32_t*, const Entry*, int64_t, const float*, int64_t, float*, int32_t, void*) { reached("launch_panel"); }

@@ -13,11 +13,11 @@
 //
 // A lane owns VEC consecutive columns; LPR lanes ("a lane group") cover one
 // slice of LPR*VEC columns; a wavefront holds G = 64 / LPR lane groups.
-//   rows kernel   - one lane group per row (short rows: first-block-column and
-//                   diagonal-block entries of the body rows, short head rows)
-//   chunks kernel - one wavefront per chunk of a long row (the head rows); the
-//                   G lane groups take entries round-robin and are combined
-//                   with wavefront shuffles
+//   product kernel - the work lists of a level in one launch: a wavefront per chunk of a
+//                   long row (the head rows), its G lane groups taking entries round-robin
+//                   and combined with wavefront shuffles; a lane group per run of short rows
+//                   (first-block-column and diagonal-block entries of the body rows, short
+//                   head rows, pieces of long rows)
 //   reduce kernel - sums the partial vectors of rows that were split into
 //                   several chunks, in a fixed order, and scatters to Y
 //   window kernel - diagonal-block tiles with their window of P_i X staged in LDS
@@ -27,9 +27,9 @@
 //   corner kernels - the dense top-left corner of the head block in tiles of 256 x 256: the
 //                   tile's staged head rows and the row panel's accumulators both live in LDS
 //   sddmm kernels - the sampled dense-dense product S = A .* (U V^T) over the same lists
-// Both product kernels fetch their entries with coalesced loads into LDS (the
-// rows kernel all entries of a workgroup's items at once, the chunk kernel 64
-// at a time into a wavefront-private strip, the next 64 already on their way)
+// The product kernel fetches its entries with coalesced loads into LDS (short
+// rows: all entries of a workgroup's items at once; chunks: 64 to 256 at a time
+// into a wavefront-private strip, the next ones already on their way)
 // and read them back per lane group, so that U row loads are in flight before
 // the first FMA and a lane group only ever waits for the rows it gathers; the
 // SIMDs are 16 lanes wide (4 cycles per wavefront instruction), so the inner
@@ -40,6 +40,7 @@
 #include <hip/hip_runtime.h>
 
 #include <climits>
+#include <cstdlib>
 #include <cstdint>
 #include <type_traits>
 
@@ -50,166 +51,130 @@ namespace arrow {
 namespace {
 
 // ---------------------------------------------------------------------------
-// rows kernel: lane group per item of the group list.  A workgroup owns kItemsPerGroupBlock
-// consecutive list slots whatever its lane-group width (the die queues of the list rely on it);
-// its lane groups take them round-robin.  Entries [lo, mid) of an item read rows of the staged
-// head buffer Xh, entries [mid, hi) read rows of X.
+// product kernel: one launch runs the wave list, the pieces and the short rows of a level; a
+// workgroup's place in the grid says which of them it works on.  The parts write different rows of
+// Y and partial slots, so they need no order among themselves, and one grid has one ramp and one
+// tail instead of three (a launch on its own costs 2 - 3 us on the stream, which is most of the
+// time of a product over a few thousand rows).
 // ---------------------------------------------------------------------------
-// The workgroup first copies the descriptors of its items and, when they fit the staging buffer
-// (they always do for the short rows), all their entries -- one contiguous range -- into LDS with
-// coalesced loads; after that the only memory latency a lane group waits for is that of the rows
-// it gathers.  A workgroup whose entries do not fit streams them per item through a strip.
-constexpr int kRowsStage = 1024;   // entries a workgroup stages at once (8 KiB)
+constexpr int kRowsStage = 1024;   // entries of the group list a workgroup stages at once (8 KiB)
 
-template <int VEC, int LPR, int U, bool SMALL>
-__global__ __launch_bounds__(kBlock) void rows_kernel(
-    const uint32_t* __restrict__ rows_ptr, const uint32_t* __restrict__ rows_mid,
-    const int32_t* __restrict__ rows_dst, const Entry* __restrict__ ent, int64_t n_rows,
-    const float* __restrict__ X, const float* __restrict__ Xh, float* __restrict__ Y,
-    float* __restrict__ partials, int k, int accumulate) {
-  using V = typename Vec<VEC>::type;
-  constexpr int GPB = kBlock / LPR;             // lane groups per workgroup
-  // entries a lane group parks in LDS per batch: four loads per lane, between 8 and 64 entries
-  constexpr int SG = 4 * LPR < 8 ? 8 : (4 * LPR > 64 ? 64 : 4 * LPR);
-  constexpr int UU = U < SG ? U : SG;
-  constexpr int NST = GPB * SG > kRowsStage ? GPB * SG : kRowsStage;   // the buffer doubles as the per-group strips
-  __shared__ Entry stage[NST];
-  __shared__ uint32_t s_ptr[kItemsPerGroupBlock + 1];
-  __shared__ uint32_t s_mid[kItemsPerGroupBlock];
-  __shared__ int32_t s_dst[kItemsPerGroupBlock];
-  const int tid = threadIdx.x;
-  const int l = tid % LPR;
-  const LaneColumns lc = lane_columns<VEC>(l, blockIdx.y * (LPR * VEC), k);
-  const int c = lc.c;
-  const bool col_ok = lc.ok;
-  const uint32_t row_bytes = 4u * (uint32_t)k;
-  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;
-  const int64_t first = (int64_t)blockIdx.x * kItemsPerGroupBlock;
-  const int n_it = n_rows - first < kItemsPerGroupBlock ? (int)(n_rows - first) : kItemsPerGroupBlock;
-  if (n_it <= 0) return;
-  if (tid <= n_it) s_ptr[tid] = rows_ptr[first + tid];
-  if (tid < n_it) { s_mid[tid] = rows_mid[first + tid]; s_dst[tid] = rows_dst[first + tid]; }
-  __syncthreads();
-  const uint32_t e0 = s_ptr[0];
-  const uint32_t total = s_ptr[n_it] - e0;
-  const bool staged = total <= (uint32_t)NST;
-  if (staged) {
-    for (uint32_t t = tid; t < total; t += kBlock) stage[t] = ent[e0 + t];
-    __syncthreads();
-  }
-  Entry* grp = stage + (tid / LPR) * SG;        // the group's SG slots when the entries are streamed
-  for (int it = tid / LPR; it < n_it; it += GPB) {
-    const int32_t dst = s_dst[it];
-    if (dst == INT32_MIN) continue;             // padding slot of the die queues
-    const uint32_t lo = s_ptr[it];
-    const uint32_t mid = s_mid[it];
-    const uint32_t hi = s_ptr[it + 1];
-    V acc = vzero<VEC>();
-    if (staged) {
-      const Entry* se = stage + (lo - e0);
-      const uint32_t n = hi - lo, ns = mid > lo ? mid - lo : 0u;
-      // entries [0, ns) read the staged head buffer, [ns, n) read X
-      for (int seg = 0; seg < 2; ++seg) {
-        const char* base = reinterpret_cast<const char*>(seg == 0 ? Xh : X);
-        const uint32_t j_hi = seg == 0 ? ns : n;
-        for (uint32_t j = seg == 0 ? 0u : ns; j < j_hi; j += UU) {
-          Entry e[UU];
-          V x[UU];
-#pragma unroll
-          for (int u = 0; u < UU; ++u) e[u] = se[j + u < j_hi ? j + u : j];
-#pragma unroll
-          for (int u = 0; u < UU; ++u)
-            x[u] = (j + u < j_hi) ? load_row<VEC, SMALL>(base, e[u].xrow, row_bytes, col_bytes) : vzero<VEC>();
-#pragma unroll
-          for (int u = 0; u < UU; ++u) vfma(acc, (j + u < j_hi) ? e[u].val : 0.f, x[u]);
-        }
-      }
-    } else {
-      for (uint32_t b0 = lo; b0 < hi; b0 += SG) {
-        const uint32_t nb = hi - b0 < (uint32_t)SG ? hi - b0 : (uint32_t)SG;
-#pragma unroll
-        for (int t = 0; t < SG / LPR; ++t) {
-          const uint32_t idx = (uint32_t)(l + t * LPR);
-          if (idx < nb) grp[idx] = ent[b0 + idx];
-        }
-        strip_sync();
-        // entries [0, ns) of the batch read the staged head buffer, [ns, nb) read X
-        const uint32_t ns = mid > b0 ? (mid - b0 < nb ? mid - b0 : nb) : 0u;
-        for (int seg = 0; seg < 2; ++seg) {
-          const char* base = reinterpret_cast<const char*>(seg == 0 ? Xh : X);
-          const uint32_t j_hi = seg == 0 ? ns : nb;
-          for (uint32_t j = seg == 0 ? 0u : ns; j < j_hi; j += UU) {
-            Entry e[UU];
-            V x[UU];
-#pragma unroll
-            for (int u = 0; u < UU; ++u) e[u] = grp[(j + u) % SG];
-#pragma unroll
-            for (int u = 0; u < UU; ++u)
-              x[u] = (j + u < j_hi) ? load_row<VEC, SMALL>(base, e[u].xrow, row_bytes, col_bytes) : vzero<VEC>();
-#pragma unroll
-            for (int u = 0; u < UU; ++u) vfma(acc, (j + u < j_hi) ? e[u].val : 0.f, x[u]);
-          }
-        }
-        strip_sync();
-      }
-    }
-    if (col_ok) {
-      if (dst >= 0) {
-        float* y = Y + (size_t)dst * (size_t)k + c;
-        if (accumulate) vadd(acc, vload_stream<VEC>(y));
-        vstore_stream<VEC>(y, acc);
-      } else {
-        vstore_stream<VEC>(partials + (size_t)(-1 - dst) * (size_t)k + c, acc);
-      }
-    }
-  }
+template <int LPR> constexpr int strip_entries() {     // entries of the wave list a wavefront parks per batch
+  constexpr int full = 64 / LPR * 8;                   // eight rows in flight for each of its lane groups
+  return full < 64 ? 64 : (full > 128 ? 128 : full);
 }
 
-// ---------------------------------------------------------------------------
-// chunks kernel: wavefront per chunk.  Entries [lo, mid) of a chunk read rows of the staged
-// head buffer Xh, entries [mid, hi) read rows of X (the chunk's entries are ordered by
-// column position, head columns first), so the base pointer is uniform inside a batch.
-// ---------------------------------------------------------------------------
-template <int VEC, int LPR, int U, bool SMALL>
-__global__ __launch_bounds__(kBlock) void chunks_kernel(
-    const uint32_t* __restrict__ chunk_ptr, const uint32_t* __restrict__ chunk_mid,
-    const int32_t* __restrict__ chunk_dst, const Entry* __restrict__ ent, int64_t n_chunks,
-    const float* __restrict__ X, const float* __restrict__ Xh, float* __restrict__ Y,
-    float* __restrict__ partials, int k, int accumulate) {
+struct alignas(16) RowsShared {
+  Entry stage[kRowsStage];
+  uint32_t ptr[kItemsPerGroupBlock + 1];
+  uint32_t mid[kItemsPerGroupBlock];
+  int32_t dst[kItemsPerGroupBlock];
+};
+
+// The items [first, first + n_it) of the group list, one lane group per item, taken round-robin.
+// Entries [lo, mid) of an item read rows of the staged head buffer Xh, entries [mid, hi) rows of X.
+// The workgroup first copies the descriptors of its items and, when they fit the staging buffer, all
+// their entries -- one contiguous range -- into LDS with coalesced loads; after that the only memory
+// latency a lane group waits for is that of the rows it gathers.  Items that do not fit are read
+// from memory entry by entry.
+template <int VEC, int LPR, bool SMALL>
+__device__ __forceinline__ void rows_part(RowsShared& sh, const ProductArgs& a, int64_t first, int n_it,
+                                          const LaneColumns lc) {
+  using V = typename Vec<VEC>::type;
+  constexpr int GPB = kBlock / LPR;
+  constexpr uint32_t U = 8;
+  const int tid = threadIdx.x;
+  const uint32_t row_bytes = 4u * (uint32_t)a.k;
+  const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
+  if (tid <= n_it) sh.ptr[tid] = a.rows_ptr[first + tid];
+  if (tid < n_it) { sh.mid[tid] = a.rows_mid[first + tid]; sh.dst[tid] = a.rows_dst[first + tid]; }
+  __syncthreads();
+  const uint32_t e0 = sh.ptr[0];
+  const uint32_t total = sh.ptr[n_it] - e0;
+  const bool staged = total <= (uint32_t)kRowsStage;
+  if (staged) {
+    // all loads before the first wait (one at a time they were up to four memory latencies in a row)
+    constexpr uint32_t Q = kRowsStage / kBlock;
+    Entry e[Q];
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) if (tid + q * kBlock < total) e[q] = a.ent[e0 + tid + q * kBlock];
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) if (tid + q * kBlock < total) sh.stage[tid + q * kBlock] = e[q];
+    __syncthreads();
+  }
+  auto run = [&](auto entry) {
+    for (int it = tid / LPR; it < n_it; it += GPB) {
+      const int32_t dst = sh.dst[it];
+      if (dst == INT32_MIN) continue;             // padding slot of the die queues
+      const uint32_t lo = sh.ptr[it], mid = sh.mid[it], hi = sh.ptr[it + 1];
+      V acc = vzero<VEC>();
+      for (int seg = 0; seg < 2; ++seg) {
+        const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Xh : a.X);
+        const uint32_t j_hi = seg == 0 ? mid : hi;
+        for (uint32_t j = seg == 0 ? lo : mid; j < j_hi; j += U) {
+          Entry e[U];
+          V x[U];
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) e[u] = entry(j + u < j_hi ? j + u : j);
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u)
+            x[u] = (j + u < j_hi) ? load_row<VEC, SMALL>(base, e[u].xrow, row_bytes, col_bytes) : vzero<VEC>();
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) vfma(acc, (j + u < j_hi) ? e[u].val : 0.f, x[u]);
+        }
+      }
+      if (lc.ok) {
+        float* y = dst >= 0 ? a.Y + (size_t)dst * (size_t)a.k + lc.c
+                            : a.partials + (size_t)(-1 - dst) * (size_t)a.k + lc.c;
+        if (a.accumulate && dst >= 0) vadd(acc, vload_stream<VEC>(y));
+        vstore_stream<VEC>(y, acc);
+      }
+    }
+  };
+  if (staged) run([&](uint32_t t) { return sh.stage[t - e0]; });
+  else run([&](uint32_t t) { return a.ent[t]; });
+}
+
+// One chunk of the wave list per wavefront.  Entries [lo, mid) of a chunk read rows of the staged
+// head buffer Xh, entries [mid, hi) read rows of X (the chunk's entries are ordered by column
+// position, head columns first), so the base pointer is uniform inside a batch.  The G lane groups
+// take the entries round-robin and are combined with a butterfly over the lane groups.
+// (Several chunks per wavefront, the next one's descriptor and entries fetched ahead, measured 3 %
+// slower for two and 10 % for four: the chunks in flight then reach over more column windows.)
+template <int VEC, int LPR, bool SMALL>
+__device__ __forceinline__ void chunk_part(Entry* mine, const ProductArgs& a, int64_t ch, const LaneColumns lc) {
   using V = typename Vec<VEC>::type;
   constexpr int G = 64 / LPR;
-  constexpr int WPB = kBlock / 64;
-  __shared__ Entry strip[WPB][64];
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-  const int64_t ch = (int64_t)blockIdx.x * WPB + wave;
-  if (ch >= n_chunks) return;          // whole wavefront leaves together
-  const uint32_t lo = chunk_ptr[ch];
-  const uint32_t hi = chunk_ptr[ch + 1];
+  constexpr uint32_t U = 8;
+  constexpr uint32_t STRIP = strip_entries<LPR>();
+  constexpr int NA = STRIP / 64;
+  const uint32_t lo = a.chunk_ptr[ch];
+  const uint32_t hi = a.chunk_ptr[ch + 1];
+  const uint32_t mid = a.chunk_mid[ch];
+  const int32_t dst = a.chunk_dst[ch];
   if (lo == hi) return;                // padding slot of the die queues
-  const uint32_t mid = chunk_mid[ch];
-  const int lane = threadIdx.x % 64;
-  const int g = lane / LPR;
-  const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * (LPR * VEC), k);
-  const int c = lc.c;
-  const bool col_ok = lc.ok;
-  const uint32_t row_bytes = 4u * (uint32_t)k;
-  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;
-  Entry* mine = strip[wave];
+  const uint32_t lane = threadIdx.x % 64;
+  const uint32_t g = lane / LPR;
+  const uint32_t row_bytes = 4u * (uint32_t)a.k;
+  const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
   const Entry* grp = mine + g;
   V acc = vzero<VEC>();
-  // the next 64 entries of the chunk are fetched while the current batch is being worked on (the
-  // two segments are consecutive in the entry array, so the fetch runs across their boundary)
-  Entry ahead = ent[lo + lane < hi ? lo + lane : lo];
+  // the next entries of the chunk are fetched while the current batch is being worked on (the two
+  // segments are consecutive in the entry array, so the fetch runs across their boundary)
+  Entry ahead[NA];
+#pragma unroll
+  for (int q = 0; q < NA; ++q) ahead[q] = a.ent[lo + lane + q * 64 < hi ? lo + lane + q * 64 : lo];
   for (int seg = 0; seg < 2; ++seg) {
-    const char* base = reinterpret_cast<const char*>(seg == 0 ? Xh : X);
+    const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Xh : a.X);
     const uint32_t s_lo = seg == 0 ? lo : mid;
     const uint32_t s_hi = seg == 0 ? mid : hi;
-    for (uint32_t b0 = s_lo; b0 < s_hi; b0 += 64) {
-      const uint32_t nb = s_hi - b0 < 64u ? s_hi - b0 : 64u;
-      mine[lane] = ahead;              // entries b0 .. b0 + 63 (those past the chunk's end are not used)
-      {
-        const uint32_t nx = b0 + nb + lane;     // first entry of the next batch, of this or the next segment
-        ahead = ent[nx < hi ? nx : lo];
+    for (uint32_t b0 = s_lo; b0 < s_hi; b0 += STRIP) {
+      const uint32_t nb = s_hi - b0 < STRIP ? s_hi - b0 : STRIP;
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {   // entries b0 .. b0 + STRIP - 1 (those past the chunk's end are not used)
+        mine[lane + q * 64] = ahead[q];
+        const uint32_t nx = b0 + nb + lane + q * 64;     // next batch, of this or the next segment
+        ahead[q] = a.ent[nx < hi ? nx : lo];
       }
       strip_sync();
       uint32_t s = 0;                  // step: lane group g handles entry s * G + g
@@ -217,26 +182,26 @@ __global__ __launch_bounds__(kBlock) void chunks_kernel(
         Entry e[U];
         V x[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) e[u] = grp[(s + u) * G];
+        for (uint32_t u = 0; u < U; ++u) e[u] = grp[(s + u) * G];
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = load_row<VEC, SMALL>(base, e[u].xrow, row_bytes, col_bytes);
+        for (uint32_t u = 0; u < U; ++u) x[u] = load_row<VEC, SMALL>(base, e[u].xrow, row_bytes, col_bytes);
 #pragma unroll
-        for (int u = 0; u < U; ++u) vfma(acc, e[u].val, x[u]);
+        for (uint32_t u = 0; u < U; ++u) vfma(acc, e[u].val, x[u]);
       }
       if (s * G < nb) {                // last, partly filled round of this batch
         Entry e[U];
         V x[U];
         bool ok[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (uint32_t u = 0; u < U; ++u) {
           ok[u] = (s + u) * G + g < nb;
-          e[u] = mine[((s + u) * G + g) % 64];
+          e[u] = mine[((s + u) * G + g) % STRIP];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (uint32_t u = 0; u < U; ++u)
           x[u] = ok[u] ? load_row<VEC, SMALL>(base, e[u].xrow, row_bytes, col_bytes) : vzero<VEC>();
 #pragma unroll
-        for (int u = 0; u < U; ++u) vfma(acc, ok[u] ? e[u].val : 0.f, x[u]);
+        for (uint32_t u = 0; u < U; ++u) vfma(acc, ok[u] ? e[u].val : 0.f, x[u]);
       }
       strip_sync();                    // the strip is rewritten by the next batch
     }
@@ -244,16 +209,59 @@ __global__ __launch_bounds__(kBlock) void chunks_kernel(
   // combine the G lane groups: butterfly over lane-id bits LPR, 2 LPR, ..., 32
 #pragma unroll
   for (int m = LPR; m < 64; m <<= 1) vadd(acc, vshfl_xor(acc, m));
-  if (g == 0 && col_ok) {
-    const int32_t dst = chunk_dst[ch];
-    if (dst >= 0) {
-      float* y = Y + (size_t)dst * (size_t)k + c;
-      if (accumulate) vadd(acc, vload_stream<VEC>(y));
-      vstore_stream<VEC>(y, acc);
-    } else {
-      vstore_stream<VEC>(partials + (size_t)(-1 - dst) * (size_t)k + c, acc);
-    }
+  if (g == 0 && lc.ok) {
+    float* y = dst >= 0 ? a.Y + (size_t)dst * (size_t)a.k + lc.c
+                        : a.partials + (size_t)(-1 - dst) * (size_t)a.k + lc.c;
+    if (a.accumulate && dst >= 0) vadd(acc, vload_stream<VEC>(y));
+    vstore_stream<VEC>(y, acc);
   }
+}
+
+// Six wavefronts per SIMD: with seven the compiler spills in the narrow shapes (A^5 X of a 2m-vertex
+// Chung-Lu graph, k = 32: 2675 -> 2747 us).
+// grid: [wave list, slice by slice][pieces, slice by slice][short rows, slice by slice][rows without
+// entries, slice by slice]; every part is a multiple of 8 workgroups per slice, so that workgroup w
+// of every slice runs on die w mod 8 (the die queues of both lists rely on it).
+template <int VEC, int LPR, bool SMALL>
+__global__ __launch_bounds__(kBlock, 6) void product_kernel(const ProductArgs a) {
+  constexpr int GPB = kBlock / LPR;
+  constexpr int WPB = kBlock / 64;
+  union Shared {
+    RowsShared rows;
+    Entry strip[WPB][strip_entries<LPR>()];
+    __device__ Shared() {}
+  };
+  __shared__ Shared sh;
+  const int tid = threadIdx.x;
+  uint32_t id = blockIdx.x;
+  int part = 0;
+  while (part < 3 && id >= a.blocks[part] * a.slices) { id -= a.blocks[part] * a.slices; ++part; }
+  const uint32_t slice = id / a.blocks[part];
+  id -= slice * a.blocks[part];
+  const LaneColumns lc = lane_columns<VEC>(tid % LPR, (int)slice * (LPR * VEC), a.k);
+  if (part == 0) {
+    // Runs of kDieRun workgroups go to one die each: the eight dies then work on different column
+    // windows at a time, and a row of X that several chunks of a run read is fetched into one L2
+    // instead of several (chunks of the Chung-Lu graph above: 255 -> 231 us per product; R-MAT 8m,
+    // k = 128: 1 %; eighths of the whole list are slower, the dies then finish at different times).
+    const uint32_t span = kDies * kDieRun;
+    const uint32_t base = id / span * span;
+    if (a.runs && base + span <= a.blocks[0]) id = base + id % kDies * kDieRun + (id - base) / kDies;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int64_t ch = (int64_t)id * WPB + wave;
+    if (ch < a.n_chunks) chunk_part<VEC, LPR, SMALL>(sh.strip[wave], a, ch, lc);
+    return;
+  }
+  const int64_t first = (int64_t)id * a.items[part] + a.begin[part];
+  const int64_t left = a.begin[part] + a.count[part] - first;
+  const int n_it = left < a.items[part] ? (int)left : a.items[part];
+  if (n_it <= 0) return;
+  if (part < 3) {
+    rows_part<VEC, LPR, SMALL>(sh.rows, a, first, n_it, lc);
+    return;
+  }
+  for (int it = tid / LPR; it < n_it; it += GPB)   // level 0 stores every row of Y
+    if (lc.ok) vstore_stream<VEC>(a.Y + (size_t)a.rows_dst[first + it] * (size_t)a.k + lc.c, vzero<VEC>());
 }
 
 // ---------------------------------------------------------------------------
@@ -998,55 +1006,52 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(const int32_t* __restric
 
 }  // namespace
 
-int launch_rows(const uint32_t* rows_ptr, const uint32_t* rows_mid, const int32_t* rows_dst,
-                const Entry* entries, int64_t n_rows, const float* X, int64_t x_rows,
-                const float* Xh, float* Y, float* partials, int32_t k, bool accumulate,
-                const LaunchTuning& t, void* stream) {
-  if (n_rows <= 0) return 0;
-  const Shape s = pick_output_shape(k, t.kc, accumulate);
-  const bool small = small_matrix(x_rows, k);
+int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, int64_t n_empty, bool die_queues,
+                   int64_t x_rows, int32_t kc, void* stream) {
+  const Shape s = pick_output_shape(a.k, kc, a.accumulate != 0);
+  const bool small = small_matrix(x_rows, a.k);    // the staged buffer has at most as many rows as X
+  if (!(parts & kPartChunks)) a.n_chunks = 0;
+  a.begin[0] = 0; a.count[0] = a.n_chunks;
+  a.items[0] = kBlock / 64;
+  a.begin[1] = 0; a.count[1] = parts & kPartPieces ? n_pieces : 0;
+  a.begin[2] = n_pieces; a.count[2] = parts & kPartShort ? n_rows - n_pieces - n_empty : 0;
+  a.begin[3] = n_rows - n_empty; a.count[3] = parts & kPartShort ? n_empty : 0;
+  // Items per workgroup: as many as the descriptor arrays hold where that still gives a few thousand
+  // workgroups, fewer (down to one per lane group) for short lists, which would otherwise leave most
+  // of the 256 compute units without one (71 K pieces of R-MAT 1m, k = 64: 56 -> 44 us).  Pieces are
+  // up to three times as long as short rows.
+  const int least = kBlock / s.lpr < kItemsPerGroupBlock ? kBlock / s.lpr : kItemsPerGroupBlock;
+  for (int p = 1; p < 4; ++p) {
+    int items = kItemsPerGroupBlock;
+    if (!(p == 1 && die_queues)) {
+      if (p == 1) items = kItemsPerGroupBlock / 4;
+      while (items > least && a.count[p] < (int64_t)items * 2048) items >>= 1;
+    }
+    a.items[p] = items;
+  }
+  a.runs = !die_queues;
+  int64_t total = 0;
+  for (int p = 0; p < 4; ++p) {
+    const int64_t blocks = ceil_div(ceil_div(a.count[p], a.items[p]), kDies) * kDies;
+    total += blocks * s.slices;
+    if (total > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
+    a.blocks[p] = (uint32_t)blocks;
+  }
+  a.slices = (uint32_t)s.slices;
+  if (total == 0) return 0;
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
-    // a multiple of 8 workgroups per column slice: workgroup w of every slice runs on die w mod 8
-    const int64_t blocks = ceil_div(ceil_div(n_rows, kItemsPerGroupBlock), kDies) * kDies;
-    if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-    dim3 grid((unsigned)blocks, (unsigned)s.slices);
     if (small)
-      hipLaunchKernelGGL((rows_kernel<VEC, LPR, 8, true>), grid, dim3(kBlock), 0, (hipStream_t)stream,
-                         rows_ptr, rows_mid, rows_dst, entries, n_rows, X, Xh, Y, partials, (int)k,
-                         accumulate ? 1 : 0);
+      hipLaunchKernelGGL((product_kernel<VEC, LPR, true>), dim3((unsigned)total), dim3(kBlock), 0, (hipStream_t)stream, a);
     else
-      hipLaunchKernelGGL((rows_kernel<VEC, LPR, 8, false>), grid, dim3(kBlock), 0, (hipStream_t)stream,
-                         rows_ptr, rows_mid, rows_dst, entries, n_rows, X, Xh, Y, partials, (int)k,
-                         accumulate ? 1 : 0);
+      hipLaunchKernelGGL((product_kernel<VEC, LPR, false>), dim3((unsigned)total), dim3(kBlock), 0, (hipStream_t)stream, a);
     return (int)hipGetLastError();
   });
 }
 
-int launch_chunks(const uint32_t* chunk_ptr, const uint32_t* chunk_mid, const int32_t* chunk_dst,
-                  const Entry* entries, int64_t n_chunks, const float* X, int64_t x_rows,
-                  const float* Xh, float* Y, float* partials, int32_t k, bool accumulate,
-                  const LaunchTuning& t, void* stream) {
-  if (n_chunks <= 0) return 0;
-  const Shape s = pick_output_shape(k, t.kc, accumulate);
-  const bool small = small_matrix(x_rows, k);    // the staged buffer has at most as many rows as X
-  return dispatch_shape(s, [&](auto V, auto L) -> int {
-    constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
-    // a multiple of 8 workgroups per column slice, so that workgroup w of every slice runs on
-    // die w mod 8 (the die queues of the chunk list rely on it)
-    const int64_t blocks = ceil_div(ceil_div(n_chunks, kBlock / 64), kDies) * kDies;
-    if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-    dim3 grid((unsigned)blocks, (unsigned)s.slices);
-    if (small)
-      hipLaunchKernelGGL((chunks_kernel<VEC, LPR, 8, true>), grid, dim3(kBlock), 0, (hipStream_t)stream,
-                         chunk_ptr, chunk_mid, chunk_dst, entries, n_chunks, X, Xh, Y, partials,
-                         (int)k, accumulate ? 1 : 0);
-    else
-      hipLaunchKernelGGL((chunks_kernel<VEC, LPR, 8, false>), grid, dim3(kBlock), 0, (hipStream_t)stream,
-                         chunk_ptr, chunk_mid, chunk_dst, entries, n_chunks, X, Xh, Y, partials,
-                         (int)k, accumulate ? 1 : 0);
-    return (int)hipGetLastError();
-  });
+bool same_shape(int32_t k, int32_t kc_a, int32_t kc_b, bool accumulate) {
+  const Shape a = pick_output_shape(k, kc_a, accumulate), b = pick_output_shape(k, kc_b, accumulate);
+  return a.vec == b.vec && a.lpr == b.lpr;
 }
 
 int launch_reduce(const uint32_t* split_ptr, const int32_t* split_y, int64_t n_split,

@@ -672,6 +672,10 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
       }
       if (list == 0) {
         P.piece_slots = (int64_t)fin.size();
+        for (size_t r = P.row_pos.size(); opt.empty_last && li == 0 && r > 0; --r, ++im.empty_slots) {
+          const int32_t p = P.row_pos[r - 1];
+          if (L.rowptr[p + 1] - L.rowptr[p] - (int64_t)P.row_skip(p) > 0) break;
+        }
         for (int32_t p : P.row_pos) {                // plain short rows follow the class pieces
           ptr.push_back((uint32_t)at);
           dst.push_back(L.perm[p]);
@@ -1032,11 +1036,14 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
       const int64_t cnt_items = list == 0 ? im.n_rows : im.n_chunks;
       const std::vector<uint32_t>& ptr = P.list_ptr[list];
       const uint32_t* mid = list_mid[list];
-#pragma omp parallel for schedule(dynamic, 4096)
+      int uses_stage = 0;
+#pragma omp parallel for schedule(dynamic, 4096) reduction(| : uses_stage)
       for (int64_t s = 0; s < cnt_items; ++s) {
         for (uint32_t e = ptr[s]; e < mid[s]; ++e) seen[P.stage_perm[ent[e].xrow]] = 1;
+        if (mid[s] > ptr[s]) uses_stage = 1;
         for (uint32_t e = mid[s]; e < ptr[s + 1]; ++e) seen[ent[e].xrow] = 1;
       }
+      im.stage_used = im.stage_used || uses_stage || im.n_panel_bins > 0 || im.n_corner_tiles > 0;
       int64_t cnt = 0;
 #pragma omp parallel for schedule(static) reduction(+ : cnt)
       for (int64_t v = 0; v < n; ++v) cnt += seen[v];
@@ -1101,7 +1108,7 @@ int verify_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, co
         double sum = 0.0;
         for (uint32_t e = lo; e < hi; ++e) {
           int64_t xr = ent[e].xrow;
-          if (e < mid) { if (xr < 0 || xr >= im.n_stage) { err = "staged row out of range"; return ARROW_EINTERNAL; } xr = stage_perm[xr]; }
+          if (e < mid) { if (!im.stage_used) { err = "entry reads a staged head that is not filled"; return ARROW_EINTERNAL; } if (xr < 0 || xr >= im.n_stage) { err = "staged row out of range"; return ARROW_EINTERNAL; } xr = stage_perm[xr]; }
           if (xr < 0 || xr >= n) { err = "X row out of range"; return ARROW_EINTERNAL; }
           sum += (double)ent[e].val * (double)(1 + xr);
           ent_row[e] = row;

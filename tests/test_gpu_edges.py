@@ -45,3 +45,23 @@ def test_shared_columns_count_once_in_dot_products(torch, k):
     fin = np.isfinite(ref)
     bound = np.abs(w.vals[fin]) * np.einsum("ij,ij->i", np.abs(U[rows[fin]]), np.abs(V[w.colidx[fin]]))
     assert np.all(np.abs(S[fin] - ref[fin]) <= TOL * bound)
+
+
+@pytest.mark.parametrize("n", [1, 7, 64, 65, 513, 20000])
+@pytest.mark.parametrize("k", [1, 4, 16, 128])
+def test_short_work_lists(torch, n, k):
+    """Lists shorter than a workgroup's share, rows without entries in between, one row of middle length."""
+    rng = np.random.default_rng(n)
+    length = np.where(rng.random(n) < 0.4, 0, rng.integers(1, min(n, 5) + 1, n))
+    length[n // 2] = min(n, 40)
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    colidx = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for m in length]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=14)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, max(1, n // 8))
+    binding.arrow_self_check(op.h)
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
+    op.close()
