@@ -148,6 +148,8 @@ int check_hip(int rc, const char* what) {
   return fail(ARROW_EHIP, "%s: %s", what, hipGetErrorString((hipError_t)rc));
 }
 
+constexpr int64_t kFewChunks = 2048;   // a list this short leaves wavefront slots empty
+
 // one product, src -> dst (device, n x k), all levels in stream order.  `ws` holds the partial
 // vectors, the staged head and the panel results (the caller's workspace, or the static scratch
 // array); every byte of it that a kernel reads has been written earlier in the same product.
@@ -177,9 +179,12 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
         int64_t kc = 256;
         while (kc > 16 && im.stage_class_rows * kc * 4 > tune.l2_resident_bytes) kc >>= 1;
         if (kc < k) tune.kc = (int32_t)kc;
-      } else if (im.staged && k > 64) {
-        // window-ordered chunks: 64-column passes halve the bytes of a column window, which the
-        // L2 hit rate of the head rows gains more from than the second pass over the entries costs
+      } else if (k > 64 && (k % 32 == 0 || (im.row_major && im.n_chunks <= kFewChunks))) {
+        // 64-column passes halve the bytes of a column window, which the L2 hit rate of the long rows
+        // gains more from than the second pass over the entries costs -- where a row fills whole
+        // 128-byte lines.  In other rows a slice starts and ends inside a line, and both neighbours
+        // fetch it: R-MAT 262k, k = 68: 235 us in two slices, 160 us in one; k = 130: 417 and 354 us.
+        // (A short list has few wavefronts and long chains instead: slices shorten them.)
         tune.kc = 64;
       }
     }
@@ -193,7 +198,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
       a.k = k; a.accumulate = acc ? 1 : 0;
       auto launch = [&](int parts, int32_t kc) -> int {
         return check_hip(arrow::launch_product(a, parts, im.piece_slots, im.n_rows, im.empty_slots, im.classes > 0,
-                                               h->n, kc, stream), "product kernel launch");
+                                               !im.row_major, h->n, kc, stream), "product kernel launch");
       };
       // the wave list and the pieces follow the chunk kernel's column slicing, the short rows run in
       // one pass over whole rows; where that is the same shape, one launch takes all of it.  A

@@ -64,6 +64,10 @@ struct Entry {
 
 constexpr int kDies = 8;             // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
 constexpr int kChunksPerGroup = 4;   // wave-list items (one per wavefront) per workgroup of the chunk kernel
+// Destination of a wave-list item whose sum is added to that of its workgroup's first item: the four
+// wavefronts of a workgroup then work on one item together (slots 4 i .. 4 i + 3, all or none).
+// INT32_MIN marks padding; partial slots end below both.
+constexpr int32_t kTeamDst = INT32_MIN + 1;
 constexpr int kItemsPerGroupBlock = 64;  // most group-list items per workgroup, and exactly that many of a die queue
 constexpr int kDieRun = 256;         // consecutive wave-list workgroups that one die takes where the list has no die queues
 // head panels: kPanelRows head rows form a group; the group's head-block entries are dealt by column
@@ -94,6 +98,7 @@ struct LevelImage {
   int64_t n_stage = 0;          // rows of the staging buffer (min(b, n_i) or 0)
   int64_t stage_class_rows = 0; // rows of the first column class in the buffer
   size_t off_stage_perm = 0;    // int32 n_stage : buffer row -> X row
+  bool row_major = false;       // the wave list is ordered by length, not by column window
   int32_t classes = 0;          // column classes used for the chunk queues (0 = none)
   // group list: items handled one per lane group (class pieces in die queues, then the short rows)
   int64_t n_rows = 0, n_real_rows = 0, rows_partials = 0, nnz_rows = 0;
@@ -107,7 +112,7 @@ struct LevelImage {
   int64_t n_chunks = 0, n_real_chunks = 0, chunks_partials = 0, nnz_chunks = 0;
   size_t off_chunk_ptr = 0;  // uint32 n_chunks + 1
   size_t off_chunk_mid = 0;  // uint32 n_chunks : entries before it read the staged head buffer, the rest read X
-  size_t off_chunk_dst = 0;  // int32  n_chunks : >= 0 -> Y row (whole row in one chunk), < 0 -> partial slot (-1 - slot)
+  size_t off_chunk_dst = 0;  // int32  n_chunks : >= 0 -> Y row (whole row in one chunk), < 0 -> partial slot (-1 - slot), kTeamDst, INT32_MIN -> padding
   size_t off_chunk_row = 0;  // int32  n_chunks : the vertex the item belongs to, -1 for padding
   // rows assembled from several chunks
   int64_t n_split = 0, n_partials = 0;
@@ -213,14 +218,16 @@ struct ProductArgs {
   uint32_t blocks[4];                   // workgroups per column slice
   int32_t items[4];                     // slots per workgroup
   uint32_t slices;
+  int32_t width;                        // columns per slice
+  int32_t piece_waves;                  // a piece per wavefront instead of per lane group
   int32_t runs;                         // deal the wave list to the dies in runs of kDieRun workgroups
 };
 enum { kPartChunks = 1, kPartPieces = 2, kPartShort = 4, kPartAll = 7 };
 // Launches the given parts.  n_pieces, n_rows, n_empty: pieces, all items and trailing empty rows of
 // the group list; x_rows = rows of X (it decides whether 32-bit offsets are enough); kc = columns per
-// pass (0: the whole row).
+// pass (0: the whole row); windows: the wave list is ordered by column window.
 int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, int64_t n_empty, bool die_queues,
-                   int64_t x_rows, int32_t kc, void* stream);
+                   bool windows, int64_t x_rows, int32_t kc, void* stream);
 // whether launches with these two kc have the same shape, so that their parts can share one
 bool same_shape(int32_t k, int32_t kc_a, int32_t kc_b, bool accumulate);
 int launch_reduce(const uint32_t* split_ptr, const int32_t* split_y, int64_t n_split,

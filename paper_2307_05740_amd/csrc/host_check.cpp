@@ -34,7 +34,7 @@ hipError_t hipEventDestroy(hipEvent_t) { reached("hipEventDestroy"); }
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { reached("hipMemcpyAsync"); }
 }
 namespace arrow {
-int launch_product(ProductArgs, int, int64_t, int64_t, int64_t, bool, int64_t, int32_t, void*) { reached("launch_product"); }
+int launch_product(ProductArgs, int, int64_t, int64_t, int64_t, bool, bool, int64_t, int32_t, void*) { reached("launch_product"); }
 bool same_shape(int32_t, int32_t, int32_t, bool) { reached("same_shape"); }
 int launch_reduce(const uint32_t*, const int32_t*, int64_t, const float*, float*, int32_t, bool, void*) { reached("launch_reduce"); }
 int launch_gather(const int32_t*, int64_t, const float*, float*, int32_t, void*) { reached("launch_gather"); }

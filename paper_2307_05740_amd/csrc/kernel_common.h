@@ -77,7 +77,7 @@ template <> __device__ __forceinline__ void gstore<4>(float* p, float4 v) {
   *reinterpret_cast<stream_v4f*>(p) = t;
 }
 
-// First column of lane l's VEC columns in the slice that starts at column c0; a lane whose columns
+// First column of lane l's VEC columns in the slice of `width` columns that starts at column c0; a lane whose columns
 // would run past the last one is moved back so that they end there.  It then shares `shared` columns
 // with the lane before it: both hold and store the same values for them.  Lanes that start at or
 // beyond column k have none (ok = false) and read column 0.
@@ -87,11 +87,11 @@ struct LaneColumns {
   bool ok;
 };
 template <int VEC>
-__device__ __forceinline__ LaneColumns lane_columns(int l, int c0, int k) {
+__device__ __forceinline__ LaneColumns lane_columns(int l, int c0, int k, int width = 1 << 20) {
   LaneColumns r;
   r.c = c0 + l * VEC;
   r.shared = 0;
-  r.ok = r.c < k;
+  r.ok = r.c < k && l * VEC < width;
   if (VEC > 1 && r.ok && r.c + VEC > k) { r.shared = r.c + VEC - k; r.c = k - VEC; }
   return r;
 }
@@ -153,6 +153,7 @@ __device__ __forceinline__ void strip_sync() {
 // ---------------------------------------------------------------------------
 struct Shape {
   int vec, lpr, slices;
+  int width;             // columns per slice where the slices are made even (a multiple of vec); lpr * vec at most
 };
 
 // Columns per lane: 4 wherever a row has that many (the last lane of a row may share columns with
@@ -173,6 +174,7 @@ struct Shape {
   while (lpr < lanes) lpr <<= 1;
   s.lpr = lpr;
   s.slices = (k + lpr * s.vec - 1) / (lpr * s.vec);
+  s.width = ((k + s.slices - 1) / s.slices + s.vec - 1) / s.vec * s.vec;
   return s;
 }
 
@@ -193,7 +195,7 @@ int dispatch_shape(const Shape& s, F&& f) {
 // the shape of a launch that writes Y: exact where it adds to Y and its last slice holds fewer than 4 columns
 [[maybe_unused]] Shape pick_output_shape(int k, int kc, bool accumulate) {
   const Shape s = pick_shape(k, kc);
-  const int last = k - (s.slices - 1) * s.lpr * s.vec;
+  const int last = k - (s.slices - 1) * s.width;
   return accumulate && s.slices > 1 && last < s.vec ? pick_shape(k, kc, true) : s;
 }
 

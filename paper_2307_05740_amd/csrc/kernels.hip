@@ -40,7 +40,6 @@
 #include <hip/hip_runtime.h>
 
 #include <climits>
-#include <cstdlib>
 #include <cstdint>
 #include <type_traits>
 
@@ -57,6 +56,7 @@ namespace {
 // tail instead of three (a launch on its own costs 2 - 3 us on the stream, which is most of the
 // time of a product over a few thousand rows).
 // ---------------------------------------------------------------------------
+constexpr int64_t kPieceWavesMax = 4096;
 constexpr int kRowsStage = 1024;   // entries of the group list a workgroup stages at once (8 KiB)
 
 template <int LPR> constexpr int strip_entries() {     // entries of the wave list a wavefront parks per batch
@@ -138,26 +138,32 @@ __device__ __forceinline__ void rows_part(RowsShared& sh, const ProductArgs& a, 
 // One chunk of the wave list per wavefront.  Entries [lo, mid) of a chunk read rows of the staged
 // head buffer Xh, entries [mid, hi) read rows of X (the chunk's entries are ordered by column
 // position, head columns first), so the base pointer is uniform inside a batch.  The G lane groups
-// take the entries round-robin and are combined with a butterfly over the lane groups.
+// take the entries round-robin and are combined with a butterfly over the lane groups; the wavefronts
+// of a team (kTeamDst) then add up in LDS, in slot order (sums: LDS for that, or null where the list
+// has no teams).
 // (Several chunks per wavefront, the next one's descriptor and entries fetched ahead, measured 3 %
 // slower for two and 10 % for four: the chunks in flight then reach over more column windows.)
 template <int VEC, int LPR, bool SMALL>
-__device__ __forceinline__ void chunk_part(Entry* mine, const ProductArgs& a, int64_t ch, const LaneColumns lc) {
+__device__ __forceinline__ void chunk_part(Entry* mine, const ProductArgs& a, const uint32_t* ptr,
+                                           const uint32_t* mids, const int32_t* dsts, int64_t ch, float* sums,
+                                           const LaneColumns lc) {
   using V = typename Vec<VEC>::type;
   constexpr int G = 64 / LPR;
   constexpr uint32_t U = 8;
   constexpr uint32_t STRIP = strip_entries<LPR>();
   constexpr int NA = STRIP / 64;
-  const uint32_t lo = a.chunk_ptr[ch];
-  const uint32_t hi = a.chunk_ptr[ch + 1];
-  const uint32_t mid = a.chunk_mid[ch];
-  const int32_t dst = a.chunk_dst[ch];
+  const uint32_t lo = ptr[ch];
+  const uint32_t hi = ptr[ch + 1];
+  const uint32_t mid = mids[ch];
+  const int32_t dst = dsts[ch];
   if (lo == hi) return;                // padding slot of the die queues
   const uint32_t lane = threadIdx.x % 64;
   const uint32_t g = lane / LPR;
   const uint32_t row_bytes = 4u * (uint32_t)a.k;
   const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
   const Entry* grp = mine + g;
+  const int64_t ch0 = ch - ch % kChunksPerGroup;
+  const bool team = sums && ch0 + 1 < a.n_chunks && dsts[ch0 + 1] == kTeamDst;
   V acc = vzero<VEC>();
   // the next entries of the chunk are fetched while the current batch is being worked on (the two
   // segments are consecutive in the entry array, so the fetch runs across their boundary)
@@ -209,6 +215,14 @@ __device__ __forceinline__ void chunk_part(Entry* mine, const ProductArgs& a, in
   // combine the G lane groups: butterfly over lane-id bits LPR, 2 LPR, ..., 32
 #pragma unroll
   for (int m = LPR; m < 64; m <<= 1) vadd(acc, vshfl_xor(acc, m));
+  const int wave = (int)(ch % kChunksPerGroup);
+  if (team) {                          // all four wavefronts of the workgroup are here
+    if (wave > 0 && g == 0) vstore<VEC>(sums + (wave * 64 + lane) * VEC, acc);
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 1; w < kChunksPerGroup; ++w) vadd(acc, vload<VEC>(sums + (w * 64 + lane % LPR) * VEC));
+  }
   if (g == 0 && lc.ok) {
     float* y = dst >= 0 ? a.Y + (size_t)dst * (size_t)a.k + lc.c
                         : a.partials + (size_t)(-1 - dst) * (size_t)a.k + lc.c;
@@ -228,7 +242,7 @@ __global__ __launch_bounds__(kBlock, 6) void product_kernel(const ProductArgs a)
   constexpr int WPB = kBlock / 64;
   union Shared {
     RowsShared rows;
-    Entry strip[WPB][strip_entries<LPR>()];
+    struct { Entry strip[WPB][strip_entries<LPR>()]; float sums[WPB * 64 * VEC]; } chunk;
     __device__ Shared() {}
   };
   __shared__ Shared sh;
@@ -238,18 +252,15 @@ __global__ __launch_bounds__(kBlock, 6) void product_kernel(const ProductArgs a)
   while (part < 3 && id >= a.blocks[part] * a.slices) { id -= a.blocks[part] * a.slices; ++part; }
   const uint32_t slice = id / a.blocks[part];
   id -= slice * a.blocks[part];
-  const LaneColumns lc = lane_columns<VEC>(tid % LPR, (int)slice * (LPR * VEC), a.k);
-  if (part == 0) {
-    // Runs of kDieRun workgroups go to one die each: the eight dies then work on different column
-    // windows at a time, and a row of X that several chunks of a run read is fetched into one L2
-    // instead of several (chunks of the Chung-Lu graph above: 255 -> 231 us per product; R-MAT 8m,
-    // k = 128: 1 %; eighths of the whole list are slower, the dies then finish at different times).
-    const uint32_t span = kDies * kDieRun;
-    const uint32_t base = id / span * span;
-    if (a.runs && base + span <= a.blocks[0]) id = base + id % kDies * kDieRun + (id - base) / kDies;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const LaneColumns lc = lane_columns<VEC>(tid % LPR, (int)slice * a.width, a.k, a.width);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  if (part == 0 || (part == 1 && a.piece_waves)) {
+    const bool list = part == 0;
     const int64_t ch = (int64_t)id * WPB + wave;
-    if (ch < a.n_chunks) chunk_part<VEC, LPR, SMALL>(sh.strip[wave], a, ch, lc);
+    if (ch < a.count[part])
+      chunk_part<VEC, LPR, SMALL>(sh.chunk.strip[wave], a, list ? a.chunk_ptr : a.rows_ptr,
+                                  list ? a.chunk_mid : a.rows_mid, list ? a.chunk_dst : a.rows_dst, ch,
+                                  list ? sh.chunk.sums : nullptr, lc);
     return;
   }
   const int64_t first = (int64_t)id * a.items[part] + a.begin[part];
@@ -262,6 +273,28 @@ __global__ __launch_bounds__(kBlock, 6) void product_kernel(const ProductArgs a)
   }
   for (int it = tid / LPR; it < n_it; it += GPB)   // level 0 stores every row of Y
     if (lc.ok) vstore_stream<VEC>(a.Y + (size_t)a.rows_dst[first + it] * (size_t)a.k + lc.c, vzero<VEC>());
+}
+
+// The wave list on its own, for lists in window order: a chunk is over in two or three rounds of row
+// loads, so what a wavefront does before the first of them counts (finding its part of the product
+// kernel's grid and looking for a team cost the chunks of the Chung-Lu graph above 7 %).
+template <int VEC, int LPR, bool SMALL>
+__global__ __launch_bounds__(kBlock) void chunks_kernel(const ProductArgs a) {
+  constexpr int WPB = kBlock / 64;
+  __shared__ Entry strip[WPB][strip_entries<LPR>()];
+  uint32_t id = blockIdx.x;
+  // Runs of kDieRun workgroups go to one die each: the eight dies then work on different column
+  // windows at a time, and a row of X that several chunks of a run read is fetched into one L2
+  // instead of several (the same chunks: 255 -> 231 us per product; R-MAT 8m, k = 128: 1 %; eighths
+  // of the whole list are slower, the dies then finish at different times).
+  const uint32_t span = kDies * kDieRun;
+  const uint32_t base = id / span * span;
+  if (a.runs && base + span <= a.blocks[0]) id = base + id % kDies * kDieRun + (id - base) / kDies;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const int64_t ch = (int64_t)id * WPB + wave;
+  if (ch >= a.n_chunks) return;
+  const LaneColumns lc = lane_columns<VEC>(threadIdx.x % LPR, (int)blockIdx.y * a.width, a.k, a.width);
+  chunk_part<VEC, LPR, SMALL>(strip[wave], a, a.chunk_ptr, a.chunk_mid, a.chunk_dst, ch, nullptr, lc);
 }
 
 // ---------------------------------------------------------------------------
@@ -278,7 +311,7 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
     const WindowTile* __restrict__ tiles, const uint32_t* __restrict__ wrow_ptr,
     const uint32_t* __restrict__ wrow_mid, const int32_t* __restrict__ wrow_y,
     const Entry* __restrict__ ent, const int32_t* __restrict__ perm, const float* __restrict__ X,
-    float* __restrict__ Y, int k, int accumulate) {
+    float* __restrict__ Y, int k, int width, int accumulate) {
   using V = typename Vec<VEC>::type;
   constexpr int GPB = kWinBlock / LPR;
   constexpr int W = LPR * VEC;                       // columns per slice = LDS row length
@@ -286,7 +319,7 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
   const WindowTile t = tiles[blockIdx.x];
   const int l = threadIdx.x % LPR;
   const int grp = threadIdx.x / LPR;
-  const LaneColumns lc = lane_columns<VEC>(l, blockIdx.y * W, k);   // lane l's columns sit at [l * VEC] of an LDS row
+  const LaneColumns lc = lane_columns<VEC>(l, blockIdx.y * width, k, width);   // lane l's columns sit at [l * VEC] of an LDS row
   const int c = lc.c;
   const bool col_ok = lc.ok;
   const float* Xc = X + (col_ok ? c : 0);
@@ -960,7 +993,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_corner_kernel(
 template <int VEC, int LPR>
 __global__ __launch_bounds__(kBlock) void reduce_kernel(
     const uint32_t* __restrict__ split_ptr, const int32_t* __restrict__ split_y, int64_t n_split,
-    const float* __restrict__ partials, float* __restrict__ Y, int k, int accumulate) {
+    const float* __restrict__ partials, float* __restrict__ Y, int k, int width, int accumulate) {
   using V = typename Vec<VEC>::type;
   constexpr int G = 64 / LPR;
   constexpr int WPB = kBlock / 64;
@@ -968,7 +1001,7 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(
   if (row >= n_split) return;
   const int lane = threadIdx.x % 64;
   const int g = lane / LPR;
-  const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * (LPR * VEC), k);
+  const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * width, k, width);
   const int c = lc.c;
   const bool col_ok = lc.ok;
   const uint32_t lo = split_ptr[row], hi = split_ptr[row + 1];
@@ -1007,7 +1040,7 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(const int32_t* __restric
 }  // namespace
 
 int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, int64_t n_empty, bool die_queues,
-                   int64_t x_rows, int32_t kc, void* stream) {
+                   bool windows, int64_t x_rows, int32_t kc, void* stream) {
   const Shape s = pick_output_shape(a.k, kc, a.accumulate != 0);
   const bool small = small_matrix(x_rows, a.k);    // the staged buffer has at most as many rows as X
   if (!(parts & kPartChunks)) a.n_chunks = 0;
@@ -1029,7 +1062,12 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
     }
     a.items[p] = items;
   }
-  a.runs = !die_queues;
+  // A piece is some 30 entries: eight to sixteen lane groups finish one in a round or two of row
+  // loads where a lane group on its own needs four to six in a row.  Worth the idle lanes only where
+  // latency decides, in a list of at most a few pieces per SIMD.
+  a.piece_waves = !die_queues && s.lpr <= 8 && a.count[1] <= kPieceWavesMax;
+  if (a.piece_waves) a.items[1] = kBlock / 64;
+  a.runs = windows && !die_queues;
   int64_t total = 0;
   for (int p = 0; p < 4; ++p) {
     const int64_t blocks = ceil_div(ceil_div(a.count[p], a.items[p]), kDies) * kDies;
@@ -1038,20 +1076,27 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
     a.blocks[p] = (uint32_t)blocks;
   }
   a.slices = (uint32_t)s.slices;
-  if (total == 0) return 0;
+  a.width = s.width;
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
-    if (small)
-      hipLaunchKernelGGL((product_kernel<VEC, LPR, true>), dim3((unsigned)total), dim3(kBlock), 0, (hipStream_t)stream, a);
-    else
-      hipLaunchKernelGGL((product_kernel<VEC, LPR, false>), dim3((unsigned)total), dim3(kBlock), 0, (hipStream_t)stream, a);
+    if (windows && a.blocks[0] > 0) {
+      dim3 grid(a.blocks[0], a.slices);
+      if (small) hipLaunchKernelGGL((chunks_kernel<VEC, LPR, true>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);
+      else hipLaunchKernelGGL((chunks_kernel<VEC, LPR, false>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);
+      total -= (int64_t)a.blocks[0] * a.slices;
+      a.blocks[0] = 0;
+    }
+    if (total > 0) {
+      if (small) hipLaunchKernelGGL((product_kernel<VEC, LPR, true>), dim3((unsigned)total), dim3(kBlock), 0, (hipStream_t)stream, a);
+      else hipLaunchKernelGGL((product_kernel<VEC, LPR, false>), dim3((unsigned)total), dim3(kBlock), 0, (hipStream_t)stream, a);
+    }
     return (int)hipGetLastError();
   });
 }
 
 bool same_shape(int32_t k, int32_t kc_a, int32_t kc_b, bool accumulate) {
   const Shape a = pick_output_shape(k, kc_a, accumulate), b = pick_output_shape(k, kc_b, accumulate);
-  return a.vec == b.vec && a.lpr == b.lpr;
+  return a.vec == b.vec && a.lpr == b.lpr && a.width == b.width;
 }
 
 int launch_reduce(const uint32_t* split_ptr, const int32_t* split_y, int64_t n_split,
@@ -1064,7 +1109,7 @@ int launch_reduce(const uint32_t* split_ptr, const int32_t* split_y, int64_t n_s
     if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
     dim3 grid((unsigned)blocks, (unsigned)s.slices);
     hipLaunchKernelGGL((reduce_kernel<VEC, LPR>), grid, dim3(kBlock), 0, (hipStream_t)stream,
-                       split_ptr, split_y, n_split, partials, Y, (int)k, accumulate ? 1 : 0);
+                       split_ptr, split_y, n_split, partials, Y, (int)k, s.width, accumulate ? 1 : 0);
     return (int)hipGetLastError();
   });
 }
@@ -1102,7 +1147,7 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, co
     dim3 grid((unsigned)n_tiles, (unsigned)s.slices);
     const size_t lds = (size_t)max_span * LPR * VEC * sizeof(float);
     hipLaunchKernelGGL((window_kernel<VEC, LPR>), grid, dim3(kWinBlock), lds, (hipStream_t)stream, tiles,
-                       wrow_ptr, wrow_mid, wrow_y, entries, perm, X, Y, (int)k, accumulate ? 1 : 0);
+                       wrow_ptr, wrow_mid, wrow_y, entries, perm, X, Y, (int)k, s.width, accumulate ? 1 : 0);
     return (int)hipGetLastError();
   });
 }

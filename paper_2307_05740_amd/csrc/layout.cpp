@@ -73,6 +73,10 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr uint32_t kPad = 0xffffffffu;
+// Measured with R-MAT and Chung-Lu graphs against column windows and the staged head: 65,000 vertices,
+// k = 16 / 64 / 128: 26 / 38 / 70 -> 19 / 28 / 49 us; 131,000: 36 / 60 / 111 -> 29 / 52 / 105 us; 262,000:
+// 61 / 109 / 212 -> 48 / 125 / 260 us.
+constexpr int64_t kRowMajorRows = 1 << 17;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -83,6 +87,7 @@ struct Rec {
   uint32_t phase;
   uint32_t key;    // column window of the first entry
   int8_t queue;    // die queue 0..7, or -1 for the window-ordered last phase
+  uint8_t team;    // 0: an item of its own; 1 .. 4: its place among the wavefronts that sum one item together
   uint8_t list;    // 0 group list, 1 wave list
   uint32_t seq;    // emission index (names the rec)
 };
@@ -239,6 +244,22 @@ void fuse_levels(const std::vector<HostLevel>& levels, std::vector<HostLevel>& e
   }
 }
 
+// Whether the columns that are read most have vertex ids with the same low bits, as the hubs of an
+// R-MAT graph over 2^s vertices do.  Rows of X a multiple of some KiB apart share L2 channels, so such
+// a graph keeps a few of an L2's 16 channels busy and the others idle; the staged head, whose rows lie
+// in order of position, spreads them (A^3 of R-MAT 2^20, k = 64: 1348 us with the buffer, 1419 us
+// without).  Elsewhere the buffer only costs its launch and its traffic: over 700,000 vertices instead
+// of 2^20, k = 16 ... 128: 2 - 6 % slower with it than without.
+bool ids_share_low_bits(const HostLevel& L, int64_t nnz) {
+  constexpr int kResidues = 64;
+  const int64_t step = std::max<int64_t>(1, nnz / 1000003);      // about a million of the entries
+  std::vector<int64_t> hits(kResidues, 0);
+  int64_t seen = 0, most = 0;
+  for (int64_t e = 0; e < nnz; e += step, ++seen) ++hits[L.perm[L.colpos[e]] % kResidues];
+  for (int64_t c : hits) most = std::max(most, c);
+  return most * kResidues > 4 * seen;
+}
+
 int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, const PackOptions& opt,
                 Image& img, std::string& err) {
   img.levels.clear();
@@ -270,9 +291,19 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
     const int64_t lev_nnz = L.rowptr[L.n_i];
     if (lev_nnz >= 0xffffffffLL - 4096) { err = "a level holds too many entries (limit 2^32 - 4097)"; return ARROW_EINVAL; }
     const int64_t head = std::min<int64_t>(b, L.n_i);
-    im.staged = opt.stage_head && li == 0 && L.n_i > b;
+    // An operand whose X the L2s and the Infinity Cache hold anyway (up to kRowMajorRows rows) gains
+    // nothing from column windows or a staged copy of the head: its long rows are items as they are,
+    // a long one shared by the four wavefronts of a workgroup, which saves the launches that fill the
+    // head buffer and, mostly, the one that sums partial vectors.
+    const bool row_major = window == PackOptions().window_rows && L.n_i <= kRowMajorRows && classes == 0 &&
+                           !opt.panel && !opt.corner;
+    const bool keep_head = opt.panel || opt.corner || classes > 0 || opt.stage_short > 0;   // these read the buffer
+    im.staged = opt.stage_head && li == 0 && L.n_i > b && !row_major && (keep_head || ids_share_low_bits(L, lev_nnz));
+    im.row_major = row_major;
     im.n_stage = im.staged ? head : 0;
-    if (im.n_stage > img.max_stage_rows) img.max_stage_rows = im.n_stage;
+    // The workspace keeps room for the buffer wherever the level could have one: what a product with k
+    // columns needs then grows with k, and a workspace bound for fewer columns is refused.
+    if (opt.stage_head && li == 0 && L.n_i > b && head > img.max_stage_rows) img.max_stage_rows = head;
     im.classes = (int32_t)classes;
 
     // ---- diagonal-block tiles whose window of P_i X is staged in LDS ---------------------------
@@ -560,7 +591,7 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
             for (int64_t j = 0; j < parts; ++j) {
               Rec& rc = out[first_rec[c] + j];
               rc.row = p; rc.len = (uint32_t)(base + (j < extra ? 1 : 0)); rc.dst = 0;
-              rc.phase = (uint32_t)(c / kDies); rc.queue = (int8_t)(c % kDies); rc.key = 0; rc.seq = 0;
+              rc.phase = (uint32_t)(c / kDies); rc.queue = (int8_t)(c % kDies); rc.key = 0; rc.seq = 0; rc.team = 0;
               rc.list = cnt[c] <= piece_max ? 0 : 1;
             }
           }
@@ -578,6 +609,25 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
           // lane-group pieces run several to a wavefront: order them by length (longest first)
           // so that the pieces sharing a wavefront finish together
           for (Rec& rc : out) if (rc.list == 0) rc.key = 0xffffu - (rc.len > 0xffffu ? 0xffffu : rc.len);
+        } else if (row_major && len > piece_max) {
+          // a wavefront takes up to chunk_nnz entries, a workgroup's four together up to eight times
+          // that; a row beyond is cut into such pieces, whose results are partial vectors
+          const int64_t cap = 8 * chunk_nnz;
+          const bool alone = len <= std::max<int64_t>(chunk_nnz, 16);      // a team's wavefronts all get entries
+          const int64_t parts = alone ? 1 : (len + cap - 1) / cap;
+          const int64_t waves = alone ? 1 : (int64_t)kChunksPerGroup * parts;
+          const int64_t base = len / waves, extra = len % waves;
+          for (int64_t j = 0; j < waves; ++j) {
+            Rec rc;
+            rc.row = p; rc.len = (uint32_t)(base + (j < extra ? 1 : 0)); rc.dst = 0;
+            rc.phase = class_phases; rc.queue = -1; rc.list = 1; rc.seq = 0;
+            rc.team = waves == 1 ? 0 : (uint8_t)(1 + j % kChunksPerGroup);
+            // teams first (they then start at a workgroup's first slot), longest first: the longest
+            // items decide when the launch ends
+            const int64_t of_item = waves == 1 ? len : len / parts;
+            rc.key = (uint32_t)(0x7fffffff - std::min<int64_t>(of_item, 0x7fffffff)) + (waves == 1 ? 0x80000000u : 0u);
+            out.push_back(rc);
+          }
         } else {
           int64_t s0 = 0;
           while (s0 < len) {
@@ -596,7 +646,7 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
               Rec rc;
               rc.row = p; rc.len = (uint32_t)piece; rc.dst = 0;
               rc.phase = class_phases;
-              rc.queue = -1; rc.list = 0; rc.key = (uint32_t)(cols[s0] / key_window); rc.seq = 0;
+              rc.queue = -1; rc.list = 0; rc.key = (uint32_t)(cols[s0] / key_window); rc.seq = 0; rc.team = 0;
               out.push_back(rc);
               s0 = e0;
               continue;
@@ -609,7 +659,7 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
               Rec rc;
               rc.row = p; rc.len = (uint32_t)sz; rc.dst = 0;
               rc.phase = class_phases;                             // the last phase
-              rc.queue = -1; rc.list = 1; rc.key = (uint32_t)(cols[at_row] / key_window); rc.seq = 0;
+              rc.queue = -1; rc.list = 1; rc.key = (uint32_t)(cols[at_row] / key_window); rc.seq = 0; rc.team = 0;
               out.push_back(rc);
               at_row += sz;
             }
@@ -626,11 +676,14 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
       P.row_first[r] = (int64_t)P.recs.size();
       std::vector<Rec>& out = per_row[r];
       const int32_t p = P.long_rows[r];
-      if (out.size() == 1) {
-        out[0].dst = L.perm[p];
+      int64_t results = 0;               // a team gives one
+      for (const Rec& rc : out) results += rc.team <= 1;
+      if (results == 1) {
+        for (Rec& rc : out) rc.dst = rc.team <= 1 ? L.perm[p] : kTeamDst;
       } else {
-        for (size_t j = 0; j < out.size(); ++j) out[j].dst = (int32_t)(-1 - (slots + (int64_t)j));
-        slots += (int64_t)out.size();
+        int64_t j = 0;
+        for (Rec& rc : out) rc.dst = rc.team <= 1 ? (int32_t)(-1 - (slots + j++)) : kTeamDst;
+        slots += results;
         P.split_ptr.push_back((uint32_t)slots);
         P.split_y.push_back(L.perm[p]);
       }
@@ -638,7 +691,7 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
       std::vector<Rec>().swap(out);
     }
     P.row_first[n_long] = (int64_t)P.recs.size();
-    if (slots > 0x7fffffffLL) { err = "too many partial slots"; return ARROW_EINVAL; }
+    if (slots > 0x7ffffff0LL) { err = "too many partial slots"; return ARROW_EINVAL; }
     if (P.recs.size() > 0x7fffff00ULL) { err = "too many work items"; return ARROW_EINVAL; }
 
     // ---- final order of both lists; entry offsets --------------------------------------------
@@ -667,7 +720,7 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
           irow.push_back(L.perm[rc.row]);
           at += rc.len;
           ++real_items[list];
-          if (rc.dst < 0) ++part_items[list];
+          if (rc.dst < 0 && rc.dst != kTeamDst) ++part_items[list];
         }
       }
       if (list == 0) {
@@ -1101,8 +1154,16 @@ int verify_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, co
         const uint32_t lo = ptrs[list][s], mid = mids[list][s], hi = ptrs[list][s + 1];
         if (lo != expect || lo > mid || mid > hi || (int64_t)hi > lev_nnz) { err = "item offsets out of order"; return ARROW_EINTERNAL; }
         expect = hi;
-        const int32_t dst = dsts[list][s];
+        int32_t dst = dsts[list][s];
         const int32_t row = rows_of[list][s];
+        const bool follows = list == 1 && dst == kTeamDst;     // the team's result goes where its first item says
+        if (follows) {
+          const int64_t head_slot = s / kChunksPerGroup * kChunksPerGroup;
+          dst = dsts[1][head_slot];
+          if (s == head_slot || dst == kTeamDst || dst == INT32_MIN || rows_of[1][head_slot] != row || hi == lo) { err = "bad team"; return ARROW_EINTERNAL; }
+        } else if (list == 1 && s % kChunksPerGroup != 0 && s + 1 < cnts[1] && (s + 1) % kChunksPerGroup != 0 && dsts[1][s + 1] == kTeamDst) {
+          err = "bad team"; return ARROW_EINTERNAL;
+        }
         if (dst == INT32_MIN) { if (hi != lo || row != -1) { err = "padding slot with entries"; return ARROW_EINTERNAL; } continue; }
         if (row < 0 || row >= n || (dst >= 0 && dst != row)) { err = "item vertex differs from its Y row"; return ARROW_EINTERNAL; }
         double sum = 0.0;
@@ -1116,11 +1177,11 @@ int verify_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, co
         covered += hi - lo;
         if (dst >= 0) {
           if (dst >= n) { err = "Y row out of range"; return ARROW_EINTERNAL; }
-          ++produced[dst]; checksum[dst] += sum;
+          produced[dst] += !follows; checksum[dst] += sum;
         } else {
           const int64_t slot = -1 - (int64_t)dst;
           if (slot >= im.n_partials) { err = "partial slot out of range"; return ARROW_EINTERNAL; }
-          ++slot_writes[slot]; slot_sum[slot] += sum; slot_row[slot] = row;
+          slot_writes[slot] += !follows; slot_sum[slot] += sum; slot_row[slot] = row;
         }
       }
     }

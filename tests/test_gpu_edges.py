@@ -65,3 +65,26 @@ def test_short_work_lists(torch, n, k):
     Yref, B = oracle.spmm(rowptr, colidx, vals, X)
     assert_within(Y.cpu().numpy(), Yref, B)
     op.close()
+
+
+@pytest.mark.parametrize("k", [1, 4, 16, 64, 68, 96, 128, 130, 200, 256])
+def test_rows_shared_by_the_wavefronts_of_a_workgroup(torch, k):
+    """Row lengths around what a lane group, a wavefront, a workgroup and several of them take."""
+    n = 6000
+    length = np.full(n, 3)
+    for i, m in enumerate([0, 1, 16, 17, 48, 49, 255, 256, 257, 258, 511, 1023, 1024, 1025, 2047, 2048, 2049, 4096, 4097, n]):
+        length[7 * i + 5] = m
+    rng = np.random.default_rng(5)
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    colidx = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for m in length]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=15)
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    Xd = torch.from_numpy(X).cuda()
+    for opt in (None, binding.arrow_options_default(chunk_nnz=40), binding.arrow_options_default(window_rows=1024)):
+        op = binding.ArrowSpMM(rowptr, colidx, vals, 500, options=opt)
+        binding.arrow_self_check(op.h)
+        Y = torch.full((n, k), float("nan"), device="cuda")
+        op.spmm(Xd, Y)
+        assert_within(Y.cpu().numpy(), Yref, B)
+        op.close()
