@@ -161,7 +161,7 @@ int arrow_set_workspace(arrow_handle *h, void *dev_ws, size_t bytes);
  * depend on scheduling (no floating-point atomics are used).
  * With profiling off the call only launches kernels on `stream` (no allocation, no memset, no
  * synchronisation), so it may be recorded into a HIP graph by a caller that captures `stream`;
- * the same holds for arrow_spmm_iter (plus one device-to-device copy for odd l) and arrow_sddmm.
+ * the same holds for arrow_spmm_iter (plus at most one device-to-device copy for odd l) and arrow_sddmm.
  * Errors: EINVAL (NULL, k < 1, misaligned; the byte ranges of X and Y overlap each other or the
  * bound workspace, or Y overlaps the device image), ENOTREADY, ETOOSMALL (workspace bound for a
  * smaller k), EHIP.
@@ -191,7 +191,9 @@ int arrow_spmm_static(arrow_handle *h, const float *X, float *Y, int32_t k, void
 
 /*
  * X <- A^l . X, l chained products rounded to fp32 after each one, result left
- * in X (l = 0 leaves X untouched).  Uses the n x k part of the workspace.
+ * in X (l = 0 leaves X untouched).  Uses the n x k part of the workspace.  An odd l ends with a copy
+ * of the result into X; for l >= 3 a workspace with n * k * 4 bytes more (rounded up to 256) than
+ * arrow_workspace_bytes(h, k) saves it.
  * Errors as arrow_spmm, plus EINVAL for l < 0.
  */
 int arrow_spmm_iter(arrow_handle *h, float *X, int32_t k, int32_t l, void *stream);

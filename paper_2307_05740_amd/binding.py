@@ -367,6 +367,14 @@ def arrow_destroy(h: int) -> None:
     lib().arrow_destroy(h)
 
 
+def _current_stream(torch, device) -> int:
+    """The current stream of `device` as an address, without building a stream object where torch allows it."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None and device.index is not None:
+        return raw(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
+
+
 class ArrowSpMM:
     """One decomposed operand bound to torch-owned device memory (plumbing only)."""
 
@@ -388,7 +396,7 @@ class ArrowSpMM:
             arrow_upload(self.h, self._image.data_ptr(), self._image.numel(), self._stream())
             torch.cuda.current_stream().synchronize()
         self._ws = None
-        self._ws_k = 0
+        self._ws_k = self._ws_second_k = 0
         self._map = None
 
     def repack(self, options: arrow_options_t | None) -> None:
@@ -398,16 +406,26 @@ class ArrowSpMM:
         self._bind_image()
 
     def _stream(self) -> int:
-        return self._torch.cuda.current_stream(self.device).cuda_stream
+        return _current_stream(self._torch, self.device)
 
-    def _ensure_workspace(self, k: int) -> None:
-        if self._ws is not None and self._ws_k >= k:
+    def _ensure_workspace(self, k: int, second: bool = False) -> None:
+        """Bind a workspace for k columns; `second`: with room for another n x k buffer, if there is memory for it."""
+        if self._ws is not None and self._ws_k >= k and (not second or self._ws_second_k >= k):
             return
         torch = self._torch
         torch.cuda.current_stream(self.device).synchronize()
-        nbytes = arrow_workspace_bytes(self.h, k)
-        self._ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=self.device)
+        k = max(k, self._ws_k)
+        nbytes = max(arrow_workspace_bytes(self.h, k), 256)
+        extra = -(-self.n * k * 4 // 256) * 256 if second or self._ws_second_k else 0
+        self._ws = None
+        try:
+            self._ws = torch.empty(nbytes + extra, dtype=torch.uint8, device=self.device)
+        except torch.OutOfMemoryError:
+            if not extra:
+                raise
+            self._ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self._ws_k = k
+        self._ws_second_k = k if extra else 0     # asked for, whether or not there was room
         arrow_set_workspace(self.h, self._ws.data_ptr(), self._ws.numel())
 
     def levels(self):
@@ -429,7 +447,7 @@ class ArrowSpMM:
         torch = self._torch
         assert X.is_cuda and X.dtype == torch.float32 and X.dim() == 2 and X.is_contiguous()
         assert X.shape[0] == self.n
-        self._ensure_workspace(X.shape[1])
+        self._ensure_workspace(X.shape[1], second=l >= 3 and l % 2 == 1)
         arrow_spmm_iter(self.h, X.data_ptr(), X.shape[1], l, self._stream())
         return X
 
@@ -556,7 +574,7 @@ class Csf3Mttkrp:
         self._ws_R = 0
 
     def _stream(self) -> int:
-        return self._torch.cuda.current_stream(self.device).cuda_stream
+        return _current_stream(self._torch, self.device)
 
     def mttkrp(self, B, C, A=None):
         torch = self._torch

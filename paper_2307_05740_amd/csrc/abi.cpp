@@ -568,15 +568,20 @@ int arrow_spmm_iter(arrow_handle* h, float* X, int32_t k, int32_t l, void* strea
     return fail(ARROW_EINVAL, "X must not overlap the workspace or the device image");
   if (l == 0) return ARROW_OK;
   h->spans_used = 0;
+  const size_t xy = align_up((size_t)h->n * (size_t)k * sizeof(float));
   float* tmp = reinterpret_cast<float*>(h->ws + scratch_bytes(h, k));
+  // An odd number of products ends in the buffer it did not start from.  With room for a second n x k
+  // buffer in the workspace the last three go X -> tmp -> tmp2 -> X; else the result is copied back.
+  float* tmp2 = l >= 3 && l % 2 == 1 && h->ws_bytes >= scratch_bytes(h, k) + 2 * xy
+                    ? reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(tmp) + xy) : nullptr;
   float* src = X;
-  float* dst = tmp;
   for (int32_t t = 0; t < l; ++t) {
+    float* dst = tmp2 && t == l - 2 ? tmp2 : (src == X ? tmp : X);
     rc = product(h, src, dst, k, (hipStream_t)stream, h->ws, true);
     if (rc) return rc;
-    float* s = src; src = dst; dst = s;
+    src = dst;
   }
-  if (src != X) {   // odd l: the last product landed in the workspace
+  if (src != X) {
     hipError_t e = hipMemcpyAsync(X, src, (size_t)h->n * (size_t)k * sizeof(float),
                                   hipMemcpyDeviceToDevice, (hipStream_t)stream);
     if (e != hipSuccess) return check_hip((int)e, "copy of the last iterate");

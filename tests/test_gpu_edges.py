@@ -88,3 +88,21 @@ def test_rows_shared_by_the_wavefronts_of_a_workgroup(torch, k):
         op.spmm(Xd, Y)
         assert_within(Y.cpu().numpy(), Yref, B)
         op.close()
+
+
+@pytest.mark.parametrize("l", [1, 2, 3, 4, 5, 7])
+@pytest.mark.parametrize("room", [False, True])
+def test_chained_products_with_and_without_a_second_buffer(torch, l, room):
+    w = synth.make_config(0, 3)
+    op = binding.ArrowSpMM(*csr_of(w), w.b)
+    X = synth.normal_matrix(w.n, 7, seed=16)
+    Xl = X.copy()
+    for _ in range(l):
+        Xl = op.spmm(torch.from_numpy(Xl).cuda()).cpu().numpy()
+    Xd = torch.from_numpy(X).cuda()
+    nbytes = binding.arrow_workspace_bytes(op.h, 7) + (-(-w.n * 7 * 4 // 256) * 256 if room else 0)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    binding.arrow_set_workspace(op.h, ws.data_ptr(), nbytes)
+    binding.arrow_spmm_iter(op.h, Xd.data_ptr(), 7, l, torch.cuda.current_stream().cuda_stream)
+    assert np.array_equal(Xd.cpu().numpy().view(np.uint32), Xl.view(np.uint32))
+    op.close()
