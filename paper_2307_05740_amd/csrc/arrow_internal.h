@@ -257,7 +257,7 @@ int launch_sddmm_corner(const uint32_t* tiles, int64_t n_tiles, const int32_t* c
 // max_span = widest window of the tiles (sizes the LDS allocation and the column slice)
 int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, const uint32_t* wrow_ptr,
                   const uint32_t* wrow_mid, const int32_t* wrow_y, const Entry* entries,
-                  const int32_t* perm, const float* X, float* Y, int32_t k, bool accumulate,
+                  const int32_t* perm, const float* X, int64_t x_rows, float* Y, int32_t k, bool accumulate,
                   void* stream);
 
 

@@ -128,16 +128,15 @@ template <> __device__ __forceinline__ float4 vload_stream<4>(const float* p) {
 // col_bytes the lane's byte offset inside a row, row_bytes = 4 k.
 // SMALL: the matrix has at most 2^24 rows and 2^32 bytes, so the byte offset is one 24-bit
 // multiply-add and the load can use (uniform base + 32-bit lane offset) addressing.
+template <bool SMALL>
+__device__ __forceinline__ auto row_offset(int32_t row, uint32_t row_bytes, uint32_t col_bytes) {
+  if constexpr (SMALL) return __umul24((uint32_t)row, row_bytes) + col_bytes;
+  else return (uint64_t)(uint32_t)row * row_bytes + col_bytes;
+}
 template <int VEC, bool SMALL>
 __device__ __forceinline__ typename Vec<VEC>::type load_row(const char* base, int32_t row,
                                                             uint32_t row_bytes, uint32_t col_bytes) {
-  if (SMALL) {
-    const uint32_t off = __umul24((uint32_t)row, row_bytes) + col_bytes;
-    return gload<VEC>(reinterpret_cast<const float*>(base + off));
-  } else {
-    const uint64_t off = (uint64_t)(uint32_t)row * row_bytes + col_bytes;
-    return gload<VEC>(reinterpret_cast<const float*>(base + off));
-  }
+  return gload<VEC>(reinterpret_cast<const float*>(base + row_offset<SMALL>(row, row_bytes, col_bytes)));
 }
 
 __device__ __forceinline__ void strip_sync() {

@@ -298,77 +298,180 @@ __global__ __launch_bounds__(kBlock) void chunks_kernel(const ProductArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// window kernel: one workgroup per tile of a diagonal block.  The tile's window of P_i X
-// (win_count consecutive positions of the level, one column slice of width LPR * VEC) is
-// gathered through perm into LDS once -- the permutation gather of these rows happens here --
-// and every diagonal-block entry of the tile's rows then reads its X row from LDS; the rows'
-// first-block-column entries read X_0 rows from memory.  One lane group per row.
+// window kernel: one workgroup per tile of a diagonal block and column slice.  The tile's window of
+// P_i X (win_count consecutive positions of the level, `width` columns) is gathered through perm into
+// LDS once -- the permutation gather of these rows happens here -- and every diagonal-block entry of
+// the tile's rows then reads its X row from LDS; the rows' other entries (first block column, other
+// blocks once levels are fused) read rows of X from memory.
+//
+// Sixteen lanes own a row of Y, whatever the number of columns (VEC = 4, 2 or 1 of them per lane), so
+// that they are one DPP row: the lanes load sixteen entries at a time, one each, and an entry reaches
+// all of them as an operand modifier of the address addition and the multiply-adds (row_newbcast).
+// An entry costs five vector instructions and one LDS read for four rows of Y.  The next row's
+// entries are on their way while the current one is worked on.  With the entries read four at a time
+// by every lane and windows of 64 KiB in slices of 32 columns, two memory latencies stood before
+// every fourth entry; 512 blocks of 512 with 48 entries per row, k = 128: 250 -> 143 us, of which the
+// LDS reads (6.4 GB at 128 B per cycle and compute unit) take two thirds.
 // ---------------------------------------------------------------------------
 constexpr int kWinBlock = 1024;   // threads of a window-kernel workgroup: 16 wavefronts share one staged window
+constexpr int kWinLanes = 16;
+constexpr int kWinFloats = 38400; // LDS floats of a window: 150 KiB, one workgroup per compute unit
 
-template <int VEC, int LPR>
+template <int U>
+__device__ __forceinline__ int row16_bcast(int v) {   // lane U's value in every lane of its sixteen
+  return __builtin_amdgcn_update_dpp(0, v, 0x150 + U, 0xf, 0xf, false);
+}
+// acc += (lane U's v) * x, the broadcast being an operand modifier of the multiply-add itself
+template <int U> __device__ __forceinline__ void fma_bcast(float& acc, float v, float x) {
+  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(v), "v"(x), "n"(U));
+}
+template <int U> __device__ __forceinline__ void vfma_bcast(float& a, float v, float x) { fma_bcast<U>(a, v, x); }
+template <int U> __device__ __forceinline__ void vfma_bcast(float2& a, float v, float2 x) {
+  fma_bcast<U>(a.x, v, x.x); fma_bcast<U>(a.y, v, x.y);
+}
+template <int U> __device__ __forceinline__ void vfma_bcast(float4& a, float v, float4 x) {
+  fma_bcast<U>(a.x, v, x.x); fma_bcast<U>(a.y, v, x.y); fma_bcast<U>(a.z, v, x.z); fma_bcast<U>(a.w, v, x.w);
+}
+
+template <int VEC, bool SMALL>
 __global__ __launch_bounds__(kWinBlock) void window_kernel(
-    const WindowTile* __restrict__ tiles, const uint32_t* __restrict__ wrow_ptr,
+    const WindowTile* __restrict__ tiles, int64_t n_tiles, const uint32_t* __restrict__ wrow_ptr,
     const uint32_t* __restrict__ wrow_mid, const int32_t* __restrict__ wrow_y,
     const Entry* __restrict__ ent, const int32_t* __restrict__ perm, const float* __restrict__ X,
-    float* __restrict__ Y, int k, int width, int accumulate) {
+    float* __restrict__ Y, int k, int width, int slices, int accumulate) {
   using V = typename Vec<VEC>::type;
-  constexpr int GPB = kWinBlock / LPR;
-  constexpr int W = LPR * VEC;                       // columns per slice = LDS row length
-  extern __shared__ float win[];                     // win_count x W floats
-  const WindowTile t = tiles[blockIdx.x];
-  const int l = threadIdx.x % LPR;
-  const int grp = threadIdx.x / LPR;
-  const LaneColumns lc = lane_columns<VEC>(l, blockIdx.y * width, k, width);   // lane l's columns sit at [l * VEC] of an LDS row
-  const int c = lc.c;
-  const bool col_ok = lc.ok;
-  const float* Xc = X + (col_ok ? c : 0);
-  // stage: lane group j loads window rows j, j + GPB, ... four at a time
-  for (uint32_t i0 = grp; i0 < t.win_count; i0 += 4 * GPB) {
-    int32_t src[4];
-    V v[4];
+  constexpr uint32_t GPB = kWinBlock / kWinLanes;
+  constexpr int QB = 4;                              // batches of sixteen window entries a row has on their way
+  constexpr uint32_t NO = 4;                         // entries outside the window loaded ahead
+  __shared__ __attribute__((aligned(16))) float win[kWinFloats];
+  // the slices of a tile follow each other on one die: its entries are read from memory once
+  const int64_t id = blockIdx.x;
+  const int64_t tile = id / (kDies * slices) * kDies + id % kDies;
+  const int slice = (int)(id / kDies % slices);
+  if (tile >= n_tiles) return;
+  const WindowTile t = tiles[tile];
+  const uint32_t l = threadIdx.x % kWinLanes;
+  const uint32_t grp = threadIdx.x / kWinLanes;
+  const LaneColumns lc = lane_columns<VEC>((int)l, slice * width, k, width);   // lane l's columns sit at [l * VEC] of an LDS row
+  const uint32_t row_bytes = 4u * (uint32_t)k;
+  const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
+  const char* Xb = reinterpret_cast<const char*>(X);
+  const bool has_lds = (int)l * VEC < width;         // lanes beyond the slice own no part of an LDS row
+  // everything of the tile is addressed relative to its first row and first entry: 32-bit offsets
+  const uint32_t n_rows = t.row_end - t.row_begin;
+  const uint32_t* __restrict__ t_ptr = wrow_ptr + t.row_begin;
+  const uint32_t* __restrict__ t_mid = wrow_mid + t.row_begin;
+  const int32_t* __restrict__ t_y = wrow_y + t.row_begin;
+  const uint32_t e0 = t_ptr[0];
+  const Entry* __restrict__ t_ent = ent + e0;
+  struct Row { uint32_t lo, mid, hi; int32_t y; };
+  auto describe = [&](uint32_t i) {
+    Row r{0, 0, 0, 0};
+    if (i < n_rows) { r.lo = t_ptr[i] - e0; r.mid = t_mid[i] - e0; r.hi = t_ptr[i + 1] - e0; r.y = t_y[i]; }
+    return r;
+  };
+  auto fetch = [&](const Row& r, Entry& out, Entry (&e)[QB]) {
+    if (l < r.mid - r.lo) out = t_ent[r.lo + l];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (uint32_t q = 0; q < QB; ++q)
+      if (r.mid + l + q * kWinLanes < r.hi) e[q] = t_ent[r.mid + l + q * kWinLanes];
+  };
+  Row r = describe(grp), r_n = describe(grp + GPB);
+  // stage: lane group j loads window rows j, j + GPB, ... eight at a time
+  for (uint32_t i0 = grp; i0 < t.win_count; i0 += 8 * GPB) {
+    int32_t src[8];
+    V v[8];
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u) {
       const uint32_t i = i0 + u * GPB;
       src[u] = i < t.win_count ? perm[t.win_begin + i] : -1;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      v[u] = (src[u] >= 0 && col_ok) ? gload<VEC>(Xc + (size_t)src[u] * (size_t)k) : vzero<VEC>();
+    for (uint32_t u = 0; u < 8; ++u)
+      v[u] = (src[u] >= 0 && lc.ok) ? load_row<VEC, SMALL>(Xb, src[u], row_bytes, col_bytes) : vzero<VEC>();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (uint32_t u = 0; u < 8; ++u) {
       const uint32_t i = i0 + u * GPB;
-      if (i < t.win_count) vstore<VEC>(win + (size_t)i * W + l * VEC, v[u]);
+      if (i < t.win_count && has_lds) vstore<VEC>(win + i * width + l * VEC, v[u]);
     }
   }
+  Entry o{0, 0.f}, o_n{0, 0.f}, e[QB] = {}, e_n[QB] = {};
+  fetch(r, o, e);
   __syncthreads();
-  for (uint32_t wr = t.row_begin + grp; wr < t.row_end; wr += GPB) {
-    const uint32_t lo = wrow_ptr[wr], mid = wrow_mid[wr], hi = wrow_ptr[wr + 1];
-    V acc = vzero<VEC>();
-    for (uint32_t j = lo; j < mid; j += 4) {         // first block column: X_0 rows from memory
-      Entry e[4];
-      V x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) e[u] = ent[j + u < mid ? j + u : lo];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        x[u] = (j + u < mid) ? gload<VEC>(Xc + (size_t)e[u].xrow * (size_t)k) : vzero<VEC>();
-#pragma unroll
-      for (int u = 0; u < 4; ++u) vfma(acc, (j + u < mid) ? e[u].val : 0.f, x[u]);
+  const char* lane_win = reinterpret_cast<const char*>(win) + (has_lds ? l * VEC * 4 : 0);
+  const int row_step = width * 4;
+  V acc;
+  // sixteen window entries, one per lane (`n` of them there)
+  auto batch = [&](const Entry& mine, uint32_t n) {
+    int off = l < n ? mine.xrow * row_step : 0;
+    float val = l < n ? mine.val : 0.f;
+    // a value read through the row_newbcast modifier must not have been written by the two
+    // instructions before
+    asm("s_nop 1" : "+v"(off), "+v"(val));
+    V x[8], x2[8];                                   // all reads on their way before the first is used
+#define ARROW_READ(U) vload<VEC>(reinterpret_cast<const float*>(lane_win + row16_bcast<U>(off)))
+    x[0] = ARROW_READ(0); x[1] = ARROW_READ(1); x[2] = ARROW_READ(2); x[3] = ARROW_READ(3);
+    x[4] = ARROW_READ(4); x[5] = ARROW_READ(5); x[6] = ARROW_READ(6); x[7] = ARROW_READ(7);
+    if (n > 8) {
+      x2[0] = ARROW_READ(8); x2[1] = ARROW_READ(9); x2[2] = ARROW_READ(10); x2[3] = ARROW_READ(11);
+      x2[4] = ARROW_READ(12); x2[5] = ARROW_READ(13); x2[6] = ARROW_READ(14); x2[7] = ARROW_READ(15);
     }
-    for (uint32_t j = mid; j < hi; j += 4) {         // diagonal block: rows of the LDS window
-      Entry e[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) e[u] = ent[j + u < hi ? j + u : mid];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (j + u < hi) vfma(acc, e[u].val, vload<VEC>(win + (size_t)e[u].xrow * W + l * VEC));
+#undef ARROW_READ
+#define ARROW_STEP(U) vfma_bcast<U>(acc, val, U < 8 ? x[U % 8] : x2[U % 8]);
+    ARROW_STEP(0) ARROW_STEP(1) ARROW_STEP(2) ARROW_STEP(3) ARROW_STEP(4) ARROW_STEP(5) ARROW_STEP(6) ARROW_STEP(7)
+    if (n > 8) {
+      ARROW_STEP(8) ARROW_STEP(9) ARROW_STEP(10) ARROW_STEP(11) ARROW_STEP(12) ARROW_STEP(13) ARROW_STEP(14) ARROW_STEP(15)
     }
-    if (col_ok) {
-      float* y = Y + (size_t)wrow_y[wr] * (size_t)k + c;
+#undef ARROW_STEP
+  };
+  for (uint32_t i = grp; i < n_rows; i += GPB) {
+    const Row r_nn = describe(i + 2 * GPB);
+    fetch(r_n, o_n, e_n);
+    acc = vzero<VEC>();
+    // the first entries outside the window: their rows of X arrive while the window entries are summed
+    const uint32_t n_out = r.mid - r.lo;
+    V xo[NO];
+#define ARROW_OUT(O)                                                                    \
+    {                                                                                   \
+      const int xrow = row16_bcast<O>(o.xrow);                                          \
+      xo[O] = vzero<VEC>();                                                             \
+      if (O < n_out) xo[O] = load_row<VEC, SMALL>(Xb, xrow, row_bytes, col_bytes);      \
+    }
+    if (n_out > 0) { ARROW_OUT(0) ARROW_OUT(1) ARROW_OUT(2) ARROW_OUT(3) }
+#undef ARROW_OUT
+    const uint32_t n_win = r.hi - r.mid;
+#pragma unroll
+    for (uint32_t q = 0; q < QB; ++q)
+      if (q * kWinLanes < n_win) batch(e[q], n_win - q * kWinLanes);
+    for (uint32_t at = QB * kWinLanes; at < n_win; at += kWinLanes) {           // rows of more than 64 window entries
+      Entry m{0, 0.f};
+      if (at + l < n_win) m = t_ent[r.mid + at + l];
+      batch(m, n_win - at);
+    }
+    if (n_out > 0) {
+      const float vo = l < n_out ? o.val : 0.f;
+#define ARROW_OUT(O) vfma(acc, __int_as_float(row16_bcast<O>(__float_as_int(vo))), xo[O]);
+      ARROW_OUT(0) ARROW_OUT(1) ARROW_OUT(2) ARROW_OUT(3)
+#undef ARROW_OUT
+      for (uint32_t j = r.lo + NO; j < r.mid; j += 4) {                         // further entries outside the window
+        Entry m[4];
+        V x[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) m[u] = t_ent[j + u < r.mid ? j + u : j];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) x[u] = j + u < r.mid ? load_row<VEC, SMALL>(Xb, m[u].xrow, row_bytes, col_bytes) : vzero<VEC>();
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) vfma(acc, j + u < r.mid ? m[u].val : 0.f, x[u]);
+      }
+    }
+    if (lc.ok) {
+      float* y = reinterpret_cast<float*>(reinterpret_cast<char*>(Y) + row_offset<SMALL>(r.y, row_bytes, col_bytes));
       if (accumulate) vadd(acc, vload_stream<VEC>(y));
       vstore_stream<VEC>(y, acc);
     }
+    r = r_n; r_n = r_nn; o = o_n;
+#pragma unroll
+    for (int q = 0; q < QB; ++q) e[q] = e_n[q];
   }
 }
 
@@ -1131,25 +1234,35 @@ int launch_gather(const int32_t* perm, int64_t n_i, const float* X, float* Xp, i
 
 int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, const uint32_t* wrow_ptr,
                   const uint32_t* wrow_mid, const int32_t* wrow_y, const Entry* entries,
-                  const int32_t* perm, const float* X, float* Y, int32_t k, bool accumulate,
+                  const int32_t* perm, const float* X, int64_t x_rows, float* Y, int32_t k, bool accumulate,
                   void* stream) {
   if (n_tiles <= 0) return 0;
-  // widest column slice whose window still fits the 64 KiB of LDS a workgroup may use
-  const int64_t lds_budget = 64 * 1024;
-  int kc = 256;
-  while (kc > 1 && max_span * kc * 4 > lds_budget) kc >>= 1;
-  if (max_span * kc * 4 > lds_budget) return (int)hipErrorInvalidValue;
-  const Shape s = pick_output_shape(k, kc, accumulate);
-  if (max_span * (int64_t)(s.lpr * s.vec) * 4 > lds_budget) return (int)hipErrorInvalidValue;
-  return dispatch_shape(s, [&](auto V, auto L) -> int {
-    constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
-    if (n_tiles > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-    dim3 grid((unsigned)n_tiles, (unsigned)s.slices);
-    const size_t lds = (size_t)max_span * LPR * VEC * sizeof(float);
-    hipLaunchKernelGGL((window_kernel<VEC, LPR>), grid, dim3(kWinBlock), lds, (hipStream_t)stream, tiles,
-                       wrow_ptr, wrow_mid, wrow_y, entries, perm, X, Y, (int)k, s.width, accumulate ? 1 : 0);
-    return (int)hipGetLastError();
-  });
+  // the widest slice whose window fits: 64, 32 or 16 columns (4, 2 or 1 per lane), 8 for the widest
+  // spans; no wider than k needs
+  int vec = 4, most = 64;
+  while (vec > 1 && (k <= most / 2 || max_span * most > kWinFloats)) { vec >>= 1; most >>= 1; }
+  if (max_span * most > kWinFloats) most = 8;
+  if (max_span * most > kWinFloats) return (int)hipErrorInvalidValue;
+  // a slice that adds to Y must not reach back into the one before it (see pick_shape)
+  int slices = (int)ceil_div(k, most);
+  int width = (int)ceil_div(ceil_div(k, slices), vec) * vec;
+  if (accumulate && slices > 1 && k - (slices - 1) * width < vec) {
+    vec = 1;
+    if (most > 16) most = 16;
+    slices = (int)ceil_div(k, most);
+    width = (int)ceil_div(k, slices);
+  }
+  const int64_t blocks = ceil_div(n_tiles, kDies) * kDies * slices;
+  if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
+  const bool small = small_matrix(x_rows, k);
+#define ARROW_LAUNCH(VEC, SM)                                                                              \
+  hipLaunchKernelGGL((window_kernel<VEC, SM>), dim3((unsigned)blocks), dim3(kWinBlock), 0, (hipStream_t)stream, tiles, \
+                     n_tiles, wrow_ptr, wrow_mid, wrow_y, entries, perm, X, Y, (int)k, width, slices, accumulate ? 1 : 0)
+  if (vec == 4) { if (small) ARROW_LAUNCH(4, true); else ARROW_LAUNCH(4, false); }
+  else if (vec == 2) { if (small) ARROW_LAUNCH(2, true); else ARROW_LAUNCH(2, false); }
+  else { if (small) ARROW_LAUNCH(1, true); else ARROW_LAUNCH(1, false); }
+#undef ARROW_LAUNCH
+  return (int)hipGetLastError();
 }
 
 namespace {

@@ -106,3 +106,35 @@ def test_chained_products_with_and_without_a_second_buffer(torch, l, room):
     binding.arrow_spmm_iter(op.h, Xd.data_ptr(), 7, l, torch.cuda.current_stream().cuda_stream)
     assert np.array_equal(Xd.cpu().numpy().view(np.uint32), Xl.view(np.uint32))
     op.close()
+
+
+@pytest.mark.parametrize("k", [1, 5, 8, 16, 20, 33, 64, 65, 130])
+@pytest.mark.parametrize("span", [96, 700, 2500, 4096])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_lds_windows(torch, k, span, fuse):
+    """Windows from narrow to the widest allowed, rows of 0 to 100 entries inside them and 0 to 7 outside."""
+    b, blocks = 4096, 3
+    n = b * blocks
+    rng = np.random.default_rng(span)
+    rows, cols = [], []
+    for i in range(b, n):
+        m = int(rng.integers(0, 101)) if i % 50 else 0
+        lo = min(max(i - span // 2, i // b * b), (i // b + 1) * b - span)
+        c = np.union1d(lo + rng.choice(span, min(m, span), replace=False), rng.choice(b, int(rng.integers(0, 8)), replace=False))
+        rows.append(np.full(len(c), i))
+        cols.append(c)
+    rows, cols = np.concatenate(rows), np.concatenate(cols)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int64)
+    vals = rng.uniform(-1, 1, len(cols)).astype(np.float32)
+    opt = binding.arrow_options_default(window_span=4096, window_tile_rows=500, window_level_share=0.0, fuse_levels=fuse,
+                                        bfs_tail=0, separators=0)
+    opt.window_reuse = 0.5
+    op = binding.ArrowSpMM(rowptr, cols.astype(np.int32), vals, b, options=opt)
+    binding.arrow_self_check(op.h)
+    assert sum(L["nnz_window"] for L in op.levels()) > 0
+    X = synth.normal_matrix(n, k, seed=17)
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    Yref, B = oracle.spmm(rowptr, cols.astype(np.int32), vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
+    op.close()
