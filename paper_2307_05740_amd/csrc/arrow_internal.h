@@ -286,8 +286,7 @@ int launch_probe_gather(const float* X, int64_t x_rows, int32_t k, int64_t regio
                         int from_lds, int64_t gathers, float* out, void* stream);
 
 // Order-3 MTTKRP over the compressed-sparse-fibre image (mttkrp.hip): one wavefront per item.
-// b_rows, c_rows = rows of the factor matrices (they decide whether 32-bit offsets are enough);
-// mean_segment = entries per segment on average (it picks how many row loads a round issues).
+// b_rows, c_rows = rows of the factor matrices (they decide whether 32-bit offsets are enough).
 // Limits of one work item of the fibre image: the wavefront that owns the item stages its entries
 // and segment descriptors in LDS, so both are bounded.
 constexpr int kCsfSegMax = 64;      // most entries of a segment
@@ -298,6 +297,6 @@ int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int3
                   const uint32_t* seg_ptr,
                   const int32_t* seg_j, const Entry* entries, int64_t n_items, const float* B,
                   int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials, int32_t R,
-                  double mean_segment, void* stream);
+                  void* stream);
 
 }  // namespace arrow

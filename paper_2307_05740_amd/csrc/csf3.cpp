@@ -2,7 +2,7 @@
 // The arithmetic of a product happens in the HIP kernels this file launches (mttkrp.hip and the
 // shared partial-vector reduction); nothing here falls back to the CPU.
 //
-// Image: the entries sorted by (i, j, k) as {k, value} pairs; SEGMENTS, runs of at most
+// Image: the entries as {k, value} pairs, by slice i; SEGMENTS, runs of at most
 // kSegMax entries of one fibre (i, j) with the fibre's j (a long fibre is cut: the product with
 // B(j, :) distributes over the pieces); ITEMS, runs of consecutive segments of one slice i with at
 // most kItemNnz entries and kItemSegs segments, one per wavefront, with a destination: row i of A when the slice is one
@@ -16,8 +16,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "arrow.h"
@@ -158,6 +160,34 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
       }
     }
     item_seg.push_back((uint32_t)h->n_seg);
+    // inside every item the segments are ordered by length, longest first (equal ones by j), so that the
+    // lane groups of the wavefront that owns it work on equally long ones; the entries move along
+    std::vector<uint32_t> from((size_t)h->n_seg);            // segment -> first entry in (i, j, k) order
+    {
+      const int64_t n_it = (int64_t)item_dst.size();
+#pragma omp parallel
+      {
+        std::vector<std::pair<uint32_t, int32_t>> segs;       // (first entry, j), in the new order
+        std::vector<uint32_t> len, at_len(kSegMax + 2);
+#pragma omp for schedule(static)
+        for (int64_t it = 0; it < n_it; ++it) {
+          const uint32_t s0 = item_seg[it], s1 = item_seg[it + 1], n_s = s1 - s0;
+          if (n_s == 0) continue;
+          len.resize(n_s); segs.resize(n_s);
+          std::fill(at_len.begin(), at_len.end(), 0u);
+          for (uint32_t q = 0; q < n_s; ++q) { len[q] = seg_ptr[s0 + q + 1] - seg_ptr[s0 + q]; ++at_len[(size_t)(kSegMax - len[q]) + 1]; }
+          for (size_t q = 1; q < at_len.size(); ++q) at_len[q] += at_len[q - 1];
+          uint32_t first = seg_ptr[s0];
+          for (uint32_t q = 0; q < n_s; ++q) segs[at_len[(size_t)(kSegMax - len[q])]++] = {seg_ptr[s0 + q], seg_j[s0 + q]};
+          std::sort(len.begin(), len.end(), std::greater<uint32_t>());
+          for (uint32_t q = 0; q < n_s; ++q) {
+            from[s0 + q] = segs[q].first; seg_j[s0 + q] = segs[q].second;
+            if (q) seg_ptr[s0 + q] = first;                   // the item's entry range stays where it is
+            first += len[q];
+          }
+        }
+      }
+    }
     // the kernel stages an item in fixed-size LDS arrays: make sure no item exceeds them
     for (size_t t = 0; t + 1 < item_seg.size(); ++t) {
       const int64_t segs = (int64_t)item_seg[t + 1] - (int64_t)item_seg[t];
@@ -200,11 +230,12 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
     if (!split_y.empty()) std::memcpy(base + h->off_split_y, split_y.data(), sizeof(int32_t) * split_y.size());
     arrow::Entry* ent = reinterpret_cast<arrow::Entry*>(base + h->off_entries);
 #pragma omp parallel for schedule(static)
-    for (int64_t p = 0; p < nnz; ++p) {
-      const int64_t q = at(p);
-      ent[p].xrow = tk[q];
-      ent[p].val = tv[q];
-    }
+    for (int64_t sg = 0; sg < h->n_seg; ++sg)
+      for (uint32_t e = seg_ptr[sg], p = from[sg]; e < seg_ptr[sg + 1]; ++e, ++p) {
+        const int64_t q = at(p);
+        ent[e].xrow = tk[q];
+        ent[e].val = tv[q];
+      }
     h->build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     *out = h;
     return ARROW_OK;
@@ -262,8 +293,7 @@ int csf3_mttkrp(csf3_handle* h, const float* B, const float* C, float* A, int32_
                                 reinterpret_cast<const uint32_t*>(at(h->off_seg_ptr)),
                                 reinterpret_cast<const int32_t*>(at(h->off_seg_j)),
                                 reinterpret_cast<const arrow::Entry*>(at(h->off_entries)), h->n_items, B,
-                                h->J, C, h->K, A, partials, R,
-                                h->n_seg ? (double)h->nnz / (double)h->n_seg : 0.0, stream);
+                                h->J, C, h->K, A, partials, R, stream);
   if (rc) return fail3(ARROW_EHIP, "mttkrp kernel launch: %s", hipGetErrorString((hipError_t)rc));
   if (prof) (void)hipEventRecord(h->ev[1], (hipStream_t)stream);
   rc = arrow::launch_reduce(reinterpret_cast<const uint32_t*>(at(h->off_split_ptr)),

@@ -10,16 +10,28 @@
 // columns, a wavefront holds G = 64 / LPR lane groups.  One wavefront per work item (a run of
 // segments of one slice i, at most kCsfItemNnz entries and kCsfItemSegs segments, each segment
 // being at most 64 entries of one fibre).  The wavefront first copies the item's entries and
-// segment descriptors into LDS with coalesced loads; its lane groups then take the segments
-// round-robin and read offsets, j and entries from there, so that the only memory latency inside
-// the loop is that of the gathered rows (the row of B and up to U rows of C at a time; working on
-// two to four segments at once was measured and is no faster).  At the end the lane groups are combined with wavefront shuffles and the
-// result goes to row i of A or, for a slice cut into several items, to a partial vector that the
-// reduction kernel sums in a fixed order.  No atomics.
+// segment descriptors into LDS with coalesced loads and reads them from there, so that the only
+// memory latency inside the loop is that of the gathered rows.
+//
+// The build sorts an item's segments by length, longest first, so the segments that the lane groups
+// take side by side are equally long nearly everywhere: such a round needs no masks and no load slot
+// stays unused.  Short segments are taken two or four per lane group at a time, which keeps four
+// to eight row loads in flight whatever their length (more of them cost registers: six wavefronts per
+// SIMD instead of eight is 12 % slower).  In the order of j a round lasted as long as the
+// longest of G random lengths, and with the masks 16 vector instructions stood for every row load, of
+// which 5 do the work: the kernel was bound by instruction issue (83 % of the cycles).  Uniform 4096^3
+// tensor, 68.7 M entries in 16.5 M fibres, R = 64: 1078 -> 855 us; what it gathers (21.8 GB from the L2 at
+// 64 B per cycle and compute unit) takes 630 us.  Skewed tensor, fibres of one entry, R = 32: 497 -> 495 us,
+// bound by the rows of B and C (8 MB each) that miss the L2.
+//
+// At the end the lane groups are combined with wavefront shuffles and the result goes to row i of A
+// or, for a slice cut into several items, to a partial vector that the reduction kernel sums in a
+// fixed order.  No atomics.
 #include <hip/hip_runtime.h>
 
 #include <climits>
 #include <cstdint>
+#include <type_traits>
 
 #include "arrow_internal.h"
 #include "kernel_common.h"
@@ -35,70 +47,159 @@ __device__ __forceinline__ void vmuladd(float4& a, float4 x, float4 b) {
   a.x = fmaf(x.x, b.x, a.x); a.y = fmaf(x.y, b.y, a.y); a.z = fmaf(x.z, b.z, a.z); a.w = fmaf(x.w, b.w, a.w);
 }
 
-template <int VEC, int LPR, int U, bool SMALL_B, bool SMALL_C>
-__global__ __launch_bounds__(kBlock) void mttkrp_kernel(
+// The staged item and what a lane needs to load rows of the factors.
+struct ItemView {
+  const Entry* ent;
+  const uint16_t* ptr;      // segment offsets relative to the item's first entry
+  const int32_t* j;
+  const char* B;
+  const char* C;
+  uint32_t row_bytes, col_bytes;
+};
+
+// Segments s0 + p * G + g, p < P, of at most U entries each (P = 1: any number, U at a time);
+// ALIKE: all of them exist and hold `len` entries.
+template <int VEC, int LPR, int P, int U, bool SMALL, bool ALIKE>
+__device__ __forceinline__ void segments(const ItemView& v, uint32_t s0, uint32_t n_seg, uint32_t len, uint32_t g,
+                                         typename Vec<VEC>::type& acc) {
+  using V = typename Vec<VEC>::type;
+  constexpr uint32_t G = 64 / LPR;
+  uint32_t lo[P], n[P];
+  V b[P], x[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const uint32_t s = s0 + p * G + g;
+    const bool there = ALIKE || s < n_seg;
+    lo[p] = there ? (uint32_t)v.ptr[s] : 0u;
+    n[p] = ALIKE ? len : (there ? (uint32_t)v.ptr[s + 1] - lo[p] : 0u);
+    b[p] = x[p] = vzero<VEC>();
+    if (there) b[p] = load_row<VEC, SMALL>(v.B, v.j[s], v.row_bytes, v.col_bytes);
+  }
+  uint32_t done = 0;
+  do {
+    Entry e[P][U];
+    V c[P][U];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (done + u < n[p]) e[p][u] = v.ent[lo[p] + done + u];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (done + u < n[p]) c[p][u] = load_row<VEC, SMALL>(v.C, e[p][u].xrow, v.row_bytes, v.col_bytes);
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (done + u < n[p]) vfma(x[p], e[p][u].val, c[p][u]);
+    done += U;
+  } while (P == 1 && done < n[0]);
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if (ALIKE || n[p] > 0) vmuladd(acc, x[p], b[p]);
+}
+
+constexpr int64_t kFewItems = 2048;
+
+template <int VEC, int LPR, bool SMALL>
+__global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
     const uint32_t* __restrict__ item_seg, const uint32_t* __restrict__ item_ent,
     const int32_t* __restrict__ item_dst, const uint32_t* __restrict__ seg_ptr,
     const int32_t* __restrict__ seg_j, const Entry* __restrict__ ent, int64_t n_items,
     const float* __restrict__ B, const float* __restrict__ C, float* __restrict__ A,
-    float* __restrict__ partials, int R) {
+    float* __restrict__ partials, int R, int team) {
   using V = typename Vec<VEC>::type;
-  constexpr int G = 64 / LPR;
+  constexpr uint32_t G = 64 / LPR;
   constexpr int WPB = kBlock / 64;
-  __shared__ Entry s_ent[WPB][kCsfItemNnz];
-  __shared__ uint32_t s_ptr[WPB][kCsfItemSegs + 1];     // segment offsets relative to the item's first entry
+  __shared__ __attribute__((aligned(16))) Entry s_ent[WPB][kCsfItemNnz];
+  __shared__ uint16_t s_ptr[WPB][kCsfItemSegs + 2];     // (16 bits: the eighth workgroup then fits the compute unit)
   __shared__ int32_t s_j[WPB][kCsfItemSegs];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-  const int64_t it = (int64_t)blockIdx.x * WPB + wave;
+  const int64_t it = team ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * WPB + wave;
   if (it >= n_items) return;            // whole wavefront leaves together
-  const uint32_t s_lo = item_seg[it], e_lo = item_ent[it];
+  uint32_t s_lo = item_seg[it], e_lo = item_ent[it];
   uint32_t n_seg = item_seg[it + 1] - s_lo, n_ent = item_ent[it + 1] - e_lo;
+  const int32_t dst = item_dst[it];
   // An item beyond what the staging arrays hold cannot come out of csf3_build, which is the one
   // place that enforces the limits; if an image ever carried one, its destination row is filled
   // with NaN (a result that announces itself) instead of being left with whatever it held.
   const bool over_limit = n_seg > (uint32_t)kCsfItemSegs || n_ent > (uint32_t)kCsfItemNnz;
   if (over_limit) { n_seg = 0; n_ent = 0; }
-  const int lane = threadIdx.x % 64;
-  const int g = lane / LPR;
+  if (team) {                           // this wavefront's quarter of the segments
+    const uint32_t first = n_seg * wave / WPB, last = n_seg * (wave + 1) / WPB, s_item = s_lo;
+    const uint32_t e_end = last < n_seg ? seg_ptr[s_item + last] : e_lo + n_ent;
+    if (first > 0) e_lo = seg_ptr[s_item + first];
+    s_lo += first;
+    n_seg = last - first;
+    n_ent = e_end - e_lo;
+  }
+  const uint32_t lane = threadIdx.x % 64;
+  const uint32_t g = lane / LPR;
   const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * (LPR * VEC), R);
-  const int c = lc.c;
-  const bool col_ok = lc.ok;
-  const uint32_t row_bytes = 4u * (uint32_t)R;
-  const uint32_t col_bytes = col_ok ? 4u * (uint32_t)c : 0u;
-  const char* Bb = reinterpret_cast<const char*>(B);
-  const char* Cb = reinterpret_cast<const char*>(C);
-  // stage the item: n_seg <= kCsfItemSegs and n_ent <= kCsfItemNnz by construction of the image
-  for (uint32_t t = lane; t <= n_seg; t += 64) s_ptr[wave][t] = seg_ptr[s_lo + t] - e_lo;
-  for (uint32_t t = lane; t < n_seg; t += 64) s_j[wave][t] = seg_j[s_lo + t];
-  for (uint32_t t = lane; t < n_ent; t += 64) s_ent[wave][t] = ent[e_lo + t];
-  strip_sync();
-  const Entry* se = s_ent[wave];
-  V acc = vzero<VEC>();
-  for (uint32_t s = g; s < n_seg; s += G) {
-    const uint32_t lo = s_ptr[wave][s], hi = s_ptr[wave][s + 1];
-    const V b = load_row<VEC, SMALL_B>(Bb, s_j[wave][s], row_bytes, col_bytes);
-    V x = vzero<VEC>();
-    for (uint32_t p = lo; p < hi; p += U) {
-      Entry e[U];
-      V cr[U];
+  const ItemView v{s_ent[wave], s_ptr[wave], s_j[wave], reinterpret_cast<const char*>(B),
+                   reinterpret_cast<const char*>(C), 4u * (uint32_t)R, lc.ok ? 4u * (uint32_t)lc.c : 0u};
+  // stage the item, the loads of up to 128 segments and 256 entries before the first wait
+  static_assert(kCsfItemSegs == 128 && kCsfItemNnz == 512, "the staging covers these sizes");
+  {
+    Entry e[4];
+    uint32_t pt[2];
+    int32_t jt[2];
 #pragma unroll
-      for (int u = 0; u < U; ++u) e[u] = se[p + u < hi ? p + u : lo];
+    for (uint32_t q = 0; q < 2; ++q)
+      if (lane + q * 64 < n_seg) { pt[q] = seg_ptr[s_lo + lane + q * 64]; jt[q] = seg_j[s_lo + lane + q * 64]; }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        cr[u] = p + u < hi ? load_row<VEC, SMALL_C>(Cb, e[u].xrow, row_bytes, col_bytes) : vzero<VEC>();
+    for (uint32_t q = 0; q < 4; ++q) if (lane + q * 64 < n_ent) e[q] = ent[e_lo + lane + q * 64];
 #pragma unroll
-      for (int u = 0; u < U; ++u) vfma(x, p + u < hi ? e[u].val : 0.f, cr[u]);
+    for (uint32_t q = 0; q < 2; ++q)
+      if (lane + q * 64 < n_seg) { s_ptr[wave][lane + q * 64] = (uint16_t)(pt[q] - e_lo); s_j[wave][lane + q * 64] = jt[q]; }
+    if (lane == 0) s_ptr[wave][n_seg] = (uint16_t)n_ent;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) if (lane + q * 64 < n_ent) s_ent[wave][lane + q * 64] = e[q];
+    if (n_ent > 256) {
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) if (lane + (q + 4) * 64 < n_ent) e[q] = ent[e_lo + lane + (q + 4) * 64];
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) if (lane + (q + 4) * 64 < n_ent) s_ent[wave][lane + (q + 4) * 64] = e[q];
     }
-    vmuladd(acc, x, b);
+  }
+  strip_sync();
+  V acc = vzero<VEC>();
+  uint32_t s = 0;
+  while (s < n_seg) {
+    // lengths of the next 64 segments, one per lane; the first is the longest of them
+    const uint32_t mine = s + lane < n_seg ? (uint32_t)v.ptr[s + lane + 1] - (uint32_t)v.ptr[s + lane] : 0u;
+    const uint32_t len = (uint32_t)__builtin_amdgcn_readfirstlane((int)mine);
+    const unsigned long long alike = __ballot(mine == len);
+    auto take = [&](auto Pc, auto Uc) {
+      constexpr int P = decltype(Pc)::value, U = decltype(Uc)::value;
+      constexpr uint32_t N = P * G;                 // at most 64
+      constexpr unsigned long long mask = ~0ULL >> (64 - N);
+      if ((alike & mask) == mask) segments<VEC, LPR, P, U, SMALL, true>(v, s, n_seg, len, g, acc);
+      else segments<VEC, LPR, P, U, SMALL, false>(v, s, n_seg, len, g, acc);
+      s += N;
+    };
+    using std::integral_constant;
+    constexpr int P4 = LPR >= 4 ? 4 : LPR, P2 = LPR >= 2 ? 2 : LPR;
+    if (len == 1) take(integral_constant<int, P4>{}, integral_constant<int, 1>{});
+    else if (len == 2) take(integral_constant<int, P2>{}, integral_constant<int, 2>{});
+        else take(integral_constant<int, 1>{}, integral_constant<int, 4>{});
   }
 #pragma unroll
   for (int m = LPR; m < 64; m <<= 1) vadd(acc, vshfl_xor(acc, m));
-  if (over_limit) vfma(acc, __builtin_nanf(""), acc);
-  if (g == 0 && col_ok) {
-    const int32_t dst = item_dst[it];
-    if (dst >= 0) gstore<VEC>(A + (size_t)dst * (size_t)R + c, acc);
-    else gstore<VEC>(partials + (size_t)(-1 - dst) * (size_t)R + c, acc);
+  if (team) {
+    // each wavefront's sum in the memory of its own entries, which it has read
+    strip_sync();
+    if (wave > 0 && g == 0) vstore<VEC>(reinterpret_cast<float*>(s_ent[wave]) + lane * VEC, acc);
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 1; w < WPB; ++w) vadd(acc, vload<VEC>(reinterpret_cast<const float*>(s_ent[w]) + lane % LPR * VEC));
   }
+  if (over_limit) vfma(acc, __builtin_nanf(""), acc);
+  if (g == 0 && lc.ok)
+    gstore<VEC>(dst >= 0 ? A + (size_t)dst * (size_t)R + lc.c : partials + (size_t)(-1 - dst) * (size_t)R + lc.c, acc);
 }
 
 }  // namespace
@@ -106,25 +207,23 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(
 int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int32_t* item_dst,
                   const uint32_t* seg_ptr, const int32_t* seg_j, const Entry* entries, int64_t n_items, const float* B,
                   int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials, int32_t R,
-                  double mean_segment, void* stream) {
+                  void* stream) {
   if (n_items <= 0) return 0;
-  // row loads issued per round of a segment: more than the segments hold only adds predicated slots
-  const int rounds = mean_segment < 2.5 ? 2 : (mean_segment < 6.0 ? 4 : 8);
   const Shape s = pick_shape(R, 0);
-  const bool small_b = small_matrix(b_rows, R), small_c = small_matrix(c_rows, R);
+  // Few items leave most wavefront slots empty, and the longest chain of row loads decides: the four
+  // wavefronts of a workgroup then share an item and add up in LDS (250 x 231 x 307 tensor of 17,720
+  // entries, R = 25: 8.4 -> 6.9 us).
+  const int team = n_items <= kFewItems ? 1 : 0;
+  const bool small = small_matrix(b_rows, R) && small_matrix(c_rows, R);
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;
-    const int64_t blocks = ceil_div(n_items, kBlock / 64);
+    const int64_t blocks = team ? n_items : ceil_div(n_items, kBlock / 64);
     if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
     dim3 grid((unsigned)blocks, (unsigned)s.slices);
-#define ARROW_LAUNCH(UU, SM)                                                                        \
-  hipLaunchKernelGGL((mttkrp_kernel<VEC, LPR, UU, SM, SM>), grid, dim3(kBlock), 0, (hipStream_t)stream, \
-                     item_seg, item_ent, item_dst, seg_ptr, seg_j, entries, n_items, B, C, A, partials, (int)R)
-    if (small_b && small_c) {
-      if (rounds == 2) ARROW_LAUNCH(2, true); else if (rounds == 4) ARROW_LAUNCH(4, true); else ARROW_LAUNCH(8, true);
-    } else {
-      if (rounds == 2) ARROW_LAUNCH(2, false); else if (rounds == 4) ARROW_LAUNCH(4, false); else ARROW_LAUNCH(8, false);
-    }
+#define ARROW_LAUNCH(SM)                                                                            \
+  hipLaunchKernelGGL((mttkrp_kernel<VEC, LPR, SM>), grid, dim3(kBlock), 0, (hipStream_t)stream,     \
+                     item_seg, item_ent, item_dst, seg_ptr, seg_j, entries, n_items, B, C, A, partials, (int)R, team)
+    if (small) ARROW_LAUNCH(true); else ARROW_LAUNCH(false);
 #undef ARROW_LAUNCH
     return (int)hipGetLastError();
   });

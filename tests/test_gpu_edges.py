@@ -138,3 +138,31 @@ def test_lds_windows(torch, k, span, fuse):
     Yref, B = oracle.spmm(rowptr, cols.astype(np.int32), vals, X)
     assert_within(Y.cpu().numpy(), Yref, B)
     op.close()
+
+
+@pytest.mark.parametrize("R", [1, 3, 4, 9, 32, 64, 130, 260])
+@pytest.mark.parametrize("I", [3, 2046, 2300])
+def test_mttkrp_fibre_lengths(torch, I, R):
+    """Few slices (a workgroup per item) and many (a wavefront per item); fibres of 1 to 130 entries, equally
+    long ones next to single ones, empty slices, a slice of several items."""
+    rng = np.random.default_rng(I)
+    J, K = 300, 140
+    ti, tj, tk = [], [], []
+    for i in range(I):
+        if i % 5 == 4:
+            continue
+        for f in range(260 if i == 1 else int(rng.integers(1, 7))):
+            j = f if i == 1 else int(rng.integers(0, J))
+            m = [1, 1, 2, 3, 4, 5, 8, 9][int(rng.integers(0, 8))] if i != 2 else int(rng.integers(60, 131))
+            ti += [i] * m
+            tj += [j] * m
+            tk += list(rng.integers(0, K, m))
+    tv = rng.uniform(-1, 1, len(ti)).astype(np.float32)
+    ti, tj, tk = (np.array(x, dtype=np.int32) for x in (ti, tj, tk))
+    Bf, Cf = synth.normal_matrix(J, R, seed=18), synth.normal_matrix(K, R, seed=19)
+    op = binding.Csf3Mttkrp((I, J, K), ti, tj, tk, tv)
+    A = torch.full((I, R), float("nan"), device="cuda")
+    op.mttkrp(torch.from_numpy(Bf).cuda(), torch.from_numpy(Cf).cuda(), A)
+    Aref, E = oracle.mttkrp((I, J, K), ti, tj, tk, tv, Bf, Cf)
+    assert_within(A.cpu().numpy(), Aref, E)
+    op.close()
