@@ -27,7 +27,7 @@ ARROW_LIB = os.path.join(PKG_DIR, "libarrow.so")
 SYNTH_LIB = os.path.join(PKG_DIR, "synth", "libsynth.so")
 ORACLE_LIB = os.path.join(REPO_DIR, "oracle", "liboracle.so")
 
-HIP_SOURCES = ["csrc/decompose.cpp", "csrc/layout.cpp", "csrc/abi.cpp", "csrc/kernels.hip",
+HIP_SOURCES = ["csrc/decompose.cpp", "csrc/layout.cpp", "csrc/abi.cpp", "csrc/kernels.hip", "csrc/sddmm.hip",
                "csrc/csf3.cpp", "csrc/mttkrp.hip", "csrc/probe.hip", "csrc/static_scratch.hip"]
 
 

@@ -274,27 +274,38 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
       if (rc) return check_hip(rc, "head staging launch");
       Vh = stage;
     }
-    if (im.n_chunks > 0) {
-      Scoped sc(h, kChunks, (int)li, stream);
-      int rc = arrow::launch_sddmm_chunks(at<uint32_t>(h, im.off_chunk_ptr), at<uint32_t>(h, im.off_chunk_mid),
-                                          at<int32_t>(h, im.off_chunk_row), ent, emap, im.n_chunks, U, V,
-                                          h->n, Vh, S, k, stream);
-      if (rc) return check_hip(rc, "sampled chunks kernel launch");
-    }
-    if (im.n_rows > 0) {
-      Scoped sc(h, kRows, (int)li, stream);
-      int rc = arrow::launch_sddmm_rows(0, at<uint32_t>(h, im.off_rows_ptr), at<uint32_t>(h, im.off_rows_mid),
-                                        at<int32_t>(h, im.off_rows_row), nullptr, nullptr, ent, emap,
-                                        im.n_rows, U, V, h->n, Vh, S, k, stream);
-      if (rc) return check_hip(rc, "sampled rows kernel launch");
-    }
-    if (im.n_wrows > 0) {
-      Scoped sc(h, kWindow, (int)li, stream);
-      int rc = arrow::launch_sddmm_rows(1, at<uint32_t>(h, im.off_wrow_ptr), at<uint32_t>(h, im.off_wrow_mid),
-                                        at<int32_t>(h, im.off_wrow_y), at<uint32_t>(h, im.off_wrow_win),
-                                        at<int32_t>(h, im.off_perm), ent, emap, im.n_wrows, U, V, h->n,
-                                        V, S, k, stream);
-      if (rc) return check_hip(rc, "sampled window-rows kernel launch");
+    {
+      arrow::SampledArgs a{};
+      a.chunk_ptr = at<uint32_t>(h, im.off_chunk_ptr); a.chunk_mid = at<uint32_t>(h, im.off_chunk_mid);
+      a.chunk_row = at<int32_t>(h, im.off_chunk_row); a.n_chunks = im.n_chunks;
+      a.rows_ptr = at<uint32_t>(h, im.off_rows_ptr); a.rows_mid = at<uint32_t>(h, im.off_rows_mid);
+      a.rows_row = at<int32_t>(h, im.off_rows_row); a.n_rows = im.n_rows;
+      a.ent = ent; a.emap = emap; a.U = U; a.V = V; a.Vh = Vh; a.S = S; a.k = k;
+      auto launch = [&](arrow::SampledArgs args, bool window_rows) -> int {
+        if (args.n_chunks == 0 && args.n_rows == 0) return ARROW_OK;
+        return check_hip(arrow::launch_sddmm(args, window_rows, im.classes > 0, !im.row_major, h->n, stream),
+                         "sampled product kernel launch");
+      };
+      int rc = ARROW_OK;
+      if (h->profiling) {                 // the lists apart, so that each has a time of its own
+        arrow::SampledArgs c = a, r = a;
+        c.n_rows = 0;
+        r.n_chunks = 0;
+        if (c.n_chunks > 0) { Scoped sc(h, kChunks, (int)li, stream); rc = launch(c, false); }
+        if (!rc && r.n_rows > 0) { Scoped sc(h, kRows, (int)li, stream); rc = launch(r, false); }
+      } else {
+        rc = launch(a, false);
+      }
+      if (rc) return rc;
+      if (im.n_wrows > 0) {
+        Scoped sc(h, kWindow, (int)li, stream);
+        a.n_chunks = 0; a.n_rows = im.n_wrows;
+        a.rows_ptr = at<uint32_t>(h, im.off_wrow_ptr); a.rows_mid = at<uint32_t>(h, im.off_wrow_mid);
+        a.rows_row = at<int32_t>(h, im.off_wrow_y); a.rows_win = at<uint32_t>(h, im.off_wrow_win);
+        a.perm = at<int32_t>(h, im.off_perm);
+        rc = launch(a, true);
+        if (rc) return rc;
+      }
     }
     if (im.n_panel_bins > 0) {
       Scoped sc(h, kPanel, (int)li, stream);

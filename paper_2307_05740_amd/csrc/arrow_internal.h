@@ -261,18 +261,25 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, co
                   void* stream);
 
 
-// Sampled dense-dense product S[emap[e]] = a_e <U[row(e)], V[col(e)]> over one work list.
-// mode 0: a group list (item_win and perm unused); mode 1: the window-row list.  emap points at the
-// level's slice of the entry map; v_rows = rows of V.
-int launch_sddmm_rows(int mode, const uint32_t* item_ptr, const uint32_t* item_mid,
-                      const int32_t* item_row, const uint32_t* item_win, const int32_t* perm,
-                      const Entry* entries, const uint32_t* emap, int64_t n_items, const float* U,
-                      const float* V, int64_t v_rows, const float* Vh, float* S, int32_t k,
-                      void* stream);
-int launch_sddmm_chunks(const uint32_t* chunk_ptr, const uint32_t* chunk_mid, const int32_t* chunk_row,
-                        const Entry* entries, const uint32_t* emap, int64_t n_chunks, const float* U,
-                        const float* V, int64_t v_rows, const float* Vh, float* S, int32_t k,
-                        void* stream);
+// Sampled dense-dense product S[emap[e]] = a_e <U[row(e)], V[col(e)]> over the wave list and the group
+// list of a level, or over its window-row list (rows_*, rows_win and perm then describe that one).
+// emap points at the level's slice of the entry map, or is null: S in image order.
+struct SampledArgs {
+  const uint32_t* chunk_ptr; const uint32_t* chunk_mid; const int32_t* chunk_row;
+  const uint32_t* rows_ptr; const uint32_t* rows_mid; const int32_t* rows_row;
+  const uint32_t* rows_win; const int32_t* perm;
+  const Entry* ent; const uint32_t* emap;
+  const float* U; const float* V; const float* Vh;
+  float* S;
+  int64_t n_chunks, n_rows;
+  int32_t k;
+  int32_t items;                        // group-list slots per workgroup
+  uint32_t chunk_blocks;
+  int32_t runs;                         // as in ProductArgs
+};
+// v_rows = rows of V; windows, die_queues: as in launch_product (the grid is filled in here).
+int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows, int64_t v_rows, void* stream);
+constexpr int kSampledBatch = 4;        // entries a lane group reduces together (= row loads in flight per lane)
 
 // Device address of the current device's copy of the static scratch array of arrow_spmm_static
 // (static_scratch.hip); NULL and a description in `err` on failure.  A lookup, never an allocation.

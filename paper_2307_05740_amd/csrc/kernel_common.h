@@ -148,6 +148,66 @@ __device__ __forceinline__ void strip_sync() {
 }
 
 // ---------------------------------------------------------------------------
+// dot products across the lanes of a group
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ float vdot(float u, float x) { return u * x; }
+__device__ __forceinline__ float vdot(float2 u, float2 x) { return fmaf(u.y, x.y, u.x * x.x); }
+__device__ __forceinline__ float vdot(float4 u, float4 x) {
+  return fmaf(u.w, x.w, fmaf(u.z, x.z, fmaf(u.y, x.y, u.x * x.x)));
+}
+
+// A lane that shares columns with the one before it (lane_columns) leaves them out of its dot products.
+__device__ __forceinline__ void drop_shared(float&, int) {}
+__device__ __forceinline__ void drop_shared(float2& v, int shared) { if (shared) v.x = 0.f; }
+__device__ __forceinline__ void drop_shared(float4& v, int shared) {
+  if (shared > 0) v.x = 0.f;
+  if (shared > 1) v.y = 0.f;
+  if (shared > 2) v.z = 0.f;
+}
+
+// v of a lane whose bit M differs from this lane's (M = 1, 2, 4, 8: the partner differs in lower bits
+// too where M = 4; a reduction over those bits does not mind).  A DPP operand, no LDS access.
+template <int M> __device__ __forceinline__ float across(float v) {
+  static_assert(M == 1 || M == 2 || M == 4 || M == 8, "within sixteen lanes");
+  constexpr int ctrl = M == 1 ? 0xB1 /* quad_perm 1,0,3,2 */ : M == 2 ? 0x4E /* quad_perm 2,3,0,1 */
+                     : M == 4 ? 0x141 /* row_half_mirror */ : 0x128 /* row_ror 8 */;
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false));
+}
+
+// One exchange of the transposing butterfly: lanes with bit M clear get the sum over bit M of `a`,
+// lanes with it set that of `b`.
+template <int M> __device__ __forceinline__ float exchange(float a, float b, int lane) {
+  if constexpr (M == 32 || M == 16) {
+    // swaps the halves (rows of sixteen) of one register with the other halves of the second
+    const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false)
+                           : __builtin_amdgcn_permlane16_swap(__float_as_int(a), __float_as_int(b), false, false);
+    return __int_as_float(r[0]) + __int_as_float(r[1]);
+  } else {
+    const bool upper = (lane & M) != 0;
+    return (upper ? b : a) + across<M>(upper ? a : b);
+  }
+}
+
+// Sums of NB values over the LPR lanes of a group: the upper lanes keep the upper half of the values at
+// every exchange, so that lane l ends up with the sum of value l / (LPR / NB).  With shuffles through
+// LDS instead of permlane swaps and DPP operands it took 40 vector instructions and 6 LDS accesses for
+// four values, now 10 and none.
+template <int NB, int LPR>
+__device__ __forceinline__ float group_reduce(float (&p)[NB], int l) {
+  if constexpr (LPR == 1) {
+    return p[0];
+  } else if constexpr (NB > 1) {
+    float q[NB / 2];
+#pragma unroll
+    for (int e = 0; e < NB / 2; ++e) q[e] = exchange<LPR / 2>(p[e], p[e + NB / 2], l);
+    return group_reduce<NB / 2, LPR / 2>(q, l);
+  } else {
+    float q[1] = {exchange<LPR / 2>(p[0], p[0], l)};
+    return group_reduce<1, LPR / 2>(q, l);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // host-side dispatch on (VEC, LPR)
 // ---------------------------------------------------------------------------
 struct Shape {
