@@ -191,7 +191,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
     {
       arrow::ProductArgs a{};
       a.chunk_ptr = at<uint32_t>(h, im.off_chunk_ptr); a.chunk_mid = at<uint32_t>(h, im.off_chunk_mid);
-      a.chunk_dst = at<int32_t>(h, im.off_chunk_dst); a.n_chunks = im.n_chunks;
+      a.chunk_dst = at<int32_t>(h, im.off_chunk_dst); a.n_chunks = im.n_chunks; a.longest_short = im.longest_short;
       a.rows_ptr = at<uint32_t>(h, im.off_rows_ptr); a.rows_mid = at<uint32_t>(h, im.off_rows_mid);
       a.rows_dst = at<int32_t>(h, im.off_rows_dst);
       a.ent = ent; a.X = X; a.Xh = Xh; a.Y = Y; a.partials = partials;

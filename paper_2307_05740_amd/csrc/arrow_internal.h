@@ -103,6 +103,7 @@ struct LevelImage {
   // group list: items handled one per lane group (class pieces in die queues, then the short rows)
   int64_t n_rows = 0, n_real_rows = 0, rows_partials = 0, nnz_rows = 0;
   int64_t piece_slots = 0;   // slots [0, piece_slots) hold the class pieces (die queues), the rest the short rows
+  int64_t longest_short = 0; // entries of the longest short row of the group list (pieces apart)
   int64_t empty_slots = 0;   // the last empty_slots slots are rows of Y without entries
   size_t off_rows_ptr = 0;   // uint32 n_rows + 1 (offsets into the level's entry array)
   size_t off_rows_mid = 0;   // uint32 n_rows : entries before it read the staged head buffer, the rest read X
@@ -212,6 +213,7 @@ struct ProductArgs {
   const float* X; const float* Xh;      // dense operand; staged head (X where nothing is staged)
   float* Y; float* partials;
   int64_t n_chunks;
+  int64_t longest_short;                // entries of the longest short row
   int32_t k, accumulate;                // accumulate: add to the rows of Y instead of storing them
   // parts 0 .. 3: wave list, pieces, short rows, rows without entries
   int64_t begin[4], count[4];           // slots of the part

@@ -235,7 +235,7 @@ struct Shape {
   s.slices = (k + lpr * s.vec - 1) / (lpr * s.vec);
   // slices of about the same width; where rows are whole 128-byte lines, so are the slices (k = 96 in
   // 48 and 48 columns reads four lines of a row, in 64 and 32 three: R-MAT 1.1m 1026 and 880 us)
-  const int step = k % 32 == 0 && s.vec == 4 ? 32 : s.vec;
+  const int step = k % 32 == 0 && s.vec == 4 && lpr >= 8 ? 32 : s.vec;
   s.width = ((k + s.slices - 1) / s.slices + step - 1) / step * step;
   return s;
 }

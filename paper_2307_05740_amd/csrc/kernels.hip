@@ -58,6 +58,8 @@ namespace {
 // time of a product over a few thousand rows).
 // ---------------------------------------------------------------------------
 constexpr int64_t kPieceWavesMax = 4096;
+constexpr int kFlowBatches = 4;       // batches of a workgroup of the flow kernel
+constexpr int64_t kFlowLeast = 4096;  // fewest batches it takes
 constexpr int kRowsStage = 1024;   // entries of the group list a workgroup stages at once (8 KiB)
 
 template <int LPR> constexpr int strip_entries() {     // entries of the wave list a wavefront parks per batch
@@ -72,42 +74,24 @@ struct alignas(16) RowsShared {
   int32_t dst[kItemsPerGroupBlock];
 };
 
-// The items [first, first + n_it) of the group list, one lane group per item, taken round-robin.
-// Entries [lo, mid) of an item read rows of the staged head buffer Xh, entries [mid, hi) rows of X.
-// The workgroup first copies the descriptors of its items and, when they fit the staging buffer, all
-// their entries -- one contiguous range -- into LDS with coalesced loads; after that the only memory
-// latency a lane group waits for is that of the rows it gathers.  Items that do not fit are read
-// from memory entry by entry.
+// Items [0, n_it) of a batch of the group list whose descriptors are at ptr, mid and dst, one lane group
+// per item, taken round-robin.  Entries [lo, mid) of an item read rows of the staged head buffer Xh,
+// entries [mid, hi) rows of X.  `staged`: the batch's entries, or null where they are read from memory.
 template <int VEC, int LPR, bool SMALL>
-__device__ __forceinline__ void rows_part(RowsShared& sh, const ProductArgs& a, int64_t first, int n_it,
-                                          const LaneColumns lc) {
+__device__ __forceinline__ void row_items(const uint32_t* ptr, const uint32_t* mids, const int32_t* dsts,
+                                          const Entry* staged, const ProductArgs& a, int n_it, const LaneColumns lc) {
   using V = typename Vec<VEC>::type;
   constexpr int GPB = kBlock / LPR;
   constexpr uint32_t U = 8;
   const int tid = threadIdx.x;
   const uint32_t row_bytes = 4u * (uint32_t)a.k;
   const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
-  if (tid <= n_it) sh.ptr[tid] = a.rows_ptr[first + tid];
-  if (tid < n_it) { sh.mid[tid] = a.rows_mid[first + tid]; sh.dst[tid] = a.rows_dst[first + tid]; }
-  __syncthreads();
-  const uint32_t e0 = sh.ptr[0];
-  const uint32_t total = sh.ptr[n_it] - e0;
-  const bool staged = total <= (uint32_t)kRowsStage;
-  if (staged) {
-    // all loads before the first wait (one at a time they were up to four memory latencies in a row)
-    constexpr uint32_t Q = kRowsStage / kBlock;
-    Entry e[Q];
-#pragma unroll
-    for (uint32_t q = 0; q < Q; ++q) if (tid + q * kBlock < total) e[q] = a.ent[e0 + tid + q * kBlock];
-#pragma unroll
-    for (uint32_t q = 0; q < Q; ++q) if (tid + q * kBlock < total) sh.stage[tid + q * kBlock] = e[q];
-    __syncthreads();
-  }
+  const uint32_t e0 = ptr[0];
   auto run = [&](auto entry) {
     for (int it = tid / LPR; it < n_it; it += GPB) {
-      const int32_t dst = sh.dst[it];
+      const int32_t dst = dsts[it];
       if (dst == INT32_MIN) continue;             // padding slot of the die queues
-      const uint32_t lo = sh.ptr[it], mid = sh.mid[it], hi = sh.ptr[it + 1];
+      const uint32_t lo = ptr[it], mid = mids[it], hi = ptr[it + 1];
       V acc = vzero<VEC>();
       for (int seg = 0; seg < 2; ++seg) {
         const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Xh : a.X);
@@ -132,8 +116,35 @@ __device__ __forceinline__ void rows_part(RowsShared& sh, const ProductArgs& a, 
       }
     }
   };
-  if (staged) run([&](uint32_t t) { return sh.stage[t - e0]; });
+  if (staged) run([&](uint32_t t) { return staged[t - e0]; });
   else run([&](uint32_t t) { return a.ent[t]; });
+}
+
+// The items [first, first + n_it) of the group list.  The workgroup first copies the descriptors of its
+// items and, when they fit the staging buffer, all their entries -- one contiguous range -- into LDS with
+// coalesced loads; after that the only memory latency a lane group waits for is that of the rows it
+// gathers.  Items that do not fit are read from memory entry by entry.
+template <int VEC, int LPR, bool SMALL>
+__device__ __forceinline__ void rows_part(RowsShared& sh, const ProductArgs& a, int64_t first, int n_it,
+                                          const LaneColumns lc) {
+  const int tid = threadIdx.x;
+  if (tid <= n_it) sh.ptr[tid] = a.rows_ptr[first + tid];
+  if (tid < n_it) { sh.mid[tid] = a.rows_mid[first + tid]; sh.dst[tid] = a.rows_dst[first + tid]; }
+  __syncthreads();
+  const uint32_t e0 = sh.ptr[0];
+  const uint32_t total = sh.ptr[n_it] - e0;
+  const bool staged = total <= (uint32_t)kRowsStage;
+  if (staged) {
+    // all loads before the first wait (one at a time they were up to four memory latencies in a row)
+    constexpr uint32_t Q = kRowsStage / kBlock;
+    Entry e[Q];
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) if (tid + q * kBlock < total) e[q] = a.ent[e0 + tid + q * kBlock];
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) if (tid + q * kBlock < total) sh.stage[tid + q * kBlock] = e[q];
+    __syncthreads();
+  }
+  row_items<VEC, LPR, SMALL>(sh.ptr, sh.mid, sh.dst, staged ? sh.stage : nullptr, a, n_it, lc);
 }
 
 // One chunk of the wave list per wavefront.  Entries [lo, mid) of a chunk read rows of the staged
@@ -274,6 +285,118 @@ __global__ __launch_bounds__(kBlock, 6) void product_kernel(const ProductArgs a)
   }
   for (int it = tid / LPR; it < n_it; it += GPB)   // level 0 stores every row of Y
     if (lc.ok) vstore_stream<VEC>(a.Y + (size_t)a.rows_dst[first + it] * (size_t)a.k + lc.c, vzero<VEC>());
+}
+
+// Copies the lanes' 4 or 16 bytes from `from` to consecutive places at `to` in LDS (the same for the whole
+// wavefront) without registers in between.  In assembly because the compiler waits for such a copy before
+// the next read of LDS, whatever it reads: the caller waits (vmcnt) before it reads what was copied.
+// (m0 holds nothing between instructions on this target.)
+__device__ __forceinline__ void copy_to_lds16(const void* from, const void* to) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :: "v"(from), "s"(__builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(to))) : "memory");
+}
+__device__ __forceinline__ void copy_to_lds4(const void* from, const void* to) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+               :: "v"(from), "s"(__builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(to))) : "memory");
+}
+
+struct alignas(16) FlowShared {
+  Entry stage[2][kRowsStage + 8];      // a batch's entries from an even one on; up to seven past the last are read
+  struct { uint32_t lo[kItemsPerGroupBlock], hi[kItemsPerGroupBlock], mid[kItemsPerGroupBlock]; int32_t dst[kItemsPerGroupBlock]; } of[3];
+};
+static_assert(kItemsPerGroupBlock == 64 && kBlock == 256, "one wavefront per descriptor array, one lane per item");
+
+// The short rows on their own, where they are nearly all of the product and every batch of them fits the
+// staging buffer.  A workgroup works on every gridDim.x-th batch; the next batch's entries and the
+// descriptors of the one after it are copied to LDS meanwhile.  Of the row of X that an entry of a stencil
+// reads, one in five comes from memory and the others from the L2, so it is the latency of few bytes that
+// bounds the time: three latencies per batch with the copies ahead, of which two are for rows of X, where
+// there were four.  (Grid of 1024 x 1024, k = 32, X and Y not in any cache: 82.1 -> 69.7 us, 4.8 TB/s; one
+// batch per workgroup 73.8, two 70.6, eight 74.5.  Beside long rows, whose misses fill the memory pipes, the
+// launch of its own costs more than this gives: three products of R-MAT 1m, k = 64, 1184 -> 1227 us.)
+template <int VEC, int LPR, bool SMALL>
+__global__ __launch_bounds__(kBlock, 6) void flow_kernel(const ProductArgs a) {
+  using V = typename Vec<VEC>::type;
+  constexpr int GPB = kBlock / LPR;
+  constexpr uint32_t U = 8;
+  __shared__ FlowShared sh;
+  const int tid = threadIdx.x;
+  const int lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const LaneColumns lc = lane_columns<VEC>(tid % LPR, (int)blockIdx.y * a.width, a.k, a.width);
+  const uint32_t row_bytes = 4u * (uint32_t)a.k;
+  const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
+  const int64_t step = gridDim.x;
+  auto items_of = [&](int64_t bt) {
+    const int64_t left = a.count[2] - bt * kItemsPerGroupBlock;
+    return left < 0 ? 0 : (left < kItemsPerGroupBlock ? (int)left : kItemsPerGroupBlock);
+  };
+  const uint32_t* mine = wave == 0 ? a.rows_ptr : wave == 1 ? a.rows_ptr + 1 : wave == 2 ? a.rows_mid
+                                                : reinterpret_cast<const uint32_t*>(a.rows_dst);
+  auto describe = [&](int to, int64_t bt) {
+    if (lane < items_of(bt)) copy_to_lds4(mine + a.begin[2] + bt * kItemsPerGroupBlock + lane, &sh.of[to].lo[0] + wave * 64);
+  };
+  auto fetch = [&](int buf, int to, int n) {         // two entries per lane
+    const uint32_t e0 = sh.of[to].lo[0] & ~1u, e1 = sh.of[to].hi[n - 1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int at = (q * 4 + wave) * 64;
+      if (q < 2 || wave == 0)
+        if (e0 + 2u * (uint32_t)(at + lane) < e1) copy_to_lds16(a.ent + e0 + 2 * (at + lane), sh.stage[buf] + 2 * at);
+    }
+  };
+  // (__syncthreads would wait for the stores of Y as well)
+  auto arrived = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+  auto sync = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  int64_t bt = blockIdx.x;
+  int n = items_of(bt);
+  if (n == 0) return;
+  describe(0, bt);
+  describe(1, bt + step);
+  arrived();
+  sync();
+  fetch(0, 0, n);
+  arrived();
+  sync();
+  for (int cur = 0, buf = 0;; buf ^= 1) {
+    const int nxt = cur == 2 ? 0 : cur + 1;
+    const int n_next = items_of(bt + step);
+    if (n_next > 0) {
+      fetch(buf ^ 1, nxt, n_next);
+      describe(nxt == 2 ? 0 : nxt + 1, bt + 2 * step);
+    }
+    const auto& b = sh.of[cur];
+    const uint32_t e0 = b.lo[0] & ~1u;
+    for (int it = tid / LPR; it < n; it += GPB) {
+      const uint32_t mid = b.mid[it], hi = b.hi[it];
+      V acc = vzero<VEC>();
+      for (int seg = 0; seg < 2; ++seg) {
+        const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Xh : a.X);
+        const uint32_t j_hi = seg == 0 ? mid : hi;
+        for (uint32_t j = seg == 0 ? b.lo[it] : mid; j < j_hi; j += U) {
+          Entry e[U];
+          V x[U];
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) e[u] = sh.stage[buf][j - e0 + u];
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u)
+            x[u] = (j + u < j_hi) ? load_row<VEC, SMALL>(base, e[u].xrow, row_bytes, col_bytes) : vzero<VEC>();
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) vfma(acc, (j + u < j_hi) ? e[u].val : 0.f, x[u]);
+        }
+      }
+      arrived();                                     // older than the rows just used: no wait but for the first item's store
+      if (lc.ok) {
+        float* y = a.Y + (size_t)b.dst[it] * (size_t)a.k + lc.c;
+        if (a.accumulate) vadd(acc, vload_stream<VEC>(y));
+        vstore_stream<VEC>(y, acc);
+      }
+    }
+    if (n_next == 0) return;
+    if (wave * (64 / LPR) >= n) arrived();           // a wavefront without items has not waited yet
+    sync();
+    bt += step; n = n_next; cur = nxt;
+  }
 }
 
 // The wave list on its own, for lists in window order: a chunk is over in two or three rounds of row
@@ -933,6 +1056,7 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
                    bool windows, int64_t x_rows, int32_t kc, void* stream) {
   const Shape s = pick_output_shape(a.k, kc, a.accumulate != 0);
   const bool small = small_matrix(x_rows, a.k);    // the staged buffer has at most as many rows as X
+  const int64_t n_long = a.n_chunks;
   if (!(parts & kPartChunks)) a.n_chunks = 0;
   a.begin[0] = 0; a.count[0] = a.n_chunks;
   a.items[0] = kBlock / 64;
@@ -967,6 +1091,9 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
   }
   a.slices = (uint32_t)s.slices;
   a.width = s.width;
+  // stencils, meshes, bands: hardly any long rows, and enough batches for every compute unit to have several in turn
+  const bool flow = a.longest_short * (int64_t)kItemsPerGroupBlock <= kRowsStage &&
+                    a.count[2] >= kItemsPerGroupBlock * kFlowLeast && a.count[2] >= 64 * (n_long + a.count[1]);
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
     if (windows && a.blocks[0] > 0) {
@@ -975,6 +1102,14 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
       else hipLaunchKernelGGL((chunks_kernel<VEC, LPR, false>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);
       total -= (int64_t)a.blocks[0] * a.slices;
       a.blocks[0] = 0;
+    }
+    if (flow) {
+      const int64_t blocks = ceil_div(a.count[2], (int64_t)kItemsPerGroupBlock * kFlowBatches);
+      dim3 grid((unsigned)(ceil_div(blocks, kDies) * kDies), a.slices);
+      if (small) hipLaunchKernelGGL((flow_kernel<VEC, LPR, true>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);
+      else hipLaunchKernelGGL((flow_kernel<VEC, LPR, false>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);
+      total -= (int64_t)a.blocks[2] * a.slices;
+      a.blocks[2] = 0;
     }
     if (total > 0) {
       if (small) hipLaunchKernelGGL((product_kernel<VEC, LPR, true>), dim3((unsigned)total), dim3(kBlock), 0, (hipStream_t)stream, a);

@@ -733,7 +733,9 @@ int pack_levels(int64_t n, int32_t b, const std::vector<HostLevel>& levels, cons
           ptr.push_back((uint32_t)at);
           dst.push_back(L.perm[p]);
           irow.push_back(L.perm[p]);
-          at += L.rowptr[p + 1] - L.rowptr[p] - P.row_skip(p);
+          const int64_t len = L.rowptr[p + 1] - L.rowptr[p] - P.row_skip(p);
+          im.longest_short = std::max(im.longest_short, len);
+          at += len;
           ++real_items[0];
         }
       }

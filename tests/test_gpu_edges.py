@@ -166,3 +166,24 @@ def test_mttkrp_fibre_lengths(torch, I, R):
     Aref, E = oracle.mttkrp((I, J, K), ti, tj, tk, tv, Bf, Cf)
     assert_within(A.cpu().numpy(), Aref, E)
     op.close()
+
+
+@pytest.mark.parametrize("k", [1, 6, 32, 72])
+@pytest.mark.parametrize("n,full", [(4096 * 64, True), (4096 * 64 + 301, True), (4096 * 64 + 301, False), (300001, False)])
+def test_many_batches_of_short_rows(torch, n, full, k):
+    """Short rows only, enough of them for several batches per workgroup: batches that fill the staging
+    buffer to the last entry, rows without entries, an incomplete last batch."""
+    rng = np.random.default_rng(n)
+    length = np.full(n, 16) if full else rng.integers(0, 17, n)
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    row = np.repeat(np.arange(n), length)
+    step = 1 + rng.integers(0, 3, n)
+    colidx = (np.clip(np.arange(n) - 20, 0, n - 64)[row] + (np.arange(len(row)) - rowptr[row]) * step[row]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=21)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, 4096)
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    op.close()
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
