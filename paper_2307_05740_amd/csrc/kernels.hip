@@ -58,8 +58,9 @@ namespace {
 // time of a product over a few thousand rows).
 // ---------------------------------------------------------------------------
 constexpr int64_t kPieceWavesMax = 4096;
-constexpr int kFlowBatches = 4;       // batches of a workgroup of the flow kernel
-constexpr int64_t kFlowLeast = 4096;  // fewest batches it takes
+constexpr int kFlowBatches = 4;        // batches of a workgroup of the flow kernel; fewer where that leaves
+constexpr int64_t kFlowBlocks = 1536;  // less than these workgroups, the ones the chip holds at a time
+constexpr int64_t kFlowLeast = 1024;   // fewest batches it takes (100489 rows, k = 32: 13.2 -> 10.2 us; 40000, k = 16: 5.3 and 5.6)
 constexpr int kRowsStage = 1024;   // entries of the group list a workgroup stages at once (8 KiB)
 
 template <int LPR> constexpr int strip_entries() {     // entries of the wave list a wavefront parks per batch
@@ -1104,7 +1105,8 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
       a.blocks[0] = 0;
     }
     if (flow) {
-      const int64_t blocks = ceil_div(a.count[2], (int64_t)kItemsPerGroupBlock * kFlowBatches);
+      const int64_t batches = ceil_div(a.count[2], (int64_t)kItemsPerGroupBlock);
+      const int64_t blocks = std::max(ceil_div(batches, (int64_t)kFlowBatches), std::min(batches, kFlowBlocks));
       dim3 grid((unsigned)(ceil_div(blocks, kDies) * kDies), a.slices);
       if (small) hipLaunchKernelGGL((flow_kernel<VEC, LPR, true>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);
       else hipLaunchKernelGGL((flow_kernel<VEC, LPR, false>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);

@@ -169,7 +169,7 @@ def test_mttkrp_fibre_lengths(torch, I, R):
 
 
 @pytest.mark.parametrize("k", [1, 6, 32, 72])
-@pytest.mark.parametrize("n,full", [(4096 * 64, True), (4096 * 64 + 301, True), (4096 * 64 + 301, False), (300001, False)])
+@pytest.mark.parametrize("n,full", [(1024 * 64, True), (1024 * 64 + 301, False), (4096 * 64 + 301, True), (300001, False)])
 def test_many_batches_of_short_rows(torch, n, full, k):
     """Short rows only, enough of them for several batches per workgroup: batches that fill the staging
     buffer to the last entry, rows without entries, an incomplete last batch."""
