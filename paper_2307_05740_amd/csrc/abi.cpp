@@ -149,6 +149,7 @@ int check_hip(int rc, const char* what) {
 }
 
 constexpr int64_t kFewChunks = 2048;   // a list this short leaves wavefront slots empty
+constexpr int64_t kFewRows = 16384;    // and so does this one
 
 // one product, src -> dst (device, n x k), all levels in stream order.  `ws` holds the partial
 // vectors, the staged head and the panel results (the caller's workspace, or the static scratch
@@ -201,7 +202,9 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
                                                !im.row_major, h->n, kc, stream), "product kernel launch");
       };
       // the wave list and the pieces follow the chunk kernel's column slicing, the short rows run in
-      // one pass over whole rows; where that is the same shape, one launch takes all of it.  A
+      // one pass over whole rows; where that is the same shape, or where both lists are so short that a
+      // second launch is most of the time, one launch takes all of it (Chung-Lu 3326, k = 128: 11.1 -> 6.7
+      // us; R-MAT 7914, k = 135: 16.0 -> 11.3 us).  A
       // profiled product keeps the lists apart so that each has a time of its own.
       using namespace arrow;
       int rc = ARROW_OK;
@@ -212,7 +215,8 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
           rc = launch(kPartPieces, tune.kc);
           if (!rc) rc = launch(kPartShort, h->tuning.kc);
         }
-      } else if (same_shape(k, tune.kc, h->tuning.kc, acc)) {
+      } else if (same_shape(k, tune.kc, h->tuning.kc, acc) ||
+                 (im.row_major && im.n_chunks <= kFewChunks && im.n_rows <= kFewRows)) {
         rc = launch(kPartAll, tune.kc);
       } else {
         rc = launch(kPartChunks | kPartPieces, tune.kc);
