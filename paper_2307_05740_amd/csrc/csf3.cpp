@@ -50,6 +50,7 @@ constexpr int64_t kItemSegs = arrow::kCsfItemSegs;  // ... or more segments than
 
 struct csf3_handle {
   int64_t I = 0, J = 0, K = 0, nnz = 0;
+  int64_t longest = 0;       // entries and segments of the longest item
   int64_t slices = 0, fibers = 0, n_seg = 0, n_items = 0, n_split = 0, n_partials = 0;
   int64_t distinct_j = 0, distinct_k = 0;
   double build_seconds = 0.0;
@@ -140,16 +141,22 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
         item_dst.push_back((int32_t)i);
         continue;
       }
-      while (s < h->n_seg && seg_i[s] == i) {
+      // how many items the slice needs when each takes what it can hold, and then as many that cost
+      // about the same (rows gathered: one per entry and one per segment)
+      auto fits = [&](int64_t at_seg, int64_t cnt, int64_t segs) {
+        return at_seg < h->n_seg && seg_i[at_seg] == i && segs < kItemSegs &&
+               (cnt == 0 || cnt + (seg_ptr[at_seg + 1] - seg_ptr[at_seg]) <= kItemNnz);
+      };
+      int64_t end = s, least = 0;
+      while (end < h->n_seg && seg_i[end] == i) {
+        ++least;
+        for (int64_t cnt = 0, segs = 0; fits(end, cnt, segs); ++segs, ++end) cnt += seg_ptr[end + 1] - seg_ptr[end];
+      }
+      const int64_t share = ((int64_t)(seg_ptr[end] - seg_ptr[s]) + (end - s) + least - 1) / least;
+      while (s < end) {
         item_seg.push_back((uint32_t)s);
         item_dst.push_back((int32_t)i);
-        int64_t cnt = 0, segs = 0;
-        while (s < h->n_seg && seg_i[s] == i && segs < kItemSegs &&
-               (cnt == 0 || cnt + (seg_ptr[s + 1] - seg_ptr[s]) <= kItemNnz)) {
-          cnt += seg_ptr[s + 1] - seg_ptr[s];
-          ++segs;
-          ++s;
-        }
+        for (int64_t cnt = 0, segs = 0; cnt + segs < share && fits(s, cnt, segs); ++segs, ++s) cnt += seg_ptr[s + 1] - seg_ptr[s];
       }
       const size_t n_it = item_dst.size() - first_item;
       if (n_it > 1) {                                  // split slice: consecutive partial slots
@@ -192,6 +199,7 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
     for (size_t t = 0; t + 1 < item_seg.size(); ++t) {
       const int64_t segs = (int64_t)item_seg[t + 1] - (int64_t)item_seg[t];
       const int64_t ents = (int64_t)seg_ptr[item_seg[t + 1]] - (int64_t)seg_ptr[item_seg[t]];
+      h->longest = std::max(h->longest, segs + ents);
       if (segs < 0 || segs > kItemSegs || ents < 0 || ents > kItemNnz) {
         delete h;
         return fail3(ARROW_EINTERNAL, "work item %zu holds %lld segments / %lld entries", t, (long long)segs, (long long)ents);
@@ -293,7 +301,7 @@ int csf3_mttkrp(csf3_handle* h, const float* B, const float* C, float* A, int32_
                                 reinterpret_cast<const uint32_t*>(at(h->off_seg_ptr)),
                                 reinterpret_cast<const int32_t*>(at(h->off_seg_j)),
                                 reinterpret_cast<const arrow::Entry*>(at(h->off_entries)), h->n_items, B,
-                                h->J, C, h->K, A, partials, R, stream);
+                                h->J, C, h->K, A, partials, R, (int32_t)h->longest, stream);
   if (rc) return fail3(ARROW_EHIP, "mttkrp kernel launch: %s", hipGetErrorString((hipError_t)rc));
   if (prof) (void)hipEventRecord(h->ev[1], (hipStream_t)stream);
   rc = arrow::launch_reduce(reinterpret_cast<const uint32_t*>(at(h->off_split_ptr)),

@@ -101,7 +101,9 @@ __device__ __forceinline__ void segments(const ItemView& v, uint32_t s0, uint32_
     if (ALIKE || n[p] > 0) vmuladd(acc, x[p], b[p]);
 }
 
-constexpr int64_t kFewItems = 2048;
+constexpr int64_t kFewItems = 2048;       // a few wavefronts per compute unit
+constexpr int64_t kResidentItems = 8192;  // wavefronts the chip holds
+constexpr int64_t kLongChain = 64;        // rows one after the other in a lane group
 
 template <int VEC, int LPR, bool SMALL>
 __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
@@ -207,13 +209,16 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
 int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int32_t* item_dst,
                   const uint32_t* seg_ptr, const int32_t* seg_j, const Entry* entries, int64_t n_items, const float* B,
                   int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials, int32_t R,
-                  void* stream) {
+                  int32_t longest, void* stream) {
   if (n_items <= 0) return 0;
   const Shape s = pick_shape(R, 0);
   // Few items leave most wavefront slots empty, and the longest chain of row loads decides: the four
   // wavefronts of a workgroup then share an item and add up in LDS (250 x 231 x 307 tensor of 17,720
-  // entries, R = 25: 8.4 -> 6.9 us).
-  const int team = n_items <= kFewItems ? 1 : 0;
+  // entries, R = 25: 8.4 -> 6.9 us).  Where every item has a wavefront on the chip at once it still pays if
+  // the longest one keeps a lane group busy for long: 159 x 2469 x 3954 of 1.55 M entries, R = 41 (150 rows):
+  // 41 -> 38 us; skewed 5882 x 1176 x 588 of 188 K, R = 30 (hub slices): 21 -> 16 us; but 1704 x 389 x 887 of
+  // 588 K, R = 14 (18 rows): 11.6 -> 14.2 us.
+  const int team = n_items <= kFewItems || (n_items <= kResidentItems && (int64_t)longest * s.lpr >= 64 * kLongChain) ? 1 : 0;
   const bool small = small_matrix(b_rows, R) && small_matrix(c_rows, R);
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;

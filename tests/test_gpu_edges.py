@@ -187,3 +187,46 @@ def test_many_batches_of_short_rows(torch, n, full, k):
     op.close()
     Yref, B = oracle.spmm(rowptr, colidx, vals, X)
     assert_within(Y.cpu().numpy(), Yref, B)
+
+
+@pytest.mark.parametrize("k", [8, 20, 70])
+@pytest.mark.parametrize("n,b", [(200, 64), (4000, 500), (17 * 256 + 3, 256)])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_tiles_shared_by_workgroups(torch, n, b, k, fuse):
+    """Fewer window tiles than compute units: workgroups take parts of a tile's rows, some of them none."""
+    rng = np.random.default_rng(n)
+    rowptr = (np.arange(n + 1) * 30).astype(np.int64)
+    lo = np.arange(n) // b * b
+    hi = np.minimum(lo + b, n)
+    colidx = np.concatenate([np.sort(rng.permutation(hi[i] - lo[i])[:30] + lo[i]) if hi[i] - lo[i] >= 30 else np.arange(30)
+                             for i in range(n)]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=22)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, b, options=binding.arrow_options_default(fuse_levels=fuse))
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    op.close()
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
+
+
+@pytest.mark.parametrize("R", [14, 41, 128])
+@pytest.mark.parametrize("I,longest", [(2049, 60), (2049, 900), (8193, 900)])
+def test_mttkrp_items_of_unequal_length(torch, I, longest, R):
+    """Slices of one entry beside one that is cut into several items of about the same length."""
+    rng = np.random.default_rng(longest)
+    J, K = 300, 200
+    hub = rng.choice(J * K, longest, replace=False)
+    ti = np.concatenate([np.arange(I), np.full(longest, I // 2)]).astype(np.int32)
+    tj = np.concatenate([rng.integers(0, J, I), hub // K]).astype(np.int32)
+    tk = np.concatenate([rng.integers(0, K, I), hub % K]).astype(np.int32)
+    tv = rng.uniform(-1, 1, len(ti)).astype(np.float32)
+    Bm, Cm = synth.normal_matrix(J, R, seed=23), synth.normal_matrix(K, R, seed=24)
+    h = binding.Csf3Mttkrp((I, J, K), ti, tj, tk, tv, device="cuda:0")
+    A = h.mttkrp(torch.from_numpy(Bm).cuda(), torch.from_numpy(Cm).cuda()).cpu().numpy()
+    h.close()
+    ref, bound = np.zeros((I, R)), np.zeros((I, R))
+    term = tv[:, None].astype(np.float64) * Bm[tj] * Cm[tk]
+    np.add.at(ref, ti, term)
+    np.add.at(bound, ti, np.abs(term))
+    assert_within(A, ref, bound)
