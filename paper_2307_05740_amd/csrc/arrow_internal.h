@@ -267,6 +267,7 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, co
 // list of a level, or over its window-row list (rows_*, rows_win and perm then describe that one).
 // emap points at the level's slice of the entry map, or is null: S in image order.
 struct SampledArgs {
+  uint32_t chunk_parts;                 // wavefronts that share a chunk (filled in by the launch)
   const uint32_t* chunk_ptr; const uint32_t* chunk_mid; const int32_t* chunk_row;
   const uint32_t* rows_ptr; const uint32_t* rows_mid; const int32_t* rows_row;
   const uint32_t* rows_win; const int32_t* perm;

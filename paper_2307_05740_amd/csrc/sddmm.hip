@@ -24,6 +24,7 @@
 namespace arrow {
 namespace {
 
+constexpr int64_t kResidentWaves = 8192;   // wavefronts the chip holds
 constexpr int kSampledStage = 1024;   // entries of the group list a workgroup stages at once
 
 struct alignas(16) SampledShared {
@@ -78,14 +79,20 @@ __device__ __forceinline__ float dots(const SampledArgs& a, const char* base, co
 // One chunk of the wave list per wavefront: the G lane groups take the entries round-robin, NB rounds at
 // a time; nothing is combined across lane groups.  Entries [lo, mid) read rows of the staged head Vh.
 template <int VEC, int LPR, int NB, bool SMALL>
-__device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const SampledArgs& a, int64_t ch) {
+__device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const SampledArgs& a, int64_t ch, uint32_t part) {
   using V = typename Vec<VEC>::type;
   constexpr uint32_t G = 64 / LPR;
   constexpr uint32_t SPAN = LPR / NB;               // lanes that end up with the same entry's sum
-  const uint32_t lo = a.chunk_ptr[ch];
-  const uint32_t hi = a.chunk_ptr[ch + 1];
-  const uint32_t mid = a.chunk_mid[ch];
+  uint32_t lo = a.chunk_ptr[ch];
+  uint32_t hi = a.chunk_ptr[ch + 1];
+  uint32_t mid = a.chunk_mid[ch];
   const int32_t row = a.chunk_row[ch];
+  if (a.chunk_parts > 1) {                          // this wavefront's share of the chunk
+    const uint32_t len = hi - lo, first = lo;
+    lo = first + len * part / a.chunk_parts;
+    hi = first + len * (part + 1) / a.chunk_parts;
+    mid = mid < lo ? lo : (mid > hi ? hi : mid);
+  }
   if (lo == hi) return;                             // padding slot of the die queues
   const uint32_t lane = threadIdx.x % 64;
   const uint32_t g = lane / LPR;
@@ -244,8 +251,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_chunks_kernel(const SampledArgs 
   const uint32_t base = id / span * span;
   if (a.runs && base + span <= gridDim.x) id = base + id % kDies * kDieRun + (id - base) / kDies;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
-  const int64_t ch = (int64_t)id * WPB + wave;
-  if (ch < a.n_chunks) sampled_chunk<VEC, LPR, NB, SMALL>(ents[wave], ats[wave], a, ch);
+  const int64_t ch = (int64_t)id * WPB + wave;      // (a list in window order is never short)
+  if (ch < a.n_chunks) sampled_chunk<VEC, LPR, NB, SMALL>(ents[wave], ats[wave], a, ch, 0);
 }
 
 template <int VEC, int LPR, int NB, bool SMALL, bool WINDOW>
@@ -268,8 +275,10 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SampledArgs a) {
   __shared__ Shared sh;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   if (blockIdx.x < a.chunk_blocks) {
-    const int64_t ch = (int64_t)blockIdx.x * WPB + wave;
-    if (ch < a.n_chunks) sampled_chunk<VEC, LPR, NB, SMALL>(sh.chunk.ents[wave], sh.chunk.ats[wave], a, ch);
+    const uint32_t slot = blockIdx.x * WPB + wave;  // fewer than 2^31, the launch sees to that
+    const int64_t ch = slot / a.chunk_parts;
+    if (ch < a.n_chunks)
+      sampled_chunk<VEC, LPR, NB, SMALL>(sh.chunk.ents[wave], sh.chunk.ats[wave], a, ch, slot % a.chunk_parts);
     return;
   }
   const int64_t first = (int64_t)(blockIdx.x - a.chunk_blocks) * a.items;
@@ -288,7 +297,15 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   a.items = window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock;   // rows of dense blocks are long
   if (!die_queues)
     while (a.items > least && a.n_rows < (int64_t)a.items * 2048) a.items >>= 1;
-  const int64_t chunk_blocks = ceil_div(ceil_div(a.n_chunks, kBlock / 64), kDies) * kDies;
+  // Few chunks leave wavefront slots empty, and where a row takes 16 lanes or more a chunk of 256 entries is
+  // 16 to 64 rounds of row loads one after the other: wavefronts share it as far as that leaves eight rounds
+  // (nothing has to be combined).  R-MAT 7419, k = 73: 30.7 -> 10.3 us; 12527, k = 128: 33.2 -> 13.7; 51952,
+  // k = 128: 50.2 -> 28.5; but 30011, k = 24, in two: 17.0 -> 19.2, and twice as many wavefronts as the chip
+  // holds: Chung-Lu 104057, k = 133: 139 -> 145 us.
+  a.chunk_parts = 1;
+  if (!window_rows && !windows && !die_queues)
+    while ((int)a.chunk_parts * 16 <= s.lpr && a.n_chunks * a.chunk_parts * 2 <= kResidentWaves) a.chunk_parts *= 2;
+  const int64_t chunk_blocks = ceil_div(ceil_div(a.n_chunks * a.chunk_parts, kBlock / 64), kDies) * kDies;
   const int64_t row_blocks = ceil_div(ceil_div(a.n_rows, a.items), kDies) * kDies;
   if (chunk_blocks + row_blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
   a.runs = windows && !die_queues;
@@ -301,7 +318,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
 #define ARROW_COMMA ,
     if (window_rows) {
       if (row_blocks > 0) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA true); }
-    } else if (!windows && chunk_blocks > 0 && row_blocks > 0) {
+    } else if (!windows && chunk_blocks > 0) {
       a.chunk_blocks = (uint32_t)chunk_blocks;
       ARROW_LAUNCH(sddmm_kernel, chunk_blocks + row_blocks, );
     } else {

@@ -230,3 +230,22 @@ def test_mttkrp_items_of_unequal_length(torch, I, longest, R):
     np.add.at(ref, ti, term)
     np.add.at(bound, ti, np.abs(term))
     assert_within(A, ref, bound)
+
+
+@pytest.mark.parametrize("k", [4, 33, 64, 65, 128, 200, 300])
+def test_dot_products_of_long_rows_shared_by_wavefronts(torch, k):
+    """A few long rows of any length beside short ones: wavefronts share a chunk, some of them get nothing of it."""
+    n = 700
+    rng = np.random.default_rng(k)
+    length = rng.integers(0, 4, n)
+    length[:12] = [17, 18, 33, 49, 64, 100, 255, 256, 257, 511, 699, 700]
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    colidx = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for m in length]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    U, V = synth.normal_matrix(n, k, seed=25), synth.normal_matrix(n, k, seed=26)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, 64)
+    S = op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda()).cpu().numpy()
+    op.close()
+    rows = np.repeat(np.arange(n), length)
+    prod = U[rows].astype(np.float64) * V[colidx]
+    assert_within(S, vals * prod.sum(1), np.abs(vals) * np.abs(prod).sum(1))
