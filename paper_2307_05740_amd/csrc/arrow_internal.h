@@ -307,6 +307,6 @@ int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int3
                   const uint32_t* seg_ptr,
                   const int32_t* seg_j, const Entry* entries, int64_t n_items, const float* B,
                   int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials, int32_t R,
-                  int32_t longest, void* stream);   // longest: entries and segments of the longest item
+                  int32_t longest, int32_t average, void* stream);   // entries and segments of the longest item and of one on average
 
 }  // namespace arrow

@@ -301,7 +301,7 @@ int csf3_mttkrp(csf3_handle* h, const float* B, const float* C, float* A, int32_
                                 reinterpret_cast<const uint32_t*>(at(h->off_seg_ptr)),
                                 reinterpret_cast<const int32_t*>(at(h->off_seg_j)),
                                 reinterpret_cast<const arrow::Entry*>(at(h->off_entries)), h->n_items, B,
-                                h->J, C, h->K, A, partials, R, (int32_t)h->longest, stream);
+                                h->J, C, h->K, A, partials, R, (int32_t)h->longest, (int32_t)((h->nnz + h->n_seg) / h->n_items), stream);
   if (rc) return fail3(ARROW_EHIP, "mttkrp kernel launch: %s", hipGetErrorString((hipError_t)rc));
   if (prof) (void)hipEventRecord(h->ev[1], (hipStream_t)stream);
   rc = arrow::launch_reduce(reinterpret_cast<const uint32_t*>(at(h->off_split_ptr)),

@@ -53,7 +53,7 @@ unsigned char* static_scratch(std::string&) { reached("static_scratch"); }
 int64_t probe_out_floats(int64_t) { reached("probe_out_floats"); }
 int launch_probe_gather(const float*, int64_t, int32_t, int64_t, int, int, int64_t, float*, void*) { reached("launch_probe_gather"); }
 int launch_mttkrp(const uint32_t*, const uint32_t*, const int32_t*, const uint32_t*, const int32_t*, const Entry*,
-                  int64_t, const float*, int64_t, const float*, int64_t, float*, float*, int32_t, int32_t, void*) { reached("launch_mttkrp"); }
+                  int64_t, const float*, int64_t, const float*, int64_t, float*, float*, int32_t, int32_t, int32_t, void*) { reached("launch_mttkrp"); }
 }  // namespace arrow
 
 // ---- operands ---------------------------------------------------------------------------------------

@@ -101,9 +101,7 @@ __device__ __forceinline__ void segments(const ItemView& v, uint32_t s0, uint32_
     if (ALIKE || n[p] > 0) vmuladd(acc, x[p], b[p]);
 }
 
-constexpr int64_t kFewItems = 2048;       // a few wavefronts per compute unit
 constexpr int64_t kResidentItems = 8192;  // wavefronts the chip holds
-constexpr int64_t kLongChain = 64;        // rows one after the other in a lane group
 
 template <int VEC, int LPR, bool SMALL>
 __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
@@ -111,7 +109,7 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
     const int32_t* __restrict__ item_dst, const uint32_t* __restrict__ seg_ptr,
     const int32_t* __restrict__ seg_j, const Entry* __restrict__ ent, int64_t n_items,
     const float* __restrict__ B, const float* __restrict__ C, float* __restrict__ A,
-    float* __restrict__ partials, int R, int team) {
+    float* __restrict__ partials, int R, int team_log) {
   using V = typename Vec<VEC>::type;
   constexpr uint32_t G = 64 / LPR;
   constexpr int WPB = kBlock / 64;
@@ -119,8 +117,14 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
   __shared__ uint16_t s_ptr[WPB][kCsfItemSegs + 2];     // (16 bits: the eighth workgroup then fits the compute unit)
   __shared__ int32_t s_j[WPB][kCsfItemSegs];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-  const int64_t it = team ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * WPB + wave;
-  if (it >= n_items) return;            // whole wavefront leaves together
+  // 1 << team_log wavefronts share an item (the last workgroup's may have none)
+  const int64_t slot = ((int64_t)blockIdx.x * WPB + wave) >> team_log;
+  const int team = 1 << team_log, part = wave & (team - 1);
+  int64_t it = slot;
+  if (slot >= n_items) {
+    if (team == 1) return;                              // whole wavefront leaves together
+    it = n_items - 1;
+  }
   uint32_t s_lo = item_seg[it], e_lo = item_ent[it];
   uint32_t n_seg = item_seg[it + 1] - s_lo, n_ent = item_ent[it + 1] - e_lo;
   const int32_t dst = item_dst[it];
@@ -129,8 +133,8 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
   // with NaN (a result that announces itself) instead of being left with whatever it held.
   const bool over_limit = n_seg > (uint32_t)kCsfItemSegs || n_ent > (uint32_t)kCsfItemNnz;
   if (over_limit) { n_seg = 0; n_ent = 0; }
-  if (team) {                           // this wavefront's quarter of the segments
-    const uint32_t first = n_seg * wave / WPB, last = n_seg * (wave + 1) / WPB, s_item = s_lo;
+  if (team > 1) {                       // this wavefront's share of the segments
+    const uint32_t first = n_seg * part >> team_log, last = n_seg * (part + 1) >> team_log, s_item = s_lo;
     const uint32_t e_end = last < n_seg ? seg_ptr[s_item + last] : e_lo + n_ent;
     if (first > 0) e_lo = seg_ptr[s_item + first];
     s_lo += first;
@@ -190,14 +194,13 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
   }
 #pragma unroll
   for (int m = LPR; m < 64; m <<= 1) vadd(acc, vshfl_xor(acc, m));
-  if (team) {
+  if (team > 1) {
     // each wavefront's sum in the memory of its own entries, which it has read
     strip_sync();
-    if (wave > 0 && g == 0) vstore<VEC>(reinterpret_cast<float*>(s_ent[wave]) + lane * VEC, acc);
+    if (part > 0 && g == 0) vstore<VEC>(reinterpret_cast<float*>(s_ent[wave]) + lane * VEC, acc);
     __syncthreads();
-    if (wave > 0) return;
-#pragma unroll
-    for (int w = 1; w < WPB; ++w) vadd(acc, vload<VEC>(reinterpret_cast<const float*>(s_ent[w]) + lane % LPR * VEC));
+    if (part > 0 || slot >= n_items) return;
+    for (int w = 1; w < team; ++w) vadd(acc, vload<VEC>(reinterpret_cast<const float*>(s_ent[wave + w]) + lane % LPR * VEC));
   }
   if (over_limit) vfma(acc, __builtin_nanf(""), acc);
   if (g == 0 && lc.ok)
@@ -209,25 +212,30 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
 int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int32_t* item_dst,
                   const uint32_t* seg_ptr, const int32_t* seg_j, const Entry* entries, int64_t n_items, const float* B,
                   int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials, int32_t R,
-                  int32_t longest, void* stream) {
+                  int32_t longest, int32_t average, void* stream) {
   if (n_items <= 0) return 0;
   const Shape s = pick_shape(R, 0);
-  // Few items leave most wavefront slots empty, and the longest chain of row loads decides: the four
-  // wavefronts of a workgroup then share an item and add up in LDS (250 x 231 x 307 tensor of 17,720
-  // entries, R = 25: 8.4 -> 6.9 us).  Where every item has a wavefront on the chip at once it still pays if
-  // the longest one keeps a lane group busy for long: 159 x 2469 x 3954 of 1.55 M entries, R = 41 (150 rows):
-  // 41 -> 38 us; skewed 5882 x 1176 x 588 of 188 K, R = 30 (hub slices): 21 -> 16 us; but 1704 x 389 x 887 of
-  // 588 K, R = 14 (18 rows): 11.6 -> 14.2 us.
-  const int team = n_items <= kFewItems || (n_items <= kResidentItems && (int64_t)longest * s.lpr >= 64 * kLongChain) ? 1 : 0;
+  // Few items leave most wavefront slots empty, and the longest chain of row loads decides: wavefronts of a
+  // workgroup then share an item and add up in LDS.  Four where they all find a slot on the chip (250 x 231
+  // x 307 tensor of 17,720 entries, R = 25: 8.4 -> 6.9 us), two where two of them do and a lane group has
+  // more than a few rows to go through (1322 x 161 x 3035 of 646 K, R = 32, 45 rows: 17.0 -> 14.3 us; 1704 x
+  // 389 x 887 of 588 K, R = 14, 20 rows: 11.6 -> 11.9).  Four again where items are few enough for a slot
+  // each and the longest are much longer than most (hub slices, skewed 5882 x 1176 x 588 of 188 K, R = 30:
+  // 21.3 -> 17.5 us).
+  const int64_t chain = (int64_t)longest * s.lpr / 64;   // rows one after the other in a lane group
+  int team_log = 0;
+  if (n_items <= kResidentItems / 4) team_log = 2;
+  else if (n_items <= kResidentItems && chain >= 64 && longest > 4 * average) team_log = 2;
+  else if (n_items <= kResidentItems / 2 && chain >= 32) team_log = 1;
   const bool small = small_matrix(b_rows, R) && small_matrix(c_rows, R);
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;
-    const int64_t blocks = team ? n_items : ceil_div(n_items, kBlock / 64);
+    const int64_t blocks = ceil_div(n_items << team_log, kBlock / 64);
     if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
     dim3 grid((unsigned)blocks, (unsigned)s.slices);
 #define ARROW_LAUNCH(SM)                                                                            \
   hipLaunchKernelGGL((mttkrp_kernel<VEC, LPR, SM>), grid, dim3(kBlock), 0, (hipStream_t)stream,     \
-                     item_seg, item_ent, item_dst, seg_ptr, seg_j, entries, n_items, B, C, A, partials, (int)R, team)
+                     item_seg, item_ent, item_dst, seg_ptr, seg_j, entries, n_items, B, C, A, partials, (int)R, team_log)
     if (small) ARROW_LAUNCH(true); else ARROW_LAUNCH(false);
 #undef ARROW_LAUNCH
     return (int)hipGetLastError();

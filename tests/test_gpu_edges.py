@@ -211,7 +211,7 @@ def test_tiles_shared_by_workgroups(torch, n, b, k, fuse):
 
 
 @pytest.mark.parametrize("R", [14, 41, 128])
-@pytest.mark.parametrize("I,longest", [(2049, 60), (2049, 900), (8193, 900)])
+@pytest.mark.parametrize("I,longest", [(2047, 900), (2049, 60), (2049, 900), (4097, 900), (8190, 900)])
 def test_mttkrp_items_of_unequal_length(torch, I, longest, R):
     """Slices of one entry beside one that is cut into several items of about the same length."""
     rng = np.random.default_rng(longest)
