@@ -133,7 +133,35 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
     std::vector<uint32_t> item_seg, split_ptr;
     std::vector<int32_t> item_dst, split_y;
     split_ptr.push_back(0);
+    // How many items a slice needs when each takes what it can hold, and then as many that cost about the
+    // same (rows gathered: one per entry and one per segment).
+    auto fits = [&](int64_t at_seg, int64_t cnt, int64_t segs) {
+      return at_seg < h->n_seg && seg_i[at_seg] == seg_i[at_seg - segs] && segs < kItemSegs &&
+             (cnt == 0 || cnt + (seg_ptr[at_seg + 1] - seg_ptr[at_seg]) <= kItemNnz);
+    };
+    std::vector<std::pair<int64_t, int64_t>> need;   // of the slices with entries: (end, items)
+    need.reserve((size_t)h->slices);
+    bool split = false;
+    int64_t wanted = I - h->slices;
+    for (int64_t at_seg = 0; at_seg < h->n_seg;) {
+      const int32_t i = seg_i[at_seg];
+      int64_t items = 0;
+      while (at_seg < h->n_seg && seg_i[at_seg] == i) {
+        ++items;
+        for (int64_t cnt = 0, segs = 0; fits(at_seg, cnt, segs); ++segs, ++at_seg) cnt += seg_ptr[at_seg + 1] - seg_ptr[at_seg];
+      }
+      need.push_back({at_seg, items});
+      split = split || items > 1;
+      wanted += items;
+    }
+    // A tensor that does not fill the chip's wavefronts with full items gets shorter ones, as many as there
+    // are wavefronts: the longest chain of row loads decides then.  (Not where no slice has to be split: the
+    // launch that adds up the parts would cost more; nor below 1024 items, which four wavefronts share
+    // each.)  697 x 254 x 2633 of 466 K, R = 128: 26.1 -> 22.3 us;
+    // skewed 16640 x 2080 x 2377 of 532 K, R = 32: 24.7 -> 20.4 us; items of 128 rows are slower again.
+    const int64_t cost_max = split && wanted >= 1024 ? std::max<int64_t>(192, (nnz + h->n_seg) / 7168) : kItemNnz + kItemSegs;
     int64_t s = 0, slots = 0;
+    size_t slice = 0;
     for (int64_t i = 0; i < I; ++i) {
       const size_t first_item = item_dst.size();
       if (s >= h->n_seg || seg_i[s] != i) {          // empty slice: one item without segments
@@ -141,18 +169,10 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
         item_dst.push_back((int32_t)i);
         continue;
       }
-      // how many items the slice needs when each takes what it can hold, and then as many that cost
-      // about the same (rows gathered: one per entry and one per segment)
-      auto fits = [&](int64_t at_seg, int64_t cnt, int64_t segs) {
-        return at_seg < h->n_seg && seg_i[at_seg] == i && segs < kItemSegs &&
-               (cnt == 0 || cnt + (seg_ptr[at_seg + 1] - seg_ptr[at_seg]) <= kItemNnz);
-      };
-      int64_t end = s, least = 0;
-      while (end < h->n_seg && seg_i[end] == i) {
-        ++least;
-        for (int64_t cnt = 0, segs = 0; fits(end, cnt, segs); ++segs, ++end) cnt += seg_ptr[end + 1] - seg_ptr[end];
-      }
-      const int64_t share = ((int64_t)(seg_ptr[end] - seg_ptr[s]) + (end - s) + least - 1) / least;
+      const int64_t end = need[slice].first, cost = (int64_t)(seg_ptr[end] - seg_ptr[s]) + (end - s);
+      const int64_t items = std::max(need[slice].second, (cost + cost_max - 1) / cost_max);
+      const int64_t share = (cost + items - 1) / items;
+      ++slice;
       while (s < end) {
         item_seg.push_back((uint32_t)s);
         item_dst.push_back((int32_t)i);
