@@ -292,8 +292,10 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   const Shape s = pick_shape(a.k, 0);
   const bool small = small_matrix(v_rows, a.k);
   const hipStream_t st = (hipStream_t)stream;
-  // items per workgroup as in launch_product
-  const int least = kBlock / s.lpr < kItemsPerGroupBlock ? kBlock / s.lpr : kItemsPerGroupBlock;
+  // Items per workgroup: fewer for short lists, down to what leaves several lane groups for each item, so
+  // that all of its rounds of row loads are on their way at once (R-MAT 3416, k = 8: 10.6 -> 5.7 us; R-MAT
+  // 30124, k = 16: 17.0 -> 10.3; Chung-Lu 36286, k = 16: 19.7 -> 11.5; dense blocks, 9000, k = 16: 22.7 -> 11.3).
+  const int least = kBlock / s.lpr < 8 ? kBlock / s.lpr : 8;
   a.items = window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock;   // rows of dense blocks are long
   if (!die_queues)
     while (a.items > least && a.n_rows < (int64_t)a.items * 2048) a.items >>= 1;
