@@ -299,14 +299,15 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   a.items = window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock;   // rows of dense blocks are long
   if (!die_queues)
     while (a.items > least && a.n_rows < (int64_t)a.items * 2048) a.items >>= 1;
-  // Few chunks leave wavefront slots empty, and where a row takes 16 lanes or more a chunk of 256 entries is
-  // 16 to 64 rounds of row loads one after the other: wavefronts share it as far as that leaves eight rounds
-  // (nothing has to be combined).  R-MAT 7419, k = 73: 30.7 -> 10.3 us; 12527, k = 128: 33.2 -> 13.7; 51952,
-  // k = 128: 50.2 -> 28.5; but 30011, k = 24, in two: 17.0 -> 19.2, and twice as many wavefronts as the chip
-  // holds: Chung-Lu 104057, k = 133: 139 -> 145 us.
+  // Few chunks leave wavefront slots empty, and a chunk of 256 entries is four to 64 rounds of row loads one
+  // after the other: wavefronts share it as far as that leaves each a few rounds (nothing has to be
+  // combined).  R-MAT 7419, k = 73: 30.7 -> 10.5 us; 12527, k = 128: 33.2 -> 13.7; 51952, k = 128: 50.2 ->
+  // 28.4; 30011, k = 24: 16.5 -> 12.0; but with twice as many wavefronts as the chip holds: Chung-Lu 104057,
+  // k = 133: 139 -> 145 us.
   a.chunk_parts = 1;
+  const uint32_t most = s.lpr < 4 ? 1u : (s.lpr < 8 ? 2u : (uint32_t)s.lpr / 4);
   if (!window_rows && !windows && !die_queues)
-    while ((int)a.chunk_parts * 16 <= s.lpr && a.n_chunks * a.chunk_parts * 2 <= kResidentWaves) a.chunk_parts *= 2;
+    while (a.chunk_parts < most && a.n_chunks * a.chunk_parts * 2 <= kResidentWaves) a.chunk_parts *= 2;
   const int64_t chunk_blocks = ceil_div(ceil_div(a.n_chunks * a.chunk_parts, kBlock / 64), kDies) * kDies;
   const int64_t row_blocks = ceil_div(ceil_div(a.n_rows, a.items), kDies) * kDies;
   if (chunk_blocks + row_blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
