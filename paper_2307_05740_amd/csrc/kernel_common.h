@@ -139,6 +139,18 @@ __device__ __forceinline__ typename Vec<VEC>::type load_row(const char* base, in
   return gload<VEC>(reinterpret_cast<const float*>(base + row_offset<SMALL>(row, row_bytes, col_bytes)));
 }
 
+// a load of what is read once: it leaves the rows of X in the L2 alone
+template <typename T> __device__ __forceinline__ T stream_load(const T* p) {
+  if constexpr (sizeof(T) == 8) {
+    const unsigned long long v = __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(p));
+    T t;
+    __builtin_memcpy(&t, &v, 8);
+    return t;
+  } else {
+    return __builtin_nontemporal_load(p);
+  }
+}
+
 __device__ __forceinline__ void strip_sync() {
   // the strip is written and read by lanes of ONE wavefront: LDS executes a wavefront's
   // instructions in order, so only the compiler has to be kept from reordering

@@ -154,9 +154,9 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
     int32_t jt[2];
 #pragma unroll
     for (uint32_t q = 0; q < 2; ++q)
-      if (lane + q * 64 < n_seg) { pt[q] = seg_ptr[s_lo + lane + q * 64]; jt[q] = seg_j[s_lo + lane + q * 64]; }
+      if (lane + q * 64 < n_seg) { pt[q] = stream_load(&seg_ptr[s_lo + lane + q * 64]); jt[q] = stream_load(&seg_j[s_lo + lane + q * 64]); }
 #pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) if (lane + q * 64 < n_ent) e[q] = ent[e_lo + lane + q * 64];
+    for (uint32_t q = 0; q < 4; ++q) if (lane + q * 64 < n_ent) e[q] = stream_load(&ent[e_lo + lane + q * 64]);
 #pragma unroll
     for (uint32_t q = 0; q < 2; ++q)
       if (lane + q * 64 < n_seg) { s_ptr[wave][lane + q * 64] = (uint16_t)(pt[q] - e_lo); s_j[wave][lane + q * 64] = jt[q]; }
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
     for (uint32_t q = 0; q < 4; ++q) if (lane + q * 64 < n_ent) s_ent[wave][lane + q * 64] = e[q];
     if (n_ent > 256) {
 #pragma unroll
-      for (uint32_t q = 0; q < 4; ++q) if (lane + (q + 4) * 64 < n_ent) e[q] = ent[e_lo + lane + (q + 4) * 64];
+      for (uint32_t q = 0; q < 4; ++q) if (lane + (q + 4) * 64 < n_ent) e[q] = stream_load(&ent[e_lo + lane + (q + 4) * 64]);
 #pragma unroll
       for (uint32_t q = 0; q < 4; ++q) if (lane + (q + 4) * 64 < n_ent) s_ent[wave][lane + (q + 4) * 64] = e[q];
     }

@@ -186,7 +186,7 @@ __device__ __forceinline__ void sampled_rows(SampledShared& sh, const SampledArg
 #pragma unroll
           for (uint32_t q = 0; q < Q; ++q) {
             const uint32_t t = from[q] + t0;
-            if (t < to[q]) { e[q] = a.ent[t]; at[q] = a.emap ? a.emap[t] : t; }
+            if (t < to[q]) { e[q] = stream_load(&a.ent[t]); at[q] = a.emap ? stream_load(&a.emap[t]) : t; }
           }
 #pragma unroll
           for (uint32_t q = 0; q < Q; ++q)
