@@ -148,6 +148,10 @@ int check_hip(int rc, const char* what) {
   return fail(ARROW_EHIP, "%s: %s", what, hipGetErrorString((hipError_t)rc));
 }
 
+// Entries beyond this leave the caches to the rows of X.  Streaming loads of the short rows' entries: 6.2 M
+// entries (R-MAT 300k, k = 50) 149 -> 144 us, 40 M (Chung-Lu 2m, k = 32, five products) 2530 -> 2498; but 5 M
+// (R-MAT 171k, k = 32) 47.8 -> 51.4, 2.5 M (R-MAT 185k, k = 96) 92.8 -> 95.7.
+constexpr int64_t kEntriesOnce = 48 << 20;
 constexpr int64_t kFewChunks = 2048;   // a list this short leaves wavefront slots empty
 constexpr int64_t kFewRows = 16384;    // and so does this one
 
@@ -197,6 +201,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
       a.rows_dst = at<int32_t>(h, im.off_rows_dst);
       a.ent = ent; a.X = X; a.Xh = Xh; a.Y = Y; a.partials = partials;
       a.k = k; a.accumulate = acc ? 1 : 0;
+      a.entries_once = (im.nnz_rows + im.nnz_chunks) * (int64_t)sizeof(arrow::Entry) > kEntriesOnce;
       auto launch = [&](int parts, int32_t kc) -> int {
         return check_hip(arrow::launch_product(a, parts, im.piece_slots, im.n_rows, im.empty_slots, im.classes > 0,
                                                !im.row_major, h->n, kc, stream), "product kernel launch");

@@ -222,6 +222,7 @@ struct ProductArgs {
   uint32_t slices;
   int32_t width;                        // columns per slice
   int32_t piece_waves;                  // a piece per wavefront instead of per lane group
+  int32_t entries_once;                 // the entries are too many to be found in a cache the next time
   int32_t runs;                         // deal the wave list to the dies in runs of kDieRun workgroups
 };
 enum { kPartChunks = 1, kPartPieces = 2, kPartShort = 4, kPartAll = 7 };

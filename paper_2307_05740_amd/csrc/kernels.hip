@@ -140,7 +140,8 @@ __device__ __forceinline__ void rows_part(RowsShared& sh, const ProductArgs& a, 
     constexpr uint32_t Q = kRowsStage / kBlock;
     Entry e[Q];
 #pragma unroll
-    for (uint32_t q = 0; q < Q; ++q) if (tid + q * kBlock < total) e[q] = a.ent[e0 + tid + q * kBlock];
+    for (uint32_t q = 0; q < Q; ++q)
+      if (tid + q * kBlock < total) e[q] = a.entries_once ? stream_load(a.ent + e0 + tid + q * kBlock) : a.ent[e0 + tid + q * kBlock];
 #pragma unroll
     for (uint32_t q = 0; q < Q; ++q) if (tid + q * kBlock < total) sh.stage[tid + q * kBlock] = e[q];
     __syncthreads();
