@@ -444,6 +444,7 @@ constexpr int kWinLanes = 16;
 constexpr int kWinParts = 8;      // most workgroups that share the rows of a tile
 constexpr int kComputeUnits = 256;
 constexpr int kWinFloats = 38400; // LDS floats of a window: 150 KiB, one workgroup per compute unit
+constexpr int kWinColumns = 64;   // most columns of a slice
 
 template <int U>
 __device__ __forceinline__ int row16_bcast(int v) {   // lane U's value in every lane of its sixteen
@@ -471,7 +472,9 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
   constexpr uint32_t GPB = kWinBlock / kWinLanes;
   constexpr int QB = 4;                              // batches of sixteen window entries a row has on their way
   constexpr uint32_t NO = 4;                         // entries outside the window loaded ahead
-  __shared__ __attribute__((aligned(16))) float win[kWinFloats];
+  // The window, and behind it a row of zeros for the lanes that hold no entry: with a row of the window in
+  // its place an infinity or NaN there would reach rows of Y that have no entry in its column (0 * inf).
+  __shared__ __attribute__((aligned(16))) float win[kWinFloats + kWinColumns];
   // the slices of a tile follow each other on one die: its entries are read from memory once
   const int64_t id = blockIdx.x;
   const int64_t tile = id / (kDies * slices * parts) * kDies + id % kDies;
@@ -511,6 +514,7 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
       if (r.mid + l + q * kWinLanes < r.hi) e[q] = t_ent[r.mid + l + q * kWinLanes];
   };
   Row r = describe(grp), r_n = describe(grp + GPB);
+  if (threadIdx.x < kWinColumns) win[kWinFloats + threadIdx.x] = 0.f;
   // stage: lane group j loads window rows j, j + GPB, ... eight at a time
   for (uint32_t i0 = grp; i0 < t.win_count; i0 += 8 * GPB) {
     int32_t src[8];
@@ -537,7 +541,7 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
   V acc;
   // sixteen window entries, one per lane (`n` of them there)
   auto batch = [&](const Entry& mine, uint32_t n) {
-    int off = l < n ? mine.xrow * row_step : 0;
+    int off = l < n ? mine.xrow * row_step : kWinFloats * 4;
     float val = l < n ? mine.val : 0.f;
     // a value read through the row_newbcast modifier must not have been written by the two
     // instructions before
@@ -1172,7 +1176,7 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, co
   if (n_tiles <= 0) return 0;
   // the widest slice whose window fits: 64, 32 or 16 columns (4, 2 or 1 per lane), 8 for the widest
   // spans; no wider than k needs
-  int vec = 4, most = 64;
+  int vec = 4, most = kWinColumns;
   while (vec > 1 && (k <= most / 2 || max_span * most > kWinFloats)) { vec >>= 1; most >>= 1; }
   if (max_span * most > kWinFloats) most = 8;
   if (max_span * most > kWinFloats) return (int)hipErrorInvalidValue;

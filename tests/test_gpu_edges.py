@@ -249,3 +249,51 @@ def test_dot_products_of_long_rows_shared_by_wavefronts(torch, k):
     rows = np.repeat(np.arange(n), length)
     prod = U[rows].astype(np.float64) * V[colidx]
     assert_within(S, vals * prod.sum(1), np.abs(vals) * np.abs(prod).sum(1))
+
+
+def window_operand(b=64, blocks=9):
+    """Blocks of b rows with 1 to 33 entries inside the row's block and three anywhere."""
+    n = b * blocks
+    rng = np.random.default_rng(27)
+    cols = []
+    for i in range(n):
+        inside = i // b * b + rng.choice(b, 1 + i % 33, replace=False)
+        cols.append(np.union1d(inside, rng.integers(0, n, 3)))
+    rowptr = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int64)
+    colidx = np.concatenate(cols).astype(np.int32)
+    return n, b, rowptr, colidx, rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+
+
+@pytest.mark.parametrize("k", [8, 24, 64, 70])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_non_finite_rows_of_a_window_stay_with_their_readers(torch, k, fuse):
+    """The first row of every window (and another one) holds an infinity or NaN: rows without an entry
+    in its column stay finite, however many of a batch's places they leave empty."""
+    n, b, rowptr, colidx, vals = window_operand()
+    opt = binding.arrow_options_default(window_level_share=0.0, fuse_levels=fuse)
+    opt.window_reuse = 0.5
+    op = binding.ArrowSpMM(rowptr, colidx, vals, b, options=opt)
+    binding.arrow_self_check(op.h)
+    levels = op.levels()
+    assert levels[0]["window_tiles"] > 0 and (fuse or any(L["window_tiles"] for L in levels[1:]))
+    X = synth.normal_matrix(n, k, seed=28)
+    rng = np.random.default_rng(k)
+    for level in range(len(levels)):
+        perm, r, c, _ = binding.arrow_export_level(op.h, level)
+        diag = c[(r >= b) & (c >= b) & (r // b == c // b)]
+        for block in np.unique(diag // b):
+            inside = diag[diag // b == block]
+            for q, bad in ((inside.min(), np.inf), (rng.choice(inside), (-np.inf, np.nan)[block % 2])):
+                X[perm[q], (q + level) % k] = bad
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    op.close()
+    Y = Y.cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        term = vals[:, None].astype(np.float64) * X[colidx]
+        ref = np.add.reduceat(term, rowptr[:-1])                  # no row is empty
+    bound = np.add.reduceat(np.abs(np.where(np.isfinite(term), term, 0.0)), rowptr[:-1])
+    fin = np.isfinite(ref)
+    assert 0.5 < fin.mean() < 1.0
+    assert np.array_equal(np.isnan(Y), np.isnan(ref)) and np.array_equal(Y[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32))
+    assert np.all(np.abs(Y[fin] - ref[fin]) <= TOL * bound[fin])
