@@ -396,7 +396,7 @@ class ArrowSpMM:
             arrow_upload(self.h, self._image.data_ptr(), self._image.numel(), self._stream())
             torch.cuda.current_stream().synchronize()
         self._ws = None
-        self._ws_k = self._ws_second_k = 0
+        self._ws_k = 0
         self._map = None
 
     def repack(self, options: arrow_options_t | None) -> None:
@@ -409,14 +409,15 @@ class ArrowSpMM:
         return _current_stream(self._torch, self.device)
 
     def _ensure_workspace(self, k: int, second: bool = False) -> None:
-        """Bind a workspace for k columns; `second`: with room for another n x k buffer, if there is memory for it."""
-        if self._ws is not None and self._ws_k >= k and (not second or self._ws_second_k >= k):
+        """Bind a workspace for k columns; `second`: with room for another n x k buffer, if there is memory for it.
+        One that is bound and suffices without that room stays: a captured graph may hold its address, and a
+        call may be captured itself."""
+        if self._ws is not None and self._ws_k >= k:
             return
         torch = self._torch
         torch.cuda.current_stream(self.device).synchronize()
-        k = max(k, self._ws_k)
         nbytes = max(arrow_workspace_bytes(self.h, k), 256)
-        extra = -(-self.n * k * 4 // 256) * 256 if second or self._ws_second_k else 0
+        extra = -(-self.n * k * 4 // 256) * 256 if second else 0
         self._ws = None
         try:
             self._ws = torch.empty(nbytes + extra, dtype=torch.uint8, device=self.device)
@@ -425,7 +426,6 @@ class ArrowSpMM:
                 raise
             self._ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self._ws_k = k
-        self._ws_second_k = k if extra else 0     # asked for, whether or not there was room
         arrow_set_workspace(self.h, self._ws.data_ptr(), self._ws.numel())
 
     def levels(self):

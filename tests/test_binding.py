@@ -1,0 +1,51 @@
+"""When the binding allocates and binds a workspace (on the CPU: the calls are recorded, nothing is launched)."""
+import types
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2307_05740_amd import binding
+
+
+@pytest.fixture
+def handle(monkeypatch):
+    """An ArrowSpMM without a device, and the list of what its workspace handling does."""
+    did = []
+
+    def empty(nbytes, dtype, device):
+        did.append(("empty", nbytes))
+        return torch.empty(nbytes, dtype=dtype)
+
+    stream = types.SimpleNamespace(synchronize=lambda: did.append(("synchronize",)))
+    op = binding.ArrowSpMM.__new__(binding.ArrowSpMM)
+    op._torch = types.SimpleNamespace(cuda=types.SimpleNamespace(current_stream=lambda device: stream), empty=empty,
+                                      uint8=torch.uint8, OutOfMemoryError=torch.OutOfMemoryError)
+    op.device, op._ws, op._ws_k = torch.device("cpu"), None, 0
+    op.n = 300
+    op.h = binding.arrow_decompose(np.arange(301, dtype=np.int64), np.arange(300, dtype=np.int32), np.ones(300, np.float32), 64)
+    monkeypatch.setattr(binding, "arrow_set_workspace", lambda h, ptr, nbytes: did.append(("bind", ptr, nbytes)))
+    yield op, did
+    binding.arrow_destroy(op.h)
+    op.h = 0
+
+
+def test_a_workspace_that_suffices_stays(handle):
+    """A captured graph may hold its address, and a call that finds it may be captured itself: no second buffer is
+    worth another workspace."""
+    op, did = handle
+    op._ensure_workspace(24)
+    ws = op._ws
+    del did[:]
+    for k, second in ((24, True), (24, False), (7, True), (1, False)):
+        op._ensure_workspace(k, second=second)
+    assert did == [] and op._ws is ws
+
+
+def test_a_second_buffer_is_asked_for_only_where_it_is_used(handle):
+    op, did = handle
+    extra = []
+    for k, second in ((8, True), (16, False), (32, True)):
+        op._ensure_workspace(k, second=second)
+        extra.append(op._ws.numel() - max(binding.arrow_workspace_bytes(op.h, k), 256))
+    assert extra == [-(-300 * 8 * 4 // 256) * 256, 0, -(-300 * 32 * 4 // 256) * 256]

@@ -552,6 +552,36 @@ def test_product_under_graph_capture(torch):
     op.close()
 
 
+def test_graphs_outlive_a_chained_product_of_odd_length(torch):
+    """A graph captured from products of k columns is replayed after an eager A^3 X with the same k; and A^3 X is
+    captured on a handle that so far has only multiplied once."""
+    w = synth.make_config(0)
+    op = binding.ArrowSpMM(*csr_of(w), w.b)
+    X = torch.from_numpy(synth.normal_matrix(w.n, 24, seed=910)).cuda()
+    Y, Z = torch.empty_like(X), torch.empty_like(X)
+    op.spmm(X, Y)                                       # sizes the workspace
+    torch.cuda.synchronize()
+    once, chain = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(once):
+        op.spmm(X, Y)
+    with torch.cuda.graph(chain):
+        Z.copy_(X)
+        op.spmm_iter(Z, 3)
+    for t in range(3):
+        X.copy_(torch.from_numpy(synth.normal_matrix(w.n, 24, seed=911 + t)))
+        Ze = X.clone()
+        op.spmm_iter(Ze, 3)                             # eager work before the replays
+        other = [torch.full_like(X, float("nan")) for _ in range(8)]   # what a freed workspace would be given to
+        once.replay()
+        chain.replay()
+        torch.cuda.synchronize()
+        assert all(bool(o.isnan().all()) for o in other), t
+        assert torch.equal(Y, op.spmm(X)) and torch.equal(Z, Ze), t
+        Yref, B = oracle.spmm(*csr_of(w), X.cpu().numpy())
+        assert_within(Y.cpu().numpy(), Yref, B)
+    op.close()
+
+
 def test_gather_probe_runs_and_validates(torch):
     """The bare row gather that bench.py uses as its yardstick: every mode launches and completes;
     regions that do not fit, unsupported k and short output buffers are refused on the host."""
