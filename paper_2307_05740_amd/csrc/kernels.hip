@@ -292,15 +292,17 @@ __global__ __launch_bounds__(kBlock, 6) void product_kernel(const ProductArgs a)
 // Copies the lanes' 4 or 16 bytes from `from` to consecutive places at `to` in LDS (the same for the whole
 // wavefront) without registers in between.  In assembly because the compiler waits for such a copy before
 // the next read of LDS, whatever it reads: the caller waits (vmcnt) before it reads what was copied.
-// (m0 holds nothing between instructions on this target.)
-__device__ __forceinline__ void copy_to_lds16(const void* from, const void* to) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :: "v"(from), "s"(__builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(to))) : "memory");
-}
-__device__ __forceinline__ void copy_to_lds4(const void* from, const void* to) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-               :: "v"(from), "s"(__builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(to))) : "memory");
-}
+// m0, which holds the place in LDS, gets back what it held: the compiler reserves the register and does
+// not heed it in a list of clobbers.
+#define ARROW_TO_LDS(INSTRUCTION)                                                                                     \
+  int m0_was;                                                                                                         \
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\t" INSTRUCTION " %1, off\n\ts_mov_b32 m0, %0"        \
+               : "=&s"(m0_was)                                                                                        \
+               : "v"(from), "s"(__builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(to)))       \
+               : "memory")
+__device__ __forceinline__ void copy_to_lds16(const void* from, const void* to) { ARROW_TO_LDS("global_load_lds_dwordx4"); }
+__device__ __forceinline__ void copy_to_lds4(const void* from, const void* to) { ARROW_TO_LDS("global_load_lds_dword"); }
+#undef ARROW_TO_LDS
 
 struct alignas(16) FlowShared {
   Entry stage[2][kRowsStage + 8];      // a batch's entries from an even one on; up to seven past the last are read
