@@ -1125,9 +1125,12 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
   }
   a.slices = (uint32_t)s.slices;
   a.width = s.width;
-  // stencils, meshes, bands: hardly any long rows, and enough batches for every compute unit to have several in turn
+  // Stencils, meshes, bands: hardly any long rows or pieces of them, whichever launch those are in, and enough
+  // batches for every compute unit to have several in turn.  (1m rows of 3 to 8 random entries and one in
+  // twenty of 20 to 40, k = 96: 448 us with the flow kernel, 443 without; one in five: 735 and 727; 200k rows,
+  // one in fifty of 20 to 40 and one in 500 of 300, k = 128: 116 and 119.)
   const bool flow = a.longest_short * (int64_t)kItemsPerGroupBlock <= kRowsStage &&
-                    a.count[2] >= kItemsPerGroupBlock * kFlowLeast && a.count[2] >= 64 * (n_long + a.count[1]);
+                    a.count[2] >= kItemsPerGroupBlock * kFlowLeast && a.count[2] >= 64 * (n_long + n_pieces);
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
     if (windows && a.blocks[0] > 0) {
