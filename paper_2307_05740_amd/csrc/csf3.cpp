@@ -12,11 +12,13 @@
 #include <omp.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <memory>
 #include <new>
 #include <string>
 #include <utility>
@@ -106,8 +108,7 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
     }
     auto at = [&](int64_t p) -> int64_t { return sorted ? p : (int64_t)order[p]; };
 
-    csf3_handle* h = new (std::nothrow) csf3_handle;
-    if (!h) return fail3(ARROW_ENOMEM, "out of host memory");
+    auto h = std::make_unique<csf3_handle>();
     h->I = I; h->J = J; h->K = K; h->nnz = nnz;
     // segments: a new one starts where the fibre changes or the current one is full
     std::vector<uint32_t> seg_ptr;
@@ -187,6 +188,15 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
       }
     }
     item_seg.push_back((uint32_t)h->n_seg);
+    // the kernel stages an item in fixed-size LDS arrays: make sure no item exceeds them
+    for (size_t t = 0; t + 1 < item_seg.size(); ++t) {
+      const int64_t segs = (int64_t)item_seg[t + 1] - (int64_t)item_seg[t];
+      const int64_t ents = (int64_t)seg_ptr[item_seg[t + 1]] - (int64_t)seg_ptr[item_seg[t]];
+      h->longest = std::max(h->longest, segs + ents);
+      if (segs < 0 || segs > kItemSegs || ents < 0 || ents > kItemNnz) {
+        return fail3(ARROW_EINTERNAL, "work item %zu holds %lld segments / %lld entries", t, (long long)segs, (long long)ents);
+      }
+    }
     // inside every item the segments are ordered by length, longest first (equal ones by j), so that the
     // lane groups of the wavefront that owns it work on equally long ones; the entries move along
     std::vector<uint32_t> from((size_t)h->n_seg);            // segment -> first entry in (i, j, k) order
@@ -194,19 +204,19 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
       const int64_t n_it = (int64_t)item_dst.size();
 #pragma omp parallel
       {
-        std::vector<std::pair<uint32_t, int32_t>> segs;       // (first entry, j), in the new order
-        std::vector<uint32_t> len, at_len(kSegMax + 2);
+        std::array<std::pair<uint32_t, int32_t>, kItemSegs> segs;   // (first entry, j), in the new order
+        std::array<uint32_t, kItemSegs> len;                        // (nothing here may throw)
+        std::array<uint32_t, kSegMax + 2> at_len;
 #pragma omp for schedule(static)
         for (int64_t it = 0; it < n_it; ++it) {
           const uint32_t s0 = item_seg[it], s1 = item_seg[it + 1], n_s = s1 - s0;
           if (n_s == 0) continue;
-          len.resize(n_s); segs.resize(n_s);
           std::fill(at_len.begin(), at_len.end(), 0u);
           for (uint32_t q = 0; q < n_s; ++q) { len[q] = seg_ptr[s0 + q + 1] - seg_ptr[s0 + q]; ++at_len[(size_t)(kSegMax - len[q]) + 1]; }
           for (size_t q = 1; q < at_len.size(); ++q) at_len[q] += at_len[q - 1];
           uint32_t first = seg_ptr[s0];
           for (uint32_t q = 0; q < n_s; ++q) segs[at_len[(size_t)(kSegMax - len[q])]++] = {seg_ptr[s0 + q], seg_j[s0 + q]};
-          std::sort(len.begin(), len.end(), std::greater<uint32_t>());
+          std::sort(len.begin(), len.begin() + n_s, std::greater<uint32_t>());
           for (uint32_t q = 0; q < n_s; ++q) {
             from[s0 + q] = segs[q].first; seg_j[s0 + q] = segs[q].second;
             if (q) seg_ptr[s0 + q] = first;                   // the item's entry range stays where it is
@@ -215,17 +225,7 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
         }
       }
     }
-    // the kernel stages an item in fixed-size LDS arrays: make sure no item exceeds them
-    for (size_t t = 0; t + 1 < item_seg.size(); ++t) {
-      const int64_t segs = (int64_t)item_seg[t + 1] - (int64_t)item_seg[t];
-      const int64_t ents = (int64_t)seg_ptr[item_seg[t + 1]] - (int64_t)seg_ptr[item_seg[t]];
-      h->longest = std::max(h->longest, segs + ents);
-      if (segs < 0 || segs > kItemSegs || ents < 0 || ents > kItemNnz) {
-        delete h;
-        return fail3(ARROW_EINTERNAL, "work item %zu holds %lld segments / %lld entries", t, (long long)segs, (long long)ents);
-      }
-    }
-    if (slots > 0x7fffffffLL || item_dst.size() > 0x7fffff00ULL) { delete h; return fail3(ARROW_EINVAL, "too many work items"); }
+    if (slots > 0x7fffffffLL || item_dst.size() > 0x7fffff00ULL) return fail3(ARROW_EINVAL, "too many work items");
     h->n_items = (int64_t)item_dst.size();
     h->n_split = (int64_t)split_y.size();
     h->n_partials = slots;
@@ -265,7 +265,7 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
         ent[e].val = tv[q];
       }
     h->build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-    *out = h;
+    *out = h.release();
     return ARROW_OK;
   } catch (const std::bad_alloc&) {
     return fail3(ARROW_ENOMEM, "out of host memory while building the fibre image");

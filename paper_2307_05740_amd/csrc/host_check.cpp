@@ -8,10 +8,12 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -55,6 +57,19 @@ int launch_probe_gather(const float*, int64_t, int32_t, int64_t, int, int, int64
 int launch_mttkrp(const uint32_t*, const uint32_t*, const int32_t*, const uint32_t*, const int32_t*, const Entry*,
                   int64_t, const float*, int64_t, const float*, int64_t, float*, float*, int32_t, int32_t, int32_t, void*) { reached("launch_mttkrp"); }
 }  // namespace arrow
+
+// ---- memory that runs out ---------------------------------------------------------------------------
+static std::atomic<long> allocations_left{-1};       // the one after these fails; none does where it is negative
+void* operator new(size_t bytes, const std::nothrow_t&) noexcept {
+  if (allocations_left.load() >= 0 && allocations_left.fetch_sub(1) == 0) return nullptr;
+  return std::malloc(bytes ? bytes : 1);
+}
+void* operator new(size_t bytes) {
+  if (void* p = operator new(bytes, std::nothrow)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 // ---- operands ---------------------------------------------------------------------------------------
 namespace {
@@ -259,6 +274,17 @@ int main(int argc, char** argv) {
       csf3_info_t ci;
       EXPECT(csf3_info(t, &ci) == 0 && ci.nnz == 3000 && ci.I == 40, "csf3_info");
       EXPECT(csf3_device_bytes(t) > 0 && csf3_workspace_bytes(t, 16) > 0, "csf3 sizes");
+      csf3_destroy(t);
+    }
+    // whichever allocation of the build fails: an error (or the build does without it), and nothing is left behind
+    bool failed = true;
+    for (long n = 0; failed; ++n) {
+      t = nullptr;
+      allocations_left = n;
+      const int rc = csf3_build(40, 40, 7, (int64_t)tv.size(), ti.data(), tj.data(), tk.data(), tv.data(), &t);
+      failed = allocations_left < 0;
+      allocations_left = -1;
+      EXPECT(rc == ARROW_OK ? t != nullptr : rc == ARROW_ENOMEM && !t && failed, "csf3_build with %ld allocations", n);
       csf3_destroy(t);
     }
     tk[5] = 7;
