@@ -19,8 +19,10 @@ layout instead (one step = one ``arrow_sddmm`` call); the default, and the headl
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -151,18 +153,32 @@ def hit_path_rate(torch, binding, k, dev):
     return round(n * per_row / (min(ms) * 1e-3) / 1e9, 2)
 
 
-def stored_traffic(path, launch_nnz, launch_items):
-    """Counter bytes of a launch from a stored rocprofv3 summary, or None when there is none or when
-    it was taken on another image (its entry / item counts differ from the live ones)."""
+def kernel_code(op):
+    """Fingerprint of the sources that decide what an operation's kernels move: the kernels, what lays
+    out their input and what launches them, without comments and white space."""
+    files = {"spmm": ("kernels.hip", "decompose.cpp", "layout.cpp", "abi.cpp"),
+             "sddmm": ("sddmm.hip", "kernels.hip", "decompose.cpp", "layout.cpp", "abi.cpp"),
+             "mttkrp": ("mttkrp.hip", "csf3.cpp")}[op]
+    h = hashlib.sha256()
+    for name in files + ("kernel_common.h", "arrow_internal.h"):
+        with open(os.path.join(ROOT, "paper_2307_05740_amd", "csrc", name)) as f:
+            h.update(re.sub(r"//[^\n]*|/\*.*?\*/|\s+", "", f.read(), flags=re.S).encode())
+    return h.hexdigest()[:16]
+
+
+def stored_traffic(path, op, launch):
+    """The stored rocprofv3 counter record of a launch and where it is, or None where there is none or it
+    was taken on another image (its entry / item counts differ from the live ones) or with other kernels."""
     if not os.path.exists(path):
         return None, None
     with open(path) as f:
         rec = json.load(f)
     src = os.path.relpath(path, ROOT)
-    fp = rec.get("launch")
-    if not fp or fp.get("nnz") != launch_nnz or fp.get("items") != launch_items:
+    if rec.get("launch") != launch:
         return None, src + " (stale: taken on another packed image; ignored)"
-    return rec.get("hbm_bytes_per_launch"), src
+    if rec.get("code") != kernel_code(op):
+        return None, src + " (stale: taken with other kernels; ignored)"
+    return rec, src
 
 
 def bench_mttkrp(args, torch, binding, synth, dev) -> int:
@@ -216,19 +232,19 @@ def bench_mttkrp(args, torch, binding, synth, dev) -> int:
     alg = (8 * nnz + 8 * info["segments"] + 8 * info["items"] + row * (info["distinct_j"] + info["distinct_k"])
            + row * info["items"])
     achieved = alg / (k_ms * 1e-3) / 1e9 if k_ms > 0 else 0.0
-    traffic = None
-    tpath = os.path.join(ROOT, "profiles", f"hbm_traffic_mttkrp_kernel_{w.name}.json")
-    if os.path.exists(tpath):
-        with open(tpath) as f:
-            traffic = json.load(f).get("hbm_bytes_per_launch")
+    launch = {"nnz": int(nnz), "items": int(info["items"])}
+    rec, traffic_source = stored_traffic(os.path.join(ROOT, "profiles", f"hbm_traffic_mttkrp_{w.name}.json"), "mttkrp", launch)
+    traffic = rec["hbm_bytes_per_launch"] if rec else None
     roofline = {"bound": "hbm", "kernel": "mttkrp_kernel", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "avg_launch_ms": round(k_ms, 4), "launches_per_step": 1, "algorithmic_bytes_per_launch": int(alg),
-                "traffic_source": os.path.relpath(tpath, ROOT) if traffic else None,
-                # the HBM figure is the required one, but it is not what holds this kernel back: its
-                # counter traffic is about its algorithmic bytes, the factor rows live in L2, and the
-                # time goes into gathering them from there
-                "limiter": "L2-to-L1 gather of factor rows (HBM traffic ~ algorithmic bytes)",
+                "traffic_source": traffic_source, "launch": launch,
+                # the HBM figure is the required one, but the time goes into gathering factor rows: out of the L2
+                # where the factors fit it (the counter traffic is then about the algorithmic bytes), else
+                # from behind it
+                "limiter": ("unknown: no counter record of these kernels" if not rec else
+                            "L2-to-L1 gather of factor rows (HBM traffic ~ algorithmic bytes)" if traffic < 2 * alg else
+                            "gather of factor rows that miss the L2"),
                 "gathered_rows_per_launch": int(nnz + info["fibers"]), "row_bytes": row,
                 "gather_Grows_per_s": round((nnz + info["fibers"]) / (k_ms * 1e-3) / 1e9, 2) if k_ms > 0 else None}
     cpu_baseline = None
@@ -396,14 +412,18 @@ def main() -> int:
                 "corner": "corner_tiles"}.get(dom[0])
     launch_nnz = levels[dom[1]][nnz_key] if nnz_key else 0
     launch_items = levels[dom[1]][item_key] if item_key else 0
-    tpath = os.path.join(ROOT, "profiles", f"hbm_traffic_{kname}_kernel_level{dom[1]}_{w.name}.json")
-    traffic, traffic_source = stored_traffic(tpath, launch_nnz, launch_items)
-    roofline = {"bound": "hbm", "kernel": f"{kname}_kernel (level {dom[1]})", "achieved": round(achieved, 1),
+    launch = {"nnz": int(launch_nnz), "items": int(launch_items)}
+    tpath = os.path.join(ROOT, "profiles", f"hbm_traffic_{kname}_level{dom[1]}_{w.name}.json")
+    rec, traffic_source = stored_traffic(tpath, args.op, launch)
+    traffic = rec["hbm_bytes_per_launch"] if rec else None
+    # (the launch of the short rows picks the flow or the product kernel: the record says which)
+    kernel = re.sub(r"^.*::|<.*$", "", rec["kernel"]) if rec else kname + " launch" if kname == "rows" else kname + "_kernel"
+    roofline = {"bound": "hbm", "kernel": f"{kernel} (level {dom[1]})", "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "traffic_source": traffic_source,
                 "avg_launch_ms": round(avg_ms, 4), "launches_per_step": 1,
                 "algorithmic_bytes_per_launch": int(bytes_per_launch),
-                "launch": {"nnz": int(launch_nnz), "items": int(launch_items)}}
+                "launch": launch}
     if traffic and avg_ms > 0:
         # the counter bytes over the live launch time, and how much of them the method asks for
         roofline["counter_GBps"] = round(traffic / (avg_ms * 1e-3) / 1e9, 1)
