@@ -148,9 +148,14 @@ int check_hip(int rc, const char* what) {
   return fail(ARROW_EHIP, "%s: %s", what, hipGetErrorString((hipError_t)rc));
 }
 
-// Entries beyond this leave the caches to the rows of X.  Streaming loads of the short rows' entries: 6.2 M
-// entries (R-MAT 300k, k = 50) 149 -> 144 us, 40 M (Chung-Lu 2m, k = 32, five products) 2530 -> 2498; but 5 M
-// (R-MAT 171k, k = 32) 47.8 -> 51.4, 2.5 M (R-MAT 185k, k = 96) 92.8 -> 95.7.
+// Bytes of entries from which on the short rows' entries are loaded with the streaming hint.  The line is drawn
+// where it measured best, not derived from a cache's size: the L2s hold 32 MB, the cache behind them 256 MB.  Where
+// the operand comes from memory the hint gains: R-MAT 300k (6.6 M entries, 53 MB), k = 50, 148 -> 144 us; Chung-Lu
+// 2m (287 MB), k = 32, five products 2584 -> 2518; six operands of 54 to 91 MB in turn 0 to 2 %.  Where one product
+// with the same operand follows another and the cache behind the L2s still holds its entries it costs: R-MAT 300k,
+// k = 64, 118.6 -> 121.7 us, R-MAT 500k (89 MB), k = 16, 92.1 -> 94.8; from about 400 MB of entries, X and Y
+// together it gains there too (R-MAT 600k, k = 128, 425 -> 421).  Below the line it costs more: R-MAT 171k (37 MB),
+// k = 64, 80.1 -> 84.2 us.
 constexpr int64_t kEntriesOnce = 48 << 20;
 constexpr int64_t kFewChunks = 2048;   // a list this short leaves wavefront slots empty
 constexpr int64_t kFewRows = 16384;    // and so does this one

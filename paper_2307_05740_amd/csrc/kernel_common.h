@@ -98,8 +98,8 @@ __device__ __forceinline__ LaneColumns lane_columns(int l, int c0, int k, int wi
 
 // Store of a result row that this product does not read again: the non-temporal hint keeps the
 // 4 k bytes per output row from displacing rows of X in the L2 (measured on the R-MAT workload:
-// rows kernel 3.97 -> 3.71 ms, reduction 0.38 -> 0.33 ms; the same hint on loads of X rows or of
-// the entry stream made the product slower).
+// short rows 3.97 -> 3.71 ms, reduction 0.38 -> 0.33 ms; the same hint on loads of X rows made the
+// product slower; for the entries see stream_load).
 template <int VEC>
 __device__ __forceinline__ void vstore_stream(float* p, typename Vec<VEC>::type v);
 template <> __device__ __forceinline__ void vstore_stream<1>(float* p, float v) { __builtin_nontemporal_store(v, p); }
@@ -139,7 +139,9 @@ __device__ __forceinline__ typename Vec<VEC>::type load_row(const char* base, in
   return gload<VEC>(reinterpret_cast<const float*>(base + row_offset<SMALL>(row, row_bytes, col_bytes)));
 }
 
-// a load of what is read once: it leaves the rows of X in the L2 alone
+// A load of what is read once: it leaves the rows of X in the L2 alone.  Entries of the order-3 product and of
+// window rows always, those of the product's short rows from a size on (kEntriesOnce); the entries of the wave
+// list, which a column pass reads again, never.
 template <typename T> __device__ __forceinline__ T stream_load(const T* p) {
   if constexpr (sizeof(T) == 8) {
     const unsigned long long v = __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(p));

@@ -315,8 +315,8 @@ static_assert(kItemsPerGroupBlock == 64 && kBlock == 256, "one wavefront per des
 // descriptors of the one after it are copied to LDS meanwhile.  Of the row of X that an entry of a stencil
 // reads, one in five comes from memory and the others from the L2, so it is the latency of few bytes that
 // bounds the time: three latencies per batch with the copies ahead, of which two are for rows of X, where
-// there were four.  (Grid of 1024 x 1024, k = 32, X and Y not in any cache: 82.1 -> 69.7 us, 4.8 TB/s; one
-// batch per workgroup 73.8, two 70.6, eight 74.5.  Beside long rows, whose misses fill the memory pipes, the
+// there were four.  (Grid of 1024 x 1024, k = 32, X and Y not in any cache: 80.1 -> 65.4 us, 4.8 TB/s; when
+// it was built four batches took 69.7, one 73.8, two 70.6, eight 74.5.  Beside long rows, whose misses fill the memory pipes, the
 // launch of its own costs more than this gives: three products of R-MAT 1m, k = 64, 1184 -> 1227 us.)
 template <int VEC, int LPR, bool SMALL>
 __global__ __launch_bounds__(kBlock, 6) void flow_kernel(const ProductArgs a) {
@@ -438,8 +438,8 @@ __global__ __launch_bounds__(kBlock) void chunks_kernel(const ProductArgs a) {
 // An entry costs five vector instructions and one LDS read for four rows of Y.  The next row's
 // entries are on their way while the current one is worked on.  With the entries read four at a time
 // by every lane and windows of 64 KiB in slices of 32 columns, two memory latencies stood before
-// every fourth entry; 512 blocks of 512 with 48 entries per row, k = 128: 250 -> 143 us, of which the
-// LDS reads (6.4 GB at 128 B per cycle and compute unit) take two thirds.
+// every fourth entry; 512 blocks of 512 with 48 entries per row, k = 128: 250 -> 145 us, of which the
+// LDS reads (6.4 GB at the 78 TB/s that all compute units together reach) take 82.
 // ---------------------------------------------------------------------------
 constexpr int kWinBlock = 1024;   // threads of a window-kernel workgroup: 16 wavefronts share one staged window
 constexpr int kWinLanes = 16;

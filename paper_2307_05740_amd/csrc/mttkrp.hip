@@ -20,9 +20,10 @@
 // SIMD instead of eight is 12 % slower).  In the order of j a round lasted as long as the
 // longest of G random lengths, and with the masks 16 vector instructions stood for every row load, of
 // which 5 do the work: the kernel was bound by instruction issue (83 % of the cycles).  Uniform 4096^3
-// tensor, 68.7 M entries in 16.5 M fibres, R = 64: 1078 -> 855 us; what it gathers (21.8 GB from the L2 at
-// 64 B per cycle and compute unit) takes 630 us.  Skewed tensor, fibres of one entry, R = 32: 497 -> 495 us,
-// bound by the rows of B and C (8 MB each) that miss the L2.
+// tensor, 68.7 M entries in 16.5 M fibres, R = 64: 1078 -> 850 us; what it gathers (21.8 GB from the L2 at
+// 64 B per cycle and compute unit) takes 630 us.  The skewed tensor of 16.4 M fibres of one entry, R = 32, gains
+// nothing (507 us): B and C are 8 MiB each and an L2 is 4 MiB, so that 68 % of the requests miss it, 3.3 GB that
+// come at 6.6 TB/s.
 //
 // At the end the lane groups are combined with wavefront shuffles and the result goes to row i of A
 // or, for a slice cut into several items, to a partial vector that the reduction kernel sums in a

@@ -10,8 +10,9 @@
 // the matrix product's 64-column slices (a dot product needs the whole row), and writes 4 bytes to a
 // place of its own.  The entries' places in S used to be loaded when their dot products were ready, a
 // second memory latency after every batch of rows, and the entries of a list one batch at a time; both
-// are now on their way while the batch before is worked on (R-MAT 1m, k = 128: chunks 944 -> 867 us, short
-// rows and pieces 448 -> 416 us, both then at 6.7 TB/s of rows that miss the L2; R-MAT 30k, k = 24: 47 -> 19 us).
+// are now on their way while the batch before is worked on (R-MAT 1m, k = 128: chunks 944 -> 868 us, short
+// rows and pieces 448 -> 363 us, at 6.4 and 7.1 TB/s of what crosses the L2's boundary; R-MAT 30k, k = 24: 47 ->
+// 19 us, 12 since wavefronts share chunks, launch_sddmm).
 #include <hip/hip_runtime.h>
 
 #include <climits>
