@@ -310,4 +310,28 @@ int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int3
                   int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials, int32_t R,
                   int32_t longest, int32_t average, void* stream);   // entries and segments of the longest item and of one on average
 
+// The other form of the fibre image, for factors whose rows all fit the LDS of a compute unit four columns at a
+// time (resident_kernel in mttkrp.hip): the segments of an item side by side, one per lane, as a sequence of
+// STEPS, in each of which a lane reads one row from LDS and has a value for it.  In LDS lie the K rows of C, a
+// row of zeros (which the steps that fill up read) and the J rows of B.  A bit per step says that its rows are
+// rows of B, which end a batch of 64 segments.  Steps come in blocks of eight, an item has at least one.
+constexpr int kCsfRowsInLds = 10200;    // rows of four columns, 16 bytes each
+constexpr int kCsfBlockSteps = 8;
+constexpr int kCsfBlocksAhead = 4;      // blocks the kernel may read past the last one
+struct ResidentBlock {
+  // of two steps: the first one's row << 4, the second one's << 18; bits 0 and 1: their rows are of B
+  struct alignas(16) Offsets { uint32_t pair[4]; };
+  struct alignas(16) Values { float v[4]; };
+  Offsets offsets[64];                  // by lane
+  Values values[2][64];
+};
+static_assert(kCsfRowsInLds < 1 << 14, "bits of a row");
+struct ResidentItem {
+  uint32_t block, blocks;   // first block and their number
+  int32_t dst;              // as in the other form
+};
+int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* blocks, int64_t n_items, int64_t n_blocks,
+                           const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials,
+                           int32_t R, void* stream);
+
 }  // namespace arrow

@@ -8,6 +8,7 @@
 // most kItemNnz entries and kItemSegs segments, one per wavefront, with a destination: row i of A when the slice is one
 // item, else a partial-vector slot that the reduction pass sums in a fixed order.  Every i in
 // [0, I) has at least one item (an empty one stores zeros), so A is fully overwritten.
+// Tensors whose factors fit the LDS get another form (pack_resident).
 #include <hip/hip_runtime.h>
 #include <omp.h>
 
@@ -58,12 +59,197 @@ struct csf3_handle {
   std::vector<unsigned char> bytes;   // packed host copy of the image
   size_t off_seg_ptr = 0, off_seg_j = 0, off_item_seg = 0, off_item_dst = 0, off_item_ent = 0, off_split_ptr = 0,
          off_split_y = 0, off_entries = 0;
+  bool resident = false;              // the image is in the form for factors that fit the LDS
+  size_t off_items = 0;
+  int64_t n_blocks = 0;
   unsigned char* dev = nullptr;
   unsigned char* ws = nullptr;
   size_t ws_bytes = 0;
   bool profiling = false, profiled = false;
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};   // before the kernel, between, after the reduction
 };
+
+namespace {
+
+// Where the resident form pays (both forms measured, us, R = 8 / 64 / 128):
+//   1300^3 of 2.2 M, 1.17 steps per 64 rows     18.6 / 43.6 / 76.6 -> 11.5 / 31.8 / 52.2
+//   1000^3 of 1.0 M, 1.26                       11.2 / 23.1 / 38.5 ->  8.9 / 19.4 / 31.7
+//   520 x 1000 x 1000 of 520 K, 1.26             9.5 / 16.6 / 24.5 ->  8.2 / 12.7 / 19.4
+//   4096 x 2000 x 300 of 2.5 M, 1.37            22.4 / 54.8 / 93.8 -> 11.7 / 47.4 / 88.8
+// and where it does not: fill (4000 x 4000 x 128 of 2.0 M, 1.52: 20.5 / 46.1 / 79.3 -> 12.2 / 47.1 / 86.1), few items
+// (128 x 4000 x 1000 of 512 K, 128 items: 9.6 / 17.0 / 28.5 -> 14.1 / 18.1 / 19.8), few entries to pay for
+// copying the factors to LDS (1000 x 1000 x 200 of 200 K: 7.6 / 10.6 / 14.6 -> 6.6 / 11.6 / 18.5).
+constexpr int64_t kResidentNnz = 1 << 19;
+constexpr int64_t kResidentItems = 512;
+constexpr double kResidentFill = 1.4;
+constexpr int64_t kResidentSegs = 4096;    // segments of an item
+// Lanes whose 16-byte reads of LDS are served together (found by timing reads whose rows lie in different banks
+// for one grouping only: 2.7 ns a wavefront's read against 3.7 to 7 for the other groupings and 5.0 at random).
+constexpr uint8_t kSixteens[4][16] = {{0, 1, 2, 3, 12, 13, 14, 15, 20, 21, 22, 23, 24, 25, 26, 27},
+                                      {4, 5, 6, 7, 8, 9, 10, 11, 16, 17, 18, 19, 28, 29, 30, 31},
+                                      {32, 33, 34, 35, 44, 45, 46, 47, 52, 53, 54, 55, 56, 57, 58, 59},
+                                      {36, 37, 38, 39, 40, 41, 42, 43, 48, 49, 50, 51, 60, 61, 62, 63}};
+
+// Packs the segments in the resident form (arrow_internal.h), or leaves the image alone and returns false where that form does
+// not pay: factors that do not fit the LDS, too few entries to pay for copying them there, or so few fibres per
+// slice, or of so unequal length, that the lanes would work on fill.  `at` gives the caller's index of an entry.
+//
+// An item's segments go to batches of 64 by length, longest first, one per lane; what a lane reads in a step is
+// free to choose.  Sixteen lanes are served together and wait for the bank that most of them want, 3.1 of them
+// at random: so a batch's segments are dealt to the sixteens by the bank of their row of B, and of its entries
+// a lane takes first the one whose bank is wanted least in this step and most in those to come, which leaves 2.0
+// (uniform 4096^3, R = 64: 529 -> 463 us; entries and rows of B are added in this order, not in that of j and k).
+template <typename At>
+bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const std::vector<int32_t>& seg_j,
+                   const std::vector<int32_t>& seg_i, At at, const int32_t* tk, const float* tv) {
+  if (h.J + h.K + 1 > arrow::kCsfRowsInLds || h.nnz < kResidentNnz) return false;
+  const double most = kResidentFill * (double)(h.nnz + h.n_seg);           // rows read, fill included
+  if (64.0 * arrow::kCsfBlockSteps * (double)h.I > most) return false;     // (a block per slice at least)
+  struct Part { uint32_t seg, n, block, blocks; int32_t dst; };
+  std::vector<Part> parts;
+  std::vector<uint32_t> split_ptr{0};
+  std::vector<int32_t> split_y;
+  int64_t slots = 0;
+  // A slice is cut where it holds more segments than an item may, or much more rows than the items' average.
+  // (Whole slices where possible: every cut adds fill, at the lengths of its own, and a partial vector.)
+  const int64_t cost_max = std::max<int64_t>(4096, (h.nnz + h.n_seg) / 2048);
+  for (int64_t i = 0, s = 0; i < h.I; ++i) {
+    int64_t end = s;
+    while (end < h.n_seg && seg_i[end] == i) ++end;
+    const int64_t segs = end - s, cost = segs ? (int64_t)(seg_ptr[end] - seg_ptr[s]) + segs : 0;
+    const int64_t n = std::max<int64_t>({1, (segs + kResidentSegs - 1) / kResidentSegs, cost / cost_max});
+    for (int64_t t = 0; t < n; ++t) {
+      const int64_t lo = s + segs * t / n, hi = s + segs * (t + 1) / n;
+      parts.push_back({(uint32_t)lo, (uint32_t)(hi - lo), 0, 0, n == 1 ? (int32_t)i : (int32_t)(-1 - (slots + t))});
+    }
+    if (n > 1) {
+      slots += n;
+      split_ptr.push_back((uint32_t)slots);
+      split_y.push_back((int32_t)i);
+    }
+    s = end;
+  }
+  if (slots > 0x7fffffffLL || parts.size() > 0x7fffff00ULL || (int64_t)parts.size() < kResidentItems) return false;
+  // segments by length, longest first: at_len[l] = where those of length kSegMax - l begin
+  auto by_length = [&](const Part& p, std::array<uint32_t, kSegMax + 2>& at_len) {
+    at_len.fill(0);
+    for (uint32_t q = p.seg; q < p.seg + p.n; ++q) ++at_len[(size_t)(kSegMax - (seg_ptr[q + 1] - seg_ptr[q])) + 1];
+    for (size_t q = 1; q < at_len.size(); ++q) at_len[q] += at_len[q - 1];
+  };
+  const int64_t n_parts = (int64_t)parts.size();
+#pragma omp parallel for schedule(dynamic, 16)
+  for (int64_t t = 0; t < n_parts; ++t) {
+    std::array<uint32_t, kSegMax + 2> at_len;
+    by_length(parts[t], at_len);
+    uint32_t steps = 0;
+    for (uint32_t first = 0, l = 0; first < parts[t].n; first += 64) {     // l: kSegMax - the length of segment `first`
+      while (at_len[l + 1] <= first) ++l;
+      steps += (uint32_t)kSegMax - l + 1;
+    }
+    parts[t].blocks = std::max(1u, (steps + arrow::kCsfBlockSteps - 1) / arrow::kCsfBlockSteps);
+  }
+  int64_t blocks = 0;
+  for (Part& p : parts) {
+    if (blocks > 0xffffffffLL) return false;
+    p.block = (uint32_t)blocks;
+    blocks += p.blocks;
+  }
+  if ((double)(blocks * 64 * arrow::kCsfBlockSteps) > most) return false;
+  size_t total = 0;
+  h.off_items = total;     total = align3(total + sizeof(arrow::ResidentItem) * parts.size());
+  h.off_split_ptr = total; total = align3(total + sizeof(uint32_t) * split_ptr.size());
+  h.off_split_y = total;   total = align3(total + sizeof(int32_t) * split_y.size());
+  h.off_entries = total;   total = align3(total + sizeof(arrow::ResidentBlock) * (size_t)(blocks + arrow::kCsfBlocksAhead));
+  h.bytes.assign(total, 0);
+  unsigned char* base = h.bytes.data();
+  std::memcpy(base + h.off_split_ptr, split_ptr.data(), sizeof(uint32_t) * split_ptr.size());
+  if (!split_y.empty()) std::memcpy(base + h.off_split_y, split_y.data(), sizeof(int32_t) * split_y.size());
+  // the longest items first: the wavefronts take them in turn
+  std::vector<uint32_t> turn(parts.size());
+  for (size_t t = 0; t < turn.size(); ++t) turn[t] = (uint32_t)t;
+  std::stable_sort(turn.begin(), turn.end(), [&](uint32_t a, uint32_t b) { return parts[a].blocks > parts[b].blocks; });
+  arrow::ResidentItem* items = reinterpret_cast<arrow::ResidentItem*>(base + h.off_items);
+  for (size_t t = 0; t < turn.size(); ++t) {
+    const Part& p = parts[turn[t]];
+    items[t] = {p.block, p.blocks, p.dst};
+  }
+  arrow::ResidentBlock* image = reinterpret_cast<arrow::ResidentBlock*>(base + h.off_entries);
+  const uint32_t zeros = (uint32_t)h.K;
+#pragma omp parallel for schedule(dynamic, 16)
+  for (int64_t t = 0; t < n_parts; ++t) {                        // (nothing in here may throw)
+    const Part& p = parts[t];
+    std::array<uint32_t, kSegMax + 2> at_len;
+    std::array<uint16_t, kResidentSegs> order;
+    by_length(p, at_len);
+    for (uint32_t q = 0; q < p.n; ++q) order[at_len[(size_t)(kSegMax - (seg_ptr[p.seg + q + 1] - seg_ptr[p.seg + q]))]++] = (uint16_t)q;
+    auto put = [&](uint32_t step, uint32_t lane, uint32_t row, float v, bool end = false) {
+      arrow::ResidentBlock& b = image[p.block + step / 8];
+      b.offsets[lane].pair[step % 8 / 2] |= row << (step % 2 ? 18 : 4) | (uint32_t)end << step % 2;
+      b.values[step % 8 / 4][lane].v[step % 4] = v;
+    };
+    uint32_t step = 0;
+    for (uint32_t first = 0; first < p.n; first += 64) {
+      const uint32_t longest = seg_ptr[p.seg + order[first] + 1] - seg_ptr[p.seg + order[first]];
+      const uint32_t m = std::min<uint32_t>(64, p.n - first);
+      // lanes: the segments by the bank of their row of B, dealt to the sixteens
+      std::array<uint32_t, 17> at_bank{};
+      auto end_of = [&](uint32_t q) { return zeros + 1 + (uint32_t)seg_j[p.seg + order[first + q]]; };
+      for (uint32_t q = 0; q < m; ++q) ++at_bank[end_of(q) % 16 + 1];
+      for (size_t q = 1; q < 17; ++q) at_bank[q] += at_bank[q - 1];
+      std::array<uint8_t, 64> dealt;
+      for (uint32_t q = 0; q < m; ++q) dealt[at_bank[end_of(q) % 16]++] = (uint8_t)q;
+      for (uint32_t g = 0; g < 4; ++g) {
+        std::array<std::array<uint32_t, kSegMax>, 16> src;      // caller's index of the entries of the sixteen lanes
+        std::array<std::array<uint8_t, kSegMax>, 16> bank;
+        std::array<uint32_t, 16> n{};
+        std::array<uint32_t, 16> left{};                        // entries still to come, by bank
+        for (uint32_t x = 0; x < 16; ++x) {
+          const uint32_t lane = kSixteens[g][x];
+          uint32_t end = zeros;
+          if (x * 4 + g < m) {
+            const uint32_t q = p.seg + order[first + dealt[x * 4 + g]], from = seg_ptr[q];
+            n[x] = seg_ptr[q + 1] - from;
+            end = zeros + 1 + (uint32_t)seg_j[q];
+            for (uint32_t l = 0; l < n[x]; ++l) {
+              src[x][l] = (uint32_t)at(from + l);
+              bank[x][l] = (uint8_t)(tk[src[x][l]] % 16);
+              ++left[bank[x][l]];
+            }
+          }
+          put(step + longest, lane, end, 0.f, true);
+        }
+        for (uint32_t l = 0; l < longest; ++l) {
+          std::array<uint32_t, 16> taken{};                     // lanes of this step, by bank
+          for (uint32_t x = 0; x < 16; ++x) {
+            const uint32_t lane = kSixteens[g][x];
+            if (l >= n[x]) { put(step + l, lane, zeros, 0.f); continue; }
+            uint32_t best = l, cost = ~0u;
+            for (uint32_t c = l; c < n[x]; ++c) {
+              const uint32_t b = bank[x][c], at_b = taken[b] * 1024 + 1023 - std::min(left[b], 1023u);
+              if (at_b < cost) { cost = at_b; best = c; }
+            }
+            std::swap(src[x][l], src[x][best]);
+            std::swap(bank[x][l], bank[x][best]);
+            ++taken[bank[x][l]];
+            --left[bank[x][l]];
+            put(step + l, lane, (uint32_t)tk[src[x][l]], tv[src[x][l]]);
+          }
+        }
+      }
+      step += longest + 1;
+    }
+    for (; step < p.blocks * 8; ++step)
+      for (uint32_t lane = 0; lane < 64; ++lane) put(step, lane, zeros, 0.f);
+  }
+  h.n_items = n_parts;
+  h.n_split = (int64_t)split_y.size();
+  h.n_partials = slots;
+  h.n_blocks = blocks;
+  h.resident = true;
+  return true;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -128,6 +314,17 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
     }
     seg_ptr.push_back((uint32_t)nnz);
     h->n_seg = (int64_t)seg_j.size();
+    {
+      std::vector<uint8_t> seen_j((size_t)J, 0), seen_k((size_t)K, 0);
+      for (int64_t p = 0; p < nnz; ++p) { seen_j[tj[p]] = 1; seen_k[tk[p]] = 1; }
+      for (uint8_t v : seen_j) h->distinct_j += v;
+      for (uint8_t v : seen_k) h->distinct_k += v;
+    }
+    if (pack_resident(*h, seg_ptr, seg_j, seg_i, at, tk, tv)) {
+      h->build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+      *out = h.release();
+      return ARROW_OK;
+    }
     // items: per slice i (empty slices included), consecutive segments up to kItemNnz entries
     // and kItemSegs segments
     std::vector<uint32_t> item_seg, split_ptr;
@@ -200,12 +397,6 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
     h->n_items = (int64_t)item_dst.size();
     h->n_split = (int64_t)split_y.size();
     h->n_partials = slots;
-    {
-      std::vector<uint8_t> seen_j((size_t)J, 0), seen_k((size_t)K, 0);
-      for (int64_t p = 0; p < nnz; ++p) { seen_j[tj[p]] = 1; seen_k[tk[p]] = 1; }
-      for (uint8_t v : seen_j) h->distinct_j += v;
-      for (uint8_t v : seen_k) h->distinct_k += v;
-    }
     size_t total = 0;
     h->off_seg_ptr = total;   total = align3(total + sizeof(uint32_t) * seg_ptr.size());
     h->off_seg_j = total;     total = align3(total + sizeof(int32_t) * seg_j.size());
@@ -312,7 +503,10 @@ int csf3_mttkrp(csf3_handle* h, const float* B, const float* C, float* A, int32_
   auto at = [&](size_t off) { return h->dev + off; };
   const bool prof = h->profiling && h->ev[0];
   if (prof) (void)hipEventRecord(h->ev[0], (hipStream_t)stream);
-  int rc = arrow::launch_mttkrp(reinterpret_cast<const uint32_t*>(at(h->off_item_seg)),
+  int rc = h->resident ? arrow::launch_mttkrp_resident(reinterpret_cast<const arrow::ResidentItem*>(at(h->off_items)),
+                                                       reinterpret_cast<const arrow::ResidentBlock*>(at(h->off_entries)), h->n_items,
+                                                       h->n_blocks, B, h->J, C, h->K, A, partials, R, stream)
+                       : arrow::launch_mttkrp(reinterpret_cast<const uint32_t*>(at(h->off_item_seg)),
                                 reinterpret_cast<const uint32_t*>(at(h->off_item_ent)),
                                 reinterpret_cast<const int32_t*>(at(h->off_item_dst)),
                                 reinterpret_cast<const uint32_t*>(at(h->off_seg_ptr)),

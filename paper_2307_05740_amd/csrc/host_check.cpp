@@ -56,6 +56,8 @@ int64_t probe_out_floats(int64_t) { reached("probe_out_floats"); }
 int launch_probe_gather(const float*, int64_t, int32_t, int64_t, int, int, int64_t, float*, void*) { reached("launch_probe_gather"); }
 int launch_mttkrp(const uint32_t*, const uint32_t*, const int32_t*, const uint32_t*, const int32_t*, const Entry*,
                   int64_t, const float*, int64_t, const float*, int64_t, float*, float*, int32_t, int32_t, int32_t, void*) { reached("launch_mttkrp"); }
+int launch_mttkrp_resident(const ResidentItem*, const ResidentBlock*, int64_t, int64_t, const float*, int64_t, const float*, int64_t,
+                           float*, float*, int32_t, void*) { reached("launch_mttkrp_resident"); }
 }  // namespace arrow
 
 // ---- memory that runs out ---------------------------------------------------------------------------
@@ -286,6 +288,25 @@ int main(int argc, char** argv) {
       allocations_left = -1;
       EXPECT(rc == ARROW_OK ? t != nullptr : rc == ARROW_ENOMEM && !t && failed, "csf3_build with %ld allocations", n);
       csf3_destroy(t);
+    }
+    {
+      // large enough for the form whose factors lie in LDS: 520 slices, a hub slice, one without entries, long fibres
+      std::vector<int32_t> ui, uj, uk;
+      std::vector<float> uv;
+      for (int e = 0; e < 620000; ++e) {
+        const int32_t i = (int32_t)(next_u64(s) % 520);
+        ui.push_back(i == 9 || i % 64 == 3 ? 1 : i);
+        uj.push_back(e < 300 ? 5 : (int32_t)(next_u64(s) % 700)); uk.push_back((int32_t)(next_u64(s) % 900));
+        uv.push_back((float)(e % 13) - 6.f);
+        if (e < 300) ui.back() = 7;
+      }
+      t = nullptr;
+      EXPECT(csf3_build(520, 700, 900, (int64_t)uv.size(), ui.data(), uj.data(), uk.data(), uv.data(), &t) == 0 && t, "csf3_build, factors in LDS");
+      if (t) {
+        csf3_info_t ci;
+        EXPECT(csf3_info(t, &ci) == 0 && ci.items == 520 - ci.split_rows + ci.partials && ci.items < 600, "items of whole slices");
+        csf3_destroy(t);
+      }
     }
     tk[5] = 7;
     EXPECT(csf3_build(40, 40, 7, (int64_t)tv.size(), ti.data(), tj.data(), tk.data(), tv.data(), &t) != 0, "csf3 index out of range");

@@ -21,7 +21,8 @@
 // longest of G random lengths, and with the masks 16 vector instructions stood for every row load, of
 // which 5 do the work: the kernel was bound by instruction issue (83 % of the cycles).  Uniform 4096^3
 // tensor, 68.7 M entries in 16.5 M fibres, R = 64: 1078 -> 850 us; what it gathers (21.8 GB from the L2 at
-// 64 B per cycle and compute unit) takes 630 us.  The skewed tensor of 16.4 M fibres of one entry, R = 32, gains
+// 64 B per cycle and compute unit) takes 630 us, which is why factors that fit the LDS are read from there
+// (resident_kernel).  The skewed tensor of 16.4 M fibres of one entry, R = 32, gains
 // nothing (507 us): B and C are 8 MiB each and an L2 is 4 MiB, so that 68 % of the requests miss it, 3.3 GB that
 // come at 6.6 TB/s.
 //
@@ -208,7 +209,182 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
     gstore<VEC>(dst >= 0 ? A + (size_t)dst * (size_t)R + lc.c : partials + (size_t)(-1 - dst) * (size_t)R + lc.c, acc);
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// resident kernel: both factors in LDS, four columns at a time.  A workgroup copies its four columns of all rows
+// of C and B (16 bytes a row, at most 10200 rows) and keeps them while its sixteen wavefronts go through
+// items.  A lane owns a segment: in every step it reads one row of C from LDS and adds it, times the value, to
+// the segment's sum, until the step that multiplies the sum by the row of B.  All lanes of a batch do this in
+// the same step, so the choice is a scalar one; the image holds the offsets and values in this order (ResidentBlock), so
+// the entries come with coalesced 16-byte loads and no lane waits for anything but LDS.
+//
+// Why: with the rows gathered from the L2 an entry moves 4 R bytes over the path of 64 bytes per cycle into the
+// compute unit; from LDS they come twice as fast, random 16-byte rows at 51 TB/s against 26.  The price is
+// that the entries are read R / 4 times, 6 bytes a step; the workgroups of one die that
+// differ in their columns go through the same items at the same time, so that 95 % of these loads hit the L2.
+// Uniform 4096^3 tensor, 68.7 M entries in 16.5 M fibres: R = 64 850 -> 443 us, R = 8 378 -> 107, R = 128 1636 ->
+// 822; 1300^3, 2.2 M entries, R = 64: 43.6 -> 31.8 us.  Of the 443 us (R = 64) LDS works 360, the loads of the entries
+// 315, the vector units 300.  Entry and offset as a pair of eight bytes per step: 593 us, with loads of 8 bytes per lane
+// 792 (those move 75 bytes per ns into a compute unit, 16-byte ones 120).
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kResidentBlock = 1024;
+
+// One step: a record of a batch adds its row to the sums of the fibres, the one that ends it adds their products
+// with the row of B to acc.  The bit is the same for the whole wavefront; written out because the compiler
+// turned the choice into sixteen register moves a step.
+template <int BIT>
+__device__ __forceinline__ void resident_step(float4& acc, float4& x, uint32_t bits, float v, float4 c) {
+  asm volatile(
+      "s_bitcmp1_b32 %[m], %[bit]\n\t"
+      "s_cbranch_scc1 1f\n\t"
+      "v_fmac_f32 %[x0], %[v], %[c0]\n\t"
+      "v_fmac_f32 %[x1], %[v], %[c1]\n\t"
+      "v_fmac_f32 %[x2], %[v], %[c2]\n\t"
+      "v_fmac_f32 %[x3], %[v], %[c3]\n\t"
+      "s_branch 2f\n"
+      "1:\n\t"
+      "v_fmac_f32 %[a0], %[x0], %[c0]\n\t"
+      "v_fmac_f32 %[a1], %[x1], %[c1]\n\t"
+      "v_fmac_f32 %[a2], %[x2], %[c2]\n\t"
+      "v_fmac_f32 %[a3], %[x3], %[c3]\n\t"
+      "v_mov_b32 %[x0], 0\n\t"
+      "v_mov_b32 %[x1], 0\n\t"
+      "v_mov_b32 %[x2], 0\n\t"
+      "v_mov_b32 %[x3], 0\n"
+      "2:"
+      : [x0] "+v"(x.x), [x1] "+v"(x.y), [x2] "+v"(x.z), [x3] "+v"(x.w),
+        [a0] "+v"(acc.x), [a1] "+v"(acc.y), [a2] "+v"(acc.z), [a3] "+v"(acc.w)
+      : [m] "s"(bits), [bit] "n"(BIT), [v] "v"(v), [c0] "v"(c.x), [c1] "v"(c.y), [c2] "v"(c.z), [c3] "v"(c.w)
+      : "scc");
+}
+
+constexpr int kResidentGroups = 256;     // workgroups: one per compute unit, which holds one window of rows
+
+__global__ __launch_bounds__(kResidentBlock) void resident_kernel(
+    const ResidentItem* __restrict__ items, const ResidentBlock* __restrict__ blocks, int n_items,
+    const float* __restrict__ B, int J, const float* __restrict__ C, int K, float* __restrict__ A,
+    float* __restrict__ partials, int R, int slices, int replicas) {
+  __shared__ float4 s_row[kCsfRowsInLds];
+  const int per_die = gridDim.x / 8, q = (int)(blockIdx.x % 8) * per_die + (int)(blockIdx.x / 8);
+  if (q >= slices * replicas) return;
+  const int slice = q % slices, c0 = R >= 4 ? min(4 * slice, R - 4) : 0;
+  auto row_of = [&](const float* M, int r) {
+    const float* p = M + (size_t)r * (size_t)R + c0;
+    if (R >= 4) return gload<4>(p);
+    return make_float4(p[0], R > 1 ? p[1] : 0.f, R > 2 ? p[2] : 0.f, 0.f);
+  };
+  for (int r = threadIdx.x; r < K; r += kResidentBlock) s_row[r] = row_of(C, r);
+  for (int r = threadIdx.x; r < J; r += kResidentBlock) s_row[K + 1 + r] = row_of(B, r);
+  if (threadIdx.x == 0) s_row[K] = vzero<4>();
+  __syncthreads();
+  const char* lds = reinterpret_cast<const char*>(s_row);
+  constexpr int U = kCsfBlockSteps, N = 3;              // blocks on their way
+  static_assert(U == 8 && kCsfBlocksAhead >= N, "the steps of a block, and blocks past the last item");
+  const uint32_t lane = threadIdx.x % 64;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+  const int workers = replicas * (kResidentBlock / 64);
+  int it = q / slices * (kResidentBlock / 64) + wave;
+  if (it >= n_items) return;
+  // The blocks of this wavefront's items as one sequence, N of them on their way: `f` is the item that is
+  // fetched from, `d` the one that is summed; what follows an item is loaded while there is time.
+  auto item = [&](int i) { return items[min(i, n_items - 1)]; };
+  ResidentItem d = item(it), d_next = item(it + workers), f = d, f_next = d_next;
+  int f_it = it;
+  const ResidentBlock* p = blocks + f.block;
+  uint4 of[N];
+  float4 lo[N], hi[N];
+  auto fetch = [&](int h) {
+    of[h] = *reinterpret_cast<const uint4*>(&p->offsets[lane]);
+    lo[h] = *reinterpret_cast<const float4*>(&p->values[0][lane]);
+    hi[h] = *reinterpret_cast<const float4*>(&p->values[1][lane]);
+    ++p;
+    if (--f.blocks == 0) {
+      f = f_next;
+      f_it = min(f_it, n_items) + workers;
+      f_next = item(f_it + workers);
+      p = blocks + f.block;
+    }
+  };
+#pragma unroll
+  for (int h = 0; h < N; ++h) fetch(h);
+  float4 sum = vzero<4>(), part = vzero<4>(), acc = vzero<4>(), x = vzero<4>();
+  auto store = [&] {
+#pragma unroll
+    for (int w = 1; w < 64; w <<= 1) vadd(sum, vshfl_xor(sum, w));
+    if (lane == 0) {
+      float* out = (d.dst >= 0 ? A + (size_t)d.dst * (size_t)R : partials + (size_t)(-1 - d.dst) * (size_t)R) + c0;
+      if (R >= 4) {
+        gstore<4>(out, sum);
+      } else {
+        out[0] = sum.x;
+        if (R > 1) out[1] = sum.y;
+        if (R > 2) out[2] = sum.z;
+      }
+    }
+    sum = vzero<4>();
+  };
+  while (true) {
+#pragma unroll
+    for (int h = 0; h < N; ++h) {
+      const uint32_t w[4] = {of[h].x, of[h].y, of[h].z, of[h].w};
+      const float v[U] = {lo[h].x, lo[h].y, lo[h].z, lo[h].w, hi[h].x, hi[h].y, hi[h].z, hi[h].w};
+      float4 c[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        c[u] = *reinterpret_cast<const float4*>(lds + ((u % 2 ? w[u / 2] >> 14 : w[u / 2]) & 0x3fff0u));
+      uint32_t ends[U / 2];
+#pragma unroll
+      for (int u = 0; u < U / 2; ++u) ends[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[u]);
+#pragma unroll
+      for (int u = 0; u < U; u += 2) {
+        resident_step<0>(acc, x, ends[u / 2], v[u], c[u]);
+        resident_step<1>(acc, x, ends[u / 2], v[u + 1], c[u + 1]);
+      }
+      fetch(h);
+      if (--d.blocks % 4 == 0) {                        // short chains of additions: as exact as the other kernel
+        vadd(part, acc);
+        acc = vzero<4>();
+        if (d.blocks % 16 == 0) {
+          vadd(sum, part);
+          part = vzero<4>();
+        }
+      }
+      if (d.blocks == 0) {
+        store();
+        it += workers;
+        if (it >= n_items) return;
+        d = d_next;
+        d_next = item(it + workers);
+      }
+    }
+  }
+}
+
 }  // namespace
+
+int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* blocks, int64_t n_items, int64_t n_blocks,
+                           const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials,
+                           int32_t R, void* stream) {
+  if (n_items <= 0) return 0;
+  if (b_rows + c_rows + 1 > kCsfRowsInLds || n_items > INT_MAX) return (int)hipErrorInvalidValue;
+  // Replicas: workgroups that share the items of a column slice.  One round of workgroups where the slices divide
+  // the compute units well; else more of them, each of which copies the factors again, four rows in about
+  // the time of a wavefront's step.  (1300^3, R = 520, 130 slices: 338 -> 218 us with three
+  // workgroups per slice in two rounds.)
+  const int64_t slices = ceil_div(R, 4), copy = (b_rows + c_rows) / 4;
+  int64_t replicas = 1;
+  double best = 0.0;
+  for (int64_t rounds = 1; rounds <= 4; ++rounds) {
+    const int64_t n = kResidentGroups * rounds / slices;
+    if (n < 1) continue;
+    const double cost = (double)rounds * ((double)(n_blocks * kCsfBlockSteps) / (double)n + (double)copy);
+    if (best == 0.0 || cost < best) { best = cost; replicas = n; }
+  }
+  const int64_t groups = ceil_div(slices * replicas, 8) * 8;
+  if (groups > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(resident_kernel, dim3((unsigned)groups), dim3(kResidentBlock), 0, (hipStream_t)stream, items, blocks,
+                     (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)slices, (int)replicas);
+  return (int)hipGetLastError();
+}
 
 int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int32_t* item_dst,
                   const uint32_t* seg_ptr, const int32_t* seg_j, const Entry* entries, int64_t n_items, const float* B,

@@ -297,3 +297,39 @@ def test_non_finite_rows_of_a_window_stay_with_their_readers(torch, k, fuse):
     assert 0.5 < fin.mean() < 1.0
     assert np.array_equal(np.isnan(Y), np.isnan(ref)) and np.array_equal(Y[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32))
     assert np.all(np.abs(Y[fin] - ref[fin]) <= TOL * bound[fin])
+
+
+@pytest.mark.parametrize("I,J,K,nnz,R", [
+    (600, 1700, 1300, 700_000, 1), (600, 1700, 1300, 700_000, 2), (600, 1700, 1300, 700_000, 3),
+    (600, 1700, 1300, 700_000, 4), (600, 1700, 1300, 700_000, 7), (513, 5000, 300, 700_000, 33),
+    (700, 600, 9599, 1_200_000, 6), (700, 9899, 300, 600_000, 6), (520, 900, 900, 535_000, 130),
+    (600, 700, 700, 600_000, 520), (600, 700, 700, 600_000, 1030)])
+def test_mttkrp_factors_in_lds(torch, I, J, K, nnz, R):
+    """The form for factors that fit the LDS, up to the last row of it (J + K + 1 = 10200): fibres of one entry
+    and of more than a segment holds, a slice of several items (but for the smallest), slices of one entry and without any,
+    rows of the factors that no entry refers to (infinite here), duplicates, entries in any order."""
+    rng = np.random.default_rng(I + R)
+    i = rng.integers(0, I, nnz)
+    i[i % 97 == 5] = 1                                       # a hub slice, empty ones
+    j, k = rng.integers(1, J - 1, nnz), rng.integers(1, K - 1, nnz)
+    i[:300], j[:300] = 7, 1                                  # one fibre of five segments
+    i[300:700], j[300:700], k[300:700] = 8, J - 2, K - 2     # a coordinate that repeats
+    drop = (i >= 20) & (i < 23)
+    i, j, k = i[~drop], j[~drop], k[~drop]
+    only = np.flatnonzero(i == 30)[1:]                       # a slice of a single entry
+    i[only] = 31
+    v = rng.uniform(-1, 1, len(i)).astype(np.float32)
+    i, j, k = (x.astype(np.int32) for x in (i, j, k))
+    B, C = synth.normal_matrix(J, R, seed=31), synth.normal_matrix(K, R, seed=32)
+    Aref, E = oracle.mttkrp((I, J, K), i, j, k, v, B, C)
+    B[[0, -1]], C[[0, -1]] = np.inf, np.nan                  # what no entry refers to has no effect
+    op = binding.Csf3Mttkrp((I, J, K), i, j, k, v)
+    assert op.info["items"] == I - op.info["split_rows"] + op.info["partials"]
+    assert op.info["nnz"] + op.info["segments"] > 128 * op.info["items"]      # (not the form with items of 512 entries)
+    A = torch.full((I, R), float("nan"), device="cuda")
+    op.mttkrp(torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(), A)
+    assert_within(A.cpu().numpy(), Aref, E)
+    first = A.clone()
+    op.mttkrp(torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(), A)
+    assert torch.equal(first, A)
+    op.close()
