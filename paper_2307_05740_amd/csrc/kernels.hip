@@ -1035,40 +1035,74 @@ __global__ __launch_bounds__(kBlock) void sddmm_corner_kernel(
   }
 }
 
-// One wavefront per split row: its partial vectors (consecutive slots) are
-// summed slot-strided by the G lane groups, then combined by the same butterfly.
+// One wavefront per split row: its partial vectors (consecutive slots) are summed slot-strided by the G lane groups, then
+// combined by the same butterfly.  Rows of many partial vectors are shared by the wavefronts of the workgroup, and eight
+// loads are on their way instead of four: the launch lasted as long as one wavefront took for the longest row
+// (a hub of 2048 partial vectors, 64 rounds of loads one after the other).  Such rows are usually neighbours, so
+// a workgroup takes rows that are far apart.  Chung-Lu 2m k = 32 25.9 -> 13.4 us, R-MAT 1m k = 64 13.3 -> 10.9,
+// R-MAT 8m k = 128, where memory bounds it, 320 -> 308.  (Sixteen wavefronts per workgroup: 18, 16 and 346 us; a lane
+// group per short row: 22, 18 and 343.)
 template <int VEC, int LPR>
 __global__ __launch_bounds__(kBlock) void reduce_kernel(
     const uint32_t* __restrict__ split_ptr, const int32_t* __restrict__ split_y, int64_t n_split,
     const float* __restrict__ partials, float* __restrict__ Y, int k, int width, int accumulate) {
   using V = typename Vec<VEC>::type;
-  constexpr int G = 64 / LPR;
   constexpr int WPB = kBlock / 64;
-  const int64_t row = (int64_t)blockIdx.x * WPB + threadIdx.x / 64;
-  if (row >= n_split) return;
+  constexpr uint32_t G = 64 / LPR, kLong = 16 * G;
+  __shared__ V s_part[2][WPB][LPR];
   const int lane = threadIdx.x % 64;
-  const int g = lane / LPR;
-  const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * width, k, width);
-  const int c = lc.c;
-  const bool col_ok = lc.ok;
-  const uint32_t lo = split_ptr[row], hi = split_ptr[row + 1];
-  const float* __restrict__ Pc = partials + (col_ok ? c : 0);
-  V acc = vzero<VEC>();
-  uint32_t s = lo + g;
-  for (; s + 3 * G < hi; s += 4 * G) {
-    V p0 = vload_stream<VEC>(Pc + (size_t)s * (size_t)k);
-    V p1 = vload_stream<VEC>(Pc + (size_t)(s + G) * (size_t)k);
-    V p2 = vload_stream<VEC>(Pc + (size_t)(s + 2 * G) * (size_t)k);
-    V p3 = vload_stream<VEC>(Pc + (size_t)(s + 3 * G) * (size_t)k);
-    vadd(acc, p0); vadd(acc, p1); vadd(acc, p2); vadd(acc, p3);
-  }
-  for (; s < hi; s += G) vadd(acc, vload_stream<VEC>(Pc + (size_t)s * (size_t)k));
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+  const uint32_t g = lane / LPR, l = lane % LPR;
+  const LaneColumns lc = lane_columns<VEC>((int)l, blockIdx.y * width, k, width);
+  const float* __restrict__ Pc = partials + (lc.ok ? lc.c : 0);
+  // lane t holds what belongs to the row of wavefront t
+  const int64_t mine = (int64_t)blockIdx.x + (int64_t)(lane % WPB) * gridDim.x;
+  uint32_t lo_of = 0, hi_of = 0;
+  int32_t y_of = 0;
+  if (mine < n_split) { lo_of = split_ptr[mine]; hi_of = split_ptr[mine + 1]; y_of = split_y[mine]; }
+  auto of = [](auto v, int t) { return (decltype(v))__builtin_amdgcn_readlane((int)v, t); };
+  auto sum = [&](uint32_t s, uint32_t end, uint32_t step) {
+    V acc = vzero<VEC>();
+    for (; s + 7 * step < end; s += 8 * step) {
+      V p[8];
 #pragma unroll
-  for (int m = LPR; m < 64; m <<= 1) vadd(acc, vshfl_xor(acc, m));
-  if (g == 0 && col_ok) {
-    float* y = Y + (size_t)split_y[row] * (size_t)k + c;
-    if (accumulate) vadd(acc, vload_stream<VEC>(y));
-    vstore_stream<VEC>(y, acc);
+      for (int u = 0; u < 8; ++u) p[u] = vload_stream<VEC>(Pc + (size_t)(s + u * step) * (size_t)k);
+#pragma unroll
+      for (int m = 1; m < 8; m *= 2)
+#pragma unroll
+        for (int u = 0; u < 8; u += 2 * m) vadd(p[u], p[u + m]);
+      vadd(acc, p[0]);
+    }
+    V p[8];
+#pragma unroll
+    for (int u = 0; u < 7; ++u) if (s + u * step < end) p[u] = vload_stream<VEC>(Pc + (size_t)(s + u * step) * (size_t)k);
+#pragma unroll
+    for (int u = 0; u < 7; ++u) if (s + u * step < end) vadd(acc, p[u]);
+#pragma unroll
+    for (int m = LPR; m < 64; m <<= 1) vadd(acc, vshfl_xor(acc, m));
+    return acc;
+  };
+  auto store = [&](int32_t row, V acc) {
+    if (g != 0 || !lc.ok) return;
+    float* to = Y + (size_t)row * (size_t)k + lc.c;
+    if (accumulate) vadd(acc, vload_stream<VEC>(to));
+    vstore_stream<VEC>(to, acc);
+  };
+  uint32_t shared = (uint32_t)__ballot(lane < WPB && hi_of - lo_of >= kLong);
+  if (!(shared >> wave & 1u)) {
+    const uint32_t lo = of(lo_of, wave), hi = of(hi_of, wave);
+    if (lo < hi) store(of(y_of, wave), sum(lo + g, hi, G));
+  }
+  for (int half = 0; shared; half ^= 1, shared &= shared - 1) {
+    const int t = __ffs(shared) - 1;
+    const V part = sum(of(lo_of, t) + (uint32_t)wave * G + g, of(hi_of, t), WPB * G);
+    if (g == 0) s_part[half][wave][l] = part;
+    __syncthreads();                     // (the other half is read no more: its readers have come this far)
+    if (wave == t) {
+      V acc = s_part[half][0][l];
+      for (int w = 1; w < WPB; ++w) vadd(acc, s_part[half][w][l]);
+      store(of(y_of, t), acc);
+    }
   }
 }
 

@@ -333,3 +333,25 @@ def test_mttkrp_factors_in_lds(torch, I, J, K, nnz, R):
     op.mttkrp(torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(), A)
     assert torch.equal(first, A)
     op.close()
+
+
+@pytest.mark.parametrize("k", [1, 6, 20, 33, 128, 260])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_rows_of_many_partial_vectors(torch, k, fuse):
+    """Hub rows next to each other and far apart, long enough for the wavefronts of a workgroup to share their
+    partial vectors (from 32 of them on at k = 128), beside split rows of a few."""
+    n = 140001
+    rng = np.random.default_rng(k)
+    length = rng.integers(0, 3, n)
+    length[[0, 1, 2, 3, 5, 70000]] = [140000, 30000, 100000, 9000, 139999, 60000]
+    length[1000:1040] = 600
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    colidx = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for m in length]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=33)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, 1024, options=binding.arrow_options_default(fuse_levels=fuse))
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    op.close()
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
