@@ -334,4 +334,33 @@ int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* block
                            const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials,
                            int32_t R, void* stream);
 
+// A third form, for tensors of many small slices and fibres of about one entry, whose factors do not fit an L2
+// (streams_kernel in mttkrp.hip): a wavefront owns rows of A and keeps their sums in LDS; each of its eight lane
+// groups goes through the entries of rows of its own, ordered by windows of one factor's rows, so that all lane
+// groups of the chip read the same part of that factor at a time.
+constexpr int kCsfStreamRows = 71;      // most rows of a wavefront; one more takes what fills up
+constexpr int kCsfStreamGroups = 8;     // lane groups
+constexpr int kCsfStreamTeam = 16;      // wavefronts of a workgroup, which wait for each other
+constexpr uint32_t kCsfStreamTurn = 4;  // ... after so many blocks
+constexpr int64_t kCsfStreamRowsOfB = 1 << 25;   // most rows of B: an index shares a word with the place of the sum
+struct StreamBlock {                    // eight entries of each lane group: word 8 g + s is entry s of group g
+  struct Record { uint32_t j_slot; int32_t k; float val; };   // row of B << 7 | place of the sum
+  Record rec[64];
+};
+struct StreamWave {
+  uint32_t block, blocks;               // first block and their number
+  uint32_t turns;                       // of kCsfStreamTurn blocks, in the wavefront of the team that has most
+  uint32_t zero, zeros;                 // its part of the rows of A without entries
+};
+// dst[kCsfStreamRows * w + place]: row of A, -1 - partial vector, or kCsfNoRow
+constexpr int32_t kCsfNoRow = INT32_MIN;
+int launch_mttkrp_streams(const StreamWave* waves, const StreamBlock* blocks, const int32_t* dst, const int32_t* zero_rows,
+                          int64_t n_waves, const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A,
+                          float* partials, float* scratch, int32_t R, void* stream);
+// Columns a wavefront of that form sums at a time, and floats of the scratch it may need (growing with R).
+constexpr int stream_slice(int32_t R) { return R > 16 ? 32 : R > 8 ? 16 : 8; }
+constexpr int64_t stream_scratch(int64_t b_rows, int64_t c_rows, int32_t R) {
+  return (b_rows + c_rows) * ((R + (int64_t)stream_slice(R) - 1) / stream_slice(R)) * stream_slice(R);
+}
+
 }  // namespace arrow

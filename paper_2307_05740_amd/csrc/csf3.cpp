@@ -8,7 +8,8 @@
 // most kItemNnz entries and kItemSegs segments, one per wavefront, with a destination: row i of A when the slice is one
 // item, else a partial-vector slot that the reduction pass sums in a fixed order.  Every i in
 // [0, I) has at least one item (an empty one stores zeros), so A is fully overwritten.
-// Tensors whose factors fit the LDS get another form (pack_resident).
+// Tensors whose factors fit the LDS, and tensors of many small slices whose factors do not fit an L2, get
+// other forms (pack_resident, pack_streams).
 #include <hip/hip_runtime.h>
 #include <omp.h>
 
@@ -62,6 +63,9 @@ struct csf3_handle {
   bool resident = false;              // the image is in the form for factors that fit the LDS
   size_t off_items = 0;
   int64_t n_blocks = 0;
+  bool streams = false;               // the form for many small slices and factors that do not fit an L2
+  size_t off_waves = 0, off_dst = 0, off_zero = 0;
+  int64_t n_waves = 0;
   unsigned char* dev = nullptr;
   unsigned char* ws = nullptr;
   size_t ws_bytes = 0;
@@ -249,6 +253,195 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
   return true;
 }
 
+// Where the streams form pays (both forms measured, us, R = 8 / 32 / 50 / 128; skewed tensors of 32 entries per slice unless
+// said otherwise):
+//   524288 x 65536 x 65536 of 16.8 M           329 / 507 / 1136 / 2164 -> 205 / 289 / 618 / 1170
+//   180000 x 22500 x 22500 of 5.8 M            111 / 144 /  254 /  615 ->  75 /  93 / 196 /  355
+//    90000 x  7500 x 18000 of 2.9 M             58 /  72 /  107 /  248 ->  42 /  53 / 108 /  195
+//   400000 x  2000 x  2000 of 4.2 M, uniform   177 / 203 /  228 /  288 ->  54 /  72 / 185 /  287
+// and where it does not: factors that an L2 holds, unless slices are short (45000 x 5625 x 5000: 31 / 39 / 55 / 104 ->
+// 26 / 34 / 69 / 119; 200000 x 5000 x 5200 of 4.8 M, uniform: 96 / 122 / 158 / 255 -> 57 / 73 / 158 / 284), long
+// slices, whose items go through B in order by themselves (500 x 30000 x 30000 of 8.4 M: 84 / 149 / 406 / 905 -> 139 /
+// 197 / 327 / 571), fibres of several entries, for each of which it reads the row of B again.
+constexpr int64_t kStreamNnz = 1 << 21;
+constexpr int64_t kStreamSlice = 64;       // most entries of a slice on average,
+constexpr int64_t kStreamShort = 12;       // ... and where the factors have fewer rows than this:
+constexpr int64_t kStreamRows = 24000;
+constexpr int64_t kStreamWaves = 4096;     // wavefronts that are resident at a time
+// Windows of one factor's rows, each with the same share of the entries.  Few of them leave more rows in use at a time,
+// many leave a row's entries one by one (they are added up by window first): 6 / 8 / 16 windows 300 / 289 / 280 us,
+// 2-norm of the error 0.83 / 0.85 / 0.9e-7 (512k x 64k x 64k, R = 32; 0.82e-7 in the other form).
+constexpr int kStreamWindows = 8;
+
+// Packs the entries in the streams form (arrow_internal.h), or leaves the image alone and returns false.
+// Rows of A (pieces of the longest) are dealt to the lane groups of all wavefronts so that every group has
+// about the same number of entries, and groups to wavefronts so that none has more rows than it has room for.
+template <typename At>
+bool pack_streams(csf3_handle& h, At at, const int32_t* ti, const int32_t* tj, const int32_t* tk, const float* tv) {
+  constexpr int64_t G = arrow::kCsfStreamGroups, room = arrow::kCsfStreamRows;
+  if (h.nnz < kStreamNnz || h.J > arrow::kCsfStreamRowsOfB || h.fibers * 4 < h.nnz * 3 || h.nnz > kStreamSlice * h.I) return false;
+  if (h.J + h.K < kStreamRows && h.nnz > kStreamShort * h.I) return false;
+  struct Row { uint32_t first, n; int32_t i; };                   // a slice with entries
+  std::vector<Row> rows;
+  std::vector<int32_t> zero;
+  rows.reserve((size_t)h.slices);
+  zero.reserve((size_t)(h.I - h.slices));
+  for (int64_t p = 0, i = 0; i < h.I; ++i) {
+    const int64_t first = p;
+    while (p < h.nnz && ti[at(p)] == i) ++p;
+    if (p > first) rows.push_back({(uint32_t)first, (uint32_t)(p - first), (int32_t)i});
+    else zero.push_back((int32_t)i);
+  }
+  struct Piece { uint32_t first, n; int32_t dst; };
+  std::vector<Piece> pieces;
+  std::vector<uint32_t> split_ptr, group_of, order;
+  std::vector<int32_t> split_y;
+  std::vector<uint32_t> group_rows;
+  int64_t slots = 0, n_waves = 0;
+  for (int64_t rounds = ((int64_t)rows.size() + kStreamWaves * room - 1) / (kStreamWaves * room);; ++rounds) {
+    n_waves = kStreamWaves * rounds;
+    if (n_waves * G > 0x7fffffffLL || rounds > 64) return false;
+    const uint32_t share = (uint32_t)std::max<int64_t>(16, (h.nnz + n_waves * G - 1) / (n_waves * G));   // entries of a group
+    pieces.clear(); split_y.clear(); split_ptr.assign(1, 0);
+    slots = 0;
+    for (const Row& r : rows) {
+      const uint32_t n = (r.n + share - 1) / share;
+      for (uint32_t t = 0; t < n; ++t) {
+        const uint32_t lo = (uint32_t)((uint64_t)r.n * t / n), hi = (uint32_t)((uint64_t)r.n * (t + 1) / n);
+        pieces.push_back({r.first + lo, hi - lo, n == 1 ? r.i : (int32_t)(-1 - (slots + t))});
+      }
+      if (n > 1) {
+        slots += n;
+        split_ptr.push_back((uint32_t)slots);
+        split_y.push_back(r.i);
+      }
+    }
+    if (slots > 0x7fffffffLL) return false;
+    if ((int64_t)pieces.size() > n_waves * room) continue;
+    // longest piece first to the group with the fewest entries, groups in lists by how many they have
+    std::vector<uint32_t> at_len(share + 2, 0);
+    for (const Piece& p : pieces) ++at_len[share - p.n + 1];
+    for (size_t q = 1; q < at_len.size(); ++q) at_len[q] += at_len[q - 1];
+    order.resize(pieces.size());
+    for (size_t q = 0; q < pieces.size(); ++q) order[at_len[share - pieces[q].n]++] = (uint32_t)q;
+    const size_t n_groups = (size_t)(n_waves * G);
+    constexpr uint32_t none = ~0u;
+    std::vector<uint32_t> next(n_groups), head(2 * (size_t)share + 2, none);
+    for (size_t q = 0; q < n_groups; ++q) next[q] = q + 1 < n_groups ? (uint32_t)(q + 1) : none;
+    head[0] = 0;
+    size_t least = 0;
+    group_of.resize(pieces.size());
+    group_rows.assign(n_groups, 0);
+    for (const uint32_t q : order) {
+      while (head[least] == none) ++least;
+      const uint32_t g = head[least];
+      head[least] = next[g];
+      const size_t load = least + pieces[q].n;                     // (at most twice the share: the least load is no more than it)
+      next[g] = head[load];
+      head[load] = g;
+      group_of[q] = g;
+      ++group_rows[g];
+    }
+    // eight groups to a wavefront, those with many rows beside those with few
+    const uint32_t most = *std::max_element(group_rows.begin(), group_rows.end());
+    std::vector<uint32_t> at_rows(most + 2, 0), place(n_groups);
+    for (const uint32_t r : group_rows) ++at_rows[most - r + 1];
+    for (size_t q = 1; q < at_rows.size(); ++q) at_rows[q] += at_rows[q - 1];
+    for (size_t g = 0; g < n_groups; ++g) {
+      const size_t rank = at_rows[most - group_rows[g]]++, turn = rank / (size_t)n_waves, w = rank % (size_t)n_waves;
+      place[g] = (uint32_t)((turn % 2 ? (size_t)n_waves - 1 - w : w) * G + turn);
+    }
+    std::vector<uint32_t> wave_rows((size_t)n_waves, 0);
+    for (size_t g = 0; g < n_groups; ++g) wave_rows[place[g] / G] += group_rows[g];
+    if (*std::max_element(wave_rows.begin(), wave_rows.end()) > (uint32_t)room) continue;
+    for (uint32_t& g : group_of) g = place[g];
+    break;
+  }
+  // pieces by group, and their entries by window of the rows of the factor with more of them
+  const size_t n_groups = (size_t)(n_waves * G);
+  std::vector<uint32_t> group_ptr(n_groups + 1, 0), by_group(pieces.size());
+  for (const uint32_t g : group_of) ++group_ptr[g + 1];
+  for (size_t g = 0; g < n_groups; ++g) group_ptr[g + 1] += group_ptr[g];
+  {
+    std::vector<uint32_t> to(group_ptr.begin(), group_ptr.end() - 1);
+    for (size_t q = 0; q < pieces.size(); ++q) by_group[to[group_of[q]]++] = (uint32_t)q;
+  }
+  const bool by_k = h.distinct_k >= h.distinct_j;
+  const int32_t* key = by_k ? tk : tj;
+  std::vector<uint8_t> window((size_t)(by_k ? h.K : h.J));
+  {
+    std::vector<uint32_t> uses(window.size(), 0);
+    for (int64_t p = 0; p < h.nnz; ++p) ++uses[key[p]];
+    uint64_t before = 0;
+    for (size_t r = 0; r < window.size(); ++r) {
+      window[r] = (uint8_t)(before * kStreamWindows / (uint64_t)h.nnz);
+      before += uses[r];
+    }
+  }
+  std::vector<arrow::StreamWave> waves((size_t)n_waves);
+  std::vector<uint32_t> group_nnz(n_groups, 0);
+  for (size_t q = 0; q < pieces.size(); ++q) group_nnz[group_of[q]] += pieces[q].n;
+  uint64_t blocks = 0;
+  for (int64_t w = 0; w < n_waves; ++w) {
+    uint32_t longest = 0;
+    for (int64_t g = 0; g < G; ++g) longest = std::max(longest, group_nnz[(size_t)(w * G + g)]);
+    const uint32_t n = (longest + 7) / 8;
+    const uint64_t z = zero.size();
+    waves[(size_t)w] = {(uint32_t)blocks, n, 0, (uint32_t)(z * w / n_waves), (uint32_t)(z * (w + 1) / n_waves - z * w / n_waves)};
+    blocks += n;
+  }
+  if (blocks > 0xffffffffULL) return false;
+  for (size_t w = 0; w < waves.size(); ++w)
+    for (size_t t = w / arrow::kCsfStreamTeam * arrow::kCsfStreamTeam; t < waves.size() && t / arrow::kCsfStreamTeam == w / arrow::kCsfStreamTeam; ++t)
+      waves[w].turns = std::max(waves[w].turns, waves[t].blocks / arrow::kCsfStreamTurn);
+  size_t total = 0;
+  h.off_waves = total;     total = align3(total + sizeof(arrow::StreamWave) * waves.size());
+  h.off_dst = total;       total = align3(total + sizeof(int32_t) * (size_t)(n_waves * room));
+  h.off_zero = total;      total = align3(total + sizeof(int32_t) * zero.size());
+  h.off_split_ptr = total; total = align3(total + sizeof(uint32_t) * split_ptr.size());
+  h.off_split_y = total;   total = align3(total + sizeof(int32_t) * split_y.size());
+  h.off_entries = total;   total = align3(total + sizeof(arrow::StreamBlock) * (size_t)(blocks + 1));
+  h.bytes.assign(total, 0);
+  unsigned char* base = h.bytes.data();
+  std::memcpy(base + h.off_waves, waves.data(), sizeof(arrow::StreamWave) * waves.size());
+  if (!zero.empty()) std::memcpy(base + h.off_zero, zero.data(), sizeof(int32_t) * zero.size());
+  std::memcpy(base + h.off_split_ptr, split_ptr.data(), sizeof(uint32_t) * split_ptr.size());
+  if (!split_y.empty()) std::memcpy(base + h.off_split_y, split_y.data(), sizeof(int32_t) * split_y.size());
+  int32_t* dst = reinterpret_cast<int32_t*>(base + h.off_dst);
+  arrow::StreamBlock* image = reinterpret_cast<arrow::StreamBlock*>(base + h.off_entries);
+#pragma omp parallel for schedule(static)
+  for (int64_t w = 0; w < n_waves; ++w) {                          // (nothing in here may throw)
+    const arrow::StreamWave& d = waves[(size_t)w];
+    uint32_t place = 0;
+    for (uint32_t g = 0; g < (uint32_t)G; ++g) {
+      const size_t group = (size_t)(w * G + g);
+      std::array<uint32_t, kStreamWindows + 1> to{};
+      for (uint32_t q = group_ptr[group]; q < group_ptr[group + 1]; ++q) {
+        const Piece& p = pieces[by_group[q]];
+        for (uint32_t e = p.first; e < p.first + p.n; ++e) ++to[window[(size_t)key[at(e)]] + 1];
+      }
+      for (size_t v = 1; v < to.size(); ++v) to[v] += to[v - 1];
+      auto record = [&](uint32_t s) -> arrow::StreamBlock::Record& { return image[d.block + s / 8].rec[g * 8 + s % 8]; };
+      for (uint32_t q = group_ptr[group]; q < group_ptr[group + 1]; ++q, ++place) {
+        const Piece& p = pieces[by_group[q]];
+        dst[w * room + place] = p.dst;
+        for (uint32_t e = p.first; e < p.first + p.n; ++e) {
+          const int64_t src = at(e);
+          record(to[window[(size_t)key[src]]]++) = {(uint32_t)tj[src] << 7 | place, tk[src], tv[src]};
+        }
+      }
+      for (uint32_t s = group_nnz[group]; s < d.blocks * 8; ++s) record(s) = {(uint32_t)room, 0, 0.f};
+    }
+    for (; place < (uint32_t)room; ++place) dst[w * room + place] = arrow::kCsfNoRow;
+  }
+  h.n_items = (int64_t)(pieces.size() + zero.size());
+  h.n_split = (int64_t)split_y.size();
+  h.n_partials = slots;
+  h.n_waves = n_waves;
+  h.streams = true;
+  return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -320,7 +513,7 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* ti, 
       for (uint8_t v : seen_j) h->distinct_j += v;
       for (uint8_t v : seen_k) h->distinct_k += v;
     }
-    if (pack_resident(*h, seg_ptr, seg_j, seg_i, at, tk, tv)) {
+    if (pack_resident(*h, seg_ptr, seg_j, seg_i, at, tk, tv) || pack_streams(*h, at, ti, tj, tk, tv)) {
       h->build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
       *out = h.release();
       return ARROW_OK;
@@ -477,7 +670,8 @@ int csf3_upload(csf3_handle* h, void* dev_buf, size_t bytes, void* stream) {
 
 size_t csf3_workspace_bytes(const csf3_handle* h, int32_t R) {
   if (!h || R < 1) return 0;
-  return align3((size_t)h->n_partials * (size_t)R * sizeof(float)) + kAlign3;
+  const size_t scratch = h->streams ? sizeof(float) * (size_t)arrow::stream_scratch(h->J, h->K, R) : 0;
+  return align3((size_t)h->n_partials * (size_t)R * sizeof(float)) + align3(scratch) + kAlign3;
 }
 
 int csf3_set_workspace(csf3_handle* h, void* dev_ws, size_t bytes) {
@@ -503,16 +697,25 @@ int csf3_mttkrp(csf3_handle* h, const float* B, const float* C, float* A, int32_
   auto at = [&](size_t off) { return h->dev + off; };
   const bool prof = h->profiling && h->ev[0];
   if (prof) (void)hipEventRecord(h->ev[0], (hipStream_t)stream);
-  int rc = h->resident ? arrow::launch_mttkrp_resident(reinterpret_cast<const arrow::ResidentItem*>(at(h->off_items)),
-                                                       reinterpret_cast<const arrow::ResidentBlock*>(at(h->off_entries)), h->n_items,
-                                                       h->n_blocks, B, h->J, C, h->K, A, partials, R, stream)
-                       : arrow::launch_mttkrp(reinterpret_cast<const uint32_t*>(at(h->off_item_seg)),
-                                reinterpret_cast<const uint32_t*>(at(h->off_item_ent)),
-                                reinterpret_cast<const int32_t*>(at(h->off_item_dst)),
-                                reinterpret_cast<const uint32_t*>(at(h->off_seg_ptr)),
-                                reinterpret_cast<const int32_t*>(at(h->off_seg_j)),
-                                reinterpret_cast<const arrow::Entry*>(at(h->off_entries)), h->n_items, B,
-                                h->J, C, h->K, A, partials, R, (int32_t)h->longest, (int32_t)((h->nnz + h->n_seg) / h->n_items), stream);
+  int rc;
+  if (h->resident)
+    rc = arrow::launch_mttkrp_resident(reinterpret_cast<const arrow::ResidentItem*>(at(h->off_items)),
+                                       reinterpret_cast<const arrow::ResidentBlock*>(at(h->off_entries)), h->n_items,
+                                       h->n_blocks, B, h->J, C, h->K, A, partials, R, stream);
+  else if (h->streams)
+    rc = arrow::launch_mttkrp_streams(reinterpret_cast<const arrow::StreamWave*>(at(h->off_waves)),
+                                      reinterpret_cast<const arrow::StreamBlock*>(at(h->off_entries)),
+                                      reinterpret_cast<const int32_t*>(at(h->off_dst)),
+                                      reinterpret_cast<const int32_t*>(at(h->off_zero)), h->n_waves, B, h->J, C, h->K, A,
+                                      partials, partials + align3((size_t)h->n_partials * (size_t)R * sizeof(float)) / sizeof(float), R, stream);
+  else
+    rc = arrow::launch_mttkrp(reinterpret_cast<const uint32_t*>(at(h->off_item_seg)),
+                              reinterpret_cast<const uint32_t*>(at(h->off_item_ent)),
+                              reinterpret_cast<const int32_t*>(at(h->off_item_dst)),
+                              reinterpret_cast<const uint32_t*>(at(h->off_seg_ptr)),
+                              reinterpret_cast<const int32_t*>(at(h->off_seg_j)),
+                              reinterpret_cast<const arrow::Entry*>(at(h->off_entries)), h->n_items, B, h->J, C, h->K, A,
+                              partials, R, (int32_t)h->longest, (int32_t)((h->nnz + h->n_seg) / h->n_items), stream);
   if (rc) return fail3(ARROW_EHIP, "mttkrp kernel launch: %s", hipGetErrorString((hipError_t)rc));
   if (prof) (void)hipEventRecord(h->ev[1], (hipStream_t)stream);
   rc = arrow::launch_reduce(reinterpret_cast<const uint32_t*>(at(h->off_split_ptr)),

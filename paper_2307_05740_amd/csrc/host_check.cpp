@@ -58,6 +58,8 @@ int launch_mttkrp(const uint32_t*, const uint32_t*, const int32_t*, const uint32
                   int64_t, const float*, int64_t, const float*, int64_t, float*, float*, int32_t, int32_t, int32_t, void*) { reached("launch_mttkrp"); }
 int launch_mttkrp_resident(const ResidentItem*, const ResidentBlock*, int64_t, int64_t, const float*, int64_t, const float*, int64_t,
                            float*, float*, int32_t, void*) { reached("launch_mttkrp_resident"); }
+int launch_mttkrp_streams(const StreamWave*, const StreamBlock*, const int32_t*, const int32_t*, int64_t, const float*, int64_t,
+                          const float*, int64_t, float*, float*, float*, int32_t, void*) { reached("launch_mttkrp_streams"); }
 }  // namespace arrow
 
 // ---- memory that runs out ---------------------------------------------------------------------------
@@ -305,6 +307,24 @@ int main(int argc, char** argv) {
       if (t) {
         csf3_info_t ci;
         EXPECT(csf3_info(t, &ci) == 0 && ci.items == 520 - ci.split_rows + ci.partials && ci.items < 600, "items of whole slices");
+        csf3_destroy(t);
+      }
+    }
+    {
+      // large enough for the form whose sums lie in LDS: small slices, a hub slice, some without entries
+      const int n = 1 << 21;
+      std::vector<int32_t> ui(n), uj(n), uk(n);
+      std::vector<float> uv(n, 1.f);
+      for (int e = 0; e < n; ++e) {
+        ui[e] = e < 5000 ? 3 : (int32_t)(next_u64(s) % 180000);
+        uj[e] = (int32_t)(next_u64(s) % 1000); uk[e] = (int32_t)(next_u64(s) % 2000);
+      }
+      t = nullptr;
+      EXPECT(csf3_build(180000, 1000, 2000, n, ui.data(), uj.data(), uk.data(), uv.data(), &t) == 0 && t, "csf3_build, sums in LDS");
+      if (t) {
+        csf3_info_t ci;
+        EXPECT(csf3_info(t, &ci) == 0 && ci.items == 180000 - ci.split_rows + ci.partials && ci.split_rows > 0, "items of small slices");
+        EXPECT(csf3_workspace_bytes(t, 33) > csf3_workspace_bytes(t, 32), "workspace grows with the columns");
         csf3_destroy(t);
       }
     }

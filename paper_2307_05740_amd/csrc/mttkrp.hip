@@ -22,9 +22,9 @@
 // which 5 do the work: the kernel was bound by instruction issue (83 % of the cycles).  Uniform 4096^3
 // tensor, 68.7 M entries in 16.5 M fibres, R = 64: 1078 -> 850 us; what it gathers (21.8 GB from the L2 at
 // 64 B per cycle and compute unit) takes 630 us, which is why factors that fit the LDS are read from there
-// (resident_kernel).  The skewed tensor of 16.4 M fibres of one entry, R = 32, gains
-// nothing (507 us): B and C are 8 MiB each and an L2 is 4 MiB, so that 68 % of the requests miss it, 3.3 GB that
-// come at 6.6 TB/s.
+// (resident_kernel).  A skewed tensor of 16.4 M fibres of one entry, R = 32, gained
+// nothing (507 us): B and C are 8 MiB each and an L2 is 4 MiB, so that 68 % of the requests missed it, 3.3 GB that
+// came at 6.6 TB/s; such tensors have a form of their own too (streams_kernel).
 //
 // At the end the lane groups are combined with wavefront shuffles and the result goes to row i of A
 // or, for a slice cut into several items, to a partial vector that the reduction kernel sums in a
@@ -47,6 +47,12 @@ __device__ __forceinline__ void vmuladd(float2& a, float2 x, float2 b) {
 }
 __device__ __forceinline__ void vmuladd(float4& a, float4 x, float4 b) {
   a.x = fmaf(x.x, b.x, a.x); a.y = fmaf(x.y, b.y, a.y); a.z = fmaf(x.z, b.z, a.z); a.w = fmaf(x.w, b.w, a.w);
+}
+
+__device__ __forceinline__ void vselect(float& a, bool c, float b) { a = c ? b : a; }
+__device__ __forceinline__ void vselect(float2& a, bool c, float2 b) { a.x = c ? b.x : a.x; a.y = c ? b.y : a.y; }
+__device__ __forceinline__ void vselect(float4& a, bool c, float4 b) {
+  a.x = c ? b.x : a.x; a.y = c ? b.y : a.y; a.z = c ? b.z : a.z; a.w = c ? b.w : a.w;
 }
 
 // The staged item and what a lane needs to load rows of the factors.
@@ -359,7 +365,181 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// streams kernel: sums in LDS, entries in the order of one factor's rows.  Where slices are small and the factors do
+// not fit an L2, rows of B and C come from behind it whatever the order of the slices: what is in flight at a
+// time touches more rows than an L2 holds.  Here a wavefront owns up to 71 rows of A for the whole launch, so its
+// entries may come in any order, and all wavefronts go through the rows of one factor together, window by window: a
+// part of that factor is in the L2 while everyone needs it, and the rest of the L2 is left to the other factor.  The scheduler
+// prefers a compute unit's older wavefronts; a barrier every 32 entries of a lane group keeps them in step
+// (338 -> 288 us).  Sixteen wavefronts of 10 KiB fill the LDS.  Records are taken from LDS, rows of four
+// entries per lane group are on their way while four others are added.
+//
+// A sum in LDS is read when its row comes up and written after every entry; what follows of the row meanwhile is
+// added up apart, eight entries at a time, so that chains of additions stay short.
+//
+// Skewed 512k x 64k x 64k tensor, 16.8 M entries, R = 32: 507 -> 289 us; 39 % of the requests miss the L2 instead of 68 %,
+// 1.7 GB instead of 3.3, which still bounds it (6.2 TB/s).  R = 128: 2164 -> 1170.  Rows that are no whole
+// lines touch more of them than they need to in every slice of columns: laid out anew (slices_kernel, 33 MB in
+// 15 us) R = 50 takes 618 instead of 1286 us, before 1136.  Error against 64 bits, R = 32: 2-norm 0.82e-7 before, 0.85e-7 now,
+// largest over root mean square 4.2e-5 and 2.1e-5.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kStreamBlock = 64 * kCsfStreamTeam;
+
+template <int VEC, bool SMALL>
+__global__ __launch_bounds__(kStreamBlock) void streams_kernel(
+    const StreamWave* __restrict__ waves, const StreamBlock* __restrict__ blocks, const int32_t* __restrict__ dsts,
+    const int32_t* __restrict__ zero_rows, int64_t n_waves, const float* __restrict__ B, const float* __restrict__ C,
+    float* __restrict__ A, float* __restrict__ partials, int R, int stride, int64_t slice_floats) {
+  using V = typename Vec<VEC>::type;
+  constexpr uint32_t LPR = 8;
+  constexpr int WPB = kStreamBlock / 64, U = 4;        // U: entries of a lane group whose rows are loaded together
+  __shared__ V s_sum[WPB][(kCsfStreamRows + 1) * LPR];
+  __shared__ uint4 s_rec[WPB][64];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+  const int64_t w = (int64_t)blockIdx.x * WPB + wave;
+  if (w >= n_waves) return;
+  const StreamWave d = waves[w];
+  const uint32_t lane = threadIdx.x % 64, g = lane / LPR, l = lane % LPR;
+  // this lane's columns of the slice: a part of them may lie beyond R in factors laid out anew, never in the caller's
+  const int c = (int)(blockIdx.y * LPR + l) * VEC;
+  const bool ok = c < R;
+  const uint32_t row_bytes = 4u * (uint32_t)stride, col_bytes = ok ? 4u * l * VEC : 0u;
+  const char* Bc = reinterpret_cast<const char*>(B + (int64_t)blockIdx.y * slice_floats);
+  const char* Cc = reinterpret_cast<const char*>(C + (int64_t)blockIdx.y * slice_floats);
+  V* sums = s_sum[wave] + l;
+#pragma unroll
+  for (uint32_t r = 0; r < (kCsfStreamRows + 1) / 8; ++r) sums[(r * 8 + g) * LPR] = vzero<VEC>();
+  strip_sync();
+  struct Batch { V b[U], c[U]; float val[U]; uint32_t at[U]; } q[2];
+  V base = vzero<VEC>(), y = vzero<VEC>(), x = vzero<VEC>();
+  uint32_t prev = ~0u;
+  auto issue = [&](Batch& t, int s0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint4 r = s_rec[wave][g * 8 + s0 + u];
+      t.at[u] = (r.x & 127u) * LPR;
+      t.val[u] = __uint_as_float(r.z);
+      t.b[u] = load_row<VEC, SMALL>(Bc, (int32_t)(r.x >> 7), row_bytes, col_bytes);
+      t.c[u] = load_row<VEC, SMALL>(Cc, (int32_t)r.y, row_bytes, col_bytes);
+    }
+  };
+  auto sum = [&](const Batch& t) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const V old = sums[t.at[u]];
+      const bool other = t.at[u] != prev;
+      prev = t.at[u];
+      vselect(base, other, old);
+      vselect(y, other, vzero<VEC>());
+      vselect(x, other, vzero<VEC>());
+      V p = vzero<VEC>();
+      vfma(p, t.val[u], t.c[u]);
+      vmuladd(x, p, t.b[u]);
+      V now = y;
+      vadd(now, x);
+      vadd(now, base);
+      sums[t.at[u]] = now;
+    }
+  };
+  StreamBlock::Record next;
+  auto load = [&](uint32_t n) {
+    const StreamBlock::Record* p = &blocks[d.block + min(n, d.blocks - 1)].rec[lane];
+    return StreamBlock::Record{stream_load(&p->j_slot), stream_load(&p->k), stream_load(&p->val)};
+  };
+  auto put = [&] { s_rec[wave][lane] = make_uint4(next.j_slot, (uint32_t)next.k, __float_as_uint(next.val), 0u); };
+  if (d.blocks > 0) {
+    next = load(0);
+    put();
+    strip_sync();
+    next = load(1);
+    issue(q[0], 0);
+    for (uint32_t n = 0; n < d.blocks; ++n) {
+      issue(q[1], U);
+      strip_sync();
+      put();
+      strip_sync();
+      next = load(n + 2);
+      sum(q[0]);
+      if (n + 1 < d.blocks) issue(q[0], 0);
+      sum(q[1]);
+      vadd(y, x);
+      x = vzero<VEC>();
+      if (n % 4 == 3) prev = ~0u;
+      if ((n + 1) % kCsfStreamTurn == 0) __builtin_amdgcn_s_barrier();      // (nothing is handed over)
+    }
+  }
+  for (uint32_t n = d.blocks / kCsfStreamTurn; n < d.turns; ++n) __builtin_amdgcn_s_barrier();
+  strip_sync();
+  auto store = [&](float* row, V v) {
+    if (c + VEC <= R) { vstore_stream<VEC>(row + c, v); return; }
+    float f[VEC];
+    __builtin_memcpy(f, &v, sizeof f);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      if (c + e < R) row[c + e] = f[e];
+  };
+#pragma unroll
+  for (uint32_t r = 0; r < (kCsfStreamRows + 1) / 8; ++r) {
+    const uint32_t slot = r * 8 + g;
+    const int32_t dst = slot < (uint32_t)kCsfStreamRows ? dsts[w * kCsfStreamRows + slot] : kCsfNoRow;
+    if (dst != kCsfNoRow) store(dst >= 0 ? A + (size_t)dst * (size_t)R : partials + (size_t)(-1 - dst) * (size_t)R, sums[slot * LPR]);
+  }
+  for (uint32_t z = g; z < d.zeros; z += 8) store(A + (size_t)zero_rows[d.zero + z] * (size_t)R, vzero<VEC>());
+}
+
+// Rows of B, then of C, in slices of `width` columns one after the other; zeros in the columns from R on.
+__global__ __launch_bounds__(kBlock) void slices_kernel(const float* __restrict__ B, int64_t J, const float* __restrict__ C,
+                                                        int64_t K, int R, int width, float4* __restrict__ out, int64_t n) {
+  const int64_t at = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (at >= n) return;
+  const int quads = width / 4;
+  const int64_t row = at / quads % (J + K);
+  const int c = (int)(at / quads / (J + K)) * width + (int)(at % quads) * 4;
+  const float* p = row < J ? B + row * R : C + (row - J) * R;
+  float4 v = vzero<4>();
+  if (c + 4 <= R) v = gload<4>(p + c);
+  else {
+    if (c < R) v.x = p[c];
+    if (c + 1 < R) v.y = p[c + 1];
+    if (c + 2 < R) v.z = p[c + 2];
+  }
+  out[at] = v;
+}
+
 }  // namespace
+
+int launch_mttkrp_streams(const StreamWave* waves, const StreamBlock* blocks, const int32_t* dst, const int32_t* zero_rows,
+                          int64_t n_waves, const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A,
+                          float* partials, float* scratch, int32_t R, void* stream) {
+  if (n_waves <= 0) return 0;
+  // Where rows are no whole lines of 128 bytes, or parts of one, the factors are laid out anew in slices that are.
+  const int width = stream_slice(R), vec = width / 8;
+  const int64_t slices = ceil_div(R, width);
+  const bool whole = (R % width == 0 || width % R == 0) && ((uintptr_t)B | (uintptr_t)C) % 128 == 0;
+  const bool small = small_matrix(b_rows, whole ? R : width) && small_matrix(c_rows, whole ? R : width);
+  int64_t slice_floats = width;
+  if (!whole) {
+    const int64_t n = (b_rows + c_rows) * slices * width / 4, blocks = ceil_div(n, kBlock);
+    if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(slices_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, (hipStream_t)stream, B, b_rows, C, c_rows, (int)R,
+                       width, reinterpret_cast<float4*>(scratch), n);
+    slice_floats = (b_rows + c_rows) * width;
+    B = scratch;
+    C = scratch + b_rows * width;
+  }
+  const int64_t groups = ceil_div(n_waves, kStreamBlock / 64);
+  if (groups > 0x7fffffffLL || slices > 65535) return (int)hipErrorInvalidConfiguration;
+  const dim3 grid((unsigned)groups, (unsigned)slices);
+#define ARROW_LAUNCH(V, SM)                                                                                             \
+  hipLaunchKernelGGL((streams_kernel<V, SM>), grid, dim3(kStreamBlock), 0, (hipStream_t)stream, waves, blocks, dst, zero_rows, \
+                     n_waves, B, C, A, partials, (int)R, whole ? (int)R : width, slice_floats)
+#define ARROW_VEC(SM) if (vec == 4) ARROW_LAUNCH(4, SM); else if (vec == 2) ARROW_LAUNCH(2, SM); else ARROW_LAUNCH(1, SM)
+  if (small) { ARROW_VEC(true); } else { ARROW_VEC(false); }
+#undef ARROW_VEC
+#undef ARROW_LAUNCH
+  return (int)hipGetLastError();
+}
 
 int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* blocks, int64_t n_items, int64_t n_blocks,
                            const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials,

@@ -355,3 +355,38 @@ def test_rows_of_many_partial_vectors(torch, k, fuse):
     op.close()
     Yref, B = oracle.spmm(rowptr, colidx, vals, X)
     assert_within(Y.cpu().numpy(), Yref, B)
+
+
+@pytest.mark.parametrize("I,J,K,R,offset", [
+    (70001, 13001, 12000, 1, 0), (70001, 13001, 12000, 3, 0), (70001, 12000, 13001, 8, 0), (70001, 13001, 12000, 9, 4),
+    (200000, 900, 1000, 12, 0), (200000, 1000, 900, 16, 0), (200000, 1000, 900, 16, 8), (330007, 13001, 12000, 17, 0),
+    (70001, 13001, 12000, 32, 0), (70001, 13001, 12000, 32, 4), (200000, 900, 1000, 33, 0), (70001, 13001, 12000, 96, 0)])
+def test_mttkrp_rows_summed_in_lds(torch, I, J, K, R, offset):
+    """The form for many small slices: hub slices cut into pieces, slices of one entry and without any, more rows
+    than fit the wavefronts of the chip at once (330007), factors whose rows are no whole lines or do not begin
+    at one (`offset` floats), duplicates, rows that no entry refers to (infinite), entries in any order."""
+    rng = np.random.default_rng(I + R)
+    nnz = 2_300_000
+    i = (I * rng.random(nnz) ** 1.5).astype(np.int64)
+    i[:40000], i[40000:41000] = 11, I - 1
+    j, k = rng.integers(1, J - 1, nnz), rng.integers(1, K - 1, nnz)
+    i[-30:], j[-30:], k[-30:] = 77, 5, 6
+    i[(i > 500) & (i < 600)] = 601
+    v = rng.uniform(-1, 1, nnz).astype(np.float32)
+    i, j, k = (x.astype(np.int32) for x in (i, j, k))
+    B, C = synth.normal_matrix(J, R, seed=34), synth.normal_matrix(K, R, seed=35)
+    Aref, E = oracle.mttkrp((I, J, K), i, j, k, v, B, C)
+    B[[0, -1]], C[[0, -1]] = np.inf, np.nan
+    op = binding.Csf3Mttkrp((I, J, K), i, j, k, v)
+    assert op.info["items"] == I - op.info["split_rows"] + op.info["partials"] and op.info["split_rows"] > 0
+    Bd, Cd = (torch.empty(M.size + 64, device="cuda")[offset:offset + M.size].view(M.shape).copy_(torch.from_numpy(M)) for M in (B, C))
+    A = torch.full((I, R), float("nan"), device="cuda")
+    op.mttkrp(Bd, Cd, A)
+    assert_within(A.cpu().numpy(), Aref, E)
+    first = A.clone()
+    op.mttkrp(Bd, Cd, A)
+    assert torch.equal(first, A)
+    op.mttkrp(torch.ones((J, R + 1), device="cuda"), torch.ones((K, R + 1), device="cuda"))   # a larger workspace, then
+    op.mttkrp(Bd, Cd, A)                                                                      # fewer columns again
+    assert torch.equal(first, A)
+    op.close()
