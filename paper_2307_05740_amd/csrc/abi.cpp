@@ -209,13 +209,13 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
       a.entries_once = (im.nnz_rows + im.nnz_chunks) * (int64_t)sizeof(arrow::Entry) > kEntriesOnce;
       auto launch = [&](int parts, int32_t kc) -> int {
         return check_hip(arrow::launch_product(a, parts, im.piece_slots, im.n_rows, im.empty_slots, im.classes > 0,
-                                               !im.row_major, h->n, kc, stream), "product kernel launch");
+                                               !im.row_major && im.n_chunks > kFewChunks, h->n, kc, stream), "product kernel launch");
       };
       // the wave list and the pieces follow the chunk kernel's column slicing, the short rows run in
       // one pass over whole rows; where that is the same shape, or where both lists are so short that a
       // second launch is most of the time, one launch takes all of it (Chung-Lu 3326, k = 128: 11.1 -> 6.7
-      // us; R-MAT 7914, k = 135: 16.0 -> 11.3 us).  A
-      // profiled product keeps the lists apart so that each has a time of its own.
+      // us; R-MAT 7914, k = 135: 16.0 -> 11.3 us; the head rows beside 511 window tiles of 512 rows, k = 128, 13.3 ->
+      // 8.9 us).  A profiled product keeps the lists apart so that each has a time of its own.
       using namespace arrow;
       int rc = ARROW_OK;
       if (h->profiling && prof) {
@@ -226,7 +226,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
           if (!rc) rc = launch(kPartShort, h->tuning.kc);
         }
       } else if (same_shape(k, tune.kc, h->tuning.kc, acc) ||
-                 (im.row_major && im.n_chunks <= kFewChunks && im.n_rows <= kFewRows)) {
+                 (im.n_chunks <= kFewChunks && im.n_rows <= kFewRows)) {
         rc = launch(kPartAll, tune.kc);
       } else {
         rc = launch(kPartChunks | kPartPieces, tune.kc);

@@ -390,3 +390,29 @@ def test_mttkrp_rows_summed_in_lds(torch, I, J, K, R, offset):
     op.mttkrp(Bd, Cd, A)                                                                      # fewer columns again
     assert torch.equal(first, A)
     op.close()
+
+
+@pytest.mark.parametrize("k", [7, 20, 64, 128, 150])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_short_work_lists_beside_window_tiles(torch, k, fuse):
+    """More rows than the wave list is ordered by rows for, nearly all of them in window tiles: what is left, chunks of
+    long rows, pieces and short rows, goes into one launch."""
+    n, b, m = 140001, 512, 14
+    rng = np.random.default_rng(k)
+    lo = np.arange(n) // b * b
+    inside = lo[:, None] + (rng.random((n, m)) * np.minimum(b, n - lo)[:, None]).astype(np.int64)
+    hub = rng.choice(64, 5, replace=False)
+    far = np.concatenate([np.stack([np.full(c, h), rng.choice(n, c, replace=False)], 1) for h, c in zip(hub, (3000, 1500, 900, 600, 400))])
+    key = np.unique(np.concatenate([(np.arange(n)[:, None] * n + inside).ravel(), far[:, 0] * n + far[:, 1]]))
+    row, colidx = key // n, (key % n).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(row, minlength=n))]).astype(np.int64)
+    vals = rng.uniform(-1, 1, len(key)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=36)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, b, options=binding.arrow_options_default(fuse_levels=fuse))
+    level = op.levels()[0]
+    assert level["window_tiles"] > 200 and 0 < level["chunks"] <= 2048 and level["short_rows"] <= 16384
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    op.close()
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
