@@ -1073,11 +1073,18 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(
         for (int u = 0; u < 8; u += 2 * m) vadd(p[u], p[u + m]);
       vadd(acc, p[0]);
     }
-    V p[8];
+    if (s + 3 * step < end) {
+      V p[4];
 #pragma unroll
-    for (int u = 0; u < 7; ++u) if (s + u * step < end) p[u] = vload_stream<VEC>(Pc + (size_t)(s + u * step) * (size_t)k);
+      for (int u = 0; u < 4; ++u) p[u] = vload_stream<VEC>(Pc + (size_t)(s + u * step) * (size_t)k);
+      vadd(p[0], p[1]); vadd(p[2], p[3]); vadd(p[0], p[2]); vadd(acc, p[0]);
+      s += 4 * step;
+    }
+    V p[3];
 #pragma unroll
-    for (int u = 0; u < 7; ++u) if (s + u * step < end) vadd(acc, p[u]);
+    for (int u = 0; u < 3; ++u) if (s + u * step < end) p[u] = vload_stream<VEC>(Pc + (size_t)(s + u * step) * (size_t)k);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) if (s + u * step < end) vadd(acc, p[u]);
 #pragma unroll
     for (int m = LPR; m < 64; m <<= 1) vadd(acc, vshfl_xor(acc, m));
     return acc;
