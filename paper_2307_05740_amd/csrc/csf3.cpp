@@ -83,8 +83,11 @@ namespace {
 // and where it does not: fill (4000 x 4000 x 128 of 2.0 M, 1.52: 20.5 / 46.1 / 79.3 -> 12.2 / 47.1 / 86.1), few items
 // (128 x 4000 x 1000 of 512 K, 128 items: 9.6 / 17.0 / 28.5 -> 14.1 / 18.1 / 19.8), few entries to pay for
 // copying the factors to LDS (1000 x 1000 x 200 of 200 K: 7.6 / 10.6 / 14.6 -> 6.6 / 11.6 / 18.5).
-constexpr int64_t kResidentNnz = 1 << 19;
-constexpr int64_t kResidentItems = 512;
+// Fewer items do where they are short (438 x 789 x 1882 of 650 K: 10.1 / 13.4 / 28.2 -> 9.4 / 10.0 / 21.9; 215 x 2391 x 356 of
+// 183 K: 8.9 / 9.7 / 14.8 -> 8.1 / 9.1 / 12.8; but 337 x 3065 x 1819 of 1.9 M: 15.8 / 23.2 / 63 -> 20.5 / 22.3 / 44.5), and fewer
+// entries where fibres hold more than one (708 x 2340 x 201 of 333 K, 1.1 each, R = 128: 19.5 -> 20.1).
+constexpr int64_t kResidentNnz = 1 << 17, kResidentNnzSingle = 1 << 19;
+constexpr int64_t kResidentItems = 512, kResidentItemsShort = 200, kResidentShort = 2200;   // (rows of a short item)
 constexpr double kResidentFill = 1.4;
 constexpr int64_t kResidentSegs = 4096;    // segments of an item
 // Lanes whose 16-byte reads of LDS are served together (found by timing reads whose rows lie in different banks
@@ -106,7 +109,7 @@ constexpr uint8_t kSixteens[4][16] = {{0, 1, 2, 3, 12, 13, 14, 15, 20, 21, 22, 2
 template <typename At>
 bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const std::vector<int32_t>& seg_j,
                    const std::vector<int32_t>& seg_i, At at, const int32_t* tk, const float* tv) {
-  if (h.J + h.K + 1 > arrow::kCsfRowsInLds || h.nnz < kResidentNnz) return false;
+  if (h.J + h.K + 1 > arrow::kCsfRowsInLds || h.nnz < (h.nnz * 20 < h.n_seg * 23 ? kResidentNnzSingle : kResidentNnz)) return false;
   const double most = kResidentFill * (double)(h.nnz + h.n_seg);           // rows read, fill included
   if (64.0 * arrow::kCsfBlockSteps * (double)h.I > most) return false;     // (a block per slice at least)
   struct Part { uint32_t seg, n, block, blocks; int32_t dst; };
@@ -133,7 +136,9 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
     }
     s = end;
   }
-  if (slots > 0x7fffffffLL || parts.size() > 0x7fffff00ULL || (int64_t)parts.size() < kResidentItems) return false;
+  if (slots > 0x7fffffffLL || parts.size() > 0x7fffff00ULL) return false;
+  const int64_t least = h.nnz + h.n_seg <= kResidentShort * (int64_t)parts.size() ? kResidentItemsShort : kResidentItems;
+  if ((int64_t)parts.size() < least) return false;
   // segments by length, longest first: at_len[l] = where those of length kSegMax - l begin
   auto by_length = [&](const Part& p, std::array<uint32_t, kSegMax + 2>& at_len) {
     at_len.fill(0);
