@@ -27,6 +27,13 @@ namespace {
 
 constexpr int64_t kResidentWaves = 8192;   // wavefronts the chip holds
 constexpr int kSampledStage = 1024;   // entries of the group list a workgroup stages at once
+// Bytes of U from which on the rows of U that short rows read carry the streaming hint: they then leave the caches to the rows
+// of V, and where everything still fits the cache behind the L2s they are better kept there.  R-MAT 100k, k = 96 (37
+// MiB) 61.2 us, with the hint 63.6; k = 128 (49 MiB) 74.1 and 75.5; 300k, k = 50 (57 MiB) 162.4 and 155.0; 200k, k = 100 (76 MiB)
+// 199.0 and 190.0; 1m, k = 128 1233 and 1227; grid of 350 x 350, k = 96 (45 MiB) 35.2 and 37.2, 500 x 500, k = 100 (95 MiB) 71.5
+// and 62.2; dense blocks, 150k, k = 128 (73 MiB) 217.6 and 212.8.  (Not in the launch
+// of both lists together: the choice alone costs 30k, k = 24, 0.6 % there.)
+constexpr int64_t kSampledOnce = 56 << 20;
 
 struct alignas(16) SampledShared {
   Entry ent[kSampledStage];
@@ -143,7 +150,7 @@ __device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const 
 // an item where it is longer than that).  As many lane groups as there are to spare share an item.
 // (With entries that do not fit read from memory one batch after the other instead: the 55-entry rows of
 // dense diagonal blocks, 2.9 M rows, k = 16, 3510 us; 2180 us with a strip of 16 entries per lane group.)
-template <int VEC, int LPR, int NB, bool SMALL, bool WINDOW>
+template <int VEC, int LPR, int NB, bool SMALL, bool WINDOW, bool ONCE>
 __device__ __forceinline__ void sampled_rows(SampledShared& sh, const SampledArgs& a, int64_t first, int n_it) {
   using V = typename Vec<VEC>::type;
   constexpr int GPB = kBlock / LPR;
@@ -221,7 +228,8 @@ __device__ __forceinline__ void sampled_rows(SampledShared& sh, const SampledArg
       const uint32_t mid = sh.mid[it] < lo ? lo : (sh.mid[it] > hi ? hi : sh.mid[it]);
       const uint32_t skip = (uint32_t)(tid / LPR % share) * NB;
       const float* Urow = a.U + (size_t)row * (size_t)a.k;
-      V u0 = lc0.ok ? gload<VEC>(Urow + lc0.c) : vzero<VEC>();
+      V u0 = vzero<VEC>();
+      if (lc0.ok) u0 = ONCE ? vload_stream<VEC>(Urow + lc0.c) : gload<VEC>(Urow + lc0.c);
       drop_shared(u0, lc0.shared);
       for (int seg = WINDOW ? 1 : 0; seg < 2; ++seg) {
         const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Vh : a.V);
@@ -256,12 +264,12 @@ __global__ __launch_bounds__(kBlock) void sddmm_chunks_kernel(const SampledArgs 
   if (ch < a.n_chunks) sampled_chunk<VEC, LPR, NB, SMALL>(ents[wave], ats[wave], a, ch, 0);
 }
 
-template <int VEC, int LPR, int NB, bool SMALL, bool WINDOW>
+template <int VEC, int LPR, int NB, bool SMALL, bool WINDOW, bool ONCE>
 __global__ __launch_bounds__(kBlock) void sddmm_rows_kernel(const SampledArgs a) {
   __shared__ SampledShared sh;
   const int64_t first = (int64_t)blockIdx.x * a.items;
   const int n_it = a.n_rows - first < a.items ? (int)(a.n_rows - first) : a.items;
-  if (n_it > 0) sampled_rows<VEC, LPR, NB, SMALL, WINDOW>(sh, a, first, n_it);
+  if (n_it > 0) sampled_rows<VEC, LPR, NB, SMALL, WINDOW, ONCE>(sh, a, first, n_it);
 }
 
 // Both lists in one launch (short lists: the second launch would be most of the time).
@@ -284,7 +292,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SampledArgs a) {
   }
   const int64_t first = (int64_t)(blockIdx.x - a.chunk_blocks) * a.items;
   const int n_it = a.n_rows - first < a.items ? (int)(a.n_rows - first) : a.items;
-  if (n_it > 0) sampled_rows<VEC, LPR, NB, SMALL, false>(sh.rows, a, first, n_it);
+  if (n_it > 0) sampled_rows<VEC, LPR, NB, SMALL, false, false>(sh.rows, a, first, n_it);
 }
 
 }  // namespace
@@ -313,6 +321,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   const int64_t row_blocks = ceil_div(ceil_div(a.n_rows, a.items), kDies) * kDies;
   if (chunk_blocks + row_blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
   a.runs = windows && !die_queues;
+  const bool once = v_rows * a.k * (int64_t)sizeof(float) >= kSampledOnce;
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;
     constexpr int NB = LPR < kSampledBatch ? LPR : kSampledBatch;
@@ -321,13 +330,15 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   else hipLaunchKernelGGL((KERNEL<VEC, LPR, NB, false __VA_ARGS__>), dim3((unsigned)(BLOCKS)), dim3(kBlock), 0, st, a)
 #define ARROW_COMMA ,
     if (window_rows) {
-      if (row_blocks > 0) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA true); }
+      if (row_blocks > 0 && once) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA true ARROW_COMMA true); }
+      else if (row_blocks > 0) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA true ARROW_COMMA false); }
     } else if (!windows && chunk_blocks > 0) {
       a.chunk_blocks = (uint32_t)chunk_blocks;
       ARROW_LAUNCH(sddmm_kernel, chunk_blocks + row_blocks, );
     } else {
       if (chunk_blocks > 0) { ARROW_LAUNCH(sddmm_chunks_kernel, chunk_blocks, ); }
-      if (row_blocks > 0) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA false); }
+      if (row_blocks > 0 && once) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA false ARROW_COMMA true); }
+      else if (row_blocks > 0) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA false ARROW_COMMA false); }
     }
 #undef ARROW_COMMA
 #undef ARROW_LAUNCH

@@ -416,3 +416,28 @@ def test_short_work_lists_beside_window_tiles(torch, k, fuse):
     op.close()
     Yref, B = oracle.spmm(rowptr, colidx, vals, X)
     assert_within(Y.cpu().numpy(), Yref, B)
+
+
+@pytest.mark.parametrize("blocks", [False, True])
+@pytest.mark.parametrize("k", [105, 107, 112])
+def test_sampled_product_of_large_factors(torch, k, blocks):
+    """Factors beyond the size from which the rows of U are read past the caches: short rows, long ones and rows of
+    window tiles, a row length that is no multiple of four columns."""
+    n, b = 140003, 512
+    assert n * k * 4 >= 56 << 20
+    rng = np.random.default_rng(k)
+    m = 14 if blocks else 3
+    lo = np.arange(n) // b * b
+    near = lo[:, None] + (rng.random((n, m)) * np.minimum(b, n - lo)[:, None]).astype(np.int64) if blocks else rng.integers(0, n, (n, m))
+    hub = np.repeat([3, 5, 7], [9000, 700, 90])
+    key = np.unique(np.concatenate([(np.arange(n)[:, None] * n + near).ravel(), hub * n + rng.integers(0, n, len(hub))]))
+    row, colidx = key // n, (key % n).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(row, minlength=n))]).astype(np.int64)
+    vals = rng.uniform(-1, 1, len(key)).astype(np.float32)
+    U, V = synth.normal_matrix(n, k, seed=37), synth.normal_matrix(n, k, seed=38)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, b)
+    S = torch.full((len(key),), float("nan"), device="cuda")
+    op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), S)
+    op.close()
+    Sref, B = oracle.sddmm(rowptr, colidx, vals, U, V)
+    assert_within(S.cpu().numpy(), Sref, B)
