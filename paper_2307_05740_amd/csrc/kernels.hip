@@ -1039,7 +1039,9 @@ __global__ __launch_bounds__(kBlock) void sddmm_corner_kernel(
 // combined by the same butterfly.  Rows of many partial vectors are shared by the wavefronts of the workgroup, and eight
 // loads are on their way instead of four: the launch lasted as long as one wavefront took for the longest row
 // (a hub of 2048 partial vectors, 64 rounds of loads one after the other).  Such rows are usually neighbours, so
-// a workgroup takes rows that are far apart.  Chung-Lu 2m k = 32 25.9 -> 13.4 us, R-MAT 1m k = 64 13.3 -> 10.9,
+// a workgroup takes rows that are far apart.  Partial vectors shorter than a line are left to one wavefront per row, neighbours
+// beside each other: they share lines, and 16 and more lane groups take them (Chung-Lu 500k, k = 16, 5.6 us a launch, shared
+// 7.6).  Chung-Lu 2m k = 32 25.9 -> 13.4 us, R-MAT 1m k = 64 13.3 -> 10.9,
 // R-MAT 8m k = 128, where memory bounds it, 320 -> 308.  (Sixteen wavefronts per workgroup: 18, 16 and 346 us; a lane
 // group per short row: 22, 18 and 343.)
 template <int VEC, int LPR>
@@ -1055,30 +1057,32 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(
   const uint32_t g = lane / LPR, l = lane % LPR;
   const LaneColumns lc = lane_columns<VEC>((int)l, blockIdx.y * width, k, width);
   const float* __restrict__ Pc = partials + (lc.ok ? lc.c : 0);
+  const bool apart = LPR * VEC >= 32 && k >= 32;
   // lane t holds what belongs to the row of wavefront t
-  const int64_t mine = (int64_t)blockIdx.x + (int64_t)(lane % WPB) * gridDim.x;
+  const int64_t mine = !apart ? (int64_t)blockIdx.x * WPB + lane % WPB : (int64_t)blockIdx.x + (int64_t)(lane % WPB) * gridDim.x;
   uint32_t lo_of = 0, hi_of = 0;
   int32_t y_of = 0;
   if (mine < n_split) { lo_of = split_ptr[mine]; hi_of = split_ptr[mine + 1]; y_of = split_y[mine]; }
   auto of = [](auto v, int t) { return (decltype(v))__builtin_amdgcn_readlane((int)v, t); };
   auto sum = [&](uint32_t s, uint32_t end, uint32_t step) {
     V acc = vzero<VEC>();
-    for (; s + 7 * step < end; s += 8 * step) {
-      V p[8];
+    if constexpr (LPR * VEC >= 16) {
+      for (; s + 7 * step < end; s += 8 * step) {
+        V p[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) p[u] = vload_stream<VEC>(Pc + (size_t)(s + u * step) * (size_t)k);
+        for (int u = 0; u < 8; ++u) p[u] = vload_stream<VEC>(Pc + (size_t)(s + u * step) * (size_t)k);
 #pragma unroll
-      for (int m = 1; m < 8; m *= 2)
+        for (int m = 1; m < 8; m *= 2)
 #pragma unroll
-        for (int u = 0; u < 8; u += 2 * m) vadd(p[u], p[u + m]);
-      vadd(acc, p[0]);
+          for (int u = 0; u < 8; u += 2 * m) vadd(p[u], p[u + m]);
+        vadd(acc, p[0]);
+      }
     }
-    if (s + 3 * step < end) {
+    for (; s + 3 * step < end; s += 4 * step) {
       V p[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) p[u] = vload_stream<VEC>(Pc + (size_t)(s + u * step) * (size_t)k);
       vadd(p[0], p[1]); vadd(p[2], p[3]); vadd(p[0], p[2]); vadd(acc, p[0]);
-      s += 4 * step;
     }
     V p[3];
 #pragma unroll
@@ -1095,7 +1099,7 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(
     if (accumulate) vadd(acc, vload_stream<VEC>(to));
     vstore_stream<VEC>(to, acc);
   };
-  uint32_t shared = (uint32_t)__ballot(lane < WPB && hi_of - lo_of >= kLong);
+  uint32_t shared = (uint32_t)__ballot(apart && lane < WPB && hi_of - lo_of >= kLong);
   if (!(shared >> wave & 1u)) {
     const uint32_t lo = of(lo_of, wave), hi = of(hi_of, wave);
     if (lo < hi) store(of(y_of, wave), sum(lo + g, hi, G));
