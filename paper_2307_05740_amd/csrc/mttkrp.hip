@@ -49,12 +49,6 @@ __device__ __forceinline__ void vmuladd(float4& a, float4 x, float4 b) {
   a.x = fmaf(x.x, b.x, a.x); a.y = fmaf(x.y, b.y, a.y); a.z = fmaf(x.z, b.z, a.z); a.w = fmaf(x.w, b.w, a.w);
 }
 
-__device__ __forceinline__ void vselect(float& a, bool c, float b) { a = c ? b : a; }
-__device__ __forceinline__ void vselect(float2& a, bool c, float2 b) { a.x = c ? b.x : a.x; a.y = c ? b.y : a.y; }
-__device__ __forceinline__ void vselect(float4& a, bool c, float4 b) {
-  a.x = c ? b.x : a.x; a.y = c ? b.y : a.y; a.z = c ? b.z : a.z; a.w = c ? b.w : a.w;
-}
-
 // The staged item and what a lane needs to load rows of the factors.
 struct ItemView {
   const Entry* ent;
@@ -372,17 +366,19 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
 // entries may come in any order, and all wavefronts go through the rows of one factor together, window by window: a
 // part of that factor is in the L2 while everyone needs it, and the rest of the L2 is left to the other factor.  The scheduler
 // prefers a compute unit's older wavefronts; a barrier every 32 entries of a lane group keeps them in step
-// (338 -> 288 us).  Sixteen wavefronts of 10 KiB fill the LDS.  Records are taken from LDS, rows of four
+// (338 -> 288 us with sums in 32 bits).  Sixteen wavefronts of 10 KiB fill the LDS.  Records are taken from LDS, rows of four
 // entries per lane group are on their way while four others are added.
 //
 // A sum in LDS is read when its row comes up and written after every entry; what follows of the row meanwhile is
-// added up apart, eight entries at a time, so that chains of additions stay short.
+// added in 64 bits, whose additions and products take no longer here than those of 32: rounded once per run of a
+// row's entries, not per entry (in 32 bits with chains of 8 and 32 entries 290 us instead of 293, but the error
+// below was 0.85e-7).
 //
-// Skewed 512k x 64k x 64k tensor, 16.8 M entries, R = 32: 507 -> 289 us; 39 % of the requests miss the L2 instead of 68 %,
+// Skewed 512k x 64k x 64k tensor, 16.8 M entries, R = 32: 506 -> 293 us; 39 % of the requests miss the L2 instead of 68 %,
 // 1.7 GB instead of 3.3, which still bounds it (6.2 TB/s).  R = 128: 2164 -> 1170.  Rows that are no whole
 // lines touch more of them than they need to in every slice of columns: laid out anew (slices_kernel, 33 MB in
-// 15 us) R = 50 takes 618 instead of 1286 us, before 1136.  Error against 64 bits, R = 32: 2-norm 0.82e-7 before, 0.85e-7 now,
-// largest over root mean square 4.2e-5 and 2.1e-5.
+// 15 us) R = 50 takes 618 instead of 1286 us, before 1136.  Error against 64 bits, R = 32: 2-norm
+// 0.82 -> 0.61e-7, largest over root mean square 4.2 -> 1.6e-5; 400k x 2000 x 2000 uniform, R = 25: 0.60 -> 0.54e-7.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kStreamBlock = 64 * kCsfStreamTeam;
 
@@ -412,7 +408,7 @@ __global__ __launch_bounds__(kStreamBlock) void streams_kernel(
   for (uint32_t r = 0; r < (kCsfStreamRows + 1) / 8; ++r) sums[(r * 8 + g) * LPR] = vzero<VEC>();
   strip_sync();
   struct Batch { V b[U], c[U]; float val[U]; uint32_t at[U]; } q[2];
-  V base = vzero<VEC>(), y = vzero<VEC>(), x = vzero<VEC>();
+  double acc[VEC] = {};
   uint32_t prev = ~0u;
   auto issue = [&](Batch& t, int s0) {
 #pragma unroll
@@ -430,16 +426,18 @@ __global__ __launch_bounds__(kStreamBlock) void streams_kernel(
       const V old = sums[t.at[u]];
       const bool other = t.at[u] != prev;
       prev = t.at[u];
-      vselect(base, other, old);
-      vselect(y, other, vzero<VEC>());
-      vselect(x, other, vzero<VEC>());
+      float was[VEC], b[VEC], x[VEC], now[VEC];
       V p = vzero<VEC>();
       vfma(p, t.val[u], t.c[u]);
-      vmuladd(x, p, t.b[u]);
-      V now = y;
-      vadd(now, x);
-      vadd(now, base);
-      sums[t.at[u]] = now;
+      __builtin_memcpy(was, &old, sizeof was);
+      __builtin_memcpy(b, &t.b[u], sizeof b);
+      __builtin_memcpy(x, &p, sizeof x);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        acc[e] = fma((double)x[e], (double)b[e], other ? (double)was[e] : acc[e]);
+        now[e] = (float)acc[e];
+      }
+      __builtin_memcpy(&sums[t.at[u]], now, sizeof now);
     }
   };
   StreamBlock::Record next;
@@ -463,9 +461,6 @@ __global__ __launch_bounds__(kStreamBlock) void streams_kernel(
       sum(q[0]);
       if (n + 1 < d.blocks) issue(q[0], 0);
       sum(q[1]);
-      vadd(y, x);
-      x = vzero<VEC>();
-      if (n % 4 == 3) prev = ~0u;
       if ((n + 1) % kCsfStreamTurn == 0) __builtin_amdgcn_s_barrier();      // (nothing is handed over)
     }
   }
