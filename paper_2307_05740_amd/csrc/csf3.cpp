@@ -260,22 +260,24 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
 
 // Where the streams form pays (both forms measured, us, R = 8 / 32 / 50 / 128; skewed tensors of 32 entries per slice unless
 // said otherwise):
-//   524288 x 65536 x 65536 of 16.8 M           329 / 507 / 1136 / 2164 -> 205 / 289 / 618 / 1170
-//   180000 x 22500 x 22500 of 5.8 M            111 / 144 /  254 /  615 ->  75 /  93 / 196 /  355
-//    90000 x  7500 x 18000 of 2.9 M             58 /  72 /  107 /  248 ->  42 /  53 / 108 /  195
-//   400000 x  2000 x  2000 of 4.2 M, uniform   177 / 203 /  228 /  288 ->  54 /  72 / 185 /  287
-// and where it does not: factors that an L2 holds, unless slices are short (45000 x 5625 x 5000: 31 / 39 / 55 / 104 ->
-// 26 / 34 / 69 / 119; 200000 x 5000 x 5200 of 4.8 M, uniform: 96 / 122 / 158 / 255 -> 57 / 73 / 158 / 284), long
+//   524288 x 65536 x 65536 of 16.8 M           329 / 505 / 1149 / 2179 -> 199 / 293 / 624 / 1180
+//   180000 x 22500 x 22500 of 5.8 M            110 / 144 /  253 /  621 ->  72 /  96 / 201 /  364
+//   800000 x  2000 x  2000 of 4.2 M, uniform   R = 33 / 66 / 100 / 128: 397 / 458 / 464 / 467 -> 201 / 332 / 473 / 362
+// The rank is not known here, and ranks that are no multiple of 32 pay for the columns that fill the last slice: R = 33 / 66 /
+// 100 take 192 / 291 / 388 instead of 197 / 350 / 545 us at 180000 x 22500 x 22500.  So it stays away where they would lose
+// to factors that an L2 holds (90000 x 7500 x 18000: 94 / 149 / 208 -> 108 / 162 / 212, although R = 32 takes 55 instead of
+// 72; 120000 x 20000 x 24000: 134 / 235 / 364 -> 139 / 210 / 280), unless slices are short, whose items the other form cannot fill
+// (400000 x 2000 x 2000 of 4.2 M: 228 / 271 / 285 -> 160 / 255 / 356), and from long
 // slices, whose items go through B in order by themselves (500 x 30000 x 30000 of 8.4 M: 84 / 149 / 406 / 905 -> 139 /
-// 197 / 327 / 571), fibres of several entries, for each of which it reads the row of B again.
+// 197 / 327 / 571), and fibres of several entries, for each of which it reads the row of B again.
 constexpr int64_t kStreamNnz = 1 << 21;
 constexpr int64_t kStreamSlice = 64;       // most entries of a slice on average,
-constexpr int64_t kStreamShort = 12;       // ... and where the factors have fewer rows than this:
-constexpr int64_t kStreamRows = 24000;
+constexpr int64_t kStreamShort = 4;        // ... and where the factors have fewer rows than this:
+constexpr int64_t kStreamRows = 45000;
 constexpr int64_t kStreamWaves = 4096;     // wavefronts that are resident at a time
 // Windows of one factor's rows, each with the same share of the entries.  Few of them leave more rows in use at a time,
-// many leave a row's entries one by one (they are added up by window first): 6 / 8 / 16 windows 300 / 289 / 280 us,
-// 2-norm of the error 0.83 / 0.85 / 0.9e-7 (512k x 64k x 64k, R = 32; 0.82e-7 in the other form).
+// many leave a row's entries one by one, and its sum is rounded for each (they are added up by window first): 8 / 16 windows
+// 293 / 286 us, 2-norm of the error 0.61 / 0.74e-7 (512k x 64k x 64k, R = 32; 0.82e-7 in the other form).
 constexpr int kStreamWindows = 8;
 
 // Packs the entries in the streams form (arrow_internal.h), or leaves the image alone and returns false.

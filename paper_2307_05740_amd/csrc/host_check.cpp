@@ -316,14 +316,14 @@ int main(int argc, char** argv) {
       std::vector<int32_t> ui(n), uj(n), uk(n);
       std::vector<float> uv(n, 1.f);
       for (int e = 0; e < n; ++e) {
-        ui[e] = e < 5000 ? 3 : (int32_t)(next_u64(s) % 180000);
+        ui[e] = e < 5000 ? 3 : (int32_t)(next_u64(s) % 600000);
         uj[e] = (int32_t)(next_u64(s) % 1000); uk[e] = (int32_t)(next_u64(s) % 2000);
       }
       t = nullptr;
-      EXPECT(csf3_build(180000, 1000, 2000, n, ui.data(), uj.data(), uk.data(), uv.data(), &t) == 0 && t, "csf3_build, sums in LDS");
+      EXPECT(csf3_build(600000, 1000, 2000, n, ui.data(), uj.data(), uk.data(), uv.data(), &t) == 0 && t, "csf3_build, sums in LDS");
       if (t) {
         csf3_info_t ci;
-        EXPECT(csf3_info(t, &ci) == 0 && ci.items == 180000 - ci.split_rows + ci.partials && ci.split_rows > 0, "items of small slices");
+        EXPECT(csf3_info(t, &ci) == 0 && ci.items == 600000 - ci.split_rows + ci.partials && ci.split_rows > 0, "items of small slices");
         EXPECT(csf3_workspace_bytes(t, 33) > csf3_workspace_bytes(t, 32), "workspace grows with the columns");
         csf3_destroy(t);
       }

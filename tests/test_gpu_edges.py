@@ -358,9 +358,9 @@ def test_rows_of_many_partial_vectors(torch, k, fuse):
 
 
 @pytest.mark.parametrize("I,J,K,R,offset", [
-    (70001, 13001, 12000, 1, 0), (70001, 13001, 12000, 3, 0), (70001, 12000, 13001, 8, 0), (70001, 13001, 12000, 9, 4),
-    (200000, 900, 1000, 12, 0), (200000, 1000, 900, 16, 0), (200000, 1000, 900, 16, 8), (330007, 13001, 12000, 17, 0),
-    (70001, 13001, 12000, 32, 0), (70001, 13001, 12000, 32, 4), (200000, 900, 1000, 33, 0), (70001, 13001, 12000, 96, 0)])
+    (70001, 33001, 12000, 1, 0), (70001, 33001, 12000, 3, 0), (70001, 12000, 33001, 8, 0), (70001, 33001, 12000, 9, 4),
+    (600000, 900, 1000, 12, 0), (600000, 1000, 900, 16, 0), (600000, 1000, 900, 16, 8), (330007, 33001, 12000, 17, 0),
+    (70001, 33001, 12000, 32, 0), (70001, 33001, 12000, 32, 4), (600000, 900, 1000, 33, 0), (70001, 33001, 12000, 96, 0)])
 def test_mttkrp_rows_summed_in_lds(torch, I, J, K, R, offset):
     """The form for many small slices: hub slices cut into pieces, slices of one entry and without any, more rows
     than fit the wavefronts of the chip at once (330007), factors whose rows are no whole lines or do not begin
