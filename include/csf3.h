@@ -57,7 +57,8 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t *ti, 
 size_t csf3_device_bytes(const csf3_handle *h);
 int csf3_upload(csf3_handle *h, void *dev_buf, size_t bytes, void *stream);
 
-/* DEVICE workspace for rank R (partial vectors of split slices); 256-byte aligned. */
+/* DEVICE workspace for rank R (partial vectors of split slices and, where the image's form asks for it, the factors
+ * laid out anew); 256-byte aligned. */
 size_t csf3_workspace_bytes(const csf3_handle *h, int32_t R);
 int csf3_set_workspace(csf3_handle *h, void *dev_ws, size_t bytes);
 
