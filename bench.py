@@ -235,7 +235,9 @@ def bench_mttkrp(args, torch, binding, synth, dev) -> int:
     launch = {"nnz": int(nnz), "items": int(info["items"])}
     rec, traffic_source = stored_traffic(os.path.join(ROOT, "profiles", f"hbm_traffic_mttkrp_{w.name}.json"), "mttkrp", launch)
     traffic = rec["hbm_bytes_per_launch"] if rec else None
-    roofline = {"bound": "hbm", "kernel": "fibre kernel (mttkrp.hip)", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+    kernel = {binding.CSF3_FORM_ITEMS: "mttkrp_kernel", binding.CSF3_FORM_FACTORS_IN_LDS: "resident_kernel",
+              binding.CSF3_FORM_SUMS_IN_LDS: "streams_kernel"}[binding.csf3_form(op.h)]
+    roofline = {"bound": "hbm", "kernel": kernel, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "avg_launch_ms": round(k_ms, 4), "launches_per_step": 1, "algorithmic_bytes_per_launch": int(alg),
                 "traffic_source": traffic_source, "launch": launch,

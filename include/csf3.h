@@ -72,6 +72,14 @@ int csf3_mttkrp(csf3_handle *h, const float *B, const float *C, float *A, int32_
 
 int csf3_info(const csf3_handle *h, csf3_info_t *out);
 
+/* The form of the image, which csf3_build picks by the sizes of the tensor and which names the kernel that runs. */
+enum {
+  CSF3_FORM_ITEMS = 0,          /* a wavefront per item, rows of both factors from memory (mttkrp_kernel)        */
+  CSF3_FORM_FACTORS_IN_LDS = 1, /* both factors in LDS, a few columns at a time (resident_kernel)                */
+  CSF3_FORM_SUMS_IN_LDS = 2     /* rows of A in LDS, entries in the order of one factor's rows (streams_kernel)  */
+};
+int csf3_form(const csf3_handle *h); /* EINVAL for NULL */
+
 /*
  * Profiling: when enabled, csf3_mttkrp brackets its two launches with HIP events on the caller's
  * stream; csf3_get_profile waits for them and returns the times of the most recent product in

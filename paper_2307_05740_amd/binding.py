@@ -30,7 +30,7 @@ EXPORTED = [
     "arrow_options_default", "arrow_decompose_with", "arrow_load_with", "arrow_repack",
     "arrow_destroy",
     "csf3_build", "csf3_device_bytes", "csf3_upload", "csf3_workspace_bytes", "csf3_set_workspace",
-    "csf3_mttkrp", "csf3_info", "csf3_set_profiling", "csf3_get_profile", "csf3_last_error", "csf3_destroy",
+    "csf3_mttkrp", "csf3_info", "csf3_form", "csf3_set_profiling", "csf3_get_profile", "csf3_last_error", "csf3_destroy",
 ]
 
 
@@ -171,6 +171,8 @@ def lib():
     L.csf3_mttkrp.argtypes = [vp, vp, vp, vp, i32, vp]
     L.csf3_info.restype = ctypes.c_int
     L.csf3_info.argtypes = [vp, ctypes.POINTER(csf3_info_t)]
+    L.csf3_form.restype = ctypes.c_int
+    L.csf3_form.argtypes = [vp]
     L.csf3_set_profiling.restype = ctypes.c_int
     L.csf3_set_profiling.argtypes = [vp, i32]
     L.csf3_get_profile.restype = ctypes.c_int
@@ -540,6 +542,16 @@ def csf3_info(h: int) -> dict:
     out = csf3_info_t()
     _check3(lib().csf3_info(h, ctypes.byref(out)))
     return {f: getattr(out, f) for f, _ in out._fields_}
+
+
+CSF3_FORM_ITEMS, CSF3_FORM_FACTORS_IN_LDS, CSF3_FORM_SUMS_IN_LDS = 0, 1, 2
+
+
+def csf3_form(h: int) -> int:
+    form = int(lib().csf3_form(h))
+    if form < 0:
+        _check3(form)
+    return form
 
 
 def csf3_set_profiling(h: int, enabled: bool) -> None:

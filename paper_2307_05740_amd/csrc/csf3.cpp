@@ -764,6 +764,11 @@ int csf3_info(const csf3_handle* h, csf3_info_t* out) {
   return ARROW_OK;
 }
 
+int csf3_form(const csf3_handle* h) {
+  if (!h) return fail3(ARROW_EINVAL, "handle is NULL");
+  return h->resident ? CSF3_FORM_FACTORS_IN_LDS : h->streams ? CSF3_FORM_SUMS_IN_LDS : CSF3_FORM_ITEMS;
+}
+
 void csf3_destroy(csf3_handle* h) {
   if (!h) return;
   for (hipEvent_t e : h->ev)

@@ -307,6 +307,7 @@ int main(int argc, char** argv) {
       if (t) {
         csf3_info_t ci;
         EXPECT(csf3_info(t, &ci) == 0 && ci.items == 520 - ci.split_rows + ci.partials && ci.items < 600, "items of whole slices");
+        EXPECT(csf3_form(t) == CSF3_FORM_FACTORS_IN_LDS, "form: factors in LDS");
         csf3_destroy(t);
       }
     }
@@ -324,6 +325,7 @@ int main(int argc, char** argv) {
       if (t) {
         csf3_info_t ci;
         EXPECT(csf3_info(t, &ci) == 0 && ci.items == 600000 - ci.split_rows + ci.partials && ci.split_rows > 0, "items of small slices");
+        EXPECT(csf3_form(t) == CSF3_FORM_SUMS_IN_LDS, "form: sums in LDS");
         EXPECT(csf3_workspace_bytes(t, 33) > csf3_workspace_bytes(t, 32), "workspace grows with the columns");
         csf3_destroy(t);
       }

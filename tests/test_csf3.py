@@ -82,3 +82,31 @@ def test_items_are_capped_by_segments_as_well_as_entries():
     assert info["split_rows"] == 2
     assert info["partials"] == 3 + 2            # 128 + 128 + 44 segments; 512 + 488 entries
     assert info["items"] == 3 + 2 + 1           # plus the empty slice 2
+
+
+def uniform(I, J, K, nnz, seed=3):
+    """`nnz` entries at uniformly drawn places, as a handle."""
+    rng = np.random.default_rng(seed)
+    i, j, k = (rng.integers(0, d, nnz, dtype=np.int32) for d in (I, J, K))
+    return binding.csf3_build((I, J, K), i, j, k, np.ones(nnz, np.float32))
+
+
+@pytest.mark.parametrize("I,J,K,nnz,form", [
+    (250, 231, 307, 17_730, binding.CSF3_FORM_ITEMS),                   # few entries
+    (520, 1000, 1000, 520_000, binding.CSF3_FORM_FACTORS_IN_LDS),       # factors of 2000 rows, read 400 times each
+    (520, 8000, 3000, 560_000, binding.CSF3_FORM_ITEMS),                # more rows than the LDS holds
+    (180_000, 30_000, 22_500, 2_200_000, binding.CSF3_FORM_SUMS_IN_LDS),
+    (600_000, 1000, 2000, 2_200_000, binding.CSF3_FORM_SUMS_IN_LDS),    # slices of under four entries
+    (500, 30_000, 30_000, 2_200_000, binding.CSF3_FORM_ITEMS)])         # long slices
+def test_form_of_the_image(I, J, K, nnz, form):
+    h = uniform(I, J, K, nnz)
+    try:
+        assert binding.csf3_form(h) == form
+    finally:
+        binding.csf3_destroy(h)
+
+
+def test_form_of_no_image():
+    with pytest.raises(binding.ArrowError) as e:
+        binding.csf3_form(0)
+    assert e.value.code == binding.ARROW_EINVAL

@@ -325,7 +325,7 @@ def test_mttkrp_factors_in_lds(torch, I, J, K, nnz, R):
     B[[0, -1]], C[[0, -1]] = np.inf, np.nan                  # what no entry refers to has no effect
     op = binding.Csf3Mttkrp((I, J, K), i, j, k, v)
     assert op.info["items"] == I - op.info["split_rows"] + op.info["partials"]
-    assert op.info["nnz"] + op.info["segments"] > 128 * op.info["items"]      # (not the form with items of 512 entries)
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_FACTORS_IN_LDS
     A = torch.full((I, R), float("nan"), device="cuda")
     op.mttkrp(torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(), A)
     assert_within(A.cpu().numpy(), Aref, E)
@@ -379,6 +379,7 @@ def test_mttkrp_rows_summed_in_lds(torch, I, J, K, R, offset):
     B[[0, -1]], C[[0, -1]] = np.inf, np.nan
     op = binding.Csf3Mttkrp((I, J, K), i, j, k, v)
     assert op.info["items"] == I - op.info["split_rows"] + op.info["partials"] and op.info["split_rows"] > 0
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_SUMS_IN_LDS
     Bd, Cd = (torch.empty(M.size + 64, device="cuda")[offset:offset + M.size].view(M.shape).copy_(torch.from_numpy(M)) for M in (B, C))
     A = torch.full((I, R), float("nan"), device="cuda")
     op.mttkrp(Bd, Cd, A)
