@@ -57,8 +57,11 @@ int csf3_build(int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t *ti, 
 size_t csf3_device_bytes(const csf3_handle *h);
 int csf3_upload(csf3_handle *h, void *dev_buf, size_t bytes, void *stream);
 
-/* DEVICE workspace for rank R (partial vectors of split slices and, where the image's form asks for it, the factors
- * laid out anew); 256-byte aligned. */
+/* DEVICE workspace for rank R; 256-byte aligned.  It holds the partial vectors of split slices and, in the form with
+ * sums in LDS at ranks whose rows are no whole 128-byte lines or parts of one, the factors laid out anew: J + K rows
+ * of R columns, rounded up to slices of 8, 16 or 32.  A workspace for one rank serves every smaller one too:
+ * where it lacks the room for the second part, the factors are read where they are, which takes up to twice as long.
+ * Factors that do not begin at a line are laid out anew at any rank that the workspace has the room for. */
 size_t csf3_workspace_bytes(const csf3_handle *h, int32_t R);
 int csf3_set_workspace(csf3_handle *h, void *dev_ws, size_t bytes);
 

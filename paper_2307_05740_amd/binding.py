@@ -588,6 +588,26 @@ class Csf3Mttkrp:
     def _stream(self) -> int:
         return _current_stream(self._torch, self.device)
 
+    def _bind_workspace(self, R: int) -> None:
+        """A workspace for R columns and every smaller number of them, in the form with sums in LDS with the room that
+        factors laid out anew take at R and at the ranks below it; where there is no memory for that, without."""
+        torch = self._torch
+        torch.cuda.current_stream(self.device).synchronize()
+        size = least = csf3_workspace_bytes(self.h, R)
+        if csf3_form(self.h) == CSF3_FORM_SUMS_IN_LDS:
+            least, below = (-(-self.info["partials"] * r * 4 // 256) * 256 + 256 for r in (R, R - 1))
+            if R > 1:
+                size = max(size, least + csf3_workspace_bytes(self.h, R - 1) - below)
+        self._ws = None
+        try:
+            self._ws = torch.empty(size, dtype=torch.uint8, device=self.device)
+        except torch.OutOfMemoryError:
+            if size == least:
+                raise
+            self._ws = torch.empty(least, dtype=torch.uint8, device=self.device)
+        self._ws_R = R
+        csf3_set_workspace(self.h, self._ws.data_ptr(), self._ws.numel())
+
     def mttkrp(self, B, C, A=None):
         torch = self._torch
         for M, rows in ((B, self.info["J"]), (C, self.info["K"])):
@@ -599,10 +619,7 @@ class Csf3Mttkrp:
             A = torch.empty((self.info["I"], R), dtype=torch.float32, device=self.device)
         assert A.shape == (self.info["I"], R) and A.dtype == torch.float32 and A.is_contiguous()
         if self._ws is None or self._ws_R < R:
-            torch.cuda.current_stream(self.device).synchronize()
-            self._ws = torch.empty(csf3_workspace_bytes(self.h, R), dtype=torch.uint8, device=self.device)
-            self._ws_R = R
-            csf3_set_workspace(self.h, self._ws.data_ptr(), self._ws.numel())
+            self._bind_workspace(R)
         csf3_mttkrp(self.h, B.data_ptr(), C.data_ptr(), A.data_ptr(), R, self._stream())
         return A
 

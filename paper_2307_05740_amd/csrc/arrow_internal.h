@@ -357,8 +357,11 @@ constexpr int32_t kCsfNoRow = INT32_MIN;
 int launch_mttkrp_streams(const StreamWave* waves, const StreamBlock* blocks, const int32_t* dst, const int32_t* zero_rows,
                           int64_t n_waves, const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A,
                           float* partials, float* scratch, int32_t R, void* stream);
-// Columns a wavefront of that form sums at a time, and floats of the scratch it may need (growing with R).
+// Columns a wavefront of that form sums at a time; whether rows of R columns are whole lines or parts of one, so that
+// slices of them are too where the factor begins at a line; and floats of the scratch that factors take
+// which are laid out anew because they are not (may be null: they are read where they are).
 constexpr int stream_slice(int32_t R) { return R > 16 ? 32 : R > 8 ? 16 : 8; }
+constexpr bool stream_lines(int32_t R) { return R % stream_slice(R) == 0 || stream_slice(R) % R == 0; }
 constexpr int64_t stream_scratch(int64_t b_rows, int64_t c_rows, int32_t R) {
   return (b_rows + c_rows) * ((R + (int64_t)stream_slice(R) - 1) / stream_slice(R)) * stream_slice(R);
 }

@@ -449,6 +449,12 @@ bool pack_streams(csf3_handle& h, At at, const int32_t* ti, const int32_t* tj, c
   return true;
 }
 
+// workspace layout: [partial vectors][factors laid out anew]
+size_t partial_bytes(const csf3_handle& h, int32_t R) { return align3((size_t)h.n_partials * (size_t)R * sizeof(float)); }
+size_t laid_out_bytes(const csf3_handle& h, int32_t R) {
+  return h.streams ? align3(sizeof(float) * (size_t)arrow::stream_scratch(h.J, h.K, R)) : 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -677,8 +683,7 @@ int csf3_upload(csf3_handle* h, void* dev_buf, size_t bytes, void* stream) {
 
 size_t csf3_workspace_bytes(const csf3_handle* h, int32_t R) {
   if (!h || R < 1) return 0;
-  const size_t scratch = h->streams ? sizeof(float) * (size_t)arrow::stream_scratch(h->J, h->K, R) : 0;
-  return align3((size_t)h->n_partials * (size_t)R * sizeof(float)) + align3(scratch) + kAlign3;
+  return partial_bytes(*h, R) + (arrow::stream_lines(R) ? 0 : laid_out_bytes(*h, R)) + kAlign3;
 }
 
 int csf3_set_workspace(csf3_handle* h, void* dev_ws, size_t bytes) {
@@ -695,12 +700,15 @@ int csf3_mttkrp(csf3_handle* h, const float* B, const float* C, float* A, int32_
   if (R < 1) return fail3(ARROW_EINVAL, "R must be >= 1 (got %d)", R);
   if (!h->dev) return fail3(ARROW_ENOTREADY, "csf3_upload has not been called");
   if (!h->ws) return fail3(ARROW_ENOTREADY, "csf3_set_workspace has not been called");
-  if (h->ws_bytes < csf3_workspace_bytes(h, R))
-    return fail3(ARROW_ETOOSMALL, "workspace holds %zu bytes, R = %d needs %zu", h->ws_bytes, R, csf3_workspace_bytes(h, R));
+  if (h->ws_bytes < partial_bytes(*h, R) + kAlign3)
+    return fail3(ARROW_ETOOSMALL, "workspace holds %zu bytes, R = %d needs %zu", h->ws_bytes, R, partial_bytes(*h, R) + kAlign3);
   if (!B || !C || !A) return fail3(ARROW_EINVAL, "B, C or A is NULL");
   if (A == B || A == C) return fail3(ARROW_EINVAL, "A must not overlap B or C");
   if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) % 16) return fail3(ARROW_EINVAL, "A, B and C must be 16-byte aligned");
   float* partials = reinterpret_cast<float*>(h->ws);
+  // Where the workspace has room for it, also at ranks that need it only for a factor which does not begin at a line.
+  const bool room = h->ws_bytes >= partial_bytes(*h, R) + laid_out_bytes(*h, R);
+  float* scratch = room ? reinterpret_cast<float*>(h->ws + partial_bytes(*h, R)) : nullptr;
   auto at = [&](size_t off) { return h->dev + off; };
   const bool prof = h->profiling && h->ev[0];
   if (prof) (void)hipEventRecord(h->ev[0], (hipStream_t)stream);
@@ -714,7 +722,7 @@ int csf3_mttkrp(csf3_handle* h, const float* B, const float* C, float* A, int32_
                                       reinterpret_cast<const arrow::StreamBlock*>(at(h->off_entries)),
                                       reinterpret_cast<const int32_t*>(at(h->off_dst)),
                                       reinterpret_cast<const int32_t*>(at(h->off_zero)), h->n_waves, B, h->J, C, h->K, A,
-                                      partials, partials + align3((size_t)h->n_partials * (size_t)R * sizeof(float)) / sizeof(float), R, stream);
+                                      partials, scratch, R, stream);
   else
     rc = arrow::launch_mttkrp(reinterpret_cast<const uint32_t*>(at(h->off_item_seg)),
                               reinterpret_cast<const uint32_t*>(at(h->off_item_ent)),

@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kStreamBlock = 64 * kCsfStreamTeam;
 
-template <int VEC, bool SMALL>
+template <int VEC, bool SMALL, bool SHARED>
 __global__ __launch_bounds__(kStreamBlock) void streams_kernel(
     const StreamWave* __restrict__ waves, const StreamBlock* __restrict__ blocks, const int32_t* __restrict__ dsts,
     const int32_t* __restrict__ zero_rows, int64_t n_waves, const float* __restrict__ B, const float* __restrict__ C,
@@ -397,10 +397,12 @@ __global__ __launch_bounds__(kStreamBlock) void streams_kernel(
   if (w >= n_waves) return;
   const StreamWave d = waves[w];
   const uint32_t lane = threadIdx.x % 64, g = lane / LPR, l = lane % LPR;
-  // this lane's columns of the slice: a part of them may lie beyond R in factors laid out anew, never in the caller's
-  const int c = (int)(blockIdx.y * LPR + l) * VEC;
+  // this lane's columns: a part of them may lie beyond R in factors laid out anew; in the caller's (SHARED) such a
+  // lane is moved back and holds columns of the one before it as well (R >= VEC)
+  int c = (int)(blockIdx.y * LPR + l) * VEC;
   const bool ok = c < R;
-  const uint32_t row_bytes = 4u * (uint32_t)stride, col_bytes = ok ? 4u * l * VEC : 0u;
+  if (SHARED && ok) c = min(c, R - VEC);
+  const uint32_t row_bytes = 4u * (uint32_t)stride, col_bytes = ok ? 4u * (SHARED ? (uint32_t)c : l * VEC) : 0u;
   const char* Bc = reinterpret_cast<const char*>(B + (int64_t)blockIdx.y * slice_floats);
   const char* Cc = reinterpret_cast<const char*>(C + (int64_t)blockIdx.y * slice_floats);
   V* sums = s_sum[wave] + l;
@@ -508,13 +510,15 @@ int launch_mttkrp_streams(const StreamWave* waves, const StreamBlock* blocks, co
                           int64_t n_waves, const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A,
                           float* partials, float* scratch, int32_t R, void* stream) {
   if (n_waves <= 0) return 0;
-  // Where rows are no whole lines of 128 bytes, or parts of one, the factors are laid out anew in slices that are.
+  // Where rows are no whole lines of 128 bytes, or parts of one, the factors are laid out anew in slices that are,
+  // if there is room for that.  (512k x 64k x 64k, R = 33 / 50 / 100: 609 / 644 / 1243 us, without room 996 / 1353 / 2525.)
   const int width = stream_slice(R), vec = width / 8;
   const int64_t slices = ceil_div(R, width);
-  const bool whole = (R % width == 0 || width % R == 0) && ((uintptr_t)B | (uintptr_t)C) % 128 == 0;
-  const bool small = small_matrix(b_rows, whole ? R : width) && small_matrix(c_rows, whole ? R : width);
-  int64_t slice_floats = width;
-  if (!whole) {
+  const bool lines = stream_lines(R), anew = scratch && !(lines && ((uintptr_t)B | (uintptr_t)C) % 128 == 0);
+  const int stride = anew ? width : R;
+  const bool small = small_matrix(b_rows, stride) && small_matrix(c_rows, stride), shared = !anew && !lines;
+  int64_t slice_floats = shared ? 0 : width;             // (lanes that share columns count them from the row's first)
+  if (anew) {
     const int64_t n = (b_rows + c_rows) * slices * width / 4, blocks = ceil_div(n, kBlock);
     if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(slices_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, (hipStream_t)stream, B, b_rows, C, c_rows, (int)R,
@@ -526,11 +530,13 @@ int launch_mttkrp_streams(const StreamWave* waves, const StreamBlock* blocks, co
   const int64_t groups = ceil_div(n_waves, kStreamBlock / 64);
   if (groups > 0x7fffffffLL || slices > 65535) return (int)hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)groups, (unsigned)slices);
-#define ARROW_LAUNCH(V, SM)                                                                                             \
-  hipLaunchKernelGGL((streams_kernel<V, SM>), grid, dim3(kStreamBlock), 0, (hipStream_t)stream, waves, blocks, dst, zero_rows, \
-                     n_waves, B, C, A, partials, (int)R, whole ? (int)R : width, slice_floats)
-#define ARROW_VEC(SM) if (vec == 4) ARROW_LAUNCH(4, SM); else if (vec == 2) ARROW_LAUNCH(2, SM); else ARROW_LAUNCH(1, SM)
-  if (small) { ARROW_VEC(true); } else { ARROW_VEC(false); }
+#define ARROW_LAUNCH(V, SM, SH)                                                                                         \
+  hipLaunchKernelGGL((streams_kernel<V, SM, SH>), grid, dim3(kStreamBlock), 0, (hipStream_t)stream, waves, blocks, dst, zero_rows, \
+                     n_waves, B, C, A, partials, (int)R, stride, slice_floats)
+#define ARROW_VEC(SM, SH) if (vec == 4) ARROW_LAUNCH(4, SM, SH); else if (vec == 2) ARROW_LAUNCH(2, SM, SH); else ARROW_LAUNCH(1, SM, SH)
+#define ARROW_SHARED(SM) if (shared) { ARROW_VEC(SM, true); } else { ARROW_VEC(SM, false); }
+  if (small) { ARROW_SHARED(true) } else { ARROW_SHARED(false) }
+#undef ARROW_SHARED
 #undef ARROW_VEC
 #undef ARROW_LAUNCH
   return (int)hipGetLastError();

@@ -49,3 +49,38 @@ def test_a_second_buffer_is_asked_for_only_where_it_is_used(handle):
         op._ensure_workspace(k, second=second)
         extra.append(op._ws.numel() - max(binding.arrow_workspace_bytes(op.h, k), 256))
     assert extra == [-(-300 * 8 * 4 // 256) * 256, 0, -(-300 * 32 * 4 // 256) * 256]
+
+
+@pytest.mark.parametrize("free", [1 << 40, 700_000])
+@pytest.mark.parametrize("R", [50, 64])
+def test_a_workspace_without_room_for_laid_out_factors_will_do(monkeypatch, R, free):
+    """The order-3 product asks for the room that the layout of the factors takes at this rank and the ones below it, then
+    for the partial vectors alone: short of memory it is slower, not refused."""
+    partials, J, K = 40, 1000, 2000
+    least = {50: 8192 + 256, 64: 10_240 + 256}[R]
+    want = [768_000 + least] if free > 768_000 + least else [768_000 + least, least]
+    asked, bound = [], []
+
+    def empty(nbytes, dtype, device):
+        asked.append(nbytes)
+        if nbytes > free:
+            raise torch.OutOfMemoryError
+        return torch.empty(nbytes, dtype=dtype)
+
+    def workspace_bytes(h, r):
+        up = lambda n: -(-n // 256) * 256
+        return up(partials * r * 4) + (0 if r in (1, 2, 4, 8, 16) or r % 32 == 0 else up((J + K) * -(-r // 32) * 32 * 4)) + 256
+
+    monkeypatch.setattr(binding, "csf3_workspace_bytes", workspace_bytes)
+    monkeypatch.setattr(binding, "csf3_set_workspace", lambda h, ptr, nbytes: bound.append(nbytes))
+    op = binding.Csf3Mttkrp.__new__(binding.Csf3Mttkrp)
+    stream = types.SimpleNamespace(synchronize=lambda: None)
+    op._torch = types.SimpleNamespace(cuda=types.SimpleNamespace(current_stream=lambda device: stream), empty=empty,
+                                      uint8=torch.uint8, OutOfMemoryError=torch.OutOfMemoryError)
+    op.device, op._ws, op._ws_R, op.h, op.info = torch.device("cpu"), None, 0, 0, {"partials": partials, "J": J, "K": K}
+    monkeypatch.setattr(binding, "csf3_form", lambda h: binding.CSF3_FORM_SUMS_IN_LDS)
+    op._bind_workspace(R)
+    assert asked == want and bound == want[-1:] and op._ws.numel() == want[-1] and op._ws_R == R
+    free = 0
+    with pytest.raises(torch.OutOfMemoryError):
+        op._bind_workspace(R + 1)

@@ -110,3 +110,25 @@ def test_form_of_no_image():
     with pytest.raises(binding.ArrowError) as e:
         binding.csf3_form(0)
     assert e.value.code == binding.ARROW_EINVAL
+
+
+def test_workspace_holds_laid_out_factors_only_where_they_are():
+    """Beyond the partial vectors, room for both factors at ranks whose rows are no whole lines or parts of one."""
+    I, J, K = 600_000, 1000, 2000
+    rng = np.random.default_rng(4)
+    i = rng.integers(0, I, 2_200_000, dtype=np.int32)
+    i[:5000] = 3                                                        # a slice of several pieces
+    j, k = (rng.integers(0, d, len(i), dtype=np.int32) for d in (J, K))
+    h = binding.csf3_build((I, J, K), i, j, k, np.ones(len(i), np.float32))
+    try:
+        assert binding.csf3_form(h) == binding.CSF3_FORM_SUMS_IN_LDS
+        partials = binding.csf3_info(h)["partials"]
+        assert partials > 1
+        for R in (1, 2, 4, 8, 16, 32, 64, 96, 128, 3, 5, 9, 17, 33, 50, 100):
+            width = 8 if R <= 8 else 16 if R <= 16 else 32
+            lines = R in (1, 2, 4, 8, 16) or R % 32 == 0
+            laid_out = 0 if lines else (J + K) * -(-R // width) * width * 4
+            up = lambda nbytes: -(-nbytes // 256) * 256
+            assert binding.csf3_workspace_bytes(h, R) == up(partials * R * 4) + up(laid_out) + 256, R
+    finally:
+        binding.csf3_destroy(h)

@@ -393,6 +393,34 @@ def test_mttkrp_rows_summed_in_lds(torch, I, J, K, R, offset):
     op.close()
 
 
+def test_mttkrp_without_room_for_laid_out_factors(torch):
+    """A workspace for the partial vectors alone: the factors are read where they are, with the last lanes of a row
+    moved back, and every sum has the same terms in the same order."""
+    I, J, K = 600000, 900, 1000
+    rng = np.random.default_rng(41)
+    i = rng.integers(0, I, 2_200_000)
+    i[:9000] = 11
+    i, j, k = (x.astype(np.int32) for x in (i, rng.integers(0, J, len(i)), rng.integers(0, K, len(i))))
+    op = binding.Csf3Mttkrp((I, J, K), i, j, k, rng.uniform(-1, 1, len(i)).astype(np.float32))
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_SUMS_IN_LDS and op.info["split_rows"] > 0
+    stream = torch.cuda.current_stream().cuda_stream
+    for R, offset in ((1, 0), (3, 0), (7, 4), (8, 4), (9, 0), (15, 0), (16, 8), (17, 0), (31, 4), (32, 0), (32, 4), (33, 0), (50, 0), (100, 12)):
+        Bd, Cd = (torch.randn(rows * R + 64, device="cuda")[offset:offset + rows * R].view(rows, R) for rows in (J, K))
+        full = op.mttkrp(Bd, Cd)
+        least = -(-op.info["partials"] * R * 4 // 256) * 256 + 256
+        ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+        binding.csf3_set_workspace(op.h, ws.data_ptr(), least)
+        A = torch.full((I, R), float("nan"), device="cuda")
+        binding.csf3_mttkrp(op.h, Bd.data_ptr(), Cd.data_ptr(), A.data_ptr(), R, stream)
+        assert torch.equal(A, full), (R, offset)
+        with pytest.raises(binding.ArrowError) as e:
+            binding.csf3_set_workspace(op.h, ws.data_ptr(), least - 256)
+            binding.csf3_mttkrp(op.h, Bd.data_ptr(), Cd.data_ptr(), A.data_ptr(), R, stream)
+        assert e.value.code == binding.ARROW_ETOOSMALL
+        op._ws = None
+    op.close()
+
+
 @pytest.mark.parametrize("k", [7, 20, 64, 128, 150])
 @pytest.mark.parametrize("fuse", [0, 1])
 def test_short_work_lists_beside_window_tiles(torch, k, fuse):
