@@ -89,6 +89,22 @@ namespace {
 constexpr int64_t kResidentNnz = 1 << 17, kResidentNnzSingle = 1 << 19;
 constexpr int64_t kResidentItems = 512, kResidentItemsShort = 200, kResidentShort = 2200;   // (rows of a short item)
 constexpr double kResidentFill = 1.4;
+// And every workgroup copies all J + K rows, which has to be paid for by the rows that are read, entries and segments.
+// The rank is not known here; 32 gains least (whole lines for the other form, and all compute units copy) (us, R = 8 / 32 /
+// 64 / 128; in brackets rows read per row copied, geometric mean over those ranks and 12, 24, 50 and 100 where
+// they were measured):
+//   520 x 9000 x 1000 of 560 K [109, +17 %]       9.8 / 12.2 / 16.9 / 31.2 -> 10.7 / 17.0 / 20.5 / 32.1
+//   600 x 1000 x 9100 of 500 K  [83, +18 %]       9.9 / 11.7 / 15.5 / 30.7 ->  8.8 / 18.1 / 21.2 / 31.4
+//   783 x 1736 x 7090 of 806 K [160, -3 %]        R = 32 +27 %, 64 +16 %, 12 -27 %
+//   785 x 8113 x 1294 of 1.2 M [246, -17 %]      15.4 / 20.2 / 30.9 / 60.4 -> 13.0 / 22.4 / 31.3 / 48.0
+//   3000 x 2525 x 7575 of 1.2 M [228, -4 %]      16.8 / 20.5 / 31.6 / 63.7 -> 10.5 / 25.7 / 39.4 / 67.0
+//   757 x 1673 x 3882 of 874 K [271, -17 %]       R = 32 +5 %, 64 -9 %, 12 -37 %
+//   3000 x 2525 x 7575 of 2.5 M [455, -26 %]     28.0 / 34.6 / 55.4 / 114  -> 15.8 / 32.7 / 51.7 / 90.1
+// so from 200 on, where they all gain on average (700 x 9000 x 1000 of 1.25 M [240]: 15.1 / 20.5 / 32.4 / 62.5 -> 13.8 / 24.5 /
+// 29.5 / 47.5).  From 400 on rank 32 would lose 7 % at most, but others would give up as much as 45 %.  Where there is hardly more than an
+// item per wavefront the other form is not filled either, and the first 2600 rows are free: 299 x 503 x 3305 of 371 K [134] and
+// 340 x 830 x 1821 of 229 K [146] gain 5 to 37 % at every rank; 520 x 5000 x 5000 of 600 K [114, +8 %] and of 1.2 M [216, -5 %].
+constexpr int64_t kResidentReuse = 200, kResidentFew = 640, kResidentFree = 2600;
 constexpr int64_t kResidentSegs = 4096;    // segments of an item
 // Lanes whose 16-byte reads of LDS are served together (found by timing reads whose rows lie in different banks
 // for one grouping only: 2.7 ns a wavefront's read against 3.7 to 7 for the other groupings and 5.0 at random).
@@ -139,6 +155,8 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
   if (slots > 0x7fffffffLL || parts.size() > 0x7fffff00ULL) return false;
   const int64_t least = h.nnz + h.n_seg <= kResidentShort * (int64_t)parts.size() ? kResidentItemsShort : kResidentItems;
   if ((int64_t)parts.size() < least) return false;
+  const int64_t copied = h.J + h.K - ((int64_t)parts.size() <= kResidentFew ? kResidentFree : 0);
+  if (h.nnz + h.n_seg < kResidentReuse * copied) return false;
   // segments by length, longest first: at_len[l] = where those of length kSegMax - l begin
   auto by_length = [&](const Part& p, std::array<uint32_t, kSegMax + 2>& at_len) {
     at_len.fill(0);

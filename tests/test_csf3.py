@@ -95,6 +95,13 @@ def uniform(I, J, K, nnz, seed=3):
     (250, 231, 307, 17_730, binding.CSF3_FORM_ITEMS),                   # few entries
     (520, 1000, 1000, 520_000, binding.CSF3_FORM_FACTORS_IN_LDS),       # factors of 2000 rows, read 400 times each
     (520, 8000, 3000, 560_000, binding.CSF3_FORM_ITEMS),                # more rows than the LDS holds
+    (520, 9000, 1000, 560_000, binding.CSF3_FORM_ITEMS),                # too few entries for copying the factors to LDS
+    (520, 3000, 7000, 560_000, binding.CSF3_FORM_ITEMS),
+    (600, 1000, 9100, 500_000, binding.CSF3_FORM_ITEMS),
+    (700, 9000, 1000, 1_000_000, binding.CSF3_FORM_ITEMS),              # 192 rows read for every row copied
+    (700, 9000, 1000, 1_100_000, binding.CSF3_FORM_FACTORS_IN_LDS),     # 211
+    (520, 9000, 1000, 800_000, binding.CSF3_FORM_FACTORS_IN_LDS),       # 154, but an item per wavefront
+    (340, 830, 1821, 230_000, binding.CSF3_FORM_FACTORS_IN_LDS),
     (180_000, 30_000, 22_500, 2_200_000, binding.CSF3_FORM_SUMS_IN_LDS),
     (600_000, 1000, 2000, 2_200_000, binding.CSF3_FORM_SUMS_IN_LDS),    # slices of under four entries
     (500, 30_000, 30_000, 2_200_000, binding.CSF3_FORM_ITEMS)])         # long slices

@@ -302,7 +302,7 @@ def test_non_finite_rows_of_a_window_stay_with_their_readers(torch, k, fuse):
 @pytest.mark.parametrize("I,J,K,nnz,R", [
     (600, 1700, 1300, 700_000, 1), (600, 1700, 1300, 700_000, 2), (600, 1700, 1300, 700_000, 3),
     (600, 1700, 1300, 700_000, 4), (600, 1700, 1300, 700_000, 7), (513, 5000, 300, 700_000, 33),
-    (700, 600, 9599, 1_200_000, 6), (700, 9899, 300, 600_000, 6), (520, 900, 900, 535_000, 130),
+    (520, 600, 9599, 1_900_000, 6), (520, 9899, 300, 1_200_000, 6), (520, 900, 900, 535_000, 130),
     (600, 700, 700, 600_000, 520), (600, 700, 700, 600_000, 1030), (230, 400, 1500, 260_000, 9)])
 def test_mttkrp_factors_in_lds(torch, I, J, K, nnz, R):
     """The form for factors that fit the LDS, up to the last row of it (J + K + 1 = 10200): fibres of one entry
