@@ -58,8 +58,8 @@ size_t csf3_device_bytes(const csf3_handle *h);
 int csf3_upload(csf3_handle *h, void *dev_buf, size_t bytes, void *stream);
 
 /* DEVICE workspace for rank R; 256-byte aligned.  It holds the partial vectors of split slices and, in the form with
- * sums in LDS at ranks whose rows are no whole 128-byte lines or parts of one, the factors laid out anew: J + K rows
- * of R columns, rounded up to slices of 8, 16 or 32.  A workspace for one rank serves every smaller one too:
+ * sums in LDS at ranks whose rows are no whole 128-byte lines or parts of one, the factors laid out anew (unless they
+ * have too many rows for the tensor's entries): J + K rows of R columns, rounded up to slices of 8, 16 or 32.  A workspace for one rank serves every smaller one too:
  * where it lacks the room for the second part, the factors are read where they are, which takes up to twice as long.
  * Factors that do not begin at a line are laid out anew at any rank that the workspace has the room for. */
 size_t csf3_workspace_bytes(const csf3_handle *h, int32_t R);

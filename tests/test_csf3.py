@@ -139,3 +139,20 @@ def test_workspace_holds_laid_out_factors_only_where_they_are():
             assert binding.csf3_workspace_bytes(h, R) == up(partials * R * 4) + up(laid_out) + 256, R
     finally:
         binding.csf3_destroy(h)
+
+
+def test_workspace_holds_no_factors_that_are_large_for_the_tensor():
+    """Laying the factors out anew copies all of their rows; with fewer than three entries for each the product reads them
+    where they are, at every rank and with any workspace."""
+    for J, K, laid_out in ((400_000, 300_000, True), (400_000, 340_000, False), (3_000_000, 9_000, False)):
+        h = uniform(600_000, J, K, 2_200_000)
+        try:
+            assert binding.csf3_form(h) == binding.CSF3_FORM_SUMS_IN_LDS
+            partials = binding.csf3_info(h)["partials"]
+            for R in (3, 12, 25, 50):
+                width = 8 if R <= 8 else 16 if R <= 16 else 32
+                up = lambda nbytes: -(-nbytes // 256) * 256
+                more = up((J + K) * -(-R // width) * width * 4) if laid_out else 0
+                assert binding.csf3_workspace_bytes(h, R) == up(partials * R * 4) + more + 256, (J, K, R)
+        finally:
+            binding.csf3_destroy(h)
