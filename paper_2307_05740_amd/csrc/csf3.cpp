@@ -288,10 +288,24 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
 // (400000 x 2000 x 2000 of 4.2 M: 228 / 271 / 285 -> 160 / 255 / 356), and from long
 // slices, whose items go through B in order by themselves (500 x 30000 x 30000 of 8.4 M: 84 / 149 / 406 / 905 -> 139 /
 // 197 / 327 / 571), and fibres of several entries, for each of which it reads the row of B again.
+// Where the factors have many rows for the tensor's entries, hardly one is read again while it is in an L2, and at
+// ranks that are no whole lines every pass over the columns touches lines of its neighbours (this form over the
+// ordinary one at R = 8 / 24 / 32 / 50 / 100 / 128; geometric mean with R = 4, 12 and 64; uniform tensors):
+//   500k slices, 16 M, rows 1/8 of the entries  .86 / .79 / .95 / 1.02 / 1.27 /  .98   .94
+//                           1/4                 .93 / .89 / 1.0 / 1.20 / 1.32 /  .90   .99
+//                           1/2                 .96 / .98 / .95 / 1.57 / 1.63 /  .86   1.05
+//   500k slices,  8 M       1/8                 .81 / .77 / .86 / 1.03 / 1.26 / 1.04   .90
+//                           1/2                 .95 / .95 / .86 / 1.75 / 1.69 /  .88   1.05
+//   800k slices,  6.4 M     1/8                 .52 / .64 / .63 / 1.00 / 1.35 / 1.12   .74
+//                           1/1                 .68 / .76 / .58 / 1.61 / 1.81 /  .88   .87
+//   4 M  slices,  8 M       1/1                 R = 6 / 12 / 24 / 50 / 100: .23 / .25 / .35 / 1.02 / 1.54
+// so from 1/4 on it stays away unless slices have fewer than kStreamLong entries.
 constexpr int64_t kStreamNnz = 1 << 21;
 constexpr int64_t kStreamSlice = 64;       // most entries of a slice on average,
 constexpr int64_t kStreamShort = 4;        // ... and where the factors have fewer rows than this:
 constexpr int64_t kStreamRows = 45000;
+constexpr int64_t kStreamReuse = 4;        // fewest entries per row of the factors, and where there are fewer:
+constexpr int64_t kStreamLong = 12;        // most entries of a slice on average
 constexpr int64_t kStreamWaves = 4096;     // wavefronts that are resident at a time
 // Windows of one factor's rows, each with the same share of the entries.  Few of them leave more rows in use at a time,
 // many leave a row's entries one by one, and its sum is rounded for each (they are added up by window first): 8 / 16 windows
@@ -306,6 +320,7 @@ bool pack_streams(csf3_handle& h, At at, const int32_t* ti, const int32_t* tj, c
   constexpr int64_t G = arrow::kCsfStreamGroups, room = arrow::kCsfStreamRows;
   if (h.nnz < kStreamNnz || h.J > arrow::kCsfStreamRowsOfB || h.fibers * 4 < h.nnz * 3 || h.nnz > kStreamSlice * h.I) return false;
   if (h.J + h.K < kStreamRows && h.nnz > kStreamShort * h.I) return false;
+  if (h.nnz < kStreamReuse * (h.J + h.K) && h.nnz > kStreamLong * h.I) return false;
   struct Row { uint32_t first, n; int32_t i; };                   // a slice with entries
   std::vector<Row> rows;
   std::vector<int32_t> zero;

@@ -104,7 +104,10 @@ def uniform(I, J, K, nnz, seed=3):
     (340, 830, 1821, 230_000, binding.CSF3_FORM_FACTORS_IN_LDS),
     (180_000, 30_000, 22_500, 2_200_000, binding.CSF3_FORM_SUMS_IN_LDS),
     (600_000, 1000, 2000, 2_200_000, binding.CSF3_FORM_SUMS_IN_LDS),    # slices of under four entries
-    (500, 30_000, 30_000, 2_200_000, binding.CSF3_FORM_ITEMS)])         # long slices
+    (500, 30_000, 30_000, 2_200_000, binding.CSF3_FORM_ITEMS),          # long slices
+    (180_000, 270_000, 270_000, 2_200_000, binding.CSF3_FORM_SUMS_IN_LDS),   # 4.1 entries for every row of the factors
+    (180_000, 280_000, 280_000, 2_200_000, binding.CSF3_FORM_ITEMS),         # 3.9
+    (190_000, 9000, 3_000_000, 2_200_000, binding.CSF3_FORM_SUMS_IN_LDS)])   # 0.7, but slices of under twelve entries
 def test_form_of_the_image(I, J, K, nnz, form):
     h = uniform(I, J, K, nnz)
     try:
