@@ -300,8 +300,18 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
 //                           1/1                 .68 / .76 / .58 / 1.61 / 1.81 /  .88   .87
 //   4 M  slices,  8 M       1/1                 R = 6 / 12 / 24 / 50 / 100: .23 / .25 / .35 / 1.02 / 1.54
 // so from 1/4 on it stays away unless slices have fewer than kStreamLong entries.
+// Empty slices do not make the others short.  200k slices of which few hold 8.4 M entries, J = K = 30000 (this form over the
+// ordinary one, R = 8 / 12 / 25 / 32 / 50 / 64 / 100 / 128; geometric mean):
+//   500, 16800 entries each   1.33 / 1.79 / 1.24 / 1.39 / .91 / .90 / .79 / .70   1.08
+//   5000, 1680                1.15 / 1.47 / 1.00 / 1.18 / .88 / .92 / .81 / .74   1.00
+//   10000, 840                1.00 / 1.25 /  .89 / 1.06 / .81 / .84 / .79 / .73   .91
+//   60000, 140                 .65 /    -  /  .60 /  .65 / .59 /   -  /   -  / .55
+// but the ordinary form takes a wavefront for each of them too: 500 of 600k slices .79 / 1.15 / 1.04 / 1.07 / 1.03 / .94 / .91 /
+// .73 (.95), 500 of 1.1 M with 4.2 M entries .32 to 1.39 (.72).
 constexpr int64_t kStreamNnz = 1 << 21;
 constexpr int64_t kStreamSlice = 64;       // most entries of a slice on average,
+constexpr int64_t kStreamFull = 1024;      // ... of those that are not empty, unless
+constexpr int64_t kStreamEmpty = 16;       // ... there is an empty one for so many entries,
 constexpr int64_t kStreamShort = 4;        // ... and where the factors have fewer rows than this:
 constexpr int64_t kStreamRows = 45000;
 constexpr int64_t kStreamReuse = 4;        // fewest entries per row of the factors, and where there are fewer:
@@ -319,6 +329,7 @@ template <typename At>
 bool pack_streams(csf3_handle& h, At at, const int32_t* ti, const int32_t* tj, const int32_t* tk, const float* tv) {
   constexpr int64_t G = arrow::kCsfStreamGroups, room = arrow::kCsfStreamRows;
   if (h.nnz < kStreamNnz || h.J > arrow::kCsfStreamRowsOfB || h.fibers * 4 < h.nnz * 3 || h.nnz > kStreamSlice * h.I) return false;
+  if (h.nnz > kStreamFull * h.slices && h.nnz > kStreamEmpty * (h.I - h.slices)) return false;
   if (h.J + h.K < kStreamRows && h.nnz > kStreamShort * h.I) return false;
   if (h.nnz < kStreamReuse * (h.J + h.K) && h.nnz > kStreamLong * h.I) return false;
   struct Row { uint32_t first, n; int32_t i; };                   // a slice with entries

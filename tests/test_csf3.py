@@ -116,6 +116,22 @@ def test_form_of_the_image(I, J, K, nnz, form):
         binding.csf3_destroy(h)
 
 
+@pytest.mark.parametrize("I,J,live,form", [
+    (60_000, 30_000, 700, binding.CSF3_FORM_ITEMS),              # slices of 3143 entries between empty ones
+    (60_000, 30_000, 3000, binding.CSF3_FORM_SUMS_IN_LDS),       # of 733
+    (150_000, 30_000, 700, binding.CSF3_FORM_SUMS_IN_LDS),       # an empty one for every 15 entries
+    (130_000, 30_000, 700, binding.CSF3_FORM_ITEMS)])            # for every 17
+def test_empty_slices_do_not_make_the_others_short(I, J, live, form):
+    rng = np.random.default_rng(5)
+    i = (rng.integers(0, live, 2_200_000) * (I // live)).astype(np.int32)
+    j, k = (rng.integers(0, J, len(i), dtype=np.int32) for _ in range(2))
+    h = binding.csf3_build((I, J, J), i, j, k, np.ones(len(i), np.float32))
+    try:
+        assert binding.csf3_info(h)["slices"] == live and binding.csf3_form(h) == form
+    finally:
+        binding.csf3_destroy(h)
+
+
 def test_form_of_no_image():
     with pytest.raises(binding.ArrowError) as e:
         binding.csf3_form(0)
