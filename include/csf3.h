@@ -61,7 +61,9 @@ int csf3_upload(csf3_handle *h, void *dev_buf, size_t bytes, void *stream);
  * sums in LDS at ranks whose rows are no whole 128-byte lines or parts of one, the factors laid out anew (unless they
  * have too many rows for the tensor's entries): J + K rows of R columns, rounded up to slices of 8, 16 or 32.  A workspace for one rank serves every smaller one too:
  * where it lacks the room for the second part, the factors are read where they are, which takes up to twice as long.
- * Factors that do not begin at a line are laid out anew at any rank that the workspace has the room for. */
+ * Factors that do not begin at a line are laid out anew at any rank that the workspace has the room for.
+ * A product may write the workspace, so those of a handle must not overlap in time unless csf3_set_workspace (which the
+ * product reads at the call) has given each its own; nor may the calls for one handle themselves overlap. */
 size_t csf3_workspace_bytes(const csf3_handle *h, int32_t R);
 int csf3_set_workspace(csf3_handle *h, void *dev_ws, size_t bytes);
 

@@ -84,3 +84,31 @@ def test_a_workspace_without_room_for_laid_out_factors_will_do(monkeypatch, R, f
     free = 0
     with pytest.raises(torch.OutOfMemoryError):
         op._bind_workspace(R + 1)
+
+
+def test_products_that_share_a_workspace_follow_each_other(monkeypatch):
+    """A call on another stream than the last one waits for it, unless it is captured or nothing is written to the workspace."""
+    waits, now = [], {}
+
+    class Stream:
+        def __init__(self, n): self.cuda_stream = n
+        def wait_stream(self, other): waits.append((self.cuda_stream, other.cuda_stream))
+
+    op = binding.Csf3Mttkrp.__new__(binding.Csf3Mttkrp)
+    op._torch = types.SimpleNamespace(cuda=types.SimpleNamespace(
+        current_stream=lambda device: Stream(now["stream"]), is_current_stream_capturing=lambda: now["captured"]))
+    op.device, op.h, op._last, op._writes_ws = torch.device("cpu"), 0, None, True
+
+    def call(stream, captured=False):
+        now.update(stream=stream, captured=captured)
+        op._in_turn(stream)
+
+    for stream in (0, 0, 7, 7, 0):
+        call(stream)
+    assert waits == [(7, 0), (0, 7)]
+    call(9, captured=True)
+    call(0)
+    assert len(waits) == 2
+    op._writes_ws = False
+    call(7)
+    assert len(waits) == 2

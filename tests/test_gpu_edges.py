@@ -421,6 +421,31 @@ def test_mttkrp_without_room_for_laid_out_factors(torch):
     op.close()
 
 
+@pytest.mark.parametrize("R", [32, 50])
+def test_mttkrp_on_several_streams(torch, R):
+    """Products of one tensor on two streams with factors of their own: they share the partial vectors of split slices and,
+    at R = 50, the room for factors that are laid out anew."""
+    I, J, K = 600000, 900, 1000
+    rng = np.random.default_rng(43)
+    i = rng.integers(0, I, 2_200_000)
+    i[:9000] = 11
+    i, j, k = (x.astype(np.int32) for x in (i, rng.integers(0, J, len(i)), rng.integers(0, K, len(i))))
+    op = binding.Csf3Mttkrp((I, J, K), i, j, k, rng.uniform(-1, 1, len(i)).astype(np.float32))
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_SUMS_IN_LDS and op.info["split_rows"] > 0
+    factors = [[torch.randn(rows, R, device="cuda") for rows in (J, K)] for _ in range(2)]
+    want = [op.mttkrp(*f) for f in factors]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = [torch.full((I, R), float("nan"), device="cuda") for _ in range(6)]
+    torch.cuda.synchronize()
+    for n, A in enumerate(got):
+        with torch.cuda.stream(streams[n % 2]):
+            op.mttkrp(*factors[n % 2], A)
+    torch.cuda.synchronize()
+    assert all(torch.equal(A, want[n % 2]) for n, A in enumerate(got))
+    op.close()
+
+
 @pytest.mark.parametrize("k", [7, 20, 64, 128, 150])
 @pytest.mark.parametrize("fuse", [0, 1])
 def test_short_work_lists_beside_window_tiles(torch, k, fuse):
