@@ -81,3 +81,33 @@ def test_mttkrp_factor_matrices_beyond_4gib(torch):
     Aref, E = oracle.mttkrp(dims, i, j, k, v, B, C)
     assert np.all(np.abs(A - Aref) <= TOL * E) and np.all(A[E == 0] == 0)
     op.close()
+
+
+@pytest.mark.parametrize("J,R", [(17_000_000, 3), (17_000_000, 8), (17_000_000, 12), (17_000_000, 16), (17_000_000, 20),
+                                 (17_000_000, 32), (17_000_000, 96), (17_000_000, 100), (700_000, 1600), (700_000, 1601)])
+def test_mttkrp_rows_summed_in_lds_beyond_4gib(torch, J, R):
+    """The form for many small slices with 64-bit row offsets: more than 2^24 rows, which are read where they are, and
+    rows of more than 4 GiB, at R = 1601 laid out anew.  Some columns are checked: the first, the last, and those at the
+    ends of a slice of 32."""
+    I, K, nnz = 600_000, 1000, 2_300_000
+    assert J > 1 << 24 or J * R * 4 > 1 << 32
+    rng = np.random.default_rng(R)
+    i, j, k = (rng.integers(0, n, nnz, dtype=np.int32) for n in (I, J, K))
+    i[:6000] = 11                                       # a slice of several pieces
+    j[-2000:] = J - 1 - rng.integers(0, 3, 2000)        # the last rows of both factors
+    k[-2000:] = K - 1 - rng.integers(0, 3, 2000)
+    v = rng.uniform(-1, 1, nnz).astype(np.float32)
+    op = binding.Csf3Mttkrp((I, J, K), i, j, k, v)
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_SUMS_IN_LDS and op.info["split_rows"] > 0
+    anew = binding.csf3_workspace_bytes(op.h, R) > -(-op.info["partials"] * R * 4 // 256) * 256 + 256
+    assert anew == (R == 1601)
+    B, C = torch.randn(J, R, device="cuda"), torch.randn(K, R, device="cuda")
+    A = torch.full((I, R), float("nan"), device="cuda")
+    op.mttkrp(B, C, A)
+    torch.cuda.synchronize()
+    op.close()
+    cols = sorted({c for c in (0, 7, 31, 32, R // 2, R - 33, R - 2, R - 1) if 0 <= c < R})
+    at = torch.tensor(cols, device="cuda")
+    Aref, E = oracle.mttkrp((I, J, K), i, j, k, v, *(M[:, at].cpu().numpy() for M in (B, C)))
+    got = A[:, at].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - Aref) <= TOL * E) and np.all(got[E == 0] == 0)
