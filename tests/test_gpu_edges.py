@@ -472,6 +472,30 @@ def test_short_work_lists_beside_window_tiles(torch, k, fuse):
     assert_within(Y.cpu().numpy(), Yref, B)
 
 
+@pytest.mark.parametrize("k", [7, 16, 32, 128])
+def test_only_chunks_beside_window_tiles(torch, k):
+    """All that window tiles leave is long rows, a few chunks of them: those keep a kernel of their own."""
+    n, b, m = 140001, 512, 62
+    rng = np.random.default_rng(3)
+    lo = np.arange(n) // b * b
+    inside = lo[:, None] + (rng.random((n, m)) * np.minimum(b, n - lo)[:, None]).astype(np.int64)
+    hub = rng.choice(64, 2, replace=False)
+    far = np.concatenate([np.stack([np.full(c, h), rng.choice(n, c, replace=False)], 1) for h, c in zip(hub, (3000, 2048))])
+    key = np.unique(np.concatenate([(np.arange(n)[:, None] * n + inside).ravel(), far[:, 0] * n + far[:, 1]]))
+    row, colidx = key // n, (key % n).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(row, minlength=n))]).astype(np.int64)
+    vals = rng.uniform(-1, 1, len(key)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=39)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, b)
+    level = op.levels()[0]
+    assert level["window_tiles"] > 200 and 0 < level["chunks"] <= 2048 and level["short_rows"] == 0
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    op.close()
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
+
+
 @pytest.mark.parametrize("blocks", [False, True])
 @pytest.mark.parametrize("k", [105, 107, 112])
 def test_sampled_product_of_large_factors(torch, k, blocks):
