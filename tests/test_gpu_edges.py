@@ -189,6 +189,30 @@ def test_many_batches_of_short_rows(torch, n, full, k):
     assert_within(Y.cpu().numpy(), Yref, B)
 
 
+@pytest.mark.parametrize("k", [1, 6, 32, 72])
+@pytest.mark.parametrize("n,full", [(1024 * 64, True), (1024 * 64 + 1, True), (75011, False), (4096 * 64 + 301, True)])
+def test_many_batches_of_short_rows_without_window_tiles(torch, n, full, k):
+    """The same rows with the window tiles off, which take most of them above: at least as many short rows as the
+    kernel that copies batches ahead begins at (1024 batches of 64)."""
+    rng = np.random.default_rng(n)
+    length = np.full(n, 16) if full else rng.integers(0, 17, n)
+    assert np.count_nonzero(length) >= 1024 * 64
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    row = np.repeat(np.arange(n), length)
+    step = 1 + rng.integers(0, 3, n)
+    colidx = (np.clip(np.arange(n) - 20, 0, n - 64)[row] + (np.arange(len(row)) - rowptr[row]) * step[row]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=21)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, 4096, options=binding.arrow_options_default(window_span=0))
+    level = op.levels()[0]
+    assert level["short_rows"] == n and level["chunks"] == 0 and level["window_tiles"] == 0
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    op.close()
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
+
+
 @pytest.mark.parametrize("k", [8, 20, 70])
 @pytest.mark.parametrize("n,b", [(200, 64), (4000, 500), (17 * 256 + 3, 256)])
 @pytest.mark.parametrize("fuse", [0, 1])
