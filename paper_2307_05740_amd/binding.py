@@ -585,26 +585,26 @@ class Csf3Mttkrp:
             torch.cuda.current_stream().synchronize()
         self._ws = None
         self._ws_R = 0
-        # whether a product may write the workspace, and the stream of the last one that did
+        # whether a product may write the workspace, and the stream of the last one (at first: of the upload); where none
+        # does, the ranks up to which there is nothing to wait for
         self._writes_ws = self.info["partials"] > 0 or csf3_form(self.h) == CSF3_FORM_SUMS_IN_LDS
-        self._last = None
+        self._last = torch.cuda.current_stream(self.device)
+        self._last_raw = self._last.cuda_stream
+        self._free_R = 0
         self._lock = threading.Lock()
 
     def _stream(self) -> int:
         return _current_stream(self._torch, self.device)
 
-    def _in_turn(self, stream: int) -> None:
-        """There is one workspace: a product that may write it waits for the last one, also on another stream.  One that
+    def _in_turn(self) -> None:
+        """There is one workspace: a product that may write it waits for the last one on another stream.  One that
         is captured does not, and the caller keeps its replays apart from other products."""
         torch = self._torch
-        if not self._writes_ws or (self._last is not None and self._last.cuda_stream == stream):
-            return
         if torch.cuda.is_current_stream_capturing():
             return
         now = torch.cuda.current_stream(self.device)
-        if self._last is not None:
-            now.wait_stream(self._last)
-        self._last = now
+        now.wait_stream(self._last)
+        self._last, self._last_raw = now, now.cuda_stream
 
     def _bind_workspace(self, R: int) -> None:
         """A workspace for R columns and every smaller number of them, in the form with sums in LDS with the room that
@@ -637,10 +637,15 @@ class Csf3Mttkrp:
             A = torch.empty((self.info["I"], R), dtype=torch.float32, device=self.device)
         assert A.shape == (self.info["I"], R) and A.dtype == torch.float32 and A.is_contiguous()
         stream = self._stream()
+        if R <= self._free_R:
+            csf3_mttkrp(self.h, B.data_ptr(), C.data_ptr(), A.data_ptr(), R, stream)
+            return A
         with self._lock:
-            self._in_turn(stream)
+            if self._writes_ws and stream != self._last_raw:
+                self._in_turn()
             if self._ws is None or self._ws_R < R:
                 self._bind_workspace(R)
+                self._free_R = 0 if self._writes_ws else R
             csf3_mttkrp(self.h, B.data_ptr(), C.data_ptr(), A.data_ptr(), R, stream)
         return A
 

@@ -1,4 +1,5 @@
 """When the binding allocates and binds a workspace (on the CPU: the calls are recorded, nothing is launched)."""
+import threading
 import types
 
 import numpy as np
@@ -94,14 +95,28 @@ def test_products_that_share_a_workspace_follow_each_other(monkeypatch):
         def __init__(self, n): self.cuda_stream = n
         def wait_stream(self, other): waits.append((self.cuda_stream, other.cuda_stream))
 
+    def product(h, B, C, A, R, stream):
+        assert stream == now["stream"]
+
     op = binding.Csf3Mttkrp.__new__(binding.Csf3Mttkrp)
-    op._torch = types.SimpleNamespace(cuda=types.SimpleNamespace(
+    op._torch = types.SimpleNamespace(float32=torch.float32, cuda=types.SimpleNamespace(
         current_stream=lambda device: Stream(now["stream"]), is_current_stream_capturing=lambda: now["captured"]))
-    op.device, op.h, op._last, op._writes_ws = torch.device("cpu"), 0, None, True
+    monkeypatch.setattr(binding, "_current_stream", lambda torch, device: now["stream"])
+    monkeypatch.setattr(binding, "csf3_mttkrp", product)
+    op.device, op.h, op.info, op._ws_R = torch.device("cpu"), 0, {"I": 2, "J": 3, "K": 4}, 8
+    op._ws, op._free_R = object(), 0
+    op._last, op._last_raw, op._writes_ws, op._lock = Stream(0), 0, True, threading.Lock()
+
+    class Dense:
+        is_cuda, dtype = True, torch.float32
+        def __init__(self, rows): self.shape = (rows, 5)
+        def dim(self): return 2
+        def is_contiguous(self): return True
+        def data_ptr(self): return 0
 
     def call(stream, captured=False):
         now.update(stream=stream, captured=captured)
-        op._in_turn(stream)
+        op.mttkrp(Dense(3), Dense(4), Dense(2))
 
     for stream in (0, 0, 7, 7, 0):
         call(stream)
