@@ -314,10 +314,10 @@ int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int3
 // time (resident_kernel in mttkrp.hip): the segments of an item side by side, one per lane, as a sequence of
 // STEPS, in each of which a lane reads one row from LDS and has a value for it.  In LDS lie the K rows of C, a
 // row of zeros (which the steps that fill up read) and the J rows of B.  A bit per step says that its rows are
-// rows of B, which end a batch of 64 segments.  Steps come in blocks of eight, an item has at least one.
+// rows of B, which end a batch of 64 segments.  Steps come in blocks of eight, an item has at least one: what the kernel
+// loads ahead of an item is the next one's, at last the last one's again, and never lies beyond the blocks.
 constexpr int kCsfRowsInLds = 10200;    // rows of four columns, 16 bytes each
 constexpr int kCsfBlockSteps = 8;
-constexpr int kCsfBlocksAhead = 4;      // blocks the kernel may read past the last one
 struct ResidentBlock {
   // of two steps: the first one's row << 4, the second one's << 18; bits 0 and 1: their rows are of B
   struct alignas(16) Offsets { uint32_t pair[4]; };

@@ -186,7 +186,7 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
   h.off_items = total;     total = align3(total + sizeof(arrow::ResidentItem) * parts.size());
   h.off_split_ptr = total; total = align3(total + sizeof(uint32_t) * split_ptr.size());
   h.off_split_y = total;   total = align3(total + sizeof(int32_t) * split_y.size());
-  h.off_entries = total;   total = align3(total + sizeof(arrow::ResidentBlock) * (size_t)(blocks + arrow::kCsfBlocksAhead));
+  h.off_entries = total;   total = align3(total + sizeof(arrow::ResidentBlock) * (size_t)blocks);
   h.bytes.assign(total, 0);
   unsigned char* base = h.bytes.data();
   std::memcpy(base + h.off_split_ptr, split_ptr.data(), sizeof(uint32_t) * split_ptr.size());
@@ -451,7 +451,7 @@ bool pack_streams(csf3_handle& h, At at, const int32_t* ti, const int32_t* tj, c
   h.off_zero = total;      total = align3(total + sizeof(int32_t) * zero.size());
   h.off_split_ptr = total; total = align3(total + sizeof(uint32_t) * split_ptr.size());
   h.off_split_y = total;   total = align3(total + sizeof(int32_t) * split_y.size());
-  h.off_entries = total;   total = align3(total + sizeof(arrow::StreamBlock) * (size_t)(blocks + 1));
+  h.off_entries = total;   total = align3(total + sizeof(arrow::StreamBlock) * (size_t)blocks);
   h.bytes.assign(total, 0);
   unsigned char* base = h.bytes.data();
   std::memcpy(base + h.off_waves, waves.data(), sizeof(arrow::StreamWave) * waves.size());

@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
   __syncthreads();
   const char* lds = reinterpret_cast<const char*>(s_row);
   constexpr int U = kCsfBlockSteps, N = 3;              // blocks on their way
-  static_assert(U == 8 && kCsfBlocksAhead >= N, "the steps of a block, and blocks past the last item");
+  static_assert(U == 8, "the steps of a block");
   const uint32_t lane = threadIdx.x % 64;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
   const int workers = replicas * (kResidentBlock / 64);
