@@ -181,6 +181,12 @@ def stored_traffic(path, op, launch):
     return rec, src
 
 
+def algorithmic_bytes_mttkrp(info, image_bytes, R):
+    """What the order-3 kernel must move in any form of the image: the image, every referenced row of B and C once,
+    every row of A or partial vector written once."""
+    return image_bytes + 4 * R * (info["distinct_j"] + info["distinct_k"] + info["items"])
+
+
 def bench_mttkrp(args, torch, binding, synth, dev) -> int:
     """One step = one order-3 MTTKRP A = T x (B, C) through ``csf3_mttkrp`` (fibre kernel +
     reduction of split slices), tensor image and factor matrices resident in HBM."""
@@ -227,10 +233,7 @@ def bench_mttkrp(args, torch, binding, synth, dev) -> int:
         r_ms += p["reduce_ms"] / runs
     binding.csf3_set_profiling(op.h, False)
     row = 4 * R
-    # bytes the fibre kernel must move: entries, segment and item words, every referenced row of B
-    # and C once, every row of A or partial vector written once
-    alg = (8 * nnz + 8 * info["segments"] + 8 * info["items"] + row * (info["distinct_j"] + info["distinct_k"])
-           + row * info["items"])
+    alg = algorithmic_bytes_mttkrp(info, binding.csf3_device_bytes(op.h), R)
     achieved = alg / (k_ms * 1e-3) / 1e9 if k_ms > 0 else 0.0
     launch = {"nnz": int(nnz), "items": int(info["items"])}
     rec, traffic_source = stored_traffic(os.path.join(ROOT, "profiles", f"hbm_traffic_mttkrp_{w.name}.json"), "mttkrp", launch)
