@@ -33,8 +33,9 @@ typedef struct csf3_info_t {
   int64_t slices;      /* distinct i with at least one entry                                 */
   int64_t fibers;      /* distinct (i, j)                                                    */
   int64_t segments;    /* fibres cut into runs of at most 64 entries                         */
-  int64_t items;       /* work items (one per wavefront): runs of segments of one slice      */
-  int64_t split_rows;  /* slices cut into several items, combined by the reduction pass      */
+  int64_t items;       /* whole slices (empty ones too) and the parts of split ones: each    */
+                       /* gives a row of A or a partial vector                               */
+  int64_t split_rows;  /* slices cut into several parts, combined by the reduction pass      */
   int64_t partials;    /* partial vectors those slices produce                               */
   int64_t distinct_j, distinct_k; /* rows of B / C the tensor references                    */
   double build_seconds;
@@ -86,9 +87,10 @@ enum {
 int csf3_form(const csf3_handle *h); /* EINVAL for NULL */
 
 /*
- * Profiling: when enabled, csf3_mttkrp brackets its two launches with HIP events on the caller's
+ * Profiling: when enabled, csf3_mttkrp brackets its launches with HIP events on the caller's
  * stream; csf3_get_profile waits for them and returns the times of the most recent product in
- * milliseconds (the fibre kernel, and the reduction over the partial vectors of split slices).
+ * milliseconds (the form's kernel with what lays the factors out anew for it, and the reduction over the
+ * partial vectors of split slices).
  * Errors: EINVAL, ENOTREADY (no profiled product has run), EHIP.
  */
 int csf3_set_profiling(csf3_handle *h, int32_t enabled);

@@ -455,8 +455,9 @@ __device__ __forceinline__ int row16_bcast(int v) {   // lane U's value in every
 // acc += (the v of lane U + u) * x[u] for u = 0 .. 3 in turn, the broadcast being an operand modifier of the
 // multiply-adds themselves (out of the builtin the compiler makes a move per entry).  The compiler does not
 // look into the statement, so the wait that the modifier needs stands in it as well: the register that is
-// read must not have been written by the two instructions before, nor the lane mask, which can change before
-// the first and the third four of a batch, by one of the five before.  (512 blocks of 512, k = 128: with one
+// read must not have been written by the two instructions before, nor the lane mask by a vector instruction among the
+// five before; the mask can change before the first and the third four of a batch, and which kind of instruction does that
+// is the compiler's choice.  (512 blocks of 512, k = 128: with one
 // wait per batch, which nothing ties to the multiply-adds, 158.2 us, so 159.4.)
 #define ARROW_BCAST(A, V, X, U) "v_fmac_f32_dpp %" #A ", %" #V ", %" #X " row_newbcast:%" #U " row_mask:0xf bank_mask:0xf\n\t"
 template <int U> __device__ __forceinline__ void fma_bcast4(float& a, float v, const float* x) {

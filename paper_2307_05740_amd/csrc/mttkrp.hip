@@ -374,10 +374,10 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
 // row's entries, not per entry (in 32 bits with chains of 8 and 32 entries 290 us instead of 293, but the error
 // below was 0.85e-7).
 //
-// Skewed 512k x 64k x 64k tensor, 16.8 M entries, R = 32: 506 -> 293 us; 39 % of the requests miss the L2 instead of 68 %,
-// 1.7 GB instead of 3.3, which still bounds it (6.2 TB/s).  R = 128: 2164 -> 1170.  Rows that are no whole
+// Skewed 512k x 64k x 64k tensor, 16.8 M entries, R = 32: 506 -> 293 us; 40 % of the requests miss the L2 instead of 68 %,
+// 1.84 GB instead of 3.3, which still bounds it (6.3 TB/s).  R = 128: 2164 -> 1170.  Rows that are no whole
 // lines touch more of them than they need to in every slice of columns: laid out anew (slices_kernel, 33 MB in
-// 15 us) R = 50 takes 618 instead of 1286 us, before 1136.  Error against 64 bits, R = 32: 2-norm
+// 15 us) R = 50 takes 644 instead of 1353 us, in the other form 1136.  Error against 64 bits, R = 32: 2-norm
 // 0.82 -> 0.61e-7, largest over root mean square 4.2 -> 1.6e-5; 400k x 2000 x 2000 uniform, R = 25: 0.60 -> 0.54e-7.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kStreamBlock = 64 * kCsfStreamTeam;

@@ -27,8 +27,8 @@ namespace {
 
 constexpr int64_t kResidentWaves = 8192;   // wavefronts the chip holds
 constexpr int kSampledStage = 1024;   // entries of the group list a workgroup stages at once
-// Bytes of U from which on the rows of U that short rows read carry the streaming hint: they then leave the caches to the rows
-// of V, and where everything still fits the cache behind the L2s they are better kept there.  R-MAT 100k, k = 96 (37
+// Bytes of U (V has as many) from which on the rows of U that short rows read carry the streaming hint: they then leave
+// the caches to the rows of V, and where everything still fits the cache behind the L2s they are better kept there.  R-MAT 100k, k = 96 (37
 // MiB) 61.2 us, with the hint 63.6; k = 128 (49 MiB) 74.1 and 75.5; 300k, k = 50 (57 MiB) 162.4 and 155.0; 200k, k = 100 (76 MiB)
 // 199.0 and 190.0; 1m, k = 128 1233 and 1227; grid of 350 x 350, k = 96 (45 MiB) 35.2 and 37.2, 500 x 500, k = 100 (95 MiB) 71.5
 // and 62.2; dense blocks, 150k, k = 128 (73 MiB) 217.6 and 212.8.  (Not in the launch
