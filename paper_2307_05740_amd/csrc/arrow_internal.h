@@ -220,6 +220,7 @@ struct ProductArgs {
   uint32_t blocks[4];                   // workgroups per column slice
   int32_t items[4];                     // slots per workgroup
   uint32_t slices;
+  uint32_t sets_log;                    // logarithm of the sets of dies that the slices are dealt to (0: every die works on all)
   int32_t width;                        // columns per slice
   int32_t piece_waves;                  // a piece per wavefront instead of per lane group
   int32_t entries_once;                 // the entries are too many to be found in a cache the next time

@@ -61,6 +61,8 @@ constexpr int64_t kPieceWavesMax = 4096;
 constexpr int kFlowBatches = 4;        // batches of a workgroup of the flow kernel; fewer where that leaves
 constexpr int64_t kFlowBlocks = 1536;  // less than these workgroups, the ones the chip holds at a time
 constexpr int64_t kFlowLeast = 1024;   // fewest batches it takes (100489 rows, k = 32: 13.2 -> 10.2 us; 40000, k = 16: 5.3 and 5.6)
+constexpr int64_t kDieSetsLeast = 8LL << 20;     // smallest X whose column slices are dealt to sets of dies,
+constexpr int64_t kDieSetsMost = 512LL << 20;    // ... and the largest where there are more than two of them
 constexpr int kRowsStage = 1024;   // entries of the group list a workgroup stages at once (8 KiB)
 
 template <int LPR> constexpr int strip_entries() {     // entries of the wave list a wavefront parks per batch
@@ -245,11 +247,26 @@ __device__ __forceinline__ void chunk_part(Entry* mine, const ProductArgs& a, co
   }
 }
 
+// The column slices are dealt to the dies in 1 << sets_log sets of neighbours: a die of set t works on the t-th share of
+// the slices, one after the other, so that its L2 holds rows of X of that many columns only and fetches them for that many.
+// Which slice and which of its `blocks` workgroups the id-th workgroup of a part is (a multiple of kDies per slice; the
+// part begins at die 0):
+constexpr uint32_t kDiesLog = 3;
+static_assert(kDies == 1 << kDiesLog, "a power of two of dies");
+struct SliceBlock { uint32_t slice, block; };
+__device__ __forceinline__ SliceBlock slice_block(const ProductArgs& a, uint32_t id, uint32_t blocks) {
+  const uint32_t dies_log = kDiesLog - a.sets_log, die = id % kDies;
+  uint32_t at = (id / kDies << dies_log) + (die & ((1u << dies_log) - 1u));
+  uint32_t slice = (die >> dies_log) * (a.slices >> a.sets_log);
+  for (; at >= blocks; at -= blocks) ++slice;       // (few slices: a division costs more)
+  return {slice, at};
+}
+
 // Six wavefronts per SIMD: with seven the compiler spills in the narrow shapes (A^5 X of a 2m-vertex
 // Chung-Lu graph, k = 32: 2675 -> 2747 us).
-// grid: [wave list, slice by slice][pieces, slice by slice][short rows, slice by slice][rows without
-// entries, slice by slice]; every part is a multiple of 8 workgroups per slice, so that workgroup w
-// of every slice runs on die w mod 8 (the die queues of both lists rely on it).
+// grid: [wave list][pieces][short rows][rows without entries], each slice by slice on every set of dies
+// (slice_block); every part is a multiple of 8 workgroups per slice, so that workgroup w of every slice
+// runs on die w mod 8 where there is one set (the die queues of both lists rely on it).
 template <int VEC, int LPR, bool SMALL>
 __global__ __launch_bounds__(kBlock, 6) void product_kernel(const ProductArgs a) {
   constexpr int GPB = kBlock / LPR;
@@ -264,9 +281,9 @@ __global__ __launch_bounds__(kBlock, 6) void product_kernel(const ProductArgs a)
   uint32_t id = blockIdx.x;
   int part = 0;
   while (part < 3 && id >= a.blocks[part] * a.slices) { id -= a.blocks[part] * a.slices; ++part; }
-  const uint32_t slice = id / a.blocks[part];
-  id -= slice * a.blocks[part];
-  const LaneColumns lc = lane_columns<VEC>(tid % LPR, (int)slice * a.width, a.k, a.width);
+  const SliceBlock at = slice_block(a, id, a.blocks[part]);
+  id = at.block;
+  const LaneColumns lc = lane_columns<VEC>(tid % LPR, (int)at.slice * a.width, a.k, a.width);
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   if (part == 0 || (part == 1 && a.piece_waves)) {
     const bool list = part == 0;
@@ -410,18 +427,19 @@ template <int VEC, int LPR, bool SMALL>
 __global__ __launch_bounds__(kBlock) void chunks_kernel(const ProductArgs a) {
   constexpr int WPB = kBlock / 64;
   __shared__ Entry strip[WPB][strip_entries<LPR>()];
-  uint32_t id = blockIdx.x;
+  const SliceBlock at = slice_block(a, blockIdx.x, a.blocks[0]);
+  uint32_t id = at.block;
   // Runs of kDieRun workgroups go to one die each: the eight dies then work on different column
   // windows at a time, and a row of X that several chunks of a run read is fetched into one L2
   // instead of several (the same chunks: 255 -> 231 us per product; R-MAT 8m, k = 128: 1 %; eighths
   // of the whole list are slower, the dies then finish at different times).
-  const uint32_t span = kDies * kDieRun;
-  const uint32_t base = id / span * span;
-  if (a.runs && base + span <= a.blocks[0]) id = base + id % kDies * kDieRun + (id - base) / kDies;
+  const uint32_t dies_log = kDiesLog - a.sets_log, dies = 1u << dies_log, span = dies * kDieRun;
+  const uint32_t base = id & ~(span - 1u);
+  if (a.runs && base + span <= a.blocks[0]) id = base + (id & (dies - 1u)) * kDieRun + ((id - base) >> dies_log);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int64_t ch = (int64_t)id * WPB + wave;
   if (ch >= a.n_chunks) return;
-  const LaneColumns lc = lane_columns<VEC>(threadIdx.x % LPR, (int)blockIdx.y * a.width, a.k, a.width);
+  const LaneColumns lc = lane_columns<VEC>(threadIdx.x % LPR, (int)at.slice * a.width, a.k, a.width);
   chunk_part<VEC, LPR, SMALL>(strip[wave], a, a.chunk_ptr, a.chunk_mid, a.chunk_dst, ch, nullptr, lc);
 }
 
@@ -1171,6 +1189,20 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
   }
   a.slices = (uint32_t)s.slices;
   a.width = s.width;
+  // Two sets of dies (slice_block) wherever there is an even number of slices that share no lines, or hardly any: an L2
+  // then holds and fetches half of every row of X (us, all slices on every die / two sets / four; R-MAT unless said
+  // otherwise): 10k, k = 256: 20.7 / 20.0 / 17.1; 65k, 256: 76.7 / 68.1 / 71.5; 131k, 256: 200 / 190 / 174; 180k, 256: 256 /
+  // 245 / 251; 200k, 384: 325 / 313 / 324; 65k, 512: 174 / 152 / 146; 524k, 128: 419 / 412; 8m, 128: 11631 / 11553;
+  // Chung-Lu 60k, 256: 82.5 / 76.9 / 74.2, 250k: 336 / 318 / 327.  Narrow slices that end inside a line are fetched by both
+  // sets (R-MAT 17.5k, k = 70: 15.1 / 16.5; but 65k, k = 260, 102 / 94), and more than two slices of an X that no cache holds
+  // are worse off (800k, k = 256: 907 / 921).
+  // Slices of unequal width would leave dies idle (k = 96, 64 + 32 columns: 20.9 / 22.4).
+  const bool lines = s.width % 32 == 0 || s.width >= 128, equal = a.k > (s.slices - 1) * s.width + s.width * 3 / 4;
+  // And an X that an L2 nearly holds gains nothing (10k, k = 128: 14.7 / 15.0).
+  const int64_t x_bytes = x_rows * a.k * (int64_t)sizeof(float);
+  const bool sets = !die_queues && s.slices % 2 == 0 && lines && equal && x_bytes >= kDieSetsLeast &&
+                    (s.slices == 2 || x_bytes <= kDieSetsMost);
+  a.sets_log = sets ? 1 : 0;
   // Stencils, meshes, bands: hardly any long rows or pieces of them, whichever launch those are in, and enough
   // batches for every compute unit to have several in turn.  (1m rows of 3 to 8 random entries and one in
   // twenty of 20 to 40, k = 96: 448 us with the flow kernel, 443 without; one in five: 735 and 727; 200k rows,
@@ -1180,7 +1212,7 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
   return dispatch_shape(s, [&](auto V, auto L) -> int {
     constexpr int VEC = decltype(V)::value, LPR = decltype(L)::value;
     if (windows && a.blocks[0] > 0) {
-      dim3 grid(a.blocks[0], a.slices);
+      dim3 grid(a.blocks[0] * a.slices);
       if (small) hipLaunchKernelGGL((chunks_kernel<VEC, LPR, true>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);
       else hipLaunchKernelGGL((chunks_kernel<VEC, LPR, false>), grid, dim3(kBlock), 0, (hipStream_t)stream, a);
       total -= (int64_t)a.blocks[0] * a.slices;

@@ -543,3 +543,30 @@ def test_sampled_product_of_large_factors(torch, k, blocks):
     op.close()
     Sref, B = oracle.sddmm(rowptr, colidx, vals, U, V)
     assert_within(S.cpu().numpy(), Sref, B)
+
+
+@pytest.mark.parametrize("n,k,kc,fuse", [(8192, 256, 0, 1), (17001, 128, 0, 1), (17001, 96, 0, 1), (17001, 160, 0, 0), (17001, 192, 0, 1),
+                                         (8192, 260, 0, 1), (17001, 128, 32, 0), (8192, 512, 0, 1), (17001, 150, 0, 1), (135000, 128, 0, 1)])
+def test_column_slices_dealt_to_dies(torch, n, k, kc, fuse):
+    """Long, middle and short rows in two, three, four and eight column slices, equal and unequal ones, X on both sides of the
+    sizes from which on halves of the dies take halves of the slices; lists in row order and (more than 2^17 rows) in
+    window order, whose workgroups fill several runs and a part of one.  Every element is written once per product."""
+    rng = np.random.default_rng(n + k)
+    length = rng.integers(0, 17, n)
+    length[rng.choice(n, n // 40, replace=False)] = rng.integers(17, 300, n // 40)
+    length[:4] = (3000, 2500, 700, 49)
+    row = np.repeat(np.arange(n), length)
+    key = np.unique(row * n + (n * rng.random(len(row)) ** 3).astype(np.int64))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int64)
+    colidx = (key % n).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=23)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, max(256, n // 16), options=binding.arrow_options_default(kc=kc, fuse_levels=fuse))
+    Xd, Y = torch.from_numpy(X).cuda(), torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(Xd, Y)
+    first = Y.clone()
+    op.spmm(Xd, Y.fill_(float("nan")))
+    assert torch.equal(first, Y)
+    op.close()
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
