@@ -157,6 +157,7 @@ int check_hip(int rc, const char* what) {
 // together it gains there too (R-MAT 600k, k = 128, 425 -> 421).  Below the line it costs more: R-MAT 171k (37 MB),
 // k = 64, 80.1 -> 84.2 us.
 constexpr int64_t kEntriesOnce = 48 << 20;
+constexpr int64_t kSlicedShort = 256LL << 20;   // largest X that the cache behind the L2s has room for
 constexpr int64_t kFewChunks = 2048;   // a list this short leaves wavefront slots empty
 constexpr int64_t kFewRows = 16384;    // and so does this one
 
@@ -194,10 +195,21 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
         // gains more from than the second pass over the entries costs -- where a row fills whole
         // 128-byte lines.  In other rows a slice starts and ends inside a line, and both neighbours
         // fetch it: R-MAT 262k, k = 68: 235 us in two slices, 160 us in one; k = 130: 417 and 354 us.
-        // (A short list has few wavefronts and long chains instead: slices shorten them.)
-        tune.kc = 64;
+        // (A short list has few wavefronts and long chains instead: slices shorten them.  Where they share lines anyway,
+        // fewer of them: R-MAT 20k, k = 150 / 200 / 260, all rows so: 24.1 / 29.0 / 36.4 us in 64 columns, 22.7 / 25.1 / 32.9 in 128.)
+        tune.kc = k % 32 != 0 && k > 128 ? 128 : 64;
       }
     }
+    // Beside long ones the short rows run in one pass over whole rows, of which they read each only a few times, unless a cache holds X: they
+    // then take the slices of the long ones and with them their launch (one launch / two, us).  Lists in row order always: R-MAT 20k,
+    // k = 70 / 96 / 128 / 200: 16.6 / 21.9, 15.5 / 20.3, 16.3 / 21.4, 25.1 / 37.1; 65k, 96 / 128: 34.5 / 41.3, 37.8 / 44.1; 131k, 128: 83.3 /
+    // 84.6; directed 30k, 128: 17.9 / 24.8.  Others where the cache behind the L2s has room for X and the slices are equal: R-MAT 180k,
+    // k = 128: 133 / 140; 262k, 192: 256 / 265; 400k, 128: 220 / 228; Chung-Lu 250k, 128: 167 / 179; beyond (524k, 192, 384 MiB):
+    // 636 / 638; Chung-Lu 700k, 128: 524 / 520; unequal ones (k = 96, Chung-Lu 250k, two sets of dies) 158 / 153.
+    int32_t short_kc = h->tuning.kc;
+    if (short_kc == 0 && im.n_chunks + im.piece_slots > 0 &&
+        (im.row_major || (k % 64 == 0 && im.classes == 0 && (int64_t)h->n * k * (int64_t)sizeof(float) <= kSlicedShort)))
+      short_kc = tune.kc;
     {
       arrow::ProductArgs a{};
       a.chunk_ptr = at<uint32_t>(h, im.off_chunk_ptr); a.chunk_mid = at<uint32_t>(h, im.off_chunk_mid);
@@ -214,8 +226,8 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
         return check_hip(arrow::launch_product(a, parts, im.piece_slots, im.n_rows, im.empty_slots, im.classes > 0,
                                                apart, h->n, kc, stream), "product kernel launch");
       };
-      // the wave list and the pieces follow the chunk kernel's column slicing, the short rows run in
-      // one pass over whole rows; where that is the same shape, or where both lists are so short that a
+      // the wave list and the pieces follow the chunk kernel's column slicing, the short rows have their own
+      // (short_kc); where that is the same shape, or where both lists are so short that a
       // second launch is most of the time, one launch takes all of it (Chung-Lu 3326, k = 128: 11.1 -> 6.7
       // us; R-MAT 7914, k = 135: 16.0 -> 11.3 us; the head rows beside 511 window tiles of 512 rows, k = 128, 13.3 ->
       // 8.9 us).  A profiled product keeps the lists apart so that each has a time of its own.
@@ -226,14 +238,14 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
         if (!rc && im.n_rows > 0) {
           Scoped sc(h, kRows, (int)li, stream);
           rc = launch(kPartPieces, tune.kc);
-          if (!rc) rc = launch(kPartShort, h->tuning.kc);
+          if (!rc) rc = launch(kPartShort, short_kc);
         }
-      } else if (same_shape(k, tune.kc, h->tuning.kc, acc) ||
+      } else if (same_shape(k, tune.kc, short_kc, acc) ||
                  (im.n_chunks <= kFewChunks && im.n_rows <= kFewRows)) {
         rc = launch(kPartAll, tune.kc);
       } else {
         rc = launch(kPartChunks | kPartPieces, tune.kc);
-        if (!rc) rc = launch(kPartShort, h->tuning.kc);
+        if (!rc) rc = launch(kPartShort, short_kc);
       }
       if (rc) return rc;
     }
