@@ -252,7 +252,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
     if (im.n_wtiles > 0) {
       Scoped sc(h, kWindow, (int)li, stream, prof);
       int rc = arrow::launch_window(at<arrow::WindowTile>(h, im.off_wtiles), im.n_wtiles,
-                                    h->img.max_window_span, at<uint32_t>(h, im.off_wrow_ptr),
+                                    h->img.max_window_span, im.nnz_w, at<uint32_t>(h, im.off_wrow_ptr),
                                     at<uint32_t>(h, im.off_wrow_mid), at<int32_t>(h, im.off_wrow_y), ent,
                                     at<int32_t>(h, im.off_perm), X, h->n, Y, k, acc, stream);
       if (rc) return check_hip(rc, "window kernel launch");

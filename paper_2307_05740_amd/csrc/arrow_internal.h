@@ -258,8 +258,8 @@ int launch_corner_combine(const uint32_t* panel_ptr, const int32_t* corner_y, in
 int launch_sddmm_corner(const uint32_t* tiles, int64_t n_tiles, const int32_t* corner_y, const Entry* entries,
                         const uint32_t* emap, const float* U, const float* Vh, int64_t vh_rows, float* S,
                         int32_t k, void* stream);
-// max_span = widest window of the tiles (sizes the LDS allocation and the column slice)
-int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, const uint32_t* wrow_ptr,
+// max_span = widest window of the tiles (sizes the LDS allocation and the column slice), nnz = entries of all of them
+int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, int64_t nnz, const uint32_t* wrow_ptr,
                   const uint32_t* wrow_mid, const int32_t* wrow_y, const Entry* entries,
                   const int32_t* perm, const float* X, int64_t x_rows, float* Y, int32_t k, bool accumulate,
                   void* stream);

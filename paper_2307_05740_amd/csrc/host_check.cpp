@@ -48,7 +48,7 @@ int launch_corner(const uint32_t*, const uint32_t*, int64_t, const Entry*, const
 int launch_corner_combine(const uint32_t*, const int32_t*, int64_t, const float*, float*, int32_t, void*) { reached("launch_corner_combine"); }
 int launch_sddmm_corner(const uint32_t*, int64_t, const int32_t*, const Entry*, const uint32_t*, const float*,
                         const float*, int64_t, float*, int32_t, void*) { reached("launch_sddmm_corner"); }
-int launch_window(const WindowTile*, int64_t, int64_t, const uint32_t*, const uint32_t*, const int32_t*, const Entry*,
+int launch_window(const WindowTile*, int64_t, int64_t, int64_t, const uint32_t*, const uint32_t*, const int32_t*, const Entry*,
                   const int32_t*, const float*, int64_t, float*, int32_t, bool, void*) { reached("launch_window"); }
 int launch_sddmm(SampledArgs, bool, bool, bool, int64_t, void*) { reached("launch_sddmm"); }
 unsigned char* static_scratch(std::string&) { reached("static_scratch"); }

@@ -459,11 +459,15 @@ __global__ __launch_bounds__(kBlock) void chunks_kernel(const ProductArgs a) {
 // every fourth entry; 512 blocks of 512 with 48 entries per row, k = 128: 250 -> 145 us, of which the
 // LDS reads (6.4 GB at the 78 TB/s that all compute units together reach) take 82.
 // ---------------------------------------------------------------------------
-constexpr int kWinBlock = 1024;   // threads of a window-kernel workgroup: 16 wavefronts share one staged window
+constexpr int kWinBlock = 1024;   // threads of a window-kernel workgroup: 16 wavefronts share one staged window,
+constexpr int kWinBlockHalf = 512;   // ... or 8 where a compute unit holds two windows and registers are short
+constexpr int64_t kWinHalfTiles = 768;   // fewest workgroups of 8 wavefronts
 constexpr int kWinLanes = 16;
 constexpr int kWinParts = 8;      // most workgroups that share the rows of a tile
 constexpr int kComputeUnits = 256;
-constexpr int kWinFloats = 38400; // LDS floats of a window: 150 KiB, one workgroup per compute unit
+constexpr int kWinFloats = 38400; // LDS floats of a window: 150 KiB, one workgroup per compute unit,
+constexpr int kWinFloatsHalf = 19200;   // ... or two
+constexpr double kWinStage = 6.0; // entries that a row of Y adds in the time that a row of the window takes to arrive
 constexpr int kWinColumns = 64;   // most columns of a slice
 
 template <int U>
@@ -504,19 +508,19 @@ template <int U> __device__ __forceinline__ void fma_bcast4(float4& a, float v, 
 }
 #undef ARROW_BCAST
 
-template <int VEC, bool SMALL>
-__global__ __launch_bounds__(kWinBlock) void window_kernel(
+template <int VEC, bool SMALL, int BLOCK, int FLOATS>
+__global__ __launch_bounds__(BLOCK, BLOCK / 256 * (kWinFloats / FLOATS)) void window_kernel(
     const WindowTile* __restrict__ tiles, int64_t n_tiles, const uint32_t* __restrict__ wrow_ptr,
     const uint32_t* __restrict__ wrow_mid, const int32_t* __restrict__ wrow_y,
     const Entry* __restrict__ ent, const int32_t* __restrict__ perm, const float* __restrict__ X,
     float* __restrict__ Y, int k, int width, int slices, int parts, int accumulate) {
   using V = typename Vec<VEC>::type;
-  constexpr uint32_t GPB = kWinBlock / kWinLanes;
+  constexpr uint32_t GPB = BLOCK / kWinLanes;
   constexpr int QB = 4;                              // batches of sixteen window entries a row has on their way
   constexpr uint32_t NO = 4;                         // entries outside the window loaded ahead
   // The window, and behind it a row of zeros for the lanes that hold no entry: with a row of the window in
   // its place an infinity or NaN there would reach rows of Y that have no entry in its column (0 * inf).
-  __shared__ __attribute__((aligned(16))) float win[kWinFloats + kWinColumns];
+  __shared__ __attribute__((aligned(16))) float win[FLOATS + kWinColumns];
   // the slices of a tile follow each other on one die: its entries are read from memory once
   const int64_t id = blockIdx.x;
   const int64_t tile = id / (kDies * slices * parts) * kDies + id % kDies;
@@ -556,7 +560,7 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
       if (r.mid + l + q * kWinLanes < r.hi) e[q] = t_ent[r.mid + l + q * kWinLanes];
   };
   Row r = describe(grp), r_n = describe(grp + GPB);
-  if (threadIdx.x < kWinColumns) win[kWinFloats + threadIdx.x] = 0.f;
+  if (threadIdx.x < kWinColumns) win[FLOATS + threadIdx.x] = 0.f;
   // stage: lane group j loads window rows j, j + GPB, ... eight at a time
   for (uint32_t i0 = grp; i0 < t.win_count; i0 += 8 * GPB) {
     int32_t src[8];
@@ -583,7 +587,7 @@ __global__ __launch_bounds__(kWinBlock) void window_kernel(
   V acc;
   // sixteen window entries, one per lane (`n` of them there)
   auto batch = [&](const Entry& mine, uint32_t n) {
-    const int off = l < n ? mine.xrow * row_step : kWinFloats * 4;
+    const int off = l < n ? mine.xrow * row_step : FLOATS * 4;
     const float val = l < n ? mine.val : 0.f;
     V x[8], x2[8];                                   // all reads on their way before the first is used
 #define ARROW_READ(U) vload<VEC>(reinterpret_cast<const float*>(lane_win + row16_bcast<U>(off)))
@@ -1270,7 +1274,7 @@ int launch_gather(const int32_t* perm, int64_t n_i, const float* X, float* Xp, i
   });
 }
 
-int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, const uint32_t* wrow_ptr,
+int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, int64_t nnz, const uint32_t* wrow_ptr,
                   const uint32_t* wrow_mid, const int32_t* wrow_y, const Entry* entries,
                   const int32_t* perm, const float* X, int64_t x_rows, float* Y, int32_t k, bool accumulate,
                   void* stream) {
@@ -1290,19 +1294,38 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, co
     slices = (int)ceil_div(k, most);
     width = (int)ceil_div(k, slices);
   }
-  // Fewer tiles than compute units: several workgroups stage the same window and share its rows (18 tiles
-  // of 512 rows, k = 8: 25.8 -> 11.5 us).
+  // Several workgroups stage the same window and share its rows where that fills the compute units better: by the number of
+  // rounds of workgroups times the time that one takes for its window and its share of the entries.  (Tiles of 512 rows
+  // with 30 to 60 entries, 1 / 2 / 3 / 4 / 6 workgroups a tile, us: k = 64, 130 tiles 44 / 45 / 36 / 41 / 42, 180 47 / 49 / 51 / 44 /
+  // 53, 258 74 / 63 / 60 / 62 / 67, 380 78 / 67 / 75 / 74 / 85, 700 129 / 137 / 141 / 153 / 174; k = 32, 70 tiles 37 / 23 / 19 / 18 / 16,
+  // 130 49 / 32 / 26 / 29 / 29; k = 128, 512 tiles 155 / - ; two workgroups of one compute unit share its time: k = 16, 380
+  // tiles 39 / 37 / 39 / 38 / 43, 700 65 / 70 / 72 / 72 / 82.)
   int parts = 1;
-  while (parts < kWinParts && n_tiles * slices * parts * 2 <= kComputeUnits) parts *= 2;
+  double best = 0.0;
+  const double tile_nnz = (double)nnz / (double)n_tiles;
+  for (int p = 1; p <= kWinParts; p += p < 4 ? 1 : 2) {
+    const double cost = (double)ceil_div(n_tiles * slices * p, kComputeUnits) * (kWinStage * (double)max_span + tile_nnz / p);
+    if (p == 1 || cost < best) { best = cost; parts = p; }
+  }
   const int64_t blocks = ceil_div(n_tiles, kDies) * kDies * slices * parts;
   if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
   const bool small = small_matrix(x_rows, k);
-#define ARROW_LAUNCH(VEC, SM)                                                                              \
-  hipLaunchKernelGGL((window_kernel<VEC, SM>), dim3((unsigned)blocks), dim3(kWinBlock), 0, (hipStream_t)stream, tiles, \
+  // A compute unit takes two workgroups where two windows fit it: one sums while the other waits for its window.  Of 16
+  // wavefronts each where a lane has one column (64 registers are enough for it; 512 tiles, k = 8 / 16: 59.6 -> 43.0, 61.1 -> 45.3
+  // us; 1367, 16: 130 -> 93), of 8 each where it has two, which pays from three a compute unit on (781 tiles, k = 24: 89.7 ->
+  // 86.6; 976, 20: 120.5 -> 114.1; 1953, 32: 184 -> 176; but 511, 32: 66.9 -> 71.3).
+  const bool half = max_span * (int64_t)width <= kWinFloatsHalf && (vec == 1 || (vec == 2 && n_tiles * slices * parts >= kWinHalfTiles));
+#define ARROW_LAUNCH(VEC, SM, BLOCK, FLOATS)                                                                              \
+  hipLaunchKernelGGL((window_kernel<VEC, SM, BLOCK, FLOATS>), dim3((unsigned)blocks), dim3(BLOCK), 0, (hipStream_t)stream, tiles, \
                      n_tiles, wrow_ptr, wrow_mid, wrow_y, entries, perm, X, Y, (int)k, width, slices, parts, accumulate ? 1 : 0)
-  if (vec == 4) { if (small) ARROW_LAUNCH(4, true); else ARROW_LAUNCH(4, false); }
-  else if (vec == 2) { if (small) ARROW_LAUNCH(2, true); else ARROW_LAUNCH(2, false); }
-  else { if (small) ARROW_LAUNCH(1, true); else ARROW_LAUNCH(1, false); }
+#define ARROW_SMALL(VEC, BLOCK, FLOATS) \
+  if (small) ARROW_LAUNCH(VEC, true, BLOCK, FLOATS); else ARROW_LAUNCH(VEC, false, BLOCK, FLOATS)
+  if (vec == 4) { ARROW_SMALL(4, kWinBlock, kWinFloats); }
+  else if (vec == 2 && half) { ARROW_SMALL(2, kWinBlockHalf, kWinFloatsHalf); }
+  else if (vec == 2) { ARROW_SMALL(2, kWinBlock, kWinFloats); }
+  else if (half) { ARROW_SMALL(1, kWinBlock, kWinFloatsHalf); }
+  else { ARROW_SMALL(1, kWinBlock, kWinFloats); }
+#undef ARROW_SMALL
 #undef ARROW_LAUNCH
   return (int)hipGetLastError();
 }

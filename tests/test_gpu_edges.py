@@ -570,3 +570,28 @@ def test_column_slices_dealt_to_dies(torch, n, k, kc, fuse):
     op.close()
     Yref, B = oracle.spmm(rowptr, colidx, vals, X)
     assert_within(Y.cpu().numpy(), Yref, B)
+
+
+@pytest.mark.parametrize("b,tiles,k", [(64, 800, 20), (64, 800, 33), (64, 70, 64), (512, 40, 32), (512, 70, 7), (100, 180, 128), (1100, 12, 16),
+                                       (1300, 12, 16), (512, 3, 5)])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_windows_of_two_workgroups_and_shares_of_tiles(torch, b, tiles, k, fuse):
+    """Windows of which a compute unit holds two (up to 1200 positions of 16 columns, 600 of 32 where there are many tiles)
+    and one; one, two, three, four, six and eight workgroups to a tile, also more than it has sixteens of rows for."""
+    rng = np.random.default_rng(b + tiles)
+    n = b * (tiles + 1) - 7
+    deg = 12
+    inside = rng.integers(0, b, (n, deg)) + (np.arange(n) // b * b)[:, None]
+    col = np.concatenate([np.minimum(inside, n - 1), rng.integers(0, 8, (n, 1))], 1)
+    key = np.unique((np.repeat(np.arange(n), deg + 1) * n + col.ravel()))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int64)
+    colidx = (key % n).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=24)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, b, options=binding.arrow_options_default(fuse_levels=fuse))
+    assert op.levels()[0]["window_tiles"] >= tiles - 1
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    op.close()
+    Yref, B = oracle.spmm(rowptr, colidx, vals, X)
+    assert_within(Y.cpu().numpy(), Yref, B)
