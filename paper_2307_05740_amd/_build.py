@@ -1,8 +1,9 @@
 """Compile the native pieces in-tree.
 
-Three independent shared objects are produced:
+Four independent shared objects are produced:
 
 * ``paper_2307_05740_amd/libarrow.so``        -- HIP kernels + host decomposition + C-ABI (hipcc, gfx950)
+* ``paper_2307_05740_amd/tensor_call.so``     -- calls of that library on torch tensors, for the Python classes (g++)
 * ``paper_2307_05740_amd/synth/libsynth.so``  -- seeded input generators (gcc)
 * ``oracle/liboracle.so``                     -- the fp64 CPU checker (gcc); building it is not using it
 
@@ -25,6 +26,7 @@ REPO_DIR = os.path.dirname(PKG_DIR)
 
 ARROW_LIB = os.path.join(PKG_DIR, "libarrow.so")
 SYNTH_LIB = os.path.join(PKG_DIR, "synth", "libsynth.so")
+CALL_LIB = os.path.join(PKG_DIR, "tensor_call.so")
 ORACLE_LIB = os.path.join(REPO_DIR, "oracle", "liboracle.so")
 
 HIP_SOURCES = ["csrc/decompose.cpp", "csrc/layout.cpp", "csrc/abi.cpp", "csrc/kernels.hip", "csrc/sddmm.hip",
@@ -76,6 +78,20 @@ def build_arrow() -> str:
     return ARROW_LIB
 
 
+def build_call() -> str:
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm_inc = os.path.join(os.path.dirname(os.path.dirname(_hipcc())), "include")
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", sysconfig.get_paths()["include"],
+          "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+          "-I", rocm_inc, os.path.join(PKG_DIR, "csrc", "tensor_call.cpp"), "-L", os.path.join(root, "lib"),
+          "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", CALL_LIB])
+    return CALL_LIB
+
+
 HOST_CHECK = os.path.join(PKG_DIR, "arrow_host_check")
 HOST_SOURCES = ["csrc/decompose.cpp", "csrc/layout.cpp", "csrc/abi.cpp", "csrc/csf3.cpp", "csrc/host_check.cpp"]
 
@@ -99,6 +115,7 @@ def build_host_check(sanitize: bool = True) -> str:
 def build_all() -> None:
     build_synth()
     build_oracle()
+    build_call()
     build_arrow()
 
 
@@ -110,6 +127,6 @@ if __name__ == "__main__":
         if w == "arrow" and "--sanitize" in what:
             build_host_check(sanitize=True)        # the host half of the library under ASan + UBSan
             continue
-        {"all": build_all, "synth": build_synth, "oracle": build_oracle, "arrow": build_arrow,
+        {"all": build_all, "synth": build_synth, "oracle": build_oracle, "arrow": build_arrow, "call": build_call,
          "host_check": lambda: build_host_check(sanitize=False)}[w]()
     print("built:", ", ".join(what))

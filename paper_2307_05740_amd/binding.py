@@ -378,8 +378,22 @@ def _current_stream(torch, device) -> int:
     return torch.cuda.current_stream(device).cuda_stream
 
 
+def _tensor_call(device):
+    """The module that calls the library on torch tensors (csrc/tensor_call.cpp), where the device has a number."""
+    if device.type != "cuda" or device.index is None:
+        return None
+    from . import tensor_call      # built with the library; no fallback that would hide that it is missing
+    return tensor_call
+
+
+def _address(function) -> int:
+    return ctypes.cast(function, ctypes.c_void_p).value
+
+
 class ArrowSpMM:
     """One decomposed operand bound to torch-owned device memory (plumbing only)."""
+
+    _call = None                   # _tensor_call
 
     def __init__(self, rowptr=None, colidx=None, vals=None, b: int = 0, device="cuda:0", handle=None,
                  options: arrow_options_t | None = None):
@@ -390,6 +404,9 @@ class ArrowSpMM:
         self.info = arrow_info(self.h)
         self.n = self.info["n"]
         self._bind_image()
+        self._call = _tensor_call(self.device)
+        self._index, self._nnz = self.device.index, self.info["nnz"]
+        self._spmm, self._sddmm = _address(lib().arrow_spmm), _address(lib().arrow_sddmm)
 
     def _bind_image(self) -> None:
         torch = self._torch
@@ -435,6 +452,11 @@ class ArrowSpMM:
         return [arrow_level_info(self.h, i) for i in range(self.info["levels"])]
 
     def spmm(self, X, Y=None):
+        if Y is not None and self._call is not None:
+            rc = self._call.spmm(self._spmm, self.h, self._index, self.n, self._ws_k, X, Y)
+            if rc == 1:
+                return Y
+            _check(rc)
         torch = self._torch
         assert X.is_cuda and X.dtype == torch.float32 and X.dim() == 2 and X.is_contiguous()
         assert X.shape[0] == self.n
@@ -456,6 +478,11 @@ class ArrowSpMM:
 
     def sddmm(self, U, V, S=None):
         """``S[p] = a_p <U[i], V[j]>`` for the nonzeros p = (i, j), in the caller's CSR order."""
+        if S is not None and self._map is not None and self._call is not None:
+            rc = self._call.sddmm(self._sddmm, self.h, self._index, self.n, self._ws_k, self._nnz, U, V, S)
+            if rc == 1:
+                return S
+            _check(rc)
         torch = self._torch
         for M in (U, V):
             assert M.is_cuda and M.dtype == torch.float32 and M.dim() == 2 and M.is_contiguous()
@@ -572,6 +599,8 @@ def csf3_destroy(h: int) -> None:
 class Csf3Mttkrp:
     """One order-3 tensor bound to torch-owned device memory (plumbing only)."""
 
+    _call = None                   # _tensor_call
+
     def __init__(self, dims, ti, tj, tk, tv, device="cuda:0"):
         import torch
         self._torch = torch
@@ -592,6 +621,9 @@ class Csf3Mttkrp:
         self._last_raw = self._last.cuda_stream
         self._free_R = 0
         self._lock = threading.Lock()
+        self._call = _tensor_call(self.device)
+        self._sizes = self.device.index, self.info["I"], self.info["J"], self.info["K"]
+        self._product = _address(lib().csf3_mttkrp)
 
     def _stream(self) -> int:
         return _current_stream(self._torch, self.device)
@@ -627,6 +659,11 @@ class Csf3Mttkrp:
         csf3_set_workspace(self.h, self._ws.data_ptr(), self._ws.numel())
 
     def mttkrp(self, B, C, A=None):
+        if A is not None and self._free_R and self._call is not None:
+            rc = self._call.mttkrp(self._product, self.h, *self._sizes, self._free_R, B, C, A)
+            if rc == 1:
+                return A
+            _check3(rc)
         torch = self._torch
         for M, rows in ((B, self.info["J"]), (C, self.info["K"])):
             assert M.is_cuda and M.dtype == torch.float32 and M.dim() == 2 and M.is_contiguous()

@@ -1,4 +1,5 @@
 """When the binding allocates and binds a workspace (on the CPU: the calls are recorded, nothing is launched)."""
+import ctypes
 import threading
 import types
 
@@ -127,3 +128,23 @@ def test_products_that_share_a_workspace_follow_each_other(monkeypatch):
     op._writes_ws = False
     call(7)
     assert len(waits) == 2
+
+
+def test_anything_but_plain_tensors_goes_the_general_way():
+    """The native calls take dense float32 tensors on the handle's device only; for everything else they call nothing and
+    say so, and the Python methods then assert and allocate as ever."""
+    from paper_2307_05740_amd import tensor_call
+    called = []
+    product = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * 3, ctypes.c_int, ctypes.c_void_p)(lambda *a: called.append(a) or 0)
+    at = ctypes.cast(product, ctypes.c_void_p).value
+    X = torch.zeros(4, 8)
+    for x in (X, X.double(), X[:, ::2], X[0], torch.nn.Parameter(X), X.to("meta"), X.to_sparse(), X.numpy(), None):
+        assert tensor_call.spmm(at, 0, 0, 4, 8, x, X) == 0
+        assert tensor_call.sddmm(at, 0, 0, 4, 8, 3, x, X, X) == 0
+        assert tensor_call.mttkrp(at, 0, 0, 4, 4, 4, 8, x, X, X) == 0
+    assert called == []
+    for call in (tensor_call.spmm, tensor_call.sddmm, tensor_call.mttkrp):
+        with pytest.raises(TypeError):
+            call(at, 0)
+        with pytest.raises(TypeError):
+            call(*["0"] * {"spmm": 7, "sddmm": 9, "mttkrp": 10}[call.__name__])

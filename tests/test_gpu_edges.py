@@ -595,3 +595,44 @@ def test_windows_of_two_workgroups_and_shares_of_tiles(torch, b, tiles, k, fuse)
     op.close()
     Yref, B = oracle.spmm(rowptr, colidx, vals, X)
     assert_within(Y.cpu().numpy(), Yref, B)
+
+
+def test_what_the_python_methods_take_and_refuse(torch):
+    """The native calls stand before the general way: results, refusals and allocations are the same on both."""
+    w = synth.make_config(0, 2)
+    op = binding.ArrowSpMM(*csr_of(w), w.b)
+    X = torch.from_numpy(synth.normal_matrix(w.n, 24, seed=25)).cuda()
+    Y, S = torch.empty_like(X), torch.empty(op.info["nnz"], device="cuda")
+    general, sampled = op.spmm(X), op.sddmm(X, X)
+    for x in (X, torch.nn.Parameter(X), X.clone().requires_grad_()):
+        with torch.no_grad():
+            assert op.spmm(x, Y.fill_(float("nan"))) is Y and torch.equal(Y, general)
+            assert op.sddmm(x, X, S.fill_(float("nan"))) is S and torch.equal(S, sampled)
+    wide = torch.cat([X, X], 1)                       # more columns than the workspace was bound for
+    out = torch.empty_like(wide)
+    assert torch.equal(op.spmm(wide, out)[:, 24:], out[:, :24])
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        op.spmm(X, Y.fill_(float("nan")))
+    side.synchronize()
+    assert torch.equal(Y, general)
+    for x, y in ((X.double(), Y), (X, Y.double()), (X[:-1], Y[:-1]), (X, Y[:, :8]), (X.t().contiguous().t(), Y), (X.cpu(), Y), (X[0], Y[0])):
+        with pytest.raises(AssertionError):
+            op.spmm(x, y)
+    for u, v, s in ((X, X[:, :8], S), (X, X.double(), S), (X, X, S[:-1]), (X.cpu(), X, S), (X[:, ::2], X, S)):
+        with pytest.raises(AssertionError):
+            op.sddmm(u, v, s)
+    with pytest.raises(binding.ArrowError):
+        op.spmm(X, X)                                 # overlap, which the library refuses
+    op.close()
+    t = [np.array([0, 0, 2], np.int32), np.array([1, 2, 0], np.int32), np.array([3, 0, 1], np.int32)]
+    h = binding.Csf3Mttkrp((3, 4, 5), *t, np.array([1, 2, 3], np.float32))
+    B, C = torch.rand(4, 6, device="cuda"), torch.rand(5, 6, device="cuda")
+    A = torch.empty(3, 6, device="cuda")
+    ref = h.mttkrp(B, C)
+    assert h.mttkrp(B, C, A) is A and torch.equal(A, ref)
+    for b, c, a in ((B[:-1], C, A), (B, C[:, :5], A), (B, C.double(), A), (B, C, A[:-1]), (B.cpu(), C, A)):
+        with pytest.raises(AssertionError):
+            h.mttkrp(b, c, a)
+    h.close()
