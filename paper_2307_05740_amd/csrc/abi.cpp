@@ -306,13 +306,13 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
     {
       arrow::SampledArgs a{};
       a.chunk_ptr = at<uint32_t>(h, im.off_chunk_ptr); a.chunk_mid = at<uint32_t>(h, im.off_chunk_mid);
-      a.chunk_row = at<int32_t>(h, im.off_chunk_row); a.n_chunks = im.n_chunks;
+      a.chunk_row = at<int32_t>(h, im.off_chunk_row); a.n_chunks = im.n_chunks; a.nnz_chunks = im.nnz_chunks;
       a.rows_ptr = at<uint32_t>(h, im.off_rows_ptr); a.rows_mid = at<uint32_t>(h, im.off_rows_mid);
       a.rows_row = at<int32_t>(h, im.off_rows_row); a.n_rows = im.n_rows;
       a.ent = ent; a.emap = emap; a.U = U; a.V = V; a.Vh = Vh; a.S = S; a.k = k;
       auto launch = [&](arrow::SampledArgs args, bool window_rows) -> int {
         if (args.n_chunks == 0 && args.n_rows == 0) return ARROW_OK;
-        return check_hip(arrow::launch_sddmm(args, window_rows, im.classes > 0, !im.row_major, h->n, stream),
+        return check_hip(arrow::launch_sddmm(args, window_rows, im.classes > 0, !im.row_major, im.piece_slots > 0, h->n, stream),
                          "sampled product kernel launch");
       };
       int rc = ARROW_OK;

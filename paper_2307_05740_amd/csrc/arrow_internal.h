@@ -277,13 +277,15 @@ struct SampledArgs {
   const float* U; const float* V; const float* Vh;
   float* S;
   int64_t n_chunks, n_rows;
+  int64_t nnz_chunks;
   int32_t k;
-  int32_t items;                        // group-list slots per workgroup
+  int32_t items;                        // group-list slots per workgroup (filled in by the launch)
   uint32_t chunk_blocks;
   int32_t runs;                         // as in ProductArgs
 };
-// v_rows = rows of V; windows, die_queues: as in launch_product (the grid is filled in here).
-int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows, int64_t v_rows, void* stream);
+// v_rows = rows of V; windows, die_queues: as in launch_product (the grid is filled in here); unequal: the group list
+// holds pieces of long rows, not only short ones.
+int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows, bool unequal, int64_t v_rows, void* stream);
 constexpr int kSampledBatch = 4;        // entries a lane group reduces together (= row loads in flight per lane)
 
 // Device address of the current device's copy of the static scratch array of arrow_spmm_static

@@ -50,7 +50,7 @@ int launch_sddmm_corner(const uint32_t*, int64_t, const int32_t*, const Entry*, 
                         const float*, int64_t, float*, int32_t, void*) { reached("launch_sddmm_corner"); }
 int launch_window(const WindowTile*, int64_t, int64_t, int64_t, const uint32_t*, const uint32_t*, const int32_t*, const Entry*,
                   const int32_t*, const float*, int64_t, float*, int32_t, bool, void*) { reached("launch_window"); }
-int launch_sddmm(SampledArgs, bool, bool, bool, int64_t, void*) { reached("launch_sddmm"); }
+int launch_sddmm(SampledArgs, bool, bool, bool, bool, int64_t, void*) { reached("launch_sddmm"); }
 unsigned char* static_scratch(std::string&) { reached("static_scratch"); }
 int64_t probe_out_floats(int64_t) { reached("probe_out_floats"); }
 int launch_probe_gather(const float*, int64_t, int32_t, int64_t, int, int, int64_t, float*, void*) { reached("launch_probe_gather"); }

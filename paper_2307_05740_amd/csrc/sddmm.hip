@@ -15,7 +15,9 @@
 // 19 us, 12 since wavefronts share chunks, launch_sddmm).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
@@ -26,6 +28,7 @@ namespace arrow {
 namespace {
 
 constexpr int64_t kResidentWaves = 8192;   // wavefronts the chip holds
+constexpr int64_t kSampledGroups = 12500;  // most workgroups for a list of rows, if they may have more items each
 constexpr int kSampledStage = 1024;   // entries of the group list a workgroup stages at once
 // Bytes of U (V has as many) from which on the rows of U that short rows read carry the streaming hint: they then leave
 // the caches to the rows of V, and where everything still fits the cache behind the L2s they are better kept there.  R-MAT 100k, k = 96 (37
@@ -297,26 +300,56 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SampledArgs a) {
 
 }  // namespace
 
-int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows, int64_t v_rows, void* stream) {
+namespace {
+
+// Items of the group list (or window rows) per workgroup.  Few of them leave several lane groups for each, so that all
+// of its rounds of row loads are on their way at once, and balance rows of unequal length; many of them pay once for what
+// a workgroup does before its first row arrives.  The best number grows about as the square root of the list's
+// length up to some 12500 workgroups: fitted to (us by items 4 / 8 / 16 / 32 / 64)
+//   R-MAT 4000, k = 128     6.5 /  9.6 /    - /    - /    -  (2: 5.9)      30000, k = 64     15.9 / 13.7 / 14.2 / 21.0 / 38.6
+//         100000, k = 64      - / 32.8 / 29.0 / 41.5 / 62.8  (two wavefronts a chunk)  180000, k = 8   62.4 / 43.9 / 35.3 / 33.3 / 40.3
+//         180000, k = 128   156 /  136 /  131 /  145 /  178                  400000, k = 64     212 /  163 /  142 /  134 /  154
+//         1m, k = 64        616 /  490 /  434 /  412 /  404                  Chung-Lu 300k, 64  216 /  161 /  136 /  128 /  144
+//         Chung-Lu 600k, k = 64  - /   - /    - /  207 /  199
+// Where no row is longer than the short ones all are about alike and need less sharing:
+//   grid  10000, k = 16     6.2 /  4.2 /  3.9 /  3.8 /  4.0                  29929, k = 16     16.7 / 10.4 /  7.2 /  4.6 /  4.9
+//         99856, k = 64    45.7 / 26.0 / 20.8 / 19.6 / 18.5                  10000, k = 128     8.8 /  6.6 /  7.4 / 10.1 / 16.2
+// and rows of dense blocks (40 entries) leave each lane group at most one or two:
+//         9000, k = 64     14.5 / 17.3 / 24.3 / 49.8 / 90.3                  100000, k = 32    72.8 / 56.7 / 53.3 / 69.6 / 89.8
+//         100000, k = 128   117 /  117 /  155 /  239 /  313                  300000, k = 200    569 /  627 /  913 / 1224 / 1391
+// (Before, as many as gave 2048 workgroups, 64 at most, 16 for rows of dense blocks, 8 at least: 30000, k = 64 of the grid 11.7,
+// 180000, k = 8 / 64 41.1 / 106, dense blocks 300000, k = 200 891 us.)
+int items_of(int64_t n, int lpr, bool unequal, bool window_rows) {
+  const double per = unequal || window_rows ? (lpr <= 8 ? 14.0 : lpr == 16 ? 20.0 : lpr == 32 ? 25.0 : 32.0)
+                                            : (lpr <= 8 ? 5.0 : lpr == 16 ? 6.0 : lpr == 32 ? 9.0 : 12.0);
+  const int most = window_rows ? std::min(16, std::max(4, kBlock / lpr / 2)) : kItemsPerGroupBlock;
+  const double want = std::sqrt((double)n) / per;
+  int items = 2;
+  while (items < most && (want > 1.414 * items || (!window_rows && n > kSampledGroups * items))) items *= 2;
+  return items;
+}
+
+}  // namespace
+
+int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows, bool unequal, int64_t v_rows, void* stream) {
   const Shape s = pick_shape(a.k, 0);
   const bool small = small_matrix(v_rows, a.k);
   const hipStream_t st = (hipStream_t)stream;
-  // Items per workgroup: fewer for short lists, down to what leaves several lane groups for each item, so
-  // that all of its rounds of row loads are on their way at once (R-MAT 3416, k = 8: 10.6 -> 5.7 us; R-MAT
-  // 30124, k = 16: 17.0 -> 10.3; Chung-Lu 36286, k = 16: 19.7 -> 11.5; dense blocks, 9000, k = 16: 22.7 -> 11.3).
-  const int least = kBlock / s.lpr < 8 ? kBlock / s.lpr : 8;
-  a.items = window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock;   // rows of dense blocks are long
-  if (!die_queues)
-    while (a.items > least && a.n_rows < (int64_t)a.items * 2048) a.items >>= 1;
+  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(a.n_rows, s.lpr, unequal, window_rows);
   // Few chunks leave wavefront slots empty, and a chunk of 256 entries is four to 64 rounds of row loads one
   // after the other: wavefronts share it as far as that leaves each a few rounds (nothing has to be
   // combined).  R-MAT 7419, k = 73: 30.7 -> 10.5 us; 12527, k = 128: 33.2 -> 13.7; 51952, k = 128: 50.2 ->
-  // 28.4; 30011, k = 24: 16.5 -> 12.0; but with twice as many wavefronts as the chip holds: Chung-Lu 104057,
-  // k = 133: 139 -> 145 us.
+  // 28.4; 30011, k = 24: 16.5 -> 12.0.  Up to twice as many wavefronts as the chip holds where each is left three rounds
+  // (1 / 2 / 4 wavefronts, us: R-MAT 60k, k = 64 / 100 / 200: 29.3 / 25.4 / 28.6, 55.5 / 38.8 / 42.7, 113 / 69 / 75; 30k, 128: - /
+  // 24.4 / 19.8, but 64: - / 13.7 / 14.4; Chung-Lu 80k, 50: 35.1 / 30.0 / 32.2; 130k, 64: 61.2 / 65.5).
   a.chunk_parts = 1;
   const uint32_t most = s.lpr < 4 ? 1u : (s.lpr < 8 ? 2u : (uint32_t)s.lpr / 4);
+  const int64_t rounds = 3 * (64 / s.lpr) * kSampledBatch;
   if (!window_rows && !windows && !die_queues)
-    while (a.chunk_parts < most && a.n_chunks * a.chunk_parts * 2 <= kResidentWaves) a.chunk_parts *= 2;
+    while (a.chunk_parts < most && (a.n_chunks * a.chunk_parts * 2 <= kResidentWaves ||
+                                    (a.n_chunks * a.chunk_parts * 2 <= 2 * kResidentWaves &&
+                                     a.nnz_chunks >= a.n_chunks * a.chunk_parts * 2 * rounds)))
+      a.chunk_parts *= 2;
   const int64_t chunk_blocks = ceil_div(ceil_div(a.n_chunks * a.chunk_parts, kBlock / 64), kDies) * kDies;
   const int64_t row_blocks = ceil_div(ceil_div(a.n_rows, a.items), kDies) * kDies;
   if (chunk_blocks + row_blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;

@@ -298,3 +298,25 @@ def test_errors(torch):
         binding.arrow_sddmm(op.h, U.data_ptr(), U.data_ptr(), S.data_ptr(), 4096, 0)
     assert e.value.code == binding.ARROW_ETOOSMALL
     op.close()
+
+
+@pytest.mark.parametrize("n", [2, 3, 7, 120, 5000, 41000, 140001])
+@pytest.mark.parametrize("k", [8, 50, 64, 100, 200])
+@pytest.mark.parametrize("longest", [5, 40])
+def test_items_per_workgroup_and_wavefronts_per_chunk(torch, n, k, longest):
+    """Lists of so many items that a workgroup takes 2, 4, ... 64 of them, the last one fewer, of equal rows and of rows of
+    up to 40 entries beside chunks that one, two and four wavefronts share."""
+    rng = np.random.default_rng(n + k + longest)
+    length = rng.integers(0, min(longest, n) + 1, n)
+    if longest > 16 and n >= 120:
+        length[:n // 40] = min(n // 2, 300)
+    key = np.unique(np.repeat(np.arange(n), length) * n + (n * rng.random(length.sum()) ** 2).astype(np.int64))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int64)
+    colidx = (key % n).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(key)).astype(np.float32)
+    U, V = synth.normal_matrix(n, k, seed=26), synth.normal_matrix(n, k, seed=27)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, max(1, n // 16))
+    S = torch.full((len(key),), float("nan"), device="cuda")
+    op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), S)
+    op.close()
+    assert_within(S.cpu().numpy(), *oracle.sddmm(rowptr, colidx, vals, U, V))
