@@ -89,7 +89,7 @@ __device__ __forceinline__ float dots(const SampledArgs& a, const char* base, co
 
 // One chunk of the wave list per wavefront: the G lane groups take the entries round-robin, NB rounds at
 // a time; nothing is combined across lane groups.  Entries [lo, mid) read rows of the staged head Vh.
-template <int VEC, int LPR, int NB, bool SMALL>
+template <int VEC, int LPR, int NB, bool SMALL, bool AHEAD>
 __device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const SampledArgs& a, int64_t ch, uint32_t part) {
   using V = typename Vec<VEC>::type;
   constexpr uint32_t G = 64 / LPR;
@@ -129,6 +129,44 @@ __device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const 
         ahead_at = a.emap ? a.emap[nx] : nx;
       }
       strip_sync();
+      // A chunk that a wavefront has to itself in a short list is many rounds of rows one after the other: the next
+      // round's rows arrive while this one's are multiplied.  (R-MAT 60k, k = 32: 18.4 -> 16.4 us; 100k, 200: 148 -> 132; shared
+      // chunks lose, 16k, 64: 8.9 -> 9.3, and the registers cost the long lists and the rows their occupancy.)
+      if (AHEAD && a.k <= LPR * VEC) {
+        const uint32_t row_bytes = 4u * (uint32_t)a.k, col_bytes = lc0.ok ? 4u * (uint32_t)lc0.c : 0u;
+        auto load = [&](V (&x)[NB], uint32_t s) {
+#pragma unroll
+          for (int u = 0; u < NB; ++u) {
+            const uint32_t i = (s + u) * G + g;
+            x[u] = i < nb && lc0.ok ? load_row<VEC, SMALL>(base, ents[i % 64].xrow, row_bytes, col_bytes) : vzero<VEC>();
+          }
+        };
+        auto finish = [&](V (&x)[NB], uint32_t s) {
+          float p[NB];
+          if (a.k % VEC != 0) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) drop_shared(x[u], lc0.shared);
+          }
+#pragma unroll
+          for (int u = 0; u < NB; ++u) p[u] = vdot(u0, x[u]);
+          const float dot = group_reduce<NB, LPR>(p, (int)l);
+          const uint32_t idx = (s + l / SPAN) * G + g;
+          if (l % SPAN == 0 && idx < nb) a.S[ats[idx]] = ents[idx].val * dot;
+        };
+        V x0[NB], x1[NB];
+        load(x0, 0);
+        for (uint32_t s = 0;; s += 2 * NB) {
+          const bool more = (s + NB) * G < nb, more2 = (s + 2 * NB) * G < nb;
+          if (more) load(x1, s + NB);
+          finish(x0, s);
+          if (!more) break;
+          if (more2) load(x0, s + 2 * NB);
+          finish(x1, s + NB);
+          if (!more2) break;
+        }
+        strip_sync();
+        continue;
+      }
       for (uint32_t s = 0; s * G < nb; s += NB) {   // round s + u: lane group g handles entry (s + u) * G + g
         float dot;
         if ((s + NB) * G <= nb)
@@ -264,7 +302,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_chunks_kernel(const SampledArgs 
   if (a.runs && base + span <= gridDim.x) id = base + id % kDies * kDieRun + (id - base) / kDies;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int64_t ch = (int64_t)id * WPB + wave;      // (a list in window order is never short)
-  if (ch < a.n_chunks) sampled_chunk<VEC, LPR, NB, SMALL>(ents[wave], ats[wave], a, ch, 0);
+  if (ch < a.n_chunks) sampled_chunk<VEC, LPR, NB, SMALL, false>(ents[wave], ats[wave], a, ch, 0);
 }
 
 template <int VEC, int LPR, int NB, bool SMALL, bool WINDOW, bool ONCE>
@@ -275,8 +313,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_rows_kernel(const SampledArgs a)
   if (n_it > 0) sampled_rows<VEC, LPR, NB, SMALL, WINDOW, ONCE>(sh, a, first, n_it);
 }
 
-// Both lists in one launch (short lists: the second launch would be most of the time).
-template <int VEC, int LPR, int NB, bool SMALL>
+// Both lists in one launch (short lists: the second launch would be most of the time).  AHEAD: see sampled_chunk.
+template <int VEC, int LPR, int NB, bool SMALL, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SampledArgs a) {
   constexpr int WPB = kBlock / 64;
   union Shared {
@@ -290,7 +328,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SampledArgs a) {
     const uint32_t slot = blockIdx.x * WPB + wave;  // fewer than 2^31, the launch sees to that
     const int64_t ch = slot / a.chunk_parts;
     if (ch < a.n_chunks)
-      sampled_chunk<VEC, LPR, NB, SMALL>(sh.chunk.ents[wave], sh.chunk.ats[wave], a, ch, slot % a.chunk_parts);
+      sampled_chunk<VEC, LPR, NB, SMALL, AHEAD>(sh.chunk.ents[wave], sh.chunk.ats[wave], a, ch, slot % a.chunk_parts);
     return;
   }
   const int64_t first = (int64_t)(blockIdx.x - a.chunk_blocks) * a.items;
@@ -344,7 +382,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   // 24.4 / 19.8, but 64: - / 13.7 / 14.4; Chung-Lu 80k, 50: 35.1 / 30.0 / 32.2; 130k, 64: 61.2 / 65.5).
   a.chunk_parts = 1;
   const uint32_t most = s.lpr < 4 ? 1u : (s.lpr < 8 ? 2u : (uint32_t)s.lpr / 4);
-  const int64_t rounds = 3 * (64 / s.lpr) * kSampledBatch;
+  const int64_t rounds = 7 * (64 / s.lpr) * kSampledBatch / 2;
   if (!window_rows && !windows && !die_queues)
     while (a.chunk_parts < most && (a.n_chunks * a.chunk_parts * 2 <= kResidentWaves ||
                                     (a.n_chunks * a.chunk_parts * 2 <= 2 * kResidentWaves &&
@@ -367,7 +405,8 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
       else if (row_blocks > 0) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA true ARROW_COMMA false); }
     } else if (!windows && chunk_blocks > 0) {
       a.chunk_blocks = (uint32_t)chunk_blocks;
-      ARROW_LAUNCH(sddmm_kernel, chunk_blocks + row_blocks, );
+      if (a.chunk_parts == 1) { ARROW_LAUNCH(sddmm_kernel, chunk_blocks + row_blocks, ARROW_COMMA true); }
+      else { ARROW_LAUNCH(sddmm_kernel, chunk_blocks + row_blocks, ARROW_COMMA false); }
     } else {
       if (chunk_blocks > 0) { ARROW_LAUNCH(sddmm_chunks_kernel, chunk_blocks, ); }
       if (row_blocks > 0 && once) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA false ARROW_COMMA true); }

@@ -320,3 +320,23 @@ def test_items_per_workgroup_and_wavefronts_per_chunk(torch, n, k, longest):
     op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), S)
     op.close()
     assert_within(S.cpu().numpy(), *oracle.sddmm(rowptr, colidx, vals, U, V))
+
+
+@pytest.mark.parametrize("k", [5, 20, 50, 128, 256, 257])
+def test_chunks_of_a_wavefront_each(torch, k):
+    """So many chunks that each has a wavefront to itself, of 49 to 256 entries: whole and partly filled strips and rounds,
+    an odd and an even number of them."""
+    n = 9000
+    rng = np.random.default_rng(k)
+    length = rng.integers(49, 257, n)
+    col = [np.sort(rng.choice(n, m, replace=False)) for m in length]
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    colidx = np.concatenate(col).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    U, V = synth.normal_matrix(n, k, seed=28), synth.normal_matrix(n, k, seed=29)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, 600)
+    assert op.levels()[0]["chunks"] > 8192
+    S = torch.full((len(colidx),), float("nan"), device="cuda")
+    op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), S)
+    op.close()
+    assert_within(S.cpu().numpy(), *oracle.sddmm(rowptr, colidx, vals, U, V))
