@@ -195,14 +195,15 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
         // gains more from than the second pass over the entries costs -- where a row fills whole
         // 128-byte lines.  In other rows a slice starts and ends inside a line, and both neighbours
         // fetch it: R-MAT 262k, k = 68: 235 us in two slices, 160 us in one; k = 130: 417 and 354 us.
-        // (A short list has few wavefronts and long chains instead: slices shorten them.  Where they share lines anyway,
-        // fewer of them: R-MAT 20k, k = 150 / 200 / 260, all rows so: 24.1 / 29.0 / 36.4 us in 64 columns, 22.7 / 25.1 / 32.9 in 128.)
-        tune.kc = k % 32 != 0 && k > 128 ? 128 : 64;
+        // (A short list has few wavefronts and long chains instead: slices shorten them.  128 columns are faster
+        // where slices share lines, R-MAT 20k, k = 150 / 200 / 260: 24.1 / 29.0 / 36.4 -> 22.7 / 25.1 / 32.9 us, but two lane
+        // groups add a chunk then instead of four, and the error against 64 bits grows, at k = 130 1.14e-7 -> 1.47e-7 of the norm.)
+        tune.kc = 64;
       }
     }
     // Beside long ones the short rows run in one pass over whole rows, of which they read each only a few times, unless a cache holds X: they
     // then take the slices of the long ones and with them their launch (one launch / two, us).  Lists in row order always: R-MAT 20k,
-    // k = 70 / 96 / 128 / 200: 16.6 / 21.9, 15.5 / 20.3, 16.3 / 21.4, 25.1 / 37.1; 65k, 96 / 128: 34.5 / 41.3, 37.8 / 44.1; 131k, 128: 83.3 /
+    // k = 70 / 96 / 128 / 200: 16.6 / 21.9, 15.5 / 20.3, 16.3 / 21.4, 29.0 / 37.1; 65k, 96 / 128: 34.5 / 41.3, 37.8 / 44.1; 131k, 128: 83.3 /
     // 84.6; directed 30k, 128: 17.9 / 24.8.  Others where the cache behind the L2s has room for X and the slices are equal: R-MAT 180k,
     // k = 128: 133 / 140; 262k, 192: 256 / 265; 400k, 128: 220 / 228; Chung-Lu 250k, 128: 167 / 179; beyond (524k, 192, 384 MiB):
     // 636 / 638; Chung-Lu 700k, 128: 524 / 520; unequal ones (k = 96, Chung-Lu 250k, two sets of dies) 158 / 153.
