@@ -202,6 +202,16 @@ template <int M> __device__ __forceinline__ float exchange(float a, float b, int
   }
 }
 
+// The sum over all lanes, in every lane: over bit 0 first, then bits 1 to 5.
+__device__ __forceinline__ float wave_sum(float v) {
+  v += across<1>(v);
+  v += across<2>(v);
+  v += across<4>(v);
+  v += across<8>(v);
+  v = exchange<16>(v, v, 0);
+  return exchange<32>(v, v, 0);
+}
+
 // Sums of NB values over the LPR lanes of a group: the upper lanes keep the upper half of the values at
 // every exchange, so that lane l ends up with the sum of value l / (LPR / NB).  With shuffles through
 // LDS instead of permlane swaps and DPP operands it took 40 vector instructions and 6 LDS accesses for

@@ -222,9 +222,15 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
 // that the entries are read R / 4 times, 6 bytes a step; the workgroups of one die that
 // differ in their columns go through the same items at the same time, so that 95 % of these loads hit the L2.
 // Uniform 4096^3 tensor, 68.7 M entries in 16.5 M fibres: R = 64 850 -> 443 us, R = 8 378 -> 107, R = 128 1636 ->
-// 822; 1300^3, 2.2 M entries, R = 64: 43.6 -> 31.8 us.  Of the 443 us (R = 64) LDS works 360, the loads of the entries
-// 315, the vector units 300.  Entry and offset as a pair of eight bytes per step: 593 us, with loads of 8 bytes per lane
-// 792 (those move 75 bytes per ns into a compute unit, 16-byte ones 120).
+// 822.  What bounds it is what comes back to the registers, 16 bytes of a row and 6 of the image per lane and
+// step: 943 k cycles at 128 bytes a cycle, of 955 k that pass.  LDS works 735 k of them (bank conflicts included; an order of the
+// entries with a third fewer of those gained 1 %), the vector units 625 k.  Entry and offset as a pair of eight bytes
+// per step: 593 us.  Rows of the next half block read from LDS ahead of the sums: 465 us (smaller tensors gained 1 to 2 %).
+//
+// Where items are short, what an item ends with counts: its 64 sums were added with 24 shuffles through LDS, six latencies in
+// a row, behind which the rows of the next block waited.  DPP operands and permlane swaps instead (the same sums), and
+// two blocks on their way instead of three: 3000 x 500 x 2500, 3.75 M entries, R = 96: 68.2 -> 56.9 us; 1300^3, 2.2 M,
+// R = 64: 31.0 -> 26.7; 1000 x 2000 x 3000, 6 M, R = 32: 29.2 -> 27.5; 4096^3, R = 64: 450.6 -> 448.0.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kResidentBlock = 1024;
 
@@ -277,7 +283,7 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
   if (threadIdx.x == 0) s_row[K] = vzero<4>();
   __syncthreads();
   const char* lds = reinterpret_cast<const char*>(s_row);
-  constexpr int U = kCsfBlockSteps, N = 3;              // blocks on their way
+  constexpr int U = kCsfBlockSteps, N = 2;              // blocks on their way
   static_assert(U == 8, "the steps of a block");
   const uint32_t lane = threadIdx.x % 64;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
@@ -308,8 +314,7 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
   for (int h = 0; h < N; ++h) fetch(h);
   float4 sum = vzero<4>(), part = vzero<4>(), acc = vzero<4>(), x = vzero<4>();
   auto store = [&] {
-#pragma unroll
-    for (int w = 1; w < 64; w <<= 1) vadd(sum, vshfl_xor(sum, w));
+    sum = make_float4(wave_sum(sum.x), wave_sum(sum.y), wave_sum(sum.z), wave_sum(sum.w));
     if (lane == 0) {
       float* out = (d.dst >= 0 ? A + (size_t)d.dst * (size_t)R : partials + (size_t)(-1 - d.dst) * (size_t)R) + c0;
       if (R >= 4) {
