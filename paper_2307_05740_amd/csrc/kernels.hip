@@ -62,7 +62,7 @@ constexpr int kFlowBatches = 4;        // batches of a workgroup of the flow ker
 constexpr int64_t kFlowBlocks = 1536;  // less than these workgroups, the ones the chip holds at a time
 constexpr int64_t kFlowLeast = 1024;   // fewest batches it takes (100489 rows, k = 32: 13.2 -> 10.2 us; 40000, k = 16: 5.3 and 5.6)
 constexpr int64_t kDieSetsLeast = 8LL << 20;     // smallest X whose column slices are dealt to sets of dies,
-constexpr int64_t kDieSetsMost = 512LL << 20;    // ... and the largest where there are more than two of them
+constexpr int64_t kDieSetsMost = 512LL << 20;    // ... and the largest
 constexpr int kRowsStage = 1024;   // entries of the group list a workgroup stages at once (8 KiB)
 
 template <int LPR> constexpr int strip_entries() {     // entries of the wave list a wavefront parks per batch
@@ -258,6 +258,10 @@ __device__ __forceinline__ SliceBlock slice_block(const ProductArgs& a, uint32_t
   const uint32_t dies_log = kDiesLog - a.sets_log, die = id % kDies;
   uint32_t at = (id / kDies << dies_log) + (die & ((1u << dies_log) - 1u));
   uint32_t slice = (die >> dies_log) * (a.slices >> a.sets_log);
+  if (a.slices > 8) {
+    const uint32_t more = at / blocks;
+    return {slice + more, at - more * blocks};
+  }
   for (; at >= blocks; at -= blocks) ++slice;       // (few slices: a division costs more)
   return {slice, at};
 }
@@ -1196,16 +1200,16 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
   // Two sets of dies (slice_block) wherever there is an even number of slices that share no lines, or hardly any: an L2
   // then holds and fetches half of every row of X (us, all slices on every die / two sets / four; R-MAT unless said
   // otherwise): 10k, k = 256: 20.7 / 20.0 / 17.1; 65k, 256: 76.7 / 68.1 / 71.5; 131k, 256: 200 / 190 / 174; 180k, 256: 256 /
-  // 245 / 251; 200k, 384: 325 / 313 / 324; 65k, 512: 174 / 152 / 146; 524k, 128: 419 / 412; 8m, 128: 11631 / 11553;
-  // Chung-Lu 60k, 256: 82.5 / 76.9 / 74.2, 250k: 336 / 318 / 327.  Narrow slices that end inside a line are fetched by both
-  // sets (R-MAT 17.5k, k = 70: 15.1 / 16.5; but 65k, k = 260, 102 / 94), and more than two slices of an X that no cache holds
-  // are worse off (800k, k = 256: 907 / 921).
+  // 245 / 251; 200k, 384: 325 / 313 / 324; 65k, 512: 174 / 152 / 146; 524k, 128: 419 / 412; Chung-Lu 60k, 256: 82.5 / 76.9 / 74.2,
+  // 250k: 336 / 318 / 327.  Narrow slices that end inside a line are fetched by both sets (R-MAT 17.5k, k = 70: 15.1 / 16.5;
+  // but 65k, k = 260, 102 / 94).  Beyond twice the cache behind the L2s it depends on the graph (k = 128: Chung-Lu 900k, 460 MB,
+  // 725 / 718, 1.5m 1224 / 1228, 2m 1728 / 1737; R-MAT 1.5m 1568 / 1520, 4m 5537 / 5500, 8m 11620 / 11680; 800k, k = 256, 820 MB,
+  // 907 / 921).
   // Slices of unequal width would leave dies idle (k = 96, 64 + 32 columns: 20.9 / 22.4).
   const bool lines = s.width % 32 == 0 || s.width >= 128, equal = a.k > (s.slices - 1) * s.width + s.width * 3 / 4;
   // And an X that an L2 nearly holds gains nothing (10k, k = 128: 14.7 / 15.0).
   const int64_t x_bytes = x_rows * a.k * (int64_t)sizeof(float);
-  const bool sets = !die_queues && s.slices % 2 == 0 && lines && equal && x_bytes >= kDieSetsLeast &&
-                    (s.slices == 2 || x_bytes <= kDieSetsMost);
+  const bool sets = !die_queues && s.slices % 2 == 0 && lines && equal && x_bytes >= kDieSetsLeast && x_bytes <= kDieSetsMost;
   a.sets_log = sets ? 1 : 0;
   // Stencils, meshes, bands: hardly any long rows or pieces of them, whichever launch those are in, and enough
   // batches for every compute unit to have several in turn.  (1m rows of 3 to 8 random entries and one in
