@@ -313,7 +313,7 @@ int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int3
                   int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials, int32_t R,
                   int32_t longest, int32_t average, void* stream);   // entries and segments of the longest item and of one on average
 
-// The other form of the fibre image, for factors whose rows all fit the LDS of a compute unit four columns at a
+// The other form of the fibre image, for factors whose rows all fit the LDS of a compute unit four (or even eight) columns at a
 // time (resident_kernel in mttkrp.hip): the segments of an item side by side, one per lane, as a sequence of
 // STEPS, in each of which a lane reads one row from LDS and has a value for it.  In LDS lie the K rows of C, a
 // row of zeros (which the steps that fill up read) and the J rows of B.  A bit per step says that its rows are

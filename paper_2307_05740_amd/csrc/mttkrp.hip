@@ -31,6 +31,7 @@
 // fixed order.  No atomics.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cstdint>
 #include <type_traits>
@@ -210,8 +211,8 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// resident kernel: both factors in LDS, four columns at a time.  A workgroup copies its four columns of all rows
-// of C and B (16 bytes a row, at most 10200 rows) and keeps them while its sixteen wavefronts go through
+// resident kernel: both factors in LDS, four or eight columns at a time.  A workgroup copies its columns of all rows
+// of C and B (16 bytes a row and four columns, at most 10200 of them) and keeps them while its sixteen wavefronts go through
 // items.  A lane owns a segment: in every step it reads one row of C from LDS and adds it, times the value, to
 // the segment's sum, until the step that multiplies the sum by the row of B.  All lanes of a batch do this in
 // the same step, so the choice is a scalar one; the image holds the offsets and values in this order (ResidentBlock), so
@@ -230,7 +231,15 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
 // Where items are short, what an item ends with counts: its 64 sums were added with 24 shuffles through LDS, six latencies in
 // a row, behind which the rows of the next block waited.  DPP operands and permlane swaps instead (the same sums), and
 // two blocks on their way instead of three: 3000 x 500 x 2500, 3.75 M entries, R = 96: 68.2 -> 56.9 us; 1300^3, 2.2 M,
-// R = 64: 31.0 -> 26.7; 1000 x 2000 x 3000, 6 M, R = 32: 29.2 -> 27.5; 4096^3, R = 64: 450.6 -> 448.0.
+// R = 64: 31.0 -> 26.7; 1000 x 2000 x 3000, 6 M, R = 32: 29.2 -> 27.5; 4096^3, R = 64: 450.6 -> 448.0.  What items are left
+// after whole turns of all wavefronts are spread over the workgroups, not given to the first of them: 2100 x 1500 x 2000, 6.3 M,
+// R = 8: 18.2 -> 16.0; 900 x 2000 x 3000, 5.4 M, R = 9: 15.6 -> 13.8; 700 x 2000 x 1500, 2.1 M, R = 100: 34.9 -> 32.8.
+//
+// Half as many rows fit with eight columns of each, in two planes (the banks of a step stay those that the image was ordered
+// for): 38 bytes come back for eight columns instead of 44, and the offsets are taken apart once.  Fewer rows read ahead of the
+// sums are better, the other wavefronts of a SIMD fill the wait: eight columns, rows of 4 / 2 / 1 steps together: 4096 x 2500 x
+// 2500 of 25.6 M, R = 64, 165.3 / 161.3 / 150.5 us (four columns: 8 / 4 / 2 steps 170.6 / 166.9 / 172.3; 4096^3 453.0 / 449.8 /
+// 466.4, and with a third block on its way 443.6).
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kResidentBlock = 1024;
 
@@ -238,7 +247,7 @@ constexpr int kResidentBlock = 1024;
 // with the row of B to acc.  The bit is the same for the whole wavefront; written out because the compiler
 // turned the choice into sixteen register moves a step.
 template <int BIT>
-__device__ __forceinline__ void resident_step(float4& acc, float4& x, uint32_t bits, float v, float4 c) {
+__device__ __forceinline__ void resident_step(float4 (&acc)[1], float4 (&x)[1], uint32_t bits, float v, const float4 (&c)[1]) {
   asm volatile(
       "s_bitcmp1_b32 %[m], %[bit]\n\t"
       "s_cbranch_scc1 1f\n\t"
@@ -257,14 +266,58 @@ __device__ __forceinline__ void resident_step(float4& acc, float4& x, uint32_t b
       "v_mov_b32 %[x2], 0\n\t"
       "v_mov_b32 %[x3], 0\n"
       "2:"
-      : [x0] "+v"(x.x), [x1] "+v"(x.y), [x2] "+v"(x.z), [x3] "+v"(x.w),
-        [a0] "+v"(acc.x), [a1] "+v"(acc.y), [a2] "+v"(acc.z), [a3] "+v"(acc.w)
-      : [m] "s"(bits), [bit] "n"(BIT), [v] "v"(v), [c0] "v"(c.x), [c1] "v"(c.y), [c2] "v"(c.z), [c3] "v"(c.w)
+      : [x0] "+v"(x[0].x), [x1] "+v"(x[0].y), [x2] "+v"(x[0].z), [x3] "+v"(x[0].w),
+        [a0] "+v"(acc[0].x), [a1] "+v"(acc[0].y), [a2] "+v"(acc[0].z), [a3] "+v"(acc[0].w)
+      : [m] "s"(bits), [bit] "n"(BIT), [v] "v"(v), [c0] "v"(c[0].x), [c1] "v"(c[0].y), [c2] "v"(c[0].z), [c3] "v"(c[0].w)
+      : "scc");
+}
+template <int BIT>
+__device__ __forceinline__ void resident_step(float4 (&acc)[2], float4 (&x)[2], uint32_t bits, float v, const float4 (&c)[2]) {
+  asm volatile(
+      "s_bitcmp1_b32 %[m], %[bit]\n\t"
+      "s_cbranch_scc1 1f\n\t"
+      "v_fmac_f32 %[x0], %[v], %[c0]\n\t"
+      "v_fmac_f32 %[x1], %[v], %[c1]\n\t"
+      "v_fmac_f32 %[x2], %[v], %[c2]\n\t"
+      "v_fmac_f32 %[x3], %[v], %[c3]\n\t"
+      "v_fmac_f32 %[x4], %[v], %[c4]\n\t"
+      "v_fmac_f32 %[x5], %[v], %[c5]\n\t"
+      "v_fmac_f32 %[x6], %[v], %[c6]\n\t"
+      "v_fmac_f32 %[x7], %[v], %[c7]\n\t"
+      "s_branch 2f\n"
+      "1:\n\t"
+      "v_fmac_f32 %[a0], %[x0], %[c0]\n\t"
+      "v_fmac_f32 %[a1], %[x1], %[c1]\n\t"
+      "v_fmac_f32 %[a2], %[x2], %[c2]\n\t"
+      "v_fmac_f32 %[a3], %[x3], %[c3]\n\t"
+      "v_fmac_f32 %[a4], %[x4], %[c4]\n\t"
+      "v_fmac_f32 %[a5], %[x5], %[c5]\n\t"
+      "v_fmac_f32 %[a6], %[x6], %[c6]\n\t"
+      "v_fmac_f32 %[a7], %[x7], %[c7]\n\t"
+      "v_mov_b32 %[x0], 0\n\t"
+      "v_mov_b32 %[x1], 0\n\t"
+      "v_mov_b32 %[x2], 0\n\t"
+      "v_mov_b32 %[x3], 0\n\t"
+      "v_mov_b32 %[x4], 0\n\t"
+      "v_mov_b32 %[x5], 0\n\t"
+      "v_mov_b32 %[x6], 0\n\t"
+      "v_mov_b32 %[x7], 0\n"
+      "2:"
+      : [x0] "+v"(x[0].x), [x1] "+v"(x[0].y), [x2] "+v"(x[0].z), [x3] "+v"(x[0].w),
+        [x4] "+v"(x[1].x), [x5] "+v"(x[1].y), [x6] "+v"(x[1].z), [x7] "+v"(x[1].w),
+        [a0] "+v"(acc[0].x), [a1] "+v"(acc[0].y), [a2] "+v"(acc[0].z), [a3] "+v"(acc[0].w),
+        [a4] "+v"(acc[1].x), [a5] "+v"(acc[1].y), [a6] "+v"(acc[1].z), [a7] "+v"(acc[1].w)
+      : [m] "s"(bits), [bit] "n"(BIT), [v] "v"(v), [c0] "v"(c[0].x), [c1] "v"(c[0].y), [c2] "v"(c[0].z), [c3] "v"(c[0].w),
+        [c4] "v"(c[1].x), [c5] "v"(c[1].y), [c6] "v"(c[1].z), [c7] "v"(c[1].w)
       : "scc");
 }
 
 constexpr int kResidentGroups = 256;     // workgroups: one per compute unit, which holds one window of rows
+constexpr int kResidentLong = 4096;      // steps of a wavefront from which on a third block on its way gains more than it costs at first
 
+// P: quads of columns of a workgroup, each in a plane of its own of all rows; UR: steps whose rows are read together; N: blocks
+// on their way.
+template <int P, int UR, int N>
 __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
     const ResidentItem* __restrict__ items, const ResidentBlock* __restrict__ blocks, int n_items,
     const float* __restrict__ B, int J, const float* __restrict__ C, int K, float* __restrict__ A,
@@ -272,23 +325,32 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
   __shared__ float4 s_row[kCsfRowsInLds];
   const int per_die = gridDim.x / 8, q = (int)(blockIdx.x % 8) * per_die + (int)(blockIdx.x / 8);
   if (q >= slices * replicas) return;
-  const int slice = q % slices, c0 = R >= 4 ? min(4 * slice, R - 4) : 0;
-  auto row_of = [&](const float* M, int r) {
+  const int rows = K + 1 + J;                           // (P planes of them fit, the launch sees to that)
+  const int slice = q % slices, c0 = R >= 4 * P ? min(4 * P * slice, R - 4 * P) : 0;
+  auto copy = [&](const float* M, int r, int at) {
     const float* p = M + (size_t)r * (size_t)R + c0;
-    if (R >= 4) return gload<4>(p);
-    return make_float4(p[0], R > 1 ? p[1] : 0.f, R > 2 ? p[2] : 0.f, 0.f);
+    if (P > 1 || R >= 4) {
+      float4 v[P];
+#pragma unroll
+      for (int e = 0; e < P; ++e) v[e] = gload<4>(p + 4 * e);
+#pragma unroll
+      for (int e = 0; e < P; ++e) s_row[e * rows + at] = v[e];
+    } else {
+      s_row[at] = make_float4(p[0], R > 1 ? p[1] : 0.f, R > 2 ? p[2] : 0.f, 0.f);
+    }
   };
-  for (int r = threadIdx.x; r < K; r += kResidentBlock) s_row[r] = row_of(C, r);
-  for (int r = threadIdx.x; r < J; r += kResidentBlock) s_row[K + 1 + r] = row_of(B, r);
-  if (threadIdx.x == 0) s_row[K] = vzero<4>();
+  for (int r = threadIdx.x; r < K; r += kResidentBlock) copy(C, r, r);
+  for (int r = threadIdx.x; r < J; r += kResidentBlock) copy(B, r, K + 1 + r);
+  if (threadIdx.x < P) s_row[threadIdx.x * rows + K] = vzero<4>();
   __syncthreads();
   const char* lds = reinterpret_cast<const char*>(s_row);
-  constexpr int U = kCsfBlockSteps, N = 2;              // blocks on their way
+  const uint32_t plane = (uint32_t)rows * (uint32_t)sizeof(float4);
+  constexpr int U = kCsfBlockSteps;
   static_assert(U == 8, "the steps of a block");
   const uint32_t lane = threadIdx.x % 64;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
   const int workers = replicas * (kResidentBlock / 64);
-  int it = q / slices * (kResidentBlock / 64) + wave;
+  int it = wave * replicas + q / slices;                // what is left after whole turns goes to all workgroups
   if (it >= n_items) return;
   // The blocks of this wavefront's items as one sequence, N of them on their way: `f` is the item that is
   // fetched from, `d` the one that is summed; what follows an item is loaded while there is time.
@@ -312,45 +374,63 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
   };
 #pragma unroll
   for (int h = 0; h < N; ++h) fetch(h);
-  float4 sum = vzero<4>(), part = vzero<4>(), acc = vzero<4>(), x = vzero<4>();
+  float4 sum[P], part[P], acc[P], x[P];
+#pragma unroll
+  for (int e = 0; e < P; ++e) sum[e] = part[e] = acc[e] = x[e] = vzero<4>();
   auto store = [&] {
-    sum = make_float4(wave_sum(sum.x), wave_sum(sum.y), wave_sum(sum.z), wave_sum(sum.w));
+#pragma unroll
+    for (int e = 0; e < P; ++e) sum[e] = make_float4(wave_sum(sum[e].x), wave_sum(sum[e].y), wave_sum(sum[e].z), wave_sum(sum[e].w));
     if (lane == 0) {
       float* out = (d.dst >= 0 ? A + (size_t)d.dst * (size_t)R : partials + (size_t)(-1 - d.dst) * (size_t)R) + c0;
-      if (R >= 4) {
-        gstore<4>(out, sum);
+      if (P > 1 || R >= 4) {
+#pragma unroll
+        for (int e = 0; e < P; ++e) gstore<4>(out + 4 * e, sum[e]);
       } else {
-        out[0] = sum.x;
-        if (R > 1) out[1] = sum.y;
-        if (R > 2) out[2] = sum.z;
+        out[0] = sum[0].x;
+        if (R > 1) out[1] = sum[0].y;
+        if (R > 2) out[2] = sum[0].z;
       }
     }
-    sum = vzero<4>();
+#pragma unroll
+    for (int e = 0; e < P; ++e) sum[e] = vzero<4>();
   };
   while (true) {
 #pragma unroll
     for (int h = 0; h < N; ++h) {
       const uint32_t w[4] = {of[h].x, of[h].y, of[h].z, of[h].w};
       const float v[U] = {lo[h].x, lo[h].y, lo[h].z, lo[h].w, hi[h].x, hi[h].y, hi[h].z, hi[h].w};
-      float4 c[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        c[u] = *reinterpret_cast<const float4*>(lds + ((u % 2 ? w[u / 2] >> 14 : w[u / 2]) & 0x3fff0u));
       uint32_t ends[U / 2];
 #pragma unroll
-      for (int u = 0; u < U / 2; ++u) ends[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[u]);
+      for (int u0 = 0; u0 < U; u0 += UR) {
+        float4 c[UR][P];
 #pragma unroll
-      for (int u = 0; u < U; u += 2) {
-        resident_step<0>(acc, x, ends[u / 2], v[u], c[u]);
-        resident_step<1>(acc, x, ends[u / 2], v[u + 1], c[u + 1]);
+        for (int u = u0; u < u0 + UR; ++u)
+#pragma unroll
+          for (int e = 0; e < P; ++e)
+            c[u - u0][e] = *reinterpret_cast<const float4*>(lds + ((u % 2 ? w[u / 2] >> 14 : w[u / 2]) & 0x3fff0u) + e * plane);
+        if (u0 == 0) {
+#pragma unroll
+          for (int u = 0; u < U / 2; ++u) ends[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[u]);
+        }
+#pragma unroll
+        for (int u = u0; u < u0 + UR; ++u) {
+          if (u % 2 == 0) resident_step<0>(acc, x, ends[u / 2], v[u], c[u - u0]);
+          else resident_step<1>(acc, x, ends[u / 2], v[u], c[u - u0]);
+        }
       }
       fetch(h);
       if (--d.blocks % 4 == 0) {                        // short chains of additions: as exact as the other kernel
-        vadd(part, acc);
-        acc = vzero<4>();
+#pragma unroll
+        for (int e = 0; e < P; ++e) {
+          vadd(part[e], acc[e]);
+          acc[e] = vzero<4>();
+        }
         if (d.blocks % 16 == 0) {
-          vadd(sum, part);
-          part = vzero<4>();
+#pragma unroll
+          for (int e = 0; e < P; ++e) {
+            vadd(sum[e], part[e]);
+            part[e] = vzero<4>();
+          }
         }
       }
       if (d.blocks == 0) {
@@ -556,19 +636,50 @@ int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* block
   // the compute units well; else more of them, each of which copies the factors again, four rows in about
   // the time of a wavefront's step.  (1300^3, R = 520, 130 slices: 338 -> 218 us with three
   // workgroups per slice in two rounds.)
-  const int64_t slices = ceil_div(R, 4), copy = (b_rows + c_rows) / 4;
-  int64_t replicas = 1;
-  double best = 0.0;
-  for (int64_t rounds = 1; rounds <= 4; ++rounds) {
-    const int64_t n = kResidentGroups * rounds / slices;
-    if (n < 1) continue;
-    const double cost = (double)rounds * ((double)(n_blocks * kCsfBlockSteps) / (double)n + (double)copy);
-    if (best == 0.0 || cost < best) { best = cost; replicas = n; }
+  struct Split { int64_t slices, replicas; double cost; };
+  const double copy = (double)((b_rows + c_rows) / 4), steps = (double)(n_blocks * kCsfBlockSteps);
+  constexpr int64_t waves = kResidentBlock / 64;
+  auto split = [&](int quads, double step, int64_t tail, double copied) {
+    Split s{ceil_div(R, 4 * quads), 1, 0.0};
+    double best = 0.0;
+    for (int64_t rounds = 1; rounds <= 4; ++rounds) {
+      const int64_t n = kResidentGroups * rounds / s.slices;
+      if (n < 1) continue;
+      const double cost = (double)rounds * (steps / (double)n + copy);
+      if (best != 0.0 && cost >= best) continue;
+      best = cost;
+      s.replicas = n;
+      // the items of a workgroup: `tail` of them at least in a last turn, of which each takes as long on its own
+      const int64_t turns = n_items / (n * waves), rest = n_items - turns * n * waves;
+      const int64_t load = turns * waves + (rest > 0 ? std::max(ceil_div(rest, n), tail) : 0);
+      s.cost = (double)rounds * (step * (double)load * steps / (double)n_items + copied * copy);
+    }
+    return s;
+  };
+  // Eight columns at a time where the rows fit the LDS so: the entries are read half as often, and a step takes 1.7
+  // times as long instead of twice.  Half as many slices leave twice as many wavefronts for the items, though, and a wavefront
+  // that has its SIMD to itself waits longer for each of its rows.  With the numbers below the cost's ratio is within 10 % of the
+  // measured one and on its side of 1 (four / eight columns, us): 4096 x 2500 x 2500 of 25.6 M, R = 64, 166.1 / 150.2; 4000 x 1000 x 1000 of 4 M,
+  // 128, 84.9 / 70.6; 3000 x 500 x 2500 of 3.75 M, 96, 56.5 / 46.8; 2100 x 1500 x 2000 of 6.3 M, 8, 16.0 / 13.9; 2500 x 600 x 1200 of 1.8 M, 32,
+  // 14.8 / 12.9; 1300^3 of 2.2 M, 64, 24.2 / 22.7; 3000 x 2000 x 1000 of 6 M, 16, 18.5 / 18.3; but 3000 x 3000 x 1000 of 9 M, 24, 34.0 / 35.1;
+  // 700 x 2000 x 1500 of 2.1 M, 100, 32.8 / 34.3; 1100 x 2500 x 2500 of 6.9 M, 32, 34.7 / 38.3; 512 x 1000 x 1000 of 512 K, 32, 7.4 / 7.8;
+  // 900 x 2000 x 3000 of 5.4 M, 9, 13.8 / 17.5.
+  Split s = split(1, 1.0, 5, 0.6);
+  bool two = false;
+  if (R >= 8 && 2 * (b_rows + c_rows + 1) <= kCsfRowsInLds) {
+    const Split t = split(2, 1.72, 10, 0.7);
+    two = t.cost < s.cost;
+    if (two) s = t;
   }
-  const int64_t groups = ceil_div(slices * replicas, 8) * 8;
+  const int64_t groups = ceil_div(s.slices * s.replicas, 8) * 8;
   if (groups > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(resident_kernel, dim3((unsigned)groups), dim3(kResidentBlock), 0, (hipStream_t)stream, items, blocks,
-                     (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)slices, (int)replicas);
+#define ARROW_LAUNCH(...)                                                                                                  \
+  hipLaunchKernelGGL((resident_kernel<__VA_ARGS__>), dim3((unsigned)groups), dim3(kResidentBlock), 0, (hipStream_t)stream, items, blocks, \
+                     (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)s.slices, (int)s.replicas)
+  if (two) ARROW_LAUNCH(2, 1, 2);
+  else if (steps >= (double)(s.replicas * waves) * kResidentLong) ARROW_LAUNCH(1, 4, 3);
+  else ARROW_LAUNCH(1, 4, 2);
+#undef ARROW_LAUNCH
   return (int)hipGetLastError();
 }
 

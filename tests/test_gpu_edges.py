@@ -359,6 +359,30 @@ def test_mttkrp_factors_in_lds(torch, I, J, K, nnz, R):
     op.close()
 
 
+@pytest.mark.parametrize("I,J,K,nnz,R", [
+    (2000, 2549, 2550, 1_500_000, 57), (2000, 2549, 2551, 1_500_000, 57), (2100, 1500, 2000, 6_000_000, 8),
+    (2000, 900, 1200, 1_500_000, 16), (1300, 1100, 700, 1_200_000, 63), (1300, 1100, 700, 1_200_000, 64), (600, 4000, 1500, 3_000_000, 1024)])
+def test_mttkrp_factors_in_lds_eight_columns(torch, I, J, K, nnz, R):
+    """The same form where eight columns at a time take less (not in the second and the last case, whose rows do not fit so): up
+    to the last row that fits (J + K + 1 = 5100), ranks that are no multiple of eight; the last case has the longest shares of a wavefront."""
+    rng = np.random.default_rng(I + R)
+    i, j, k = (rng.integers(0, d, nnz).astype(np.int32) for d in (I, J, K))
+    i[:9000] = 1                                             # a slice of several items
+    j[:300], j[300:600], k[300:600] = J - 1, 0, K - 1        # a fibre of several segments, a coordinate that repeats
+    v = rng.uniform(-1, 1, nnz).astype(np.float32)
+    B, C = synth.normal_matrix(J, R, seed=31), synth.normal_matrix(K, R, seed=32)
+    Aref, E = oracle.mttkrp((I, J, K), i, j, k, v, B, C)
+    op = binding.Csf3Mttkrp((I, J, K), i, j, k, v)
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_FACTORS_IN_LDS and op.info["partials"] > 0
+    A = torch.full((I, R), float("nan"), device="cuda")
+    op.mttkrp(torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(), A)
+    assert_within(A.cpu().numpy(), Aref, E)
+    first = A.clone()
+    op.mttkrp(torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(), A)
+    assert torch.equal(first, A)
+    op.close()
+
+
 @pytest.mark.parametrize("k", [1, 6, 20, 33, 128, 260])
 @pytest.mark.parametrize("fuse", [0, 1])
 def test_rows_of_many_partial_vectors(torch, k, fuse):
