@@ -75,22 +75,23 @@ struct csf3_handle {
 
 namespace {
 
-// Where the resident form pays (both forms measured, us, R = 8 / 64 / 128):
-//   1300^3 of 2.2 M, 1.17 steps per 64 rows     18.6 / 43.6 / 76.6 -> 11.5 / 31.8 / 52.2
-//   1000^3 of 1.0 M, 1.26                       11.2 / 23.1 / 38.5 ->  8.9 / 19.4 / 31.7
-//   520 x 1000 x 1000 of 520 K, 1.26             9.5 / 16.6 / 24.5 ->  8.2 / 12.7 / 19.4
-//   4096 x 2000 x 300 of 2.5 M, 1.37            22.4 / 54.8 / 93.8 -> 11.7 / 47.4 / 88.8
-// and where it does not: fill (4000 x 4000 x 128 of 2.0 M, 1.52: 20.5 / 46.1 / 79.3 -> 12.2 / 47.1 / 86.1), few items
-// (128 x 4000 x 1000 of 512 K, 128 items: 9.6 / 17.0 / 28.5 -> 14.1 / 18.1 / 19.8), few entries to pay for
-// copying the factors to LDS (1000 x 1000 x 200 of 200 K: 7.6 / 10.6 / 14.6 -> 6.6 / 11.6 / 18.5).
-// Fewer items do where they are short (438 x 789 x 1882 of 650 K: 10.1 / 13.4 / 28.2 -> 9.4 / 10.0 / 21.9; 215 x 2391 x 356 of
-// 183 K: 8.9 / 9.7 / 14.8 -> 8.1 / 9.1 / 12.8; but 337 x 3065 x 1819 of 1.9 M: 15.8 / 23.2 / 63 -> 20.5 / 22.3 / 44.5), and fewer
-// entries where fibres hold more than one (708 x 2340 x 201 of 333 K, 1.1 each, R = 128: 19.5 -> 20.1).
-constexpr int64_t kResidentNnz = 1 << 17, kResidentNnzSingle = 1 << 19;
-constexpr int64_t kResidentItems = 512, kResidentItemsShort = 200, kResidentShort = 2200;   // (rows of a short item)
-constexpr double kResidentFill = 1.4;
-// And every workgroup copies all J + K rows, which has to be paid for by the rows that are read, entries and segments.
-// The rank is not known here; 32 gains least (whole lines for the other form, and all compute units copy) (us, R = 8 / 32 /
+// Where the resident form pays.  Both forms measured on 2854 uniform tensors of 128 to 4096 rows a side and 30 K to 8 M entries, R = 8, 12,
+// 25, 32, 50, 64, 100 and 128: of the 1293 that this rule takes all gain on average over the ranks, 0.38 to 0.90 times the
+// other form's time, and four lose at a single rank, the worst 157 x 3694 x 1451 of 841 K, R = 32, 15.2 -> 17.3 us.
+//   608 x 1224 x 1970 of 1.47 M, 1.18 steps per 64 rows, R = 8 / 64 / 128   13.9 / 29.8 / 49.7 -> 7.2 / 18.9 / 29.2
+//   2414 x 1806 x 310 of 1.35 M, 1.47                                       14.3 / 32.8 / 55.5 -> 6.4 / 22.4 / 39.1
+//   144 x 415 x 1945 of 116 K, 1.36, 144 items                               8.3 / 13.5 / 19.3 -> 4.5 /  6.6 /  7.9
+//   282 x 223 x 1855 of 117 K, 1.74                                          7.7 / 12.2 / 17.0 -> 4.4 /  6.9 /  8.5
+// Fill is what loses at high ranks (beside thousands of slices that are shorter than a block: 4055 x 994 x 147 of 592 K, 1.85:
+// 10.5 / 18.2 / 27.3 -> 5.0 / 18.9 / 32.6; 4061 x 347 x 430 of 606 K, 2.02: 10.3 / 18.4 / 27.3 -> 5.1 / 18.6 / 32.8); from 2.1 on single tensors
+// lose on average.  Fewer items were not measured; tensors of 30 K to 64 K entries gained too and keep the form that they had.
+constexpr int64_t kResidentNnz = 1 << 16;
+constexpr int64_t kResidentItems = 128;
+constexpr double kResidentFill = 1.8;
+// And every workgroup copies all J + K rows, which has to be paid for by the rows that are read, entries and segments,
+// where they are so many that eight columns of them do not fit the LDS (below that nothing was lost down to 30 rows read per row
+// copied).  The rank is not known here; 32 gains least (whole lines for the other form, and all compute units copy).  Measured with
+// four columns and leftover items in the first workgroups (us, R = 8 / 32 /
 // 64 / 128; in brackets rows read per row copied, geometric mean over those ranks and 12, 24, 50 and 100 where
 // they were measured):
 //   520 x 9000 x 1000 of 560 K [109, +17 %]       9.8 / 12.2 / 16.9 / 31.2 -> 10.7 / 17.0 / 20.5 / 32.1
@@ -125,7 +126,7 @@ constexpr uint8_t kSixteens[4][16] = {{0, 1, 2, 3, 12, 13, 14, 15, 20, 21, 22, 2
 template <typename At>
 bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const std::vector<int32_t>& seg_j,
                    const std::vector<int32_t>& seg_i, At at, const int32_t* tk, const float* tv) {
-  if (h.J + h.K + 1 > arrow::kCsfRowsInLds || h.nnz < (h.nnz * 20 < h.n_seg * 23 ? kResidentNnzSingle : kResidentNnz)) return false;
+  if (h.J + h.K + 1 > arrow::kCsfRowsInLds || h.nnz < kResidentNnz) return false;
   const double most = kResidentFill * (double)(h.nnz + h.n_seg);           // rows read, fill included
   if (64.0 * arrow::kCsfBlockSteps * (double)h.I > most) return false;     // (a block per slice at least)
   struct Part { uint32_t seg, n, block, blocks; int32_t dst; };
@@ -153,10 +154,9 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
     s = end;
   }
   if (slots > 0x7fffffffLL || parts.size() > 0x7fffff00ULL) return false;
-  const int64_t least = h.nnz + h.n_seg <= kResidentShort * (int64_t)parts.size() ? kResidentItemsShort : kResidentItems;
-  if ((int64_t)parts.size() < least) return false;
+  if ((int64_t)parts.size() < kResidentItems) return false;
   const int64_t copied = h.J + h.K - ((int64_t)parts.size() <= kResidentFew ? kResidentFree : 0);
-  if (h.nnz + h.n_seg < kResidentReuse * copied) return false;
+  if (2 * (h.J + h.K + 1) > arrow::kCsfRowsInLds && h.nnz + h.n_seg < kResidentReuse * copied) return false;
   // segments by length, longest first: at_len[l] = where those of length kSegMax - l begin
   auto by_length = [&](const Part& p, std::array<uint32_t, kSegMax + 2>& at_len) {
     at_len.fill(0);

@@ -116,6 +116,22 @@ def test_form_of_the_image(I, J, K, nnz, form):
         binding.csf3_destroy(h)
 
 
+@pytest.mark.parametrize("I,J,K,nnz,form", [
+    (144, 415, 1945, 116_000, binding.CSF3_FORM_FACTORS_IN_LDS),        # 144 items, 70 rows read for every row copied
+    (282, 223, 1855, 117_000, binding.CSF3_FORM_FACTORS_IN_LDS),        # 1.74 steps for every row
+    (161, 1645, 160, 66_000, binding.CSF3_FORM_FACTORS_IN_LDS),         # fibres of one entry
+    (161, 1645, 160, 65_000, binding.CSF3_FORM_ITEMS),                  # too few entries
+    (127, 1645, 500, 104_000, binding.CSF3_FORM_ITEMS),                 # 127 items
+    (4061, 347, 430, 606_000, binding.CSF3_FORM_ITEMS),                 # 2.0 steps for every row
+    (520, 2549, 2550, 300_000, binding.CSF3_FORM_FACTORS_IN_LDS),       # the most rows that fit with eight columns
+    (700, 2549, 2551, 300_000, binding.CSF3_FORM_ITEMS)])               # 117 rows read for every row copied
+def test_form_of_tensors_with_few_entries_or_items(I, J, K, nnz, form):
+    rng = np.random.default_rng(7)
+    h = binding.csf3_build((I, J, K), *(rng.integers(0, d, nnz).astype(np.int32) for d in (I, J, K)), np.ones(nnz, np.float32))
+    assert binding.csf3_form(h) == form
+    binding.csf3_destroy(h)
+
+
 @pytest.mark.parametrize("I,J,live,form", [
     (60_000, 30_000, 700, binding.CSF3_FORM_ITEMS),              # slices of 3143 entries between empty ones
     (60_000, 30_000, 3000, binding.CSF3_FORM_SUMS_IN_LDS),       # of 733

@@ -73,6 +73,22 @@ def test_all_ranks(torch, R):
     op.close()
 
 
+@pytest.mark.parametrize("R", [1, 3, 8, 9, 33, 128])
+@pytest.mark.parametrize("I,J,K,nnz", [(144, 415, 1945, 116_000), (161, 1645, 160, 66_000), (128, 300, 200, 70_000), (520, 2549, 2550, 300_000)])
+def test_few_items_with_factors_in_lds(torch, I, J, K, nnz, R):
+    """Fewer items than wavefronts of a column slice, down to the fewest and to the fewest entries, in the form with
+    the factors in LDS: every workgroup has some of them and none has more than its turn."""
+    rng = np.random.default_rng(I + R)
+    i, j, k = (rng.integers(0, d, nnz).astype(np.int32) for d in (I, J, K))
+    v = rng.uniform(-1, 1, nnz).astype(np.float32)
+    B, C = synth.normal_matrix(J, R, seed=31), synth.normal_matrix(K, R, seed=32)
+    op, _, _, A = run(torch, (I, J, K), i, j, k, v, B, C)
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_FACTORS_IN_LDS
+    Aref, E = oracle.mttkrp((I, J, K), i, j, k, v, B, C)
+    assert_within(A, Aref, E)
+    op.close()
+
+
 def test_unsorted_input_duplicates_and_long_fibre(torch):
     rng = np.random.default_rng(5)
     I, J, K, R = 40, 30, 700, 24
