@@ -1299,7 +1299,9 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, in
     width = (int)ceil_div(k, slices);
   }
   // Several workgroups stage the same window and share its rows where that fills the compute units better: by the number of
-  // rounds of workgroups times the time that one takes for its window and its share of the entries.  (Tiles of 512 rows
+  // rounds of workgroups times the time that one takes for its window and its share of the entries.  A tile's workgroups run on
+  // one die, so the rounds are those of the die with most tiles (14 tiles in three slices, k = 141: six workgroups a tile are
+  // 252, but 36 for the 32 compute units of six dies: 29.6 us, with four a tile 24.5).  (Tiles of 512 rows
   // with 30 to 60 entries, 1 / 2 / 3 / 4 / 6 workgroups a tile, us: k = 64, 130 tiles 44 / 45 / 36 / 41 / 42, 180 47 / 49 / 51 / 44 /
   // 53, 258 74 / 63 / 60 / 62 / 67, 380 78 / 67 / 75 / 74 / 85, 700 129 / 137 / 141 / 153 / 174; k = 32, 70 tiles 37 / 23 / 19 / 18 / 16,
   // 130 49 / 32 / 26 / 29 / 29; k = 128, 512 tiles 155 / - ; two workgroups of one compute unit share its time: k = 16, 380
@@ -1308,7 +1310,8 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, in
   double best = 0.0;
   const double tile_nnz = (double)nnz / (double)n_tiles;
   for (int p = 1; p <= kWinParts; p += p < 4 ? 1 : 2) {
-    const double cost = (double)ceil_div(n_tiles * slices * p, kComputeUnits) * (kWinStage * (double)max_span + tile_nnz / p);
+    const double rounds = (double)ceil_div(ceil_div(n_tiles, kDies) * slices * p, kComputeUnits / kDies);
+    const double cost = rounds * (kWinStage * (double)max_span + tile_nnz / p);
     if (p == 1 || cost < best) { best = cost; parts = p; }
   }
   const int64_t blocks = ceil_div(n_tiles, kDies) * kDies * slices * parts;
