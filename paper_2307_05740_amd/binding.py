@@ -431,13 +431,15 @@ class ArrowSpMM:
     def _ensure_workspace(self, k: int, second: bool = False) -> None:
         """Bind a workspace for k columns; `second`: with room for another n x k buffer, if there is memory for it.
         One that is bound and suffices without that room stays: a captured graph may hold its address, and a
-        call may be captured itself."""
+        call may be captured itself.  `_ws_k` names columns only while a workspace for them is bound: the native
+        calls go by it alone, also where no memory is left for the new one."""
         if self._ws is not None and self._ws_k >= k:
             return
         torch = self._torch
         torch.cuda.current_stream(self.device).synchronize()
         nbytes = max(arrow_workspace_bytes(self.h, k), 256)
         extra = -(-self.n * k * 4 // 256) * 256 if second else 0
+        self._ws_k = 0
         self._ws = None
         try:
             self._ws = torch.empty(nbytes + extra, dtype=torch.uint8, device=self.device)
@@ -445,8 +447,8 @@ class ArrowSpMM:
             if not extra:
                 raise
             self._ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-        self._ws_k = k
         arrow_set_workspace(self.h, self._ws.data_ptr(), self._ws.numel())
+        self._ws_k = k
 
     def levels(self):
         return [arrow_level_info(self.h, i) for i in range(self.info["levels"])]

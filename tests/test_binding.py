@@ -53,6 +53,64 @@ def test_a_second_buffer_is_asked_for_only_where_it_is_used(handle):
     assert extra == [-(-300 * 8 * 4 // 256) * 256, 0, -(-300 * 32 * 4 // 256) * 256]
 
 
+class Dense:
+    """What the general way asks of a tensor."""
+    is_cuda, dtype = True, torch.float32
+    def __init__(self, *shape): self.shape = shape
+    def dim(self): return len(self.shape)
+    def is_contiguous(self): return True
+    def numel(self): return int(np.prod(self.shape))
+    def data_ptr(self): return 4096
+
+
+def test_a_workspace_that_could_not_be_replaced_is_offered_to_no_call(handle, monkeypatch):
+    """The old one is given back before the new one is asked for, so a call after that has none, however few columns it
+    has: the native call must not be made with the old number of them, but the general way bind a new one."""
+    op, did = handle
+    offered, room = [], [1 << 40]
+    torch_empty = op._torch.empty
+
+    def empty(nbytes, dtype, device):
+        if nbytes > room[0]:
+            raise torch.OutOfMemoryError
+        return torch_empty(nbytes, dtype, device)
+
+    def native(name, most):                        # as in tensor_call.cpp: a call with more columns than `most` is not plain
+        def call(*args):
+            offered.append((name, args[most], op._ws is not None))
+            return 1 if args[-1].shape[-1] <= args[most] else 0
+        return call
+
+    op._torch.empty, op._torch.float32 = empty, torch.float32
+    op._call = types.SimpleNamespace(spmm=native("spmm", 4), sddmm=lambda *a: native("sddmm", 4)(*a[:-1]))
+    op._index, op._nnz, op._map, op.info, op._spmm, op._sddmm = 0, 300, object(), {"nnz": 300}, 0, 0
+    monkeypatch.setattr(binding, "_current_stream", lambda torch, device: 0)
+    monkeypatch.setattr(binding, "arrow_spmm", lambda h, x, y, k, stream: did.append(("spmm", k)))
+    monkeypatch.setattr(binding, "arrow_sddmm", lambda h, u, v, s, k, stream: did.append(("sddmm", k)))
+    X, wide, S = Dense(300, 8), Dense(300, 4096), Dense(300)
+    for call in (lambda: op.spmm(X, X), lambda: op.sddmm(X, X, S)):
+        op._ensure_workspace(8)
+        room[0] = 1 << 16
+        with pytest.raises(torch.OutOfMemoryError):
+            op.spmm(wide, wide)
+        room[0] = 1 << 40
+        del offered[:], did[:]
+        call()
+        assert offered[0][1:] == (0, False) and op._ws is not None and op._ws_k == 8
+        assert [d[0] for d in did[1:3]] == ["empty", "bind"] and did[-1][1] == 8
+        call()
+        assert offered[1][1:] == (8, True) and len(did) == 4
+        op._ws, op._ws_k = None, 0
+
+    def refused(h, ptr, nbytes):
+        raise binding.ArrowError(-1, "refused")
+
+    monkeypatch.setattr(binding, "arrow_set_workspace", refused)
+    with pytest.raises(binding.ArrowError):
+        op._ensure_workspace(8)
+    assert op._ws_k == 0
+
+
 @pytest.mark.parametrize("free", [1 << 40, 700_000])
 @pytest.mark.parametrize("R", [50, 64])
 def test_a_workspace_without_room_for_laid_out_factors_will_do(monkeypatch, R, free):
