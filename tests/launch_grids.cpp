@@ -1,0 +1,63 @@
+// Launches of the library recorded instead of made: HIP takes a grid dimension of fewer than 2^32 work items, and
+// operands that a card has room for must not be refused for the shape of a grid.  No device memory is touched, so the
+// pointers are made up.  `launch_grids <case>`; exit status 0 = accepted, and the grid holds all of the work.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <string>
+#include <vector>
+
+#include "arrow_internal.h"
+
+namespace {
+
+struct Launch { dim3 grid, block; uint64_t groups() const { return (uint64_t)grid.x * grid.y * grid.z; } };
+std::vector<Launch>& launches() { static std::vector<Launch> l; return l; }
+hipError_t last = hipSuccess;
+dim3 pushed_grid, pushed_block;
+
+}  // namespace
+
+extern "C" {
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t) { pushed_grid = grid; pushed_block = block; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hipStream_t* stream) {
+  *grid = pushed_grid; *block = pushed_block; *shared = 0; *stream = nullptr;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void**, size_t, hipStream_t) {
+  launches().push_back({grid, block});
+  const uint64_t items[3] = {(uint64_t)grid.x * block.x, (uint64_t)grid.y * block.y, (uint64_t)grid.z * block.z};
+  bool fits = grid.x > 0 && grid.y > 0 && grid.z > 0 && grid.y < 65536 && grid.z < 65536;
+  for (uint64_t n : items) fits = fits && n < 1ull << 32;
+  last = fits ? hipSuccess : hipErrorInvalidConfiguration;
+  return last;
+}
+hipError_t hipGetLastError() { const hipError_t e = last; last = hipSuccess; return e; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipGetDevice(int*) { return hipErrorNoDevice; }
+}
+
+namespace {
+
+float* address(int which) { return reinterpret_cast<float*>((uintptr_t)(which + 1) << 44); }
+
+// Chunks of long rows in window order, `slices` of them.
+int chunks(int64_t n, int32_t k, int32_t kc, int64_t n_chunks, uint64_t slices) {
+  arrow::ProductArgs a{};
+  a.X = a.Xh = address(0); a.Y = address(1); a.partials = address(2);
+  a.n_chunks = n_chunks; a.k = k;
+  const int rc = arrow::launch_product(a, arrow::kPartChunks, 0, 0, 0, false, true, n, kc, nullptr);
+  std::printf("rc %d, %zu launches, %u x %u groups\n", rc, launches().size(), launches()[0].grid.x, launches()[0].grid.y);
+  return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kChunksPerGroup >= (uint64_t)n_chunks * slices ? 0 : 1;
+}
+
+}  // namespace
+
+int main(int, char** argv) {
+  const std::string c = argv[1];
+  if (c == "chunks") return chunks(8 << 20, 1024, 64, 4400000, 16);
+  if (c == "chunks in narrow slices") return chunks(8 << 20, 512, 32, 4400000, 16);
+  if (c == "chunks, two sets of dies") return chunks(1 << 20, 128, 64, 16000000, 2);
+  return 2;
+}

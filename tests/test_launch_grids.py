@@ -1,0 +1,24 @@
+"""Grids of launches that no test has the memory for, recorded on the CPU (launch_grids.cpp) with the library as it was built."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2307_05740_amd import _build
+
+
+@pytest.fixture(scope="module")
+def launch_grids(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("launch_grids") / "launch_grids")
+    rocm = os.path.dirname(os.path.dirname(_build._hipcc()))
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"),
+                    "-I", os.path.join(_build.REPO_DIR, "include"), "-I", os.path.join(_build.PKG_DIR, "csrc"),
+                    os.path.join(_build.REPO_DIR, "tests", "launch_grids.cpp"), _build.ARROW_LIB,
+                    f"-Wl,-rpath,{_build.PKG_DIR}", "-L", os.path.join(rocm, "lib"), "-lamdhip64", "-o", out], check=True)
+    return out
+
+
+@pytest.mark.parametrize("case", ["chunks", "chunks in narrow slices", "chunks, two sets of dies"])
+def test_work_that_fits_a_card_fits_a_grid(launch_grids, case):
+    proc = subprocess.run([launch_grids, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
