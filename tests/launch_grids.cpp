@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "arrow.h"
 #include "arrow_internal.h"
 
 namespace {
@@ -52,6 +53,29 @@ int chunks(int64_t n, int32_t k, int32_t kc, int64_t n_chunks, uint64_t slices) 
   return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kChunksPerGroup >= (uint64_t)n_chunks * slices ? 0 : 1;
 }
 
+// A product in row order whose rows have so many columns that slices of 64 for all of its parts are too many for one grid.
+int short_rows() {
+  const int64_t n = 32768;
+  const int32_t k = 1 << 19;
+  std::vector<int64_t> ptr(n + 1, 0);
+  std::vector<int32_t> col;
+  for (int64_t i = 0; i < n; ++i) {
+    const int64_t entries = i < 64 ? 2048 : 3;
+    for (int64_t e = 0; e < entries; ++e) col.push_back((int32_t)((e * (n / entries) + i) % (n / entries) + e * (n / entries)));
+    ptr[i + 1] = (int64_t)col.size();
+  }
+  const std::vector<float> val(col.size(), 1.f);
+  arrow_handle* h = nullptr;
+  int rc = arrow_decompose(n, ptr.data(), col.data(), val.data(), 1024, &h);
+  if (rc == 0) rc = arrow_upload(h, address(0), arrow_device_bytes(h), nullptr);
+  if (rc == 0) rc = arrow_set_workspace(h, address(1), arrow_workspace_bytes(h, k));
+  if (rc == 0) rc = arrow_spmm(h, address(2), address(3), k, nullptr);
+  std::printf("rc %d (%s)\n", rc, arrow_last_error());
+  for (const Launch& l : launches()) std::printf("%u x %u groups\n", l.grid.x, l.grid.y);
+  arrow_destroy(h);
+  return rc == 0 ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int, char** argv) {
@@ -59,5 +83,6 @@ int main(int, char** argv) {
   if (c == "chunks") return chunks(8 << 20, 1024, 64, 4400000, 16);
   if (c == "chunks in narrow slices") return chunks(8 << 20, 512, 32, 4400000, 16);
   if (c == "chunks, two sets of dies") return chunks(1 << 20, 128, 64, 16000000, 2);
+  if (c == "short rows") return short_rows();
   return 2;
 }
