@@ -158,7 +158,6 @@ int check_hip(int rc, const char* what) {
 // k = 64, 80.1 -> 84.2 us.
 constexpr int64_t kEntriesOnce = 48 << 20;
 constexpr int64_t kSlicedShort = 256LL << 20;   // largest X that the cache behind the L2s has room for
-constexpr int64_t kMostGroups = (1LL << 24) - 1;   // workgroups of 256 in a dimension of a grid: HIP takes fewer than 2^32 work items
 constexpr int64_t kFewChunks = 2048;   // a list this short leaves wavefront slots empty
 constexpr int64_t kFewRows = 16384;    // and so does this one
 
@@ -210,7 +209,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
     // 636 / 638; Chung-Lu 700k, 128: 524 / 520; unequal ones (k = 96, Chung-Lu 250k, two sets of dies) 158 / 153.
     // (Where the narrower slices of all parts could take more workgroups than a grid: two launches.)
     int32_t short_kc = h->tuning.kc;
-    const bool fits = ((im.n_chunks + im.n_rows) / 4 + 4 * arrow::kDies) * (int64_t)(k / 32 + 1) <= kMostGroups;
+    const bool fits = ((im.n_chunks + im.n_rows) / 4 + 4 * arrow::kDies) * (int64_t)(k / 32 + 1) <= arrow::kMostGroups;
     if (short_kc == 0 && fits && im.n_chunks + im.piece_slots > 0 &&
         (im.row_major || (k % 64 == 0 && im.classes == 0 && (int64_t)h->n * k * (int64_t)sizeof(float) <= kSlicedShort)))
       short_kc = tune.kc;

@@ -69,6 +69,7 @@ constexpr int kChunksPerGroup = 4;   // wave-list items (one per wavefront) per 
 // INT32_MIN marks padding; partial slots end below both.
 constexpr int32_t kTeamDst = INT32_MIN + 1;
 constexpr int kItemsPerGroupBlock = 64;  // most group-list items per workgroup, and exactly that many of a die queue
+constexpr int64_t kMostGroups = (1LL << 24) - 1;   // workgroups of 256 in a dimension of a grid: HIP takes fewer than 2^32 work items
 constexpr int kDieRun = 256;         // consecutive wave-list workgroups that one die takes where the list has no die queues
 // head panels: kPanelRows head rows form a group; the group's head-block entries are dealt by column
 // class (staged head row mod kDies) to kDies workgroups, one per accelerator die, each keeping the

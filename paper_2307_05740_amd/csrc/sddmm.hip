@@ -364,6 +364,7 @@ int items_of(int64_t n, int lpr, bool unequal, bool window_rows) {
   const double want = std::sqrt((double)n) / per;
   int items = 2;
   while (items < most && (want > 1.414 * items || (!window_rows && n > kSampledGroups * items))) items *= 2;
+  while (items < kItemsPerGroupBlock && n > (kMostGroups - kDies) * items) items *= 2;   // (what a grid holds)
   return items;
 }
 

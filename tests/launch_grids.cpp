@@ -76,6 +76,16 @@ int short_rows() {
   return rc == 0 ? 0 : 1;
 }
 
+// Rows of dense blocks of a sampled product.
+int window_rows(int64_t n, int32_t k) {
+  arrow::SampledArgs a{};
+  a.U = address(0); a.V = a.Vh = address(1); a.S = address(2);
+  a.n_rows = n; a.k = k;
+  const int rc = arrow::launch_sddmm(a, true, false, true, false, n, nullptr);
+  std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
+  return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kItemsPerGroupBlock >= (uint64_t)n ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int, char** argv) {
@@ -84,5 +94,6 @@ int main(int, char** argv) {
   if (c == "chunks in narrow slices") return chunks(8 << 20, 512, 32, 4400000, 16);
   if (c == "chunks, two sets of dies") return chunks(1 << 20, 128, 64, 16000000, 2);
   if (c == "short rows") return short_rows();
+  if (c == "window rows") return window_rows(80000000, 128);
   return 2;
 }

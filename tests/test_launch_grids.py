@@ -18,7 +18,7 @@ def launch_grids(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["chunks", "chunks in narrow slices", "chunks, two sets of dies", "short rows"])
+@pytest.mark.parametrize("case", ["chunks", "chunks in narrow slices", "chunks, two sets of dies", "short rows", "window rows"])
 def test_work_that_fits_a_card_fits_a_grid(launch_grids, case):
     proc = subprocess.run([launch_grids, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
