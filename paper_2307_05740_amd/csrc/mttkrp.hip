@@ -313,15 +313,22 @@ __device__ __forceinline__ void resident_step(float4 (&acc)[2], float4 (&x)[2], 
 }
 
 constexpr int kResidentGroups = 256;     // workgroups: one per compute unit, which holds one window of rows
-constexpr int kResidentLong = 4096;      // steps of a wavefront from which on a third block on its way gains more than it costs at first
+// A third block on its way, four columns at a time: gains where both a wavefront's share and its items are long (two / three blocks, us, by
+// steps a wavefront and blocks an item: 6147, 24: 489.5 / 479.7; 5382, 42: 449.6 / 448.2), not in shorter shares (4075, 32: 343.7 / 343.9; 3074, 24: 255.7
+// / 258.0; 2691, 42: 250.2 / 255.3) or items (6647, 13: 477.6 / 480.3; 5973, 12: 420.1 / 423.6; 4725, 16: 337.0 / 338.0).
+constexpr int kResidentLong = 4096, kResidentLongItem = 20;
+// Blocks of an item on average from which on four of them are a chain of additions, below that two.  Error against 64 bits with two / four, 1e-7
+// of the norm: 13 blocks 0.99 / 1.04, 16 0.96 / 1.01, 24 1.02 / 1.05, 32 1.04 / 1.06, 42 1.08 / 1.07 and 1.12 / 1.08 (the other kernel, R = 12 / 64: 0.94 to 1.03 /
+// 0.97 to 1.38); four are up to 1 % faster.  By the image alone: a column of A does not depend on the number of columns.
+constexpr int kResidentChain = 32;
 
 // P: quads of columns of a workgroup, each in a plane of its own of all rows; UR: steps whose rows are read together; N: blocks
-// on their way.
+// on their way.  `chain`: blocks whose additions are a chain, a power of two.
 template <int P, int UR, int N>
 __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
     const ResidentItem* __restrict__ items, const ResidentBlock* __restrict__ blocks, int n_items,
     const float* __restrict__ B, int J, const float* __restrict__ C, int K, float* __restrict__ A,
-    float* __restrict__ partials, int R, int slices, int replicas) {
+    float* __restrict__ partials, int R, int slices, int replicas, uint32_t chain) {
   __shared__ float4 s_row[kCsfRowsInLds];
   const int per_die = gridDim.x / 8, q = (int)(blockIdx.x % 8) * per_die + (int)(blockIdx.x / 8);
   if (q >= slices * replicas) return;
@@ -347,9 +354,6 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
   const uint32_t plane = (uint32_t)rows * (uint32_t)sizeof(float4);
   constexpr int U = kCsfBlockSteps;
   static_assert(U == 8, "the steps of a block");
-  // Blocks whose additions are a chain.  Two: error against 64 bits 0.92 to 1.03e-7, with four 0.98 to 1.08e-7 and 1 % faster, which
-  // the long shares keep (the other kernel, R = 12 / 64: 0.94 to 1.03 / 0.97 to 1.38e-7).
-  constexpr uint32_t CHAIN = N > 2 ? 4 : 2;
   const uint32_t lane = threadIdx.x % 64;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
   const int workers = replicas * (kResidentBlock / 64);
@@ -422,13 +426,13 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
         }
       }
       fetch(h);
-      if (--d.blocks % CHAIN == 0) {                    // short chains of additions: as exact as the other kernel
+      if ((--d.blocks & (chain - 1)) == 0) {                    // short chains of additions: as exact as the other kernel
 #pragma unroll
         for (int e = 0; e < P; ++e) {
           vadd(part[e], acc[e]);
           acc[e] = vzero<4>();
         }
-        if (d.blocks % (4 * CHAIN) == 0) {
+        if ((d.blocks & (4 * chain - 1)) == 0) {
 #pragma unroll
           for (int e = 0; e < P; ++e) {
             vadd(sum[e], part[e]);
@@ -674,13 +678,14 @@ int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* block
     two = t.cost < s.cost;
     if (two) s = t;
   }
+  const uint32_t chain = n_blocks >= n_items * kResidentChain ? 4 : 2;
   const int64_t groups = ceil_div(s.slices * s.replicas, 8) * 8;
   if (groups > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
 #define ARROW_LAUNCH(...)                                                                                                  \
   hipLaunchKernelGGL((resident_kernel<__VA_ARGS__>), dim3((unsigned)groups), dim3(kResidentBlock), 0, (hipStream_t)stream, items, blocks, \
-                     (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)s.slices, (int)s.replicas)
+                     (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)s.slices, (int)s.replicas, chain)
   if (two) ARROW_LAUNCH(2, 1, 2);
-  else if (steps >= (double)(s.replicas * waves) * kResidentLong) ARROW_LAUNCH(1, 4, 3);
+  else if (steps >= (double)(s.replicas * waves) * kResidentLong && n_blocks >= n_items * kResidentLongItem) ARROW_LAUNCH(1, 4, 3);
   else ARROW_LAUNCH(1, 4, 2);
 #undef ARROW_LAUNCH
   return (int)hipGetLastError();

@@ -89,6 +89,26 @@ def test_few_items_with_factors_in_lds(torch, I, J, K, nnz, R):
     op.close()
 
 
+@pytest.mark.parametrize("I,J,K,nnz,ranks", [
+    (600, 3000, 3000, 3_000_000, (1024, 520)),      # items of 16 blocks, shares of a wavefront up to 4725 steps
+    (1100, 3000, 3000, 7_950_000, (512, 256)),      # 21 blocks, up to 5708 steps: a third block on its way at R = 512
+    (1100, 2000, 2000, 20_000_000, (128, 64))])     # items of 42 blocks; eight columns at a time at R = 128, four at R = 64
+def test_columns_do_not_depend_on_their_number(torch, I, J, K, nnz, ranks):
+    """With the factors in LDS and no slice in parts, the sums of a column are added in an order that the image alone decides."""
+    rng = np.random.default_rng(I)
+    i, j, k = (rng.integers(0, d, nnz).astype(np.int32) for d in (I, J, K))
+    v = rng.uniform(-1, 1, nnz).astype(np.float32)
+    B, C = synth.normal_matrix(J, ranks[0], seed=31), synth.normal_matrix(K, ranks[0], seed=32)
+    op, Bd, Cd, A = run(torch, (I, J, K), i, j, k, v, B, C)
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_FACTORS_IN_LDS and op.info["partials"] == 0
+    Aref, E = oracle.mttkrp((I, J, K), i, j, k, v, np.ascontiguousarray(B[:, :8]), np.ascontiguousarray(C[:, :8]))
+    assert_within(A[:, :8], Aref, E)
+    for R in (*ranks[1:], 8, 4, 1):
+        fewer = op.mttkrp(Bd[:, :R].contiguous(), Cd[:, :R].contiguous()).cpu().numpy()
+        assert np.array_equal(fewer.view(np.uint32), np.ascontiguousarray(A[:, :R]).view(np.uint32)), R
+    op.close()
+
+
 def test_unsorted_input_duplicates_and_long_fibre(torch):
     rng = np.random.default_rng(5)
     I, J, K, R = 40, 30, 700, 24
