@@ -323,12 +323,12 @@ constexpr int kResidentLong = 4096, kResidentLongItem = 20;
 constexpr int kResidentChain = 32;
 
 // P: quads of columns of a workgroup, each in a plane of its own of all rows; UR: steps whose rows are read together; N: blocks
-// on their way.  `chain`: blocks whose additions are a chain, a power of two.
-template <int P, int UR, int N>
+// on their way; CHAIN: blocks whose additions are a chain (as an argument of the launch it cost 4096^3 half a percent).
+template <int P, int UR, int N, uint32_t CHAIN>
 __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
     const ResidentItem* __restrict__ items, const ResidentBlock* __restrict__ blocks, int n_items,
     const float* __restrict__ B, int J, const float* __restrict__ C, int K, float* __restrict__ A,
-    float* __restrict__ partials, int R, int slices, int replicas, uint32_t chain) {
+    float* __restrict__ partials, int R, int slices, int replicas) {
   __shared__ float4 s_row[kCsfRowsInLds];
   const int per_die = gridDim.x / 8, q = (int)(blockIdx.x % 8) * per_die + (int)(blockIdx.x / 8);
   if (q >= slices * replicas) return;
@@ -426,13 +426,13 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
         }
       }
       fetch(h);
-      if ((--d.blocks & (chain - 1)) == 0) {                    // short chains of additions: as exact as the other kernel
+      if (--d.blocks % CHAIN == 0) {                    // short chains of additions: as exact as the other kernel
 #pragma unroll
         for (int e = 0; e < P; ++e) {
           vadd(part[e], acc[e]);
           acc[e] = vzero<4>();
         }
-        if ((d.blocks & (4 * chain - 1)) == 0) {
+        if (d.blocks % (4 * CHAIN) == 0) {
 #pragma unroll
           for (int e = 0; e < P; ++e) {
             vadd(sum[e], part[e]);
@@ -678,15 +678,18 @@ int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* block
     two = t.cost < s.cost;
     if (two) s = t;
   }
-  const uint32_t chain = n_blocks >= n_items * kResidentChain ? 4 : 2;
   const int64_t groups = ceil_div(s.slices * s.replicas, 8) * 8;
   if (groups > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-#define ARROW_LAUNCH(...)                                                                                                  \
-  hipLaunchKernelGGL((resident_kernel<__VA_ARGS__>), dim3((unsigned)groups), dim3(kResidentBlock), 0, (hipStream_t)stream, items, blocks, \
-                     (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)s.slices, (int)s.replicas, chain)
-  if (two) ARROW_LAUNCH(2, 1, 2);
-  else if (steps >= (double)(s.replicas * waves) * kResidentLong && n_blocks >= n_items * kResidentLongItem) ARROW_LAUNCH(1, 4, 3);
-  else ARROW_LAUNCH(1, 4, 2);
+#define ARROW_CHAIN(CHAIN, ...)                                                                                            \
+  hipLaunchKernelGGL((resident_kernel<__VA_ARGS__, CHAIN>), dim3((unsigned)groups), dim3(kResidentBlock), 0, (hipStream_t)stream, items, blocks, \
+                     (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)s.slices, (int)s.replicas)
+#define ARROW_LAUNCH(...) if (chain4) ARROW_CHAIN(4, __VA_ARGS__); else ARROW_CHAIN(2, __VA_ARGS__)
+  const bool chain4 = n_blocks >= n_items * kResidentChain;
+  const bool third = steps >= (double)(s.replicas * waves) * kResidentLong && n_blocks >= n_items * kResidentLongItem;
+  if (two) { ARROW_LAUNCH(2, 1, 2); }
+  else if (third) { ARROW_LAUNCH(1, 4, 3); }
+  else { ARROW_LAUNCH(1, 4, 2); }
+#undef ARROW_CHAIN
 #undef ARROW_LAUNCH
   return (int)hipGetLastError();
 }
