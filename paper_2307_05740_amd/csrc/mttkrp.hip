@@ -649,7 +649,10 @@ int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* block
   auto split = [&](int quads, double step, int64_t tail, double copied) {
     Split s{ceil_div(R, 4 * quads), 1, 0.0};
     double best = 0.0;
-    for (int64_t rounds = 1; rounds <= 4; ++rounds) {
+    // (more slices than four rounds hold: as many rounds as give each a workgroup.  Four / eight
+    // columns, us, 2000 x 1000 x 1000 of 1 M: R = 5120 1129 / 1150, 6144 1355 / 1156, 8192 1803 / 1538)
+    const int64_t most = std::max<int64_t>(4, ceil_div(s.slices, kResidentGroups));
+    for (int64_t rounds = 1; rounds <= most; ++rounds) {
       const int64_t n = kResidentGroups * rounds / s.slices;
       if (n < 1) continue;
       const double cost = (double)rounds * (steps / (double)n + copy);

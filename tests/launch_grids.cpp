@@ -86,6 +86,13 @@ int window_rows(int64_t n, int32_t k) {
   return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kItemsPerGroupBlock >= (uint64_t)n ? 0 : 1;
 }
 
+// The order-3 product with the factors in LDS, 2000 items of 2.75 blocks: `slices` of columns with `replicas` workgroups each.
+int factors_in_lds(int32_t R, uint32_t slices, uint32_t replicas) {
+  const int rc = arrow::launch_mttkrp_resident(nullptr, nullptr, 2000, 5500, address(0), 1000, address(1), 1000, address(2), address(3), R, nullptr);
+  std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
+  return rc == 0 && launches().size() == 1 && launches()[0].grid.x == (slices * replicas + 7) / 8 * 8 ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int, char** argv) {
@@ -95,5 +102,10 @@ int main(int, char** argv) {
   if (c == "chunks, two sets of dies") return chunks(1 << 20, 128, 64, 16000000, 2);
   if (c == "short rows") return short_rows();
   if (c == "window rows") return window_rows(80000000, 128);
+  // beyond 1024 slices of four columns: four columns, or eight where those take fewer rounds of workgroups
+  if (c == "factors in LDS, 4096 columns") return factors_in_lds(4096, 512, 1);
+  if (c == "factors in LDS, 5120 columns") return factors_in_lds(5120, 1280, 1);
+  if (c == "factors in LDS, 6144 columns") return factors_in_lds(6144, 768, 1);
+  if (c == "factors in LDS, 9000 columns") return factors_in_lds(9000, 1125, 1);
   return 2;
 }

@@ -361,10 +361,11 @@ def test_mttkrp_factors_in_lds(torch, I, J, K, nnz, R):
 
 @pytest.mark.parametrize("I,J,K,nnz,R", [
     (2000, 2549, 2550, 1_500_000, 57), (2000, 2549, 2551, 1_500_000, 57), (2100, 1500, 2000, 6_000_000, 8),
-    (2000, 900, 1200, 1_500_000, 16), (1300, 1100, 700, 1_200_000, 63), (1300, 1100, 700, 1_200_000, 64), (600, 4000, 1500, 3_000_000, 1024)])
+    (2000, 900, 1200, 1_500_000, 16), (1300, 1100, 700, 1_200_000, 63), (1300, 1100, 700, 1_200_000, 64), (600, 4000, 1500, 3_000_000, 1024),
+    (200, 900, 800, 200_000, 6145)])
 def test_mttkrp_factors_in_lds_eight_columns(torch, I, J, K, nnz, R):
-    """The same form where eight columns at a time take less (not in the second and the last case, whose rows do not fit so): up
-    to the last row that fits (J + K + 1 = 5100), ranks that are no multiple of eight; the last case has the longest shares of a wavefront."""
+    """The same form where eight columns at a time take less (not in the second and the last but one, whose rows do not fit so): up
+    to the last row that fits (J + K + 1 = 5100), ranks that are no multiple of eight, more slices of columns than four rounds of workgroups."""
     rng = np.random.default_rng(I + R)
     i, j, k = (rng.integers(0, d, nnz).astype(np.int32) for d in (I, J, K))
     i[:9000] = 1                                             # a slice of several items

@@ -1,4 +1,4 @@
-"""Grids of launches that no test has the memory for, recorded on the CPU (launch_grids.cpp) with the library as it was built."""
+"""Grids of launches that no test has the memory or the time for, recorded on the CPU (launch_grids.cpp) with the library as it was built."""
 import os
 import subprocess
 
@@ -21,4 +21,10 @@ def launch_grids(tmp_path_factory):
 @pytest.mark.parametrize("case", ["chunks", "chunks in narrow slices", "chunks, two sets of dies", "short rows", "window rows"])
 def test_work_that_fits_a_card_fits_a_grid(launch_grids, case):
     proc = subprocess.run([launch_grids, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
+
+
+@pytest.mark.parametrize("columns", [4096, 5120, 6144, 9000])
+def test_columns_of_a_slice_follow_their_cost_at_every_rank(launch_grids, columns):
+    proc = subprocess.run([launch_grids, f"factors in LDS, {columns} columns"], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
