@@ -84,10 +84,10 @@ def build_call() -> str:
     import torch
     root = os.path.dirname(torch.__file__)
     rocm_inc = os.path.join(os.path.dirname(os.path.dirname(_hipcc())), "include")
-    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", sysconfig.get_paths()["include"],
-          "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-          "-I", rocm_inc, os.path.join(PKG_DIR, "csrc", "tensor_call.cpp"), "-L", os.path.join(root, "lib"),
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", sysconfig.get_paths()["include"],
+          "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+          "-isystem", rocm_inc, os.path.join(PKG_DIR, "csrc", "tensor_call.cpp"), "-L", os.path.join(root, "lib"),
           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", CALL_LIB])
     return CALL_LIB
 
