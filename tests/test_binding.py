@@ -189,8 +189,8 @@ def test_products_that_share_a_workspace_follow_each_other(monkeypatch):
 
 
 def test_anything_but_plain_tensors_goes_the_general_way():
-    """The native calls take dense float32 tensors on the handle's device only; for everything else they call nothing and
-    say so, and the Python methods then assert and allocate as ever."""
+    """The native calls take tensors on the handle's device only; for everything else they call nothing and say so, and the
+    Python methods then assert and allocate as ever.  (What they ask of a tensor there: test_gpu_edges.py.)"""
     from paper_2307_05740_amd import tensor_call
     called = []
     product = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * 3, ctypes.c_int, ctypes.c_void_p)(lambda *a: called.append(a) or 0)

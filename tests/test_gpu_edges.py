@@ -571,9 +571,10 @@ def test_sampled_product_of_large_factors(torch, k, blocks):
 
 
 @pytest.mark.parametrize("n,k,kc,fuse", [(8192, 256, 0, 1), (17001, 128, 0, 1), (17001, 96, 0, 1), (17001, 160, 0, 0), (17001, 192, 0, 1),
-                                         (8192, 260, 0, 1), (17001, 128, 32, 0), (8192, 512, 0, 1), (17001, 150, 0, 1), (135000, 128, 0, 1)])
+                                         (8192, 260, 0, 1), (17001, 128, 32, 0), (8192, 512, 0, 1), (17001, 150, 0, 1), (135000, 128, 0, 1),
+                                         (8192, 320, 32, 1), (8192, 640, 0, 1), (135000, 320, 32, 1)])
 def test_column_slices_dealt_to_dies(torch, n, k, kc, fuse):
-    """Long, middle and short rows in two, three, four and eight column slices, equal and unequal ones, X on both sides of the
+    """Long, middle and short rows in two, three, four, eight and ten column slices, equal and unequal ones, X on both sides of the
     sizes from which on halves of the dies take halves of the slices; lists in row order and (more than 2^17 rows) in
     window order, whose workgroups fill several runs and a part of one.  Every element is written once per product."""
     rng = np.random.default_rng(n + k)
@@ -636,16 +637,20 @@ def test_what_the_python_methods_take_and_refuse(torch):
     wide = torch.cat([X, X], 1)                       # more columns than the workspace was bound for
     out = torch.empty_like(wide)
     assert torch.equal(op.spmm(wide, out)[:, 24:], out[:, :24])
-    side = torch.cuda.Stream()
+    side, late = torch.cuda.Stream(), torch.full_like(X, float("nan"))
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
-        op.spmm(X, Y.fill_(float("nan")))
+        torch.cuda._sleep(40_000_000)                 # (a call on another stream would find no values in `late`)
+        late.copy_(X)
+        op.spmm(late, Y.fill_(float("nan")))
+        op.sddmm(late, late, S.fill_(float("nan")))
     side.synchronize()
-    assert torch.equal(Y, general)
+    assert torch.equal(Y, general) and torch.equal(S, sampled)
     for x, y in ((X.double(), Y), (X, Y.double()), (X[:-1], Y[:-1]), (X, Y[:, :8]), (X.t().contiguous().t(), Y), (X.cpu(), Y), (X[0], Y[0])):
         with pytest.raises(AssertionError):
             op.spmm(x, y)
-    for u, v, s in ((X, X[:, :8], S), (X, X.double(), S), (X, X, S[:-1]), (X.cpu(), X, S), (X[:, ::2], X, S)):
+    for u, v, s in ((X, X[:, :8], S), (X, X.double(), S), (X, X, S[:-1]), (X.cpu(), X, S), (X[:, ::2], X, S),
+                    (X, wide[:, ::2], S), (X, X, torch.cat([S, S])[::2])):
         with pytest.raises(AssertionError):
             op.sddmm(u, v, s)
     with pytest.raises(binding.ArrowError):
@@ -657,7 +662,46 @@ def test_what_the_python_methods_take_and_refuse(torch):
     A = torch.empty(3, 6, device="cuda")
     ref = h.mttkrp(B, C)
     assert h.mttkrp(B, C, A) is A and torch.equal(A, ref)
-    for b, c, a in ((B[:-1], C, A), (B, C[:, :5], A), (B, C.double(), A), (B, C, A[:-1]), (B.cpu(), C, A)):
+    apart = lambda M: torch.cat([M, M], 1)[:, ::2]
+    for b, c, a in ((B[:-1], C, A), (B, C[:, :5], A), (B, C.double(), A), (B, C, A[:-1]), (B.cpu(), C, A), (B.double(), C, A), (B, C, A.double()),
+                    (apart(B), C, A), (B, apart(C), A), (B, C, apart(A))):
         with pytest.raises(AssertionError):
             h.mttkrp(b, c, a)
     h.close()
+
+
+def test_what_the_native_calls_hand_to_the_library(torch):
+    """Plain tensors: their addresses, the columns and the current stream.  Anything else in any place: no call."""
+    import ctypes
+    from paper_2307_05740_amd import tensor_call
+    called = []
+
+    def library(tensors):                             # a C function of a handle, so many addresses, the columns and a stream
+        return ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * (1 + tensors), ctypes.c_int, ctypes.c_void_p)(
+            lambda *a: called.append(a) or 0)
+
+    two, three = library(2), library(3)
+    at = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    dense = lambda *shape: torch.zeros(shape, device="cuda")
+    calls = [   # the call, its tensors
+        (lambda *t: tensor_call.spmm(at(two), 77, 0, 6, 8, *t), [dense(6, 8), dense(6, 8)]),
+        (lambda *t: tensor_call.sddmm(at(three), 77, 0, 6, 8, 5, *t), [dense(6, 8), dense(6, 8), dense(5)]),
+        (lambda *t: tensor_call.mttkrp(at(three), 77, 0, 3, 4, 5, 8, *t), [dense(4, 8), dense(5, 8), dense(3, 8)])]
+    side = torch.cuda.Stream()
+    for call, good in calls:
+        for stream in (torch.cuda.current_stream(), side):
+            with torch.cuda.stream(stream):
+                assert call(*good) == 1
+            assert called.pop() == (77, *[t.data_ptr() for t in good], 8, stream.cuda_stream or None) and not called
+        assert call(*[torch.nn.Parameter(t) for t in good]) == 1 and called.pop()
+        for place, t in enumerate(good):
+            others = [t.double(), t.half(), t.int(), t.cpu(), t.to("meta"), t.to_sparse(), t[:-1], torch.cat([t, t]), t[..., None],
+                      torch.cat([t, t], -1)[..., ::2], t.numpy(force=True), None, 1]
+            if t.dim() == 2:
+                others += [t.t().contiguous().t(), t[:, :4], t[0], torch.cat([t, t], 1)[:, :8], torch.cat([t, t], 1)]
+            for bad in others:
+                if t.dim() == 1 and bad is not None and getattr(bad, "shape", None) == (5, 1):
+                    continue                          # (the entries in any dense shape, as ever)
+                assert call(*[bad if q == place else g for q, g in enumerate(good)]) == 0, (place, bad)
+        assert call(*[torch.cat([t, t], 1) if t.dim() == 2 else t for t in good]) == 0   # more columns than the workspace has room for
+        assert not called

@@ -77,7 +77,7 @@ def test_all_ranks(torch, R):
 @pytest.mark.parametrize("I,J,K,nnz", [(144, 415, 1945, 116_000), (161, 1645, 160, 66_000), (128, 300, 200, 70_000), (520, 2549, 2550, 300_000)])
 def test_few_items_with_factors_in_lds(torch, I, J, K, nnz, R):
     """Fewer items than wavefronts of a column slice, down to the fewest and to the fewest entries, in the form with
-    the factors in LDS: every workgroup has some of them and none has more than its turn."""
+    the factors in LDS: workgroups without any at the lowest ranks, none with more than its turn."""
     rng = np.random.default_rng(I + R)
     i, j, k = (rng.integers(0, d, nnz).astype(np.int32) for d in (I, J, K))
     v = rng.uniform(-1, 1, nnz).astype(np.float32)
