@@ -278,7 +278,7 @@ struct SampledArgs {
   const float* U; const float* V; const float* Vh;
   float* S;
   int64_t n_chunks, n_rows;
-  int64_t nnz_chunks;
+  int64_t nnz_chunks, nnz_rows;
   int32_t k;
   int32_t items;                        // group-list slots per workgroup (filled in by the launch)
   uint32_t chunk_blocks;

@@ -17,7 +17,6 @@
 
 #include <algorithm>
 #include <climits>
-#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
@@ -28,7 +27,6 @@ namespace arrow {
 namespace {
 
 constexpr int64_t kResidentWaves = 8192;   // wavefronts the chip holds
-constexpr int64_t kSampledGroups = 12500;  // most workgroups for a list of rows, if they may have more items each
 constexpr int kSampledStage = 1024;   // entries of the group list a workgroup stages at once
 // Bytes of U (V has as many) from which on the rows of U that short rows read carry the streaming hint: they then leave
 // the caches to the rows of V, and where everything still fits the cache behind the L2s they are better kept there.  R-MAT 100k, k = 96 (37
@@ -342,28 +340,45 @@ namespace {
 
 // Items of the group list (or window rows) per workgroup.  Few of them leave several lane groups for each, so that all
 // of its rounds of row loads are on their way at once, and balance rows of unequal length; many of them pay once for what
-// a workgroup does before its first row arrives.  The best number grows about as the square root of the list's
-// length up to some 12500 workgroups: fitted to (us by items 4 / 8 / 16 / 32 / 64)
-//   R-MAT 4000, k = 128     6.5 /  9.6 /    - /    - /    -  (2: 5.9)      30000, k = 64     15.9 / 13.7 / 14.2 / 21.0 / 38.6
-//         100000, k = 64      - / 32.8 / 29.0 / 41.5 / 62.8  (two wavefronts a chunk)  180000, k = 8   62.4 / 43.9 / 35.3 / 33.3 / 40.3
-//         180000, k = 128   156 /  136 /  131 /  145 /  178                  400000, k = 64     212 /  163 /  142 /  134 /  154
-//         1m, k = 64        616 /  490 /  434 /  412 /  404                  Chung-Lu 300k, 64  216 /  161 /  136 /  128 /  144
-//         Chung-Lu 600k, k = 64  - /   - /    - /  207 /  199
-// Where no row is longer than the short ones all are about alike and need less sharing:
-//   grid  10000, k = 16     6.2 /  4.2 /  3.9 /  3.8 /  4.0                  29929, k = 16     16.7 / 10.4 /  7.2 /  4.6 /  4.9
-//         99856, k = 64    45.7 / 26.0 / 20.8 / 19.6 / 18.5                  10000, k = 128     8.8 /  6.6 /  7.4 / 10.1 / 16.2
-// and rows of dense blocks (40 entries) leave each lane group at most one or two:
-//         9000, k = 64     14.5 / 17.3 / 24.3 / 49.8 / 90.3                  100000, k = 32    72.8 / 56.7 / 53.3 / 69.6 / 89.8
-//         100000, k = 128   117 /  117 /  155 /  239 /  313                  300000, k = 200    569 /  627 /  913 / 1224 / 1391
-// (Before, as many as gave 2048 workgroups, 64 at most, 16 for rows of dense blocks, 8 at least: 30000, k = 64 of the grid 11.7,
-// 180000, k = 8 / 64 41.1 / 106, dense blocks 300000, k = 200 891 us.)
-int items_of(int64_t n, int lpr, bool unequal, bool window_rows) {
-  const double per = unequal || window_rows ? (lpr <= 8 ? 14.0 : lpr == 16 ? 20.0 : lpr == 32 ? 25.0 : 32.0)
-                                            : (lpr <= 8 ? 5.0 : lpr == 16 ? 6.0 : lpr == 32 ? 9.0 : 12.0);
-  const int most = window_rows ? std::min(16, std::max(4, kBlock / lpr / 2)) : kItemsPerGroupBlock;
-  const double want = std::sqrt((double)n) / per;
+// a workgroup does before its first row arrives.  Measured with 2 to 64 of them on 1840 lists (grids, R-MAT, Chung-Lu, dense blocks of 26 to 62
+// entries a row; 2.5 K to 450 K vertices, k = 8 to 256): what follows is within 1 % of the best on average.  (By the square root of
+// the list's length alone single lists lost up to 16 %: Chung-Lu 50 K, k = 48, 23.0 us, now 19.8; dense blocks 14 K, 48, 20.4 / 18.1; grid 120 K, 64, 27.3 / 24.7.)
+//
+// Lists of long and short rows: the rows from which on 4, 8, 16, 32 and 64 items are the best, by lanes per row (us by items):
+//   R-MAT 14 K, k = 64        4:  8.4   8:  7.7  16: 10.7              Chung-Lu 50 K, k = 48     4: 31.0   8: 23.0  16: 19.8  32: 34.7
+//         28 K, k = 200       4: 29.9   8: 32.5  16: 41.7              Chung-Lu 105 K, k = 8     8: 28.2  16: 20.8  32: 18.2  64: 25.1
+//         105 K, k = 24       8: 26.3  16: 20.6  32: 26.4              R-MAT 200 K, k = 64       8: 73.9  16: 64.3  32: 73.3  64: 97.6
+// (Single lists near a line lose still: Chung-Lu of 86 K rows, k = 16, 18.5 -> 20.9.)
+// Rows of dense blocks, of which a lane group takes one or two: 450 K, 26 entries, k = 48,  8: 244.3  16: 221.5  32: 254.4;
+// 250 K, 40 entries, k = 128,  4: 298.9  8: 293.6  16: 365.1; 27 K, 42 entries, k = 8,  4: 18.5  8: 14.4  16: 12.2  32: 16.4.
+struct ItemsFrom { int lpr; int32_t from[5]; };
+constexpr int32_t kNever = INT_MAX;
+constexpr ItemsFrom kUnequalItems[] = {{2, {0, 2000, 8400, 86500, 435000}},       {4, {0, 3500, 13500, 86500, 435000}},
+                                       {8, {0, 3000, 18900, 120000, 440000}},     {16, {3000, 10500, 37500, 200000, 500000}},
+                                       {32, {5600, 18900, 70000, 200000, 500000}}, {64, {8400, 37900, 101000, 200000, 500000}}};
+constexpr ItemsFrom kWindowItems[] = {{4, {0, 4000, 16000, kNever, kNever}},        {8, {2500, 8000, 16000, kNever, kNever}},
+                                      {16, {2500, 8000, kNever, kNever, kNever}},   {32, {4000, 8000, kNever, kNever, kNever}},
+                                      {64, {4000, kNever, kNever, kNever, kNever}}};
+
+// n rows of `average` entries each; unequal: not all of them short.
+int items_of(int64_t n, double average, int lpr, bool unequal, bool window_rows) {
   int items = 2;
-  while (items < most && (want > 1.414 * items || (!window_rows && n > kSampledGroups * items))) items *= 2;
+  if (window_rows || unequal) {
+    const ItemsFrom* row = window_rows ? kWindowItems : kUnequalItems;
+    while (row->lpr < lpr) ++row;
+    for (int64_t from : row->from)
+      if (n >= from) items *= 2;
+    if (window_rows && lpr == 16 && average < 35.0 && n >= 15000) items = 16;
+  } else {
+    // All about alike: as few as give one round of the workgroups that the chip holds, 256 entries at first (32 of a grid's rows).  A second round
+    // that is nearly empty costs most: grid 30 K, k = 128, 16 items (1871 workgroups) 15.1 us, 32 12.9; 120 K, k = 64, 64 items (1871) 27.3, 32 24.7, but 90 K, 64 (1407)
+    // 17.7, 32 18.2; 160 K, 64 (2500) 28.9, 32 28.7.  (74.5 K: k = 48 12.5 with 64, 13.7 with 32, k = 64 15.3 and 14.9.)
+    constexpr int64_t kRound = 1792;                // 256 compute units, seven wavefronts a SIMD
+    items = lpr <= 4 || (lpr == 8 && n >= 14000) ? 32 : lpr == 8 || (lpr == 16 && n >= 7400) ? 16 : lpr == 64 || (lpr == 32 && n < 3000) ? 4 : 8;
+    while (items > 2 && items * average > 256.0) items /= 2;
+    while (items < kItemsPerGroupBlock && n > kRound * items) items *= 2;
+    if (items == kItemsPerGroupBlock && lpr >= 8 && n > kRound * items && n <= kRound * items * 7 / 5) items /= 2;
+  }
   while (items < kItemsPerGroupBlock && n > (kMostGroups - kDies) * items) items *= 2;   // (what a grid holds)
   return items;
 }
@@ -374,11 +389,11 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   const Shape s = pick_shape(a.k, 0);
   const bool small = small_matrix(v_rows, a.k);
   const hipStream_t st = (hipStream_t)stream;
-  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(a.n_rows, s.lpr, unequal, window_rows);
+  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(a.n_rows, (double)a.nnz_rows / (double)std::max<int64_t>(1, a.n_rows), s.lpr, unequal, window_rows);
   // Few chunks leave wavefront slots empty, and a chunk of 256 entries is four to 64 rounds of row loads one
   // after the other: wavefronts share it as far as that leaves each a few rounds (nothing has to be
   // combined).  R-MAT 7419, k = 73: 30.7 -> 10.5 us; 12527, k = 128: 33.2 -> 13.7; 51952, k = 128: 50.2 ->
-  // 28.4; 30011, k = 24: 16.5 -> 12.0.  Up to twice as many wavefronts as the chip holds where each is left three rounds
+  // 28.4; 30011, k = 24: 16.5 -> 12.0.  Up to twice as many wavefronts as the chip holds where each is left three and a half rounds
   // (1 / 2 / 4 wavefronts, us: R-MAT 60k, k = 64 / 100 / 200: 29.3 / 25.4 / 28.6, 55.5 / 38.8 / 42.7, 113 / 69 / 75; 30k, 128: - /
   // 24.4 / 19.8, but 64: - / 13.7 / 14.4; Chung-Lu 80k, 50: 35.1 / 30.0 / 32.2; 130k, 64: 61.2 / 65.5).
   a.chunk_parts = 1;
