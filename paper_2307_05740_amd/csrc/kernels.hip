@@ -1322,10 +1322,12 @@ int launch_window(const WindowTile* tiles, int64_t n_tiles, int64_t max_span, in
   if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
   const bool small = small_matrix(x_rows, k);
   // A compute unit takes two workgroups where two windows fit it: one sums while the other waits for its window.  Of 16
-  // wavefronts each where a lane has one column (64 registers are enough for it; 512 tiles, k = 8 / 16: 59.6 -> 43.0, 61.1 -> 45.3
+  // wavefronts each where a lane has one column (of 64 registers it misses one or two, stored once and loaded once a row; 512 tiles, k = 8 / 16: 59.6 -> 43.0, 61.1 -> 45.3
   // us; 1367, 16: 130 -> 93), of 8 each where it has two, which pays from three a compute unit on (781 tiles, k = 24: 89.7 ->
-  // 86.6; 976, 20: 120.5 -> 114.1; 1953, 32: 184 -> 176; but 511, 32: 66.9 -> 71.3).
-  const bool half = max_span * (int64_t)width <= kWinFloatsHalf && (vec == 1 || (vec == 2 && n_tiles * slices * parts >= kWinHalfTiles));
+  // 86.6; 976, 20: 120.5 -> 114.1; 1953, 32: 184 -> 176; but 511, 32: 66.9 -> 71.3).  Where no die has more workgroups than compute units there is nothing
+  // for a second one (196 tiles, k = 8, 21.4 us in the large form, 22.3 in this one).
+  const bool shared = ceil_div(n_tiles, kDies) * slices * parts > kComputeUnits / kDies;
+  const bool half = shared && max_span * (int64_t)width <= kWinFloatsHalf && (vec == 1 || (vec == 2 && n_tiles * slices * parts >= kWinHalfTiles));
 #define ARROW_LAUNCH(VEC, SM, BLOCK, FLOATS)                                                                              \
   hipLaunchKernelGGL((window_kernel<VEC, SM, BLOCK, FLOATS>), dim3((unsigned)blocks), dim3(BLOCK), 0, (hipStream_t)stream, tiles, \
                      n_tiles, wrow_ptr, wrow_mid, wrow_y, entries, perm, X, Y, (int)k, width, slices, parts, accumulate ? 1 : 0)

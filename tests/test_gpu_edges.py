@@ -599,7 +599,7 @@ def test_column_slices_dealt_to_dies(torch, n, k, kc, fuse):
 
 
 @pytest.mark.parametrize("b,tiles,k", [(64, 800, 20), (64, 800, 33), (64, 70, 64), (512, 40, 32), (512, 70, 7), (100, 180, 128), (1100, 12, 16),
-                                       (1300, 12, 16), (512, 14, 141), (512, 3, 5)])
+                                       (1300, 12, 16), (512, 14, 141), (512, 3, 5), (64, 800, 7), (300, 270, 16)])
 @pytest.mark.parametrize("fuse", [0, 1])
 def test_windows_of_two_workgroups_and_shares_of_tiles(torch, b, tiles, k, fuse):
     """Windows of which a compute unit holds two (up to 1200 positions of 16 columns, 600 of 32 where there are many tiles)
