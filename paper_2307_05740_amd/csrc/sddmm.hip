@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
@@ -340,44 +341,47 @@ namespace {
 
 // Items of the group list (or window rows) per workgroup.  Few of them leave several lane groups for each, so that all
 // of its rounds of row loads are on their way at once, and balance rows of unequal length; many of them pay once for what
-// a workgroup does before its first row arrives.  Measured with 2 to 64 of them on 1840 lists (grids, R-MAT, Chung-Lu, dense blocks of 26 to 62
-// entries a row; 2.5 K to 450 K vertices, k = 8 to 256): what follows is within 1 % of the best on average.  (By the square root of
-// the list's length alone single lists lost up to 16 %: Chung-Lu 50 K, k = 48, 23.0 us, now 19.8; dense blocks 14 K, 48, 20.4 / 18.1; grid 120 K, 64, 27.3 / 24.7.)
+// a workgroup does before its first row arrives.  Measured with 2 to 64 of them on 2605 lists (grids, R-MAT, Chung-Lu, dense blocks of 26 to 62
+// entries a row; 1.5 K to 450 K vertices, k = 8 to 256): what follows is within 1 % of the best on average, 2 % for the widest equal rows.  (By the square
+// root of the list's length single lists lost up to 16 %: Chung-Lu 50 K, k = 48, 23.0 us, now 19.8; dense blocks 14 K, 48, 20.4 / 18.1; grid 120 K, 64, 27.3 / 24.7.)
 //
-// Lists of long and short rows: the rows from which on 4, 8, 16, 32 and 64 items are the best, by lanes per row (us by items):
+// Lists of long and short rows: the root of rows times entries from which on 4, 8, 16, 32 and 64 items are the best, by lanes per row (rows alone put R-MAT
+// and Chung-Lu, whose short rows are longer, on the wrong side of some line by up to 13 %).  us by items:
 //   R-MAT 14 K, k = 64        4:  8.4   8:  7.7  16: 10.7              Chung-Lu 50 K, k = 48     4: 31.0   8: 23.0  16: 19.8  32: 34.7
 //         28 K, k = 200       4: 29.9   8: 32.5  16: 41.7              Chung-Lu 105 K, k = 8     8: 28.2  16: 20.8  32: 18.2  64: 25.1
 //         105 K, k = 24       8: 26.3  16: 20.6  32: 26.4              R-MAT 200 K, k = 64       8: 73.9  16: 64.3  32: 73.3  64: 97.6
-// (Single lists near a line lose still: Chung-Lu of 86 K rows, k = 16, 18.5 -> 20.9.)
-// Rows of dense blocks, of which a lane group takes one or two: 450 K, 26 entries, k = 48,  8: 244.3  16: 221.5  32: 254.4;
+// Rows of dense blocks, of which a lane group takes one or two, by rows: 450 K, 26 entries, k = 48,  8: 244.3  16: 221.5  32: 254.4;
 // 250 K, 40 entries, k = 128,  4: 298.9  8: 293.6  16: 365.1; 27 K, 42 entries, k = 8,  4: 18.5  8: 14.4  16: 12.2  32: 16.4.
-struct ItemsFrom { int lpr; int32_t from[5]; };
-constexpr int32_t kNever = INT_MAX;
-constexpr ItemsFrom kUnequalItems[] = {{2, {0, 2000, 8400, 86500, 435000}},       {4, {0, 3500, 13500, 86500, 435000}},
-                                       {8, {0, 3000, 18900, 120000, 440000}},     {16, {3000, 10500, 37500, 200000, 500000}},
-                                       {32, {5600, 18900, 70000, 200000, 500000}}, {64, {8400, 37900, 101000, 200000, 500000}}};
+struct ItemsFrom { int lpr; double from[5]; };
+constexpr double kNever = 1e18;
+constexpr ItemsFrom kUnequalItems[] = {{2, {0, 5800, 21400, 226000, 909000}},       {4, {0, 12100, 31400, 186000, 909000}},
+                                       {8, {0, 7900, 50000, 253000, 962000}},       {16, {8700, 25900, 90700, 498000, 1090000}},
+                                       {32, {13500, 44800, 156000, 498000, 1090000}}, {64, {21400, 90700, 226000, 720000, kNever}}};
 constexpr ItemsFrom kWindowItems[] = {{4, {0, 4000, 16000, kNever, kNever}},        {8, {2500, 8000, 16000, kNever, kNever}},
                                       {16, {2500, 8000, kNever, kNever, kNever}},   {32, {4000, 8000, kNever, kNever, kNever}},
                                       {64, {4000, kNever, kNever, kNever, kNever}}};
 
-// n rows of `average` entries each; unequal: not all of them short.
-int items_of(int64_t n, double average, int lpr, bool unequal, bool window_rows) {
+// n rows with nnz entries; unequal: not all of them short.
+int items_of(int64_t n, int64_t nnz, int lpr, bool unequal, bool window_rows) {
+  const double average = (double)nnz / (double)std::max<int64_t>(1, n);
   int items = 2;
   if (window_rows || unequal) {
     const ItemsFrom* row = window_rows ? kWindowItems : kUnequalItems;
     while (row->lpr < lpr) ++row;
-    for (int64_t from : row->from)
-      if (n >= from) items *= 2;
+    for (double from : row->from)
+      if ((window_rows ? (double)n : std::sqrt((double)n * (double)nnz)) >= from) items *= 2;
     if (window_rows && lpr == 16 && average < 35.0 && n >= 15000) items = 16;
   } else {
-    // All about alike: as few as give one round of the workgroups that the chip holds, 256 entries at first (32 of a grid's rows).  A second round
-    // that is nearly empty costs most: grid 30 K, k = 128, 16 items (1871 workgroups) 15.1 us, 32 12.9; 120 K, k = 64, 64 items (1871) 27.3, 32 24.7, but 90 K, 64 (1407)
-    // 17.7, 32 18.2; 160 K, 64 (2500) 28.9, 32 28.7.  (74.5 K: k = 48 12.5 with 64, 13.7 with 32, k = 64 15.3 and 14.9.)
+    // All about alike: as few as give one round of the workgroups that the chip holds, 256 entries at first (32 of a grid's rows) and 64 items at most, 32
+    // of the widest rows.  A second round that is nearly empty costs most: grid 30 K, k = 128, 16 items (1871 workgroups) 15.1 us, 32 12.9; 120 K, k = 64, 64 items (1871)
+    // 27.3, 32 24.7, but 90 K, 64 (1407) 17.6, 32 18.2; 200 K, 64 (3123) 33.7, 32 35.1; 60 K, k = 150, 32 (1861) 35.2, 16 31.0.  (74.5 K: k = 48 12.5 with 64, 13.7 with
+    // 32, k = 64 15.9 and 14.9.)
     constexpr int64_t kRound = 1792;                // 256 compute units, seven wavefronts a SIMD
+    const int most = lpr == 64 ? kItemsPerGroupBlock / 2 : kItemsPerGroupBlock;
     items = lpr <= 4 || (lpr == 8 && n >= 14000) ? 32 : lpr == 8 || (lpr == 16 && n >= 7400) ? 16 : lpr == 64 || (lpr == 32 && n < 3000) ? 4 : 8;
     while (items > 2 && items * average > 256.0) items /= 2;
-    while (items < kItemsPerGroupBlock && n > kRound * items) items *= 2;
-    if (items == kItemsPerGroupBlock && lpr >= 8 && n > kRound * items && n <= kRound * items * 7 / 5) items /= 2;
+    while (items < most && n > kRound * items) items *= 2;
+    if (items == most && lpr >= 8 && n > kRound * items && n <= kRound * items * 7 / 5) items /= 2;
   }
   while (items < kItemsPerGroupBlock && n > (kMostGroups - kDies) * items) items *= 2;   // (what a grid holds)
   return items;
@@ -389,7 +393,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   const Shape s = pick_shape(a.k, 0);
   const bool small = small_matrix(v_rows, a.k);
   const hipStream_t st = (hipStream_t)stream;
-  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(a.n_rows, (double)a.nnz_rows / (double)std::max<int64_t>(1, a.n_rows), s.lpr, unequal, window_rows);
+  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(a.n_rows, a.nnz_rows, s.lpr, unequal, window_rows);
   // Few chunks leave wavefront slots empty, and a chunk of 256 entries is four to 64 rounds of row loads one
   // after the other: wavefronts share it as far as that leaves each a few rounds (nothing has to be
   // combined).  R-MAT 7419, k = 73: 30.7 -> 10.5 us; 12527, k = 128: 33.2 -> 13.7; 51952, k = 128: 50.2 ->
