@@ -400,14 +400,20 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   // 28.4; 30011, k = 24: 16.5 -> 12.0.  Up to twice as many wavefronts as the chip holds where each is left three and a half rounds
   // (1 / 2 / 4 wavefronts, us: R-MAT 60k, k = 64 / 100 / 200: 29.3 / 25.4 / 28.6, 55.5 / 38.8 / 42.7, 113 / 69 / 75; 30k, 128: - /
   // 24.4 / 19.8, but 64: - / 13.7 / 14.4; Chung-Lu 80k, 50: 35.1 / 30.0 / 32.2; 130k, 64: 61.2 / 65.5).
+  // Beyond 1.3 times what it holds six rounds, where short rows of much the same weight are in the launch to fill the slots (as they were / shared
+  // further, Chung-Lu 60k, k = 96: 31.5 / 35.2; 20k, 200: 28.0 / 30.1; but 75k, 150, 8.5 rounds: 57.5 / 55.2; R-MAT 30k, 150, few short rows: 47.3 / 31.0).
   a.chunk_parts = 1;
   const uint32_t most = s.lpr < 4 ? 1u : (s.lpr < 8 ? 2u : (uint32_t)s.lpr / 4);
-  const int64_t rounds = 7 * (64 / s.lpr) * kSampledBatch / 2;
+  const int64_t round = 64 / s.lpr * kSampledBatch;  // entries
+  const bool filled = a.nnz_rows * 5 >= a.nnz_chunks * 3;
   if (!window_rows && !windows && !die_queues)
-    while (a.chunk_parts < most && (a.n_chunks * a.chunk_parts * 2 <= kResidentWaves ||
-                                    (a.n_chunks * a.chunk_parts * 2 <= 2 * kResidentWaves &&
-                                     a.nnz_chunks >= a.n_chunks * a.chunk_parts * 2 * rounds)))
+    while (a.chunk_parts < most) {
+      const int64_t waves = a.n_chunks * a.chunk_parts * 2;
+      const bool few = waves <= kResidentWaves || (waves <= 2 * kResidentWaves && 2 * a.nnz_chunks >= 7 * round * waves &&
+                                                   (!filled || 10 * waves <= 13 * kResidentWaves || a.nnz_chunks >= 6 * round * waves));
+      if (!few) break;
       a.chunk_parts *= 2;
+    }
   const int64_t chunk_blocks = ceil_div(ceil_div(a.n_chunks * a.chunk_parts, kBlock / 64), kDies) * kDies;
   const int64_t row_blocks = ceil_div(ceil_div(a.n_rows, a.items), kDies) * kDies;
   if (chunk_blocks + row_blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
