@@ -86,6 +86,16 @@ int window_rows(int64_t n, int32_t k) {
   return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kItemsPerGroupBlock >= (uint64_t)n ? 0 : 1;
 }
 
+// Rows of a sampled product that are all alike, five entries each: `groups` workgroups.
+int equal_rows(int64_t n, int32_t k, uint32_t groups) {
+  arrow::SampledArgs a{};
+  a.U = address(0); a.V = a.Vh = address(1); a.S = address(2);
+  a.n_rows = n; a.nnz_rows = 5 * n; a.k = k;
+  const int rc = arrow::launch_sddmm(a, false, false, false, false, n, nullptr);
+  std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
+  return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
+}
+
 // The order-3 product with the factors in LDS, 2000 items of 2.75 blocks: `slices` of columns with `replicas` workgroups each.
 int factors_in_lds(int32_t R, uint32_t slices, uint32_t replicas) {
   const int rc = arrow::launch_mttkrp_resident(nullptr, nullptr, 2000, 5500, address(0), 1000, address(1), 1000, address(2), address(3), R, nullptr);
@@ -102,6 +112,11 @@ int main(int, char** argv) {
   if (c == "chunks, two sets of dies") return chunks(1 << 20, 128, 64, 16000000, 2);
   if (c == "short rows") return short_rows();
   if (c == "window rows") return window_rows(80000000, 128);
+  // one round of 1792 workgroups, then two rather than one and a little, then what 64 items give
+  if (c == "equal rows, one round") return equal_rows(114688, 64, 1792);
+  if (c == "equal rows, a row more") return equal_rows(114689, 64, 3592);
+  if (c == "equal rows, two fifths more") return equal_rows(160600, 64, 2512);
+  if (c == "equal rows, the widest") return equal_rows(250000, 192, 7816);
   // beyond 1024 slices of four columns: four columns, or eight where those take fewer rounds of workgroups
   if (c == "factors in LDS, 4096 columns") return factors_in_lds(4096, 512, 1);
   if (c == "factors in LDS, 5120 columns") return factors_in_lds(5120, 1280, 1);

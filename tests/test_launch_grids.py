@@ -28,3 +28,9 @@ def test_work_that_fits_a_card_fits_a_grid(launch_grids, case):
 def test_columns_of_a_slice_follow_their_cost_at_every_rank(launch_grids, columns):
     proc = subprocess.run([launch_grids, f"factors in LDS, {columns} columns"], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
+
+
+@pytest.mark.parametrize("case", ["one round", "a row more", "two fifths more", "the widest"])
+def test_equal_rows_fill_rounds_of_workgroups(launch_grids, case):
+    proc = subprocess.run([launch_grids, "equal rows, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
