@@ -90,21 +90,19 @@ constexpr int64_t kResidentItems = 128;
 constexpr double kResidentFill = 1.8;
 // And every workgroup copies all J + K rows, which has to be paid for by the rows that are read, entries and segments,
 // where they are so many that eight columns of them do not fit the LDS (below that nothing was lost down to 30 rows read per row
-// copied).  The rank is not known here; 32 gains least (whole lines for the other form, and all compute units copy).  Measured with
-// four columns and leftover items in the first workgroups (us, R = 8 / 32 /
-// 64 / 128; in brackets rows read per row copied, geometric mean over those ranks and 12, 24, 50 and 100 where
-// they were measured):
-//   520 x 9000 x 1000 of 560 K [109, +17 %]       9.8 / 12.2 / 16.9 / 31.2 -> 10.7 / 17.0 / 20.5 / 32.1
-//   600 x 1000 x 9100 of 500 K  [83, +18 %]       9.9 / 11.7 / 15.5 / 30.7 ->  8.8 / 18.1 / 21.2 / 31.4
-//   783 x 1736 x 7090 of 806 K [160, -3 %]        R = 32 +27 %, 64 +16 %, 12 -27 %
-//   785 x 8113 x 1294 of 1.2 M [246, -17 %]      15.4 / 20.2 / 30.9 / 60.4 -> 13.0 / 22.4 / 31.3 / 48.0
-//   3000 x 2525 x 7575 of 1.2 M [228, -4 %]      16.8 / 20.5 / 31.6 / 63.7 -> 10.5 / 25.7 / 39.4 / 67.0
-//   757 x 1673 x 3882 of 874 K [271, -17 %]       R = 32 +5 %, 64 -9 %, 12 -37 %
-//   3000 x 2525 x 7575 of 2.5 M [455, -26 %]     28.0 / 34.6 / 55.4 / 114  -> 15.8 / 32.7 / 51.7 / 90.1
-// so from 200 on, where they all gain on average (700 x 9000 x 1000 of 1.25 M [240]: 15.1 / 20.5 / 32.4 / 62.5 -> 13.8 / 24.5 /
-// 29.5 / 47.5).  From 400 on rank 32 would lose 7 % at most, but others would give up as much as 45 %.  Where there is hardly more than an
-// item per wavefront the other form is not filled either, and the first 2600 rows are free: 299 x 503 x 3305 of 371 K [134] and
-// 340 x 830 x 1821 of 229 K [146] gain 5 to 37 % at every rank; 520 x 5000 x 5000 of 600 K [114, +8 %] and of 1.2 M [216, -5 %].
+// copied).  The rank is not known here; 32 gains least (whole lines for the other form, and all compute units copy).  us, R = 8 / 32 /
+// 64 / 128; in brackets rows read per row copied, geometric mean over those ranks and 12, 24, 50 and 100:
+//   600 x 1000 x 9100 of 500 K  [83,  -6 %]       9.8 / 11.4 / 15.2 / 30.4 ->  7.2 / 15.0 / 17.4 / 26.7
+//   520 x 9000 x 1000 of 560 K [109,  -8 %]       9.7 / 12.2 / 16.7 / 30.9 ->  7.0 / 15.8 / 18.7 / 28.5
+//   783 x 1736 x 7090 of 806 K [160, -20 %]      11.7 / 14.0 / 20.4 / 38.3 ->  7.4 / 15.1 / 19.4 / 30.6
+//   3000 x 2525 x 7575 of 1.2 M [229, -27 %]     17.0 / 20.4 / 32.1 / 64.6 ->  7.9 / 21.1 / 30.1 / 50.4
+//   785 x 8113 x 1294 of 1.2 M [244, -35 %]      15.7 / 20.0 / 31.2 / 59.5 ->  8.3 / 18.3 / 24.5 / 39.0
+//   757 x 1673 x 3882 of 874 K [271, -32 %]      11.9 / 14.9 / 21.1 / 35.6 ->  7.3 / 12.4 / 16.5 / 26.9
+//   3000 x 2525 x 7575 of 2.5 M [458, -42 %]     28.1 / 34.6 / 55.7 / 115  -> 11.8 / 27.7 / 41.2 / 73.2
+// so from 200 on, where rank 32 loses 9 % at most; below that the others gain on average but it loses up to a third (24, 50, 100 at [109]: 13.6 / 18.7 /
+// 29.6 -> 12.1 / 18.5 / 24.5).  Where there is hardly more than an item per wavefront the other form is not filled either, and the first 2600 rows are
+// free: 299 x 503 x 3305 of 371 K [134, -34 %] gains at every rank, 520 x 5000 x 5000 of 600 K [114], 900 K [166] and 1.2 M [216] 14, 22 and 26 %
+// on average (R = 32: 13.0 / 15.0 / 18.0 -> 16.3 / 18.2 / 19.7).
 constexpr int64_t kResidentReuse = 200, kResidentFew = 640, kResidentFree = 2600;
 constexpr int64_t kResidentSegs = 4096;    // segments of an item
 // Lanes whose 16-byte reads of LDS are served together (found by timing reads whose rows lie in different banks
