@@ -402,6 +402,8 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   // 24.4 / 19.8, but 64: - / 13.7 / 14.4; Chung-Lu 80k, 50: 35.1 / 30.0 / 32.2; 130k, 64: 61.2 / 65.5).
   // Beyond 1.3 times what it holds six rounds, where short rows of much the same weight are in the launch to fill the slots (as they were / shared
   // further, Chung-Lu 60k, k = 96: 31.5 / 35.2; 20k, 200: 28.0 / 30.1; but 75k, 150, 8.5 rounds: 57.5 / 55.2; R-MAT 30k, 150, few short rows: 47.3 / 31.0).
+  // Four wavefronts where a row takes eight lanes: R-MAT 30k, k = 24, 3369 chunks, 10.2 -> 11.8, 20k 6.9 -> 7.4; they would gain where there are fewer than some
+  // 1000 chunks (9k 6.7 -> 5.3); two with the next round on its way 10.2.
   a.chunk_parts = 1;
   const uint32_t most = s.lpr < 4 ? 1u : (s.lpr < 8 ? 2u : (uint32_t)s.lpr / 4);
   const int64_t round = 64 / s.lpr * kSampledBatch;  // entries
