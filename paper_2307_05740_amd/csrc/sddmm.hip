@@ -404,6 +404,10 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   // further, Chung-Lu 60k, k = 96: 31.5 / 35.2; 20k, 200: 28.0 / 30.1; but 75k, 150, 8.5 rounds: 57.5 / 55.2; R-MAT 30k, 150, few short rows: 47.3 / 31.0).
   // Four wavefronts where a row takes eight lanes: R-MAT 30k, k = 24, 3369 chunks, 10.2 -> 11.8, 20k 6.9 -> 7.4; they would gain where there are fewer than some
   // 1000 chunks (9k 6.7 -> 5.3); two with the next round on its way 10.2.
+  // Chunks that are one strip each (rows of 49 to 64 entries, as dense blocks leave them) are alike and leave nothing to even out: a list of them that
+  // fills half of the chip is not shared, and its widest rows run without the next round on its way (shared / not / nor ahead; 58 or 62 entries a row:
+  // 14k, k = 200, 52.9 / 49.5 / 48.4, 20k, 150, 61.6 / 59.4 / 56.1, 20k, 256, 82.4 / 80.1 / 74.4 us, 14k, 40, not shared before either, 17.4 / 16.8, but 28k, 64, 36.5 / 37.2).
+  const bool single = a.nnz_chunks <= 64 * a.n_chunks;
   a.chunk_parts = 1;
   const uint32_t most = s.lpr < 4 ? 1u : (s.lpr < 8 ? 2u : (uint32_t)s.lpr / 4);
   const int64_t round = 64 / s.lpr * kSampledBatch;  // entries
@@ -411,7 +415,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   if (!window_rows && !windows && !die_queues)
     while (a.chunk_parts < most) {
       const int64_t waves = a.n_chunks * a.chunk_parts * 2;
-      const bool few = waves <= kResidentWaves || (waves <= 2 * kResidentWaves && 2 * a.nnz_chunks >= 7 * round * waves &&
+      const bool few = waves <= kResidentWaves || (!single && waves <= 2 * kResidentWaves && 2 * a.nnz_chunks >= 7 * round * waves &&
                                                    (!filled || 10 * waves <= 13 * kResidentWaves || a.nnz_chunks >= 6 * round * waves));
       if (!few) break;
       a.chunk_parts *= 2;
@@ -433,7 +437,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
       else if (row_blocks > 0) { ARROW_LAUNCH(sddmm_rows_kernel, row_blocks, ARROW_COMMA true ARROW_COMMA false); }
     } else if (!windows && chunk_blocks > 0) {
       a.chunk_blocks = (uint32_t)chunk_blocks;
-      if (a.chunk_parts == 1) { ARROW_LAUNCH(sddmm_kernel, chunk_blocks + row_blocks, ARROW_COMMA true); }
+      if (a.chunk_parts == 1 && !(single && s.lpr >= 32)) { ARROW_LAUNCH(sddmm_kernel, chunk_blocks + row_blocks, ARROW_COMMA true); }
       else { ARROW_LAUNCH(sddmm_kernel, chunk_blocks + row_blocks, ARROW_COMMA false); }
     } else {
       if (chunk_blocks > 0) { ARROW_LAUNCH(sddmm_chunks_kernel, chunk_blocks, ); }

@@ -96,6 +96,16 @@ int equal_rows(int64_t n, int32_t k, uint32_t groups) {
   return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
 }
 
+// Chunks of long rows of a sampled product, in row order: `groups` workgroups of four wavefronts.
+int sampled_chunks(int64_t n_chunks, int64_t nnz, int32_t k, uint32_t groups) {
+  arrow::SampledArgs a{};
+  a.U = address(0); a.V = a.Vh = address(1); a.S = address(2);
+  a.n_chunks = n_chunks; a.nnz_chunks = nnz; a.k = k;
+  const int rc = arrow::launch_sddmm(a, false, false, false, false, 20000, nullptr);
+  std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
+  return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
+}
+
 // The order-3 product with the factors in LDS, 2000 items of 2.75 blocks: `slices` of columns with `replicas` workgroups each.
 int factors_in_lds(int32_t R, uint32_t slices, uint32_t replicas) {
   const int rc = arrow::launch_mttkrp_resident(nullptr, nullptr, 2000, 5500, address(0), 1000, address(1), 1000, address(2), address(3), R, nullptr);
@@ -117,6 +127,10 @@ int main(int, char** argv) {
   if (c == "equal rows, a row more") return equal_rows(114689, 64, 3592);
   if (c == "equal rows, two fifths more") return equal_rows(160600, 64, 2512);
   if (c == "equal rows, the widest") return equal_rows(250000, 192, 7816);
+  // a wavefront each, or two where chunks are more than a strip, or four where they leave the chip half empty
+  if (c == "chunks of a strip") return sampled_chunks(5000, 5000 * 64, 200, 1256);
+  if (c == "chunks of a strip and more") return sampled_chunks(5000, 5000 * 64 + 1, 200, 2504);
+  if (c == "chunks of a strip, few") return sampled_chunks(2000, 2000 * 56, 200, 2000);
   // beyond 1024 slices of four columns: four columns, or eight where those take fewer rounds of workgroups
   if (c == "factors in LDS, 4096 columns") return factors_in_lds(4096, 512, 1);
   if (c == "factors in LDS, 5120 columns") return factors_in_lds(5120, 1280, 1);

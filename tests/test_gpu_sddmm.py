@@ -340,3 +340,23 @@ def test_chunks_of_a_wavefront_each(torch, k):
     op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), S)
     op.close()
     assert_within(S.cpu().numpy(), *oracle.sddmm(rowptr, colidx, vals, U, V))
+
+
+@pytest.mark.parametrize("k", [50, 100, 130, 256, 257])
+def test_chunks_of_one_strip(torch, k):
+    """More than 4096 chunks of 49 to 64 entries: a wavefront each, without the next round on its way in the widest rows."""
+    n = 5003
+    rng = np.random.default_rng(k)
+    length = rng.integers(49, 65, n)
+    col = [np.sort(rng.choice(n, m, replace=False)) for m in length]
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    colidx = np.concatenate(col).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    U, V = synth.normal_matrix(n, k, seed=30), synth.normal_matrix(n, k, seed=31)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, 300)
+    level = op.levels()[0]
+    assert 4096 < level["chunks"] < 8192 and level["nnz_chunks"] <= 64 * level["chunks"]
+    S = torch.full((len(colidx),), float("nan"), device="cuda")
+    op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), S)
+    op.close()
+    assert_within(S.cpu().numpy(), *oracle.sddmm(rowptr, colidx, vals, U, V))

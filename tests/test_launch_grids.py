@@ -34,3 +34,9 @@ def test_columns_of_a_slice_follow_their_cost_at_every_rank(launch_grids, column
 def test_equal_rows_fill_rounds_of_workgroups(launch_grids, case):
     proc = subprocess.run([launch_grids, "equal rows, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
+
+
+@pytest.mark.parametrize("case", ["chunks of a strip", "chunks of a strip and more", "chunks of a strip, few"])
+def test_chunks_of_one_strip_are_not_shared_further(launch_grids, case):
+    proc = subprocess.run([launch_grids, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
