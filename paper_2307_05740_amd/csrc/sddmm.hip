@@ -371,6 +371,10 @@ int items_of(int64_t n, int64_t nnz, int lpr, bool unequal, bool window_rows) {
     for (double from : row->from)
       if ((window_rows ? (double)n : std::sqrt((double)n * (double)nnz)) >= from) items *= 2;
     if (window_rows && lpr == 16 && average < 35.0 && n >= 15000) items = 16;
+    // (Eight long rows of 32 lanes to a workgroup are one to one and a half rounds of the 1536 workgroups that the chip holds of them: the second round is
+    // mostly empty.  k = 128, us, 4 / 8 items: 54 entries, 9.4 K rows 31.9 / 30.2, 14.0 K 41.0 / 42.9, 16.5 K 49.4 / 53.8; 62, 19.0 K 58.5 / 64.0; 46, 15.1 K
+    // 39.6 / 42.0, 23.4 K 38.2 / 37.3; 36, 19.4 K 31.0 / 31.4; 26, 21.4 K 29.2 / 27.8.)
+    if (window_rows && lpr == 32 && average >= 40.0 && n > 8 * 1536 && n <= 8 * 1536 * 8 / 5) items = 4;
   } else {
     // All about alike: as few as give one round of the workgroups that the chip holds, 256 entries at first (32 of a grid's rows) and 64 items at most, 32
     // of the widest rows.  A second round that is nearly empty costs most: grid 30 K, k = 128, 16 items (1871 workgroups) 15.1 us, 32 12.9; 120 K, k = 64, 64 items (1871)

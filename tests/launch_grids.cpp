@@ -76,14 +76,15 @@ int short_rows() {
   return rc == 0 ? 0 : 1;
 }
 
-// Rows of dense blocks of a sampled product.
-int window_rows(int64_t n, int32_t k) {
+// Rows of dense blocks of a sampled product: `groups` workgroups, if given.
+int window_rows(int64_t n, int32_t k, int64_t nnz = 0, uint32_t groups = 0) {
   arrow::SampledArgs a{};
   a.U = address(0); a.V = a.Vh = address(1); a.S = address(2);
-  a.n_rows = n; a.k = k;
+  a.n_rows = n; a.nnz_rows = nnz; a.k = k;
   const int rc = arrow::launch_sddmm(a, true, false, true, false, n, nullptr);
   std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
-  return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kItemsPerGroupBlock >= (uint64_t)n ? 0 : 1;
+  return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kItemsPerGroupBlock >= (uint64_t)n &&
+         (groups == 0 || launches()[0].grid.x == groups) ? 0 : 1;
 }
 
 // Rows of a sampled product that are all alike, five entries each: `groups` workgroups.
@@ -122,6 +123,11 @@ int main(int, char** argv) {
   if (c == "chunks, two sets of dies") return chunks(1 << 20, 128, 64, 16000000, 2);
   if (c == "short rows") return short_rows();
   if (c == "window rows") return window_rows(80000000, 128);
+  // one round of 1536 workgroups of eight rows, then half as many rows each, then eight again; shorter rows eight always
+  if (c == "window rows, one round") return window_rows(12288, 128, 12288 * 50, 1536);
+  if (c == "window rows, a row more") return window_rows(12289, 128, 12289 * 50, 3080);
+  if (c == "window rows, three fifths more") return window_rows(19661, 128, 19661 * 50, 2464);
+  if (c == "window rows, short") return window_rows(12289, 128, 12289 * 39, 1544);
   // one round of 1792 workgroups, then two rather than one and a little, then what 64 items give
   if (c == "equal rows, one round") return equal_rows(114688, 64, 1792);
   if (c == "equal rows, a row more") return equal_rows(114689, 64, 3592);

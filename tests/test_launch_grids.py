@@ -40,3 +40,9 @@ def test_equal_rows_fill_rounds_of_workgroups(launch_grids, case):
 def test_chunks_of_one_strip_are_not_shared_further(launch_grids, case):
     proc = subprocess.run([launch_grids, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
+
+
+@pytest.mark.parametrize("case", ["one round", "a row more", "three fifths more", "short"])
+def test_rows_of_dense_blocks_fill_rounds_of_workgroups(launch_grids, case):
+    proc = subprocess.run([launch_grids, "window rows, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
