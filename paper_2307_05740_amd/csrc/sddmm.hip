@@ -361,8 +361,8 @@ constexpr ItemsFrom kWindowItems[] = {{4, {0, 4000, 16000, kNever, kNever}},    
                                       {16, {2500, 8000, kNever, kNever, kNever}},   {32, {4000, 8000, kNever, kNever, kNever}},
                                       {64, {4000, kNever, kNever, kNever, kNever}}};
 
-// n rows with nnz entries; unequal: not all of them short.
-int items_of(int64_t n, int64_t nnz, int lpr, bool unequal, bool window_rows) {
+// n rows with nnz entries; unequal: not all of them short; chunks: behind some of those.
+int items_of(int64_t n, int64_t nnz, int lpr, bool unequal, bool window_rows, bool chunks) {
   const double average = (double)nnz / (double)std::max<int64_t>(1, n);
   int items = 2;
   if (window_rows || unequal) {
@@ -370,6 +370,10 @@ int items_of(int64_t n, int64_t nnz, int lpr, bool unequal, bool window_rows) {
     while (row->lpr < lpr) ++row;
     for (double from : row->from)
       if ((window_rows ? (double)n : std::sqrt((double)n * (double)nnz)) >= from) items *= 2;
+    // (What dense blocks leave beside their tiles are rows of 30 to 48 entries.  Behind chunks they end the launch, and two of the widest are better for longer: k = 256,
+    // us, 2 / 4 items, 12 K vertices of 50 entries 43.6 / 46.4, 14 K 52.1 / 55.3, 20 K 66.8 / 69.9, 24 K (root 39 K) 78.3 / 82.2; k = 150, 14 K, 44.4 / 45.2, 12 K 37.4 /
+    // 36.8; but without chunks k = 150, 14 K of 46 entries 42.2 / 40.3, 17 K of 36 40.8 / 38.9.)
+    if (chunks && lpr == 64 && average >= 32.0 && items == 4 && std::sqrt((double)n * (double)nnz) < 45000.0) items = 2;
     if (window_rows && lpr == 16 && average < 35.0 && n >= 15000) items = 16;
     // (Eight long rows of 32 lanes to a workgroup are one to one and a half rounds of the 1536 workgroups that the chip holds of them: the second round is
     // mostly empty.  k = 128, us, 4 / 8 items: 54 entries, 9.4 K rows 31.9 / 30.2, 14.0 K 41.0 / 42.9, 16.5 K 49.4 / 53.8; 62, 19.0 K 58.5 / 64.0; 46, 15.1 K
@@ -397,7 +401,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   const Shape s = pick_shape(a.k, 0);
   const bool small = small_matrix(v_rows, a.k);
   const hipStream_t st = (hipStream_t)stream;
-  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(a.n_rows, a.nnz_rows, s.lpr, unequal, window_rows);
+  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(a.n_rows, a.nnz_rows, s.lpr, unequal, window_rows, a.n_chunks > 0);
   // Few chunks leave wavefront slots empty, and a chunk of 256 entries is four to 64 rounds of row loads one
   // after the other: wavefronts share it as far as that leaves each a few rounds (nothing has to be
   // combined).  R-MAT 7419, k = 73: 30.7 -> 10.5 us; 12527, k = 128: 33.2 -> 13.7; 51952, k = 128: 50.2 ->

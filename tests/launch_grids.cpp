@@ -97,6 +97,16 @@ int equal_rows(int64_t n, int32_t k, uint32_t groups) {
   return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
 }
 
+// Rows of a sampled product that are not all short, `groups` workgroups of them, behind some chunks.
+int unequal_rows(int64_t n, int64_t nnz, int32_t k, uint32_t groups, int64_t n_chunks) {
+  arrow::SampledArgs a{};
+  a.U = address(0); a.V = a.Vh = address(1); a.S = address(2);
+  a.n_rows = n; a.nnz_rows = nnz; a.n_chunks = n_chunks; a.nnz_chunks = 50 * n_chunks; a.k = k;
+  const int rc = arrow::launch_sddmm(a, false, false, false, true, n, nullptr);
+  std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
+  return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
+}
+
 // Chunks of long rows of a sampled product, in row order: `groups` workgroups of four wavefronts.
 int sampled_chunks(int64_t n_chunks, int64_t nnz, int32_t k, uint32_t groups) {
   arrow::SampledArgs a{};
@@ -133,6 +143,11 @@ int main(int, char** argv) {
   if (c == "equal rows, a row more") return equal_rows(114689, 64, 3592);
   if (c == "equal rows, two fifths more") return equal_rows(160600, 64, 2512);
   if (c == "equal rows, the widest") return equal_rows(250000, 192, 7816);
+  // two of the widest to a workgroup behind chunks (32 of these, which 16 wavefronts share), or four where they are many, shorter or alone
+  if (c == "unequal rows, long") return unequal_rows(6000, 6000 * 45, 200, 128 + 3000, 32);
+  if (c == "unequal rows, many") return unequal_rows(6800, 6800 * 45, 200, 128 + 1704, 32);
+  if (c == "unequal rows, short") return unequal_rows(16000, 16000 * 8, 200, 128 + 4000, 32);
+  if (c == "unequal rows, alone") return unequal_rows(6000, 6000 * 45, 200, 1504, 0);
   // a wavefront each, or two where chunks are more than a strip, or four where they leave the chip half empty
   if (c == "chunks of a strip") return sampled_chunks(5000, 5000 * 64, 200, 1256);
   if (c == "chunks of a strip and more") return sampled_chunks(5000, 5000 * 64 + 1, 200, 2504);

@@ -46,3 +46,9 @@ def test_chunks_of_one_strip_are_not_shared_further(launch_grids, case):
 def test_rows_of_dense_blocks_fill_rounds_of_workgroups(launch_grids, case):
     proc = subprocess.run([launch_grids, "window rows, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
+
+
+@pytest.mark.parametrize("case", ["long", "many", "short", "alone"])
+def test_long_rows_behind_chunks_are_two_to_a_workgroup(launch_grids, case):
+    proc = subprocess.run([launch_grids, "unequal rows, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
