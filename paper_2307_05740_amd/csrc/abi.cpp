@@ -311,7 +311,8 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
       a.chunk_ptr = at<uint32_t>(h, im.off_chunk_ptr); a.chunk_mid = at<uint32_t>(h, im.off_chunk_mid);
       a.chunk_row = at<int32_t>(h, im.off_chunk_row); a.n_chunks = im.n_chunks; a.nnz_chunks = im.nnz_chunks;
       a.rows_ptr = at<uint32_t>(h, im.off_rows_ptr); a.rows_mid = at<uint32_t>(h, im.off_rows_mid);
-      a.rows_row = at<int32_t>(h, im.off_rows_row); a.n_rows = im.n_rows; a.nnz_rows = im.nnz_rows;
+      a.rows_row = at<int32_t>(h, im.off_rows_row); a.n_rows = im.n_rows - im.empty_slots; a.nnz_rows = im.nnz_rows;
+      a.n_pieces = im.piece_slots;
       a.ent = ent; a.emap = emap; a.U = U; a.V = V; a.Vh = Vh; a.S = S; a.k = k;
       auto launch = [&](arrow::SampledArgs args, bool window_rows) -> int {
         if (args.n_chunks == 0 && args.n_rows == 0) return ARROW_OK;
@@ -322,6 +323,7 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
       if (h->profiling) {                 // the lists apart, so that each has a time of its own
         arrow::SampledArgs c = a, r = a;
         c.n_rows = 0;
+        c.n_pieces = 0;
         r.n_chunks = 0;
         if (c.n_chunks > 0) { Scoped sc(h, kChunks, (int)li, stream); rc = launch(c, false); }
         if (!rc && r.n_rows > 0) { Scoped sc(h, kRows, (int)li, stream); rc = launch(r, false); }
@@ -331,7 +333,7 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
       if (rc) return rc;
       if (im.n_wrows > 0) {
         Scoped sc(h, kWindow, (int)li, stream);
-        a.n_chunks = 0; a.n_rows = im.n_wrows; a.nnz_rows = im.nnz_w;
+        a.n_chunks = a.n_pieces = 0; a.n_rows = im.n_wrows; a.nnz_rows = im.nnz_w;
         a.rows_ptr = at<uint32_t>(h, im.off_wrow_ptr); a.rows_mid = at<uint32_t>(h, im.off_wrow_mid);
         a.rows_row = at<int32_t>(h, im.off_wrow_y); a.rows_win = at<uint32_t>(h, im.off_wrow_win);
         a.perm = at<int32_t>(h, im.off_perm);

@@ -277,10 +277,14 @@ struct SampledArgs {
   const Entry* ent; const uint32_t* emap;
   const float* U; const float* V; const float* Vh;
   float* S;
-  int64_t n_chunks, n_rows;
+  int64_t n_chunks, n_rows;             // (rows without entries, the last ones of a group list, are left out)
+  int64_t n_pieces;                     // the first n_pieces of the rows are pieces of long rows
   int64_t nnz_chunks, nnz_rows;
   int32_t k;
-  int32_t items;                        // group-list slots per workgroup (filled in by the launch)
+  int32_t items;                        // group-list slots per workgroup (filled in by the launch),
+  int32_t piece_items;                  // ... of the pieces,
+  uint32_t piece_blocks;                // ... which have the first of the workgroups of the rows; the short rows'
+  uint32_t short_base;                  // ... begin at item id * items + short_base (mod 2^32)
   uint32_t chunk_blocks;
   int32_t runs;                         // as in ProductArgs
 };

@@ -183,6 +183,15 @@ __device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const 
   }
 }
 
+// Which items the id-th workgroup of the rows has: pieces first.  (In 32 bits, n is below 2^31; with 64 grids of 500 K vertices took 1 % longer.)
+struct ItemRange { uint32_t first; int n; };
+__device__ __forceinline__ ItemRange items_at(const SampledArgs& a, uint32_t id) {
+  const bool piece = id < a.piece_blocks;
+  const uint32_t items = (uint32_t)(piece ? a.piece_items : a.items), end = (uint32_t)(piece ? a.n_pieces : a.n_rows);
+  const uint32_t first = id * items + (piece ? 0u : a.short_base);
+  return {first, first < end ? (int)(end - first < items ? end - first : items) : 0};
+}
+
 // Items [first, first + n_it) of the group list (WINDOW false: entries before `mid` read the staged head
 // Vh, the rest rows of V) or of the window-row list (WINDOW true: entries before `mid` name rows of V, the
 // rest positions inside the row's tile window, translated through perm).  The workgroup copies the items'
@@ -307,9 +316,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_chunks_kernel(const SampledArgs 
 template <int VEC, int LPR, int NB, bool SMALL, bool WINDOW, bool ONCE>
 __global__ __launch_bounds__(kBlock) void sddmm_rows_kernel(const SampledArgs a) {
   __shared__ SampledShared sh;
-  const int64_t first = (int64_t)blockIdx.x * a.items;
-  const int n_it = a.n_rows - first < a.items ? (int)(a.n_rows - first) : a.items;
-  if (n_it > 0) sampled_rows<VEC, LPR, NB, SMALL, WINDOW, ONCE>(sh, a, first, n_it);
+  const ItemRange it = items_at(a, blockIdx.x);
+  if (it.n > 0) sampled_rows<VEC, LPR, NB, SMALL, WINDOW, ONCE>(sh, a, it.first, it.n);
 }
 
 // Both lists in one launch (short lists: the second launch would be most of the time).  AHEAD: see sampled_chunk.
@@ -330,9 +338,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SampledArgs a) {
       sampled_chunk<VEC, LPR, NB, SMALL, AHEAD>(sh.chunk.ents[wave], sh.chunk.ats[wave], a, ch, slot % a.chunk_parts);
     return;
   }
-  const int64_t first = (int64_t)(blockIdx.x - a.chunk_blocks) * a.items;
-  const int n_it = a.n_rows - first < a.items ? (int)(a.n_rows - first) : a.items;
-  if (n_it > 0) sampled_rows<VEC, LPR, NB, SMALL, false, false>(sh.rows, a, first, n_it);
+  const ItemRange it = items_at(a, blockIdx.x - a.chunk_blocks);
+  if (it.n > 0) sampled_rows<VEC, LPR, NB, SMALL, false, false>(sh.rows, a, it.first, it.n);
 }
 
 }  // namespace
@@ -345,40 +352,56 @@ namespace {
 // entries a row; 1.5 K to 450 K vertices, k = 8 to 256): what follows is within 1 % of the best on average, 2 % for the widest equal rows.  (By the square
 // root of the list's length single lists lost up to 16 %: Chung-Lu 50 K, k = 48, 23.0 us, now 19.8; dense blocks 14 K, 48, 20.4 / 18.1; grid 120 K, 64, 27.3 / 24.7.)
 //
-// Lists of long and short rows: the root of rows times entries from which on 4, 8, 16, 32 and 64 items are the best, by lanes per row (rows alone put R-MAT
-// and Chung-Lu, whose short rows are longer, on the wrong side of some line by up to 13 %).  us by items:
-//   R-MAT 14 K, k = 64        4:  8.4   8:  7.7  16: 10.7              Chung-Lu 50 K, k = 48     4: 31.0   8: 23.0  16: 19.8  32: 34.7
-//         28 K, k = 200       4: 29.9   8: 32.5  16: 41.7              Chung-Lu 105 K, k = 8     8: 28.2  16: 20.8  32: 18.2  64: 25.1
-//         105 K, k = 24       8: 26.3  16: 20.6  32: 26.4              R-MAT 200 K, k = 64       8: 73.9  16: 64.3  32: 73.3  64: 97.6
+// Short rows behind pieces of long ones, which are several times as long: the two have workgroups of their own, by the number of each from which on 4, 8, 16, 32 and
+// 64 short rows and 2, 4, 8 and 16 pieces are the best, by lanes per row.  (One number for both, by the root of rows times entries, let the first workgroups,
+// which are all pieces, end the launch, or gave short rows more workgroups than the chip holds beside the chunks: R-MAT 30 K, k = 24, started them after 3 to 6 of 11 us.
+// 441 lists of 3 K to 1.5 M vertices, R-MAT and Chung-Lu, at five ranks each, rows without entries left out: 0.96 times the time on average, within 1 % of the
+// best numbers.  us before / now: R-MAT 30 K, k = 24, 10.9 / 9.5; 6 K, 96, 6.1 / 5.5; 14 K, 43, 8.8 / 8.0; 70 K, 66, 45.8 / 44.0; 1.5 M, 20, 364.5 / 356.3; Chung-Lu 25 K, 37,
+// 12.4 / 10.8; 67 K, 32, 17.7 / 16.9.)  Wider lists of more than 131072 vertices gain less than they scatter (Chung-Lu 540 K, k = 64, 175.8 us, apart 178.2) and
+// lists of more pieces than short rows lose (dense blocks, 12 K vertices of 44 entries, k = 128, 23.9 us, apart 27.3; 17 K, 43, 65, 24.9 and 28.1): one number for both, as it was.
 // Rows of dense blocks, of which a lane group takes one or two, by rows: 450 K, 26 entries, k = 48,  8: 244.3  16: 221.5  32: 254.4;
 // 250 K, 40 entries, k = 128,  4: 298.9  8: 293.6  16: 365.1; 27 K, 42 entries, k = 8,  4: 18.5  8: 14.4  16: 12.2  32: 16.4.
-struct ItemsFrom { int lpr; double from[5]; };
+struct ItemsFrom { int lpr; double from[5]; };      // ... items at least from[0], from[1], ... rows
 constexpr double kNever = 1e18;
 constexpr ItemsFrom kUnequalItems[] = {{2, {0, 5800, 21400, 226000, 909000}},       {4, {0, 12100, 31400, 186000, 909000}},
                                        {8, {0, 7900, 50000, 253000, 962000}},       {16, {8700, 25900, 90700, 498000, 1090000}},
                                        {32, {13500, 44800, 156000, 498000, 1090000}}, {64, {21400, 90700, 226000, 720000, kNever}}};
+constexpr ItemsFrom kShortItems[] = {{2, {0, 1700, 5500, 17500, 49500}},            {4, {0, 1700, 1900, 10800, 70000}},
+                                     {8, {0, 1800, 1900, 17800, 60000}},            {16, {0, 2000, 10400, 40800, 145000}},
+                                     {32, {0, 5600, 15500, 90000, 690000}},         {64, {0, 20000, 46000, 263000, kNever}}};
+constexpr ItemsFrom kPieceItems[] = {{2, {0, 3900, 4800, 6000, kNever}},            {4, {0, 900, 1450, 3400, kNever}},
+                                     {8, {0, 300, 1100, 4000, kNever}},             {16, {0, 950, 2500, 11000, kNever}},
+                                     {32, {0, 1200, 3600, 8600, kNever}},           {64, {0, 2400, 20000, kNever, kNever}}};
 constexpr ItemsFrom kWindowItems[] = {{4, {0, 4000, 16000, kNever, kNever}},        {8, {2500, 8000, 16000, kNever, kNever}},
                                       {16, {2500, 8000, kNever, kNever, kNever}},   {32, {4000, 8000, kNever, kNever, kNever}},
                                       {64, {4000, kNever, kNever, kNever, kNever}}};
 
-// n rows with nnz entries; unequal: not all of them short; chunks: behind some of those.
-int items_of(int64_t n, int64_t nnz, int lpr, bool unequal, bool window_rows, bool chunks) {
+int items_from(const ItemsFrom* row, int least, int lpr, double n) {
+  while (row->lpr < lpr) ++row;
+  int items = least / 2;
+  for (double from : row->from)
+    if (n >= from) items *= 2;
+  return items;
+}
+
+// Of a list of n rows with nnz entries: rows of dense blocks, long and short rows, pieces of long rows, short rows behind those, or rows that are all alike.  chunks: behind some of those.
+enum class Rows { kWindow, kUnequal, kPieces, kShort, kAlike };
+int items_of(int64_t n, int64_t nnz, int lpr, Rows rows, bool chunks) {
   const double average = (double)nnz / (double)std::max<int64_t>(1, n);
-  int items = 2;
-  if (window_rows || unequal) {
-    const ItemsFrom* row = window_rows ? kWindowItems : kUnequalItems;
-    while (row->lpr < lpr) ++row;
-    for (double from : row->from)
-      if ((window_rows ? (double)n : std::sqrt((double)n * (double)nnz)) >= from) items *= 2;
+  int items;
+  if (rows != Rows::kAlike) {
+    items = rows == Rows::kPieces    ? items_from(kPieceItems, 2, lpr, (double)n)
+            : rows == Rows::kUnequal ? items_from(kUnequalItems, 4, lpr, std::sqrt((double)n * (double)nnz))
+                                     : items_from(rows == Rows::kWindow ? kWindowItems : kShortItems, 4, lpr, (double)n);
     // (What dense blocks leave beside their tiles are rows of 30 to 48 entries.  Behind chunks they end the launch, and two of the widest are better for longer: k = 256,
     // us, 2 / 4 items, 12 K vertices of 50 entries 43.6 / 46.4, 14 K 52.1 / 55.3, 20 K 66.8 / 69.9, 24 K (root 39 K) 78.3 / 82.2; k = 150, 14 K, 44.4 / 45.2, 12 K 37.4 /
     // 36.8; but without chunks k = 150, 14 K of 46 entries 42.2 / 40.3, 17 K of 36 40.8 / 38.9.)
-    if (chunks && lpr == 64 && average >= 32.0 && items == 4 && std::sqrt((double)n * (double)nnz) < 45000.0) items = 2;
-    if (window_rows && lpr == 16 && average < 35.0 && n >= 15000) items = 16;
+    if ((rows == Rows::kWindow || rows == Rows::kUnequal) && chunks && lpr == 64 && average >= 32.0 && items == 4 && std::sqrt((double)n * (double)nnz) < 45000.0) items = 2;
+    if (rows == Rows::kWindow && lpr == 16 && average < 35.0 && n >= 15000) items = 16;
     // (Eight long rows of 32 lanes to a workgroup are one to one and a half rounds of the 1536 workgroups that the chip holds of them: the second round is
     // mostly empty.  k = 128, us, 4 / 8 items: 54 entries, 9.4 K rows 31.9 / 30.2, 14.0 K 41.0 / 42.9, 16.5 K 49.4 / 53.8; 62, 19.0 K 58.5 / 64.0; 46, 15.1 K
     // 39.6 / 42.0, 23.4 K 38.2 / 37.3; 36, 19.4 K 31.0 / 31.4; 26, 21.4 K 29.2 / 27.8.)
-    if (window_rows && lpr == 32 && average >= 40.0 && n > 8 * 1536 && n <= 8 * 1536 * 8 / 5) items = 4;
+    if (rows == Rows::kWindow && lpr == 32 && average >= 40.0 && n > 8 * 1536 && n <= 8 * 1536 * 8 / 5) items = 4;
   } else {
     // All about alike: as few as give one round of the workgroups that the chip holds, 256 entries at first (32 of a grid's rows) and 64 items at most, 32
     // of the widest rows.  A second round that is nearly empty costs most: grid 30 K, k = 128, 16 items (1871 workgroups) 15.1 us, 32 12.9; 120 K, k = 64, 64 items (1871)
@@ -401,7 +424,11 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   const Shape s = pick_shape(a.k, 0);
   const bool small = small_matrix(v_rows, a.k);
   const hipStream_t st = (hipStream_t)stream;
-  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(a.n_rows, a.nnz_rows, s.lpr, unequal, window_rows, a.n_chunks > 0);
+  if (window_rows || die_queues || (windows && s.lpr >= 16) || 2 * a.n_pieces > a.n_rows) a.n_pieces = 0;
+  const Rows rows = window_rows ? Rows::kWindow : a.n_pieces > 0 ? Rows::kShort : unequal ? Rows::kUnequal : Rows::kAlike;
+  const int64_t n_short = a.n_rows - a.n_pieces;
+  a.piece_items = items_of(a.n_pieces, a.nnz_rows, s.lpr, Rows::kPieces, a.n_chunks > 0);
+  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(n_short, a.nnz_rows, s.lpr, rows, a.n_chunks > 0);
   // Few chunks leave wavefront slots empty, and a chunk of 256 entries is four to 64 rounds of row loads one
   // after the other: wavefronts share it as far as that leaves each a few rounds (nothing has to be
   // combined).  R-MAT 7419, k = 73: 30.7 -> 10.5 us; 12527, k = 128: 33.2 -> 13.7; 51952, k = 128: 50.2 ->
@@ -429,7 +456,10 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
       a.chunk_parts *= 2;
     }
   const int64_t chunk_blocks = ceil_div(ceil_div(a.n_chunks * a.chunk_parts, kBlock / 64), kDies) * kDies;
-  const int64_t row_blocks = ceil_div(ceil_div(a.n_rows, a.items), kDies) * kDies;
+  const int64_t piece_blocks = ceil_div(ceil_div(a.n_pieces, a.piece_items), kDies) * kDies;
+  const int64_t row_blocks = piece_blocks + ceil_div(ceil_div(n_short, a.items), kDies) * kDies;
+  a.piece_blocks = (uint32_t)piece_blocks;
+  a.short_base = (uint32_t)a.n_pieces - a.piece_blocks * (uint32_t)a.items;
   if (chunk_blocks + row_blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
   a.runs = windows && !die_queues;
   const bool once = v_rows * a.k * (int64_t)sizeof(float) >= kSampledOnce;

@@ -107,6 +107,16 @@ int unequal_rows(int64_t n, int64_t nnz, int32_t k, uint32_t groups, int64_t n_c
   return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
 }
 
+// Pieces of long rows of a sampled product before its short rows, eight entries each: `groups` workgroups.
+int pieces(int64_t n_pieces, int64_t n_short, int32_t k, bool windows, uint32_t groups) {
+  arrow::SampledArgs a{};
+  a.U = address(0); a.V = a.Vh = address(1); a.S = address(2);
+  a.n_rows = n_pieces + n_short; a.n_pieces = n_pieces; a.nnz_rows = 8 * a.n_rows; a.k = k;
+  const int rc = arrow::launch_sddmm(a, false, false, windows, true, a.n_rows, nullptr);
+  std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
+  return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
+}
+
 // Chunks of long rows of a sampled product, in row order: `groups` workgroups of four wavefronts.
 int sampled_chunks(int64_t n_chunks, int64_t nnz, int32_t k, uint32_t groups) {
   arrow::SampledArgs a{};
@@ -148,6 +158,11 @@ int main(int, char** argv) {
   if (c == "unequal rows, many") return unequal_rows(6800, 6800 * 45, 200, 128 + 1704, 32);
   if (c == "unequal rows, short") return unequal_rows(16000, 16000 * 8, 200, 128 + 4000, 32);
   if (c == "unequal rows, alone") return unequal_rows(6000, 6000 * 45, 200, 1504, 0);
+  // eight pieces and 32 short rows to a workgroup; eight of both where pieces are more than half; in window order 16 and 64, or 32 of both in wide rows
+  if (c == "pieces, fewer") return pieces(3000, 20000, 24, false, 376 + 632);
+  if (c == "pieces, more") return pieces(7000, 6000, 24, false, 1632);
+  if (c == "pieces, in window order") return pieces(9000, 300000, 24, true, 568 + 4688);
+  if (c == "pieces, in window order, wide") return pieces(9000, 300000, 64, true, 9664);
   // a wavefront each, or two where chunks are more than a strip, or four where they leave the chip half empty
   if (c == "chunks of a strip") return sampled_chunks(5000, 5000 * 64, 200, 1256);
   if (c == "chunks of a strip and more") return sampled_chunks(5000, 5000 * 64 + 1, 200, 2504);

@@ -360,3 +360,26 @@ def test_chunks_of_one_strip(torch, k):
     op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), S)
     op.close()
     assert_within(S.cpu().numpy(), *oracle.sddmm(rowptr, colidx, vals, U, V))
+
+
+@pytest.mark.parametrize("n,pieces,short", [(700, 1, 30), (3000, 8, 100), (5003, 9, 1905), (9001, 1101, 1910), (30011, 4001, 20000),
+                                            (140001, 4001, 60001)])
+@pytest.mark.parametrize("k", [8, 20, 50, 128, 200])
+def test_pieces_before_short_rows(torch, n, pieces, short, k):
+    """Rows of 17 to 48 entries and rows of 1 to 16 have workgroups of their own, of 2 to 16 and of 4 to 64 items, the last of
+    each not full; rows without entries, the last of the list, have none."""
+    rng = np.random.default_rng(n + k)
+    length = np.zeros(n, np.int64)
+    length[:pieces] = rng.integers(17, 49, pieces)
+    length[pieces:pieces + short] = rng.integers(1, 17, short)
+    rng.shuffle(length)
+    key = np.unique(np.repeat(np.arange(n), length) * n + (n * rng.random(length.sum())).astype(np.int64))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int64)
+    colidx = (key % n).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(key)).astype(np.float32)
+    U, V = synth.normal_matrix(n, k, seed=32), synth.normal_matrix(n, k, seed=33)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, max(1, n // 16))
+    S = torch.full((len(key),), float("nan"), device="cuda")
+    op.sddmm(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), S)
+    op.close()
+    assert_within(S.cpu().numpy(), *oracle.sddmm(rowptr, colidx, vals, U, V))

@@ -52,3 +52,9 @@ def test_rows_of_dense_blocks_fill_rounds_of_workgroups(launch_grids, case):
 def test_long_rows_behind_chunks_are_two_to_a_workgroup(launch_grids, case):
     proc = subprocess.run([launch_grids, "unequal rows, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
+
+
+@pytest.mark.parametrize("case", ["fewer", "more", "in window order", "in window order, wide"])
+def test_pieces_of_long_rows_have_workgroups_of_their_own(launch_grids, case):
+    proc = subprocess.run([launch_grids, "pieces, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
