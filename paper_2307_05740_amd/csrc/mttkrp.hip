@@ -401,8 +401,6 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
 #pragma unroll
     for (int e = 0; e < P; ++e) sum[e] = vzero<4>();
   };
-  __builtin_amdgcn_s_setprio(3);
-  const int first = it, quarter = (n_items - it + 3) / 4;
   while (true) {
 #pragma unroll
     for (int h = 0; h < N; ++h) {
@@ -445,9 +443,6 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
       if (d.blocks == 0) {
         store();
         it += workers;
-        if (it - first >= 3 * quarter) __builtin_amdgcn_s_setprio(0);
-        else if (it - first >= 2 * quarter) __builtin_amdgcn_s_setprio(1);
-        else if (it - first >= quarter) __builtin_amdgcn_s_setprio(2);
         if (it >= n_items) return;
         d = d_next;
         d_next = item(it + workers);
