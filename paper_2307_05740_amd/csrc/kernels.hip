@@ -1199,6 +1199,15 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
   // loads where a lane group on its own needs four to six in a row.  Worth the idle lanes only where
   // latency decides, in a list of at most a few pieces per SIMD.
   a.piece_waves = !die_queues && s.lpr <= 8 && a.count[1] <= kPieceWavesMax;
+  // Four lane groups too (33 to 64 columns, and slices of wider rows) where four workgroups to a compute unit or fewer come of it, or more than the six that it holds
+  // but no more than some three rounds; just below six two ranks in five lose by up to 10 %.  (Ten thousand lists of 2500 to 100 K vertices, R-MAT and Chung-Lu: up
+  // to 1024 workgroups 0.74 to 1.05 times the time, 0.93 on average, 1024 to 1536 0.98, 1536 to 4000 0.97, beyond 1.0 to 1.04.  us: R-MAT 2504, k = 40, 6.7 -> 5.2;
+  // 12.6 K, 10.3 -> 9.3; Chung-Lu 15 K, 14.2 -> 13.1; but R-MAT 3850, k = 200, 8.0 and 8.8, Chung-Lu 97 K, k = 40, 29.6 and 31.9.)
+  if (!die_queues && !windows && s.lpr == 16 && a.count[1] > 0) {
+    int64_t groups = 0;
+    for (int p = 0; p < 3; ++p) groups += ceil_div(ceil_div(a.count[p], p == 1 ? kBlock / 64 : a.items[p]), kDies) * kDies * s.slices;
+    a.piece_waves = groups <= 4 * kComputeUnits || (groups > 6 * kComputeUnits && groups <= 4000);
+  }
   if (a.piece_waves) a.items[1] = kBlock / 64;
   a.runs = windows && !die_queues;
   int64_t total = 0;

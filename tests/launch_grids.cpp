@@ -53,6 +53,16 @@ int chunks(int64_t n, int32_t k, int32_t kc, int64_t n_chunks, uint64_t slices) 
   return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kChunksPerGroup >= (uint64_t)n_chunks * slices ? 0 : 1;
 }
 
+// Pieces of long rows and short rows of a product in row order, four lane groups to a wavefront: `groups` workgroups.
+int product_pieces(int64_t n_pieces, int64_t n_short, uint32_t groups) {
+  arrow::ProductArgs a{};
+  a.X = a.Xh = address(0); a.Y = address(1); a.partials = address(2);
+  a.k = 64;
+  const int rc = arrow::launch_product(a, arrow::kPartAll, n_pieces, n_pieces + n_short, 0, false, false, 100000, 0, nullptr);
+  std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
+  return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
+}
+
 // A product in row order whose rows have so many columns that slices of 64 for all of its parts are too many for one grid.
 int short_rows() {
   const int64_t n = 32768;
@@ -142,6 +152,11 @@ int main(int, char** argv) {
   if (c == "chunks in narrow slices") return chunks(8 << 20, 512, 32, 4400000, 16);
   if (c == "chunks, two sets of dies") return chunks(1 << 20, 128, 64, 16000000, 2);
   if (c == "short rows") return short_rows();
+  // a wavefront to a piece up to 1024 workgroups, sixteen pieces to a workgroup beyond, a wavefront again from 1537 to 4000
+  if (c == "pieces of a product, four workgroups a unit") return product_pieces(2000, 8320, 1024);
+  if (c == "pieces of a product, a row more") return product_pieces(2000, 8321, 128 + 528);
+  if (c == "pieces of a product, six and more") return product_pieces(4000, 8600, 1000 + 544);
+  if (c == "pieces of a product, too many") return product_pieces(13000, 12000, 816 + 752);
   if (c == "window rows") return window_rows(80000000, 128);
   // one round of 1536 workgroups of eight rows, then half as many rows each, then eight again; shorter rows eight always
   if (c == "window rows, one round") return window_rows(12288, 128, 12288 * 50, 1536);

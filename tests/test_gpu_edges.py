@@ -213,6 +213,27 @@ def test_many_batches_of_short_rows_without_window_tiles(torch, n, full, k):
     assert_within(Y.cpu().numpy(), Yref, B)
 
 
+@pytest.mark.parametrize("k", [33, 50, 64, 128, 200])
+@pytest.mark.parametrize("n,pieces,short", [(60, 3, 20), (3000, 501, 1999), (11000, 2000, 8321), (15000, 4001, 8601)])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_pieces_of_a_wavefront_each(torch, n, pieces, short, k, fuse):
+    """Rows of 17 to 48 entries that four lane groups share, or that they have one by one, beside short rows and rows without entries."""
+    rng = np.random.default_rng(n + k)
+    length = np.zeros(n, np.int64)
+    length[:pieces] = rng.integers(17, 49, pieces)
+    length[pieces:pieces + short] = rng.integers(1, 17, short)
+    rng.shuffle(length)
+    colidx = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for m in length]).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    vals = rng.uniform(-1, 1, len(colidx)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=34)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, max(1, n // 16), options=binding.arrow_options_default(fuse_levels=fuse))
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    op.spmm(torch.from_numpy(X).cuda(), Y)
+    assert_within(Y.cpu().numpy(), *oracle.spmm(rowptr, colidx, vals, X))
+    op.close()
+
+
 @pytest.mark.parametrize("k", [8, 20, 70])
 @pytest.mark.parametrize("n,b", [(200, 64), (4000, 500), (17 * 256 + 3, 256)])
 @pytest.mark.parametrize("fuse", [0, 1])

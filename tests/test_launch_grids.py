@@ -58,3 +58,9 @@ def test_long_rows_behind_chunks_are_two_to_a_workgroup(launch_grids, case):
 def test_pieces_of_long_rows_have_workgroups_of_their_own(launch_grids, case):
     proc = subprocess.run([launch_grids, "pieces, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
+
+
+@pytest.mark.parametrize("case", ["four workgroups a unit", "a row more", "six and more", "too many"])
+def test_pieces_of_a_product_have_a_wavefront_each_where_it_fits_the_chip(launch_grids, case):
+    proc = subprocess.run([launch_grids, "pieces of a product, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
