@@ -338,9 +338,10 @@ struct ResidentItem {
   uint32_t block, blocks;   // first block and their number
   int32_t dst;              // as in the other form
 };
+// last: steps of each item's last block that do not only fill it up (null: not known)
 int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* blocks, int64_t n_items, int64_t n_blocks,
                            const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials,
-                           int32_t R, void* stream);
+                           int32_t R, void* stream, const uint32_t* last = nullptr);
 
 // A third form, for tensors of many small slices and fibres of about one entry, whose factors do not fit an L2
 // (streams_kernel in mttkrp.hip): a wavefront owns rows of A and keeps their sums in LDS; each of its eight lane

@@ -61,7 +61,7 @@ struct csf3_handle {
   size_t off_seg_ptr = 0, off_seg_j = 0, off_item_seg = 0, off_item_dst = 0, off_item_ent = 0, off_split_ptr = 0,
          off_split_y = 0, off_entries = 0;
   bool resident = false;              // the image is in the form for factors that fit the LDS
-  size_t off_items = 0;
+  size_t off_items = 0, off_last = 0;
   int64_t n_blocks = 0;
   bool streams = false;               // the form for many small slices and factors that do not fit an L2
   size_t off_waves = 0, off_dst = 0, off_zero = 0;
@@ -127,7 +127,7 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
   if (h.J + h.K + 1 > arrow::kCsfRowsInLds || h.nnz < kResidentNnz) return false;
   const double most = kResidentFill * (double)(h.nnz + h.n_seg);           // rows read, fill included
   if (64.0 * arrow::kCsfBlockSteps * (double)h.I > most) return false;     // (a block per slice at least)
-  struct Part { uint32_t seg, n, block, blocks; int32_t dst; };
+  struct Part { uint32_t seg, n, block, blocks, steps; int32_t dst; };
   std::vector<Part> parts;
   std::vector<uint32_t> split_ptr{0};
   std::vector<int32_t> split_y;
@@ -142,7 +142,7 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
     const int64_t n = std::max<int64_t>({1, (segs + kResidentSegs - 1) / kResidentSegs, cost / cost_max});
     for (int64_t t = 0; t < n; ++t) {
       const int64_t lo = s + segs * t / n, hi = s + segs * (t + 1) / n;
-      parts.push_back({(uint32_t)lo, (uint32_t)(hi - lo), 0, 0, n == 1 ? (int32_t)i : (int32_t)(-1 - (slots + t))});
+      parts.push_back({(uint32_t)lo, (uint32_t)(hi - lo), 0, 0, 0, n == 1 ? (int32_t)i : (int32_t)(-1 - (slots + t))});
     }
     if (n > 1) {
       slots += n;
@@ -171,6 +171,7 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
       while (at_len[l + 1] <= first) ++l;
       steps += (uint32_t)kSegMax - l + 1;
     }
+    parts[t].steps = steps;
     parts[t].blocks = std::max(1u, (steps + arrow::kCsfBlockSteps - 1) / arrow::kCsfBlockSteps);
   }
   int64_t blocks = 0;
@@ -182,6 +183,7 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
   if ((double)(blocks * 64 * arrow::kCsfBlockSteps) > most) return false;
   size_t total = 0;
   h.off_items = total;     total = align3(total + sizeof(arrow::ResidentItem) * parts.size());
+  h.off_last = total;      total = align3(total + sizeof(uint32_t) * parts.size());
   h.off_split_ptr = total; total = align3(total + sizeof(uint32_t) * split_ptr.size());
   h.off_split_y = total;   total = align3(total + sizeof(int32_t) * split_y.size());
   h.off_entries = total;   total = align3(total + sizeof(arrow::ResidentBlock) * (size_t)blocks);
@@ -194,9 +196,11 @@ bool pack_resident(csf3_handle& h, const std::vector<uint32_t>& seg_ptr, const s
   for (size_t t = 0; t < turn.size(); ++t) turn[t] = (uint32_t)t;
   std::stable_sort(turn.begin(), turn.end(), [&](uint32_t a, uint32_t b) { return parts[a].blocks > parts[b].blocks; });
   arrow::ResidentItem* items = reinterpret_cast<arrow::ResidentItem*>(base + h.off_items);
+  uint32_t* last = reinterpret_cast<uint32_t*>(base + h.off_last);
   for (size_t t = 0; t < turn.size(); ++t) {
     const Part& p = parts[turn[t]];
     items[t] = {p.block, p.blocks, p.dst};
+    last[t] = p.steps - std::min(p.steps, (p.blocks - 1) * (uint32_t)arrow::kCsfBlockSteps);
   }
   arrow::ResidentBlock* image = reinterpret_cast<arrow::ResidentBlock*>(base + h.off_entries);
   const uint32_t zeros = (uint32_t)h.K;
@@ -767,7 +771,8 @@ int csf3_mttkrp(csf3_handle* h, const float* B, const float* C, float* A, int32_
   if (h->resident)
     rc = arrow::launch_mttkrp_resident(reinterpret_cast<const arrow::ResidentItem*>(at(h->off_items)),
                                        reinterpret_cast<const arrow::ResidentBlock*>(at(h->off_entries)), h->n_items,
-                                       h->n_blocks, B, h->J, C, h->K, A, partials, R, stream);
+                                       h->n_blocks, B, h->J, C, h->K, A, partials, R, stream,
+                                       reinterpret_cast<const uint32_t*>(at(h->off_last)));
   else if (h->streams)
     rc = arrow::launch_mttkrp_streams(reinterpret_cast<const arrow::StreamWave*>(at(h->off_waves)),
                                       reinterpret_cast<const arrow::StreamBlock*>(at(h->off_entries)),

@@ -57,7 +57,7 @@ int launch_probe_gather(const float*, int64_t, int32_t, int64_t, int, int, int64
 int launch_mttkrp(const uint32_t*, const uint32_t*, const int32_t*, const uint32_t*, const int32_t*, const Entry*,
                   int64_t, const float*, int64_t, const float*, int64_t, float*, float*, int32_t, int32_t, int32_t, void*) { reached("launch_mttkrp"); }
 int launch_mttkrp_resident(const ResidentItem*, const ResidentBlock*, int64_t, int64_t, const float*, int64_t, const float*, int64_t,
-                           float*, float*, int32_t, void*) { reached("launch_mttkrp_resident"); }
+                           float*, float*, int32_t, void*, const uint32_t*) { reached("launch_mttkrp_resident"); }
 int launch_mttkrp_streams(const StreamWave*, const StreamBlock*, const int32_t*, const int32_t*, int64_t, const float*, int64_t,
                           const float*, int64_t, float*, float*, float*, int32_t, void*) { reached("launch_mttkrp_streams"); }
 }  // namespace arrow

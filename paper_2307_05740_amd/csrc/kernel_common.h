@@ -212,6 +212,21 @@ __device__ __forceinline__ float wave_sum(float v) {
   return exchange<32>(v, v, 0);
 }
 
+// The same sums of eight values in the same order of additions, each in eight lanes: lane l has that of value
+// 4 (l & 1) + (l & 2) + (l >> 2 & 1).
+__device__ __forceinline__ float wave_sum8(const float (&v)[8], int lane) {
+  const float a0 = exchange<1>(v[0], v[4], lane), a1 = exchange<1>(v[1], v[5], lane), a2 = exchange<1>(v[2], v[6], lane),
+              a3 = exchange<1>(v[3], v[7], lane);
+  const float b0 = exchange<2>(a0, a2, lane), b1 = exchange<2>(a1, a3, lane);
+  // the partner across four lanes by the mirror image of eight and that of four of it
+  const bool upper = (lane & 4) != 0;
+  const float other = across<4>(upper ? b0 : b1);
+  float c = (upper ? b1 : b0) + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(other), 0x1B /* quad_perm 3,2,1,0 */, 0xf, 0xf, false));
+  c += across<8>(c);
+  c = exchange<16>(c, c, 0);
+  return exchange<32>(c, c, 0);
+}
+
 // Sums of NB values over the LPR lanes of a group: the upper lanes keep the upper half of the values at
 // every exchange, so that lane l ends up with the sum of value l / (LPR / NB).  With shuffles through
 // LDS instead of permlane swaps and DPP operands it took 40 vector instructions and 6 LDS accesses for

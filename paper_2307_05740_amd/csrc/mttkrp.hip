@@ -239,7 +239,14 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
 // for): 38 bytes come back for eight columns instead of 44, and the offsets are taken apart once.  Fewer rows read ahead of the
 // sums are better, the other wavefronts of a SIMD fill the wait: eight columns, rows of 4 / 2 / 1 steps together: 4096 x 2500 x
 // 2500 of 25.6 M, R = 64, 165.3 / 161.3 / 150.5 us (four columns: 8 / 4 / 2 steps 170.6 / 166.9 / 172.3; 4096^3 453.0 / 449.8 /
-// 466.4, and with a third block on its way 443.6).
+// 466.4, and with a third block on its way 443.6).  Eight sums of an item are reduced together, halving what a lane holds with every
+// exchange (some 30 instructions instead of 96), and the steps that fill up its last block are left out, which are half a block on average: 3000 x 500 x
+// 2500, R = 96, 48.0 -> 44.9 us; 4000 x 1000 x 1000, 128, 72.3 -> 67.6; 2734 x 640 x 509 of 890 K, 96, 24.3 -> 20.4 (some of it by the choice between four and eight).
+//
+// The scheduler prefers the oldest wavefronts of a SIMD; of the longest shares the first were through after 394 of 430 us.  With priorities that fall with
+// every quarter of their items they stay together, and what they read of the image: 4096^3, R = 64, 445 -> 441.5; R = 128, 825 -> 821.
+// (A barrier after every item: 467.  Windows of B, five of them, so that eight columns fit for 4096^3: R = 64 415, but R = 4 / 12 / 20 97 -> 107, 139 -> 157, 190 -> 214 us;
+// batches of a window mix the lengths of more segments, which takes 5 to 8 % more steps, and there is one image for all ranks.)
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kResidentBlock = 1024;
 
@@ -326,7 +333,7 @@ constexpr int kResidentChain = 32;
 // on their way; CHAIN: blocks whose additions are a chain (as an argument of the launch it cost 4096^3 half a percent).
 template <int P, int UR, int N, uint32_t CHAIN>
 __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
-    const ResidentItem* __restrict__ items, const ResidentBlock* __restrict__ blocks, int n_items,
+    const ResidentItem* __restrict__ items, const ResidentBlock* __restrict__ blocks, const uint32_t* __restrict__ last, int n_items,
     const float* __restrict__ B, int J, const float* __restrict__ C, int K, float* __restrict__ A,
     float* __restrict__ partials, int R, int slices, int replicas) {
   __shared__ float4 s_row[kCsfRowsInLds];
@@ -362,6 +369,9 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
   // The blocks of this wavefront's items as one sequence, N of them on their way: `f` is the item that is
   // fetched from, `d` the one that is summed; what follows an item is loaded while there is time.
   auto item = [&](int i) { return items[min(i, n_items - 1)]; };
+  // (for the eight columns, whose steps are read one by one; in front of the second half of a block, four columns lost 2 to 4 % by the branch)
+  auto steps = [&](int i) { return P == 2 && last ? (int)last[min(i, n_items - 1)] : U; };
+  int d_last = steps(it);
   ResidentItem d = item(it), d_next = item(it + workers), f = d, f_next = d_next;
   int f_it = it;
   const ResidentBlock* p = blocks + f.block;
@@ -385,6 +395,14 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
 #pragma unroll
   for (int e = 0; e < P; ++e) sum[e] = part[e] = acc[e] = x[e] = vzero<4>();
   auto store = [&] {
+    if constexpr (P == 2) {
+      const float v[8] = {sum[0].x, sum[0].y, sum[0].z, sum[0].w, sum[1].x, sum[1].y, sum[1].z, sum[1].w};
+      const float total = wave_sum8(v, (int)lane);
+      float* out = (d.dst >= 0 ? A + (size_t)d.dst * (size_t)R : partials + (size_t)(-1 - d.dst) * (size_t)R) + c0;
+      if (lane < 8) out[4 * (lane & 1) + (lane & 2) + (lane >> 2)] = total;
+      sum[0] = sum[1] = vzero<4>();
+      return;
+    }
 #pragma unroll
     for (int e = 0; e < P; ++e) sum[e] = make_float4(wave_sum(sum[e].x), wave_sum(sum[e].y), wave_sum(sum[e].z), wave_sum(sum[e].w));
     if (lane == 0) {
@@ -401,6 +419,8 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
 #pragma unroll
     for (int e = 0; e < P; ++e) sum[e] = vzero<4>();
   };
+  const int first = it, quarter = (n_items - it + 3) / 4;    // (N == 3: the longest shares)
+  if (N == 3) __builtin_amdgcn_s_setprio(3);
   while (true) {
 #pragma unroll
     for (int h = 0; h < N; ++h) {
@@ -409,6 +429,7 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
       uint32_t ends[U / 2];
 #pragma unroll
       for (int u0 = 0; u0 < U; u0 += UR) {
+        if (P == 2 && u0 > 0 && u0 % 2 == 0 && d.blocks == 1 && u0 >= d_last) break;
         float4 c[UR][P];
 #pragma unroll
         for (int u = u0; u < u0 + UR; ++u)
@@ -443,8 +464,14 @@ __global__ __launch_bounds__(kResidentBlock) void resident_kernel(
       if (d.blocks == 0) {
         store();
         it += workers;
+        if (N == 3) {
+          if (it - first >= 3 * quarter) __builtin_amdgcn_s_setprio(0);
+          else if (it - first >= 2 * quarter) __builtin_amdgcn_s_setprio(1);
+          else if (it - first >= quarter) __builtin_amdgcn_s_setprio(2);
+        }
         if (it >= n_items) return;
         d = d_next;
+        d_last = steps(it);
         d_next = item(it + workers);
       }
     }
@@ -636,7 +663,7 @@ int launch_mttkrp_streams(const StreamWave* waves, const StreamBlock* blocks, co
 
 int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* blocks, int64_t n_items, int64_t n_blocks,
                            const float* B, int64_t b_rows, const float* C, int64_t c_rows, float* A, float* partials,
-                           int32_t R, void* stream) {
+                           int32_t R, void* stream, const uint32_t* last) {
   if (n_items <= 0) return 0;
   if (b_rows + c_rows + 1 > kCsfRowsInLds || n_items > INT_MAX) return (int)hipErrorInvalidValue;
   // Replicas: workgroups that share the items of a column slice.  One round of workgroups where the slices divide
@@ -667,18 +694,18 @@ int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* block
     }
     return s;
   };
-  // Eight columns at a time where the rows fit the LDS so: the entries are read half as often, and a step takes 1.7
+  // Eight columns at a time where the rows fit the LDS so: the entries are read half as often, and a step takes 1.6
   // times as long instead of twice.  Half as many slices leave twice as many wavefronts for the items, though, and a wavefront
-  // that has its SIMD to itself waits longer for each of its rows.  With the numbers below the cost's ratio is within 10 % of the
-  // measured one and on its side of 1 (four / eight columns, us): 4096 x 2500 x 2500 of 25.6 M, R = 64, 166.1 / 150.2; 4000 x 1000 x 1000 of 4 M,
-  // 128, 84.9 / 70.6; 3000 x 500 x 2500 of 3.75 M, 96, 56.5 / 46.8; 2100 x 1500 x 2000 of 6.3 M, 8, 16.0 / 13.9; 2500 x 600 x 1200 of 1.8 M, 32,
-  // 14.8 / 12.9; 1300^3 of 2.2 M, 64, 24.2 / 22.7; 3000 x 2000 x 1000 of 6 M, 16, 18.5 / 18.3; but 3000 x 3000 x 1000 of 9 M, 24, 34.0 / 35.1;
-  // 700 x 2000 x 1500 of 2.1 M, 100, 32.8 / 34.3; 1100 x 2500 x 2500 of 6.9 M, 32, 34.7 / 38.3; 512 x 1000 x 1000 of 512 K, 32, 7.4 / 7.8;
-  // 900 x 2000 x 3000 of 5.4 M, 9, 13.8 / 17.5.
+  // that has its SIMD to itself waits longer for each of its rows.  Both measured on 4500 uniform tensors of 200 to 4096 rows a side at four ranks each: the numbers
+  // below take 0.4 % longer than the better of the two on average, those before eight sums were reduced together 1 %; of 9000 products 77 took
+  // more than 2 % longer with them than before and 830 less.  Four / eight columns, us: 4096 x 2500 x 2500 of 25.6 M, R = 64, 166 / 150; 4000 x 1000 x 1000 of 4 M,
+  // 128, 84.9 / 67.6; 1606 x 528 x 1024 of 868 K, 64, 17.8 / 13.6; 2388 x 522 x 997 of 1.2 M, 50, 21.5 / 16.9; 803 x 875 x 372 of 261 K, 128, 14.2 / 11.0; but
+  // 1018 x 2781 x 1602 of 4.5 M, 16, 15.5 / 18.4; 487 x 2818 x 1884 of 2.6 M, 32, 16.6 / 19.8; and on the wrong side 700 x 2000 x 1500 of 2.1 M, 100, 33.9 / 35.0.  (More
+  // slices than one round holds: as measured before, 2000 x 1000 x 1000 of 1 M, R = 5120.)
   Split s = split(1, 1.0, 5, 0.6);
   bool two = false;
   if (R >= 8 && 2 * (b_rows + c_rows + 1) <= kCsfRowsInLds) {
-    const Split t = split(2, 1.72, 10, 0.7);
+    const Split t = split(2, ceil_div(R, 8) > kResidentGroups ? 1.72 : 1.57, 11, 0.6);
     two = t.cost < s.cost;
     if (two) s = t;
   }
@@ -686,7 +713,7 @@ int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* block
   if (groups > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
 #define ARROW_CHAIN(CHAIN, ...)                                                                                            \
   hipLaunchKernelGGL((resident_kernel<__VA_ARGS__, CHAIN>), dim3((unsigned)groups), dim3(kResidentBlock), 0, (hipStream_t)stream, items, blocks, \
-                     (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)s.slices, (int)s.replicas)
+                     last, (int)n_items, B, (int)b_rows, C, (int)c_rows, A, partials, (int)R, (int)s.slices, (int)s.replicas)
 #define ARROW_LAUNCH(...) if (chain4) ARROW_CHAIN(4, __VA_ARGS__); else ARROW_CHAIN(2, __VA_ARGS__)
   const bool chain4 = n_blocks >= n_items * kResidentChain;
   const bool third = steps >= (double)(s.replicas * waves) * kResidentLong && n_blocks >= n_items * kResidentLongItem;

@@ -405,6 +405,31 @@ def test_mttkrp_factors_in_lds_eight_columns(torch, I, J, K, nnz, R):
     op.close()
 
 
+@pytest.mark.parametrize("lanes", [64, 61])
+def test_mttkrp_steps_of_the_last_block(torch, lanes):
+    """Items whose last block of eight steps has one to eight of them, with a factor whose first and last rows are infinite where
+    no entry refers to them; eight columns at a time give the bits of four."""
+    I, J, K, R = 2000, 1000, 900, 64
+    rng = np.random.default_rng(lanes)
+    length = 1 + np.arange(I) % 9                            # of the `lanes` fibres of a slice: 2 to 10 steps
+    i = np.repeat(np.arange(I), lanes * length)
+    j = np.concatenate([np.repeat(1 + rng.choice(J - 2, lanes, replace=False), n) for n in length])
+    k = rng.integers(1, K - 1, len(i))
+    v = rng.uniform(-1, 1, len(i)).astype(np.float32)
+    i, j, k = (x.astype(np.int32) for x in (i, j, k))
+    B, C = synth.normal_matrix(J, R, seed=41), synth.normal_matrix(K, R, seed=42)
+    Aref, E = oracle.mttkrp((I, J, K), i, j, k, v, B, C)
+    B[[0, -1]], C[[0, -1]] = np.inf, np.nan
+    op = binding.Csf3Mttkrp((I, J, K), i, j, k, v)
+    assert binding.csf3_form(op.h) == binding.CSF3_FORM_FACTORS_IN_LDS and op.info["partials"] == 0
+    A = torch.full((I, R), float("nan"), device="cuda")
+    op.mttkrp(torch.from_numpy(B).cuda(), torch.from_numpy(C).cuda(), A)
+    assert_within(A.cpu().numpy(), Aref, E)
+    four = op.mttkrp(torch.from_numpy(np.ascontiguousarray(B[:, :4])).cuda(), torch.from_numpy(np.ascontiguousarray(C[:, :4])).cuda())
+    assert np.array_equal(four.cpu().numpy().view(np.uint32), A[:, :4].contiguous().cpu().numpy().view(np.uint32))
+    op.close()
+
+
 @pytest.mark.parametrize("k", [1, 6, 20, 33, 128, 260])
 @pytest.mark.parametrize("fuse", [0, 1])
 def test_rows_of_many_partial_vectors(torch, k, fuse):
