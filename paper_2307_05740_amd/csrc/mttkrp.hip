@@ -106,7 +106,10 @@ __device__ __forceinline__ void segments(const ItemView& v, uint32_t s0, uint32_
 
 constexpr int64_t kResidentItems = 8192;  // wavefronts the chip holds
 
-template <int VEC, int LPR, bool SMALL>
+// TOGETHER: the four wavefronts of a workgroup share an item and stage all of it together.  (What a wavefront stages for itself is the segments of its share, whose
+// entries it knows only when their offsets have come: one more memory latency, 250 x 231 x 307 of 17,720, R = 25, 5.3 -> 5.0 us, 1086 x 338 x 234 of
+// 86 K, 32, 5.3 -> 4.9; 300 x 200 x 307 of 18.4 K, 8, 3.7 -> 3.45.  Where items are many the wavefronts would wait for each other: skewed 5897 x 491 x 536, 8, 13.9 -> 14.2.)
+template <int VEC, int LPR, bool SMALL, bool TOGETHER>
 __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
     const uint32_t* __restrict__ item_seg, const uint32_t* __restrict__ item_ent,
     const int32_t* __restrict__ item_dst, const uint32_t* __restrict__ seg_ptr,
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
   // with NaN (a result that announces itself) instead of being left with whatever it held.
   const bool over_limit = n_seg > (uint32_t)kCsfItemSegs || n_ent > (uint32_t)kCsfItemNnz;
   if (over_limit) { n_seg = 0; n_ent = 0; }
-  if (team > 1) {                       // this wavefront's share of the segments
+  if (!TOGETHER && team > 1) {          // this wavefront's share of the segments
     const uint32_t first = n_seg * part >> team_log, last = n_seg * (part + 1) >> team_log, s_item = s_lo;
     const uint32_t e_end = last < n_seg ? seg_ptr[s_item + last] : e_lo + n_ent;
     if (first > 0) e_lo = seg_ptr[s_item + first];
@@ -147,11 +150,25 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
   const uint32_t lane = threadIdx.x % 64;
   const uint32_t g = lane / LPR;
   const LaneColumns lc = lane_columns<VEC>(lane % LPR, blockIdx.y * (LPR * VEC), R);
-  const ItemView v{s_ent[wave], s_ptr[wave], s_j[wave], reinterpret_cast<const char*>(B),
+  const int at = TOGETHER ? 0 : wave;
+  const ItemView v{s_ent[at], s_ptr[at], s_j[at], reinterpret_cast<const char*>(B),
                    reinterpret_cast<const char*>(C), 4u * (uint32_t)R, lc.ok ? 4u * (uint32_t)lc.c : 0u};
   // stage the item, the loads of up to 128 segments and 256 entries before the first wait
   static_assert(kCsfItemSegs == 128 && kCsfItemNnz == 512, "the staging covers these sizes");
-  {
+  if constexpr (TOGETHER) {
+    const uint32_t me = threadIdx.x;
+    Entry e[kCsfItemNnz / kBlock];
+    uint32_t pt = 0;
+    int32_t jt = 0;
+    if (me < n_seg) { pt = stream_load(&seg_ptr[s_lo + me]); jt = stream_load(&seg_j[s_lo + me]); }
+#pragma unroll
+    for (uint32_t q = 0; q < kCsfItemNnz / kBlock; ++q) if (me + q * kBlock < n_ent) e[q] = stream_load(&ent[e_lo + me + q * kBlock]);
+    if (me < n_seg) { s_ptr[0][me] = (uint16_t)(pt - e_lo); s_j[0][me] = jt; }
+    if (me == 0) s_ptr[0][n_seg] = (uint16_t)n_ent;
+#pragma unroll
+    for (uint32_t q = 0; q < kCsfItemNnz / kBlock; ++q) if (me + q * kBlock < n_ent) s_ent[0][me + q * kBlock] = e[q];
+    __syncthreads();
+  } else {
     Entry e[4];
     uint32_t pt[2];
     int32_t jt[2];
@@ -176,6 +193,10 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
   strip_sync();
   V acc = vzero<VEC>();
   uint32_t s = 0;
+  if constexpr (TOGETHER) {                             // this wavefront's share of the segments
+    s = n_seg * part / WPB;
+    n_seg = n_seg * (part + 1) / WPB;
+  }
   while (s < n_seg) {
     // lengths of the next 64 segments, one per lane; the first is the longest of them
     const uint32_t mine = s + lane < n_seg ? (uint32_t)v.ptr[s + lane + 1] - (uint32_t)v.ptr[s + lane] : 0u;
@@ -198,7 +219,7 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
 #pragma unroll
   for (int m = LPR; m < 64; m <<= 1) vadd(acc, vshfl_xor(acc, m));
   if (team > 1) {
-    // each wavefront's sum in the memory of its own entries, which it has read
+    // each wavefront's sum in the memory of its own entries, which it has read (TOGETHER: which no entries are in)
     strip_sync();
     if (part > 0 && g == 0) vstore<VEC>(reinterpret_cast<float*>(s_ent[wave]) + lane * VEC, acc);
     __syncthreads();
@@ -749,10 +770,11 @@ int launch_mttkrp(const uint32_t* item_seg, const uint32_t* item_ent, const int3
     const int64_t blocks = ceil_div(n_items << team_log, kBlock / 64);
     if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
     dim3 grid((unsigned)blocks, (unsigned)s.slices);
-#define ARROW_LAUNCH(SM)                                                                            \
-  hipLaunchKernelGGL((mttkrp_kernel<VEC, LPR, SM>), grid, dim3(kBlock), 0, (hipStream_t)stream,     \
+    const bool together = small && n_items <= kResidentItems / 4;      // (four wavefronts an item)
+#define ARROW_LAUNCH(SM, TOGETHER)                                                                  \
+  hipLaunchKernelGGL((mttkrp_kernel<VEC, LPR, SM, TOGETHER>), grid, dim3(kBlock), 0, (hipStream_t)stream,     \
                      item_seg, item_ent, item_dst, seg_ptr, seg_j, entries, n_items, B, C, A, partials, (int)R, team_log)
-    if (small) ARROW_LAUNCH(true); else ARROW_LAUNCH(false);
+    if (together) ARROW_LAUNCH(true, true); else if (small) ARROW_LAUNCH(true, false); else ARROW_LAUNCH(false, false);
 #undef ARROW_LAUNCH
     return (int)hipGetLastError();
   });
