@@ -70,7 +70,12 @@ constexpr int kChunksPerGroup = 4;   // wave-list items (one per wavefront) per 
 constexpr int32_t kTeamDst = INT32_MIN + 1;
 constexpr int kItemsPerGroupBlock = 64;  // most group-list items per workgroup, and exactly that many of a die queue
 constexpr int64_t kMostGroups = (1LL << 24) - 1;   // workgroups of 256 in a dimension of a grid: HIP takes fewer than 2^32 work items
-constexpr int kDieRun = 256;         // consecutive wave-list workgroups that one die takes where the list has no die queues
+// Consecutive wave-list workgroups that one die takes where the list has no die queues (a power of two): long enough for its L2 to gain, and several of
+// them for every die of a short list, whose last ones else go round-robin or leave dies idle.  (On 604 lists of 132 K to 900 K vertices, R-MAT and
+// Chung-Lu, at two ranks each: 64 take 0.96 times the time of 256 below 4000 workgroups and 0.99 to 7300, 128 0.99 to 9600, beyond that nothing gains on
+// average; us, 256 / 128 / 64: directed 300 K, k = 50, 136.1 / 136.0 / 133.6; Chung-Lu 250 K, 48, 84.3 / 81.0 / 81.5; sampled product, Chung-Lu 400 K, 32, 95.7 /
+// 92.5 / 91.2; R-MAT 500 K, 128, 331.6 / 335.6 / 337.8.)
+inline uint32_t die_run(int64_t blocks) { return blocks < 7300 ? 64 : blocks < 9600 ? 128 : 256; }
 // head panels: kPanelRows head rows form a group; the group's head-block entries are dealt by column
 // class (staged head row mod kDies) to kDies workgroups, one per accelerator die, each keeping the
 // group's accumulators in LDS and streaming its entries in kPanelBins lane-group streams
@@ -225,7 +230,7 @@ struct ProductArgs {
   int32_t width;                        // columns per slice
   int32_t piece_waves;                  // a piece per wavefront instead of per lane group
   int32_t entries_once;                 // the entries are too many to be found in a cache the next time
-  int32_t runs;                         // deal the wave list to the dies in runs of kDieRun workgroups
+  uint32_t run;                         // workgroups of the wave list that a die takes one after the other (die_run), or 0
 };
 enum { kPartChunks = 1, kPartPieces = 2, kPartShort = 4, kPartAll = 7 };
 // Launches the given parts.  n_pieces, n_rows, n_empty: pieces, all items and trailing empty rows of
@@ -286,7 +291,7 @@ struct SampledArgs {
   uint32_t piece_blocks;                // ... which have the first of the workgroups of the rows; the short rows'
   uint32_t short_base;                  // ... begin at item id * items + short_base (mod 2^32)
   uint32_t chunk_blocks;
-  int32_t runs;                         // as in ProductArgs
+  uint32_t run;                         // as in ProductArgs
 };
 // v_rows = rows of V; windows, die_queues: as in launch_product (the grid is filled in here); unequal: the group list
 // holds pieces of long rows, not only short ones.

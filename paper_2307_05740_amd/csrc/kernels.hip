@@ -441,13 +441,13 @@ __global__ __launch_bounds__(kBlock) void chunks_kernel(const ProductArgs a) {
   const uint32_t dies_log = kDiesLog - a.sets_log, dies = 1u << dies_log, die = blockIdx.x % kDies;
   uint32_t id = (blockIdx.x / kDies << dies_log) + (die & (dies - 1u));
   const uint32_t slice = (die >> dies_log) * gridDim.y + blockIdx.y;
-  // Runs of kDieRun workgroups go to one die each: the eight dies then work on different column
+  // Runs of some 256 workgroups (die_run) go to one die each: the eight dies then work on different column
   // windows at a time, and a row of X that several chunks of a run read is fetched into one L2
   // instead of several (the same chunks: 255 -> 231 us per product; R-MAT 8m, k = 128: 1 %; eighths
   // of the whole list are slower, the dies then finish at different times).
-  const uint32_t span = dies * kDieRun;
+  const uint32_t span = dies * a.run;
   const uint32_t base = id & ~(span - 1u);
-  if (a.runs && base + span <= a.blocks[0]) id = base + (id & (dies - 1u)) * kDieRun + ((id - base) >> dies_log);
+  if (a.run && base + span <= a.blocks[0]) id = base + (id & (dies - 1u)) * a.run + ((id - base) >> dies_log);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int64_t ch = (int64_t)id * WPB + wave;
   if (ch >= a.n_chunks) return;
@@ -1213,7 +1213,7 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
     a.piece_waves = groups <= 4 * kComputeUnits || (groups > 6 * kComputeUnits && groups <= 4000);
   }
   if (a.piece_waves) a.items[1] = kBlock / 64;
-  a.runs = windows && !die_queues;
+  a.run = windows && !die_queues ? die_run(ceil_div(a.count[0], a.items[0])) : 0;
   int64_t total = 0;
   for (int p = 0; p < 4; ++p) {
     const int64_t blocks = ceil_div(ceil_div(a.count[p], a.items[p]), kDies) * kDies;

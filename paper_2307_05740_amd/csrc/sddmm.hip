@@ -321,11 +321,11 @@ __global__ __launch_bounds__(kBlock) void sddmm_chunks_kernel(const SampledArgs 
   constexpr int WPB = kBlock / 64;
   __shared__ Entry ents[WPB][64];
   __shared__ uint32_t ats[WPB][64];
-  // runs of kDieRun workgroups to one die each, as in the product's chunks kernel
+  // runs of workgroups to one die each, as in the product's chunks kernel
   uint32_t id = blockIdx.x;
-  const uint32_t span = kDies * kDieRun;
-  const uint32_t base = id / span * span;
-  if (a.runs && base + span <= gridDim.x) id = base + id % kDies * kDieRun + (id - base) / kDies;
+  const uint32_t span = kDies * a.run;
+  const uint32_t base = id & ~(span - 1u);
+  if (a.run && base + span <= gridDim.x) id = base + id % kDies * a.run + (id - base) / kDies;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int64_t ch = (int64_t)id * WPB + wave;      // (a list in window order is never short)
   if (ch < a.n_chunks) sampled_chunk<VEC, LPR, NB, SMALL, false>(ents[wave], ats[wave], a, ch, 0);
@@ -479,7 +479,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   a.piece_blocks = (uint32_t)piece_blocks;
   a.short_base = (uint32_t)a.n_pieces - a.piece_blocks * (uint32_t)a.items;
   if (chunk_blocks + row_blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-  a.runs = windows && !die_queues;
+  a.run = windows && !die_queues ? die_run(chunk_blocks) : 0;
   const bool once = v_rows * a.k * (int64_t)sizeof(float) >= kSampledOnce;
   return dispatch_shape(s, [&](auto Vc, auto L) -> int {
     constexpr int VEC = decltype(Vc)::value, LPR = decltype(L)::value;
