@@ -12,7 +12,7 @@
 // second memory latency after every batch of rows, and the entries of a list one batch at a time; both
 // are now on their way while the batch before is worked on (R-MAT 1m, k = 128: chunks 944 -> 868 us, short
 // rows and pieces 448 -> 363 us, at 6.4 and 7.1 TB/s of what crosses the L2's boundary; R-MAT 30k, k = 24: 47 ->
-// 19 us, 12 since wavefronts share chunks, launch_sddmm).
+// 19 us, 12 since wavefronts share chunks, 10.2 since the pieces of long rows come before the short rows, launch_sddmm).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
