@@ -148,7 +148,8 @@ int arrow_upload(arrow_handle *h, void *dev_buf, size_t bytes, void *stream);
  * Device workspace a product with k columns needs: head partials of the
  * largest level, the staged head rows, the results of the corner and panel
  * work items, plus one n x k buffer for the chained products of
- * arrow_spmm_iter.  arrow_set_workspace binds caller-owned device memory
+ * arrow_spmm_iter; and, where the rows of a staged head of k columns are faster in whole
+ * 128-byte lines, room for it, without which everything works as well.  arrow_set_workspace binds caller-owned device memory
  * (256-byte aligned); it may be rebound at any time the stream is idle.
  */
 size_t arrow_workspace_bytes(const arrow_handle *h, int32_t k);
@@ -177,7 +178,8 @@ int arrow_spmm(arrow_handle *h, const float *X, float *Y, int32_t k, void *strea
  * run on the current device).  The call allocates nothing, records no events even when profiling
  * is on, and only launches kernels on `stream`.
  *   X, Y    DEVICE, n x k fp32 row-major, 16-byte aligned, must not overlap; Y is overwritten
- * The scratch need is arrow_workspace_bytes(h, k) minus the n x k buffer of the chained products
+ * The scratch need is arrow_workspace_bytes(h, k) minus the n x k buffer of the chained products and
+ * the room for a head in whole lines
  * (partial vectors of the largest level + min(b, n) staged head rows of k floats); if it exceeds
  * the array the call fails with ARROW_ETOOSMALL and nothing is launched.  All calls on one GPU
  * share that GPU's array, whatever the handle or stream: calls that overlap in time on one GPU

@@ -5,12 +5,14 @@
 #include <hip/hip_runtime.h>
 #include <omp.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -161,12 +163,50 @@ constexpr int64_t kSlicedShort = 256LL << 20;   // largest X that the cache behi
 constexpr int64_t kFewChunks = 2048;   // a list this short leaves wavefront slots empty
 constexpr int64_t kFewRows = 16384;    // and so does this one
 
+// Scratch memory that a call does not need: none, or some at a multiple of kAlign
+struct Spare { unsigned char* at; size_t bytes; };
+Spare spare_after(const arrow_handle* h, size_t used) {
+  return used < h->ws_bytes ? Spare{h->ws + used, h->ws_bytes - used} : Spare{nullptr, 0};
+}
+
+// Whether a level's head may be laid out in whole lines: the panels, the corner and the classes read it with rows close together.
+// A head of at most half of the rows, in rows of at most twice the bytes, is no larger than X: 32-bit offsets that hold in X hold in it.
+bool whole_lines(const arrow::LevelImage& im) {
+  return im.stage_used && im.classes == 0 && im.n_panel_bins == 0 && im.n_corner_tiles == 0 && 2 * im.n_stage <= im.n_i;
+}
+
+// Floats between the rows of a staged head.  A row of k floats lies at a multiple of g = gcd(k, 32) floats and touches 1 + (k - g) / 32
+// lines of 128 bytes on average; laid out in whole lines it touches ceil(k / 32), but less of the head stays in the L2s.  Whole lines
+// where they are at least a tenth fewer and the bytes at most twice as many.  R-MAT, 2^20 vertices, 16 M edges, us, close / whole lines,
+// product: k = 17 376 / 356, 25 452 / 395, 50 683 / 645, 63 801 / 704, 90 1079 / 1000, 127 1542 / 1401, 150 1787 / 1714; sampled product:
+// 30 560 / 471, 63 836 / 733, 127 1501 / 1363; 2^18 vertices, 4 M edges, product: 62 167 / 154, 125 307 / 294.  Beyond the line, product,
+// 2^20: 5 215 / 244, 12 290 / 295, 36 565 / 587, 70 912 / 929, 100 1166 / 1214, 110 1281 / 1268, 200 2307 / 2358; 2^18: 180 450 / 447.
+int32_t head_columns(int32_t k) {
+  const int64_t whole = ((int64_t)k + 31) / 32 * 32;
+  return whole <= 2 * (int64_t)k && 10 * whole <= 9 * (32 + (int64_t)k - std::gcd(k, 32)) ? (int32_t)whole : k;
+}
+// Bytes of a staged head in whole lines, beside the buffer whose rows are close; 0 where no level has one.
+size_t head_bytes(const arrow_handle* h, int32_t k) {
+  const int64_t columns = head_columns(k);
+  size_t most = 0;
+  for (const arrow::LevelImage& im : h->img.levels)
+    if (columns > k && whole_lines(im)) most = std::max(most, (size_t)(im.n_stage * columns) * sizeof(float));
+  return align_up(most);
+}
+// Where a level's staged head is laid out: in whole lines if there is room for that.
+float* head_buffer(const arrow::LevelImage& im, int32_t k, float* stage, const Spare& spare, int32_t* stride) {
+  const int32_t columns = head_columns(k);
+  const bool whole = columns > k && whole_lines(im) && spare.bytes >= (size_t)im.n_stage * (size_t)columns * sizeof(float);
+  *stride = whole ? columns : k;
+  return whole ? reinterpret_cast<float*>(spare.at) : stage;
+}
+
 // one product, src -> dst (device, n x k), all levels in stream order.  `ws` holds the partial
 // vectors, the staged head and the panel results (the caller's workspace, or the static scratch
 // array); every byte of it that a kernel reads has been written earlier in the same product.
 // prof = false: no event is created or recorded, whatever the handle's profiling switch says.
 int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t stream,
-            unsigned char* ws, bool prof) {
+            unsigned char* ws, Spare spare, bool prof) {
   float* partials = reinterpret_cast<float*>(ws);
   float* stage = reinterpret_cast<float*>(ws + partial_bytes(h, k));
   float* panel_part = reinterpret_cast<float*>(ws + partial_bytes(h, k) + stage_bytes(h, k));
@@ -176,13 +216,15 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
     const bool acc = li > 0;
     const arrow::Entry* ent = at<arrow::Entry>(h, im.off_entries);
     const float* Xh = X;
+    int32_t head_stride = k;
     arrow::LaunchTuning tune = h->tuning;
     if (im.stage_used) {
       // the first-block-column window X_0 = (P_i X)[0:b], made contiguous once per product
       Scoped sc(h, kStage, (int)li, stream, prof);
-      int rc = arrow::launch_gather(at<int32_t>(h, im.off_stage_perm), im.n_stage, X, stage, k, stream);
+      float* head = head_buffer(im, k, stage, spare, &head_stride);
+      int rc = arrow::launch_gather(at<int32_t>(h, im.off_stage_perm), im.n_stage, X, head, k, head_stride, stream);
       if (rc) return check_hip(rc, "head staging launch");
-      Xh = stage;
+      Xh = head;
     }
     if (tune.kc == 0) {
       if (im.staged && im.classes > 0) {
@@ -219,7 +261,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
       a.chunk_dst = at<int32_t>(h, im.off_chunk_dst); a.n_chunks = im.n_chunks; a.longest_short = im.longest_short;
       a.rows_ptr = at<uint32_t>(h, im.off_rows_ptr); a.rows_mid = at<uint32_t>(h, im.off_rows_mid);
       a.rows_dst = at<int32_t>(h, im.off_rows_dst);
-      a.ent = ent; a.X = X; a.Xh = Xh; a.Y = Y; a.partials = partials;
+      a.ent = ent; a.X = X; a.Xh = Xh; a.head_stride = head_stride; a.Y = Y; a.partials = partials;
       a.k = k; a.accumulate = acc ? 1 : 0;
       a.entries_once = (im.nnz_rows + im.nnz_chunks) * (int64_t)sizeof(arrow::Entry) > kEntriesOnce;
       // Whether the chunks have a kernel of their own: not where few of them share a launch with other rows.  Alone they keep
@@ -294,17 +336,24 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
 int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_out, int32_t k,
                     hipStream_t stream) {
   float* stage = reinterpret_cast<float*>(h->ws + partial_bytes(h, k));
+  Spare spare = spare_after(h, scratch_bytes(h, k));     // (a caller may keep operands in the part that only chained products use)
+  const size_t xy = (size_t)h->n * (size_t)k * sizeof(float);
+  if (ranges_overlap(U, xy, spare.at, spare.bytes) || ranges_overlap(V, xy, spare.at, spare.bytes) ||
+      ranges_overlap(S_out, (size_t)h->nnz * sizeof(float), spare.at, spare.bytes))
+    spare = Spare{nullptr, 0};
   for (size_t li = 0; li < h->img.levels.size(); ++li) {
     const arrow::LevelImage& im = h->img.levels[li];
     const arrow::Entry* ent = at<arrow::Entry>(h, im.off_entries);
     const uint32_t* emap = h->sddmm_image_order ? nullptr : h->dev_map + im.map_offset;
     float* S = h->sddmm_image_order ? S_out + im.map_offset : S_out;
     const float* Vh = V;
+    int32_t head_stride = k;
     if (im.stage_used) {
       Scoped sc(h, kStage, (int)li, stream);
-      int rc = arrow::launch_gather(at<int32_t>(h, im.off_stage_perm), im.n_stage, V, stage, k, stream);
+      float* head = head_buffer(im, k, stage, spare, &head_stride);
+      int rc = arrow::launch_gather(at<int32_t>(h, im.off_stage_perm), im.n_stage, V, head, k, head_stride, stream);
       if (rc) return check_hip(rc, "head staging launch");
-      Vh = stage;
+      Vh = head;
     }
     {
       arrow::SampledArgs a{};
@@ -313,7 +362,7 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
       a.rows_ptr = at<uint32_t>(h, im.off_rows_ptr); a.rows_mid = at<uint32_t>(h, im.off_rows_mid);
       a.rows_row = at<int32_t>(h, im.off_rows_row); a.n_rows = im.n_rows - im.empty_slots; a.nnz_rows = im.nnz_rows;
       a.n_pieces = im.piece_slots;
-      a.ent = ent; a.emap = emap; a.U = U; a.V = V; a.Vh = Vh; a.S = S; a.k = k;
+      a.ent = ent; a.emap = emap; a.U = U; a.V = V; a.Vh = Vh; a.head_stride = head_stride; a.S = S; a.k = k;
       auto launch = [&](arrow::SampledArgs args, bool window_rows) -> int {
         if (args.n_chunks == 0 && args.n_rows == 0) return ARROW_OK;
         return check_hip(arrow::launch_sddmm(args, window_rows, im.classes > 0, !im.row_major, im.piece_slots > 0, h->n, stream),
@@ -565,7 +614,7 @@ int arrow_upload(arrow_handle* h, void* dev_buf, size_t bytes, void* stream) {
 
 size_t arrow_workspace_bytes(const arrow_handle* h, int32_t k) {
   if (!h || k < 1) return 0;
-  return scratch_bytes(h, k) + align_up((size_t)h->n * (size_t)k * sizeof(float));
+  return scratch_bytes(h, k) + align_up((size_t)h->n * (size_t)k * sizeof(float)) + head_bytes(h, k);   // (the last: a gain, not a need)
 }
 
 int arrow_set_workspace(arrow_handle* h, void* dev_ws, size_t bytes) {
@@ -583,7 +632,7 @@ int arrow_spmm(arrow_handle* h, const float* X, float* Y, int32_t k, void* strea
   rc = check_operands(h, X, Y, k, h->ws, h->ws_bytes);
   if (rc) return rc;
   h->spans_used = 0;
-  return product(h, X, Y, k, (hipStream_t)stream, h->ws, true);
+  return product(h, X, Y, k, (hipStream_t)stream, h->ws, spare_after(h, scratch_bytes(h, k)), true);
 }
 
 int arrow_spmm_static(arrow_handle* h, const float* X, float* Y, int32_t k, void* stream) {
@@ -599,7 +648,7 @@ int arrow_spmm_static(arrow_handle* h, const float* X, float* Y, int32_t k, void
   std::string why;
   unsigned char* ws = arrow::static_scratch(why);   // resolved by arrow_upload on this device; a lookup, not an allocation
   if (!ws) return fail(ARROW_EHIP, "%s", why.c_str());
-  return product(h, X, Y, k, (hipStream_t)stream, ws, false);
+  return product(h, X, Y, k, (hipStream_t)stream, ws, Spare{ws + need, (size_t)ARROW_STATIC_SCRATCH_BYTES - need}, false);
 }
 
 int arrow_spmm_iter(arrow_handle* h, float* X, int32_t k, int32_t l, void* stream) {
@@ -622,7 +671,7 @@ int arrow_spmm_iter(arrow_handle* h, float* X, int32_t k, int32_t l, void* strea
   float* src = X;
   for (int32_t t = 0; t < l; ++t) {
     float* dst = tmp2 && t == l - 2 ? tmp2 : (src == X ? tmp : X);
-    rc = product(h, src, dst, k, (hipStream_t)stream, h->ws, true);
+    rc = product(h, src, dst, k, (hipStream_t)stream, h->ws, spare_after(h, scratch_bytes(h, k) + (tmp2 ? 2 : 1) * xy), true);
     if (rc) return rc;
     src = dst;
   }
@@ -678,7 +727,7 @@ int arrow_gather(arrow_handle* h, int32_t level, const float* X, float* Xp, int3
   if (((uintptr_t)X | (uintptr_t)Xp) % 16) return fail(ARROW_EINVAL, "X and Xp must be 16-byte aligned");
   if (!h->dev) return fail(ARROW_ENOTREADY, "arrow_upload has not been called");
   const arrow::LevelImage& im = h->img.levels[level];
-  int rc = arrow::launch_gather(at<int32_t>(h, im.off_perm), im.n_i, X, Xp, k, stream);
+  int rc = arrow::launch_gather(at<int32_t>(h, im.off_perm), im.n_i, X, Xp, k, k, stream);
   return check_hip(rc, "gather kernel launch");
 }
 

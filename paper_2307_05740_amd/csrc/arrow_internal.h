@@ -220,6 +220,7 @@ struct ProductArgs {
   float* Y; float* partials;
   int64_t n_chunks;
   int64_t longest_short;                // entries of the longest short row
+  int32_t head_stride;                  // floats from one row of Xh to the next (those of X are k apart)
   int32_t k, accumulate;                // accumulate: add to the rows of Y instead of storing them
   // parts 0 .. 3: wave list, pieces, short rows, rows without entries
   int64_t begin[4], count[4];           // slots of the part
@@ -242,7 +243,8 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
 bool same_shape(int32_t k, int32_t kc_a, int32_t kc_b, bool accumulate);
 int launch_reduce(const uint32_t* split_ptr, const int32_t* split_y, int64_t n_split,
                   const float* partials, float* Y, int32_t k, bool accumulate, void* stream);
-int launch_gather(const int32_t* perm, int64_t n_i, const float* X, float* Xp, int32_t k,
+// Rows of k columns; those of Xp are `stride` floats apart.
+int launch_gather(const int32_t* perm, int64_t n_i, const float* X, float* Xp, int32_t k, int32_t stride,
                   void* stream);
 // Head panels.  launch_panel: every workgroup (group, class) sums its entries times rows of the
 // staged head Xh into LDS accumulators and stores them to part[class][slot][0:k].
@@ -279,6 +281,7 @@ struct SampledArgs {
   const uint32_t* chunk_ptr; const uint32_t* chunk_mid; const int32_t* chunk_row;
   const uint32_t* rows_ptr; const uint32_t* rows_mid; const int32_t* rows_row;
   const uint32_t* rows_win; const int32_t* perm;
+  int32_t head_stride;                  // floats from one row of Vh to the next (those of V are k apart)
   const Entry* ent; const uint32_t* emap;
   const float* U; const float* V; const float* Vh;
   float* S;

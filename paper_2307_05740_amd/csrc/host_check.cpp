@@ -39,7 +39,7 @@ namespace arrow {
 int launch_product(ProductArgs, int, int64_t, int64_t, int64_t, bool, bool, int64_t, int32_t, void*) { reached("launch_product"); }
 bool same_shape(int32_t, int32_t, int32_t, bool) { reached("same_shape"); }
 int launch_reduce(const uint32_t*, const int32_t*, int64_t, const float*, float*, int32_t, bool, void*) { reached("launch_reduce"); }
-int launch_gather(const int32_t*, int64_t, const float*, float*, int32_t, void*) { reached("launch_gather"); }
+int launch_gather(const int32_t*, int64_t, const float*, float*, int32_t, int32_t, void*) { reached("launch_gather"); }
 int launch_panel(const uint32_t*, const int32_t*, const Entry*, int64_t, const float*, int64_t, float*, int32_t, void*) { reached("launch_panel"); }
 int launch_panel_combine(const int32_t*, int64_t, const float*, float*, int32_t, void*) { reached("launch_panel_combine"); }
 int launch_sddmm_panel(const uint32_t*, const int32_t*, const Entry*, const uint32_t*, int64_t, const float*,

@@ -87,7 +87,6 @@ __device__ __forceinline__ void row_items(const uint32_t* ptr, const uint32_t* m
   constexpr int GPB = kBlock / LPR;
   constexpr uint32_t U = 8;
   const int tid = threadIdx.x;
-  const uint32_t row_bytes = 4u * (uint32_t)a.k;
   const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
   const uint32_t e0 = ptr[0];
   auto run = [&](auto entry) {
@@ -98,6 +97,7 @@ __device__ __forceinline__ void row_items(const uint32_t* ptr, const uint32_t* m
       V acc = vzero<VEC>();
       for (int seg = 0; seg < 2; ++seg) {
         const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Xh : a.X);
+        const uint32_t row_bytes = 4u * (uint32_t)(seg == 0 ? a.head_stride : a.k);
         const uint32_t j_hi = seg == 0 ? mid : hi;
         for (uint32_t j = seg == 0 ? lo : mid; j < j_hi; j += U) {
           Entry e[U];
@@ -179,7 +179,6 @@ __device__ __forceinline__ void chunk_part(Entry* mine, const ProductArgs& a, co
   if (lo == hi) return;                // padding slot of the die queues
   const uint32_t lane = threadIdx.x % 64;
   const uint32_t g = lane / LPR;
-  const uint32_t row_bytes = 4u * (uint32_t)a.k;
   const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
   const Entry* grp = mine + g;
   const int64_t ch0 = ch - ch % kChunksPerGroup;
@@ -192,6 +191,7 @@ __device__ __forceinline__ void chunk_part(Entry* mine, const ProductArgs& a, co
   for (int q = 0; q < NA; ++q) ahead[q] = a.ent[lo + lane + q * 64 < hi ? lo + lane + q * 64 : lo];
   for (int seg = 0; seg < 2; ++seg) {
     const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Xh : a.X);
+    const uint32_t row_bytes = 4u * (uint32_t)(seg == 0 ? a.head_stride : a.k);
     const uint32_t s_lo = seg == 0 ? lo : mid;
     const uint32_t s_hi = seg == 0 ? mid : hi;
     for (uint32_t b0 = s_lo; b0 < s_hi; b0 += STRIP) {
@@ -353,7 +353,6 @@ __global__ __launch_bounds__(kBlock, 6) void flow_kernel(const ProductArgs a) {
   const int lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const LaneColumns lc = lane_columns<VEC>(tid % LPR, (int)blockIdx.y * a.width, a.k, a.width);
-  const uint32_t row_bytes = 4u * (uint32_t)a.k;
   const uint32_t col_bytes = lc.ok ? 4u * (uint32_t)lc.c : 0u;
   const int64_t step = gridDim.x;
   auto items_of = [&](int64_t bt) {
@@ -401,6 +400,7 @@ __global__ __launch_bounds__(kBlock, 6) void flow_kernel(const ProductArgs a) {
       V acc = vzero<VEC>();
       for (int seg = 0; seg < 2; ++seg) {
         const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Xh : a.X);
+        const uint32_t row_bytes = 4u * (uint32_t)(seg == 0 ? a.head_stride : a.k);
         const uint32_t j_hi = seg == 0 ? mid : hi;
         for (uint32_t j = seg == 0 ? b.lo[it] : mid; j < j_hi; j += U) {
           Entry e[U];
@@ -1164,13 +1164,13 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(
 template <int VEC, int LPR>
 __global__ __launch_bounds__(kBlock) void gather_kernel(const int32_t* __restrict__ perm,
                                                         int64_t n_i, const float* __restrict__ X,
-                                                        float* __restrict__ Xp, int k) {
+                                                        float* __restrict__ Xp, int k, int stride) {
   constexpr int GPB = kBlock / LPR;
   const int64_t p = (int64_t)blockIdx.x * GPB + threadIdx.x / LPR;
   const LaneColumns lc = lane_columns<VEC>(threadIdx.x % LPR, blockIdx.y * (LPR * VEC), k);
   const int c = lc.c;
   if (p >= n_i || !lc.ok) return;
-  gstore<VEC>(Xp + (size_t)p * (size_t)k + c, gload<VEC>(X + (size_t)perm[p] * (size_t)k + c));
+  gstore<VEC>(Xp + (size_t)p * (size_t)stride + c, gload<VEC>(X + (size_t)perm[p] * (size_t)k + c));
 }
 
 }  // namespace
@@ -1290,7 +1290,7 @@ int launch_reduce(const uint32_t* split_ptr, const int32_t* split_y, int64_t n_s
 }
 
 int launch_gather(const int32_t* perm, int64_t n_i, const float* X, float* Xp, int32_t k,
-                  void* stream) {
+                  int32_t stride, void* stream) {
   if (n_i <= 0) return 0;
   const Shape s = pick_shape(k, 0);
   return dispatch_shape(s, [&](auto V, auto L) -> int {
@@ -1299,7 +1299,7 @@ int launch_gather(const int32_t* perm, int64_t n_i, const float* X, float* Xp, i
     if (blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
     dim3 grid((unsigned)blocks, (unsigned)s.slices);
     hipLaunchKernelGGL((gather_kernel<VEC, LPR>), grid, dim3(kBlock), 0, (hipStream_t)stream, perm,
-                       n_i, X, Xp, (int)k);
+                       n_i, X, Xp, (int)k, (int)stride);
     return (int)hipGetLastError();
   });
 }

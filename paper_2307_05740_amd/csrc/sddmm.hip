@@ -49,10 +49,9 @@ struct alignas(16) SampledShared {
 // NB entries' rows of V (valid where ok) against the row of U, all k columns.  `get(u)` names the row of
 // entry u; rows of entries that are not ok are not read.
 template <int VEC, int LPR, int NB, bool SMALL, typename Row, typename Ok>
-__device__ __forceinline__ float dots(const SampledArgs& a, const char* base, const float* Urow,
+__device__ __forceinline__ float dots(const SampledArgs& a, const char* base, uint32_t row_bytes, const float* Urow,
                                       typename Vec<VEC>::type u0, int l, const LaneColumns lc0, Row&& row, Ok&& ok) {
   using V = typename Vec<VEC>::type;
-  const uint32_t row_bytes = 4u * (uint32_t)a.k;
   float p[NB];
   {
     V x[NB];
@@ -116,6 +115,7 @@ __device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const 
   drop_shared(u0, lc0.shared);
   for (int seg = 0; seg < 2; ++seg) {
     const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Vh : a.V);
+    const uint32_t row_bytes = 4u * (uint32_t)(seg == 0 ? a.head_stride : a.k);
     const uint32_t s_lo = seg == 0 ? lo : mid;
     const uint32_t s_hi = seg == 0 ? mid : hi;
     for (uint32_t b0 = s_lo; b0 < s_hi; b0 += 64) {
@@ -132,7 +132,7 @@ __device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const 
       // round's rows arrive while this one's are multiplied.  (R-MAT 60k, k = 32: 18.4 -> 16.4 us; 100k, 200: 148 -> 132; shared
       // chunks lose, 16k, 64: 8.9 -> 9.3, and the registers cost the long lists and the rows their occupancy.)
       if (AHEAD && a.k <= LPR * VEC) {
-        const uint32_t row_bytes = 4u * (uint32_t)a.k, col_bytes = lc0.ok ? 4u * (uint32_t)lc0.c : 0u;
+        const uint32_t col_bytes = lc0.ok ? 4u * (uint32_t)lc0.c : 0u;
         auto load = [&](V (&x)[NB], uint32_t s) {
 #pragma unroll
           for (int u = 0; u < NB; ++u) {
@@ -169,10 +169,10 @@ __device__ __forceinline__ void sampled_chunk(Entry* ents, uint32_t* ats, const 
       for (uint32_t s = 0; s * G < nb; s += NB) {   // round s + u: lane group g handles entry (s + u) * G + g
         float dot;
         if ((s + NB) * G <= nb)
-          dot = dots<VEC, LPR, NB, SMALL>(a, base, Urow, u0, (int)l, lc0,
+          dot = dots<VEC, LPR, NB, SMALL>(a, base, row_bytes, Urow, u0, (int)l, lc0,
                                           [&](int u) { return ents[(s + u) * G + g].xrow; }, [](int) { return true; });
         else
-          dot = dots<VEC, LPR, NB, SMALL>(a, base, Urow, u0, (int)l, lc0,
+          dot = dots<VEC, LPR, NB, SMALL>(a, base, row_bytes, Urow, u0, (int)l, lc0,
                                           [&](int u) { return ents[((s + u) * G + g) % 64].xrow; },
                                           [&](int u) { return (s + u) * G + g < nb; });
         const uint32_t idx = (s + l / SPAN) * G + g;
@@ -300,10 +300,11 @@ __device__ __forceinline__ void sampled_rows(SampledShared& sh, const SampledArg
       drop_shared(u0, lc0.shared);
       for (int seg = WINDOW ? 1 : 0; seg < 2; ++seg) {
         const char* base = reinterpret_cast<const char*>(seg == 0 ? a.Vh : a.V);
+        const uint32_t row_bytes = 4u * (uint32_t)(seg == 0 ? a.head_stride : a.k);
         const uint32_t j_lo = WINDOW || seg == 0 ? lo : mid, j_hi = seg == 0 ? mid : hi;
         for (uint32_t j = j_lo + skip; j < j_hi; j += NB * (uint32_t)share) {
           const float dot = dots<VEC, LPR, NB, SMALL>(
-              a, base, Urow, u0, (int)l, lc0, [&](int u) { return sh.ent[(j + u < j_hi ? j + u : j) - b0].xrow; },
+              a, base, row_bytes, Urow, u0, (int)l, lc0, [&](int u) { return sh.ent[(j + u < j_hi ? j + u : j) - b0].xrow; },
               [&](int u) { return j + u < j_hi; });
           const uint32_t mine = j + l / SPAN;
           if (l % SPAN == 0 && mine < j_hi) a.S[sh.at[mine - b0]] = sh.ent[mine - b0].val * dot;

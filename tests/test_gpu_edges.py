@@ -751,3 +751,63 @@ def test_what_the_native_calls_hand_to_the_library(torch):
                 assert call(*[bad if q == place else g for q, g in enumerate(good)]) == 0, (place, bad)
         assert call(*[torch.cat([t, t], 1) if t.dim() == 2 else t for t in good]) == 0   # more columns than the workspace has room for
         assert not called
+
+
+@pytest.mark.parametrize("k", [12, 17, 20, 63, 64, 90, 100, 127, 150])
+@pytest.mark.parametrize("kc", [0, 32])
+def test_staged_head_in_whole_lines(torch, k, kc):
+    """Where there is room the staged head is laid out in whole 128-byte lines (17, 20, 63, 90, 127, 150), else with its
+    rows close together: the same results bit for bit, and nothing behind the workspace is written."""
+    w = synth.make_config(2, 8)
+    op = binding.ArrowSpMM(*csr_of(w), w.b, options=binding.arrow_options_default(stage_short=1, window_rows=1024, kc=kc))
+    n, h, st = w.n, op.h, torch.cuda.current_stream().cuda_stream
+    X, U = (synth.normal_matrix(n, k, seed=s) for s in (18, 19))
+    Xd, Ud = torch.from_numpy(X).cuda(), torch.from_numpy(U).cuda()
+    S0 = op.sddmm(Ud, Xd)
+    full = binding.arrow_workspace_bytes(h, k)
+    xy = -(-n * k * 4 // 256) * 256
+    ws = torch.empty(full + xy + 4096, dtype=torch.uint8, device="cuda")
+
+    def all_of(nbytes, l):
+        ws.fill_(0xA5)
+        binding.arrow_set_workspace(h, ws.data_ptr(), nbytes)
+        Y, S, Z = torch.full((n, k), float("nan"), device="cuda"), torch.full_like(S0, float("nan")), Xd.clone()
+        binding.arrow_spmm(h, Xd.data_ptr(), Y.data_ptr(), k, st)
+        binding.arrow_sddmm(h, Ud.data_ptr(), Xd.data_ptr(), S.data_ptr(), k, st)
+        if l:
+            binding.arrow_spmm_iter(h, Z.data_ptr(), k, l, st)
+        assert bool((ws[nbytes:] == 0xA5).all())
+        return [t.cpu().numpy().view(np.uint32) for t in (Y, S, Z)]
+
+    def accepted(nbytes):
+        try:
+            all_of(nbytes, 0)
+        except binding.ArrowError as e:
+            assert e.code == binding.ARROW_ETOOSMALL
+            return False
+        return True
+
+    low, least = 0, full // 256            # the least workspace of a product, in units of 256 bytes
+    while least - low > 1:
+        m = (low + least) // 2
+        low, least = (low, m) if accepted(256 * m) else (m, least)
+    close = all_of(256 * least, 0)
+    Yref, B = oracle.spmm(*csr_of(w), X)
+    assert_within(close[0].view(np.float32), Yref, B)
+    Sref, Bs = oracle.sddmm(*csr_of(w), U, X)
+    assert_within(close[1].view(np.float32), Sref, Bs)
+    for l in (2, 3):
+        few = all_of(256 * least + xy, l)
+        for nbytes in (full, full + xy):
+            for a, b in zip(few, all_of(nbytes, l)):
+                assert np.array_equal(a, b)
+        assert np.array_equal(few[0], close[0]) and np.array_equal(few[1], close[1])
+    binding.arrow_set_workspace(h, ws.data_ptr(), full)            # an operand where only chained products write
+    V, S = ws[256 * least:256 * least + n * k * 4].view(torch.float32).view(n, k), torch.full_like(S0, float("nan"))
+    V.copy_(Xd)
+    binding.arrow_sddmm(h, Ud.data_ptr(), V.data_ptr(), S.data_ptr(), k, st)
+    assert np.array_equal(S.cpu().numpy().view(np.uint32), close[1]) and torch.equal(V, Xd)
+    Y = torch.full((n, k), float("nan"), device="cuda")
+    binding.arrow_spmm_static(h, Xd.data_ptr(), Y.data_ptr(), k, st)
+    assert np.array_equal(Y.cpu().numpy().view(np.uint32), close[0])
+    op.close()
