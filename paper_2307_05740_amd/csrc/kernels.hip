@@ -619,14 +619,16 @@ __global__ __launch_bounds__(BLOCK, BLOCK / 256 * (kWinFloats / FLOATS)) void wi
   };
   // The scheduler prefers the oldest wavefronts of a SIMD: they were through with their rows after 17.6 us, the youngest after
   // 27.6, alone at the end.  With lower priorities for those that have fewer rows left they end after 20 to 22.7 us (512
-  // blocks of 512 with 48 entries per row, k = 128, 136.1 -> 123.8 us of a product; 300k, 50 entries, 96: 176.5 -> 160.2; 500k, 60, 16:
-  // 82.2 -> 75.4).  Not in the form of eight wavefronts, two workgroups of a compute unit would hold each other up (600k, 26, 32: 97 -> 98 us).
+  // blocks of 512 with 48 entries per row, k = 128, 136.1 -> 123.8 us of a product; 300k, 50 entries, 96: 176.5 -> 160.2).  Not where two
+  // workgroups share a compute unit: the one that sums holds up the other one's staging (437k, 62, 16: 71 -> 80 us of the kernel; 500k, 60, 16:
+  // 82 -> 75 of a product; in the form of eight wavefronts 600k, 26, 32: 97 -> 98).
+  constexpr bool RANKED = FLOATS == kWinFloats;
   uint32_t left = (n_rows + GPB - 1) / GPB;          // rows to go, this one included
-  if (BLOCK == kWinBlock && left > 3) __builtin_amdgcn_s_setprio(3);
+  if (RANKED && left > 3) __builtin_amdgcn_s_setprio(3);
   for (uint32_t i = grp; i < n_rows; i += GPB, --left) {
-    if (BLOCK == kWinBlock && left == 3) __builtin_amdgcn_s_setprio(2);
-    if (BLOCK == kWinBlock && left == 2) __builtin_amdgcn_s_setprio(1);
-    if (BLOCK == kWinBlock && left == 1) __builtin_amdgcn_s_setprio(0);
+    if (RANKED && left == 3) __builtin_amdgcn_s_setprio(2);
+    if (RANKED && left == 2) __builtin_amdgcn_s_setprio(1);
+    if (RANKED && left == 1) __builtin_amdgcn_s_setprio(0);
     const Row r_nn = describe(i + 2 * GPB);
     fetch(r_n, o_n, e_n);
     acc = vzero<VEC>();
