@@ -149,8 +149,11 @@ int arrow_upload(arrow_handle *h, void *dev_buf, size_t bytes, void *stream);
  * largest level, the staged head rows, the results of the corner and panel
  * work items, plus one n x k buffer for the chained products of
  * arrow_spmm_iter; and, where the rows of a staged head of k columns are faster in whole
- * 128-byte lines, room for it, without which everything works as well.  arrow_set_workspace binds caller-owned device memory
- * (256-byte aligned); it may be rebound at any time the stream is idle.
+ * 128-byte lines, room for it behind that buffer, without which everything works as well.  arrow_set_workspace binds caller-owned device memory
+ * (256-byte aligned); it may be rebound at any time the stream is idle.  Every call may write what is bound, except that
+ * only chained products write the n x k buffer, and that the image, the entry map and the operands of a
+ * sampled product are left alone where they lie behind the part that every product needs (those of the other
+ * products are refused there).
  */
 size_t arrow_workspace_bytes(const arrow_handle *h, int32_t k);
 int arrow_set_workspace(arrow_handle *h, void *dev_ws, size_t bytes);

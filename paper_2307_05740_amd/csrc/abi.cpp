@@ -77,7 +77,7 @@ struct arrow_handle {
 namespace {
 
 // workspace layout: [partial vectors][staged head rows][panel class results][corner item results]
-//                   [n x k buffer of the chained products]
+//                   [n x k buffer of the chained products][a staged head in whole lines (head_room)]
 size_t partial_bytes(const arrow_handle* h, int32_t k) {
   return align_up((size_t)h->img.max_partials * (size_t)k * sizeof(float));
 }
@@ -165,9 +165,6 @@ constexpr int64_t kFewRows = 16384;    // and so does this one
 
 // Scratch memory that a call does not need: none, or some at a multiple of kAlign
 struct Spare { unsigned char* at; size_t bytes; };
-Spare spare_after(const arrow_handle* h, size_t used) {
-  return used < h->ws_bytes ? Spare{h->ws + used, h->ws_bytes - used} : Spare{nullptr, 0};
-}
 
 // Whether a level's head may be laid out in whole lines: the panels, the corner and the classes read it with rows close together.
 // A head of at most half of the rows, in rows of at most twice the bytes, is no larger than X: 32-bit offsets that hold in X hold in it.
@@ -199,6 +196,18 @@ float* head_buffer(const arrow::LevelImage& im, int32_t k, float* stage, const S
   const bool whole = columns > k && whole_lines(im) && spare.bytes >= (size_t)im.n_stage * (size_t)columns * sizeof(float);
   *stride = whole ? columns : k;
   return whole ? reinterpret_cast<float*>(spare.at) : stage;
+}
+
+// The room for a head in whole lines: behind the first `used` bytes of the workspace, which are those that every product needs and the n x k
+// buffers of the chained products, so that what a caller keeps in the buffers between those is left alone; none where the workspace
+// ends before it, or where the image or the entry map lie in it.
+Spare head_room(const arrow_handle* h, int32_t k, size_t used) {
+  const size_t bytes = head_bytes(h, k);
+  if (bytes == 0 || h->ws_bytes < used + bytes) return Spare{nullptr, 0};
+  const Spare room{h->ws + used, bytes};
+  const bool taken = ranges_overlap(h->dev, h->img.bytes.size(), room.at, room.bytes) ||
+                     (h->dev_map && ranges_overlap(h->dev_map, sizeof(uint32_t) * h->img.entry_src.size(), room.at, room.bytes));
+  return taken ? Spare{nullptr, 0} : room;
 }
 
 // one product, src -> dst (device, n x k), all levels in stream order.  `ws` holds the partial
@@ -336,8 +345,8 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
 int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_out, int32_t k,
                     hipStream_t stream) {
   float* stage = reinterpret_cast<float*>(h->ws + partial_bytes(h, k));
-  Spare spare = spare_after(h, scratch_bytes(h, k));     // (a caller may keep operands in the part that only chained products use)
   const size_t xy = (size_t)h->n * (size_t)k * sizeof(float);
+  Spare spare = head_room(h, k, scratch_bytes(h, k) + align_up(xy));
   if (ranges_overlap(U, xy, spare.at, spare.bytes) || ranges_overlap(V, xy, spare.at, spare.bytes) ||
       ranges_overlap(S_out, (size_t)h->nnz * sizeof(float), spare.at, spare.bytes))
     spare = Spare{nullptr, 0};
@@ -632,7 +641,8 @@ int arrow_spmm(arrow_handle* h, const float* X, float* Y, int32_t k, void* strea
   rc = check_operands(h, X, Y, k, h->ws, h->ws_bytes);
   if (rc) return rc;
   h->spans_used = 0;
-  return product(h, X, Y, k, (hipStream_t)stream, h->ws, spare_after(h, scratch_bytes(h, k)), true);
+  return product(h, X, Y, k, (hipStream_t)stream, h->ws,
+                 head_room(h, k, scratch_bytes(h, k) + align_up((size_t)h->n * (size_t)k * sizeof(float))), true);
 }
 
 int arrow_spmm_static(arrow_handle* h, const float* X, float* Y, int32_t k, void* stream) {
@@ -668,10 +678,11 @@ int arrow_spmm_iter(arrow_handle* h, float* X, int32_t k, int32_t l, void* strea
   // buffer in the workspace the last three go X -> tmp -> tmp2 -> X; else the result is copied back.
   float* tmp2 = l >= 3 && l % 2 == 1 && h->ws_bytes >= scratch_bytes(h, k) + 2 * xy
                     ? reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(tmp) + xy) : nullptr;
+  const Spare spare = head_room(h, k, scratch_bytes(h, k) + (tmp2 ? 2 : 1) * xy);
   float* src = X;
   for (int32_t t = 0; t < l; ++t) {
     float* dst = tmp2 && t == l - 2 ? tmp2 : (src == X ? tmp : X);
-    rc = product(h, src, dst, k, (hipStream_t)stream, h->ws, spare_after(h, scratch_bytes(h, k) + (tmp2 ? 2 : 1) * xy), true);
+    rc = product(h, src, dst, k, (hipStream_t)stream, h->ws, spare, true);
     if (rc) return rc;
     src = dst;
   }

@@ -1,0 +1,160 @@
+// What the library's calls hand to their kernels: the launches are recorded instead of made, by name and with the arguments that the
+// cases below look at.  No device memory is touched, so the pointers are made up.  `launch_arguments <case>`; exit status 0 = as it has to be.
+#include <hip/hip_runtime_api.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "arrow.h"
+#include "arrow_internal.h"
+
+namespace {
+
+struct Launch {
+  std::string kernel;
+  arrow::ProductArgs product;      // of a kernel that takes one
+  arrow::SampledArgs sampled;      // of a kernel that takes one
+  const unsigned char* head;       // of gather_kernel: its result, rows of it, and the floats between those
+  int64_t rows;
+  int stride;
+};
+std::vector<Launch>& launches() { static std::vector<Launch> l; return l; }
+std::map<const void*, std::string>& names() { static std::map<const void*, std::string> n; return n; }
+dim3 pushed_grid, pushed_block;
+
+}  // namespace
+
+extern "C" {
+void __hipRegisterFunction(void**, const void* function, char*, const char* name, unsigned, void*, void*, dim3*, dim3*, int*) { names()[function] = name; }
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t) { pushed_grid = grid; pushed_block = block; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hipStream_t* stream) {
+  *grid = pushed_grid; *block = pushed_block; *shared = 0; *stream = nullptr;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* function, dim3, dim3, void** args, size_t, hipStream_t) {
+  Launch l{};
+  l.kernel = names()[function];
+  if (l.kernel.find("ProductArgs") != std::string::npos) l.product = *static_cast<const arrow::ProductArgs*>(args[0]);
+  if (l.kernel.find("SampledArgs") != std::string::npos) l.sampled = *static_cast<const arrow::SampledArgs*>(args[0]);
+  if (l.kernel.find("13gather_kernel") != std::string::npos) {
+    l.rows = *static_cast<const int64_t*>(args[1]);
+    l.head = *static_cast<unsigned char* const*>(args[3]);
+    l.stride = *static_cast<const int*>(args[5]);
+  }
+  launches().push_back(l);
+  return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipGetDevice(int*) { return hipErrorNoDevice; }
+hipError_t hipEventCreate(hipEvent_t*) { return hipErrorNoDevice; }
+}
+
+namespace {
+
+unsigned char* address(int which) { return reinterpret_cast<unsigned char*>((uintptr_t)(which + 1) << 44); }
+float* floats(int which) { return reinterpret_cast<float*>(address(which)); }
+size_t up(size_t bytes) { return (bytes + 255) / 256 * 256; }
+bool disjoint(const unsigned char* a, size_t a_bytes, const unsigned char* b, size_t b_bytes) { return a + a_bytes <= b || b + b_bytes <= a; }
+
+uint64_t state = 1;
+uint32_t below(uint32_t n) { state = state * 6364136223846793005ull + 1442695040888963407ull; return (uint32_t)((state >> 33) % n); }
+
+// An operand with the given number of entries in every row.
+arrow_handle* operand(const std::vector<int>& entries, uint32_t columns, int32_t b, const arrow_options_t& options) {
+  const int64_t n = (int64_t)entries.size();
+  std::vector<int64_t> ptr(1, 0);
+  std::vector<int32_t> col;
+  for (int m : entries) {
+    std::vector<int32_t> row;
+    while ((int)row.size() < m) {
+      row.push_back((int32_t)below(columns));
+      std::sort(row.begin(), row.end());
+      row.erase(std::unique(row.begin(), row.end()), row.end());
+    }
+    col.insert(col.end(), row.begin(), row.end());
+    ptr.push_back((int64_t)col.size());
+  }
+  const std::vector<float> val(col.size(), 1.f);
+  arrow_handle* h = nullptr;
+  if (arrow_decompose_with(n, ptr.data(), col.data(), val.data(), b, &options, &h) != 0) std::printf("%s\n", arrow_last_error());
+  return h;
+}
+
+// An operand whose head is staged, and the least workspace of a product with it.
+constexpr int64_t kRows = 4096;
+arrow_handle* staged_operand() {
+  arrow_options_t o;
+  arrow_options_default(&o);
+  o.stage_short = 1; o.window_rows = 1024;
+  std::vector<int> entries(kRows);
+  for (int& m : entries) m = 4 + (int)below(30);
+  arrow_handle* h = operand(entries, kRows, 512, o);
+  if (h && (arrow_upload(h, address(0), arrow_device_bytes(h), nullptr) || arrow_sddmm_upload(h, address(1), arrow_sddmm_device_bytes(h), nullptr))) return nullptr;
+  return h;
+}
+size_t least_workspace(arrow_handle* h, int32_t k) {
+  size_t low = 0, least = arrow_workspace_bytes(h, k) / 256;
+  while (least - low > 1) {
+    const size_t m = (low + least) / 2;
+    arrow_set_workspace(h, address(2), 256 * m);
+    if (arrow_spmm(h, floats(3), floats(4), k, nullptr) == 0) least = m; else low = m;
+  }
+  launches().clear();
+  return 256 * least;
+}
+
+// Every call that stages a head; each has to leave [kept, kept + bytes) alone.  `whole`: counts the heads laid out in whole lines.
+bool leaves_alone(arrow_handle* h, int32_t k, const unsigned char* kept, size_t bytes, int* whole) {
+  launches().clear();
+  int rc = arrow_spmm(h, floats(3), floats(4), k, nullptr);
+  if (rc == 0) rc = arrow_sddmm(h, floats(3), floats(4), floats(5), k, nullptr);
+  if (rc) { std::printf("rc %d (%s)\n", rc, arrow_last_error()); return false; }
+  int heads = 0;
+  for (const Launch& l : launches()) {
+    if (!l.head) continue;
+    ++heads;
+    if (l.stride > k) ++*whole;
+    if (!disjoint(l.head, (size_t)l.rows * (size_t)l.stride * 4, kept, bytes)) { std::printf("a head over what is kept, %d floats a row\n", l.stride); return false; }
+  }
+  return heads == 2;
+}
+
+// The head in whole lines lies where only the workspace asked for it, whatever else a caller keeps in a workspace larger than the least.
+int buffers_in_the_workspace() {
+  arrow_handle* h = staged_operand();
+  if (!h) return 1;
+  int whole = 0;
+  for (int32_t k : {17, 50, 63, 127}) {
+    const size_t least = least_workspace(h, k), xy = up((size_t)kRows * (size_t)k * 4), full = arrow_workspace_bytes(h, k);
+    unsigned char* ws = address(2);
+    // an operand of another call in the part that only chained products write
+    arrow_set_workspace(h, ws, full);
+    if (!leaves_alone(h, k, ws + least, xy, &whole) || whole == 0) return 1;
+    const size_t map = arrow_sddmm_device_bytes(h), image = arrow_device_bytes(h);
+    for (size_t at : {least, least + xy / 2 / 256 * 256, least + xy, full - 256, full}) {
+      arrow_set_workspace(h, ws, full + std::max(map, image));
+      arrow_sddmm_upload(h, ws + at, map, nullptr);
+      if (!leaves_alone(h, k, ws + at, map, &whole)) { std::printf("entry map, k = %d\n", k); return 1; }
+      arrow_sddmm_upload(h, address(1), map, nullptr);
+      if (at < least + xy) continue;             // (products are refused where Y overlaps the image, chained ones write all before)
+      arrow_upload(h, ws + at, image, nullptr);
+      if (!leaves_alone(h, k, ws + at, image, &whole)) { std::printf("image, k = %d\n", k); return 1; }
+      arrow_upload(h, address(0), image, nullptr);
+    }
+  }
+  arrow_destroy(h);
+  return 0;
+}
+
+}  // namespace
+
+int main(int, char** argv) {
+  const std::string c = argv[1];
+  if (c == "buffers in the workspace") return buffers_in_the_workspace();
+  return 2;
+}

@@ -1,0 +1,28 @@
+"""What the library's calls hand to their kernels, recorded on the CPU (launch_arguments.cpp) with the library as it was built."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2307_05740_amd import _build
+
+
+@pytest.fixture(scope="module")
+def launch_arguments(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("launch_arguments") / "launch_arguments")
+    rocm = os.path.dirname(os.path.dirname(_build._hipcc()))
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"),
+                    "-I", os.path.join(_build.REPO_DIR, "include"), "-I", os.path.join(_build.PKG_DIR, "csrc"),
+                    os.path.join(_build.REPO_DIR, "tests", "launch_arguments.cpp"), _build.ARROW_LIB,
+                    f"-Wl,-rpath,{_build.PKG_DIR}", "-L", os.path.join(rocm, "lib"), "-lamdhip64", "-o", out], check=True)
+
+    def run(case):
+        proc = subprocess.run([out, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+        assert proc.returncode == 0, proc.stdout
+
+    return run
+
+
+def test_a_staged_head_leaves_alone_what_a_caller_keeps_in_the_workspace(launch_arguments):
+    """An entry map or an image there is read by the very product, operands by another one."""
+    launch_arguments("buffers in the workspace")
