@@ -286,6 +286,8 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
       // us; R-MAT 7914, k = 135: 16.0 -> 11.3 us; the head rows beside 511 window tiles of 512 rows, k = 128, 13.3 ->
       // 8.9 us).  A profiled product keeps the lists apart so that each has a time of its own.
       using namespace arrow;
+      const bool one_launch = same_shape(k, tune.kc, short_kc, acc) || (im.n_chunks <= kFewChunks && im.n_rows <= kFewRows);
+      a.together = one_launch ? kPartAll : kPartChunks | kPartPieces;
       int rc = ARROW_OK;
       if (h->profiling && prof) {
         if (im.n_chunks > 0) { Scoped sc(h, kChunks, (int)li, stream); rc = launch(kPartChunks, tune.kc); }
@@ -294,8 +296,7 @@ int product(arrow_handle* h, const float* X, float* Y, int32_t k, hipStream_t st
           rc = launch(kPartPieces, tune.kc);
           if (!rc) rc = launch(kPartShort, short_kc);
         }
-      } else if (same_shape(k, tune.kc, short_kc, acc) ||
-                 (im.n_chunks <= kFewChunks && im.n_rows <= kFewRows)) {
+      } else if (one_launch) {
         rc = launch(kPartAll, tune.kc);
       } else {
         rc = launch(kPartChunks | kPartPieces, tune.kc);

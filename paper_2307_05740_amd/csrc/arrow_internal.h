@@ -230,6 +230,7 @@ struct ProductArgs {
   uint32_t sets_log;                    // logarithm of the sets of dies that the slices are dealt to (0: every die works on all)
   int32_t width;                        // columns per slice
   int32_t piece_waves;                  // a piece per wavefront instead of per lane group
+  int32_t together;                     // parts that share a launch where the product is not profiled (0: those of this launch)
   int32_t entries_once;                 // the entries are too many to be found in a cache the next time
   uint32_t run;                         // workgroups of the wave list that a die takes one after the other (die_run), or 0
 };

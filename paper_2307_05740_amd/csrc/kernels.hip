@@ -1193,14 +1193,15 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
   // of the 256 compute units without one (71 K pieces of R-MAT 1m, k = 64: 56 -> 44 us).  Pieces are
   // up to three times as long as short rows.
   const int least = kBlock / s.lpr < kItemsPerGroupBlock ? kBlock / s.lpr : kItemsPerGroupBlock;
-  for (int p = 1; p < 4; ++p) {
+  auto items_of = [&](int p, int64_t count) {
     int items = kItemsPerGroupBlock;
     if (!(p == 1 && die_queues)) {
       if (p == 1) items = kItemsPerGroupBlock / 4;
-      while (items > least && a.count[p] < (int64_t)items * 2048) items >>= 1;
+      while (items > least && count < (int64_t)items * 2048) items >>= 1;
     }
-    a.items[p] = items;
-  }
+    return items;
+  };
+  for (int p = 1; p < 4; ++p) a.items[p] = items_of(p, a.count[p]);
   // A piece is some 30 entries: eight to sixteen lane groups finish one in a round or two of row
   // loads where a lane group on its own needs four to six in a row.  Worth the idle lanes only where
   // latency decides, in a list of at most a few pieces per SIMD.
@@ -1209,9 +1210,12 @@ int launch_product(ProductArgs a, int parts, int64_t n_pieces, int64_t n_rows, i
   // but no more than some three rounds; just below six two ranks in five lose by up to 10 %.  (Ten thousand lists of 2500 to 100 K vertices, R-MAT and Chung-Lu: up
   // to 1024 workgroups 0.74 to 1.05 times the time, 0.93 on average, 1024 to 1536 0.98, 1536 to 4000 0.97, beyond 1.0 to 1.04.  us: R-MAT 2504, k = 40, 6.7 -> 5.2;
   // 12.6 K, 10.3 -> 9.3; Chung-Lu 15 K, 14.2 -> 13.1; but R-MAT 3850, k = 200, 8.0 and 8.8, Chung-Lu 97 K, k = 40, 29.6 and 31.9.)
+  // Of the workgroups of all lists that share the launch of a product that is not profiled: what adds up a piece decides about the bits of its sum.
   if (!die_queues && !windows && s.lpr == 16 && a.count[1] > 0) {
+    const int together = a.together ? a.together : parts;
+    const int64_t counts[3] = {together & kPartChunks ? n_long : 0, n_pieces, together & kPartShort ? n_rows - n_pieces - n_empty : 0};
     int64_t groups = 0;
-    for (int p = 0; p < 3; ++p) groups += ceil_div(ceil_div(a.count[p], p == 1 ? kBlock / 64 : a.items[p]), kDies) * kDies * s.slices;
+    for (int p = 0; p < 3; ++p) groups += ceil_div(ceil_div(counts[p], p < 2 ? kBlock / 64 : items_of(p, counts[p])), kDies) * kDies * s.slices;
     a.piece_waves = groups <= 4 * kComputeUnits || (groups > 6 * kComputeUnits && groups <= 4000);
   }
   if (a.piece_waves) a.items[1] = kBlock / 64;

@@ -151,10 +151,39 @@ int buffers_in_the_workspace() {
   return 0;
 }
 
+// Pieces of long rows, short rows and rows of several chunks of a product: the launch that holds the pieces gives them the same
+// wavefronts and workgroups where the product is profiled, which launches the lists apart.
+int profiled(int64_t n, int pieces, int shorts, int longs, int32_t k, bool wave) {
+  std::vector<int> entries((size_t)n, 0);
+  for (int64_t i = 0; i < pieces + shorts + longs; ++i) entries[(size_t)i] = i < pieces ? 17 + (int)below(31) : i < pieces + shorts ? 1 + (int)below(15) : 700;
+  arrow_options_t o;
+  arrow_options_default(&o);
+  arrow_handle* h = operand(entries, (uint32_t)n, (int32_t)(n / 16), o);
+  if (!h || arrow_upload(h, address(0), arrow_device_bytes(h), nullptr)) return 1;
+  arrow_set_workspace(h, address(2), (size_t)1 << 40);
+  arrow::ProductArgs seen[2] = {};
+  for (int p = 0; p < 2; ++p) {
+    launches().clear();
+    if (arrow_set_profiling(h, p) || arrow_spmm(h, floats(3), floats(4), k, nullptr)) { std::printf("%s\n", arrow_last_error()); return 1; }
+    for (const Launch& l : launches())
+      if (l.product.count[1] > 0) seen[p] = l.product;
+  }
+  arrow_destroy(h);
+  for (const arrow::ProductArgs& a : seen)
+    std::printf("%lld pieces, %d to a workgroup, a wavefront each: %d\n", (long long)a.count[1], a.items[1], a.piece_waves);
+  return seen[0].count[1] >= pieces && seen[0].count[1] == seen[1].count[1] && seen[0].piece_waves == (wave ? 1 : 0) && seen[1].piece_waves == seen[0].piece_waves &&
+         seen[1].items[1] == seen[0].items[1] ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int, char** argv) {
   const std::string c = argv[1];
+  if (c == "profiled, one launch") return profiled(11000, 2000, 8321, 0, 64, false);
+  if (c == "profiled, one launch, a wavefront each") return profiled(11000, 2000, 8320, 0, 64, true);
+  if (c == "profiled, seven workgroups a unit") return profiled(15000, 4001, 8601, 0, 50, true);
+  if (c == "profiled, slices and chunks") return profiled(11000, 2000, 8321, 40, 200, false);
+  if (c == "profiled, two launches") return profiled(140000, 3000, 60000, 20, 96, true);
   if (c == "buffers in the workspace") return buffers_in_the_workspace();
   return 2;
 }

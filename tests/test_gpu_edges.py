@@ -811,3 +811,33 @@ def test_staged_head_in_whole_lines(torch, k, kc):
     binding.arrow_spmm_static(h, Xd.data_ptr(), Y.data_ptr(), k, st)
     assert np.array_equal(Y.cpu().numpy().view(np.uint32), close[0])
     op.close()
+
+
+@pytest.mark.parametrize("k", [33, 48, 64, 96, 200])
+@pytest.mark.parametrize("n,pieces,short,long", [(11000, 2000, 8321, 0), (11000, 2000, 8321, 40), (15000, 4001, 8601, 0), (140000, 3000, 60000, 20)])
+def test_a_profiled_product_has_the_bits_of_any_other(torch, n, pieces, short, long, k):
+    """With a launch of its own for every list it adds up the pieces of long rows as the one launch does; so does arrow_spmm_static."""
+    rng = np.random.default_rng(n + k)
+    length = np.zeros(n, np.int64)
+    length[:pieces] = rng.integers(17, 49, pieces)
+    length[pieces:pieces + short] = rng.integers(1, 17, short)
+    length[pieces + short:pieces + short + long] = 700
+    rng.shuffle(length)
+    key = np.unique(np.repeat(np.arange(n), length) * n + (n * rng.random(length.sum())).astype(np.int64))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int64)
+    colidx, vals = (key % n).astype(np.int32), rng.uniform(-1, 1, len(key)).astype(np.float32)
+    X = synth.normal_matrix(n, k, seed=35)
+    op = binding.ArrowSpMM(rowptr, colidx, vals, n // 16)
+    Xd, st = torch.from_numpy(X).cuda(), torch.cuda.current_stream().cuda_stream
+    results = []
+    for call in (binding.arrow_spmm, binding.arrow_spmm_static):
+        for profiled in (0, 1):
+            op._ensure_workspace(k)
+            binding.arrow_set_profiling(op.h, profiled)
+            Y = torch.full((n, k), float("nan"), device="cuda")
+            call(op.h, Xd.data_ptr(), Y.data_ptr(), k, st)
+            results.append(Y.cpu().numpy())
+    op.close()
+    assert_within(results[0], *oracle.spmm(rowptr, colidx, vals, X))
+    for Y in results[1:]:
+        assert np.array_equal(Y.view(np.uint32), results[0].view(np.uint32))

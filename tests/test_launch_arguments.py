@@ -26,3 +26,9 @@ def launch_arguments(tmp_path_factory):
 def test_a_staged_head_leaves_alone_what_a_caller_keeps_in_the_workspace(launch_arguments):
     """An entry map or an image there is read by the very product, operands by another one."""
     launch_arguments("buffers in the workspace")
+
+
+@pytest.mark.parametrize("case", ["one launch", "one launch, a wavefront each", "seven workgroups a unit", "slices and chunks", "two launches"])
+def test_a_profiled_product_adds_up_pieces_as_any_other(launch_arguments, case):
+    """Whether a lane group or four of them add up a piece is not for the launch to say that it happens to be in."""
+    launch_arguments("profiled, " + case)
