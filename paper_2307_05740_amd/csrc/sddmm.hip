@@ -444,10 +444,6 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
   const bool small = small_matrix(v_rows, a.k);
   const hipStream_t st = (hipStream_t)stream;
   if (window_rows || die_queues || (windows && s.lpr >= 16) || 2 * a.n_pieces > a.n_rows) a.n_pieces = 0;
-  const Rows rows = window_rows ? Rows::kWindow : a.n_pieces > 0 ? Rows::kShort : unequal ? Rows::kUnequal : Rows::kAlike;
-  const int64_t n_short = a.n_rows - a.n_pieces;
-  a.piece_items = items_of(a.n_pieces, a.nnz_rows, s.lpr, Rows::kPieces, a.n_chunks > 0);
-  a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(n_short, a.nnz_rows, s.lpr, rows, a.n_chunks > 0);
   // Few chunks leave wavefront slots empty, and a chunk of 256 entries is four to 64 rounds of row loads one
   // after the other: wavefronts share it as far as that leaves each a few rounds (nothing has to be
   // combined).  R-MAT 7419, k = 73: 30.7 -> 10.5 us; 12527, k = 128: 33.2 -> 13.7; 51952, k = 128: 50.2 ->
@@ -475,8 +471,20 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
       a.chunk_parts *= 2;
     }
   const int64_t chunk_blocks = ceil_div(ceil_div(a.n_chunks * a.chunk_parts, kBlock / 64), kDies) * kDies;
-  const int64_t piece_blocks = ceil_div(ceil_div(a.n_pieces, a.piece_items), kDies) * kDies;
-  const int64_t row_blocks = piece_blocks + ceil_div(ceil_div(n_short, a.items), kDies) * kDies;
+  int64_t piece_blocks, row_blocks;
+  auto divide = [&] {
+    const Rows rows = window_rows ? Rows::kWindow : a.n_pieces > 0 ? Rows::kShort : unequal ? Rows::kUnequal : Rows::kAlike;
+    const int64_t n_short = a.n_rows - a.n_pieces;
+    a.piece_items = items_of(a.n_pieces, a.nnz_rows, s.lpr, Rows::kPieces, a.n_chunks > 0);
+    a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(n_short, a.nnz_rows, s.lpr, rows, a.n_chunks > 0);
+    piece_blocks = ceil_div(ceil_div(a.n_pieces, a.piece_items), kDies) * kDies;
+    row_blocks = piece_blocks + ceil_div(ceil_div(n_short, a.items), kDies) * kDies;
+  };
+  divide();
+  if (a.n_pieces > 0 && row_blocks + (windows ? 0 : chunk_blocks) > kMostGroups) {   // (more than a grid holds, with workgroups for both it may)
+    a.n_pieces = 0;
+    divide();
+  }
   a.piece_blocks = (uint32_t)piece_blocks;
   a.short_base = (uint32_t)a.n_pieces - a.piece_blocks * (uint32_t)a.items;
   if (chunk_blocks + row_blocks > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;

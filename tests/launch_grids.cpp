@@ -127,6 +127,16 @@ int pieces(int64_t n_pieces, int64_t n_short, int32_t k, bool windows, uint32_t 
   return rc == 0 && launches().size() == 1 && launches()[0].grid.x == groups ? 0 : 1;
 }
 
+// Pieces and short rows in window order that one grid holds with workgroups for both, but not with workgroups of their own.
+int pieces_apart(int64_t n_pieces, int64_t n_short, int32_t k) {
+  arrow::SampledArgs a{};
+  a.U = address(0); a.V = a.Vh = address(1); a.S = address(2);
+  a.n_rows = n_pieces + n_short; a.n_pieces = n_pieces; a.nnz_rows = 8 * a.n_rows; a.k = k;
+  const int rc = arrow::launch_sddmm(a, false, false, true, true, a.n_rows, nullptr);
+  std::printf("rc %d, %zu launches, %u groups\n", rc, launches().size(), launches()[0].grid.x);
+  return rc == 0 && launches().size() == 1 && launches()[0].groups() * arrow::kItemsPerGroupBlock >= (uint64_t)a.n_rows ? 0 : 1;
+}
+
 // Chunks of long rows of a sampled product, in row order: `groups` workgroups of four wavefronts.
 int sampled_chunks(int64_t n_chunks, int64_t nnz, int32_t k, uint32_t groups) {
   arrow::SampledArgs a{};
@@ -178,6 +188,8 @@ int main(int, char** argv) {
   if (c == "pieces, more") return pieces(7000, 6000, 24, false, 1632);
   if (c == "pieces, in window order") return pieces(9000, 300000, 24, true, 568 + 4688);
   if (c == "pieces, in window order, wide") return pieces(9000, 300000, 64, true, 9664);
+  if (c == "pieces and short rows, many") return pieces_apart(200000000, 280000000, 8);
+  if (c == "pieces and short rows, most") return pieces_apart(240000000, 700000000, 24);
   // a wavefront each, or two where chunks are more than a strip, or four where they leave the chip half empty
   if (c == "chunks of a strip") return sampled_chunks(5000, 5000 * 64, 200, 1256);
   if (c == "chunks of a strip and more") return sampled_chunks(5000, 5000 * 64 + 1, 200, 2504);

@@ -64,3 +64,9 @@ def test_pieces_of_long_rows_have_workgroups_of_their_own(launch_grids, case):
 def test_pieces_of_a_product_have_a_wavefront_each_where_it_fits_the_chip(launch_grids, case):
     proc = subprocess.run([launch_grids, "pieces of a product, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert proc.returncode == 0, proc.stdout
+
+
+@pytest.mark.parametrize("case", ["many", "most"])
+def test_pieces_and_short_rows_that_fit_one_grid_are_not_refused(launch_grids, case):
+    proc = subprocess.run([launch_grids, "pieces and short rows, " + case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert proc.returncode == 0, proc.stdout
