@@ -175,6 +175,26 @@ int profiled(int64_t n, int pieces, int shorts, int longs, int32_t k, bool wave)
          seen[1].items[1] == seen[0].items[1] ? 0 : 1;
 }
 
+// A sampled product of long and short rows in window order: `items` of them to a workgroup, which go by the rows without entries, too.
+int sampled_items(int64_t n, int pieces, int shorts, int32_t k, int items) {
+  std::vector<int> entries((size_t)n, 0);
+  for (int i = 0; i < pieces + shorts; ++i) entries[(size_t)i] = i < pieces ? 20 : 2;
+  arrow_options_t o;
+  arrow_options_default(&o);
+  arrow_handle* h = operand(entries, (uint32_t)n, (int32_t)(n / 16), o);
+  if (!h || arrow_upload(h, address(0), arrow_device_bytes(h), nullptr) || arrow_sddmm_upload(h, address(1), arrow_sddmm_device_bytes(h), nullptr)) return 1;
+  arrow_set_workspace(h, address(2), (size_t)1 << 40);
+  if (arrow_sddmm(h, floats(3), floats(4), floats(5), k, nullptr)) { std::printf("%s\n", arrow_last_error()); return 1; }
+  int rc = 1;
+  for (const Launch& l : launches())
+    if (l.sampled.n_rows > 0) {
+      std::printf("%lld rows, %lld pieces apart, %d items to a workgroup\n", (long long)l.sampled.n_rows, (long long)l.sampled.n_pieces, l.sampled.items);
+      rc = l.sampled.n_rows >= pieces + shorts && l.sampled.n_rows < n / 2 && l.sampled.n_pieces == 0 && l.sampled.items == items ? 0 : 1;
+    }
+  arrow_destroy(h);
+  return rc;
+}
+
 }  // namespace
 
 int main(int, char** argv) {
@@ -185,5 +205,9 @@ int main(int, char** argv) {
   if (c == "profiled, slices and chunks") return profiled(11000, 2000, 8321, 40, 200, false);
   if (c == "profiled, two launches") return profiled(140000, 3000, 60000, 20, 96, true);
   if (c == "buffers in the workspace") return buffers_in_the_workspace();
+  // the root of 200 K rows times 160 K entries is 179 K; of the 35 K rows with entries alone 75 K
+  if (c == "items of a sampled product, 48 columns") return sampled_items(200000, 5000, 30000, 48, 16);
+  if (c == "items of a sampled product, 100 columns") return sampled_items(200000, 5000, 30000, 100, 16);
+  if (c == "items of a sampled product, 200 columns") return sampled_items(200000, 5000, 30000, 200, 8);
   return 2;
 }

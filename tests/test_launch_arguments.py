@@ -32,3 +32,8 @@ def test_a_staged_head_leaves_alone_what_a_caller_keeps_in_the_workspace(launch_
 def test_a_profiled_product_adds_up_pieces_as_any_other(launch_arguments, case):
     """Whether a lane group or four of them add up a piece is not for the launch to say that it happens to be in."""
     launch_arguments("profiled, " + case)
+
+
+@pytest.mark.parametrize("columns", [48, 100, 200])
+def test_items_of_a_sampled_product_go_by_the_count_they_were_measured_with(launch_arguments, columns):
+    launch_arguments(f"items of a sampled product, {columns} columns")
