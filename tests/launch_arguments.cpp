@@ -195,6 +195,14 @@ int sampled_items(int64_t n, int pieces, int shorts, int32_t k, int items) {
   return rc;
 }
 
+// The order-3 product with the factors in LDS: four or eight columns of them.
+int columns(int64_t items, int64_t blocks, int64_t rows, int32_t R, int quads) {
+  const uint32_t last = 0;
+  const int rc = arrow::launch_mttkrp_resident(nullptr, nullptr, items, blocks, floats(0), rows / 2, floats(1), rows - rows / 2, floats(2), floats(3), R, nullptr, &last);
+  std::printf("rc %d, %s\n", rc, launches()[0].kernel.c_str());
+  return rc == 0 && launches().size() == 1 && launches()[0].kernel.find("resident_kernelILi" + std::to_string(quads) + "E") != std::string::npos ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int, char** argv) {
@@ -209,5 +217,11 @@ int main(int, char** argv) {
   if (c == "items of a sampled product, 48 columns") return sampled_items(200000, 5000, 30000, 48, 16);
   if (c == "items of a sampled product, 100 columns") return sampled_items(200000, 5000, 30000, 100, 16);
   if (c == "items of a sampled product, 200 columns") return sampled_items(200000, 5000, 30000, 200, 8);
+  if (c == "eight columns, 4000 items of 2.5 blocks, rank 128") return columns(4000, 10000, 2000, 128, 2);
+  if (c == "four columns, 1018 items of 12 blocks, rank 16") return columns(1018, 12216, 4383, 16, 1);
+  if (c == "eight columns, 2000 items of 1.2 blocks, rank 64") return columns(2000, 2444, 1900, 64, 2);
+  if (c == "four columns, 2000 items of 1.2 blocks, rank 4") return columns(2000, 2444, 1900, 4, 1);
+  if (c == "four columns, 430 items, rank 4742") return columns(430, 480, 2370, 4742, 1);
+  if (c == "eight columns, 229 items, rank 6881") return columns(229, 3436, 3356, 6881, 2);
   return 2;
 }
