@@ -148,7 +148,7 @@ int arrow_upload(arrow_handle *h, void *dev_buf, size_t bytes, void *stream);
  * Device workspace a product with k columns needs: head partials of the
  * largest level, the staged head rows, the results of the corner and panel
  * work items, plus one n x k buffer for the chained products of
- * arrow_spmm_iter; and, where the rows of a staged head of k columns are faster in whole
+ * arrow_spmm_iter; and, where the rows of a staged head of k columns or fewer are faster in whole
  * 128-byte lines, room for it behind that buffer, without which everything works as well.  arrow_set_workspace binds caller-owned device memory
  * (256-byte aligned); it may be rebound at any time the stream is idle.  Every call may write what is bound, except that
  * only chained products write the n x k buffer, and that the image, the entry map and the operands of a

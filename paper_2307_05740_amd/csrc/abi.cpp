@@ -182,6 +182,8 @@ int32_t head_columns(int32_t k) {
   const int64_t whole = ((int64_t)k + 31) / 32 * 32;
   return whole <= 2 * (int64_t)k && 10 * whole <= 9 * (32 + (int64_t)k - std::gcd(k, 32)) ? (int32_t)whole : k;
 }
+// The most columns with whole lines: beyond, 32 ceil(k / 32) >= k is more than 9 / 10 of 31 + k.
+constexpr int32_t kLinesMost = 279;
 // Bytes of a staged head in whole lines, beside the buffer whose rows are close; 0 where no level has one.
 size_t head_bytes(const arrow_handle* h, int32_t k) {
   const int64_t columns = head_columns(k);
@@ -624,7 +626,11 @@ int arrow_upload(arrow_handle* h, void* dev_buf, size_t bytes, void* stream) {
 
 size_t arrow_workspace_bytes(const arrow_handle* h, int32_t k) {
   if (!h || k < 1) return 0;
-  return scratch_bytes(h, k) + align_up((size_t)h->n * (size_t)k * sizeof(float)) + head_bytes(h, k);   // (the last: a gain, not a need)
+  // (the head in whole lines: a gain, not a need, but one that a workspace for k columns has room for with every smaller number of them)
+  auto bytes = [&](int32_t j) { return scratch_bytes(h, j) + align_up((size_t)h->n * (size_t)j * sizeof(float)) + head_bytes(h, j); };
+  size_t most = bytes(k);
+  for (int32_t j = std::min(k - 1, kLinesMost); j >= 1; --j) most = std::max(most, bytes(j));
+  return most;
 }
 
 int arrow_set_workspace(arrow_handle* h, void* dev_ws, size_t bytes) {

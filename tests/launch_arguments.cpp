@@ -151,6 +151,26 @@ int buffers_in_the_workspace() {
   return 0;
 }
 
+// A workspace asked for `most` columns: with k columns the head is laid out in whole lines, as in one asked for k.
+int fewer_columns(int32_t most, int32_t k) {
+  arrow_handle* h = staged_operand();
+  if (!h) return 1;
+  for (int32_t asked : {k, most}) {
+    arrow_set_workspace(h, address(2), arrow_workspace_bytes(h, asked));
+    launches().clear();
+    int rc = arrow_spmm(h, floats(3), floats(4), k, nullptr);
+    if (rc == 0) rc = arrow_sddmm(h, floats(3), floats(4), floats(5), k, nullptr);
+    if (rc == 0) rc = arrow_spmm_iter(h, floats(3), k, 2, nullptr);
+    int heads = 0, whole = 0;
+    for (const Launch& l : launches())
+      if (l.head) { ++heads; whole += l.stride % 32 == 0; }
+    std::printf("rc %d, asked for %d columns: %d of %d heads in whole lines\n", rc, asked, whole, heads);
+    if (rc || heads != 4 || whole != heads) return 1;
+  }
+  arrow_destroy(h);
+  return 0;
+}
+
 // Pieces of long rows, short rows and rows of several chunks of a product: the launch that holds the pieces gives them the same
 // wavefronts and workgroups where the product is profiled, which launches the lists apart.
 int profiled(int64_t n, int pieces, int shorts, int longs, int32_t k, bool wave) {
@@ -223,5 +243,8 @@ int main(int, char** argv) {
   if (c == "four columns, 2000 items of 1.2 blocks, rank 4") return columns(2000, 2444, 1900, 4, 1);
   if (c == "four columns, 430 items, rank 4742") return columns(430, 480, 2370, 4742, 1);
   if (c == "eight columns, 229 items, rank 6881") return columns(229, 3436, 3356, 6881, 2);
+  if (c == "127 columns in a workspace for 128") return fewer_columns(128, 127);
+  if (c == "31 columns in a workspace for 32") return fewer_columns(32, 31);
+  if (c == "20 columns in a workspace for 25") return fewer_columns(25, 20);
   return 2;
 }

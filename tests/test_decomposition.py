@@ -699,3 +699,16 @@ def test_library_exports_every_declared_symbol():
     for name in sorted(declared):
         assert hasattr(L, name), f"{name} is declared in include/ but not exported"
     assert declared == set(binding.EXPORTED)
+
+
+@pytest.mark.parametrize("stage_short", [-1, 1])
+def test_the_workspace_never_shrinks_with_more_columns(stage_short):
+    """A workspace asked for k columns has room for everything that fewer columns make use of, a head in whole lines among it."""
+    w = synth.make_config(2, 8)
+    o = binding.arrow_options_default(stage_short=stage_short, window_rows=1024)
+    h = binding.arrow_decompose_with(w.rowptr, w.colidx, w.vals, w.b, o)
+    try:
+        nbytes = [binding.arrow_workspace_bytes(h, k) for k in range(1, 400)]
+        assert all(a <= b for a, b in zip(nbytes, nbytes[1:]))
+    finally:
+        binding.arrow_destroy(h)

@@ -45,3 +45,8 @@ def test_items_of_a_sampled_product_go_by_the_count_they_were_measured_with(laun
 def test_four_or_eight_columns_of_the_factors_in_lds(launch_arguments, case):
     """At ordinary ranks (the third is the tensor of test_mttkrp_steps_of_the_last_block), and where eight columns take more than a round of workgroups."""
     launch_arguments(case)
+
+
+@pytest.mark.parametrize("case", ["127 columns in a workspace for 128", "31 columns in a workspace for 32", "20 columns in a workspace for 25"])
+def test_fewer_columns_find_room_for_a_head_in_whole_lines(launch_arguments, case):
+    launch_arguments(case)
