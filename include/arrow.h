@@ -156,6 +156,9 @@ int arrow_upload(arrow_handle *h, void *dev_buf, size_t bytes, void *stream);
  * products are refused there).
  */
 size_t arrow_workspace_bytes(const arrow_handle *h, int32_t k);
+/* The part of it that a product or sampled product with k columns cannot do without: head partials, staged head
+ * rows, results of the corner and panel work items.  0 if h is NULL or k < 1. */
+size_t arrow_scratch_bytes(const arrow_handle *h, int32_t k);
 int arrow_set_workspace(arrow_handle *h, void *dev_ws, size_t bytes);
 
 /*
@@ -181,9 +184,7 @@ int arrow_spmm(arrow_handle *h, const float *X, float *Y, int32_t k, void *strea
  * run on the current device).  The call allocates nothing, records no events even when profiling
  * is on, and only launches kernels on `stream`.
  *   X, Y    DEVICE, n x k fp32 row-major, 16-byte aligned, must not overlap; Y is overwritten
- * The scratch need is arrow_workspace_bytes(h, k) minus the n x k buffer of the chained products and
- * the room for a head in whole lines
- * (partial vectors of the largest level + min(b, n) staged head rows of k floats); if it exceeds
+ * The scratch need is arrow_scratch_bytes(h, k); if it exceeds
  * the array the call fails with ARROW_ETOOSMALL and nothing is launched.  All calls on one GPU
  * share that GPU's array, whatever the handle or stream: calls that overlap in time on one GPU
  * race and give wrong results; calls in stream order are safe.  Nothing in the array has to start

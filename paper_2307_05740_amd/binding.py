@@ -23,7 +23,7 @@ ARROW_OK, ARROW_EINVAL, ARROW_ENOMEM, ARROW_ENOTREADY, ARROW_ETOOSMALL, ARROW_EH
 
 EXPORTED = [
     "arrow_decompose", "arrow_device_bytes", "arrow_upload", "arrow_workspace_bytes",
-    "arrow_set_workspace", "arrow_spmm", "arrow_spmm_static", "arrow_spmm_iter", "arrow_sddmm_device_bytes",
+    "arrow_scratch_bytes", "arrow_set_workspace", "arrow_spmm", "arrow_spmm_static", "arrow_spmm_iter", "arrow_sddmm_device_bytes",
     "arrow_sddmm_upload", "arrow_sddmm", "arrow_export_entry_map", "arrow_gather", "arrow_info",
     "arrow_level_info", "arrow_export_level", "arrow_self_check", "arrow_set_option", "arrow_set_profiling",
     "arrow_get_profile", "arrow_get_level_profile", "arrow_save", "arrow_load", "arrow_last_error",
@@ -104,6 +104,8 @@ def lib():
     L.arrow_upload.argtypes = [vp, vp, sz, vp]
     L.arrow_workspace_bytes.restype = sz
     L.arrow_workspace_bytes.argtypes = [vp, i32]
+    L.arrow_scratch_bytes.restype = sz
+    L.arrow_scratch_bytes.argtypes = [vp, i32]
     L.arrow_set_workspace.restype = ctypes.c_int
     L.arrow_set_workspace.argtypes = [vp, vp, sz]
     L.arrow_spmm.restype = ctypes.c_int
@@ -254,6 +256,10 @@ def arrow_upload(h: int, dev_ptr: int, nbytes: int, stream: int = 0) -> None:
 
 def arrow_workspace_bytes(h: int, k: int) -> int:
     return int(lib().arrow_workspace_bytes(h, k))
+
+
+def arrow_scratch_bytes(h: int, k: int) -> int:
+    return int(lib().arrow_scratch_bytes(h, k))
 
 
 def arrow_set_workspace(h: int, dev_ptr: int, nbytes: int) -> None:

@@ -633,6 +633,8 @@ size_t arrow_workspace_bytes(const arrow_handle* h, int32_t k) {
   return most;
 }
 
+size_t arrow_scratch_bytes(const arrow_handle* h, int32_t k) { return !h || k < 1 ? 0 : scratch_bytes(h, k); }
+
 int arrow_set_workspace(arrow_handle* h, void* dev_ws, size_t bytes) {
   if (!h) return fail(ARROW_EINVAL, "handle is NULL");
   if (!dev_ws) return fail(ARROW_EINVAL, "dev_ws is NULL");

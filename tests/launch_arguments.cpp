@@ -132,6 +132,7 @@ int buffers_in_the_workspace() {
   for (int32_t k : {17, 50, 63, 127}) {
     const size_t least = least_workspace(h, k), xy = up((size_t)kRows * (size_t)k * 4), full = arrow_workspace_bytes(h, k);
     unsigned char* ws = address(2);
+    if (least != up(arrow_scratch_bytes(h, k))) return 1;
     // an operand of another call in the part that only chained products write
     arrow_set_workspace(h, ws, full);
     if (!leaves_alone(h, k, ws + least, xy, &whole) || whole == 0) return 1;

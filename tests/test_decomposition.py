@@ -712,3 +712,21 @@ def test_the_workspace_never_shrinks_with_more_columns(stage_short):
         assert all(a <= b for a, b in zip(nbytes, nbytes[1:]))
     finally:
         binding.arrow_destroy(h)
+
+
+@pytest.mark.parametrize("k", [1, 7, 17, 31, 50, 64, 127, 1000])
+def test_what_a_product_cannot_do_without(k):
+    """What is left of the workspace without the buffer of the chained products, where no head could be in whole lines (hence the option)."""
+    w = synth.make_config(2, 8)
+    for options in (dict(stage_head=0, window_rows=1024), dict(stage_short=1, window_rows=1024)):
+        h = binding.arrow_decompose_with(w.rowptr, w.colidx, w.vals, w.b, binding.arrow_options_default(**options))
+        levels = [binding.arrow_level_info(h, i) for i in range(binding.arrow_info(h)["levels"])]
+        up = lambda floats: -(-4 * floats // 256) * 256
+        try:
+            need = binding.arrow_scratch_bytes(h, k)
+            assert need >= up(max(v["partials"] for v in levels) * k)
+            left = binding.arrow_workspace_bytes(h, k) - up(w.n * k) - need
+            assert left == 0 if options.get("stage_head") == 0 else left >= 0
+        finally:
+            binding.arrow_destroy(h)
+    assert binding.arrow_scratch_bytes(0, k) == 0
