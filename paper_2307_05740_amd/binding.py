@@ -435,7 +435,8 @@ class ArrowSpMM:
         return _current_stream(self._torch, self.device)
 
     def _ensure_workspace(self, k: int, second: bool = False) -> None:
-        """Bind a workspace for k columns; `second`: with room for another n x k buffer, if there is memory for it.
+        """Bind a workspace for k columns; `second`: with room for another n x k buffer, if there is memory for it, as for what else
+        a product can do without.
         One that is bound and suffices without that room stays: a captured graph may hold its address, and a
         call may be captured itself.  `_ws_k` names columns only while a workspace for them is bound: the native
         calls go by it alone, also where no memory is left for the new one."""
@@ -443,16 +444,18 @@ class ArrowSpMM:
             return
         torch = self._torch
         torch.cuda.current_stream(self.device).synchronize()
-        nbytes = max(arrow_workspace_bytes(self.h, k), 256)
-        extra = -(-self.n * k * 4 // 256) * 256 if second else 0
+        xy = -(-self.n * k * 4 // 256) * 256
+        least = max(arrow_scratch_bytes(self.h, k) + xy, 256)
+        nbytes = max(arrow_workspace_bytes(self.h, k), least)      # with room for a head in whole lines
         self._ws_k = 0
         self._ws = None
-        try:
-            self._ws = torch.empty(nbytes + extra, dtype=torch.uint8, device=self.device)
-        except torch.OutOfMemoryError:
-            if not extra:
-                raise
-            self._ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        for size in ((nbytes + xy, nbytes, least) if second else (nbytes, least)):
+            try:
+                self._ws = torch.empty(size, dtype=torch.uint8, device=self.device)
+                break
+            except torch.OutOfMemoryError:
+                if size == least:
+                    raise
         arrow_set_workspace(self.h, self._ws.data_ptr(), self._ws.numel())
         self._ws_k = k
 

@@ -206,3 +206,32 @@ def test_anything_but_plain_tensors_goes_the_general_way():
             call(at, 0)
         with pytest.raises(TypeError):
             call(*["0"] * {"spmm": 7, "sddmm": 9, "mttkrp": 10}[call.__name__])
+
+
+@pytest.mark.parametrize("second", [False, True])
+@pytest.mark.parametrize("room", ["everything", "the whole workspace", "the least"])
+def test_a_workspace_without_room_for_a_head_in_whole_lines_will_do(handle, monkeypatch, second, room):
+    """The product asks for a second buffer, then for the workspace with the room for a head in whole lines, then for what it
+    cannot do without: short of memory it is slower, not refused."""
+    op, did = handle
+    k, xy = 31, -(-300 * 31 * 4 // 256) * 256
+    scratch = binding.arrow_scratch_bytes(op.h, k)
+    monkeypatch.setattr(binding, "arrow_workspace_bytes", lambda h, k: scratch + xy + 19200)
+    sizes = [scratch + 2 * xy + 19200] * second + [scratch + xy + 19200, scratch + xy]
+    least = {"everything": 0, "the whole workspace": 1 if second else 0, "the least": 2 if second else 1}[room]
+    asked, torch_empty = [], op._torch.empty
+
+    def empty(nbytes, dtype, device):
+        asked.append(nbytes)
+        if nbytes > sizes[least]:
+            raise torch.OutOfMemoryError
+        return torch_empty(nbytes, dtype, device)
+
+    op._torch.empty = empty
+    op._ensure_workspace(k, second=second)
+    assert asked == sizes[:least + 1] and op._ws.numel() == sizes[least] and op._ws_k == k
+    assert did[-1] == ("bind", op._ws.data_ptr(), sizes[least])
+    sizes[least] = 0
+    with pytest.raises(torch.OutOfMemoryError):
+        op._ensure_workspace(k + 1, second=second)
+    assert op._ws_k == 0
