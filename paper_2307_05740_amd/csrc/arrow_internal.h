@@ -63,6 +63,8 @@ struct Entry {
 };
 
 constexpr int kDies = 8;             // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
+constexpr uint32_t kDiesLog = 3;
+static_assert(kDies == 1 << kDiesLog, "a power of two of dies");
 constexpr int kChunksPerGroup = 4;   // wave-list items (one per wavefront) per workgroup of the chunk kernel
 // Destination of a wave-list item whose sum is added to that of its workgroup's first item: the four
 // wavefronts of a workgroup then work on one item together (slots 4 i .. 4 i + 3, all or none).
@@ -76,6 +78,12 @@ constexpr int64_t kMostGroups = (1LL << 24) - 1;   // workgroups of 256 in a dim
 // average; us, 256 / 128 / 64: directed 300 K, k = 50, 136.1 / 136.0 / 133.6; Chung-Lu 250 K, 48, 84.3 / 81.0 / 81.5; sampled product, Chung-Lu 400 K, 32, 95.7 /
 // 92.5 / 91.2; R-MAT 500 K, 128, 331.6 / 335.6 / 337.8.)
 inline uint32_t die_run(int64_t blocks) { return blocks < 7300 ? 64 : blocks < 9600 ? 128 : 256; }
+// The workgroup of the wave list that the id-th place is for, of `blocks` places that are dealt to 1 << dies_log dies round-robin: runs of `run` of
+// them to one die each, as far as every die has a whole one (run = 0: the id-th).
+constexpr uint32_t in_runs(uint32_t id, uint32_t dies_log, uint32_t run, uint32_t blocks) {
+  const uint32_t dies = 1u << dies_log, span = dies * run, base = id & ~(span - 1u);
+  return run && base + span <= blocks ? base + (id & (dies - 1u)) * run + ((id - base) >> dies_log) : id;
+}
 // head panels: kPanelRows head rows form a group; the group's head-block entries are dealt by column
 // class (staged head row mod kDies) to kDies workgroups, one per accelerator die, each keeping the
 // group's accumulators in LDS and streaming its entries in kPanelBins lane-group streams

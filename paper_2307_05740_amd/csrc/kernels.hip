@@ -255,8 +255,6 @@ __device__ __forceinline__ void chunk_part(Entry* mine, const ProductArgs& a, co
 // the slices, one after the other, so that its L2 holds rows of X of that many columns only and fetches them for that many.
 // Which slice and which of its `blocks` workgroups the id-th workgroup of a part is (a multiple of kDies per slice; the
 // part begins at die 0):
-constexpr uint32_t kDiesLog = 3;
-static_assert(kDies == 1 << kDiesLog, "a power of two of dies");
 struct SliceBlock { uint32_t slice, block; };
 __device__ __forceinline__ SliceBlock slice_block(const ProductArgs& a, uint32_t id, uint32_t blocks) {
   const uint32_t dies_log = kDiesLog - a.sets_log, die = id % kDies;
@@ -445,9 +443,7 @@ __global__ __launch_bounds__(kBlock) void chunks_kernel(const ProductArgs a) {
   // windows at a time, and a row of X that several chunks of a run read is fetched into one L2
   // instead of several (the same chunks: 255 -> 231 us per product; R-MAT 8m, k = 128: 1 %; eighths
   // of the whole list are slower, the dies then finish at different times).
-  const uint32_t span = dies * a.run;
-  const uint32_t base = id & ~(span - 1u);
-  if (a.run && base + span <= a.blocks[0]) id = base + (id & (dies - 1u)) * a.run + ((id - base) >> dies_log);
+  id = in_runs(id, dies_log, a.run, a.blocks[0]);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int64_t ch = (int64_t)id * WPB + wave;
   if (ch >= a.n_chunks) return;

@@ -323,10 +323,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_chunks_kernel(const SampledArgs 
   __shared__ Entry ents[WPB][64];
   __shared__ uint32_t ats[WPB][64];
   // runs of workgroups to one die each, as in the product's chunks kernel
-  uint32_t id = blockIdx.x;
-  const uint32_t span = kDies * a.run;
-  const uint32_t base = id & ~(span - 1u);
-  if (a.run && base + span <= gridDim.x) id = base + id % kDies * a.run + (id - base) / kDies;
+  const uint32_t id = in_runs(blockIdx.x, kDiesLog, a.run, gridDim.x);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int64_t ch = (int64_t)id * WPB + wave;      // (a list in window order is never short)
   if (ch < a.n_chunks) sampled_chunk<VEC, LPR, NB, SMALL, false>(ents[wave], ats[wave], a, ch, 0);

@@ -16,6 +16,7 @@ namespace {
 
 struct Launch {
   std::string kernel;
+  dim3 grid;
   arrow::ProductArgs product;      // of a kernel that takes one
   arrow::SampledArgs sampled;      // of a kernel that takes one
   const unsigned char* head;       // of gather_kernel: its result, rows of it, and the floats between those
@@ -35,9 +36,10 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
   *grid = pushed_grid; *block = pushed_block; *shared = 0; *stream = nullptr;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* function, dim3, dim3, void** args, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* function, dim3 grid, dim3, void** args, size_t, hipStream_t) {
   Launch l{};
   l.kernel = names()[function];
+  l.grid = grid;
   if (l.kernel.find("ProductArgs") != std::string::npos) l.product = *static_cast<const arrow::ProductArgs*>(args[0]);
   if (l.kernel.find("SampledArgs") != std::string::npos) l.sampled = *static_cast<const arrow::SampledArgs*>(args[0]);
   if (l.kernel.find("13gather_kernel") != std::string::npos) {
@@ -224,6 +226,32 @@ int columns(int64_t items, int64_t blocks, int64_t rows, int32_t R, int quads) {
   return rc == 0 && launches().size() == 1 && launches()[0].kernel.find("resident_kernelILi" + std::to_string(quads) + "E") != std::string::npos ? 0 : 1;
 }
 
+// The workgroups of a wave list in window order, of a product (k columns in slices of kc) and of a sampled one: every one is taken
+// once, `run` of them one after the other by the same die, as far as whole runs go.
+int runs(int64_t n_chunks, int32_t k, int32_t kc, uint32_t run, uint32_t sets_log) {
+  arrow::ProductArgs p{};
+  p.X = p.Xh = floats(0); p.Y = floats(1); p.partials = floats(2);
+  p.n_chunks = n_chunks; p.k = k;
+  arrow::SampledArgs s{};
+  s.U = floats(0); s.V = s.Vh = floats(1); s.S = floats(2);
+  s.n_chunks = n_chunks; s.nnz_chunks = 100 * n_chunks; s.k = k;
+  if (arrow::launch_product(p, arrow::kPartChunks, 0, 0, 0, false, true, 300000, kc, nullptr) || arrow::launch_sddmm(s, false, false, true, false, 300000, nullptr)) return 1;
+  if (launches().size() != 2 || launches()[0].product.run != run || launches()[1].sampled.run != run || launches()[0].product.sets_log != sets_log) return 1;
+  for (int which = 0; which < 2; ++which) {
+    const uint32_t dies_log = 3 - (which == 0 ? sets_log : 0), dies = 1u << dies_log;
+    const uint32_t blocks = which == 0 ? launches()[0].product.blocks[0] : launches()[1].grid.x;
+    if ((int64_t)blocks * arrow::kChunksPerGroup < n_chunks) return 1;
+    std::vector<int> taken(blocks, 0);
+    for (uint32_t id = 0; id < blocks; ++id) {
+      const uint32_t at = arrow::in_runs(id, dies_log, run, blocks);
+      if (at >= blocks || taken[at]++) { std::printf("workgroup %u of %u\n", at, blocks); return 1; }
+      const bool whole = id / (dies * run) * dies * run + dies * run <= blocks;
+      if (whole && at / run % dies != id % dies) { std::printf("workgroup %u on die %u\n", at, id % dies); return 1; }
+    }
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int, char** argv) {
@@ -247,5 +275,12 @@ int main(int, char** argv) {
   if (c == "127 columns in a workspace for 128") return fewer_columns(128, 127);
   if (c == "31 columns in a workspace for 32") return fewer_columns(32, 31);
   if (c == "20 columns in a workspace for 25") return fewer_columns(25, 20);
+  if (c == "runs of 64, a few workgroups") return runs(20, 128, 128, 64, 0);
+  if (c == "runs of 64, the shortest that has one") return runs(4 * 512, 128, 128, 64, 0);
+  if (c == "runs of 64, the longest") return runs(4 * 7296, 50, 50, 64, 0);
+  if (c == "runs of 128, the shortest") return runs(4 * 7299 + 1, 50, 50, 128, 0);
+  if (c == "runs of 128, two sets of dies") return runs(4 * 9592, 128, 64, 128, 1);
+  if (c == "runs of 256, the shortest") return runs(4 * 9599 + 1, 50, 50, 256, 0);
+  if (c == "runs of 256, two sets of dies") return runs(1000003, 128, 64, 256, 1);
   return 2;
 }

@@ -50,3 +50,9 @@ def test_four_or_eight_columns_of_the_factors_in_lds(launch_arguments, case):
 @pytest.mark.parametrize("case", ["127 columns in a workspace for 128", "31 columns in a workspace for 32", "20 columns in a workspace for 25"])
 def test_fewer_columns_find_room_for_a_head_in_whole_lines(launch_arguments, case):
     launch_arguments(case)
+
+
+@pytest.mark.parametrize("case", ["runs of 64, a few workgroups", "runs of 64, the shortest that has one", "runs of 64, the longest", "runs of 128, the shortest",
+                                  "runs of 128, two sets of dies", "runs of 256, the shortest", "runs of 256, two sets of dies"])
+def test_runs_of_workgroups_take_every_one_of_them_once(launch_arguments, case):
+    launch_arguments(case)
