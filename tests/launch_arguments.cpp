@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <map>
 #include <string>
 #include <vector>
@@ -174,6 +175,31 @@ int fewer_columns(int32_t most, int32_t k) {
   return 0;
 }
 
+// Whether the heads of a product and of a sampled product with k columns are in rows of whole lines where there is room, `columns` floats apart.
+int head_rows(int32_t k, int columns) {
+  arrow_handle* h = staged_operand();
+  if (!h) return 1;
+  const size_t full = arrow_workspace_bytes(h, k), least = up(arrow_scratch_bytes(h, k));
+  for (size_t bytes : {full, least}) {
+    arrow_set_workspace(h, address(2), bytes);
+    launches().clear();
+    int rc = arrow_spmm(h, floats(3), floats(4), k, nullptr);
+    if (rc == 0) rc = arrow_sddmm(h, floats(3), floats(4), floats(5), k, nullptr);
+    int heads = 0;
+    for (const Launch& l : launches()) {
+      if (!l.head) continue;
+      std::printf("%d columns, rows %d apart\n", k, l.stride);
+      if (l.stride != (bytes == full ? columns : k) || l.head < address(2) || l.head + (size_t)l.rows * (size_t)l.stride * 4 > address(2) + bytes) return 1;
+      ++heads;
+    }
+    bool read = false;
+    for (const Launch& l : launches()) read = read || l.product.head_stride == (bytes == full ? columns : k);
+    if (rc || heads != 2 || !read) return 1;
+  }
+  arrow_destroy(h);
+  return 0;
+}
+
 // Pieces of long rows, short rows and rows of several chunks of a product: the launch that holds the pieces gives them the same
 // wavefronts and workgroups where the product is profiled, which launches the lists apart.
 int profiled(int64_t n, int pieces, int shorts, int longs, int32_t k, bool wave) {
@@ -282,5 +308,10 @@ int main(int, char** argv) {
   if (c == "runs of 128, two sets of dies") return runs(4 * 9592, 128, 64, 128, 1);
   if (c == "runs of 256, the shortest") return runs(4 * 9599 + 1, 50, 50, 256, 0);
   if (c == "runs of 256, two sets of dies") return runs(1000003, 128, 64, 256, 1);
+  if (c.rfind("head rows of ", 0) == 0) {
+    const int k = std::atoi(c.c_str() + 13);
+    const bool whole = k == 17 || k == 20 || k == 63 || k == 90 || k == 127 || k == 150;
+    return head_rows(k, whole ? (k + 31) / 32 * 32 : k);
+  }
   return 2;
 }

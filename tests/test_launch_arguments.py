@@ -56,3 +56,9 @@ def test_fewer_columns_find_room_for_a_head_in_whole_lines(launch_arguments, cas
                                   "runs of 128, two sets of dies", "runs of 256, the shortest", "runs of 256, two sets of dies"])
 def test_runs_of_workgroups_take_every_one_of_them_once(launch_arguments, case):
     launch_arguments(case)
+
+
+@pytest.mark.parametrize("columns", [12, 17, 20, 63, 64, 90, 100, 127, 150])
+def test_rows_of_a_staged_head(launch_arguments, columns):
+    """In whole 128-byte lines with 17, 20, 63, 90, 127 and 150 columns, where there is room for that."""
+    launch_arguments(f"head rows of {columns} columns")
