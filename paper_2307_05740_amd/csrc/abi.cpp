@@ -373,7 +373,7 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
       a.chunk_row = at<int32_t>(h, im.off_chunk_row); a.n_chunks = im.n_chunks; a.nnz_chunks = im.nnz_chunks;
       a.rows_ptr = at<uint32_t>(h, im.off_rows_ptr); a.rows_mid = at<uint32_t>(h, im.off_rows_mid);
       a.rows_row = at<int32_t>(h, im.off_rows_row); a.n_rows = im.n_rows - im.empty_slots; a.nnz_rows = im.nnz_rows;
-      a.n_pieces = im.piece_slots; a.n_empty = im.empty_slots;
+      a.n_pieces = im.piece_slots;
       a.ent = ent; a.emap = emap; a.U = U; a.V = V; a.Vh = Vh; a.head_stride = head_stride; a.S = S; a.k = k;
       auto launch = [&](arrow::SampledArgs args, bool window_rows) -> int {
         if (args.n_chunks == 0 && args.n_rows == 0) return ARROW_OK;
@@ -394,7 +394,7 @@ int sampled_product(arrow_handle* h, const float* U, const float* V, float* S_ou
       if (rc) return rc;
       if (im.n_wrows > 0) {
         Scoped sc(h, kWindow, (int)li, stream);
-        a.n_chunks = a.n_pieces = a.n_empty = 0; a.n_rows = im.n_wrows; a.nnz_rows = im.nnz_w;
+        a.n_chunks = a.n_pieces = 0; a.n_rows = im.n_wrows; a.nnz_rows = im.nnz_w;
         a.rows_ptr = at<uint32_t>(h, im.off_wrow_ptr); a.rows_mid = at<uint32_t>(h, im.off_wrow_mid);
         a.rows_row = at<int32_t>(h, im.off_wrow_y); a.rows_win = at<uint32_t>(h, im.off_wrow_win);
         a.perm = at<int32_t>(h, im.off_perm);

@@ -296,7 +296,6 @@ struct SampledArgs {
   float* S;
   int64_t n_chunks, n_rows;             // (rows without entries, the last ones of a group list, are left out)
   int64_t n_pieces;                     // the first n_pieces of the rows are pieces of long rows
-  int64_t n_empty;                      // rows without entries that were left out
   int64_t nnz_chunks, nnz_rows;
   int32_t k;
   int32_t items;                        // group-list slots per workgroup (filled in by the launch),

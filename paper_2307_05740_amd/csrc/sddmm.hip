@@ -374,8 +374,7 @@ namespace {
 // 441 lists of 3 K to 1.5 M vertices, R-MAT and Chung-Lu, at five ranks each, rows without entries left out: 0.96 times the time on average, within 1 % of the
 // best numbers.  us before / now: R-MAT 30 K, k = 24, 10.9 / 9.5; 6 K, 96, 6.1 / 5.5; 14 K, 43, 8.8 / 8.0; 70 K, 66, 45.8 / 44.0; 1.5 M, 20, 364.5 / 356.3; Chung-Lu 25 K, 37,
 // 12.4 / 10.8; 67 K, 32, 17.7 / 16.9.)  Wider lists of more than 131072 vertices gain less than they scatter (Chung-Lu 540 K, k = 64, 175.8 us, apart 178.2) and
-// lists of more pieces than short rows lose (dense blocks, 12 K vertices of 44 entries, k = 128, 23.9 us, apart 27.3; 17 K, 43, 65, 24.9 and 28.1): one number for both.  Its root
-// counts the rows without entries, which are left out otherwise: with them its lines were measured.
+// lists of more pieces than short rows lose (dense blocks, 12 K vertices of 44 entries, k = 128, 23.9 us, apart 27.3; 17 K, 43, 65, 24.9 and 28.1): one number for both, as it was.
 // Rows of dense blocks, of which a lane group takes one or two, by rows: 450 K, 26 entries, k = 48,  8: 244.3  16: 221.5  32: 254.4;
 // 250 K, 40 entries, k = 128,  4: 298.9  8: 293.6  16: 365.1; 27 K, 42 entries, k = 8,  4: 18.5  8: 14.4  16: 12.2  32: 16.4.
 struct ItemsFrom { int lpr; double from[5]; };      // ... items at least from[0], from[1], ... rows
@@ -474,8 +473,7 @@ int launch_sddmm(SampledArgs a, bool window_rows, bool die_queues, bool windows,
     const Rows rows = window_rows ? Rows::kWindow : a.n_pieces > 0 ? Rows::kShort : unequal ? Rows::kUnequal : Rows::kAlike;
     const int64_t n_short = a.n_rows - a.n_pieces;
     a.piece_items = items_of(a.n_pieces, a.nnz_rows, s.lpr, Rows::kPieces, a.n_chunks > 0);
-    a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock)
-                         : items_of(n_short + (rows == Rows::kUnequal ? a.n_empty : 0), a.nnz_rows, s.lpr, rows, a.n_chunks > 0);
+    a.items = die_queues ? (window_rows ? kItemsPerGroupBlock / 4 : kItemsPerGroupBlock) : items_of(n_short, a.nnz_rows, s.lpr, rows, a.n_chunks > 0);
     piece_blocks = ceil_div(ceil_div(a.n_pieces, a.piece_items), kDies) * kDies;
     row_blocks = piece_blocks + ceil_div(ceil_div(n_short, a.items), kDies) * kDies;
   };
