@@ -374,7 +374,11 @@ namespace {
 // 441 lists of 3 K to 1.5 M vertices, R-MAT and Chung-Lu, at five ranks each, rows without entries left out: 0.96 times the time on average, within 1 % of the
 // best numbers.  us before / now: R-MAT 30 K, k = 24, 10.9 / 9.5; 6 K, 96, 6.1 / 5.5; 14 K, 43, 8.8 / 8.0; 70 K, 66, 45.8 / 44.0; 1.5 M, 20, 364.5 / 356.3; Chung-Lu 25 K, 37,
 // 12.4 / 10.8; 67 K, 32, 17.7 / 16.9.)  Wider lists of more than 131072 vertices gain less than they scatter (Chung-Lu 540 K, k = 64, 175.8 us, apart 178.2) and
-// lists of more pieces than short rows lose (dense blocks, 12 K vertices of 44 entries, k = 128, 23.9 us, apart 27.3; 17 K, 43, 65, 24.9 and 28.1): one number for both, as it was.
+// lists of more pieces than short rows lose (dense blocks, 12 K vertices of 44 entries, k = 128, 23.9 us, apart 27.3; 17 K, 43, 65, 24.9 and 28.1): one number for both,
+// by the root of rows times entries.  Its lines were measured with rows without entries in the list, which are left out since: the root is smaller, and lists
+// near a line get half as many items.  Those are the better: of 52 lists, R-MAT and Chung-Lu of 140 K to 1.5 M vertices at 40 to 200 columns, 16 take 2 to 8 % longer with
+// the number that all rows gave and the others the same within a percent (k = 64, all rows / those with entries, us: R-MAT 300 K of 8 edges a vertex 109.4 / 105.4; 600 K 219.2 / 206.8; 650 K of 6
+// 188.9 / 177.2; directed 300 K of 12, 88.6 / 82.6, k = 128 167.7 / 155.3; 700 K, 128, 375.6 / 366.0).
 // Rows of dense blocks, of which a lane group takes one or two, by rows: 450 K, 26 entries, k = 48,  8: 244.3  16: 221.5  32: 254.4;
 // 250 K, 40 entries, k = 128,  4: 298.9  8: 293.6  16: 365.1; 27 K, 42 entries, k = 8,  4: 18.5  8: 14.4  16: 12.2  32: 16.4.
 struct ItemsFrom { int lpr; double from[5]; };      // ... items at least from[0], from[1], ... rows

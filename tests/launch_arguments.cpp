@@ -224,6 +224,26 @@ int profiled(int64_t n, int pieces, int shorts, int longs, int32_t k, bool wave)
          seen[1].items[1] == seen[0].items[1] ? 0 : 1;
 }
 
+// A sampled product of long and short rows in window order: `items` of them to a workgroup, which go by the rows that have entries.
+int sampled_items(int64_t n, int pieces, int shorts, int32_t k, int items) {
+  std::vector<int> entries((size_t)n, 0);
+  for (int i = 0; i < pieces + shorts; ++i) entries[(size_t)i] = i < pieces ? 20 : 2;
+  arrow_options_t o;
+  arrow_options_default(&o);
+  arrow_handle* h = operand(entries, (uint32_t)n, (int32_t)(n / 16), o);
+  if (!h || arrow_upload(h, address(0), arrow_device_bytes(h), nullptr) || arrow_sddmm_upload(h, address(1), arrow_sddmm_device_bytes(h), nullptr)) return 1;
+  arrow_set_workspace(h, address(2), (size_t)1 << 40);
+  if (arrow_sddmm(h, floats(3), floats(4), floats(5), k, nullptr)) { std::printf("%s\n", arrow_last_error()); return 1; }
+  int rc = 1;
+  for (const Launch& l : launches())
+    if (l.sampled.n_rows > 0) {
+      std::printf("%lld rows, %lld pieces apart, %d items to a workgroup\n", (long long)l.sampled.n_rows, (long long)l.sampled.n_pieces, l.sampled.items);
+      rc = l.sampled.n_rows >= pieces + shorts && l.sampled.n_rows < n / 2 && l.sampled.n_pieces == 0 && l.sampled.items == items ? 0 : 1;
+    }
+  arrow_destroy(h);
+  return rc;
+}
+
 // The order-3 product with the factors in LDS: four or eight columns of them.
 int columns(int64_t items, int64_t blocks, int64_t rows, int32_t R, int quads) {
   const uint32_t last = 0;
@@ -268,6 +288,10 @@ int main(int, char** argv) {
   if (c == "profiled, slices and chunks") return profiled(11000, 2000, 8321, 40, 200, false);
   if (c == "profiled, two launches") return profiled(140000, 3000, 60000, 20, 96, true);
   if (c == "buffers in the workspace") return buffers_in_the_workspace();
+  // the root of 200 K rows times 160 K entries is 179 K; of the 35 K rows with entries alone 75 K
+  if (c == "items of a sampled product, 48 columns") return sampled_items(200000, 5000, 30000, 48, 8);
+  if (c == "items of a sampled product, 100 columns") return sampled_items(200000, 5000, 30000, 100, 8);
+  if (c == "items of a sampled product, 200 columns") return sampled_items(200000, 5000, 30000, 200, 4);
   if (c == "eight columns, 4000 items of 2.5 blocks, rank 128") return columns(4000, 10000, 2000, 128, 2);
   if (c == "four columns, 1018 items of 12 blocks, rank 16") return columns(1018, 12216, 4383, 16, 1);
   if (c == "eight columns, 2000 items of 1.2 blocks, rank 64") return columns(2000, 2444, 1900, 64, 2);

@@ -34,6 +34,11 @@ def test_a_profiled_product_adds_up_pieces_as_any_other(launch_arguments, case):
     launch_arguments("profiled, " + case)
 
 
+@pytest.mark.parametrize("columns", [48, 100, 200])
+def test_items_of_a_sampled_product_go_by_the_rows_with_entries(launch_arguments, columns):
+    launch_arguments(f"items of a sampled product, {columns} columns")
+
+
 @pytest.mark.parametrize("case", ["eight columns, 4000 items of 2.5 blocks, rank 128", "four columns, 1018 items of 12 blocks, rank 16",
                                   "eight columns, 2000 items of 1.2 blocks, rank 64", "four columns, 2000 items of 1.2 blocks, rank 4",
                                   "four columns, 430 items, rank 4742", "eight columns, 229 items, rank 6881"])
