@@ -381,13 +381,15 @@ namespace {
 // 188.9 / 177.2; directed 300 K of 12, 88.6 / 82.6, k = 128 167.7 / 155.3; 700 K, 128, 375.6 / 366.0).
 // Rows of dense blocks, of which a lane group takes one or two, by rows: 450 K, 26 entries, k = 48,  8: 244.3  16: 221.5  32: 254.4;
 // 250 K, 40 entries, k = 128,  4: 298.9  8: 293.6  16: 365.1; 27 K, 42 entries, k = 8,  4: 18.5  8: 14.4  16: 12.2  32: 16.4.
+// (Lines as close as 10 % are one: short rows at four and eight lanes go from 4 items to 16, with 8 between 1700 and 1900 rows nothing was faster by more than runs differ.  Pieces at two
+// lanes gain from theirs: 2 / 4 of 4679, Chung-Lu 36 K, k = 8, 10.7 / 10.0 us, 16 / 8 of 5742, 45 K, 11.5 / 11.1, though 5183, R-MAT 60 K, 12.4 / 12.7.)
 struct ItemsFrom { int lpr; double from[5]; };      // ... items at least from[0], from[1], ... rows
 constexpr double kNever = 1e18;
 constexpr ItemsFrom kUnequalItems[] = {{2, {0, 5800, 21400, 226000, 909000}},       {4, {0, 12100, 31400, 186000, 909000}},
                                        {8, {0, 7900, 50000, 253000, 962000}},       {16, {8700, 25900, 90700, 498000, 1090000}},
                                        {32, {13500, 44800, 156000, 498000, 1090000}}, {64, {21400, 90700, 226000, 720000, kNever}}};
-constexpr ItemsFrom kShortItems[] = {{2, {0, 1700, 5500, 17500, 49500}},            {4, {0, 1700, 1900, 10800, 70000}},
-                                     {8, {0, 1800, 1900, 17800, 60000}},            {16, {0, 2000, 10400, 40800, 145000}},
+constexpr ItemsFrom kShortItems[] = {{2, {0, 1700, 5500, 17500, 49500}},            {4, {0, 1800, 1800, 10800, 70000}},
+                                     {8, {0, 1800, 1800, 17800, 60000}},            {16, {0, 2000, 10400, 40800, 145000}},
                                      {32, {0, 5600, 15500, 90000, 690000}},         {64, {0, 20000, 46000, 263000, kNever}}};
 constexpr ItemsFrom kPieceItems[] = {{2, {0, 3900, 4800, 6000, kNever}},            {4, {0, 900, 1450, 3400, kNever}},
                                      {8, {0, 300, 1100, 4000, kNever}},             {16, {0, 950, 2500, 11000, kNever}},
