@@ -615,9 +615,10 @@ __global__ __launch_bounds__(BLOCK, BLOCK / 256 * (kWinFloats / FLOATS)) void wi
   };
   // The scheduler prefers the oldest wavefronts of a SIMD: they were through with their rows after 17.6 us, the youngest after
   // 27.6, alone at the end.  With lower priorities for those that have fewer rows left they end after 20 to 22.7 us (512
-  // blocks of 512 with 48 entries per row, k = 128, 136.1 -> 123.8 us of a product; 300k, 50 entries, 96: 176.5 -> 160.2).  Not where two
-  // workgroups share a compute unit: the one that sums holds up the other one's staging (437k, 62, 16: 71 -> 80 us of the kernel; 500k, 60, 16:
-  // 82 -> 75 of a product; in the form of eight wavefronts 600k, 26, 32: 97 -> 98).
+  // blocks of 512 with 48 entries per row, k = 128, 136.1 -> 123.8 us of a product; 300k, 50 entries, 96: 176.5 -> 160.2).  Where two
+  // workgroups share a compute unit the one that sums may hold up the other one's staging, and it depends on the operand: a product without / with
+  // priorities, us, 500k, 60, 16, 82.2 / 75.4; 700k, 30, 8, 73.4 / 69.7; 437k, 62, 16, 83.2 / 91.8; in the form of eight wavefronts 600k, 26, 32, 97 / 98.
+  // None there: what tells the first two from the third is not known.
   constexpr bool RANKED = FLOATS == kWinFloats;
   uint32_t left = (n_rows + GPB - 1) / GPB;          // rows to go, this one included
   if (RANKED && left > 3) __builtin_amdgcn_s_setprio(3);

@@ -261,11 +261,14 @@ __global__ __launch_bounds__(kBlock, 8) void mttkrp_kernel(
 // sums are better, the other wavefronts of a SIMD fill the wait: eight columns, rows of 4 / 2 / 1 steps together: 4096 x 2500 x
 // 2500 of 25.6 M, R = 64, 165.3 / 161.3 / 150.5 us (four columns: 8 / 4 / 2 steps 170.6 / 166.9 / 172.3; 4096^3 453.0 / 449.8 /
 // 466.4, and with a third block on its way 443.6).  Eight sums of an item are reduced together, halving what a lane holds with every
-// exchange (some 30 instructions instead of 96), and the steps that fill up its last block are left out, which are half a block on average: 3000 x 500 x
+// exchange (some 30 instructions instead of 96), and the steps that fill up its last block are left out, which are half a block on average (both for
+// eight columns only): 3000 x 500 x
 // 2500, R = 96, 48.0 -> 44.9 us; 4000 x 1000 x 1000, 128, 72.3 -> 67.6; 2734 x 640 x 509 of 890 K, 96, 24.3 -> 20.4 (some of it by the choice between four and eight).
 //
 // The scheduler prefers the oldest wavefronts of a SIMD; of the longest shares the first were through after 394 of 430 us.  With priorities that fall with
-// every quarter of their items they stay together, and what they read of the image: 4096^3, R = 64, 445 -> 441.5; R = 128, 825 -> 821.
+// every quarter of their items they stay together, and what they read of the image (the form with a third block on its way; both sides timed in turn on two
+// cards, runs of one side 0.1 to 0.2 % apart): 4096^3, R = 64, 443.5 -> 439.7 and 446.1 -> 442.8; R = 128, 823.3 -> 818.6 and 828.1 -> 825.1; 4000^3 of 50 M,
+// R = 100, 521.7 -> 518.8 and 524.9 -> 522.4.
 // (A barrier after every item: 467.  Windows of B, five of them, so that eight columns fit for 4096^3: R = 64 415, but R = 4 / 12 / 20 97 -> 107, 139 -> 157, 190 -> 214 us;
 // batches of a window mix the lengths of more segments, which takes 5 to 8 % more steps, and there is one image for all ranks.)
 // ---------------------------------------------------------------------------------------------------------
