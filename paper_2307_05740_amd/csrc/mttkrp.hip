@@ -718,18 +718,20 @@ int launch_mttkrp_resident(const ResidentItem* items, const ResidentBlock* block
     }
     return s;
   };
-  // Eight columns at a time where the rows fit the LDS so: the entries are read half as often, and a step takes 1.6
-  // times as long instead of twice.  Half as many slices leave twice as many wavefronts for the items, though, and a wavefront
-  // that has its SIMD to itself waits longer for each of its rows.  Both measured on 4500 uniform tensors of 200 to 4096 rows a side at four ranks each: the numbers
-  // below take 0.4 % longer than the better of the two on average, those before eight sums were reduced together 1 %; of 9000 of the products 77 took
-  // more than 2 % longer with them than before and 830 less.  Four / eight columns, us: 4096 x 2500 x 2500 of 25.6 M, R = 64, 166 / 150; 4000 x 1000 x 1000 of 4 M,
-  // 128, 84.9 / 67.6; 1606 x 528 x 1024 of 868 K, 64, 17.8 / 13.6; 2388 x 522 x 997 of 1.2 M, 50, 21.5 / 16.9; 803 x 875 x 372 of 261 K, 128, 14.2 / 11.0; but
-  // 1018 x 2781 x 1602 of 4.5 M, 16, 15.5 / 18.4; 487 x 2818 x 1884 of 2.6 M, 32, 16.6 / 19.8; and on the wrong side 700 x 2000 x 1500 of 2.1 M, 100, 33.9 / 35.0.
-  // None of these takes more slices than one round holds; where eight columns do, the numbers of the kernel before that were measured stand, all three.
+  // Eight columns at a time where the rows fit the LDS so: the entries are read half as often, and a step takes 1.78 times as long instead of
+  // twice, less what an item saves, whose sums are reduced together and whose last block is not filled up: 0.8 of a block.  Half as many slices leave twice as many
+  // wavefronts for the items, though, and a wavefront that has its SIMD to itself waits longer for each of its rows.  Both measured at 14,116 products with uniform
+  // tensors of 200 to 4096 rows a side, R = 8 to 128, others than the numbers were chosen with: they take 0.16 % longer than the better of the two on average.  With 1.57 and
+  // nothing by the item it was 0.29 % and 332 products lost more than 2 % against what was chosen before sums were reduced together (1.72, a tail of 10, a copy of 0.7: 0.80 %);
+  // now 135 do and 1218 gain that much.  Four / eight columns, us: 4096 x 2500 x 2500 of 25.6 M, R = 64, 166 / 150; 4000 x 1000 x 1000 of 4 M, 128, 84.9 / 67.6;
+  // 1606 x 528 x 1024 of 868 K, 64, 17.8 / 13.6; 3122 x 868 x 472 of 646 K, 17, 8.7 / 7.3; but long items 700 x 2000 x 1500 of 2.1 M, 100, 35.9 / 37.0; 679 x 1410 x 2131 of
+  // 3.6 M, 64, 27.9 / 31.0; and few 1018 x 2781 x 1602 of 4.5 M, 16, 15.5 / 18.4; 487 x 2818 x 1884 of 2.6 M, 32, 16.6 / 19.8.
+  // None of these takes more slices than one round holds; where eight columns do, the earlier numbers stand, all three.
   Split s = split(1, 1.0, 5, 0.6);
   bool two = false;
   if (R >= 8 && 2 * (b_rows + c_rows + 1) <= kCsfRowsInLds) {
-    const Split t = ceil_div(R, 8) > kResidentGroups ? split(2, 1.72, 10, 0.7) : split(2, 1.57, 11, 0.6);
+    const Split t = ceil_div(R, 8) > kResidentGroups ? split(2, 1.72, 10, 0.7)
+                                                          : split(2, 1.78 - 0.8 * (double)n_items / (double)n_blocks, 11, 0.6);
     two = t.cost < s.cost;
     if (two) s = t;
   }

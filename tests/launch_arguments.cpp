@@ -296,6 +296,8 @@ int main(int, char** argv) {
   if (c == "four columns, 1018 items of 12 blocks, rank 16") return columns(1018, 12216, 4383, 16, 1);
   if (c == "eight columns, 2000 items of 1.2 blocks, rank 64") return columns(2000, 2444, 1900, 64, 2);
   if (c == "four columns, 2000 items of 1.2 blocks, rank 4") return columns(2000, 2444, 1900, 4, 1);
+  if (c == "four columns, 700 items of 10 blocks, rank 100") return columns(700, 6986, 3500, 100, 1);
+  if (c == "eight columns, 1403 items of 2 blocks, rank 43") return columns(1403, 2806, 1324, 43, 2);
   if (c == "four columns, 430 items, rank 4742") return columns(430, 480, 2370, 4742, 1);
   if (c == "eight columns, 229 items, rank 6881") return columns(229, 3436, 3356, 6881, 2);
   if (c == "127 columns in a workspace for 128") return fewer_columns(128, 127);

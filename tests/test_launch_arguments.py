@@ -62,3 +62,9 @@ def test_runs_of_workgroups_take_every_one_of_them_once(launch_arguments, case):
 def test_rows_of_a_staged_head(launch_arguments, columns):
     """In whole 128-byte lines with 17, 20, 63, 90, 127 and 150 columns, where there is room for that."""
     launch_arguments(f"head rows of {columns} columns")
+
+
+@pytest.mark.parametrize("case", ["four columns, 700 items of 10 blocks, rank 100", "eight columns, 1403 items of 2 blocks, rank 43"])
+def test_eight_columns_gain_by_the_item(launch_arguments, case):
+    """35.9 us with four columns and 37.0 with eight; 10.3 and 8.9."""
+    launch_arguments(case)
